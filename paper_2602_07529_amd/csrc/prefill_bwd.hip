@@ -7,19 +7,19 @@
 //   k_bwd_delta   delta and -lse log2(e) per (token, query head)
 //   k_bwd_tokvis, k_bwd_weights, k_bwd_order   small tables: first visibility word per token; weight
 //                 and launch rank of the key-tile pairs (the dK/dV workgroups start heaviest first)
-//   k_bwd_dq2     head dimension 128: one workgroup per (64-row query tile, KV head, four of its
-//                 query heads), eight waves; the K / V tiles of the tile's row of the forward's
-//                 FULL-first CSR stream through an LDS ring and every tile is a fixed sequence of
-//                 48 slots (described at the kernel).  The heads that the groups of four leave
-//                 over (G not a multiple of four) run as k_bwd_dq2<true>: one head on four
-//                 consecutive query tiles per workgroup, with tile lists from k_bwd_wide_rows
-//   k_bwd_dkv2    head dimension 128: one workgroup per (pair of 64-key tiles, KV head), four
-//                 waves; the Q / dO tiles of the query tiles that see the pair stream through an LDS
-//                 ring, one (tile, query head) = 64 slots (described at the kernel); nothing is
-//                 accumulated through atomics, so the results do not depend on the order of execution
-//   k_bwd_dq, k_bwd_dkv   the first versions (tiles staged through registers, compiler-scheduled):
-//                 head dimension 64, and inside the two kernels above the "general walk" over
-//                 masked tiles of sequences with more than one visibility word per node
+//   k_bwd_dq2     one workgroup per (64-row query tile, KV head, four of its query heads), eight
+//                 waves; the K / V tiles of the tile's row of the forward's FULL-first CSR stream
+//                 through an LDS ring and every tile is a fixed sequence of 48 slots (described at
+//                 the kernel).  The heads that the groups of four leave over (G not a multiple of
+//                 four) run as k_bwd_dq2<true>: one head on four consecutive query tiles per
+//                 workgroup, with tile lists from k_bwd_wide_rows
+//   k_bwd_dkv2    one workgroup per (pair of 64-key tiles, KV head), four waves; the Q / dO tiles of
+//                 the query tiles that see the pair stream through an LDS ring, one (tile, query
+//                 head) = 64 slots (described at the kernel); nothing is accumulated through
+//                 atomics, so the results do not depend on the order of execution
+//   k_bwd64_dq, k_bwd64_dkv   the same two for head dimension 64
+//   k_bwd_dq, k_bwd_dkv   the first versions (tiles staged through registers, compiler-scheduled),
+//                 reached by a development switch only
 // Register layout of a 32x32 MFMA result C = A B:  lane (L, H) = (lane % 32, lane / 32) holds
 // column L and the 16 rows rho_H(e) = 8 (e / 4) + 4 H + e % 4.  A result is used again as the B
 // operand of the next product (contraction over its rows) straight from the registers; the A
@@ -59,15 +59,14 @@ struct BwdArgs {
   int n_seqs, W, hq, hkv, G;
   long total_rows;  // T * hq
   float scale, sc;  // sc = scale * log2(e)
-  // dQ: heads 0 .. dq_narrow - 1 of a KV head run four at a time on one query tile, the others one
-  // at a time on four query tiles (k_bwd_dq2<true>), whose tile lists k_bwd_wide_rows writes: the
-  // list of the tiles 4 c .. 4 c + 3 of a sequence lies where row 4 c of its dense block map does
+  // dQ: heads 0 .. dq_narrow - 1 of a KV head run NQ = four (head dimension 64: two) at a time on one
+  // query tile, the others one at a time on NQ query tiles, whose tile lists k_bwd_wide_rows writes:
+  // the list of the tiles NQ c .. of a sequence lies where row NQ c of its dense block map does
   int dq_narrow;
   int total_qtiles;
-  int32_t* wide_col;    // [dense map] key tiles that one of the four query tiles sees, those that all four see in full first
-  uint8_t* wide_flag;   // [dense map] block-map entries of the four query tiles, two bits each
-  int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every fourth tile)
-  int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups of four, sequence after sequence; last element: their number
+  int32_t* wide_col;    // [dense map] key tiles that one of the query tiles sees, those that all of them see in full first
+  int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every NQ-th tile)
+  int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups, sequence after sequence; last element: their number
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -173,21 +172,24 @@ __device__ __forceinline__ void dq_store(const BwdArgs& a, const DqLane<D>& me, 
 // inline-assembly LDS read that waits for itself: the loads of k_bwd_dq2's ring write LDS too, and
 // a compiler-visible LDS read might be made to wait for all of them.
 constexpr int MAX_ROW_LDS = DAG_BWD_LDS_TILES;
+template <int CAP>
 struct TileList {
   const int32_t* col;   // the row in global memory
-  const uint8_t* flag;
+  const uint8_t* flag;  // (first kernel only)
   uint32_t lds_col, lds_flag;  // LDS byte addresses of the copies
   template <int NT>
-  __device__ __forceinline__ void fill(int32_t* sCol, uint8_t* sFlg, int n) {
-    for (int x = threadIdx.x; x < min(n, MAX_ROW_LDS); x += NT) {
-      sCol[x] = col[x];
-      sFlg[x] = flag[x];
-    }
+  __device__ __forceinline__ void fill(int32_t* sCol, int n) {
+    for (int x = threadIdx.x; x < min(n, CAP); x += NT) sCol[x] = col[x];
     lds_col = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)sCol;
+  }
+  template <int NT>
+  __device__ __forceinline__ void fill(int32_t* sCol, uint8_t* sFlg, int n) {
+    fill<NT>(sCol, n);
+    for (int x = threadIdx.x; x < min(n, CAP); x += NT) sFlg[x] = flag[x];
     lds_flag = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)sFlg;
   }
   __device__ __forceinline__ int tile(int n) const {
-    if (n < MAX_ROW_LDS) {
+    if (n < CAP) {
       uint32_t v;
       asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_col + 4u * (uint32_t)n) : "memory");
       return __builtin_amdgcn_readfirstlane((int)v);
@@ -195,7 +197,7 @@ struct TileList {
     return __builtin_amdgcn_readfirstlane(col[n]);
   }
   __device__ __forceinline__ int flag_of(int n) const {
-    if (n < MAX_ROW_LDS) {
+    if (n < CAP) {
       uint32_t v;
       asm volatile("ds_read_u8 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_flag + (uint32_t)n) : "memory");
       return __builtin_amdgcn_readfirstlane((int)v);
@@ -208,11 +210,9 @@ struct TileList {
 // the tile's K and V rows go through LDS (row-major, padded) for all the waves; the next tile is
 // fetched into registers while the current one is multiplied (constant per-thread offsets, rows
 // past the end re-read the last row and are zeroed on the way to LDS, no load depends on another).
-// (fshift >= 0: a list entry's flag holds the block-map entries of four query tiles, this wave's at
-// that bit; a wave whose query tile does not see the key tile only helps to stage it)
-template <int D, int NT>
-__device__ __forceinline__ void dq_general_walk(const BwdArgs& a, unsigned char* smem, const TileList& tl, int n0, int n1, int T,
-                                                int cu, int hk, int nbase, const DqLane<D>& me, f32x16* dQ, int fshift = -1) {
+template <int D, int NT, typename List>
+__device__ __forceinline__ void dq_general_walk(const BwdArgs& a, unsigned char* smem, const List& tl, int n0, int n1, int T,
+                                                int cu, int hk, int nbase, const DqLane<D>& me, f32x16* dQ) {
   constexpr int LD = D + 8;  // padded rows: the 16-byte operand reads of 32 consecutive rows spread over the banks
   uint16_t* const sK = (uint16_t*)smem;   // [BN][LD]
   uint16_t* const sV = sK + BN * LD;      // [BN][LD]
@@ -260,8 +260,7 @@ __device__ __forceinline__ void dq_general_walk(const BwdArgs& a, unsigned char*
   fetch(kt_next);
   for (int n = n0; n < n1; ++n) {
     const int kt = kt_next;
-    int flag = tl.flag_of(n);
-    if (fshift >= 0) flag = (flag >> fshift) & 3;
+    const int flag = tl.flag_of(n);
     const int j0 = kt * BN;
     __syncthreads();  // everybody is done with the tile in LDS
     commit(kt);
@@ -270,7 +269,6 @@ __device__ __forceinline__ void dq_general_walk(const BwdArgs& a, unsigned char*
       kt_next = tl.tile(n + 1);
       fetch(kt_next);  // in flight during the products below
     }
-    if (flag == 0) continue;
     const bool need_mask = flag == 1;
 #pragma unroll 1
     for (int hh = 0; hh < 2; ++hh) {
@@ -358,10 +356,10 @@ __global__ void __launch_bounds__(128 * HG) k_bwd_dq(BwdArgs a) {
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) dQ[db][e] = 0.f;
-  TileList tl;
+  TileList<MAX_ROW_LDS> tl;
   tl.col = a.qtile_col + t.c0;
   tl.flag = a.qtile_flag + t.c0;
-  tl.fill<NT>(sCol, sFlg, t.N);
+  tl.template fill<NT>(sCol, sFlg, t.N);
   __syncthreads();
   dq_general_walk<D, NT>(a, smem, tl, 0, t.N, t.T, t.cu, hk, t.nbase, me, dQ);
   dq_store<D>(a, me, (threadIdx.x & 63) >> 5, dQ);
@@ -600,7 +598,7 @@ __device__ __forceinline__ void dkv_store(const BwdArgs& a, size_t koff, bool ke
     }
 }
 
-// First dK/dV kernel (every head dimension; the only one for 64): the general walk over all tiles.
+// First dK/dV kernel (every head dimension): the general walk over all tiles.
 template <int D>
 __global__ void __launch_bounds__(256) k_bwd_dkv(BwdArgs a) {
   constexpr int DB = D / 32;
@@ -680,65 +678,112 @@ __global__ void __launch_bounds__(256) k_bwd_dkv(BwdArgs a) {
 //     so no copy of a register that is still being written can be made
 //     (tests/test_asm_lds_reads.py checks the generated code for exactly that);
 //   * two such loops run one after the other: the iterations whose pairs are all visible (both key
-//     tiles FULL, nothing past the end of the sequence), then, when a node has one visibility
-//     word, the masked and ragged ones: Eq. 3 of a (query tile, key) pair is one 64-bit word per
-//     lane, built once per query tile from the runs of equal node ids among its rows
-//     (tile_visibility) and applied with two instructions per element; the ancestor test uses the
-//     key's column of the visibility matrix, built once per workgroup.  Both loops find their
-//     tiles through a bitmap per kind of the pair's block-map column.
-//     With more words per node the masked iterations take the general walk of k_bwd_dkv.
+//     tiles FULL, nothing past the end of the sequence), then the masked and ragged ones: Eq. 3 of
+//     a (query tile, key) pair is one 64-bit word per lane, built once per query tile from the runs
+//     of equal node ids among its rows (tile_visibility) and applied with two instructions per
+//     element; the ancestor test uses the key's column of the visibility matrix, built once per
+//     workgroup.  Both loops find their tiles through a bitmap per kind of the pair's block-map
+//     column.
 // Every iteration passes the barrier once and issues LPS loads per wave (past the end of the walk:
 // loads of the sequence's first tile, never consumed), so the vmcnt waits are constants.
 // With one wave per SIMD (the accumulators and the K / V operands of 32 keys need 192 registers)
 // nothing of a wave overlaps its own MFMAs: an iteration costs the 64 MFMAs plus the time to
 // issue everything else.
-namespace dkv2 {
-constexpr int NST = 4;              // ring depth
-constexpr int LPS = 9;              // wave-level loads per stage and wave: 4 Q blocks, 4 dO blocks, 1 of row data
-constexpr int PF = 5;               // operands in flight ahead of their MFMA
-constexpr int BLK = 1024 + 16;
-constexpr int TILEB = 16 * BLK;     // 64 rows x 128 dims
-constexpr int RD = 2 * TILEB;       // row data: -lse log2(e) [64], delta [64], node id [64]
-constexpr int STAGEB = RD + 768;
-constexpr int NSLOT = 64;
-constexpr int VAHEAD = 8;           // the row data of four rows are read this many slots before their first use
-constexpr int XR = 2;               // row-data reads per group of four rows: -lse and delta
-constexpr int opnd_reads(int o) { return o < 32 ? 1 : 2; }
-// The scores of rows 4 x .. 4 x + 3 of half h are taken in slots 16 + 16 h + 4 x ..; the XR reads of their
-// row data go out VAHEAD slots earlier, i.e. before the operand read that slot waits for, so they have
-// arrived with it.
-constexpr int extra_reads(int slot) { return slot >= 16 - VAHEAD && slot < 48 - VAHEAD && slot % 4 == 0 ? XR : 0; }
-constexpr int issued_through(int k) {  // LDS reads issued up to and including those of operand k
-  int t = 0;
-  for (int o = 0; o <= k; ++o) t += (o >= PF ? extra_reads(o - PF) : 0) + opnd_reads(o);
-  return t;
-}
-constexpr int wait_at(int i) {  // reads that may still be pending when MFMA i starts
-  const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
-  const int n = issued_through(last) - issued_through(i);
-  return n < 15 ? n : 15;
-}
-// byte offset (after the per-lane part) of operand i of the fast iteration
-constexpr int row_imm(int i) {  // i < 32: row operand of half i / 16, k-step (i % 16) / 2, of Q (even) or dO (odd)
-  return (i & 1) * TILEB + 8 * (i / 16) * BLK + (((i % 16) / 2) / 2) * 256 + (((i % 16) / 2) % 2) * 32;
-}
-constexpr int tr_imm(int i) {  // i >= 32: transposed operand (dims 32 db .., 16 rows) of dO (even) or Q (odd)
-  const int j = i - 32, h = j / 16, jj = j % 16, db = jj / 4, hh = (jj / 2) % 2;
-  return ((jj & 1) ? 0 : TILEB) + (8 * h + 4 * hh) * BLK + db * 256;
-}
-}  // namespace dkv2
+// Head dimension 64 (k_bwd64_dkv) runs the same code with half the slots: 16 score MFMAs, then 16 of
+// dV / dK, two scores per slot.  Accumulators and operands take 96 instead of 192 registers and a ring
+// of four stages 71 instead of 137 KB, so two workgroups share a compute unit and each SIMD has two
+// waves: the exponentials of one run beside the MFMAs of the other.  A 1 KiB block then holds 8
+// rows of 128 bytes, 16-byte chunk c of row r at position 8 r + (c ^ swz64(r)), blocks 1024 + 64 bytes
+// apart: eight lanes fetch one row, and both kinds of operand read fall into different banks.
+// Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 query / 8 KV heads: 2000 us with k_bwd_dkv, 517 so.
+__host__ __device__ constexpr int swz64(int r) { return ((r >> 1) & 1) * 2 + ((r >> 2) & 1); }
+// What the ring's tiles look like, for both pipelined kernels: 64 rows of D elements in blocks of 1 KiB.
+template <int D>
+struct RingTile {
+  static constexpr int RPB = 512 / D;                 // rows per block
+  static constexpr int NBLK = 64 / RPB;               // blocks per tile
+  static constexpr int BLK = 1024 + (D == 128 ? 16 : 64);
+  static constexpr int TILEB = NBLK * BLK;
+  // what lane `lane` of a wave-level load fetches: row of the block, element offset inside the row
+  __device__ static int src_row(int lane) { return D == 128 ? (lane >> 2) & 3 : lane >> 3; }
+  __device__ static uint32_t src_col(int lane) {
+    return D == 128 ? (uint32_t)(4 * (lane >> 4) + (lane & 3)) * 8 : (uint32_t)((lane & 7) ^ swz64(lane >> 3)) * 8;
+  }
+  // per-lane part of the address of a row operand (row L of 32, chunk 2 s + H): for even and for odd
+  // k-steps s (one register for both where the chunks lie in order)
+  __device__ static uint32_t row_lane(int L, int H, int odd) {
+    return D == 128 ? (uint32_t)((L >> 2) * BLK + (L & 3) * 64 + H * 16 + odd * 32)
+                    : (uint32_t)((L >> 3) * BLK + (L & 7) * 128 + ((2 * odd + H) ^ swz64(L & 7)) * 16);
+  }
+  static constexpr int row_imm(int half, int s) {  // ... and the rest, after that part for k-step s
+    return D == 128 ? 8 * half * BLK + (s / 2) * 256 : 4 * half * BLK + (s / 2) * 64;
+  }
+  // per-lane part of the address of a transposing read (rows 4 H + .., 32 columns), and the rest: 16-row
+  // group x of the tile, rows + 8 when `second`, columns 32 db ..
+  __device__ static uint32_t tr_lane(int lane) {
+    const int H = lane >> 5, g1 = (lane >> 4) & 1, p = lane & 15;
+    return D == 128 ? (uint32_t)(H * BLK + (p >> 2) * 64 + g1 * 32 + (p & 3) * 8)
+                    : (uint32_t)((4 * H + (p >> 2)) * 128 + ((2 * g1 + ((p >> 1) & 1)) ^ swz64(4 * H + (p >> 2))) * 16 + (p & 1) * 8);
+  }
+  static constexpr int tr_imm(int x, int second, int db) {
+    return D == 128 ? (4 * x + 2 * second) * BLK + db * 256 : (2 * x + second) * BLK + db * 64;
+  }
+};
+template <int D>
+struct Dkv {
+  using R = RingTile<D>;
+  static constexpr int NST = 4;                    // ring depth
+  static constexpr int NPB = R::NBLK / 4;          // blocks of a tile that one wave fetches
+  static constexpr int LPS = 2 * NPB + 1;          // wave-level loads per stage and wave: Q blocks, dO blocks, 1 of row data
+  static constexpr int PF = D == 128 ? 5 : 3;      // operands in flight ahead of their MFMA
+  static constexpr int TILEB = R::TILEB;
+  static constexpr int RD = 2 * TILEB;             // row data: -lse log2(e) [64], delta [64], node id [64]
+  static constexpr int STAGEB = RD + 768;
+  static constexpr int HS = D / 8;                 // slots of the score MFMAs of one 32-row half
+  static constexpr int NSC = 2 * HS, NSLOT = 4 * HS;
+  static constexpr int EPS = 16 / HS;              // scores turned into P and dS per slot (slots HS .. 3 HS - 1)
+  static constexpr int VAHEAD = D == 128 ? 8 : 3;  // the row data of four rows are read this many slots before their first use
+  static constexpr int XR = 2;                     // row-data reads per group of four rows: -lse and delta
+  static constexpr int opnd_reads(int o) { return o < NSC ? 1 : 2; }
+  // The scores of rows 4 x .. 4 x + 3 of half h are taken from slot HS (1 + h) + 4 x / EPS on; the XR reads
+  // of their row data go out VAHEAD >= PF slots earlier, i.e. before the operand read that slot waits
+  // for, so they have arrived with it.
+  static constexpr int extra_reads(int slot) {
+    return slot >= HS - VAHEAD && slot < 3 * HS - VAHEAD && (slot - (HS - VAHEAD)) % (4 / EPS) == 0 ? XR : 0;
+  }
+  static constexpr int issued_through(int k) {  // LDS reads issued up to and including those of operand k
+    int t = 0;
+    for (int o = 0; o <= k; ++o) t += (o >= PF ? extra_reads(o - PF) : 0) + opnd_reads(o);
+    return t;
+  }
+  static constexpr int wait_at(int i) {  // reads that may still be pending when MFMA i starts
+    const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
+    const int n = issued_through(last) - issued_through(i);
+    return n < 15 ? n : 15;
+  }
+  // byte offset (after the per-lane part) of operand i
+  static constexpr int row_imm(int i) {  // i < NSC: row operand of half i / HS, k-step (i % HS) / 2, of Q (even) or dO (odd)
+    return (i & 1) * TILEB + R::row_imm(i / HS, (i % HS) / 2);
+  }
+  static constexpr int tr_imm(int i, int second) {  // i >= NSC: transposed operand (dims 32 db .., 16 rows) of dO (even) or Q (odd)
+    const int j = i - NSC, h = j / HS, jj = j % HS, db = jj / 4, hh = (jj / 2) % 2;
+    return ((jj & 1) ? 0 : TILEB) + R::tr_imm(2 * h + hh, second, db);
+  }
+};
 
-// Eq. 3 for one 64 x 64 tile as a 64-bit word per lane (one visibility word per node): bit c says
+
+// Eq. 3 for one 64 x 64 tile as a 64-bit word per lane: bit c says
 // whether element c of the tile -- query row c for a lane that holds a key, key c for a lane that
 // holds a query row -- and the lane's own token see each other.  The tokens of a sequence lie node
 // after node, so the tile's 64 elements are a few runs of one node each: the runs are found with
 // one ballot over the node ids (LDS, `ids`: byte address of the 64 ids) and every run is switched
 // on as a whole -- for the lane's own node the elements that pass the causal test (`own`), for
-// another node n all or nothing by bit n of `word` (the lane's row or column of the visibility
-// matrix).  Elements from n_in on lie behind the end of the sequence.  Called where no operand read
+// another node n all or nothing by bit n % 64 of `word_of(n)` (word n / 64 of the lane's row or column
+// of the visibility matrix).  Elements from n_in on lie behind the end of the sequence.  Called where no operand read
 // is in flight (the LDS reads here wait for themselves; the loop branches on wave-uniform values).
-__device__ __forceinline__ uint64_t tile_visibility(uint32_t ids, int lane, uint32_t my_node, uint64_t word, uint64_t own,
-                                                    int n_in) {
+template <typename WordOf>
+__device__ __forceinline__ uint64_t tile_visibility(uint32_t ids, int lane, uint32_t my_node, uint64_t own, int n_in,
+                                                    WordOf&& word_of) {
   uint32_t n_here, n_before;
   asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)"
                : "=&v"(n_here), "=&v"(n_before)
@@ -752,7 +797,7 @@ __device__ __forceinline__ uint64_t tile_visibility(uint32_t ids, int lane, uint
     const int s1 = starts != 0 ? __builtin_ctzll(starts) : 64;
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)n_here, s0);
     const uint64_t run = (s1 == 64 ? ~0ull : (1ull << s1) - 1) & ~((1ull << s0) - 1);
-    const uint64_t sel = n == my_node ? own : 0ull - ((word >> (n & 63u)) & 1ull);
+    const uint64_t sel = n == my_node ? own : 0ull - ((word_of(n) >> (n & 63u)) & 1ull);
     m |= run & sel;
   }
   return n_in >= 64 ? m : m & ((1ull << n_in) - 1);
@@ -808,9 +853,12 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-__global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
-  using namespace dkv2;
-  constexpr int D = 128, DB = D / 32;
+template <int D>
+__device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
+  using C = Dkv<D>;
+  using R = RingTile<D>;
+  constexpr int DB = D / 32, NST = C::NST, LPS = C::LPS, NPB = C::NPB, PF = C::PF, TILEB = C::TILEB, RD = C::RD;
+  constexpr int STAGEB = C::STAGEB, HS = C::HS, NSC = C::NSC, NSLOT = C::NSLOT, EPS = C::EPS;
   typedef __attribute__((address_space(3))) void* lds_ptr_t;
   typedef __attribute__((address_space(1))) const void* gbl_ptr_t;
   typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -818,7 +866,7 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int KIND_WORDS = (MAX_QT_LDS + 63) / 64;
   __shared__ uint8_t sFlag[MAX_QT_LDS];  // block-map column of the pair: flag of tile 0 | flag of tile 1 << 2
-  __shared__ uint64_t sKind[3][KIND_WORDS];
+  __shared__ uint64_t sKind[2][KIND_WORDS];
   const int hk = blockIdx.x % a.hkv, kt = a.kt_order[blockIdx.x / a.hkv];  // heaviest pairs first
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int ktl = kt - a.ktile_start[b];
@@ -840,19 +888,36 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
     vf[s] = *(const bf16x8*)(a.v + koff + 16 * s + 8 * H);
   }
   const int nj = a.tok_node[cu + jc];
-  // (one visibility word per node) the nodes that see this lane's key: bit ni of `seen_by` = bit nj
-  // of node ni's word, i.e. the key's column of the sequence's visibility matrix
-  uint64_t seen_by = 0;
-  if (a.W == 1) {
+  // the nodes that see this lane's key: bit ni % 64 of seen_by[ni / 64] = bit nj of node ni's words,
+  // i.e. the key's column of the sequence's visibility matrix (the first 128 nodes of it; sequences
+  // with more take every word they need from memory)
+  uint64_t seen_by[2] = {0, 0};
+  if (a.W <= 2) {
     const int n_nodes = a.node_start[b + 1] - nbase;
-    const uint64_t word = lane < n_nodes ? a.node_vis[nbase + lane] : 0;
+    uint64_t word[2][2];  // word y of node 64 x + lane
 #pragma unroll
-    for (int ni = 0; ni < 64; ++ni) {
-      const uint64_t wn = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(word >> 32), ni) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)word, ni);
-      seen_by |= ((wn >> (nj & 63)) & 1ull) << ni;
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+        word[x][y] = y < a.W && 64 * x + lane < n_nodes ? a.node_vis[(int64_t)(nbase + 64 * x + lane) * a.W + y] : 0;
+    uint64_t todo = ~0ull;  // the wave's keys belong to a few nodes: one at a time, its bit of 64 nodes per ballot
+    while (todo != 0) {
+      const int n = __builtin_amdgcn_readlane(nj, __builtin_ctzll(todo));
+      todo &= ~__builtin_amdgcn_ballot_w64(nj == n);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const uint64_t column = __builtin_amdgcn_ballot_w64(((n < 64 ? word[x][0] : word[x][1]) >> (n & 63)) & 1ull);
+        if (nj == n) seen_by[x] = column;
+      }
     }
   }
+  auto word_of = [&](uint32_t n) __attribute__((always_inline)) -> uint64_t {  // (n is wave-uniform)
+    if (a.W <= 2) return n < 64 ? seen_by[0] : seen_by[1];
+    // bit n % 64 = the bit of the key's node in node n's words
+    int key_node = nj;
+    asm volatile("" : "+v"(key_node));  // (the rare case keeps no address in registers)
+    return ((a.node_vis[(int64_t)(nbase + (int)n) * a.W + (key_node >> 6)] >> (key_node & 63)) & 1ull) << (n & 63u);
+  };
   f32x16 dK[DB], dV[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -864,10 +929,8 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   auto with_fast_bit = [&](int qt, int f) {
     return f | ((f == (2 | (2 << 2)) && (qt + 1) * BM <= T && (ktl + 2) * BN <= T) ? 16 : 0);
   };
-  // Two pipelined loops: the iterations without tests, then (when a node has one visibility word)
-  // the masked ones; with more words per node the masked ones go to the general walk.
-  const bool masks_in_loop = a.W == 1;
-  auto kind_of = [&](int f) { return (f & 16) ? 0 : ((f & 15) != 0 && masks_in_loop) ? 1 : 2; };  // 2: general walk or nothing
+  // Two pipelined loops: the iterations without tests, then the masked ones.
+  auto kind_of = [&](int f) { return (f & 16) ? 0 : (f & 15) != 0 ? 1 : 2; };  // 2: nothing to do
   // The column is kept in LDS as the flags and as one bitmap per kind of iteration (bit qt % 64 of
   // word qt / 64: tile qt has a visible pair and is of that kind), so that a walk finds its next
   // tile with one 64-bit read per 64 tiles instead of one probe per tile.
@@ -882,9 +945,9 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
         f = with_fast_bit(x, f0 | (f1 << 2));
         sFlag[x] = (uint8_t)f;
       }
-      const int kind = (f & 15) != 0 ? kind_of(f) : 3;
+      const int kind = kind_of(f);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
+      for (int k = 0; k < 2; ++k) {
         const uint64_t word = __builtin_amdgcn_ballot_w64(kind == k);
         if (lane == 0 && x0 + 64 * w < QT) sKind[k][(x0 >> 6) + w] = word;
       }
@@ -913,8 +976,7 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   auto last_of_kind = [&](int kind, int qt) {  // last query tile <= qt of the kind (with a visible pair), -1 if none
     if (!flags_in_lds) {
       for (; qt >= 0; --qt) {
-        const int f = pair_flag(qt);
-        if ((f & 15) != 0 && kind_of(f) == kind) break;
+        if (kind_of(pair_flag(qt)) == kind) break;
       }
       return qt;
     }
@@ -930,8 +992,8 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
 
   // ---- loads of one stage, in LPS pieces per wave (piece p of (tile qt, head g) into stage st)
   const uint32_t row_stride = (uint32_t)(a.hq * D);  // elements
-  const uint32_t chunk8 = (uint32_t)(4 * (lane >> 4) + (lane & 3)) * 8;  // this lane's 16-byte chunk of a row
-  const int rsub = (lane >> 2) & 3;
+  const uint32_t chunk8 = R::src_col(lane);  // this lane's 16-byte chunk of a row
+  const int rsub = R::src_row(lane);
   // Row data, 4 bytes per lane, one load per wave: wave 0 fetches -lse log2(e), wave 1 delta, wave 2
   // the node ids of the rows (for the masked iterations), wave 3 -lse log2(e) once more (every wave
   // issues the same number of loads, so that the vmcnt waits are the same constants for all).
@@ -944,7 +1006,7 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   // destination and issues its load.
   struct IssueCtx {
     const uint16_t *qb, *dob;  // first row of the tile, this head
-    uint32_t voff[4];          // element offset of this lane's chunk in block w + 4 i (rows past the sequence end re-read its last row)
+    uint32_t voff[NPB];        // element offset of this lane's chunk in block w + 4 i (rows past the sequence end re-read its last row)
     const float* rd;           // this lane's row-data word
   };
   auto prepare_issue = [&](int qt, int g) __attribute__((always_inline)) {
@@ -955,16 +1017,16 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
     c.qb = a.q + slab;
     c.dob = a.dout + slab;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) c.voff[i] = (uint32_t)min(4 * (w + 4 * i) + rsub, n_in - 1) * row_stride + chunk8;
+    for (int i = 0; i < NPB; ++i) c.voff[i] = (uint32_t)min(R::RPB * (w + 4 * i) + rsub, n_in - 1) * row_stride + chunk8;
     c.rd = rd_src + ((size_t)(cu + r0 + min(lane, n_in - 1)) * rd_mul + rd_hmul * h);
     return c;
   };
   auto issue_piece = [&](int p, const IssueCtx& c, int st) __attribute__((always_inline)) {
     unsigned char* const sb = smem + st * STAGEB;
-    if (p < 8) {
-      const int blk = w + 4 * (p & 3);
-      __builtin_amdgcn_global_load_lds((gbl_ptr_t)((p < 4 ? c.qb : c.dob) + c.voff[p & 3]),
-                                       (lds_ptr_t)(sb + (p < 4 ? 0 : TILEB) + blk * BLK), 16, 0, 0);
+    if (p < 2 * NPB) {
+      const int blk = w + 4 * (p % NPB);
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)((p < NPB ? c.qb : c.dob) + c.voff[p % NPB]),
+                                       (lds_ptr_t)(sb + (p < NPB ? 0 : TILEB) + blk * R::BLK), 16, 0, 0);
     } else {
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)c.rd, (lds_ptr_t)(sb + RD + rd_dst), 4, 0, 0);
     }
@@ -976,8 +1038,8 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   };
 
   // per-lane parts of the LDS operand addresses
-  const uint32_t roff = (uint32_t)((L >> 2) * BLK + (L & 3) * 64 + H * 16);
-  const uint32_t toff = (uint32_t)(((lane >> 5) & 1) * BLK + ((lane & 15) >> 2) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+  const uint32_t roff[2] = {R::row_lane(L, H, 0), R::row_lane(L, H, 1)};
+  const uint32_t toff = R::tr_lane(lane);
   const uint32_t smem_base = lds_addr(smem);
   const float sc = a.sc;
 
@@ -987,7 +1049,8 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
   auto pipelined_iter = [&](auto msk_c, int cs, const IssueCtx& ictx, int is, uint32_t vis_lo, uint32_t vis_hi) __attribute__((always_inline)) {
     constexpr bool MSK = decltype(msk_c)::value;
     const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB;
-    const uint32_t ra = sbase + roff, ta = sbase + toff, va = sbase + RD + 16 * H;
+    const uint32_t ra[2] = {sbase + roff[0], D == 128 ? sbase + roff[0] + 32 : sbase + roff[1]};
+    const uint32_t ta = sbase + toff, va = sbase + RD + 16 * H;
     bf16x8 op[NSLOT];
     v4i16 lo[NSLOT], hi[NSLOT];
     f32x4 nl[2][4], dl[2][4];
@@ -1005,44 +1068,48 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
     };
     auto fetch = [&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
-      const uint32_t r = ra, t = ta;
+      constexpr int odd = ((i % HS) / 2) & 1;  // (k-step of a row operand)
+      const uint32_t r = D == 128 ? ra[0] : ra[odd], t = ta;
       bf16x8* const opp = op;
       v4i16* const lop = lo;
       v4i16* const hip_ = hi;
-      if constexpr (i < 32)
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(opp[i]) : "v"(r), "n"(row_imm(i)));
+      if constexpr (i < NSC)
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(opp[i]) : "v"(r), "n"(C::row_imm(i) + (D == 128 ? 32 * odd : 0)));
       else if constexpr (i < NSLOT)
         asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
                      : "=&v"(lop[i]), "=&v"(hip_[i])
-                     : "v"(t), "n"(tr_imm(i)), "n"(tr_imm(i) + 2 * BLK));
+                     : "v"(t), "n"(C::tr_imm(i, 0)), "n"(C::tr_imm(i, 1)));
     };
     static_for<0, PF>(fetch);
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
-      if constexpr (i == 32) {
+      if constexpr (i == NSC) {
         sync_mid();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (extra_reads(i) != 0) {
-        constexpr int u = (i + VAHEAD - 16) / 4;  // rows 4 u .. 4 u + 3 of the 64
+      if constexpr (C::extra_reads(i) != 0) {
+        constexpr int u = (i + C::VAHEAD - HS) / (4 / EPS);  // rows 4 u .. 4 u + 3 of the 64
         fetch_val(std::integral_constant<int, u / 4>{}, std::integral_constant<int, u % 4>{});
       }
       fetch(std::integral_constant<int, i + PF>{});
-      wait_lgkmcnt_only<wait_at(i)>();
+      wait_lgkmcnt_only<C::wait_at(i)>();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (i < 32) {
-        constexpr int rb = i / 16, s = (i % 16) / 2;
+      if constexpr (i < NSC) {
+        constexpr int rb = i / HS, s = (i % HS) / 2;
         const bf16x8 b_acc = (i & 1) == 0 ? kf[s] : vf[s];
         f32x16& acc = (i & 1) == 0 ? S[rb] : dP[rb];
-        if constexpr (s == 0)
+        if constexpr (D != 128) {
+          const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          acc = mfma32(op[i], b_acc, s == 0 ? zero : acc);
+        } else if constexpr (s == 0)
           acc = mfma32_first_v(op[i], b_acc);
         else if constexpr (s < D / 16 - 1)
           acc = mfma32_next_v(op[i], b_acc, acc);
         else
           acc = mfma32_last_v(op[i], b_acc, acc);
       } else {
-        constexpr int jx = i - 32, h = jx / 16, jj = jx % 16, db = jj / 4, hh = (jj / 2) % 2;
+        constexpr int jx = i - NSC, h = jx / HS, jj = jx % HS, db = jj / 4, hh = (jj / 2) % 2;
         const v8i16 x = {lo[i][0], lo[i][1], lo[i][2], lo[i][3], hi[i][0], hi[i][1], hi[i][2], hi[i][3]};
         const bf16x8 opx = __builtin_bit_cast(bf16x8, x);
         if constexpr ((jj & 1) == 0)
@@ -1050,9 +1117,9 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
         else
           dK[db] = mfma32(opx, dss[h][hh], dK[db]);
       }
-      if constexpr (i >= 32 && i < 32 + LPS) issue_piece(i - 32, ictx, is);
-      if constexpr (i >= 16 && i < 48) {  // one score of half 0 (slots 16..31) or half 1 (slots 32..47)
-        constexpr int h = (i - 16) / 16, e = (i - 16) % 16;
+      if constexpr (i >= NSC && i < NSC + LPS) issue_piece(i - NSC, ictx, is);
+      if constexpr (i >= HS && i < 3 * HS) static_for<EPS * (i - HS), EPS * (i - HS) + EPS>([&](auto nc) __attribute__((always_inline)) {  // scores of half 0, then of half 1
+        constexpr int h = decltype(nc)::value / 16, e = decltype(nc)::value % 16;
         float pe = __builtin_amdgcn_exp2f(fmaf(S[h][e], sc, nl[h][e >> 2][e & 3]));
         if constexpr (MSK) pe = keep_if_bit<8 * (e >> 2) + (e & 3)>(pe, h == 0 ? vis_lo : vis_hi);  // Eq. 3 and the end of the sequence
         pt[h][e] = pe;
@@ -1066,7 +1133,7 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
           dss[h][e >> 3][(e & 7) - 1] = db2[0];
           dss[h][e >> 3][e & 7] = db2[1];
         }
-      }
+      });
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -1108,14 +1175,15 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
           // the rows of tile cq that this lane's key is visible to: own node from the key's row on
           const int first = j - cq * BM;  // first such row of the tile (may lie before or behind it)
           const uint64_t own = first <= 0 ? ~0ull : first >= 64 ? 0ull : ~0ull << first;
-          vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + RD + 512, lane, (uint32_t)nj, seen_by, own, T - cq * BM);
+          vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + RD + 512, lane, (uint32_t)nj, own, T - cq * BM, word_of);
           vis = key_ok ? vis >> (4 * H) : 0ull;  // bit 32 h + 8 (e / 4) + e % 4: element e of half h
         }
       }
 #pragma unroll 1
       for (int g = 0; g < a.G; ++g) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db) asm volatile("" : "+a"(dK[db]), "+a"(dV[db]));
+        for (int db = 0; db < DB; ++db)
+          if constexpr (D == 128) asm volatile("" : "+a"(dK[db]), "+a"(dV[db]));
         const IssueCtx ic = prepare_issue(iq, ig);
         if (KIND == 0 || active) {
           pipelined_iter(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
@@ -1135,56 +1203,54 @@ __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) {
     asm volatile("" ::: "memory");
   };
   ring_loop(std::false_type{});
-  if (masks_in_loop) ring_loop(std::true_type{});
-  __syncthreads();  // the ring is free: the general walk lays its own tiles over it
-  // ---- everything else: the general walk over the tiles the loop above left out
-  auto rest_flag = [&](int qt) {
-    const int f = pair_flag(qt);
-    return kind_of(f) == 2 ? (f & 15) : 0;
-  };
-  if (last_of_kind(2, QT - 1) >= 0)  // (the same for every thread)
-    dkv_general_walk<D>(a, smem, rest_flag, QT, T, cu, hk, nbase, my_kt, nj, j, key_ok, kf, vf, dK, dV);
-  dkv_store<D>(a, koff, key_ok, H, dK, dV);
+  ring_loop(std::true_type{});
+  int key = 32 * w + L;
+  asm volatile("" : "+v"(key));  // (recomputed here: its offsets need no registers across the loops)
+  const int j_out = ktl * BN + key;
+  dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < T, H, dK, dV);
 }
+__global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) { dkv_ring_body<128>(a); }
+__global__ void __launch_bounds__(256, 2) k_bwd64_dkv(BwdArgs a) { dkv_ring_body<64>(a); }
 
-// Tile lists of the dQ workgroups that take one query head on four query tiles (the heads that do
-// not fill a group of four): one wave per query tile of the batch, those of every fourth tile of a
-// sequence work.  The list of tiles 4 c .. 4 c + 3 holds every key tile that one of them sees, with
-// the four block-map entries as its flag; the key tiles that all four see in full, with all their
-// rows and keys inside the sequence, come first (they run without tests), both parts ascending.
+// Tile lists of the dQ workgroups that take one query head on a group of NQ = four (head dimension
+// 128) or two query tiles (the heads that do not fill a workgroup on one tile): one wave per query
+// tile of the batch, those of every NQ-th tile of a sequence work.  The list of tiles NQ c ..
+// NQ c + NQ - 1 holds every key tile that one of them sees; the key tiles that all of them see in full, with all their rows and keys inside the sequence, come
+// first (they run without tests), both parts ascending.
+template <int NQ>
 __global__ void __launch_bounds__(64) k_bwd_wide_rows(BwdArgs a) {
   const int x = blockIdx.x, lane = threadIdx.x;
   const int b = dag_find_segment(a.qtile_start, a.n_seqs, x);
   const int qt = x - a.qtile_start[b];
-  if (qt & 3) return;
+  if (qt % NQ) return;
   const int T = a.cu_seqlens[b + 1] - a.cu_seqlens[b];
   const int QT = (T + BM - 1) / BM, KT = (T + BN - 1) / BN;
   const uint8_t* bm = a.block_map + a.block_map_off[b];
   const int64_t base = a.block_map_off[b] + (int64_t)qt * KT;
-  const bool rows_in = (qt + 4) * BM <= T;
+  const bool rows_in = (qt + NQ) * BM <= T;
+  constexpr int ALL_FULL = 0xAA >> (8 - 2 * NQ);
   auto entries = [&](int kt) {
     int f8 = 0;
     if (kt < KT)
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < NQ; ++i)
         if (qt + i < QT) f8 |= (int)bm[(int64_t)(qt + i) * KT + kt] << (2 * i);
     return f8;
   };
   int n = 0, nfast = 0;
   for (int k0 = 0; k0 < KT; k0 += 64) {
     const int kt = k0 + lane, f8 = entries(kt);
-    nfast += __builtin_popcountll(__builtin_amdgcn_ballot_w64(rows_in && f8 == 0xAA && (kt + 1) * BN <= T));
+    nfast += __builtin_popcountll(__builtin_amdgcn_ballot_w64(rows_in && f8 == ALL_FULL && (kt + 1) * BN <= T));
     n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(f8 != 0));
   }
   int at_fast = 0, at_rest = nfast;
   const uint64_t below = (1ull << lane) - 1;
   for (int k0 = 0; k0 < KT; k0 += 64) {
     const int kt = k0 + lane, f8 = entries(kt);
-    const bool fast = rows_in && f8 == 0xAA && (kt + 1) * BN <= T, rest = f8 != 0 && !fast;
+    const bool fast = rows_in && f8 == ALL_FULL && (kt + 1) * BN <= T, rest = f8 != 0 && !fast;
     const uint64_t mf = __builtin_amdgcn_ballot_w64(fast), mr = __builtin_amdgcn_ballot_w64(rest);
     if (fast || rest) {
       const int64_t at = base + (fast ? at_fast + __builtin_popcountll(mf & below) : at_rest + __builtin_popcountll(mr & below));
       a.wide_col[at] = kt;
-      a.wide_flag[at] = (uint8_t)f8;
     }
     at_fast += __builtin_popcountll(mf);
     at_rest += __builtin_popcountll(mr);
@@ -1193,12 +1259,12 @@ __global__ void __launch_bounds__(64) k_bwd_wide_rows(BwdArgs a) {
     a.wide_n[x] = n;
     a.wide_nfast[x] = nfast;
     // the groups of the batch, numbered through (the launch of the dQ workgroups runs over these
-    // numbers: over the query tiles, with three of four workgroups leaving at once, the ones that
-    // stay would all have the same index modulo four and land on two of the eight XCDs)
+    // numbers: over the query tiles, with e.g. three of four workgroups leaving at once, the ones
+    // that stay would all have the same index modulo four and land on two of the eight XCDs)
     int before = 0;
-    for (int bb = 0; bb < b; ++bb) before += (a.qtile_start[bb + 1] - a.qtile_start[bb] + 3) / 4;
-    a.wide_list[before + qt / 4] = x;
-    if (qt == 0 && a.qtile_start[b + 1] == a.total_qtiles) a.wide_list[a.total_qtiles] = before + (QT + 3) / 4;  // (the last sequence with tokens)
+    for (int bb = 0; bb < b; ++bb) before += (a.qtile_start[bb + 1] - a.qtile_start[bb] + NQ - 1) / NQ;
+    a.wide_list[before + qt / NQ] = x;
+    if (qt == 0 && a.qtile_start[b + 1] == a.total_qtiles) a.wide_list[a.total_qtiles] = before + (QT + NQ - 1) / NQ;  // (the last sequence with tokens)
   }
 }
 
@@ -1212,49 +1278,64 @@ __global__ void __launch_bounds__(64) k_bwd_wide_rows(BwdArgs a) {
 // the two 32-key halves (32 MFMAs, 16-byte row reads), then dQ^T += K^T dS^T of the two halves
 // (16 MFMAs, transposing reads), with the exponentials of half 0 under the score MFMAs of half 1
 // and those of half 1 under the dQ MFMAs of half 0.  The masked and ragged tiles follow in a second
-// such loop when a node has one visibility word (Eq. 3 of the tile as one 64-bit word per lane, a
-// lane being a query row here: tile_visibility over the node ids of the tile's keys, which ride
-// the ring as a fifth load), else in the general walk.
-namespace dq2 {
-constexpr int NST = 4, NSLOT = 48;
-constexpr int PF = 4;                // operands in flight ahead of their MFMA
-constexpr int BLK = dkv2::BLK, TILEB = dkv2::TILEB;
-constexpr int ND = 2 * TILEB;        // node ids of the tile's keys [64] (masked tiles)
-constexpr int STAGEB = ND + 256;     // K tile, V tile, node ids
-constexpr int opnd_reads(int o) { return o < 32 ? 1 : 2; }
-constexpr int issued_through(int k) {  // LDS reads issued up to and including those of operand k
-  int t = 0;
-  for (int o = 0; o <= k; ++o) t += opnd_reads(o);
-  return t;
-}
-constexpr int wait_at(int i) {  // reads that may still be pending when MFMA i starts
-  const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
-  const int n = issued_through(last) - issued_through(i);
-  return n < 15 ? n : 15;
-}
-constexpr int row_imm(int i) { return dkv2::row_imm(i); }  // half i / 16, k-step (i % 16) / 2, of K (even) or V (odd)
-constexpr int tr_imm(int i) {  // i >= 32: K^T operand of key half (i - 32) / 8, 16-key group x, dims 32 db ..
-  const int j = i - 32, hh = j / 8, x = (j % 8) / 4, db = j % 4;
-  return (8 * hh + 4 * x) * BLK + db * 256;
-}
-}  // namespace dq2
+// such loop (Eq. 3 of the tile as one 64-bit word per lane, a lane being a query row here:
+// tile_visibility over the node ids of the tile's keys, which ride the ring as one more load).
+// Head dimension 64 (k_bwd64_dq) runs the same code with half the slots and half the waves (two
+// query heads, or one head on two query tiles): its ring takes 71 KB, so two such workgroups share a
+// compute unit, and head groups of two and six need no padding.  (The same DAGs: 813 us with
+// k_bwd_dq, 336 so.)
+template <int D>
+struct Dq {
+  using R = RingTile<D>;
+  static constexpr int NST = 4;
+  static constexpr int NPAIR = D == 128 ? 4 : 2;   // wave pairs = query heads (or query tiles of one head) per workgroup
+  static constexpr int PF = 4;                     // operands in flight ahead of their MFMA
+  static constexpr int TILEB = R::TILEB;
+  static constexpr int NPB = R::NBLK / (2 * NPAIR);  // blocks of a tile that one wave fetches
+  static constexpr int ND = 2 * TILEB;             // node ids of the tile's keys [64] (masked tiles)
+  static constexpr int STAGEB = ND + 256;          // K tile, V tile, node ids
+  static constexpr int HS = D / 8;                 // slots of the score MFMAs of one 32-key half
+  static constexpr int NDQ = D / 16;               // slots of the dQ MFMAs of one half
+  static constexpr int NSC = 2 * HS, NSLOT = NSC + 2 * NDQ;
+  // tiles of the list kept in LDS (two workgroups per compute unit at head dimension 64)
+  static constexpr int LIST = D == 128 || MAX_ROW_LDS < 2048 ? MAX_ROW_LDS : 2048;
+  static constexpr int opnd_reads(int o) { return o < NSC ? 1 : 2; }
+  static constexpr int issued_through(int k) {  // LDS reads issued up to and including those of operand k
+    int t = 0;
+    for (int o = 0; o <= k; ++o) t += opnd_reads(o);
+    return t;
+  }
+  static constexpr int wait_at(int i) {  // reads that may still be pending when MFMA i starts
+    const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
+    const int n = issued_through(last) - issued_through(i);
+    return n < 15 ? n : 15;
+  }
+  static constexpr int row_imm(int i) {  // half i / HS, k-step (i % HS) / 2, of K (even) or V (odd)
+    return (i & 1) * TILEB + R::row_imm(i / HS, (i % HS) / 2);
+  }
+  static constexpr int tr_imm(int i, int second) {  // i >= NSC: K^T operand of key half (i - NSC) / NDQ, 16-key group x, dims 32 db ..
+    const int j = i - NSC, hh = j / NDQ, x = (j % NDQ) / (D / 32), db = j % (D / 32);
+    return R::tr_imm(2 * hh + x, second, db);
+  }
+};
 
-// WIDE: the same workgroup turned by ninety degrees -- one query head on four consecutive query
-// tiles (wave pair p takes tile 4 c + p), for the heads that do not fill a group of four: the
-// waves still share every staged K / V tile.  The tile list is the one k_bwd_wide_rows wrote.
-template <bool WIDE>
-__global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
-  using namespace dq2;
-  constexpr int D = 128, HG = 4, NT = 512;
+// WIDE: the same workgroup turned by ninety degrees -- one query head on four (two) consecutive query
+// tiles (wave pair p takes tile 4 c + p), for the heads that do not fill a group: the waves still
+// share every staged K / V tile.  The tile list is the one k_bwd_wide_rows wrote.
+template <int D, bool WIDE>
+__device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
+  using C = Dq<D>;
+  using R = RingTile<D>;
+  constexpr int NPAIR = C::NPAIR, NT = 128 * NPAIR, NW = 2 * NPAIR, NST = C::NST, PF = C::PF, NPB = C::NPB, TILEB = C::TILEB;
+  constexpr int ND = C::ND, STAGEB = C::STAGEB, HS = C::HS, NDQ = C::NDQ, NSC = C::NSC, NSLOT = C::NSLOT;
   typedef __attribute__((address_space(3))) void* lds_ptr_t;
   typedef __attribute__((address_space(1))) const void* gbl_ptr_t;
   typedef short v4i16 __attribute__((ext_vector_type(4)));
   typedef short v8i16 __attribute__((ext_vector_type(8)));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int32_t sCol[MAX_ROW_LDS];
-  __shared__ uint8_t sFlg[MAX_ROW_LDS];
+  __shared__ int32_t sCol[C::LIST];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, L = lane & 31, H = lane >> 5;
-  const int pair = w >> 1;  // (WIDE) which of the four query tiles
+  const int pair = w >> 1;  // (WIDE) which of the query tiles
   DqTile t;
   int64_t wide_base = 0;
   if constexpr (!WIDE) {
@@ -1272,7 +1353,7 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
   const int hk = blockIdx.y, cu = t.cu, T = t.T;
   DqLane<D> me;
   if constexpr (!WIDE)
-    dq_setup<D, HG>(a, t, hk, me);
+    dq_setup<D, NPAIR>(a, t, hk, me);
   else
     dq_setup_at<D>(a, t, hk, a.dq_narrow + (int)blockIdx.z, true, t.row0 + BM * pair, me);
   f32x16 dQ[D / 32];
@@ -1280,22 +1361,21 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) dQ[db][e] = 0.f;
-  TileList tl;
+  TileList<C::LIST> tl;
   tl.col = WIDE ? a.wide_col + wide_base : a.qtile_col + t.c0;
-  tl.flag = WIDE ? a.wide_flag + wide_base : a.qtile_flag + t.c0;
-  tl.fill<NT>(sCol, sFlg, t.N);
+  tl.template fill<NT>(sCol, t.N);
   __syncthreads();
   const int NF = t.nfast;  // entries 0 .. NF - 1 of the list: every pair visible, inside the sequence
 
-  // ---- loads of one stage: wave w fetches blocks w and w + 8 of the K tile and of the V tile; for
+  // ---- loads of one stage: wave w fetches blocks w and w + NW of the K tile and of the V tile; for
   // masked tiles every wave also fetches the node ids of the keys (the same 256 bytes from all
-  // eight: the number of loads a wave has in flight must not depend on the wave)
+  // of them: the number of loads a wave has in flight must not depend on the wave)
   const uint32_t row_stride = (uint32_t)(a.hkv * D);
-  const uint32_t chunk8 = (uint32_t)(4 * (lane >> 4) + (lane & 3)) * 8;
-  const int rsub = (lane >> 2) & 3;
+  const uint32_t chunk8 = R::src_col(lane);
+  const int rsub = R::src_row(lane);
   struct IssueCtx {
     const uint16_t *kb, *vb;
-    uint32_t voff[2];
+    uint32_t voff[NPB];
     const int32_t* nodes;  // this lane's key of the tile
   };
   auto prepare_issue = [&](int n, int n_end) __attribute__((always_inline)) {
@@ -1306,27 +1386,30 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
     c.kb = a.k + slab;
     c.vb = a.v + slab;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) c.voff[i] = (uint32_t)min(4 * (w + 8 * i) + rsub, n_in - 1) * row_stride + chunk8;
+    for (int i = 0; i < NPB; ++i) c.voff[i] = (uint32_t)min(R::RPB * (w + NW * i) + rsub, n_in - 1) * row_stride + chunk8;
     c.nodes = a.tok_node + cu + j0 + min(lane, n_in - 1);
     return c;
   };
   auto issue_piece = [&](int p, const IssueCtx& c, int st) __attribute__((always_inline)) {
     unsigned char* const sb = smem + st * STAGEB;
-    if (p < 4) {
-      const int blk = w + 8 * (p & 1);
-      __builtin_amdgcn_global_load_lds((gbl_ptr_t)((p < 2 ? c.kb : c.vb) + c.voff[p & 1]),
-                                       (lds_ptr_t)(sb + (p < 2 ? 0 : TILEB) + blk * BLK), 16, 0, 0);
+    if (p < 2 * NPB) {
+      const int blk = w + NW * (p % NPB);
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)((p < NPB ? c.kb : c.vb) + c.voff[p % NPB]),
+                                       (lds_ptr_t)(sb + (p < NPB ? 0 : TILEB) + blk * R::BLK), 16, 0, 0);
     } else {
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)c.nodes, (lds_ptr_t)(sb + ND), 4, 0, 0);
     }
   };
-  const uint32_t roff = (uint32_t)((L >> 2) * BLK + (L & 3) * 64 + H * 16);
-  const uint32_t toff = (uint32_t)(((lane >> 5) & 1) * BLK + ((lane & 15) >> 2) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+  const uint32_t roff[2] = {R::row_lane(L, H, 0), R::row_lane(L, H, 1)};
+  const uint32_t toff = R::tr_lane(lane);
   const uint32_t smem_base = lds_addr(smem);
   const float sc = a.sc, nl = -me.lse2, dl = me.dl;
   const int nq = me.ni, iq_row = me.i;
-  const uint64_t vis0 = me.vis0;
   const bool row_ok = me.row_ok;
+  const uint64_t* const vis_row = a.node_vis + (int64_t)(t.nbase + nq) * a.W;
+  const uint64_t vis0 = me.vis0, vis1 = a.W > 1 ? vis_row[1] : 0;  // (sequences with more than 128 nodes fetch the word they need)
+  asm volatile("" ::"v"(vis0), "v"(vis1));  // (their arrival belongs here, not between the ring's loads)
+  auto word_of = [&](uint32_t n) __attribute__((always_inline)) -> uint64_t { return n < 64 ? vis0 : n < 128 ? vis1 : vis_row[n >> 6]; };  // (n is wave-uniform)
 
   // ---- one key tile, slot by slot; MSK: with Eq. 3 (one visibility word per node) and the end of the
   // sequence applied per element from the lane's visibility word of the tile
@@ -1334,9 +1417,9 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
   // 32 hh + 8 (e / 4) + e % 4 belongs to element e of half hh, i.e. to key 64 kt + 4 H + that number)
   auto pipelined_tile = [&](auto msk_c, int cs, const IssueCtx& ictx, int is, uint32_t vis_lo, uint32_t vis_hi) __attribute__((always_inline)) {
     constexpr bool MSK = decltype(msk_c)::value;
-    constexpr int LPS = MSK ? 5 : 4, PFM = PF;
+    constexpr int LPS = 2 * NPB + (MSK ? 1 : 0), PFM = PF;
     const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB;
-    const uint32_t ra = sbase + roff, ta = sbase + toff;
+    const uint32_t ra[2] = {sbase + roff[0], sbase + roff[1]}, ta = sbase + toff;
     bf16x8 op[NSLOT];
     v4i16 lo[NSLOT], hi[NSLOT];
     f32x16 S[2], dP[2];
@@ -1344,16 +1427,17 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
     bf16x8 bds[2][2];
     auto fetch = [&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
-      const uint32_t r = ra, t = ta;  // (named here: captures inside discarded branches trip the compiler)
+      constexpr int odd = ((i % HS) / 2) & 1;  // (k-step of a row operand)
+      const uint32_t r = D == 128 ? ra[0] : ra[odd], t = ta;  // (named here: captures inside discarded branches trip the compiler)
       bf16x8* const opp = op;
       v4i16* const lop = lo;
       v4i16* const hip_ = hi;
-      if constexpr (i < 32)
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(opp[i]) : "v"(r), "n"(row_imm(i)));
+      if constexpr (i < NSC)
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(opp[i]) : "v"(r), "n"(C::row_imm(i) + (D == 128 ? 32 * odd : 0)));
       else if constexpr (i < NSLOT)
         asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
                      : "=&v"(lop[i]), "=&v"(hip_[i])
-                     : "v"(t), "n"(tr_imm(i)), "n"(tr_imm(i) + 2 * BLK));
+                     : "v"(t), "n"(C::tr_imm(i, 0)), "n"(C::tr_imm(i, 1)));
     };
     auto score = [&](auto hc, auto ec) __attribute__((always_inline)) {  // dS of key e of half h (this lane's row), packed in pairs
       constexpr int h = decltype(hc)::value, e = decltype(ec)::value;
@@ -1371,40 +1455,39 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
-      if constexpr (i == 32) {
+      if constexpr (i == NSC) {
         wait_vmcnt_only<LPS>();        // this wave's loads of the next tile's stage have landed
         __builtin_amdgcn_s_barrier();  // (bare: a __syncthreads would drain the loads in flight)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
       fetch(std::integral_constant<int, i + PFM>{});
-      wait_lgkmcnt_only<wait_at(i)>();
+      wait_lgkmcnt_only<C::wait_at(i)>();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (i < 32) {
-        constexpr int hh = i / 16, s = (i % 16) / 2;
+      if constexpr (i < NSC) {
+        constexpr int hh = i / HS, s = (i % HS) / 2;
         const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if constexpr ((i & 1) == 0)
           S[hh] = mfma32(op[i], me.qf[s], s == 0 ? zero : S[hh]);
         else
           dP[hh] = mfma32(op[i], me.dof[s], s == 0 ? zero : dP[hh]);
       } else {
-        constexpr int j = i - 32, hh = j / 8, x = (j % 8) / 4, db = j % 4;
+        constexpr int j = i - NSC, hh = j / NDQ, x = (j % NDQ) / (D / 32), db = j % (D / 32);
         const v8i16 t8 = {lo[i][0], lo[i][1], lo[i][2], lo[i][3], hi[i][0], hi[i][1], hi[i][2], hi[i][3]};
         dQ[db] = mfma32(__builtin_bit_cast(bf16x8, t8), bds[hh][x], dQ[db]);
       }
-      if constexpr (i >= 32 && i < 32 + LPS) issue_piece(i - 32, ictx, is);
-      if constexpr (i >= 16 && i < 32) score(std::integral_constant<int, 0>{}, std::integral_constant<int, i - 16>{});
-      if constexpr (i >= 32 && i < 40) {
-        score(std::integral_constant<int, 1>{}, std::integral_constant<int, 2 * (i - 32)>{});
-        score(std::integral_constant<int, 1>{}, std::integral_constant<int, 2 * (i - 32) + 1>{});
-      }
+      if constexpr (i >= NSC && i < NSC + LPS) issue_piece(i - NSC, ictx, is);
+      if constexpr (i >= HS && i < NSC)
+        static_for<16 / HS * (i - HS), 16 / HS * (i - HS + 1)>([&](auto ec) __attribute__((always_inline)) { score(std::integral_constant<int, 0>{}, ec); });
+      if constexpr (i >= NSC && i < NSC + NDQ)
+        static_for<16 / NDQ * (i - NSC), 16 / NDQ * (i - NSC + 1)>([&](auto ec) __attribute__((always_inline)) { score(std::integral_constant<int, 1>{}, ec); });
       __builtin_amdgcn_sched_barrier(0);
     });
   };
 
   // ---- the pipelined walk over entries n0 .. n1 - 1 of the tile list
   auto ring_loop = [&](auto msk_c, int n0, int n1) __attribute__((always_inline)) {
-    constexpr int LPS = decltype(msk_c)::value ? 5 : 4;
+    constexpr int LPS = 2 * NPB + (decltype(msk_c)::value ? 1 : 0);
     if (n0 >= n1) return;
     int in = n0;  // list entry whose loads are issued next
 #pragma unroll 1
@@ -1427,7 +1510,7 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
         const int kt = tl.tile(n);
         const int last = iq_row - kt * BN;  // last such key of the tile (may lie before or behind it)
         const uint64_t own = last < 0 ? 0ull : last >= 63 ? ~0ull : (2ull << last) - 1;
-        vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + ND, lane, (uint32_t)nq, vis0, own, T - kt * BN);
+        vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + ND, lane, (uint32_t)nq, own, T - kt * BN, word_of);
         vis = row_ok ? vis >> (4 * H) : 0ull;
       }
       pipelined_tile(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
@@ -1439,13 +1522,13 @@ __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) {
     asm volatile("" ::: "memory");
   };
   ring_loop(std::false_type{}, 0, NF);
-  // the masked and the ragged tiles: pipelined as well when a node has one visibility word, else the general walk
-  const int NM = a.W == 1 ? t.N : NF;
-  ring_loop(std::true_type{}, NF, NM);
-  __syncthreads();  // the ring is free: the general walk lays its own tiles over it
-  dq_general_walk<D, NT>(a, smem, tl, NM, t.N, T, cu, hk, t.nbase, me, dQ, WIDE ? 2 * pair : -1);
+  ring_loop(std::true_type{}, NF, t.N);  // the masked and the ragged tiles
   dq_store<D>(a, me, H, dQ);
 }
+template <bool WIDE>
+__global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE>(a); }
+template <bool WIDE>
+__global__ void __launch_bounds__(256, 2) k_bwd64_dq(BwdArgs a) { dq_ring_body<64, WIDE>(a); }
 
 template <int D, int HG>
 int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
@@ -1458,8 +1541,8 @@ int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
   return DAG_OK;
 }
 
-// Query heads per KV head that the dQ kernel takes one at a time on four query tiles.
-int bwd_wide_heads(int G) { return G % 4; }
+// Query heads per KV head that the dQ kernel takes one at a time on several query tiles.
+int bwd_wide_heads(int G, int head_dim) { return G % (head_dim == 128 ? Dq<128>::NPAIR : Dq<64>::NPAIR); }
 
 // Development switch, read once: DAGATTN_BWD_V1=1 runs the first dQ and dK/dV kernels for every shape.
 bool bwd_first_version() {
@@ -1480,21 +1563,23 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
   DAG_LAUNCH_CHECK();
   int rc;
   a.dq_narrow = a.G;
-  if (D == 128 && !bwd_first_version()) {
-    // the heads left over by the groups of four take four query tiles each
-    const int wide = bwd_wide_heads(a.G);
+  if (!bwd_first_version()) {
+    // the heads left over by the groups of NPAIR take NPAIR query tiles each
+    constexpr int NPAIR = Dq<D>::NPAIR, sm2 = Dq<D>::NST * Dq<D>::STAGEB;
+    const int wide = bwd_wide_heads(a.G, D);
     a.dq_narrow = a.G - wide;
-    constexpr int sm2 = dq2::NST * dq2::STAGEB;
-    if (hipFuncSetAttribute((const void*)k_bwd_dq2<false>, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
-        hipFuncSetAttribute((const void*)k_bwd_dq2<true>, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
+    auto* const one_tile = D == 128 ? k_bwd_dq2<false> : k_bwd64_dq<false>;
+    auto* const many_tiles = D == 128 ? k_bwd_dq2<true> : k_bwd64_dq<true>;
+    if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
+        hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
     if (a.dq_narrow > 0)
-      hipLaunchKernelGGL(k_bwd_dq2<false>, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)((a.dq_narrow + 3) / 4)),
-                         dim3(512), sm2, stream, a);
+      hipLaunchKernelGGL(one_tile, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)(a.dq_narrow / NPAIR)),
+                         dim3(128 * NPAIR), sm2, stream, a);
     if (wide > 0) {
-      hipLaunchKernelGGL(k_bwd_wide_rows, dim3((unsigned)total_qtiles), dim3(64), 0, stream, a);
-      const long groups_bound = std::min(total_qtiles, (total_qtiles + 3) / 4 + a.n_seqs);
-      hipLaunchKernelGGL(k_bwd_dq2<true>, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(512), sm2, stream, a);
+      hipLaunchKernelGGL(k_bwd_wide_rows<NPAIR>, dim3((unsigned)total_qtiles), dim3(64), 0, stream, a);
+      const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
+      hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
     }
     rc = hipGetLastError() == hipSuccess ? DAG_OK : DAG_ERR_HIP;
   } else {
@@ -1508,11 +1593,12 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
   hipLaunchKernelGGL(k_bwd_weights, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
   hipLaunchKernelGGL(k_bwd_order, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
   DAG_LAUNCH_CHECK();
-  if (D == 128 && !bwd_first_version()) {
-    constexpr int sm2 = dkv2::NST * dkv2::STAGEB;
-    if (hipFuncSetAttribute((const void*)k_bwd_dkv2, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
+  if (!bwd_first_version()) {
+    constexpr int sm2 = Dkv<D>::NST * Dkv<D>::STAGEB;
+    auto* const ring = D == 128 ? k_bwd_dkv2 : k_bwd64_dkv;
+    if (hipFuncSetAttribute((const void*)ring, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    hipLaunchKernelGGL(k_bwd_dkv2, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
+    hipLaunchKernelGGL(ring, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
   } else {
     hipLaunchKernelGGL((k_bwd_dkv<D>), dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm, stream, a);
   }
@@ -1710,11 +1796,11 @@ extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t h
   size_t n = 2 * dag_align_up((size_t)m->sizes.total_tokens * hq * 4, 256) +
              2 * dag_align_up((size_t)m->sizes.total_ktiles * 4, 256) +
              dag_align_up((size_t)m->sizes.total_tokens * 8, 256) + 256;
-  // head groupings that leave heads over (G not a multiple of four) at head dimension 128: the tile lists of the dQ
-  // workgroups that take four query tiles (an int32 and a byte per entry of the dense block map,
-  // three int32 per query tile)
-  if (head_dim == 128 && hq % hkv == 0 && bwd_wide_heads(hq / hkv) > 0 && m->sizes.total_tiles >= 0)
-    n += dag_align_up((size_t)m->sizes.total_tiles * 4, 256) + dag_align_up((size_t)m->sizes.total_tiles, 256) +
+  // head groupings that leave heads over (G not a multiple of four, at head dimension 64 of two): the tile
+  // lists of the dQ workgroups that take several query tiles (an int32 per entry of the dense block
+  // map, three int32 per query tile)
+  if (hq % hkv == 0 && bwd_wide_heads(hq / hkv, head_dim) > 0 && m->sizes.total_tiles >= 0)
+    n += dag_align_up((size_t)m->sizes.total_tiles * 4, 256) +
          3 * dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256);
   return n;
 }
@@ -1767,8 +1853,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.total_ktiles = (int)m->sizes.total_ktiles;
   a.tok_vis0 = (uint64_t*)(a.kt_order + dag_align_up((size_t)m->sizes.total_ktiles * 4, 256) / 4);
   a.wide_col = (int32_t*)((char*)a.tok_vis0 + dag_align_up((size_t)m->sizes.total_tokens * 8, 256));
-  a.wide_flag = (uint8_t*)((char*)a.wide_col + dag_align_up((size_t)m->sizes.total_tiles * 4, 256));
-  a.wide_n = (int32_t*)((char*)a.wide_flag + dag_align_up((size_t)m->sizes.total_tiles, 256));
+  a.wide_n = (int32_t*)((char*)a.wide_col + dag_align_up((size_t)m->sizes.total_tiles * 4, 256));
   a.wide_nfast = a.wide_n + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
   a.wide_list = a.wide_nfast + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
   a.total_qtiles = (int)m->sizes.total_qtiles;
