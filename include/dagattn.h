@@ -22,8 +22,7 @@
  *   - Process-wide state: none that a result depends on.  What the library keeps until the
  *     process ends is (a) per device, the address of the scratch array of
  *     dag_attn_decode_static (see there), (b) attributes set on its own kernels, and (c) the
- *     development knobs of the decode split sizes and of the prefill head split, read from the
- *     environment once.  It creates no streams and no events.  Calls on different streams may
+ *     development knobs of the decode split sizes, read from the environment once.  It creates no streams and no events.  Calls on different streams may
  *     overlap if their buffers (workspaces included) do not.
  */
 #ifndef DAGATTN_H
@@ -159,9 +158,10 @@ int dag_attn_prefill(const dag_meta_t* meta, const void* q, const void* k, const
 
 /* The two halves of dag_attn_prefill (Eq. 2 + Eq. 3), for callers that want them as separate
  * launches, e.g. to time the attention kernel alone or to prepare V while Q and K are still being
- * produced.  dag_prefill_prepare_v writes the key-tile-wise transposed copy of v [T][hkv][head_dim]
- * into `ws` (a no-op for DAG_F32); dag_attn_prefill_prepared is dag_attn_prefill without that
- * step: it expects `ws` as dag_prefill_prepare_v left it for the same meta, v, hkv, head_dim and
+ * produced.  dag_prefill_prepare_v writes into `ws` what the attention kernel works from -- its work
+ * list or, where it needs one, a key-tile-wise transposed copy of v [T][hkv][head_dim] -- (a no-op for
+ * DAG_F32); dag_attn_prefill_prepared is dag_attn_prefill without that
+ * step: it expects `ws` as dag_prefill_prepare_v left it for the same meta, v, hq, hkv, head_dim and
  * dtype.  Arguments, layouts, errors and the workspace size are those of dag_attn_prefill.
  * The workspace also holds the attention kernel's work-distribution counters: dag_prefill_prepare_v
  * zeroes them and every attention launch leaves them zeroed, so a workspace must go through

@@ -6,11 +6,12 @@ extern "C" size_t dag_prefill_workspace_bytes(const dag_meta_t* m, int32_t hkv, 
                                               dag_dtype_t dtype) {
   if (!m || dtype != DAG_BF16 || hkv < 1 || head_dim < 1 || m->sizes.total_ktiles < 0) return 0;
   // key-tile-wise transposed copy of V: [key tile][kv head][head_dim][tile_n] bf16, then the
-  // work-distribution counters and the tables of the 256-row query tiles, plus slack for
-  // aligning the caller's pointer to 256 bytes
-  if (m->sizes.total_qtiles < 0 || m->sizes.csr_capacity < 0) return 0;
+  // work-distribution counters, the tables of the 256-row query tiles and of the nodes' query
+  // chunks, plus slack for aligning the caller's pointer to 256 bytes
+  if (m->sizes.total_qtiles < 0 || m->sizes.csr_capacity < 0 || m->sizes.total_tokens < 0 || m->sizes.total_nodes < 0) return 0;
   return (size_t)m->sizes.total_ktiles * hkv * head_dim * m->tile_n * 2 +
-         prefill_bf16_table_bytes(m->sizes.total_qtiles, m->sizes.csr_capacity) + 256;
+         prefill_bf16_table_bytes(m->sizes.total_qtiles, m->sizes.csr_capacity) +
+         prefill_node_table_bytes(m->sizes.total_tokens, m->sizes.total_nodes, m->words_per_node) + 256;
 }
 
 namespace {
@@ -54,6 +55,23 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   a->wide_pre = need > 0 ? a->wide_cnt + m->sizes.total_qtiles : nullptr;
   a->wide_desc = need > 0 ? a->wide_pre + 8 * m->sizes.total_qtiles : nullptr;
   a->wide_col = need > 0 ? a->wide_desc + 8 * m->sizes.total_qtiles : nullptr;
+  a->node_tok_start = m->node_tok_start;
+  a->node_pos_start = m->node_pos_start;
+  a->pos_ids = m->pos_ids;
+  a->total_tokens = m->sizes.total_tokens;
+  a->total_nodes = m->sizes.total_nodes;
+  a->node_runs = nullptr;
+  if (need > 0 && m->node_tok_start && m->node_pos_start && m->pos_ids &&
+      prefill_has_node_tables(a->total_nodes, m->words_per_node)) {
+    int32_t* t = a->wide_col + m->sizes.csr_capacity;
+    a->node_runs = t += (uintptr_t)t / 4 % 2;  // 8-byte pairs
+    t += a->total_nodes * 128;
+    for (int i = 0; i < DAG_CHUNK_SIZES; ++i) {
+      const int64_t n = chunk_slots(a->total_tokens, a->total_nodes, DAG_CHUNK_ROWS[i]);
+      a->chunk[i] = {t, t + 62, t + 62 + n, t + 62 + 9 * n};
+      t += 62 + 17 * n;
+    }
+  }
   a->head0 = 0;
   a->heads = hq / hkv;
   a->n_tiles_dev = nullptr;

@@ -9,6 +9,15 @@
 // KV heads of a tile next to each other) and takes every further item from a counter, one item
 // ahead of its use.  The K/V stream of the next item is prefetched while the current one finishes.
 //
+// Two ways to cut the work.  On query chunks (k_prefill_nodes; tables from k_node_rows, where they are
+// described) the rows are cut at the borders of sibling groups and the keys of a chunk stream in the
+// order of what its node sees: all but its last tiles are free of masks, and V is read as it is
+// through the transposing LDS load.  Random DAGs of 8 x 64 nodes of 32 to 256 tokens, 32 / 8 heads: 62 %
+// of the block map's tiles are PARTIAL and 34 % of what they compute is masked; 1770 + 83 (V^T) us on
+// them, 1357 + 13 (tables) on chunks.  2048 -> 8 x 256 -> 512: 618 -> 598 us for the whole prefill, the
+// V^T pre-pass being gone; the same fork-join 16 times as long: 38.6 -> 37.7 ms.
+// On the block map's tiles (k_prefill_bf16) for nodes too short for chunks, more than 128 nodes, and
+// (PAGED) paged contexts:
 // Only the key tiles the block map lists are visited.  The CSR row of a query tile lists its FULL
 // tiles first: after the first tile they run through a steady-state loop without any test but an
 // after-the-fact overflow check; PARTIAL tiles (and a ragged last tile) follow and go through the
@@ -34,7 +43,7 @@
 //   K block = R keys x C chunks (R = 1024 / (2 D)), stride 1024 + 16 bytes:
 //             [chunk / 4][key % R][chunk % 4][16 B]
 //   V^T block = 8 output dimensions x 8 key groups, stride 1024 + 128 bytes: [key group][dim % 8][16 B]
-//             (the workspace copy is stored in this order, so its loads are linear)
+//             (the workspace copy is stored in this order, so its loads are linear); on chunks V has K's layout
 //
 // Register layout.  Scores are computed transposed, S^T = K Q^T, so that after the MFMA a lane
 // holds one query row (lane % 32) and 16 keys of the 32-key half in registers: the softmax row
@@ -48,7 +57,6 @@
 // only raised when some row of the wave exceeds it by more than 2^8 (general step) or when a row's
 // probabilities of a half sum to 2^10 or more (steady state, found afterwards); probabilities may
 // exceed 1 by such a factor, which fp32 accumulation and the final division absorb exactly.
-#include <stdlib.h>
 #include <type_traits>
 
 #include "common.h"
@@ -125,6 +133,22 @@ template <int D, bool PAGED>
 __device__ constexpr int v_imm(int st, int db) {
   constexpr int BLKV = 1024 + 16 * 8, IPV = (D / 8) / 8;
   return PAGED ? (2 * st + db / IPV + 8 * (db % IPV)) * BLKV : db * 4 * BLKV + st * 256;
+}
+// Row-major V tile (key chunks of nodes): the two transposing reads of that operand.
+template <int D>
+__device__ constexpr int v_tr_imm(int st, int db, int second) {
+  constexpr int KPB = 64 / (D / 8), BLKK = 1024 + 16;
+  return (16 * st + 4 * second) / KPB * BLKK + 4 * second % KPB * 64 + db * 64 * KPB;
+}
+
+// Where a kernel's K/V stream comes from: the packed sequence through the block map's tiles, the
+// paged pools, or the packed sequence through the runs of tokens that a node sees (k_node_rows).
+enum { STREAM_TILES = 0, STREAM_PAGES = 1, STREAM_NODES = 2 };
+typedef short v4i16_t __attribute__((ext_vector_type(4)));
+typedef short v8i16_t __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ bf16x8 join_halves(v4i16_t lo, v4i16_t hi) {
+  const v8i16_t x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, x);
 }
 
 struct Item {  // wave-uniform description of a work item
@@ -258,6 +282,96 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
   if (qt == 0 && lane == 0) *wide_count = n;
 }
 
+// Query chunks.  Consecutive nodes with the same ancestors (the siblings of a fork; most often a single
+// node) form a group, and the query rows are cut at the borders of the groups instead of every 64
+// tokens.  All rows of a chunk then see the same tokens in front of the group, the ancestors', and
+// of the group itself every row the tokens of its own node up to itself.  So with the visible keys in
+// one list -- the ancestors' tokens, then the tokens from the start of the chunk's first node u on --
+// row i (counted from u's first token) sees the positions < A (A: tokens of the ancestors) and A + (its
+// node's first row) .. A + i.  The keys of a chunk stream in that order, whatever tiles of the sequence
+// they lie in: every key tile is full, only the last one or two take a mask, and nothing
+// invisible is computed but there.  The list is a few runs of consecutive tokens (neighbouring visible
+// nodes are one run), kept per node u as {first position, token - position}.
+// One wave per node (at most 128 per sequence, so at most 64 runs): its runs, and for the first node of a
+// group the descriptors of its chunks.
+template <int W>
+__global__ void __launch_bounds__(256) k_node_rows(int n_seqs, int total_nodes, int rows, int64_t n_slots,
+                                                   const int32_t* __restrict__ node_start,
+                                                   const int32_t* __restrict__ cu_seqlens,
+                                                   const int32_t* __restrict__ tok_node,
+                                                   const int32_t* __restrict__ node_tok_start,
+                                                   const int32_t* __restrict__ node_pos_start,
+                                                   const uint64_t* __restrict__ node_vis, int32_t* __restrict__ sched,
+                                                   int32_t* __restrict__ runs, ChunkTables t) {
+  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && threadIdx.x < DAG_SCHED_INTS) sched[threadIdx.x] = 0;  // work counters of the attention kernel
+  if (gv >= total_nodes) return;
+  const int b = dag_find_segment(node_start, n_seqs, gv);
+  const int n0 = node_start[b], n = node_start[b + 1] - n0, v = gv - n0;
+  const int cu = cu_seqlens[b], T = cu_seqlens[b + 1] - cu;
+  const uint64_t below = (1ull << lane) - 1;
+  uint64_t mine[W], sees[W], same[W];  // the node's ancestors; with the node itself; nodes with the same ancestors
+#pragma unroll
+  for (int y = 0; y < W; ++y) {
+    const int bit = v - 64 * y;
+    mine[y] = node_vis[(int64_t)gv * W + y] & (bit >= 64 ? ~0ull : bit <= 0 ? 0ull : (1ull << bit) - 1);
+    sees[y] = mine[y] | (bit >= 0 && bit < 64 ? 1ull << bit : 0ull);
+  }
+  int2* const out = (int2*)runs + (int64_t)gv * 64;
+  int before = 0, n_runs = 0, anc = 0;  // tokens and runs of the words in front; tokens of the ancestors
+#pragma unroll
+  for (int x = 0; x < W; ++x) {
+    const int u = 64 * x + lane;
+    const int first = u < n ? node_tok_start[n0 + u] : T, len = (u + 1 < n ? node_tok_start[n0 + u + 1] : T) - first;
+    const int seen = (sees[x] >> lane) & 1 ? len : 0;
+    int incl = seen;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    const int pos = before + incl - seen;
+    before += __shfl(incl, 63);
+    if (v / 64 == x) anc = __shfl(pos, v % 64);
+    const uint64_t starts = sees[x] & ~(sees[x] << 1 | (x > 0 ? sees[x > 0 ? x - 1 : 0] >> 63 : 0));  // a run starts where the node in front is not visible
+    if ((starts >> lane) & 1) out[n_runs + __popcll(starts & below)] = int2{pos, cu + first - pos};
+    n_runs += __popcll(starts);
+    bool eq = u < n;
+#pragma unroll
+    for (int y = 0; y < W; ++y) {
+      const uint64_t theirs = u < n ? node_vis[(int64_t)(n0 + u) * W + y] & (y < x ? ~0ull : y == x ? below : 0ull) : 0;
+      eq = eq && theirs == mine[y];
+    }
+    same[x] = __ballot(eq);
+  }
+  if (lane >= n_runs) out[lane] = int2{INT32_MAX, 0};
+  auto is_same = [&](int u) { return ((W > 1 && u >= 64 ? same[W - 1] : same[0]) >> (u & 63)) & 1; };
+  if (v > 0 && is_same(v - 1)) return;  // the first node of the group writes its chunks
+  int end = v + 1;                      // first node behind the group
+  while (end < n && is_same(end)) ++end;
+  const int g0 = node_tok_start[gv], g1 = end < n ? node_tok_start[n0 + end] : T;
+  const int64_t slot0 = (cu + g0) / rows + gv, gend = n0 + end;
+  const int64_t slot1 = gend < total_nodes ? (int64_t)(cu + g1) / rows + gend : n_slots;
+  for (int c = lane; slot0 + c < slot1; c += 64) {
+    if (c * rows >= g1 - g0) {
+      t.cnt[slot0 + c] = -1;
+      continue;
+    }
+    const int u = tok_node[cu + g0 + c * rows];  // node of the chunk's first row
+    const int u0 = node_tok_start[n0 + u], u1 = u + 1 < n ? node_tok_start[n0 + u + 1] : T;
+    const int row0 = g0 + c * rows - u0, row_end = min(row0 + rows, g1 - u0);  // counted from u's first token
+    int32_t* d = t.pre + (slot0 + c) * 8;
+    t.cnt[slot0 + c] = (anc + row_end + TN - 1) / TN;
+    d[0] = cu + u0;
+    d[1] = g1 - u0;
+    d[2] = row0;
+    d[3] = (n0 + u) * 64;
+    d[4] = (anc + row_end + TN - 1) / TN;
+    d[5] = (row_end <= u1 - u0 ? anc + row0 + 1 : anc) / TN;  // tiles whose 64 positions every row sees
+    d[6] = anc;
+    d[7] = node_pos_start[gv];  // position id of the first token of every node of the group
+  }
+}
+
 // Work items of the paged prefill (section 4.3, phase II: the new tokens of a node are prefilled
 // against the cached KV of its predecessors, which is only referenced, never copied).  One wave
 // per (node, 64-row tile of its new tokens); slots past the node's last tile mark themselves with
@@ -333,8 +447,9 @@ __device__ unsigned long long g_tlog[4096];
 #endif
 // PAGED: K and V^T tiles come from the paged pools of the decode path through a list of pages per
 // work item instead of from the packed sequence (see k_paged_rows); the pipeline is the same.
-template <int D, int HG, int NRG, bool PAGED>
-__global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a) {
+template <int D, int HG, int NRG, int STREAM>
+__device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
+  constexpr bool PAGED = STREAM == STREAM_PAGES, NODES = STREAM == STREAM_NODES;
   constexpr int RB = 1;                      // 32-row blocks per wave
   constexpr int NW = HG * NRG;               // waves: NRG row blocks x HG query heads
   constexpr int CH = D / 8;                  // 16-byte chunks per K row
@@ -342,7 +457,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   constexpr int DB = D / 32;                 // 32-row blocks of O^T
   constexpr int KPB = 64 / CH;               // keys per K block
   constexpr int NBK = TN / KPB;              // K blocks per tile
-  constexpr int NBV = D / 8;                 // V^T blocks per tile (8 output dimensions each)
+  constexpr int NBV = NODES ? NBK : D / 8;   // V blocks per tile (V^T: 8 output dimensions each; row-major: like K)
   // Every wave issues its share of the K/V loads of a tile: the waves meet at a barrier once per
   // tile, so the tile takes as long as its slowest wave, and the load issue (with the cursor
   // arithmetic in front of it) is what makes a wave slow.
@@ -350,8 +465,10 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   constexpr int IPK = NBK / NISS, IPV = NBV / NISS;  // blocks per tile and issuing wave
   constexpr int LPT = IPK + IPV;             // loads per tile and wave
   constexpr int BLKK = 1024 + 16;            // block strides (skewed so that reads are conflict free)
-  constexpr int BLKV = 1024 + 16 * 8;
+  constexpr int BLKV = NODES ? BLKK : 1024 + 16 * 8;
   constexpr int KTILE = NBK * BLKK, VTILE = NBV * BLKV;
+  constexpr int AREC = STREAM == STREAM_TILES ? 256 : 0;  // node-id record per ring slot
+  constexpr int VRD = NODES ? 2 : 1;         // LDS reads per V operand
   constexpr float TH_LOG2 = 8.f;
   static_assert(IPK >= 1 && IPK * NISS == NBK && IPV >= 1 && IPV * NISS == NBV, "tile loads must divide over the waves");
   static_assert((NSTAGE - 2) * LPT < 64 && NSTAGE >= 3, "vmcnt range / ring depth");
@@ -378,7 +495,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
 
   const uint16_t* qg = (const uint16_t*)a.q;
   const unsigned char* kg = (const unsigned char*)a.k;
-  const unsigned char* vtg = (const unsigned char*)a.vt;
+  const unsigned char* vtg = (const unsigned char*)(NODES ? a.v : a.vt);
   const uint32_t rowbytes = (uint32_t)a.hkv * D * 2;
 
   // Work distribution.  The items are the (query tile, head group) pairs in launch order, the
@@ -406,6 +523,8 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   auto head_of = [&](const Item& I) __attribute__((always_inline)) { return I.hk * G + a.head0 + min(I.hs * HG + hj, a.heads - 1); };
   auto head_is_mine = [&](const Item& I) __attribute__((always_inline)) { return I.hs * HG + hj < a.heads; };
 
+  // NODES: K and V rows of the tile are gathered: load i fetches the same rows of both, at per-lane
+  // offsets (row of the tile -> token through the runs of the item's node), in the K block layout.
   // What this lane fetches in a wave-level load (LDS position 16*lane inside the block):
   //   K:   key (lane / 4) % KPB of the block, chunk 4 * (lane / (4 * KPB)) + lane % 4: four
   //        consecutive lanes fetch 64 consecutive bytes of one row (one cache-line lookup)
@@ -451,6 +570,45 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   unsigned char *p_kl = nullptr, *p_vl = nullptr;
   int p_last = 0;
   bool p_ragged = false;
+  // NODES: row offsets of the tile set up last (K of the pending group, V of the one after it) and of
+  // the tile before (V of the pending group); the constant part of a row's offset; the runs of the
+  // cursor's item, run e in lane e {first position, token - position}, and where the cursor is in them.
+  uint32_t p_koff[IPK], p_voff[IPK], roff_c[IPK];
+  int run_pos = 0, run_delta = 0, run_at = 0, run_end = 0, run_d = 0, is_P = 0;
+#pragma unroll
+  for (int i = 0; i < IPK; ++i) {
+    p_koff[i] = p_voff[i] = 0;
+    roff_c[i] = (uint32_t)((w + NISS * i) * KPB + kkey) * rowbytes + kchunk;
+  }
+  auto node_setup = [&](unsigned g, const unsigned char* kbase, const unsigned char* vbase, int idx) __attribute__((always_inline)) {
+    const unsigned slot = g % NSTAGE, vslot = (g + NSTAGE - 1) % NSTAGE;
+    const int p0 = idx * TN, last = min(p0 + TN, is_P) - 1;
+    int pos[IPK], tok[IPK];
+#pragma unroll
+    for (int i = 0; i < IPK; ++i) {  // (positions past the end re-read the last one and are masked)
+      pos[i] = min(p0 + (w + NISS * i) * KPB + kkey, last);
+      tok[i] = pos[i] + run_d;
+    }
+    while (run_end <= last) {  // (wave-uniform) the tile reaches into the next run
+      run_at = run_at + 1;
+      const int c = run_end;
+      run_d = __builtin_amdgcn_readlane(run_delta, run_at);
+      run_end = run_at < 63 ? __builtin_amdgcn_readlane(run_pos, run_at + 1) : INT32_MAX;
+#pragma unroll
+      for (int i = 0; i < IPK; ++i) tok[i] = pos[i] >= c ? pos[i] + run_d : tok[i];
+    }
+#pragma unroll
+    for (int i = 0; i < IPK; ++i) {
+      const uint32_t off = (uint32_t)tok[i] * rowbytes + kchunk;
+      p_voff[i] = g == 0 ? off : p_koff[i];
+      p_koff[i] = off;
+    }
+    p_ktile = kbase;
+    p_vtile = g == 0 ? vbase : v_saved;
+    v_saved = vbase;
+    p_kl = Kbase + slot * KTILE + w * BLKK;
+    p_vl = Vbase + vslot * VTILE + w * BLKV;
+  };
   auto issue_setup = [&](unsigned g, const unsigned char* kbase, const unsigned char* vbase, int cu, int T, int kt,
                          bool with_nodes) __attribute__((always_inline)) {
     const unsigned slot = g % NSTAGE, vslot = (g + NSTAGE - 1) % NSTAGE;
@@ -470,12 +628,17 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   };
   auto issue_setup_flush = [&](unsigned g) __attribute__((always_inline)) {  // the stream's last group: V^T of the last tile (its K once more)
     p_vtile = v_saved;
+    if (NODES)
+#pragma unroll
+      for (int i = 0; i < IPK; ++i) p_voff[i] = p_koff[i];
     p_kl = Kbase + (g % NSTAGE) * KTILE + w * BLKK;
     p_vl = Vbase + ((g + NSTAGE - 1) % NSTAGE) * VTILE + w * BLKV;
   };
   auto issue_part = [&](int i) __attribute__((always_inline)) {  // i = 0 .. LPT - 1, a compile-time constant at every call site
     if (i < IPK) {
-      if (PAGED) {
+      if (NODES) {
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_ktile + p_koff[i < IPK ? i : 0]), (lds_ptr_t)(p_kl + i * NISS * BLKK), 16, 0, 0);
+      } else if (PAGED) {
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_ktile + (i * 1024 + ksrc)), (lds_ptr_t)(p_kl + i * NISS * BLKK), 16, 0, 0);
       } else if (!p_ragged) {
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_ktile + (size_t)((w + NISS * i) * KPB) * rowbytes + ksrc),
@@ -485,6 +648,9 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_ktile + ((uint32_t)rk * rowbytes + kchunk)),
                                          (lds_ptr_t)(p_kl + i * NISS * BLKK), 16, 0, 0);
       }
+    } else if (NODES) {
+      const int iv = i - IPK;
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_vtile + p_voff[iv >= 0 ? iv : 0]), (lds_ptr_t)(p_vl + iv * NISS * BLKV), 16, 0, 0);
     } else {  // the transposed copy is zero padded: no ragged case
       const int iv = i - IPK;
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_vtile + (iv * VSTEP + vsrc)),
@@ -502,7 +668,11 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   const int krow = key_of_row(L);
   const uint32_t koff = PAGED ? 2 * (krow / 16) * BLKK + (krow % 16) * 16 + H * 256
                               : (krow / KPB) * BLKK + (krow % KPB) * 64 + H * 16;
-  const uint32_t voff = PAGED ? (L / 16) * 512 + H * 256 + (L % 16) * 16 : (L / 8) * BLKV + (L % 8) * 16 + H * 128;
+  // NODES: the V tile is row-major like K and is read with the transposing LDS load (16 lanes point at
+  // four rows x 16 dimensions and lane j receives dimension j of the four rows): V^T of 16 keys x 32
+  // dimensions is rows 8 H .. + 3, then 8 H + 4 .. + 7, dimensions 16 (lane / 16 % 2) ..
+  const uint32_t voff = NODES   ? 8 * H / KPB * BLKK + (lane % 16 / 4) * 64 + (lane / 16 % 2) * 32 + (lane % 4) * 8
+                        : PAGED ? (L / 16) * 512 + H * 256 + (L % 16) * 16 : (L / 8) * BLKV + (L % 8) * 16 + H * 128;
 
   f32x16 O[RB][DB];
   // Scores are kept relative to a reference maximum per row, in the exponent's units: the Q rows
@@ -626,6 +796,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     constexpr int PF = 3;  // operand reads in flight ahead of the MFMA that uses them
     constexpr int MAXSLOT = NQ + 2 < NSLOT ? NQ + 2 : NSLOT;  // where the row maxima are taken
     bf16x8 opnd[NSLOT];
+    v4i16_t vlo[NSLOT], vhi[NSLOT];  // (NODES: V operands, two reads each)
     float rs[RB];
     bool need = false;
 #pragma unroll
@@ -638,10 +809,16 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
       constexpr int i = decltype(ic)::value;
       const uint32_t ka = kaddr, va = vaddr;  // (named here: captures inside discarded branches trip the compiler)
       bf16x8* const op = opnd;
+      v4i16_t *const lop = vlo, *const hip_ = vhi;
       if constexpr (i < NQ)
         asm volatile("ds_read_b128 %0, %1 offset:%2"
                      : "=v"(op[i])
                      : "v"(ka), "n"(k_imm<D, PAGED>(HQ, i)));
+      else if constexpr (i < NSLOT && NODES)
+        asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                     : "=&v"(lop[i]), "=&v"(hip_[i])
+                     : "v"(va), "n"(v_tr_imm<D>(2 * HV + (i - NQ) / DB, (i - NQ) % DB, 0)),
+                       "n"(v_tr_imm<D>(2 * HV + (i - NQ) / DB, (i - NQ) % DB, 1)));
       else if constexpr (i < NSLOT)
         asm volatile("ds_read_b128 %0, %1 offset:%2"
                      : "=v"(op[i])
@@ -654,14 +831,16 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
       fetch(std::integral_constant<int, i + PF>{});
-      wait_lgkmcnt(NSLOT - 1 - i < PF ? NSLOT - 1 - i : PF);
+      constexpr int newest = i + PF < NSLOT ? i + PF : NSLOT - 1;  // reads behind slot i's own that may be in flight
+      wait_lgkmcnt(newest - i + (VRD - 1) * ((newest < NQ ? 0 : newest - NQ + 1) - (i < NQ ? 0 : i - NQ + 1)));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
-        if (i < NQ) {
+        if constexpr (i < NQ) {
           if (qk_on) Sn[r] = mfma32(opnd[i], qf[r][i < NQ ? i : 0], i == 0 ? negM[r] : Sn[r]);
         } else {
-          if (pv_on) O[r][(i - NQ) % DB] = mfma32(opnd[i], Pp[r][(i - NQ) / DB], O[r][(i - NQ) % DB]);
+          const bf16x8 vop = NODES ? join_halves(vlo[i], vhi[i]) : opnd[i];
+          if (pv_on) O[r][(i - NQ) % DB] = mfma32(vop, Pp[r][(i - NQ) / DB], O[r][(i - NQ) % DB]);
         }
       }
       extra(i, NSLOT);
@@ -750,10 +929,10 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   // at the start of an item, handed to the other waves through `mbox` before its last tile.
   const bool grabber = w == NW - 1;
   int grabbed = 0;
-  uint32_t* const mbox = (uint32_t*)(Abase + NSTAGE * 256);
+  uint32_t* const mbox = (uint32_t*)(Abase + NSTAGE * AREC);
   // after the mailbox: per wave, the piece of LDS that its output rows pass through
   constexpr int OROW = 64 + 16;
-  unsigned char* const Obase = Abase + NSTAGE * 256 + 16 + w * (32 * OROW);
+  unsigned char* const Obase = Abase + NSTAGE * AREC + 16 + w * (32 * OROW);
   int mslot = 0;
 
   // The K/V tile stream runs ahead of the computation, across the item boundary: `ti` groups have
@@ -766,7 +945,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   // tiles, and 64 key-tile indices of its row in a vector register (lane e holds entry
   // (iss_idx & ~63) + e; a scalar or vector load inside the tile loop would drain the K/V
   // prefetches with its wait).  col_nxt is the same for the first 64 entries of the next item.
-  int is_cu, is_T, is_c0, is_N, is_nfast, col_iss, col_nxt;
+  int is_cu, is_T, is_c0, is_N, is_nfast, col_iss, col_nxt, delta_nxt = 0;
   const unsigned char *is_kbase, *is_vbase;
   // PAGED: an entry of the item's list is a tile of four pages {page ids, token counts (a byte
   // each), tile index in the context, -}; a wave only needs the page it fetches pieces of.
@@ -774,10 +953,23 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     const int e = c0 + min(first + lane, N - 1);
     return PAGED ? a.col[(size_t)e * 8 + (w >> 1)] : a.col[e];
   };
-  auto load_cols = [&](const Item& I, int first) __attribute__((always_inline)) { return col_at(I.c0, I.N, first); };
-  auto cursor_enter = [&](const Item& I, int cols) __attribute__((always_inline)) {
+  // NODES: what lane e needs of run e of the item's node instead: first position (returned), token - position
+  auto load_cols = [&](const Item& I, int first) __attribute__((always_inline)) {
+    return NODES ? a.col[(size_t)(I.c0 + lane) * 2] : col_at(I.c0, I.N, first);
+  };
+  auto load_deltas = [&](const Item& I) __attribute__((always_inline)) { return NODES ? a.col[(size_t)(I.c0 + lane) * 2 + 1] : 0; };
+  auto cursor_enter = [&](const Item& I, int cols, int deltas) __attribute__((always_inline)) {
     is_cu = I.cu; is_T = I.T; is_c0 = I.c0; is_N = I.N; is_nfast = I.nfast;
-    if (PAGED) {
+    if (NODES) {
+      is_kbase = kg + (size_t)I.hk * (D * 2);
+      is_vbase = vtg + (size_t)I.hk * (D * 2);
+      is_P = I.nstart + min(I.row0 + 32 * NRG, I.T);
+      run_pos = cols;
+      run_delta = deltas;
+      run_at = 0;
+      run_d = __builtin_amdgcn_readlane(deltas, 0);
+      run_end = __builtin_amdgcn_readlane(cols, 1);
+    } else if (PAGED) {
       is_kbase = kg + (size_t)I.hk * (D * 32) + (w & 1) * (IPK * 1024);
       is_vbase = vtg + (size_t)I.hk * (D * 32) + (w & 1) * (IPV * 1024);
     } else {
@@ -787,8 +979,9 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     col_iss = cols;
     iss_idx = 0;
   };
-  cursor_enter(cur, load_cols(cur, 0));
+  cursor_enter(cur, load_cols(cur, 0), load_deltas(cur));
   col_nxt = has_next ? load_cols(nxt, 0) : 0;
+  delta_nxt = has_next ? load_deltas(nxt) : 0;
   const bool issuer = w < NISS;
   // First half of issuing the next tile of the stream: cursor, tile index, addresses.  The LPT
   // loads follow through issue_part (at once in try_issue, slot by slot in the pipeline).
@@ -799,7 +992,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
       if (iss_next) return false;  // (the item after the next one is not known yet)
       if (has_next) {
         iss_next = 1;
-        cursor_enter(nxt, col_nxt);
+        cursor_enter(nxt, col_nxt, delta_nxt);
       } else {                     // end of the stream: its last group
         if (flushed) return false;
         flushed = true;
@@ -808,6 +1001,9 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     }
     if (flush) {
       issue_setup_flush(ti);
+    } else if (NODES) {
+      node_setup(ti, is_kbase, is_vbase, iss_idx);
+      iss_idx = iss_idx + 1;
     } else {
       if ((iss_idx & 63) == 0 && iss_idx != 0) {  // rows with more than 64 tiles: next 64 entries
         col_iss = col_at(is_c0, is_N, iss_idx);
@@ -896,15 +1092,18 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   // Row data for the mask: node of each row (rnode), word 0 of that node's visibility bitset
   // (vis0), and the nodes of the next item's rows, fetched one item ahead so that the dependent
   // vis0 load can go out together with the next Q rows.
-  int rnode[RB], rnode_nxt[RB];
+  // NODES: how many tokens of its own node come before the row (siblings start at the same position).
+  int rnode[RB], rnode_nxt[RB], rdepth[RB];
   uint64_t vis0[RB];
+  auto row_data = [&](const Item& I, int r) __attribute__((always_inline)) { return (NODES ? a.pos_ids : a.tok_node)[token_of(I, r)]; };
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    rnode[r] = PAGED ? 0 : a.tok_node[token_of(cur, r)];
-    rnode_nxt[r] = !PAGED && has_next ? a.tok_node[token_of(nxt, r)] : 0;
+    rnode[r] = PAGED ? 0 : row_data(cur, r);
+    rnode_nxt[r] = !PAGED && has_next ? row_data(nxt, r) : 0;
+    rdepth[r] = NODES ? rnode[r] - cur.ktb : 0;
   }
 #pragma unroll
-  for (int r = 0; r < RB; ++r) vis0[r] = PAGED ? 0 : a.node_vis[(int64_t)(cur.nstart + rnode[r]) * a.W];
+  for (int r = 0; r < RB; ++r) vis0[r] = STREAM != STREAM_TILES ? 0 : a.node_vis[(int64_t)(cur.nstart + rnode[r]) * a.W];
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -920,6 +1119,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
       asm volatile("" ::"v"(vis0[r]), "v"(rnode_nxt[r]));
     }
     asm volatile("" ::"v"(col_iss), "v"(col_nxt));
+    if (NODES) asm volatile("" ::"v"(run_pos), "v"(run_delta), "v"(delta_nxt));
     // Refill the rings (the cursor could not go past the end of the old `nxt`): group g goes into
     // the slots of K tile g - NSTAGE and V^T tile g - 1 - NSTAGE, both read for the last time before
     // the old item's last barrier.  Here, behind the arrival of the row data and not at the end of
@@ -955,6 +1155,16 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
       for (int r = 0; r < RB; ++r) rm[r] = ~0ull;
       return;
 #endif
+      if constexpr (NODES) {
+        // a row sees the positions in front of `nstart` and those of its own node up to its own
+        auto first_bits = [&](int c) __attribute__((always_inline)) { return c >= 64 ? ~0ull : (c <= 0 ? 0ull : ((1ull << c) - 1)); };
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          const int own = cur.nstart + min(row_of(cur, r), cur.T - 1) - n * TN;  // the row's own position inside the tile
+          rm[r] = (first_bits(cur.nstart - n * TN) | (first_bits(own + 1) & ~first_bits(own - rdepth[r]))) >> (8 * H);
+        }
+        return;
+      }
       if constexpr (PAGED) {
         // A page of the context holds its first `count` tokens (a byte per page in the entry's word
         // 4); row i of the node's new tokens sees the slots of the context up to nstart + i (its
@@ -1066,9 +1276,11 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
         static_assert((2 * NS) % RING == 0 && KSTEPS >= PF - 4 && PF < RING, "operand ring");
         if (need) rescale(SB);
         bf16x8 opr[RING];
+        v4i16_t vlo[RING], vhi[RING];  // (NODES: V operands)
         auto ffetch = [&](auto ic, uint32_t ka, uint32_t va, uint32_t kn) __attribute__((always_inline)) {  // operand of slot ic (2 NS ..: next tile)
           constexpr int i = decltype(ic)::value;
           bf16x8* const op = opr;
+          v4i16_t *const lop = vlo, *const hip_ = vhi;
           if constexpr (i >= 2 * NS) {
             constexpr int q = i - 2 * NS;
             asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(op[i % RING]) : "v"(kn), "n"(k_imm<D, PAGED>(0, q)));
@@ -1077,6 +1289,11 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
             asm volatile("ds_read_b128 %0, %1 offset:%2"
                          : "=v"(op[i % RING])
                          : "v"(ka), "n"(k_imm<D, PAGED>(st, j)));
+          } else if constexpr (NODES) {
+            constexpr int st = i / NS, j = i % NS - KSTEPS;
+            asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                         : "=&v"(lop[i % RING]), "=&v"(hip_[i % RING])
+                         : "v"(va), "n"(v_tr_imm<D>(2 * st + j / DB, j % DB, 0)), "n"(v_tr_imm<D>(2 * st + j / DB, j % DB, 1)));
           } else {
             constexpr int st = i / NS, j = i % NS - KSTEPS;
             asm volatile("ds_read_b128 %0, %1 offset:%2"
@@ -1155,7 +1372,13 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
             constexpr int i = decltype(ic)::value, st = i / NS, j = i % NS;
             constexpr int ahead = i + PF < 2 * NS + KSTEPS ? PF : 2 * NS + KSTEPS - 1 - i;  // reads in flight after this slot's
             if constexpr (i + PF < 2 * NS + KSTEPS) ffetch(std::integral_constant<int, i + PF>{}, ka, va, kn);
-            wait_lgkmcnt(ahead);
+            // (NODES: a V operand takes two reads)
+            constexpr int ahead_v = [](int from, int to) {
+              int n = 0;
+              for (int x = from; x < to; ++x) n += x < 2 * NS && x % NS >= KSTEPS;
+              return n;
+            }(i + 1, i + 1 + ahead);
+            wait_lgkmcnt(ahead + (VRD - 1) * ahead_v);
             __builtin_amdgcn_sched_barrier(0);
             f32x16* const Sn = st ? SB : SA;
             const f32x16* const Sc = st ? SA : SB;
@@ -1164,11 +1387,30 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
               if constexpr (j < KSTEPS) Sn[r] = mfma32(opr[i % RING], qf[r][j < KSTEPS ? j : 0], j == 0 ? negM[r] : Sn[r]);
-              else O[r][(j - KSTEPS) % DB] = mfma32(opr[i % RING], Pp[r][(j - KSTEPS) / DB], O[r][(j - KSTEPS) % DB]);
+              else O[r][(j - KSTEPS) % DB] = mfma32(NODES ? join_halves(vlo[i % RING], vhi[i % RING]) : opr[i % RING],
+                                                    Pp[r][(j - KSTEPS) / DB], O[r][(j - KSTEPS) % DB]);
             }
             if constexpr (st == 0 && (j == 1 || j == NS / 2 + 1)) {
               if (j == setup_slot && ti - tc < NSTAGE) {
-                if (iss_idx < is_nfast && ((iss_idx & 63) != 0 || iss_idx == 0)) {
+                if (NODES) {
+                  if (iss_idx < is_nfast && iss_idx * TN + TN <= run_end) {  // the whole tile lies in the cursor's run
+                    const uint32_t first = (uint32_t)(iss_idx * TN + run_d) * rowbytes;
+#pragma unroll
+                    for (int x = 0; x < IPK; ++x) {
+                      p_voff[x] = p_koff[x];
+                      p_koff[x] = first + roff_c[x];
+                    }
+                    p_ktile = is_kbase;
+                    p_vtile = v_saved;
+                    v_saved = is_vbase;
+                    p_kl = Kbase + (ti % NSTAGE) * KTILE + w * BLKK;
+                    p_vl = Vbase + ((ti + NSTAGE - 1) % NSTAGE) * VTILE + w * BLKV;
+                    iss_idx = iss_idx + 1;
+                    ti = ti + 1;
+                  } else {
+                    other = true;
+                  }
+                } else if (iss_idx < is_nfast && ((iss_idx & 63) != 0 || iss_idx == 0)) {
                   const uint32_t kt = (uint32_t)__builtin_amdgcn_readlane(col_iss, iss_idx & 63);
                   p_ktile = is_kbase + (uint64_t)kt * kt_kstride;
                   p_vtile = v_saved;  // (ti > 0 here: the first tile of the stream never runs through this loop)
@@ -1190,7 +1432,9 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
               static_for<0, LPT>([&](auto xc) __attribute__((always_inline)) {
                 constexpr int x = decltype(xc)::value;
                 if constexpr (x * NS / LPT + (NS / LPT > 1 ? 1 : 0) == j) {
-                  if constexpr (x < IPK) {
+                  if constexpr (NODES) {
+                    issue_part(x);
+                  } else if constexpr (x < IPK) {
                     const uint32_t off = PAGED ? x * 1024 + ksrc : __umul24((uint32_t)min(kvrow[x], p_last), rowbytes) + kchunk;  // (rows and row sizes are far below 2^24)
                     __builtin_amdgcn_global_load_lds((gbl_ptr_t)(p_ktile + off), (lds_ptr_t)(p_kl + x * NISS * BLKK), 16, 0, 0);
                   } else {
@@ -1338,7 +1582,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
     // everything in flight there) and after the wait of sync_next, which counts tile loads only.
     if (has_next) {
       load_q(nxt);
-      if (!PAGED) {
+      if (STREAM == STREAM_TILES) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) vis0[r] = a.node_vis[(int64_t)(nxt.nstart + rnode_nxt[r]) * a.W];
       }
@@ -1416,11 +1660,15 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       rnode[r] = rnode_nxt[r];
-      if (!PAGED && has_next) rnode_nxt[r] = a.tok_node[token_of(nxt, r)];
+      rdepth[r] = NODES ? rnode[r] - cur.ktb : 0;
+      if (!PAGED && has_next) rnode_nxt[r] = row_data(nxt, r);
     }
     if (iss_next) iss_next = 0;     // the cursor was already in what is now the current item
-    else cursor_enter(cur, col_nxt);  // (all tiles of the old item were issued: start of the new one)
-    if (has_next) col_nxt = load_cols(nxt, 0);
+    else cursor_enter(cur, col_nxt, delta_nxt);  // (all tiles of the old item were issued: start of the new one)
+    if (has_next) {
+      col_nxt = load_cols(nxt, 0);
+      delta_nxt = load_deltas(nxt);
+    }
     TSTAMP(t_sw);
     TACC(5, t_o, t_sw);
   }
@@ -1463,62 +1711,117 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
 #endif
 }
 
-// How a KV head's G query heads are divided: `narrow` heads in items of four heads x 64 rows (the
-// last item padded when narrow is no multiple of 4), `wide` heads one at a time on 256 rows.  A
-// padded item wastes (4 - narrow % 4) / 4 of its time, a 256-row tile takes the mask path in more
-// of its tiles and idles more at the end of a short sequence; every left-over head goes wide (three
-// of them measured against the padded item: 16 % less time on long fork-joins, the same on short
-// random DAGs).
-void split_heads(int g, int* narrow, int* wide) {
-  static const int force = [] {
-    const char* e = getenv("DAGATTN_WIDE_HEADS");  // development: 0 = never wide, 2 = one or two left-over heads only
-    return e ? atoi(e) : -1;
-  }();
-  const int rem = g % 4;
-  *wide = force == 0 ? 0 : (force == 2 && rem == 3) ? 0 : rem;
-  *narrow = g - *wide;
+template <int D, int HG, int NRG, bool PAGED>
+__global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a) {
+  prefill_body<D, HG, NRG, PAGED ? STREAM_PAGES : STREAM_TILES>(a);
+}
+template <int D, int HG, int NRG>
+__global__ void __launch_bounds__(64 * HG * NRG, 8 / (HG * NRG)) k_prefill_nodes(PrefillArgs a) {
+  prefill_body<D, HG, NRG, STREAM_NODES>(a);
 }
 
-template <int D, int HG, int NRG, bool PAGED = false>
+// How the launches divide a KV head's G query heads.
+//   four: heads in items of four heads x 64 rows;  two: a pair in an item of its own;
+//   one:  heads one at a time in items of 256 (on chunks at head dimension 64: 128) rows.
+// On the block map's tiles there are no pairs (three left-over heads go one at a time: 16 % less
+// time than padded to four on long fork-joins, the same on short random DAGs).
+struct HeadSplit {
+  int four, two, one;
+};
+HeadSplit split_heads(int g, bool chunks) {
+  const int rem = g % 4;
+  return chunks ? HeadSplit{g - rem, rem & 2, rem & 1} : HeadSplit{g - rem, 0, rem};
+}
+
+// Whether the query rows are cut at the borders of the nodes (k_node_rows) instead of every 64 tokens.
+// Short nodes leave most of a chunk's rows empty, and the more so the more rows a chunk has (256 for
+// the single left-over head of an odd group at head dimension 128): measured on random DAGs of 64
+// nodes, time on the block map's tiles : on chunks, for an average node of 8 / 16 / 32 / 48 / 144 tokens
+// (256 for chains of long nodes): 32 / 8 heads 0.80 / 1.10 / 1.40 / 1.66 / 1.35 / 1.21; 40 / 8 heads
+// 0.68 / 0.95 / 1.28 / 1.45 / 1.37 / 1.24; 8 / 8 heads 0.61 / 0.85 / 1.11 / 1.18 / 1.58 / 1.27; 16 / 8
+// heads of dimension 64: 1.17 / 1.72 / 2.15 / 2.65 / 2.30 / 1.89; long fork-joins 1.0 to 1.4.
+bool on_chunks(const PrefillArgs& a, int head_dim) {
+  if (!a.node_runs || a.total_tokens * a.hkv * (2 * head_dim) > UINT32_MAX) return false;  // (row offsets are 32-bit)
+  const int shortest = head_dim == 128 && a.hq / a.hkv % 2 == 1 ? 32 : 16;
+  return a.total_tokens >= shortest * a.total_nodes;
+}
+
+template <int D, int HG, int NRG, int STREAM>
 int launch_one(const PrefillArgs& a, long max_tiles, hipStream_t stream) {
-  constexpr int KPB = 64 / (D / 8);
-  constexpr size_t sm = (size_t)NSTAGE * ((TN / KPB) * (1024 + 16) + (D / 8) * (1024 + 128) + 256) + 16 +
+  constexpr int KPB = 64 / (D / 8), KTILE = TN / KPB * (1024 + 16), VTILE = STREAM == STREAM_NODES ? KTILE : D / 8 * (1024 + 128);
+  constexpr size_t sm = (size_t)NSTAGE * (KTILE + VTILE + (STREAM == STREAM_TILES ? 256 : 0)) + 16 +
                         (size_t)HG * NRG * 32 * (64 + 16);  // rings + node-id records + item mailbox + output pieces
-  if (hipFuncSetAttribute((const void*)k_prefill_bf16<D, HG, NRG, PAGED>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)sm) != hipSuccess)
-    return DAG_ERR_HIP;
+  constexpr int PER_CU = 8 / (HG * NRG);  // workgroups that share a compute unit
+  static_assert(PER_CU * sm <= 160 * 1024, "LDS of a compute unit");
+  void (*kernel)(PrefillArgs);
+  if constexpr (STREAM == STREAM_NODES) kernel = k_prefill_nodes<D, HG, NRG>;
+  else kernel = k_prefill_bf16<D, HG, NRG, STREAM == STREAM_PAGES>;
+  if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess) return DAG_ERR_HIP;
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return DAG_ERR_HIP;
-  const long n_items = max_tiles * a.hkv * ((a.heads + HG - 1) / HG);
-  const unsigned grid = (unsigned)(n_items < n_cu ? n_items : n_cu);
-  hipLaunchKernelGGL((k_prefill_bf16<D, HG, NRG, PAGED>), dim3(grid), dim3(64 * HG * NRG), sm, stream, a);
+  const long n_items = max_tiles * a.hkv * ((a.heads + HG - 1) / HG), n_wg = (long)n_cu * PER_CU;
+  const unsigned grid = (unsigned)(n_items < n_wg ? n_items : n_wg);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * HG * NRG), sm, stream, a);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
 
+// Heads head0 .. head0 + heads - 1 of every KV head on chunks of 32 NRG rows.
+template <int D, int HG, int NRG>
+int launch_chunks(const PrefillArgs& a, int head0, int heads, hipStream_t stream) {
+  constexpr int R = 32 * NRG, I = R == 64 ? 0 : R == 128 ? 1 : 2;
+  static_assert(DAG_CHUNK_ROWS[I] == R, "chunk tables");
+  PrefillArgs b = a;
+  b.head0 = head0;
+  b.heads = heads;
+  b.col = a.node_runs;
+  b.qtile_desc = a.chunk[I].desc;
+  b.n_tiles_dev = a.chunk[I].count;
+  return launch_one<D, HG, NRG, STREAM_NODES>(b, chunk_slots(a.total_tokens, a.total_nodes, R), stream);
+}
+
 template <int D>
 int launch_d(const PrefillArgs& a, hipStream_t stream) {
-  int narrow, wide;
-  split_heads(a.hq / a.hkv, &narrow, &wide);
-  if (narrow > 0) {  // eight waves = 2 row blocks x 4 query heads
+  const bool chunks = on_chunks(a, D);
+  const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
+  int rc = DAG_OK;
+  if (chunks) {  // (at head dimension 64 four waves with half the rings: two workgroups per compute unit)
+    if (h.four > 0) rc = launch_chunks<D, 4, 2>(a, 0, h.four, stream);
+    if (rc == DAG_OK && h.two > 0) rc = D == 128 ? launch_chunks<128, 2, 4>(a, h.four, h.two, stream) : launch_chunks<64, 2, 2>(a, h.four, h.two, stream);
+    if (rc == DAG_OK && h.one > 0) rc = D == 128 ? launch_chunks<128, 1, 8>(a, h.four + h.two, 1, stream) : launch_chunks<64, 1, 4>(a, h.four + h.two, 1, stream);
+    return rc;
+  }
+  if (h.four > 0) {  // eight waves = 2 row blocks x 4 query heads
     PrefillArgs b = a;
     b.head0 = 0;
-    b.heads = narrow;
-    const int rc = launch_one<D, 4, 2>(b, (long)a.total_qtiles, stream);
+    b.heads = h.four;
+    rc = launch_one<D, 4, 2, STREAM_TILES>(b, (long)a.total_qtiles, stream);
     if (rc != DAG_OK) return rc;
   }
-  if (wide > 0) {  // eight waves = 8 row blocks of one query head; starts when the launch above has ended
+  if (h.one > 0) {  // eight waves = 8 row blocks of one query head; starts when the launch above has ended
     PrefillArgs b = a;
-    b.head0 = narrow;
-    b.heads = wide;
+    b.head0 = h.four;
+    b.heads = h.one;
     b.col = a.wide_col;
     b.qtile_desc = a.wide_desc;
     b.n_tiles_dev = a.wide_count;
     // (every sequence has at most a quarter of its 64-row tiles, rounded up, as 256-row tiles)
-    return launch_one<D, 1, 8>(b, ((long)a.total_qtiles + 3) / 4 + a.n_seqs, stream);
+    rc = launch_one<D, 1, 8, STREAM_TILES>(b, ((long)a.total_qtiles + 3) / 4 + a.n_seqs, stream);
   }
+  return rc;
+}
+
+// The chunk tables of one chunk size: descriptors, then launch order (by descending tile count).
+int build_chunks(const PrefillArgs& a, int i, hipStream_t stream) {
+  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[i]);
+  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream, a.n_seqs, (int)a.total_nodes,
+                     DAG_CHUNK_ROWS[i], slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start, a.node_pos_start, a.node_vis, a.sched, a.node_runs,
+                     a.chunk[i]);
+  hipLaunchKernelGGL(k_wide_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, (int)slots, a.chunk[i].cnt,
+                     a.chunk[i].pre, a.chunk[i].desc, a.chunk[i].count);
+  DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
 
@@ -1526,12 +1829,18 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
 
 template <int D>
 int launch_prepare_v(const PrefillArgs& a, hipStream_t stream) {
+  const bool chunks = on_chunks(a, D);
+  const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
+  if (chunks) {  // V is read as it is
+    int rc = h.four > 0 || (h.two > 0 && D == 64) ? build_chunks(a, 0, stream) : DAG_OK;
+    if (rc == DAG_OK && ((h.two > 0 && D == 128) || (h.one > 0 && D == 64))) rc = build_chunks(a, 1, stream);
+    if (rc == DAG_OK && h.one > 0 && D == 128) rc = build_chunks(a, 2, stream);
+    return rc;
+  }
   hipLaunchKernelGGL((k_vt_prepare<D>), dim3((unsigned)a.total_ktiles, (unsigned)a.hkv), dim3(256), 0, stream,
                      (const uint16_t*)a.v, (uint16_t*)a.vt, a.ktile_start, a.cu_seqlens, a.n_seqs, a.hkv, a.sched);
   DAG_LAUNCH_CHECK();
-  int narrow, wide;
-  split_heads(a.hq / a.hkv, &narrow, &wide);
-  if (wide > 0) {
+  if (h.one > 0) {
     const unsigned nblk = (unsigned)((a.total_qtiles + 3) / 4);
     hipLaunchKernelGGL(k_wide_rows, dim3(nblk), dim3(256), 0, stream, a.n_seqs, (int)a.total_qtiles, a.qtile_start,
                        a.block_map_off, a.cu_seqlens, a.node_start, a.ktile_start, a.block_map, a.rowptr, a.wide_cnt,
@@ -1564,7 +1873,7 @@ int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t s
   b.qtile_desc = a.wide_desc;
   b.n_tiles_dev = a.wide_count;
   // (query heads in items of four, the last item padded)
-  return head_dim == 128 ? launch_one<128, 4, 2, true>(b, slots, stream) : launch_one<64, 4, 2, true>(b, slots, stream);
+  return head_dim == 128 ? launch_one<128, 4, 2, STREAM_PAGES>(b, slots, stream) : launch_one<64, 4, 2, STREAM_PAGES>(b, slots, stream);
 }
 
 int launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t stream) {

@@ -4,6 +4,19 @@
 
 constexpr int DAG_SCHED_INTS = 128;  // [0..63] item counters, [64] finished workgroups
 
+// Query chunks (k_node_rows): tables of the chunks of DAG_CHUNK_ROWS[i] rows.  A slot may hold a chunk;
+// the group of siblings that starts with node v (of the batch) and token t owns the slots from
+// t / rows + v on.
+constexpr int DAG_CHUNK_SIZES = 3;
+constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};
+struct ChunkTables {
+  int32_t* count;  // [1] number of chunks
+  int32_t* cnt;    // [slots] key tiles of the chunk, -1: no chunk here
+  int32_t* pre;    // [slots][8] its descriptor
+  int32_t* desc;   // [slots][8] descriptors in launch order
+};
+inline int64_t chunk_slots(int64_t total_tokens, int64_t total_nodes, int rows) { return total_tokens / rows + total_nodes; }
+
 struct PrefillArgs {
   const void* q;
   const void* k;
@@ -38,7 +51,21 @@ struct PrefillArgs {
   int32_t* wide_pre;    // [total_qtiles][8] descriptor of that row
   int32_t* wide_desc;   // [total_qtiles][8] descriptors in launch order (wide_count of them)
   int32_t* wide_col;    // [csr_capacity] key tiles of the rows, row of tile qt at rowptr[qt]
+  // bf16 path, workspace: what every node sees, as runs of consecutive tokens (see k_node_rows)
+  const int32_t *node_tok_start, *node_pos_start, *pos_ids;
+  int64_t total_tokens, total_nodes;
+  int32_t* node_runs;  // [total_nodes][64][2], null when the workspace has no room for them
+  ChunkTables chunk[DAG_CHUNK_SIZES];
 };
+
+// The node tables hold 64 runs per node, the most that 128 nodes can have.
+inline bool prefill_has_node_tables(int64_t total_nodes, int words_per_node) { return words_per_node <= 2 && total_nodes > 0; }
+inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes, int words_per_node) {
+  if (!prefill_has_node_tables(total_nodes, words_per_node)) return 0;
+  size_t n = (size_t)total_nodes * 128 * 4;
+  for (int i = 0; i < DAG_CHUNK_SIZES; ++i) n += (size_t)(64 + 17 * chunk_slots(total_tokens, total_nodes, DAG_CHUNK_ROWS[i])) * 4;
+  return n;
+}
 
 // Workspace of the bf16 path behind the transposed V: counters, then the tables above.
 inline size_t prefill_bf16_table_bytes(int64_t total_qtiles, int64_t csr_capacity) {
