@@ -1,6 +1,9 @@
 // dag_meta_sizes / dag_build_meta: node table + ancestor bitsets -> per-token node ids, adaptive
 // position ids (paper section 4.2), per-node visibility sets (Eq. 3 in ancestor-closure form),
 // tile-level block map (dense + CSR), launch order, visible-pair counts.  Integer work only.
+#include <string.h>
+
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -94,220 +97,168 @@ int host_validate_bits(const dag_desc_t* d) {
 }
 
 // ------------------------------------------------------------------------------------ kernels
-// One block: per-sequence token counts and the three prefix sums over sequences; zeroes the
-// per-row tile counts that k_blockmap adds up.
-__device__ void seq_block(int n_seqs, const int32_t* node_off, const int32_t* node_len, int tile_m, int tile_n,
-                          int32_t* cu_seqlens, int32_t* qtile_start, int64_t* block_map_off, int32_t* node_start,
-                          int32_t* ktile_start, int32_t* cnt, int total_qtiles) {
-  for (int i = threadIdx.x; i < total_qtiles; i += blockDim.x) cnt[i] = 0;
+// A node table of at most kArgWords words travels as a kernel argument: three copies from pageable memory
+// cost 3 to 5 us of the stream each, an argument nothing.  (The limit keeps the arguments under 4 KB.)
+// Words: node_offsets [n_seqs + 1], padded to an even count, then ancestor bitsets, then lengths.
+constexpr int kArgWords = 896;
+struct NodeTable {
+  uint32_t w[kArgWords];
+};
+struct NoTable {};
+
+struct MetaOut {  // what the kernels write, see dag_meta_t
+  int32_t *cu_seqlens, *node_start, *qtile_start, *ktile_start;
+  int64_t* block_map_off;
+  int32_t *tok_node, *pos_ids, *node_tok_start, *node_pos_start;
+  uint64_t* node_vis;
+  uint8_t* block_map;
+  int32_t *rowptr, *col;
+  uint8_t* flag;
+  int32_t *nfull, *order, *desc;
+  int64_t* useful_pairs;
+};
+
+__device__ __forceinline__ int wave_sum(int x) {
+  for (int off = 32; off; off >>= 1) x += __shfl_xor(x, off);
+  return x;
+}
+
+// Whole block: per-sequence token counts and the prefix sums over sequences, a wave per sequence, then a scan
+// over 64 sequences at a time.
+__device__ __forceinline__ void seq_sums(int n_seqs, const int32_t* node_off, const int32_t* node_len, int tile_m, int tile_n,
+                                         int32_t* cu_seqlens, int32_t* qtile_start, int64_t* block_map_off,
+                                         int32_t* node_start, int32_t* ktile_start) {
+  const int lane = threadIdx.x & 63;
   for (int b = threadIdx.x; b <= n_seqs; b += blockDim.x) node_start[b] = node_off[b];
-  for (int b = threadIdx.x; b < n_seqs; b += blockDim.x) {
+  for (int b = threadIdx.x >> 6; b < n_seqs; b += blockDim.x >> 6) {
     int t = 0;
-    for (int v = node_off[b]; v < node_off[b + 1]; ++v) t += node_len[v];
-    cu_seqlens[b + 1] = t;  // turned into a prefix sum below
+    for (int v = node_off[b] + lane; v < node_off[b + 1]; v += 64) t += node_len[v];
+    t = wave_sum(t);
+    if (lane == 0) cu_seqlens[b + 1] = t;  // turned into a prefix sum below
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int cu = 0, qs = 0, ks = 0;
-    int64_t mo = 0;
+  if (threadIdx.x >= 64) return;
+  int cu = 0, qs = 0, ks = 0;
+  int64_t mo = 0;
+  if (lane == 0) {
     cu_seqlens[0] = 0;
     qtile_start[0] = 0;
     ktile_start[0] = 0;
     block_map_off[0] = 0;
-    for (int b = 0; b < n_seqs; ++b) {
-      int t = cu_seqlens[b + 1];
-      int qt = (t + tile_m - 1) / tile_m, kt = (t + tile_n - 1) / tile_n;
-      cu += t;
-      qs += qt;
-      ks += kt;
-      mo += (int64_t)qt * kt;
-      cu_seqlens[b + 1] = cu;
-      qtile_start[b + 1] = qs;
-      ktile_start[b + 1] = ks;
-      block_map_off[b + 1] = mo;
+  }
+  for (int b0 = 0; b0 < n_seqs; b0 += 64) {
+    const int b = b0 + lane;
+    int t = b < n_seqs ? cu_seqlens[b + 1] : 0;
+    int qt = (t + tile_m - 1) / tile_m, kt = (t + tile_n - 1) / tile_n;
+    long long m = (long long)qt * kt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int yt = __shfl_up(t, off), yq = __shfl_up(qt, off), yk = __shfl_up(kt, off);
+      const long long ym = __shfl_up(m, off);
+      if (lane >= off) {
+        t += yt;
+        qt += yq;
+        kt += yk;
+        m += ym;
+      }
     }
+    if (b < n_seqs) {
+      cu_seqlens[b + 1] = cu + t;
+      qtile_start[b + 1] = qs + qt;
+      ktile_start[b + 1] = ks + kt;
+      block_map_off[b + 1] = mo + m;
+    }
+    cu += __shfl(t, 63);
+    qs += __shfl(qt, 63);
+    ks += __shfl(kt, 63);
+    mo += __shfl(m, 63);
   }
 }
 
-// One wave per sequence: node token starts (scan), visibility sets, adaptive position starts
-// (section 4.2: 0 without ancestors, else one past the largest ancestor position), pair counts.
-// One more block (the last) does the per-sequence sums of seq_block.
-__global__ void __launch_bounds__(64) k_seq_node(int n_seqs, const int32_t* node_off, const int32_t* node_len,
-                                                 const uint64_t* anc, int W, int tile_m, int tile_n,
-                                                 int32_t* cu_seqlens, int32_t* qtile_start, int64_t* block_map_off,
-                                                 int32_t* node_start, int32_t* ktile_start, int32_t* cnt,
-                                                 int total_qtiles, int32_t* node_tok_start,
-                                                 int32_t* node_pos_start, uint64_t* node_vis,
-                                                 int64_t* useful_pairs, int anc_in_lds) {
-  extern __shared__ uint64_t s_anc[];  // [n][W] ancestor words of the sequence, then int32 [n] + [n] below
-  if ((int)blockIdx.x == n_seqs) {
-    seq_block(n_seqs, node_off, node_len, tile_m, tile_n, cu_seqlens, qtile_start, block_map_off, node_start,
-              ktile_start, cnt, total_qtiles);
-    return;
-  }
-  const int b = blockIdx.x, lane = threadIdx.x;
-  const int n0 = node_off[b], n = node_off[b + 1] - n0;
-  // (the copy of the ancestor words is skipped for node tables too large for LDS; the walk below
-  // then reads them from global memory, one dependent load per node)
-  int32_t* s_pos_end = (int32_t*)(s_anc + (anc_in_lds ? (size_t)n * W : 0));  // [n] last position used by each node
-  int32_t* s_len = s_pos_end + n;                                              // [n]
-  const uint64_t* anc_rows = anc_in_lds ? s_anc : anc + (int64_t)n0 * W;
-  if (anc_in_lds)
-    for (int i = lane; i < n * W; i += 64) s_anc[i] = anc[(int64_t)n0 * W + i];
+// Adaptive positions of one sequence (section 4.2: 0 without ancestors, else one past the largest ancestor
+// position), token starts of its nodes and the number of visible pairs; one wave.  A lane holds node c + lane
+// and what its ancestors in front have told it so far; the 64 nodes of a step are settled in order, each
+// passing its last position and length on to the lanes that have it as an ancestor.  (Gathering at
+// every node with a reduction over the lanes took 0.6 us a node: k_seq_node 41 us for 8 sequences of 64
+// nodes, 9 us this way.)
+__device__ __forceinline__ int64_t node_walk(int n, int W, const int32_t* len, const uint64_t* anc, int32_t* pos_end,
+                                             int32_t* tok_start, int32_t* pos_start) {
+  const int lane = threadIdx.x & 63;
   int run = 0;
+  long long pairs = 0;
   for (int c = 0; c < n; c += 64) {
-    int v = c + lane;
-    int x = v < n ? node_len[n0 + v] : 0;
+    const int v = c + lane;
+    const int x = v < n ? len[v] : 0;
     int incl = x;
     for (int off = 1; off < 64; off <<= 1) {
-      int y = __shfl_up(incl, off);
+      const int y = __shfl_up(incl, off);
       if (lane >= off) incl += y;
     }
-    if (v < n) {
-      node_tok_start[n0 + v] = run + incl - x;
-      s_len[v] = x;
-    }
+    if (v < n) tok_start[v] = run + incl - x;
     run += __shfl(incl, 63);
-  }
-  for (int v = lane; v < n; v += 64)
-    for (int w = 0; w < W; ++w) {
-      uint64_t bits = anc[(int64_t)(n0 + v) * W + w];  // (this lane's own row: no need to wait for the LDS copy)
-      if ((v >> 6) == w) bits |= 1ull << (v & 63);
-      node_vis[(int64_t)(n0 + v) * W + w] = bits;
-    }
-  __syncthreads();
-  long long pairs = 0;
-  for (int v = 0; v < n; ++v) {
-    int best = -1;          // largest ancestor end position seen by this lane
-    long long anc_tokens = 0;
-    for (int w = 0; w * 64 <= v; ++w) {
-      uint64_t bits = anc_rows[(size_t)v * W + w];
-      int u = w * 64 + lane;
-      if (u < v && ((bits >> lane) & 1)) {
-        int e = s_pos_end[u];
-        best = e > best ? e : best;
-        anc_tokens += s_len[u];
+    int best = -1;  // largest ancestor end position seen so far
+    long long tokens = 0;
+    for (int w = 0; w < c / 64; ++w) {
+      const uint64_t bits = v < n ? anc[(size_t)v * W + w] : 0;
+      for (int j = 0; j < 64; ++j) {
+        const int e = pos_end[w * 64 + j], l = len[w * 64 + j];
+        const bool yes = (bits >> j) & 1;
+        best = yes && e > best ? e : best;
+        tokens += yes ? l : 0;
       }
     }
-    for (int off = 32; off >= 1; off >>= 1) {
-      int o = __shfl_xor(best, off);
-      best = o > best ? o : best;
-      anc_tokens += __shfl_xor(anc_tokens, off);
+    const uint64_t own = v < n ? anc[(size_t)v * W + c / 64] & ((1ull << lane) - 1) : 0;
+    const int m = min(64, n - c);
+    for (int j = 0; j < m; ++j) {
+      const int l = __builtin_amdgcn_readlane(x, j), e = __builtin_amdgcn_readlane(best, j) + l;
+      const bool yes = (own >> j) & 1;
+      best = yes && e > best ? e : best;
+      tokens += yes ? l : 0;
     }
-    const int start = best + 1;  // -1 + 1 = 0 for a node without ancestors
-    const int len = s_len[v];
-    if (lane == 0) {
-      node_pos_start[n0 + v] = start;
-      s_pos_end[v] = start + len - 1;
-      pairs += (long long)len * anc_tokens + (long long)len * (len + 1) / 2;
+    if (v < n) {
+      pos_start[v] = best + 1;
+      pos_end[v] = best + x;
+      pairs += (long long)x * tokens + (long long)x * (x + 1) / 2;
     }
-    __syncthreads();
+    __threadfence_block();
   }
-  if (lane == 0) useful_pairs[b] = pairs;
+  for (int off = 32; off; off >>= 1) pairs += __shfl_xor(pairs, off);
+  return pairs;
 }
 
-// One block per node: expand to tokens.
-__global__ void k_tokens(int n_seqs, const int32_t* node_off, const int32_t* node_len,
-                         const int32_t* cu_seqlens, const int32_t* node_tok_start,
-                         const int32_t* node_pos_start, int32_t* tok_node, int32_t* pos_ids) {
-  const int gv = blockIdx.x;
-  const int b = dag_find_segment(node_off, n_seqs, gv);
-  const int v = gv - node_off[b];
-  const int base = cu_seqlens[b] + node_tok_start[gv];
-  const int p0 = node_pos_start[gv], len = node_len[gv];
-  for (int o = threadIdx.x; o < len; o += blockDim.x) {
-    tok_node[base + o] = v;
-    pos_ids[base + o] = p0 + o;
-  }
-}
-
-// One thread per (query tile, key tile): exact count of visible pairs among the in-range pairs
-// => SKIP / PARTIAL / FULL.  Also adds up the non-skip tiles of every query tile's row (cnt, zeroed
-// before): tiles are numbered row after row, so a block touches at most blockDim.x consecutive
-// rows; it counts them in LDS and adds each row's share to cnt once.
-__global__ void __launch_bounds__(256) k_blockmap(int n_seqs, int64_t total_tiles, const int64_t* block_map_off,
-                                                  const int32_t* cu_seqlens, const int32_t* node_off,
-                                                  const int32_t* tok_node, const int32_t* node_tok_start,
-                                                  const uint64_t* node_vis, int W, int tile_m, int tile_n,
-                                                  const int32_t* qtile_start, uint8_t* block_map, int32_t* cnt) {
-  __shared__ int s_rows[256];
-  __shared__ int s_first;
-  s_rows[threadIdx.x] = 0;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = idx < total_tiles;
-  int gq = 0;  // query tile (row of the block map) over the whole batch
-  uint8_t state = DAG_TILE_SKIP;
-  if (valid) {
-    const int b = dag_find_segment(block_map_off, n_seqs, idx);
-    const int T = cu_seqlens[b + 1] - cu_seqlens[b];
-    const int KT = (T + tile_n - 1) / tile_n;
-    const int64_t loc = idx - block_map_off[b];
-    const int a = (int)(loc / KT), kb = (int)(loc % KT);
-    gq = qtile_start[b] + a;
-    const int i0 = a * tile_m, i1 = min(T, i0 + tile_m);
-    const int j0 = kb * tile_n, j1 = min(T, j0 + tile_n);
-    if (j0 <= i1 - 1) {  // else entirely in the future of every row
-      const int32_t* tn = tok_node + cu_seqlens[b];
-      const int n0 = node_off[b];
-      const int nn = node_off[b + 1] - n0;
-      const int u_lo = tn[i0], u_hi = tn[i1 - 1], w_lo = tn[j0], w_hi = tn[j1 - 1];
-      long long allowed = 0;
-      for (int u = u_lo; u <= u_hi; ++u) {
-        const int us = node_tok_start[n0 + u];
-        const int ue = (u + 1 < nn) ? node_tok_start[n0 + u + 1] : T;
-        const int r0 = max(i0, us), r1 = min(i1, ue);
-        for (int w = w_lo; w <= w_hi && w <= u; ++w) {
-          const int ws = node_tok_start[n0 + w];
-          const int we = (w + 1 < nn) ? node_tok_start[n0 + w + 1] : T;
-          const int c0 = max(j0, ws), c1 = min(j1, we);
-          if (w == u) {
-            for (int i = r0; i < r1; ++i) {  // causal inside the node
-              int c = min(i + 1, c1) - c0;
-              if (c > 0) allowed += c;
-            }
-          } else if ((node_vis[(int64_t)(n0 + u) * W + (w >> 6)] >> (w & 63)) & 1) {
-            allowed += (long long)(r1 - r0) * (c1 - c0);
-          }
-        }
-      }
-      const long long total = (long long)(i1 - i0) * (j1 - j0);
-      state = allowed == 0 ? DAG_TILE_SKIP : (allowed == total ? DAG_TILE_FULL : DAG_TILE_PARTIAL);
+// Visible pairs among the rows i0 .. i1 - 1 and keys j0 .. j1 - 1 of a sequence => SKIP / PARTIAL / FULL.
+// The pairs of nodes are shared by `lanes` (a power of two) neighbouring lanes, of which this is number sub.
+__device__ __forceinline__ uint8_t tile_state(int T, int n, const int32_t* tok_start, const uint64_t* vis, int W, int i0,
+                                              int i1, int j0, int j1, int sub = 0, int lanes = 1) {
+  if (j0 > i1 - 1) return DAG_TILE_SKIP;  // entirely in the future of every row
+  const int u_lo = dag_find_segment(tok_start, n, i0), u_hi = dag_find_segment(tok_start, n, i1 - 1);
+  const int w_lo = dag_find_segment(tok_start, n, j0), w_hi = dag_find_segment(tok_start, n, j1 - 1);
+  int allowed = 0;  // (at most 1024 x 1024)
+  const int nw = w_hi - w_lo + 1;
+  int u = u_lo, w = w_lo + sub;
+  while (true) {
+    while (w > w_hi && u <= u_hi) {
+      w -= nw;
+      ++u;
     }
-    block_map[idx] = state;
-  }
-  if (threadIdx.x == 0) s_first = gq;  // thread 0 is always valid (the grid covers total_tiles)
-  __syncthreads();
-  if (state != DAG_TILE_SKIP) atomicAdd(&s_rows[gq - s_first], 1);
-  __syncthreads();
-  if (s_rows[threadIdx.x] != 0) atomicAdd(cnt + s_first + threadIdx.x, s_rows[threadIdx.x]);
-}
-
-// One block: exclusive scan of the per-row counts (only used for a batch without tokens).
-__global__ void __launch_bounds__(1024) k_csr_scan(int total_qtiles, const int32_t* cnt, int32_t* rowptr) {
-  __shared__ int s[1024];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int c0 = 0; c0 < total_qtiles; c0 += 1024) {
-    int i = c0 + threadIdx.x;
-    int x = i < total_qtiles ? cnt[i] : 0;
-    s[threadIdx.x] = x;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      int y = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-      __syncthreads();
-      s[threadIdx.x] += y;
-      __syncthreads();
+    if (u > u_hi) break;
+    const int ue = u + 1 < n ? tok_start[u + 1] : T, we = w + 1 < n ? tok_start[w + 1] : T;
+    const int r0 = max(i0, tok_start[u]), r1 = min(i1, ue);
+    const int c0 = max(j0, tok_start[w]), c1 = min(j1, we);
+    if (w == u) {  // causal inside the node: row i sees min(i + 1, c1) - c0 keys
+      const int a = max(r0, c0), e = min(r1, c1);
+      if (e > a) allowed += (e - a) * ((a + 1 - c0) + (e - c0)) / 2;
+      const int past = max(a, c1);
+      if (r1 > past && c1 > c0) allowed += (r1 - past) * (c1 - c0);
+    } else if (w < u && ((vis[(int64_t)u * W + (w >> 6)] >> (w & 63)) & 1)) {
+      allowed += (r1 - r0) * (c1 - c0);
     }
-    if (i < total_qtiles) rowptr[i] = carry + s[threadIdx.x] - x;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += s[1023];
-    __syncthreads();
+    w += lanes;
   }
-  if (threadIdx.x == 0) rowptr[total_qtiles] = carry;
+  for (int off = lanes / 2; off; off >>= 1) allowed += __shfl_xor(allowed, off);
+  return allowed == 0 ? DAG_TILE_SKIP : allowed == (i1 - i0) * (j1 - j0) ? DAG_TILE_FULL : DAG_TILE_PARTIAL;
 }
 
-// One wave per query tile, given the number of non-skip tiles of every row (cnt):
+// One wave, for query tile qt, given the number of non-skip tiles of every row (cnt):
 //  * CSR row start = sum of the counts in front of it, and launch slot = number of query tiles in
 //    front of it in the order (tile count descending, index ascending), both from one pass over
 //    cnt shared by the lanes.  The prefill kernel hands the launch list out dynamically, and with
@@ -318,26 +269,20 @@ __global__ void __launch_bounds__(1024) k_csr_scan(int total_qtiles, const int32
 //    query tile, in 32 bytes {token offset of the sequence, tokens in the sequence, first row of
 //    the tile, CSR row start, tiles in the row, tiles that need no mask, node offset of the
 //    sequence, first key tile of the sequence}.
-__global__ void __launch_bounds__(256) k_csr_order_desc(int n_seqs, int total_qtiles, int tile_m, int tile_n,
-                                                        const int32_t* cnt, const int32_t* qtile_start,
-                                                        const int64_t* block_map_off, const int32_t* cu_seqlens,
-                                                        const int32_t* node_start, const int32_t* ktile_start,
-                                                        const uint8_t* block_map, int32_t* rowptr, int32_t* col,
-                                                        uint8_t* flag, int32_t* nfull, int32_t* order,
-                                                        int32_t* desc) {
-  const int qt = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (qt >= total_qtiles) return;
+__device__ __forceinline__ void csr_row(int qt, int n_seqs, int total_qtiles, int tile_m, int tile_n, const int32_t* cnt,
+                                        const int32_t* qtile_start, const int64_t* block_map_off, const int32_t* cu_seqlens,
+                                        const int32_t* node_start, const int32_t* ktile_start, const uint8_t* block_map,
+                                        const MetaOut& o) {
+  const int lane = threadIdx.x & 63;
   const int mine = cnt[qt];
   int oi = 0, c0 = 0;
   for (int j = lane; j < total_qtiles; j += 64) {
-    const int o = cnt[j];
-    oi += (o > mine) || (o == mine && j < qt);
-    c0 += j < qt ? o : 0;
+    const int x = cnt[j];
+    oi += (x > mine) || (x == mine && j < qt);
+    c0 += j < qt ? x : 0;
   }
-  for (int off = 32; off; off >>= 1) {
-    oi += __shfl_xor(oi, off);
-    c0 += __shfl_xor(c0, off);
-  }
+  oi = wave_sum(oi);
+  c0 = wave_sum(c0);
   const int b = dag_find_segment(qtile_start, n_seqs, qt);
   const int T = cu_seqlens[b + 1] - cu_seqlens[b];
   const int KT = (T + tile_n - 1) / tile_n;
@@ -351,8 +296,8 @@ __global__ void __launch_bounds__(256) k_csr_order_desc(int n_seqs, int total_qt
       const uint64_t m = __ballot(f == want);
       if (f == want) {
         const int p = out + __popcll(m & ((1ull << lane) - 1));
-        col[p] = k;
-        flag[p] = f;
+        o.col[p] = k;
+        o.flag[p] = f;
       }
       out += __popcll(m);
       if (pass == 0 && m) last_full = k0 + 63 - __builtin_clzll(m);
@@ -360,12 +305,12 @@ __global__ void __launch_bounds__(256) k_csr_order_desc(int n_seqs, int total_qt
     if (pass == 0) nf = out - c0;
   }
   if (lane != 0) return;
-  rowptr[qt] = c0;
-  if (qt == total_qtiles - 1) rowptr[total_qtiles] = c0 + mine;
-  nfull[qt] = nf;
-  order[oi] = qt;
+  o.rowptr[qt] = c0;
+  if (qt == total_qtiles - 1) o.rowptr[total_qtiles] = c0 + mine;
+  o.nfull[qt] = nf;
+  o.order[oi] = qt;
   if (nf > 0 && (last_full + 1) * tile_n > T) --nf;  // a ragged last key tile needs the mask path
-  int32_t* d = desc + (int64_t)oi * 8;
+  int32_t* d = o.desc + (int64_t)oi * 8;
   d[0] = cu_seqlens[b];
   d[1] = T;
   d[2] = (qt - qtile_start[b]) * tile_m;
@@ -374,6 +319,166 @@ __global__ void __launch_bounds__(256) k_csr_order_desc(int n_seqs, int total_qt
   d[5] = nf;
   d[6] = node_start[b];
   d[7] = ktile_start[b];
+}
+
+// One block per sequence: the tables of its nodes.  One more block (the last) does the sums over
+// sequences and zeroes the per-row tile counts that k_tiles adds up.
+template <typename Table>
+__global__ void __launch_bounds__(256) k_seq_node(int n_seqs, Table table, const int32_t* node_off, const int32_t* node_len,
+                                                  const uint64_t* anc, int W, int tile_m, int tile_n, MetaOut o,
+                                                  int32_t* cnt, int total_qtiles, int anc_in_lds) {
+  extern __shared__ uint64_t s_anc[];  // [n][W] ancestor words of the sequence, then int32 [n] + [n] below
+  if constexpr (std::is_same<Table, NodeTable>::value) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_table[kArgWords];
+    for (int i = threadIdx.x; i < kArgWords; i += 256) s_table[i] = table.w[i];
+    __syncthreads();
+    node_off = (const int32_t*)s_table;
+    anc = (const uint64_t*)(s_table + ((n_seqs + 2) & ~1));
+    node_len = (const int32_t*)(anc + (int64_t)node_off[n_seqs] * W);
+  }
+  if ((int)blockIdx.x == n_seqs) {
+    for (int i = threadIdx.x; i < total_qtiles; i += 256) cnt[i] = 0;
+    if (total_qtiles == 0 && threadIdx.x == 0) o.rowptr[0] = 0;
+    seq_sums(n_seqs, node_off, node_len, tile_m, tile_n, o.cu_seqlens, o.qtile_start, o.block_map_off, o.node_start,
+             o.ktile_start);
+    return;
+  }
+  const int b = blockIdx.x;
+  const int n0 = node_off[b], n = node_off[b + 1] - n0;
+  // (the copy of the ancestor words is skipped for node tables too large for LDS; the walk below
+  // then reads them from global memory)
+  int32_t* s_pos_end = (int32_t*)(s_anc + (anc_in_lds ? (size_t)n * W : 0));  // [n] last position used by each node
+  int32_t* s_len = s_pos_end + n;                                              // [n]
+  for (int v = threadIdx.x; v < n; v += 256) s_len[v] = node_len[n0 + v];
+  for (int i = threadIdx.x; i < n * W; i += 256) {
+    const uint64_t bits = anc[(int64_t)n0 * W + i];
+    const int v = i / W, w = i % W;
+    if (anc_in_lds) s_anc[i] = bits;
+    o.node_vis[(int64_t)n0 * W + i] = bits | (v >> 6 == w ? 1ull << (v & 63) : 0ull);
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int64_t pairs = node_walk(n, W, s_len, anc_in_lds ? s_anc : anc + (int64_t)n0 * W, s_pos_end,
+                                  o.node_tok_start + n0, o.node_pos_start + n0);
+  if (threadIdx.x == 0) o.useful_pairs[b] = pairs;
+}
+
+// The first blocks: one thread per (query tile, key tile), its state in the block map.  Also adds up the
+// non-skip tiles of every query tile's row (cnt, zeroed before): tiles are numbered row after row, so
+// a block touches at most blockDim.x consecutive rows; it counts them in LDS and adds each row's
+// share to cnt once.  The remaining blocks, 1024 tokens each: node and position of every token.
+__global__ void __launch_bounds__(256) k_tiles(int n_seqs, int64_t total_tiles, int tile_blocks, int total_tokens, int W,
+                                               int tile_m, int tile_n, MetaOut o, int32_t* cnt) {
+  if ((int)blockIdx.x >= tile_blocks) {
+    const int t0 = (blockIdx.x - tile_blocks) * 1024;
+    for (int t = t0 + threadIdx.x; t < min(t0 + 1024, total_tokens); t += 256) {
+      const int b = dag_find_segment(o.cu_seqlens, n_seqs, t);
+      const int n0 = o.node_start[b], i = t - o.cu_seqlens[b];
+      const int v = dag_find_segment(o.node_tok_start + n0, o.node_start[b + 1] - n0, i);
+      o.tok_node[t] = v;
+      o.pos_ids[t] = o.node_pos_start[n0 + v] + i - o.node_tok_start[n0 + v];
+    }
+    return;
+  }
+  __shared__ int s_rows[256];
+  __shared__ int s_first;
+  s_rows[threadIdx.x] = 0;
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int gq = 0;  // query tile (row of the block map) over the whole batch
+  uint8_t state = DAG_TILE_SKIP;
+  if (idx < total_tiles) {
+    const int b = dag_find_segment(o.block_map_off, n_seqs, idx);
+    const int T = o.cu_seqlens[b + 1] - o.cu_seqlens[b];
+    const int KT = (T + tile_n - 1) / tile_n;
+    const int64_t loc = idx - o.block_map_off[b];
+    const int a = (int)(loc / KT), kb = (int)(loc % KT);
+    gq = o.qtile_start[b] + a;
+    const int n0 = o.node_start[b];
+    state = tile_state(T, o.node_start[b + 1] - n0, o.node_tok_start + n0, o.node_vis + (int64_t)n0 * W, W, a * tile_m,
+                       min(T, (a + 1) * tile_m), kb * tile_n, min(T, (kb + 1) * tile_n));
+    o.block_map[idx] = state;
+  }
+  if (threadIdx.x == 0) s_first = gq;  // thread 0 is always valid (the grid covers total_tiles)
+  __syncthreads();
+  if (state != DAG_TILE_SKIP) atomicAdd(&s_rows[gq - s_first], 1);
+  __syncthreads();
+  if (s_rows[threadIdx.x] != 0) atomicAdd(cnt + s_first + threadIdx.x, s_rows[threadIdx.x]);
+}
+
+__global__ void __launch_bounds__(256) k_csr_order_desc(int n_seqs, int total_qtiles, int tile_m, int tile_n,
+                                                        const int32_t* cnt, MetaOut o) {
+  const int qt = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (qt >= total_qtiles) return;
+  csr_row(qt, n_seqs, total_qtiles, tile_m, tile_n, cnt, o.qtile_start, o.block_map_off, o.cu_seqlens, o.node_start,
+          o.ktile_start, o.block_map, o);
+}
+
+// Small batches: everything above in one workgroup, the intermediate tables in LDS.  Three copies and four
+// launches are all latency there: 8 nodes of 600 tokens took 30 us, this kernel takes 8.  At its limits it
+// is still the faster one (8 / 64 nodes, 2048 tokens: 10 / 16 us, the launches above 14 / 19 us); with twice
+// the rows it was not (19 against 14 us), a wave taking four rows of the CSR one after another.
+constexpr int kSmallTiles = 1024, kSmallRows = 32, kSmallTokens = 2048, kSmallSeqs = 64;
+__global__ void __launch_bounds__(1024) k_meta_small(int n_seqs, NodeTable table, int W, int tile_m, int tile_n, MetaOut o,
+                                                     int total_tiles, int total_qtiles, int total_tokens) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_table[kArgWords];
+  __shared__ int32_t s_tok[kArgWords / 3], s_pos[kArgWords / 3], s_end[kArgWords / 3];
+  __shared__ int32_t s_cu[kSmallSeqs + 1], s_node[kSmallSeqs + 1], s_qs[kSmallSeqs + 1], s_ks[kSmallSeqs + 1];
+  __shared__ int64_t s_mo[kSmallSeqs + 1];
+  __shared__ int s_cnt[kSmallRows];
+  __shared__ uint8_t s_map[kSmallTiles];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < kArgWords) s_table[tid] = table.w[tid];
+  if (tid < kSmallRows) s_cnt[tid] = 0;
+  __syncthreads();
+  const int32_t* off = (const int32_t*)s_table;
+  uint64_t* anc = (uint64_t*)(s_table + ((n_seqs + 2) & ~1));
+  const int32_t* len = (const int32_t*)(anc + (int64_t)off[n_seqs] * W);
+  const int nodes = off[n_seqs];
+  for (int b = wave; b < n_seqs; b += 16) {
+    const int n0 = off[b];
+    const int64_t pairs = node_walk(off[b + 1] - n0, W, len + n0, anc + (int64_t)n0 * W, s_end + n0, s_tok + n0, s_pos + n0);
+    if (lane == 0) o.useful_pairs[b] = pairs;
+  }
+  seq_sums(n_seqs, off, len, tile_m, tile_n, s_cu, s_qs, s_mo, s_node, s_ks);  // (its barrier is also the walk's)
+  for (int b = wave; b < n_seqs; b += 16)  // a node sees itself
+    for (int v = lane; v < off[b + 1] - off[b]; v += 64) anc[(int64_t)(off[b] + v) * W + (v >> 6)] |= 1ull << (v & 63);
+  __syncthreads();
+  for (int b = tid; b <= n_seqs; b += 1024) {
+    o.cu_seqlens[b] = s_cu[b];
+    o.node_start[b] = s_node[b];
+    o.qtile_start[b] = s_qs[b];
+    o.ktile_start[b] = s_ks[b];
+    o.block_map_off[b] = s_mo[b];
+  }
+  for (int i = tid; i < nodes * W; i += 1024) o.node_vis[i] = anc[i];
+  for (int v = tid; v < nodes; v += 1024) {
+    o.node_tok_start[v] = s_tok[v];
+    o.node_pos_start[v] = s_pos[v];
+  }
+  int lanes = 1;  // of a tile: few tiles with many short nodes are shared by several lanes
+  while (lanes < 64 && 2 * lanes * total_tiles <= 1024) lanes *= 2;
+  const int sub = tid & (lanes - 1);
+  for (int idx = tid / lanes; idx < total_tiles; idx += 1024 / lanes) {
+    const int b = dag_find_segment(s_mo, n_seqs, (int64_t)idx);
+    const int T = s_cu[b + 1] - s_cu[b], KT = (T + tile_n - 1) / tile_n, loc = idx - (int)s_mo[b];
+    const int a = loc / KT, kb = loc % KT, n0 = s_node[b];
+    const uint8_t state = tile_state(T, s_node[b + 1] - n0, s_tok + n0, anc + (int64_t)n0 * W, W, a * tile_m,
+                                     min(T, (a + 1) * tile_m), kb * tile_n, min(T, (kb + 1) * tile_n), sub, lanes);
+    if (sub != 0) continue;
+    s_map[idx] = state;
+    o.block_map[idx] = state;
+    if (state != DAG_TILE_SKIP) atomicAdd(&s_cnt[s_qs[b] + a], 1);
+  }
+  for (int t = tid; t < total_tokens; t += 1024) {
+    const int b = dag_find_segment(s_cu, n_seqs, t);
+    const int n0 = s_node[b], i = t - s_cu[b];
+    const int v = dag_find_segment(s_tok + n0, s_node[b + 1] - n0, i);
+    o.tok_node[t] = v;
+    o.pos_ids[t] = s_pos[n0 + v] + i - s_tok[n0 + v];
+  }
+  __syncthreads();
+  for (int qt = wave; qt < total_qtiles; qt += 16)
+    csr_row(qt, n_seqs, total_qtiles, tile_m, tile_n, s_cnt, s_qs, s_mo, s_cu, s_node, s_ks, s_map, o);
 }
 
 }  // namespace
@@ -424,6 +529,33 @@ extern "C" int dag_build_meta(const dag_desc_t* d, const dag_meta_t* m, void* ws
 
   hipStream_t stream = (hipStream_t)stream_;
   const int W = d->words_per_node;
+  const MetaOut o = {m->cu_seqlens, m->node_start, m->qtile_start, m->ktile_start, m->block_map_off, m->tok_node,
+                     m->pos_ids, m->node_tok_start, m->node_pos_start, m->node_vis, m->block_map, m->qtile_rowptr,
+                     m->qtile_col, m->qtile_flag, m->qtile_nfull, m->qtile_order, m->qtile_desc, m->useful_pairs};
+  const int QT = (int)s.total_qtiles;
+  // A capturing stream records the copies: its replays read the caller's arrays anew.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+  const size_t words = (size_t)((d->n_seqs + 2) & ~1) + (size_t)s.total_nodes * (2 * W + 1);
+  const bool as_arg = words <= kArgWords && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+                      capture == hipStreamCaptureStatusNone;
+  NodeTable table;
+  if (as_arg) {
+    uint32_t* w = table.w;
+    memcpy(w, d->node_offsets, (size_t)(d->n_seqs + 1) * 4);
+    w += (d->n_seqs + 2) & ~1;
+    if (s.total_nodes > 0) {
+      memcpy(w, d->anc_bits, (size_t)s.total_nodes * W * 8);
+      memcpy(w + s.total_nodes * W * 2, d->node_len, (size_t)s.total_nodes * 4);
+    }
+    memset(table.w + words, 0, (kArgWords - words) * 4);
+    if (s.total_tokens > 0 && s.total_tokens <= kSmallTokens && s.total_tiles <= kSmallTiles && QT <= kSmallRows &&
+        d->n_seqs <= kSmallSeqs) {
+      hipLaunchKernelGGL(k_meta_small, dim3(1), dim3(1024), 0, stream, d->n_seqs, table, W, d->tile_m, d->tile_n, o,
+                         (int)s.total_tiles, QT, (int)s.total_tokens);
+      DAG_LAUNCH_CHECK();
+      return DAG_OK;
+    }
+  }
   char* p = (char*)dag_align_up((size_t)(uintptr_t)ws, 16);
   int32_t* d_off = (int32_t*)p;
   p += dag_align_up((size_t)(d->n_seqs + 1) * 4, 16);
@@ -432,41 +564,34 @@ extern "C" int dag_build_meta(const dag_desc_t* d, const dag_meta_t* m, void* ws
   uint64_t* d_anc = (uint64_t*)p;
   p += dag_align_up((size_t)s.total_nodes * W * 8, 16);
   int32_t* d_cnt = (int32_t*)p;
-
-  DAG_HIP_CHECK(hipMemcpyAsync(d_off, d->node_offsets, (size_t)(d->n_seqs + 1) * 4, hipMemcpyHostToDevice, stream));
-  if (s.total_nodes > 0) {
-    DAG_HIP_CHECK(hipMemcpyAsync(d_len, d->node_len, (size_t)s.total_nodes * 4, hipMemcpyHostToDevice, stream));
-    DAG_HIP_CHECK(hipMemcpyAsync(d_anc, d->anc_bits, (size_t)s.total_nodes * W * 8, hipMemcpyHostToDevice, stream));
-  }
   int max_nodes = 0;
   for (int b = 0; b < d->n_seqs; ++b) {
     int n = d->node_offsets[b + 1] - d->node_offsets[b];
     if (n > max_nodes) max_nodes = n;
   }
-  const unsigned QT = (unsigned)s.total_qtiles;
   const size_t anc_bytes = (size_t)max_nodes * W * 8;
   const int anc_in_lds = anc_bytes <= 32768;
-  hipLaunchKernelGGL(k_seq_node, dim3(d->n_seqs + 1), dim3(64), (size_t)max_nodes * 8 + 8 + (anc_in_lds ? anc_bytes : 0), stream, d->n_seqs, d_off,
-                     d_len, d_anc, W, d->tile_m, d->tile_n, m->cu_seqlens, m->qtile_start, m->block_map_off,
-                     m->node_start, m->ktile_start, d_cnt, (int)QT, m->node_tok_start, m->node_pos_start, m->node_vis,
-                     m->useful_pairs, anc_in_lds);
-  DAG_LAUNCH_CHECK();
-  if (s.total_tokens == 0) {
-    hipLaunchKernelGGL(k_csr_scan, dim3(1), dim3(1024), 0, stream, 0, d_cnt, m->qtile_rowptr);
-    DAG_LAUNCH_CHECK();
-    return DAG_OK;
+  const size_t lds = (size_t)max_nodes * 8 + 8 + (anc_in_lds ? anc_bytes : 0);
+  if (as_arg) {
+    hipLaunchKernelGGL(k_seq_node<NodeTable>, dim3(d->n_seqs + 1), dim3(256), lds, stream, d->n_seqs, table, nullptr,
+                       nullptr, nullptr, W, d->tile_m, d->tile_n, o, d_cnt, QT, anc_in_lds);
+  } else {
+    DAG_HIP_CHECK(hipMemcpyAsync(d_off, d->node_offsets, (size_t)(d->n_seqs + 1) * 4, hipMemcpyHostToDevice, stream));
+    if (s.total_nodes > 0) {
+      DAG_HIP_CHECK(hipMemcpyAsync(d_len, d->node_len, (size_t)s.total_nodes * 4, hipMemcpyHostToDevice, stream));
+      DAG_HIP_CHECK(hipMemcpyAsync(d_anc, d->anc_bits, (size_t)s.total_nodes * W * 8, hipMemcpyHostToDevice, stream));
+    }
+    hipLaunchKernelGGL(k_seq_node<NoTable>, dim3(d->n_seqs + 1), dim3(256), lds, stream, d->n_seqs, NoTable{}, d_off, d_len,
+                       d_anc, W, d->tile_m, d->tile_n, o, d_cnt, QT, anc_in_lds);
   }
-  hipLaunchKernelGGL(k_tokens, dim3((unsigned)s.total_nodes), dim3(256), 0, stream, d->n_seqs, d_off, d_len,
-                     m->cu_seqlens, m->node_tok_start, m->node_pos_start, m->tok_node, m->pos_ids);
   DAG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_blockmap, dim3((unsigned)dag_ceil_div(s.total_tiles, 256)), dim3(256), 0, stream, d->n_seqs,
-                     s.total_tiles, m->block_map_off, m->cu_seqlens, d_off, m->tok_node, m->node_tok_start,
-                     m->node_vis, W, d->tile_m, d->tile_n, m->qtile_start, m->block_map, d_cnt);
+  if (s.total_tokens == 0) return DAG_OK;
+  const int64_t tile_blocks = dag_ceil_div(s.total_tiles, 256);
+  hipLaunchKernelGGL(k_tiles, dim3((unsigned)(tile_blocks + dag_ceil_div(s.total_tokens, 1024))), dim3(256), 0, stream,
+                     d->n_seqs, s.total_tiles, (int)tile_blocks, (int)s.total_tokens, W, d->tile_m, d->tile_n, o, d_cnt);
   DAG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_csr_order_desc, dim3((QT + 3) / 4), dim3(256), 0, stream, d->n_seqs, (int)QT, d->tile_m,
-                     d->tile_n, d_cnt, m->qtile_start, m->block_map_off, m->cu_seqlens, m->node_start, m->ktile_start,
-                     m->block_map, m->qtile_rowptr, m->qtile_col, m->qtile_flag, m->qtile_nfull, m->qtile_order,
-                     m->qtile_desc);
+  hipLaunchKernelGGL(k_csr_order_desc, dim3((unsigned)((QT + 3) / 4)), dim3(256), 0, stream, d->n_seqs, QT, d->tile_m,
+                     d->tile_n, d_cnt, o);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
