@@ -5,13 +5,13 @@
 extern "C" size_t dag_prefill_workspace_bytes(const dag_meta_t* m, int32_t hkv, int32_t head_dim,
                                               dag_dtype_t dtype) {
   if (!m || dtype != DAG_BF16 || hkv < 1 || head_dim < 1 || m->sizes.total_ktiles < 0) return 0;
-  // key-tile-wise transposed copy of V: [key tile][kv head][head_dim][tile_n] bf16, then the
-  // work-distribution counters, the tables of the 256-row query tiles and of the nodes' query
-  // chunks, plus slack for aligning the caller's pointer to 256 bytes
-  if (m->sizes.total_qtiles < 0 || m->sizes.csr_capacity < 0 || m->sizes.total_tokens < 0 || m->sizes.total_nodes < 0) return 0;
+  // key-tile-wise transposed copy of V: [key tile][kv head][head_dim][tile_n] bf16 (or, where V is read
+  // as it is, the tables of the nodes' query chunks in its place), then the work-distribution
+  // counters and the tables of the 256-row query tiles, plus slack for aligning the caller's
+  // pointer to 256 bytes
+  if (m->sizes.total_qtiles < 0 || m->sizes.csr_capacity < 0) return 0;
   return (size_t)m->sizes.total_ktiles * hkv * head_dim * m->tile_n * 2 +
-         prefill_bf16_table_bytes(m->sizes.total_qtiles, m->sizes.csr_capacity) +
-         prefill_node_table_bytes(m->sizes.total_tokens, m->sizes.total_nodes, m->words_per_node) + 256;
+         prefill_bf16_table_bytes(m->sizes.total_qtiles, m->sizes.csr_capacity) + 256;
 }
 
 namespace {
@@ -61,10 +61,10 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   a->total_tokens = m->sizes.total_tokens;
   a->total_nodes = m->sizes.total_nodes;
   a->node_runs = nullptr;
-  if (need > 0 && m->node_tok_start && m->node_pos_start && m->pos_ids &&
-      prefill_has_node_tables(a->total_nodes, m->words_per_node)) {
-    int32_t* t = a->wide_col + m->sizes.csr_capacity;
-    a->node_runs = t += (uintptr_t)t / 4 % 2;  // 8-byte pairs
+  if (need > 0 && m->node_tok_start && m->node_pos_start && m->pos_ids && a->total_nodes > 0 && m->words_per_node <= 2 &&
+      prefill_node_table_bytes(a->total_tokens, a->total_nodes) <=
+          (size_t)m->sizes.total_ktiles * hkv * head_dim * m->tile_n * 2) {
+    int32_t* t = a->node_runs = (int32_t*)a->vt;
     t += a->total_nodes * 128;
     for (int i = 0; i < DAG_CHUNK_SIZES; ++i) {
       const int64_t n = chunk_slots(a->total_tokens, a->total_nodes, DAG_CHUNK_ROWS[i]);

@@ -1562,19 +1562,17 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
   hipLaunchKernelGGL(k_bwd_tokvis, dim3((unsigned)((total_tokens + 255) / 256)), dim3(256), 0, stream, a, total_tokens);
   DAG_LAUNCH_CHECK();
   int rc;
-  a.dq_narrow = a.G;
   if (!bwd_first_version()) {
     // the heads left over by the groups of NPAIR take NPAIR query tiles each
     constexpr int NPAIR = Dq<D>::NPAIR, sm2 = Dq<D>::NST * Dq<D>::STAGEB;
-    const int wide = bwd_wide_heads(a.G, D);
-    a.dq_narrow = a.G - wide;
+    const int wide = a.G - a.dq_narrow;
     auto* const one_tile = D == 128 ? k_bwd_dq2<false> : k_bwd64_dq<false>;
     auto* const many_tiles = D == 128 ? k_bwd_dq2<true> : k_bwd64_dq<true>;
     if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
         hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
     if (a.dq_narrow > 0)
-      hipLaunchKernelGGL(one_tile, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)(a.dq_narrow / NPAIR)),
+      hipLaunchKernelGGL(one_tile, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)((a.dq_narrow + NPAIR - 1) / NPAIR)),
                          dim3(128 * NPAIR), sm2, stream, a);
     if (wide > 0) {
       hipLaunchKernelGGL(k_bwd_wide_rows<NPAIR>, dim3((unsigned)total_qtiles), dim3(64), 0, stream, a);
@@ -1583,6 +1581,7 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
     }
     rc = hipGetLastError() == hipSuccess ? DAG_OK : DAG_ERR_HIP;
   } else {
+    a.dq_narrow = a.G;
     rc = a.G >= 3 ? launch_dq<D, 4>(a, total_qtiles, stream)
                   : a.G == 2 ? launch_dq<D, 2>(a, total_qtiles, stream) : launch_dq<D, 1>(a, total_qtiles, stream);
   }
@@ -1788,6 +1787,15 @@ int launch_bwd_f32(const BwdArgsF32& a, long total_qtiles, long total_ktiles, hi
 
 }  // namespace
 
+// Head groupings that leave heads over (G not a multiple of four, at head dimension 64 of two): the tile
+// lists of the dQ workgroups that take several query tiles (an int32 and, not used any more, a byte per
+// entry of the dense block map, three int32 per query tile).
+static size_t bwd_wide_list_bytes(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
+  if (hq % hkv != 0 || bwd_wide_heads(hq / hkv, head_dim) == 0 || m->sizes.total_tiles < 0) return 0;
+  return dag_align_up((size_t)m->sizes.total_tiles * 4, 256) + dag_align_up((size_t)m->sizes.total_tiles, 256) +
+         3 * dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256);
+}
+
 extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
   if (!m || hq < 1 || hkv < 1 || head_dim < 1 || m->sizes.total_tokens < 0 || m->sizes.total_qtiles < 0 ||
       m->sizes.total_ktiles < 0)
@@ -1796,13 +1804,7 @@ extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t h
   size_t n = 2 * dag_align_up((size_t)m->sizes.total_tokens * hq * 4, 256) +
              2 * dag_align_up((size_t)m->sizes.total_ktiles * 4, 256) +
              dag_align_up((size_t)m->sizes.total_tokens * 8, 256) + 256;
-  // head groupings that leave heads over (G not a multiple of four, at head dimension 64 of two): the tile
-  // lists of the dQ workgroups that take several query tiles (an int32 per entry of the dense block
-  // map, three int32 per query tile)
-  if (hq % hkv == 0 && bwd_wide_heads(hq / hkv, head_dim) > 0 && m->sizes.total_tiles >= 0)
-    n += dag_align_up((size_t)m->sizes.total_tiles * 4, 256) +
-         3 * dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256);
-  return n;
+  return n + bwd_wide_list_bytes(m, hq, hkv, head_dim);
 }
 
 extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const void* k, const void* v, const void* out,
@@ -1825,7 +1827,10 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   if (m->sizes.total_tokens * (int64_t)hq > INT32_MAX) return DAG_ERR_UNSUPPORTED;
   if (m->sizes.total_qtiles != m->sizes.total_ktiles) return DAG_ERR_BAD_LEN;  // (both tilings are 64 rows)
   const size_t need = dag_prefill_bwd_workspace_bytes(m, hq, hkv, head_dim);
-  if (!ws || ws_bytes < need) return DAG_ERR_WORKSPACE;
+  // (the lists came later at head dimension 64: a workspace without them is taken, the heads left over then
+  // run on one query tile, half of their workgroup idle)
+  const bool lists = ws_bytes >= need;
+  if (!ws || ws_bytes < need - (head_dim == 64 ? bwd_wide_list_bytes(m, hq, hkv, head_dim) : 0)) return DAG_ERR_WORKSPACE;
   if (dtype == DAG_F32) {
     BwdArgsF32 f;
     f.q = (const float*)q; f.k = (const float*)k; f.v = (const float*)v;
@@ -1857,7 +1862,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.wide_nfast = a.wide_n + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
   a.wide_list = a.wide_nfast + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
   a.total_qtiles = (int)m->sizes.total_qtiles;
-  a.dq_narrow = hq / hkv;
+  a.dq_narrow = hq / hkv - (lists ? bwd_wide_heads(hq / hkv, head_dim) : 0);
   a.cu_seqlens = m->cu_seqlens; a.node_start = m->node_start; a.tok_node = m->tok_node;
   a.qtile_start = m->qtile_start; a.ktile_start = m->ktile_start;
   a.qtile_order = m->qtile_order;

@@ -58,12 +58,12 @@ struct PrefillArgs {
   ChunkTables chunk[DAG_CHUNK_SIZES];
 };
 
-// The node tables hold 64 runs per node, the most that 128 nodes can have.
-inline bool prefill_has_node_tables(int64_t total_nodes, int words_per_node) { return words_per_node <= 2 && total_nodes > 0; }
-inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes, int words_per_node) {
-  if (!prefill_has_node_tables(total_nodes, words_per_node)) return 0;
+// The node tables hold 64 runs per node, the most that 128 nodes can have.  They take the place of the
+// transposed V, which is not needed with them: 716 bytes a node and 1.9 a token against at least 128 a
+// token, so that they fit wherever a node has six tokens on average.
+inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes) {
   size_t n = (size_t)total_nodes * 128 * 4;
-  for (int i = 0; i < DAG_CHUNK_SIZES; ++i) n += (size_t)(64 + 17 * chunk_slots(total_tokens, total_nodes, DAG_CHUNK_ROWS[i])) * 4;
+  for (int i = 0; i < DAG_CHUNK_SIZES; ++i) n += (size_t)(62 + 17 * chunk_slots(total_tokens, total_nodes, DAG_CHUNK_ROWS[i])) * 4;
   return n;
 }
 

@@ -5,7 +5,9 @@ import os
 
 import numpy as np
 import pytest
+import torch
 
+from paper_2602_07529_amd import binding as B
 from workloads import dags
 from tests.test_asm_lds_reads import HIPCC, _assembly, _conflicts_of_kernel, _kernels, _run
 from tests.test_gpu_prefill_bwd import _check_against_oracle, _forward_backward
@@ -24,6 +26,25 @@ def _ragged(rng):
 def test_bwd_head_dim_64_head_groupings(hq, hkv):
     dag_list = _ragged(np.random.Generator(np.random.PCG64(6400 + hq)))
     inputs, grads = _forward_backward(dag_list, hq, hkv, 64, 6500 + hq)
+    _check_against_oracle(dag_list, inputs, grads)
+
+
+# a workspace without room for the tile lists of left-over heads is still taken
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (5, 1), (6, 2)])
+def test_bwd_head_dim_64_without_tile_lists(hq, hkv, monkeypatch):
+    dag_list = _ragged(np.random.Generator(np.random.PCG64(6450 + hq)))
+    call = B.dag_attn_prefill_bwd
+
+    def with_small_workspace(meta, q, *args, **kw):
+        up = lambda n: -(-n // 256) * 256  # noqa: E731
+        m = meta.sizes
+        n = 2 * up(m.total_tokens * hq * 4) + 2 * up(m.total_ktiles * 4) + up(m.total_tokens * 8) + 256
+        assert n < B.dag_prefill_bwd_workspace_bytes(meta, hq, hkv, 64)
+        call(meta, q, *args, workspace=torch.empty(n, dtype=torch.uint8, device=q.device), **kw)
+
+    monkeypatch.setattr(B, "dag_attn_prefill_bwd", with_small_workspace)
+    inputs, grads = _forward_backward(dag_list, hq, hkv, 64, 6550 + hq)
     _check_against_oracle(dag_list, inputs, grads)
 
 
