@@ -935,13 +935,131 @@ __global__ void __launch_bounds__(256) k_kv_append(const int32_t* branch_page_of
     const size_t src = ((size_t)r * hkv + h) * D;
     const float lo = __uint_as_float((uint32_t)k_new[src + mi] << 16);
     const float hi = __uint_as_float((uint32_t)k_new[src + mi + half] << 16);
-    const float c = s_cos[mi], s = s_sin[mi];
+    const float c = s_cos[mi], s = s_sin[mi];  // (the products are rounded alike in k_kv_append_run)
     const size_t pb = ((size_t)page * hkv + h) * (size_t)(D * PAGE);
     const int d0 = mi, d1 = mi + half;
-    k_pool[pb + (size_t)(d0 >> 3) * (PAGE * 8) + slot * 8 + (d0 & 7)] = (uint16_t)dag_f2bf(lo * c - hi * s);
-    k_pool[pb + (size_t)(d1 >> 3) * (PAGE * 8) + slot * 8 + (d1 & 7)] = (uint16_t)dag_f2bf(hi * c + lo * s);
+    k_pool[pb + (size_t)(d0 >> 3) * (PAGE * 8) + slot * 8 + (d0 & 7)] = (uint16_t)dag_f2bf(fmaf(lo, c, -(hi * s)));
+    k_pool[pb + (size_t)(d1 >> 3) * (PAGE * 8) + slot * 8 + (d1 & 7)] = (uint16_t)dag_f2bf(fmaf(lo, s, hi * c));
     v_pool[pb + (size_t)d0 * PAGE + slot] = v_new[src + d0];
     v_pool[pb + (size_t)d1 * PAGE + slot] = v_new[src + d1];
+  }
+}
+
+// The same for many entries (the new tokens of prefilled nodes), kRunRows at a time.  Consecutive entries mostly are
+// consecutive slots of a page: the angles of an entry serve all heads, keys are rotated and stored in
+// 16-byte pieces, and the values of eight entries that fill half a page go out as one 16-byte piece per
+// dimension, the others element by element.  32768 entries of 8 heads x 128: 200 -> 58 us aligned, 82 us
+// from slot 5 on (the traffic takes 45 us at the rate of a large copy).  Few runs are divided over the
+// heads too, to about two workgroups a compute unit.
+// Entries from which on: with 8 heads runs of 512 take the same either way, 1024 take 10.3 -> 8.5 us, 4096 26 ->
+// 13 to 16; entries on pages of their own, 2048 to 4096 of them, lose 3 to 7 us (21 -> 24, 36 -> 43).
+constexpr int kRunRows = 16, kRunThreads = 256;
+constexpr int kAppendRunRows = 1024;
+__global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const int32_t* branch_page_off, const int32_t* branch_pages,
+                                                       const int32_t* branch_len, const int32_t* branch_pos,
+                                                       const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
+                                                       uint16_t* v_pool, int hkv, int D, float theta) {
+  __shared__ __attribute__((aligned(16))) float s_cos[kRunRows][64], s_sin[kRunRows][64];
+  __shared__ int s_page[kRunRows], s_slot[kRunRows], s_whole[kRunRows], s_one[kRunRows], s_wholes, s_ones;  // slot -1: nothing to store
+  const int r0 = blockIdx.x * kRunRows, tid = threadIdx.x, half = D / 2;
+  const int h0 = (int)blockIdx.y * hkv / (int)gridDim.y, heads = ((int)blockIdx.y + 1) * hkv / (int)gridDim.y - h0;
+  if (tid < 64) {  // lane: entry r0 - 7 + lane, so that every unit of eight that reaches into the block is seen
+    const int r = r0 - 7 + tid;
+    int page = 0, slot = -1;
+    if (tid < kRunRows + 14 && r >= 0 && r < n_live) {
+      const int idx = branch_len[r] - 1;
+      if (idx >= 0) {
+        page = branch_pages[branch_page_off[r] + idx / PAGE];
+        slot = idx % PAGE;
+      }
+    }
+    // Units of the value stores: eight entries on consecutive slots from a multiple of eight on (the block
+    // of the first one stores them), or one entry.
+    bool whole = slot >= 0 && slot % 8 == 0;
+    for (int e = 1; e < 8; ++e) {
+      const int p = __shfl_down(page, e), t = __shfl_down(slot, e);
+      whole = whole && p == page && t == slot + e;
+    }
+    const uint64_t mine = ((1ull << kRunRows) - 1) << 7, below = (1ull << tid) - 1, lead = __ballot(whole);
+    const bool covered = (lead & (0x7full << tid >> 7)) != 0;  // by one of the seven entries in front
+    const uint64_t wholes = lead & mine, ones = __ballot(slot >= 0 && !whole && !covered) & mine;
+    if (wholes >> tid & 1) s_whole[__popcll(wholes & below)] = tid - 7;
+    if (ones >> tid & 1) s_one[__popcll(ones & below)] = tid - 7;
+    if (mine >> tid & 1) {
+      s_page[tid - 7] = page;
+      s_slot[tid - 7] = slot;
+    }
+    if (tid == 0) {
+      s_wholes = __popcll(wholes);
+      s_ones = __popcll(ones);
+    }
+  }
+  {
+    const double freq = pow((double)theta, -2.0 * (double)(tid % half) / (double)D);  // (half divides the block)
+    for (int i = tid / half; i < kRunRows; i += kRunThreads / half) {
+      double sn = 0., cs = 1.;
+      if (r0 + i < n_live) sincos((double)branch_pos[r0 + i] * freq, &sn, &cs);
+      s_cos[i][tid % half] = (float)cs;
+      s_sin[i][tid % half] = (float)sn;
+    }
+  }
+  __syncthreads();
+  const int pairs = half / 8;  // 16-byte pieces of half a row
+  const bool by_entry = s_wholes > 0;
+  for (int x = tid; x < kRunRows * heads * pairs; x += kRunThreads) {
+    // entries fastest where they lie on consecutive slots, else pieces of a row
+    const int i = by_entry ? x % kRunRows : x / pairs % kRunRows, c = by_entry ? x / kRunRows % pairs : x % pairs;
+    const int h = h0 + x / (kRunRows * pairs);
+    const int slot = s_slot[i];
+    if (slot < 0) continue;
+    const uint16_t* src = k_new + ((size_t)(r0 + i) * hkv + h) * D + 8 * c;
+    const u32x4 lo = *(const u32x4*)src, hi = *(const u32x4*)(src + half);
+    const float *cs = &s_cos[i][8 * c], *sn = &s_sin[i][8 * c];
+    u32x4 olo, ohi;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float l0 = dag_bf_lo(lo[w]), l1 = dag_bf_hi(lo[w]), h0 = dag_bf_lo(hi[w]), h1 = dag_bf_hi(hi[w]);
+      const float c0 = cs[2 * w], c1 = cs[2 * w + 1], s0 = sn[2 * w], s1 = sn[2 * w + 1];
+      olo[w] = dag_f2bf(fmaf(l0, c0, -(h0 * s0))) | dag_f2bf(fmaf(l1, c1, -(h1 * s1))) << 16;
+      ohi[w] = dag_f2bf(fmaf(l0, s0, h0 * c0)) | dag_f2bf(fmaf(l1, s1, h1 * c1)) << 16;
+    }
+    uint16_t* dst = k_pool + ((size_t)s_page[i] * hkv + h) * (size_t)(D * PAGE) + c * (PAGE * 8) + slot * 8;
+    *(u32x4*)dst = olo;
+    *(u32x4*)(dst + half * PAGE) = ohi;
+  }
+  // Two dimensions of the values of a head; a thread takes a unit of eight, or up to four single entries.
+  const int ny = heads * half, n_wholes = s_wholes, n_ones = s_ones;
+  const size_t step = (size_t)hkv * D;
+  for (int x = tid; x < (n_wholes + (n_ones + 3) / 4) * ny; x += kRunThreads) {
+    const int y = x % ny, g = x / ny, d = 2 * (y % half), h = h0 + y / half;
+    const uint16_t* const src = v_new + ((size_t)r0 * hkv + h) * D + d;
+    uint16_t* const dst = v_pool + (size_t)h * (D * PAGE) + (size_t)d * PAGE;
+    if (g < n_wholes) {
+      const int i = s_whole[g];
+      uint32_t in[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) in[e] = *(const uint32_t*)(src + (i + e) * step);
+      u32x4 even, odd;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        even[w] = (in[2 * w] & 0xffffu) | in[2 * w + 1] << 16;
+        odd[w] = in[2 * w] >> 16 | (in[2 * w + 1] & 0xffff0000u);
+      }
+      uint16_t* const to = dst + (size_t)s_page[i] * step * PAGE + s_slot[i];
+      *(u32x4*)to = even;
+      *(u32x4*)(to + PAGE) = odd;
+    } else {
+      uint32_t in[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) in[e] = *(const uint32_t*)(src + s_one[min(4 * (g - n_wholes) + e, n_ones - 1)] * step);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = s_one[min(4 * (g - n_wholes) + e, n_ones - 1)];  // (the last one may be stored again)
+        uint16_t* const to = dst + (size_t)s_page[i] * step * PAGE + s_slot[i];
+        to[0] = (uint16_t)in[e];
+        to[PAGE] = (uint16_t)(in[e] >> 16);
+      }
+    }
   }
 }
 
@@ -1032,7 +1150,14 @@ extern "C" int dag_kv_append_rope(const dag_decode_desc_t* d, const void* k_new,
   if (!k_new || !v_new || !k_pool || !v_pool || !d->branch_page_off || !d->branch_pages || !d->branch_len ||
       !d->branch_pos)
     return DAG_ERR_NULL;
-  hipLaunchKernelGGL(k_kv_append, dim3(d->n_live), dim3(256), 0, (hipStream_t)stream_, d->branch_page_off,
+  const int64_t runs = dag_ceil_div(d->n_live, kRunRows), split = dag_ceil_div(512, runs);
+  if (d->n_live >= kAppendRunRows && dag_aligned16(k_new) && dag_aligned16(v_new) && dag_aligned16(k_pool) && dag_aligned16(v_pool))
+    hipLaunchKernelGGL(k_kv_append_run, dim3((unsigned)runs, (unsigned)(split < hkv ? split : hkv)), dim3(kRunThreads), 0, (hipStream_t)stream_,
+                       d->n_live, d->branch_page_off, d->branch_pages, d->branch_len, d->branch_pos,
+                       (const uint16_t*)k_new, (const uint16_t*)v_new, (uint16_t*)k_pool, (uint16_t*)v_pool, hkv,
+                       head_dim, theta);
+  else
+    hipLaunchKernelGGL(k_kv_append, dim3(d->n_live), dim3(256), 0, (hipStream_t)stream_, d->branch_page_off,
                      d->branch_pages, d->branch_len, d->branch_pos, (const uint16_t*)k_new, (const uint16_t*)v_new,
                      (uint16_t*)k_pool, (uint16_t*)v_pool, hkv, head_dim, theta);
   DAG_LAUNCH_CHECK();
