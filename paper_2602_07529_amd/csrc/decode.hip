@@ -526,13 +526,26 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 #pragma unroll
     for (int t = 0; t < PER; ++t) acc[t] *= keep;
     unsigned long long live = __builtin_amdgcn_ballot_w64(ls > 0.f);
-    while (live) {
-      const int j = __builtin_ctzll(live);
-      live &= live - 1;
-      const float wj = __shfl(wgt, j);
-      const uint32_t bj = (uint32_t)__shfl((int)base, j);
+    while (live) {  // eight partials at a time, their loads in flight together
+      constexpr int BATCH = 8;
+      float w[BATCH], x[BATCH][PER];
+      int n_live = 0, j = 0;
 #pragma unroll
-      for (int t = 0; t < PER; ++t) acc[t] += wj * a.part_o[(size_t)bj * D + lane * PER + t];
+      for (int n = 0; n < BATCH; ++n) {
+        if (live) {
+          j = __builtin_ctzll(live);
+          live &= live - 1;
+          n_live = n + 1;
+        }
+        w[n] = __shfl(wgt, j);
+        const float* o = a.part_o + (size_t)(uint32_t)__shfl((int)base, j) * D + lane * PER;  // (past the last one: that one again)
+#pragma unroll
+        for (int t = 0; t < PER; ++t) x[n][t] = o[t];
+      }
+#pragma unroll
+      for (int n = 0; n < BATCH; ++n)
+#pragma unroll
+        for (int t = 0; t < PER; ++t) acc[t] += n < n_live ? w[n] * x[n][t] : 0.f;
     }
   }
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
@@ -841,13 +854,18 @@ __global__ void __launch_bounds__(WIDE_MAX_THREADS) __attribute__((amdgpu_waves_
   }
 }
 
-// One wave per (branch, query head): log-sum-exp combination of its partials.
+// One wave per (branch, query head): log-sum-exp combination of its partials.  What it costs is the chain
+// of dependent loads (a binary search for the group, then the partials four at a time: 7.8 us for
+// 16 partials), so the group is found with one load per lane, and the outputs of the first 16
+// partials are on their way together with the maxima and sums: 4.7 us.
 template <int D>
 __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   const int r = blockIdx.x / a.hq, head = blockIdx.x % a.hq;
   const int hk = head / a.G, j = head % a.G;
   const int lane = threadIdx.x;
-  const int g = dag_find_segment(a.group_branch_off, a.n_groups, r);
+  int g = -1;  // the last group that starts at or before r
+  for (int g0 = 0; g0 < a.n_groups; g0 += 64)
+    g += __popcll(__ballot(g0 + lane < a.n_groups && a.group_branch_off[min(g0 + lane, a.n_groups)] <= r));
   const int row = (r - a.group_branch_off[g]) * a.G + j;
   const int rb = row >> 5, rr = row & 31;
   const size_t ia0 = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a;
@@ -861,7 +879,17 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   auto o_of = [&](int p) {
     return p < a.splits_a ? a.part_o_a + ((ia0 + p) * 32 + rr) * D : a.part_o_b + ((ib0 + (p - a.splits_a)) * a.G + j) * D;
   };
-  float acc[PER];
+  constexpr int BATCH = 16;
+  float x[BATCH][PER], acc[PER];
+  auto fetch = [&](int p0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const float* o = o_of(min(p0 + i, np - 1)) + lane * PER;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) x[i][e] = o[e];
+    }
+  };
+  fetch(0);
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
   // The reference maximum first (64 partials at a time, one per lane, so that their loads are in
@@ -887,16 +915,14 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
         wl = ls * wgt;
       }
     }
-    const int n = min(64, np - p0);
-#pragma unroll 4
-    for (int i = 0; i < n; ++i) {
-      const float wi = __shfl(wgt, i);
-      lsum += __shfl(wl, i);
-      const float* o = o_of(p0 + i) + lane * PER;  // (read in any case, so that the loads of several partials overlap)
+    for (int b0 = p0; b0 < min(p0 + 64, np); b0 += BATCH) {
+      if (b0 > 0) fetch(b0);
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const float x = o[e];
-        acc[e] += wi != 0.f ? wi * x : 0.f;
+      for (int i = 0; i < BATCH; ++i) {  // (the weight of a partial past the last one is zero)
+        const float wi = __shfl(wgt, b0 - p0 + i);
+        lsum += __shfl(wl, b0 - p0 + i);
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
       }
     }
   }
