@@ -151,6 +151,10 @@ __device__ __forceinline__ bf16x8 join_halves(v4i16_t lo, v4i16_t hi) {
   return __builtin_bit_cast(bf16x8, x);
 }
 
+// Workgroups of the attention kernel on a compute unit: at head dimension 64 the rings of two of four waves
+// fit into its LDS.
+constexpr int wgs_per_cu(int D, int waves) { return D == 64 && waves == 4 ? 2 : 1; }
+
 struct Item {  // wave-uniform description of a work item
   int cu, T, row0, c0, N, nfast, nstart, ktb, hk, hs;
 };
@@ -261,11 +265,9 @@ __global__ void __launch_bounds__(256) k_wide_rows(int n_seqs, int total_qtiles,
 
 // Launch order of the 256-row tiles: by descending tile count (ties: ascending index), as for the
 // 64-row ones; also counts them.  One wave per 64-row tile.
-__global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int32_t* __restrict__ wide_cnt,
-                                                    const int32_t* __restrict__ wide_pre,
-                                                    int32_t* __restrict__ wide_desc, int32_t* __restrict__ wide_count) {
-  const int qt = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (qt >= total_qtiles) return;
+__device__ __forceinline__ void wide_order(int qt, int total_qtiles, const int32_t* wide_cnt, const int32_t* wide_pre,
+                                           int32_t* wide_desc, int32_t* wide_count) {
+  const int lane = threadIdx.x & 63;
   const int mine = wide_cnt[qt];
   if (mine < 0 && qt != 0) return;
   int oi = 0, n = 0;
@@ -281,6 +283,12 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
   if (mine >= 0 && lane < 8) wide_desc[(int64_t)oi * 8 + lane] = wide_pre[(int64_t)qt * 8 + lane];
   if (qt == 0 && lane == 0) *wide_count = n;
 }
+__global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int32_t* __restrict__ wide_cnt,
+                                                    const int32_t* __restrict__ wide_pre,
+                                                    int32_t* __restrict__ wide_desc, int32_t* __restrict__ wide_count) {
+  const int qt = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (qt < total_qtiles) wide_order(qt, total_qtiles, wide_cnt, wide_pre, wide_desc, wide_count);
+}
 
 // Query chunks.  Consecutive nodes with the same ancestors (the siblings of a fork; most often a single
 // node) form a group, and the query rows are cut at the borders of the groups instead of every 64
@@ -295,17 +303,15 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
 // One wave per node (at most 128 per sequence, so at most 64 runs): its runs, and for the first node of a
 // group the descriptors of its chunks.
 template <int W>
-__global__ void __launch_bounds__(256) k_node_rows(int n_seqs, int total_nodes, int rows, int64_t n_slots,
-                                                   const int32_t* __restrict__ node_start,
-                                                   const int32_t* __restrict__ cu_seqlens,
-                                                   const int32_t* __restrict__ tok_node,
-                                                   const int32_t* __restrict__ node_tok_start,
-                                                   const int32_t* __restrict__ node_pos_start,
-                                                   const uint64_t* __restrict__ node_vis, int32_t* __restrict__ sched,
-                                                   int32_t* __restrict__ runs, ChunkTables t) {
-  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (blockIdx.x == 0 && threadIdx.x < DAG_SCHED_INTS) sched[threadIdx.x] = 0;  // work counters of the attention kernel
-  if (gv >= total_nodes) return;
+__device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, int rows, int64_t n_slots,
+                                          const int32_t* __restrict__ node_start,
+                                          const int32_t* __restrict__ cu_seqlens,
+                                          const int32_t* __restrict__ tok_node,
+                                          const int32_t* __restrict__ node_tok_start,
+                                          const int32_t* __restrict__ node_pos_start,
+                                          const uint64_t* __restrict__ node_vis,
+                                          int32_t* __restrict__ runs, const ChunkTables& t) {
+  const int lane = threadIdx.x & 63;
   const int b = dag_find_segment(node_start, n_seqs, gv);
   const int n0 = node_start[b], n = node_start[b + 1] - n0, v = gv - n0;
   const int cu = cu_seqlens[b], T = cu_seqlens[b + 1] - cu;
@@ -370,6 +376,29 @@ __global__ void __launch_bounds__(256) k_node_rows(int n_seqs, int total_nodes, 
     d[6] = anc;
     d[7] = node_pos_start[gv];  // position id of the first token of every node of the group
   }
+}
+
+template <int W>
+__global__ void __launch_bounds__(256) k_node_rows(int rows, int64_t n_slots, PrefillArgs a, ChunkTables t) {
+  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (blockIdx.x == 0 && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;  // work counters of the attention kernel
+  if (gv < a.total_nodes)
+    node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
+                 a.node_pos_start, a.node_vis, a.node_runs, t);
+}
+// Few nodes: the tables and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2).
+constexpr int SMALL_NODES = 64, SMALL_SLOTS = 128;
+template <int W>
+__global__ void __launch_bounds__(1024) k_node_rows_small(int rows, int n_slots, PrefillArgs a, ChunkTables t) {
+  __shared__ int32_t s_cnt[SMALL_SLOTS], s_pre[SMALL_SLOTS * 8];
+  const int w = threadIdx.x >> 6;
+  if (threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
+  const ChunkTables local = {t.count, s_cnt, s_pre, t.desc};
+  for (int gv = w; gv < a.total_nodes; gv += 16)
+    node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
+                 a.node_pos_start, a.node_vis, a.node_runs, local);
+  __syncthreads();
+  for (int i = w; i < n_slots; i += 16) wide_order(i, n_slots, s_cnt, s_pre, t.desc, t.count);
 }
 
 // Work items of the paged prefill (section 4.3, phase II: the new tokens of a node are prefilled
@@ -1266,7 +1295,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
       // checks; the operand reads run PF slots ahead of their MFMAs without a break, across the
       // two halves and into the next tile (whose K tile is published a tile ahead for that).
 #ifndef DAGATTN_NOFAST
-      if (1 < F) {
+      if (1 < F || (NODES && F == 1 && NT > 1)) {
         constexpr int NS = KSTEPS + 2 * DB;
 #ifdef DAGATTN_PF
         constexpr int PF = DAGATTN_PF, RING = DAGATTN_PF < 4 ? 4 : 8;
@@ -1358,7 +1387,10 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
         // the bytes that are there already into the same places.
         const int setup_slot = w < NW / 2 || NW == 1 ? 1 : NS / 2 + 1;
         bool other = false;
-        auto fast_tile = [&]() __attribute__((always_inline)) {
+        // MASKED (chunks only): the scores of this tile's keys that rmsk hides become -inf, each half's behind
+        // its last score MFMA.  Every row has seen the whole first tile (F > 0), so its reference is set.
+        auto fast_tile = [&](auto masked_c) __attribute__((always_inline)) {
+          constexpr bool MASKED = decltype(masked_c)::value;
           const uint32_t ka = lds_addr(Kt(tc)) + koff, va = lds_addr(Vt(tc - 1)) + voff, kn = lds_addr(Kt(tc + 1)) + koff;
           float rs[RB], pprev[RB], plast[RB];  // sums, the even partner of a pair, the exponential of the slot before
 #pragma unroll
@@ -1389,6 +1421,18 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
               if constexpr (j < KSTEPS) Sn[r] = mfma32(opr[i % RING], qf[r][j < KSTEPS ? j : 0], j == 0 ? negM[r] : Sn[r]);
               else O[r][(j - KSTEPS) % DB] = mfma32(NODES ? join_halves(vlo[i % RING], vhi[i % RING]) : opr[i % RING],
                                                     Pp[r][(j - KSTEPS) / DB], O[r][(j - KSTEPS) % DB]);
+            }
+            if constexpr (MASKED && j > KSTEPS) {
+              constexpr int m0 = (j - KSTEPS - 1) * 16 / (2 * DB - 1), m1 = (j - KSTEPS) * 16 / (2 * DB - 1);
+#pragma unroll
+              for (int r = 0; r < RB; ++r) {
+                const int word = (int)(st ? (uint32_t)(rmsk[r] >> 32) : (uint32_t)rmsk[r]);
+#pragma unroll
+                for (int e = m0; e < m1; ++e) {  // this lane's key 32 st + 16 (e / 8) + 8 H + e % 8
+                  const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(word, 16 * (e >> 3) + (e & 7), 1);
+                  Sn[r][e] = __uint_as_float((__float_as_uint(Sn[r][e]) & keep) | (0xff800000u & ~keep));
+                }
+              }
             }
             if constexpr (st == 0 && (j == 1 || j == NS / 2 + 1)) {
               if (j == setup_slot && ti - tc < NSTAGE) {
@@ -1490,7 +1534,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
           sync_next();
           TSTAMP2(tf1);
           TACC2(1, tf0, tf1);
-          fast_tile();
+          fast_tile(N_);
           if (other) {  // (a tile with a mask or a ragged one, the next item, the next 64 entries, the end of the stream)
             other = false;
             try_issue();
@@ -1499,6 +1543,21 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
           TACC2(3, tf1, tf2);
           TCOUNT(10);
           TCOUNT(7);
+        }
+        // On chunks the tiles with a mask, the last one or two of an item, go the same way: on the general
+        // path below such a tile takes 2.7 us of a lone workgroup, here 1.4 (random DAGs, 32 / 8 heads: 1639 -> 1626 us).
+        if constexpr (NODES) {
+#pragma unroll 1
+          for (; n + 1 < NT; ++n) {
+            sync_next();
+            tile_mask(n + 1, tc, rmsk);
+            fast_tile(Y);
+            if (other) {
+              other = false;
+              try_issue();
+            }
+            TCOUNT(7);
+          }
         }
         // The operands fetched ahead for a tile that takes the other path: nobody will use them, so
         // the compiler takes their registers for the temporaries of what follows -- which must not
@@ -1716,7 +1775,7 @@ __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_bf16(PrefillArgs a
   prefill_body<D, HG, NRG, PAGED ? STREAM_PAGES : STREAM_TILES>(a);
 }
 template <int D, int HG, int NRG>
-__global__ void __launch_bounds__(64 * HG * NRG, 8 / (HG * NRG)) k_prefill_nodes(PrefillArgs a) {
+__global__ void __launch_bounds__(64 * HG * NRG, wgs_per_cu(D, HG * NRG)) k_prefill_nodes(PrefillArgs a) {
   prefill_body<D, HG, NRG, STREAM_NODES>(a);
 }
 
@@ -1746,21 +1805,35 @@ bool on_chunks(const PrefillArgs& a, int head_dim) {
   return a.total_tokens >= shortest * a.total_nodes;
 }
 
+int compute_units() {  // of the current device; 0: it cannot be asked
+  int dev = 0, n = 0;
+  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+}
+
+// Batches too small to give every compute unit an item of four heads take one or two heads to an item, all of
+// them in one launch (0: not such a batch, split_heads).  40 / 8 heads, 260 / 360 tokens: 49.5 / 56.7 ->
+// 33.2 / 36.6 us with meta and RoPE, 32 / 8 heads, 650 tokens: 43.3 -> 41.9 us, 4 / 2 heads, 2450 tokens:
+// 82.7 -> 79.2 us.  One or two heads of dimension 64 per KV head stay with their items (4 / 2 heads: 60
+// against 68 us).
+int heads_of_small_batch(const PrefillArgs& a, int head_dim) {
+  const int64_t chunks = chunk_slots(a.total_tokens, a.total_nodes, 64) * a.hkv, g = a.hq / a.hkv, n = compute_units();
+  if (head_dim == 64 && g < 3) return 0;
+  return chunks * g <= n ? 1 : chunks * ((g + 1) / 2) <= n ? 2 : 0;
+}
+
 template <int D, int HG, int NRG, int STREAM>
 int launch_one(const PrefillArgs& a, long max_tiles, hipStream_t stream) {
   constexpr int KPB = 64 / (D / 8), KTILE = TN / KPB * (1024 + 16), VTILE = STREAM == STREAM_NODES ? KTILE : D / 8 * (1024 + 128);
   constexpr size_t sm = (size_t)NSTAGE * (KTILE + VTILE + (STREAM == STREAM_TILES ? 256 : 0)) + 16 +
                         (size_t)HG * NRG * 32 * (64 + 16);  // rings + node-id records + item mailbox + output pieces
-  constexpr int PER_CU = 8 / (HG * NRG);  // workgroups that share a compute unit
+  constexpr int PER_CU = wgs_per_cu(D, HG * NRG);  // workgroups that share a compute unit
   static_assert(PER_CU * sm <= 160 * 1024, "LDS of a compute unit");
   void (*kernel)(PrefillArgs);
   if constexpr (STREAM == STREAM_NODES) kernel = k_prefill_nodes<D, HG, NRG>;
   else kernel = k_prefill_bf16<D, HG, NRG, STREAM == STREAM_PAGES>;
   if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess) return DAG_ERR_HIP;
-  int dev = 0, n_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-    return DAG_ERR_HIP;
+  const int n_cu = compute_units();
+  if (n_cu < 1) return DAG_ERR_HIP;
   const long n_items = max_tiles * a.hkv * ((a.heads + HG - 1) / HG), n_wg = (long)n_cu * PER_CU;
   const unsigned grid = (unsigned)(n_items < n_wg ? n_items : n_wg);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * HG * NRG), sm, stream, a);
@@ -1787,7 +1860,10 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
   const bool chunks = on_chunks(a, D);
   const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
   int rc = DAG_OK;
-  if (chunks) {  // (at head dimension 64 four waves with half the rings: two workgroups per compute unit)
+  const int few = chunks ? heads_of_small_batch(a, D) : 0;
+  if (few > 0) {
+    return few == 1 ? launch_chunks<D, 1, 2>(a, 0, a.hq / a.hkv, stream) : launch_chunks<D, 2, 2>(a, 0, a.hq / a.hkv, stream);
+  } else if (chunks) {  // (at head dimension 64 four waves with half the rings: two workgroups per compute unit)
     if (h.four > 0) rc = launch_chunks<D, 4, 2>(a, 0, h.four, stream);
     if (rc == DAG_OK && h.two > 0) rc = D == 128 ? launch_chunks<128, 2, 4>(a, h.four, h.two, stream) : launch_chunks<64, 2, 2>(a, h.four, h.two, stream);
     if (rc == DAG_OK && h.one > 0) rc = D == 128 ? launch_chunks<128, 1, 8>(a, h.four + h.two, 1, stream) : launch_chunks<64, 1, 4>(a, h.four + h.two, 1, stream);
@@ -1816,9 +1892,14 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
 // The chunk tables of one chunk size: descriptors, then launch order (by descending tile count).
 int build_chunks(const PrefillArgs& a, int i, hipStream_t stream) {
   const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[i]);
-  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream, a.n_seqs, (int)a.total_nodes,
-                     DAG_CHUNK_ROWS[i], slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start, a.node_pos_start, a.node_vis, a.sched, a.node_runs,
-                     a.chunk[i]);
+  if (a.total_nodes <= SMALL_NODES && slots <= SMALL_SLOTS) {
+    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(1), dim3(1024), 0, stream, DAG_CHUNK_ROWS[i],
+                       (int)slots, a, a.chunk[i]);
+    DAG_LAUNCH_CHECK();
+    return DAG_OK;
+  }
+  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream,
+                     DAG_CHUNK_ROWS[i], slots, a, a.chunk[i]);
   hipLaunchKernelGGL(k_wide_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, (int)slots, a.chunk[i].cnt,
                      a.chunk[i].pre, a.chunk[i].desc, a.chunk[i].count);
   DAG_LAUNCH_CHECK();
@@ -1832,6 +1913,7 @@ int launch_prepare_v(const PrefillArgs& a, hipStream_t stream) {
   const bool chunks = on_chunks(a, D);
   const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
   if (chunks) {  // V is read as it is
+    if (heads_of_small_batch(a, D) > 0) return build_chunks(a, 0, stream);
     int rc = h.four > 0 || (h.two > 0 && D == 64) ? build_chunks(a, 0, stream) : DAG_OK;
     if (rc == DAG_OK && ((h.two > 0 && D == 128) || (h.one > 0 && D == 64))) rc = build_chunks(a, 1, stream);
     if (rc == DAG_OK && h.one > 0 && D == 128) rc = build_chunks(a, 2, stream);

@@ -52,4 +52,4 @@ def test_generated_code_of_the_chunk_kernels(tmp_path):
         assert not bad, "%s: %s" % (name, bad[:3])
         assert not any("scratch_" in l for l in lines), name
         seen += 1
-    assert seen == 6
+    assert seen == 9
