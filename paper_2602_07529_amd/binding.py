@@ -156,7 +156,8 @@ def _check(rc):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # (the handle without a torch.cuda.Stream object around it: 0.3 instead of 2.9 us a call, of 8 to 11)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ptr(t):
