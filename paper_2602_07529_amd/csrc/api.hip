@@ -64,13 +64,7 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   if (need > 0 && m->node_tok_start && m->node_pos_start && m->pos_ids && a->total_nodes > 0 && m->words_per_node <= 2 &&
       prefill_node_table_bytes(a->total_tokens, a->total_nodes) <=
           (size_t)m->sizes.total_ktiles * hkv * head_dim * m->tile_n * 2) {
-    int32_t* t = a->node_runs = (int32_t*)a->vt;
-    t += a->total_nodes * 128;
-    for (int i = 0; i < DAG_CHUNK_SIZES; ++i) {
-      const int64_t n = chunk_slots(a->total_tokens, a->total_nodes, DAG_CHUNK_ROWS[i]);
-      a->chunk[i] = {t, t + 62, t + 62 + n, t + 62 + 9 * n};
-      t += 62 + 17 * n;
-    }
+    prefill_node_tables(*a, (int32_t*)a->vt);
   }
   a->head0 = 0;
   a->heads = hq / hkv;

@@ -1908,6 +1908,8 @@ int build_chunks(const PrefillArgs& a, int i, hipStream_t stream) {
 
 }  // namespace
 
+int launch_chunk_tables(const PrefillArgs& a, int i, hipStream_t stream) { return build_chunks(a, i, stream); }
+
 template <int D>
 int launch_prepare_v(const PrefillArgs& a, hipStream_t stream) {
   const bool chunks = on_chunks(a, D);

@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "prefill_launch.h"
 
 namespace {
 
@@ -67,6 +68,10 @@ struct BwdArgs {
   int32_t* wide_col;    // [dense map] key tiles that one of the query tiles sees, those that all of them see in full first
   int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every NQ-th tile)
   int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups, sequence after sequence; last element: their number
+  // dQ on query chunks (k_node_rows): the chunk tables of 64 and of 64 NQ rows, the nodes' runs
+  ChunkTables chunk[2];
+  int64_t chunk_slots[2];
+  const int32_t *runs, *pos_ids;
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -1322,7 +1327,11 @@ struct Dq {
 // WIDE: the same workgroup turned by ninety degrees -- one query head on four (two) consecutive query
 // tiles (wave pair p takes tile 4 c + p), for the heads that do not fill a group: the waves still
 // share every staged K / V tile.  The tile list is the one k_bwd_wide_rows wrote.
-template <int D, bool WIDE>
+// NODES: on query chunks instead of query tiles (the forward's tables, k_node_rows): the keys of a chunk stream
+// in the order of what its node sees, gathered row by row, so that only its last tiles take a mask, and
+// that mask is arithmetic on positions.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of
+// dimension 64: 336 us on the block map's tiles, 240 on chunks.
+template <int D, bool WIDE, bool NODES>
 __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   using C = Dq<D>;
   using R = RingTile<D>;
@@ -1333,12 +1342,17 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   typedef short v4i16 __attribute__((ext_vector_type(4)));
   typedef short v8i16 __attribute__((ext_vector_type(8)));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int32_t sCol[C::LIST];
+  __shared__ int32_t sCol[NODES ? 1 : C::LIST];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, L = lane & 31, H = lane >> 5;
   const int pair = w >> 1;  // (WIDE) which of the query tiles
   DqTile t;
   int64_t wide_base = 0;
-  if constexpr (!WIDE) {
+  int pos0 = 0;
+  if constexpr (NODES) {
+    if ((int)blockIdx.x >= *a.chunk[WIDE].count) return;  // (the launch is sized by a bound)
+    const int32_t* d = a.chunk[WIDE].desc + (size_t)blockIdx.x * 8;
+    t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6], pos0 = d[7];
+  } else if constexpr (!WIDE) {
     t = dq_tile(a);
   } else {
     const int groups = a.wide_list[a.total_qtiles];
@@ -1362,9 +1376,24 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) dQ[db][e] = 0.f;
   TileList<C::LIST> tl;
-  tl.col = WIDE ? a.wide_col + wide_base : a.qtile_col + t.c0;
-  tl.template fill<NT>(sCol, t.N);
-  __syncthreads();
+  if constexpr (!NODES) {
+    tl.col = WIDE ? a.wide_col + wide_base : a.qtile_col + t.c0;
+    tl.template fill<NT>(sCol, t.N);
+    __syncthreads();
+  }
+  // NODES: the runs of the chunk's node, run e in lane e {first position, token - position}; where the issue
+  // cursor is in them; the tokens of its own node in front of this lane's row
+  const int anc = t.nbase, n_pos = t.nbase + min(t.row0 + (WIDE ? BM * NPAIR : BM), t.T);
+  int run_pos = 0, run_delta = 0, run_at = 0, run_end = 0, run_d = 0, depth = 0;
+  if constexpr (NODES) {
+    const int2 run = ((const int2*)a.runs)[t.c0 + lane];
+    run_pos = run.x;
+    run_delta = run.y;
+    depth = a.pos_ids[cu + min(me.i, T - 1)] - pos0;
+    asm volatile("" ::"v"(run_pos), "v"(run_delta), "v"(depth));
+    run_d = __builtin_amdgcn_readlane(run_delta, 0);
+    run_end = __builtin_amdgcn_readlane(run_pos, 1);
+  }
   const int NF = t.nfast;  // entries 0 .. NF - 1 of the list: every pair visible, inside the sequence
 
   // ---- loads of one stage: wave w fetches blocks w and w + NW of the K tile and of the V tile; for
@@ -1380,6 +1409,28 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   };
   auto prepare_issue = [&](int n, int n_end) __attribute__((always_inline)) {
     IssueCtx c;
+    if constexpr (NODES) {
+      c.kb = a.k + hk * D;
+      c.vb = a.v + hk * D;
+      const int last = min(n * BN + BN, n_pos) - 1;
+      int tok[NPB], pos[NPB];
+#pragma unroll
+      for (int i = 0; i < NPB; ++i) {  // (positions past the end re-read the last one and are masked)
+        pos[i] = min(n * BN + R::RPB * (w + NW * i) + rsub, last);
+        tok[i] = n < n_end ? pos[i] + run_d : cu;  // (past the end of the walk: any row, never consumed)
+      }
+      while (n < n_end && run_end <= last) {  // (wave-uniform) the tile reaches into the next run
+        run_at = run_at + 1;
+        const int from = run_end;
+        run_d = __builtin_amdgcn_readlane(run_delta, run_at);
+        run_end = run_at < 63 ? __builtin_amdgcn_readlane(run_pos, run_at + 1) : INT32_MAX;
+#pragma unroll
+        for (int i = 0; i < NPB; ++i) tok[i] = pos[i] >= from ? pos[i] + run_d : tok[i];
+      }
+#pragma unroll
+      for (int i = 0; i < NPB; ++i) c.voff[i] = (uint32_t)tok[i] * row_stride + chunk8;
+      return c;
+    }
     const int kv = n < n_end ? tl.tile(n) : 0;  // (past the end of the walk: the sequence's first tile, never consumed)
     const int j0 = kv * BN, n_in = min(BN, T - j0);
     const size_t slab = ((size_t)(cu + j0) * a.hkv + hk) * D;
@@ -1406,8 +1457,8 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   const float sc = a.sc, nl = -me.lse2, dl = me.dl;
   const int nq = me.ni, iq_row = me.i;
   const bool row_ok = me.row_ok;
-  const uint64_t* const vis_row = a.node_vis + (int64_t)(t.nbase + nq) * a.W;
-  const uint64_t vis0 = me.vis0, vis1 = a.W > 1 ? vis_row[1] : 0;  // (sequences with more than 128 nodes fetch the word they need)
+  const uint64_t* const vis_row = NODES ? a.node_vis : a.node_vis + (int64_t)(t.nbase + nq) * a.W;
+  const uint64_t vis0 = NODES ? 0 : me.vis0, vis1 = !NODES && a.W > 1 ? vis_row[1] : 0;  // (sequences with more than 128 nodes fetch the word they need)
   asm volatile("" ::"v"(vis0), "v"(vis1));  // (their arrival belongs here, not between the ring's loads)
   auto word_of = [&](uint32_t n) __attribute__((always_inline)) -> uint64_t { return n < 64 ? vis0 : n < 128 ? vis1 : vis_row[n >> 6]; };  // (n is wave-uniform)
 
@@ -1417,7 +1468,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   // 32 hh + 8 (e / 4) + e % 4 belongs to element e of half hh, i.e. to key 64 kt + 4 H + that number)
   auto pipelined_tile = [&](auto msk_c, int cs, const IssueCtx& ictx, int is, uint32_t vis_lo, uint32_t vis_hi) __attribute__((always_inline)) {
     constexpr bool MSK = decltype(msk_c)::value;
-    constexpr int LPS = 2 * NPB + (MSK ? 1 : 0), PFM = PF;
+    constexpr int LPS = 2 * NPB + (MSK && !NODES ? 1 : 0), PFM = PF;
     const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB;
     const uint32_t ra[2] = {sbase + roff[0], sbase + roff[1]}, ta = sbase + toff;
     bf16x8 op[NSLOT];
@@ -1487,7 +1538,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
 
   // ---- the pipelined walk over entries n0 .. n1 - 1 of the tile list
   auto ring_loop = [&](auto msk_c, int n0, int n1) __attribute__((always_inline)) {
-    constexpr int LPS = 2 * NPB + (decltype(msk_c)::value ? 1 : 0);
+    constexpr int LPS = 2 * NPB + (decltype(msk_c)::value && !NODES ? 1 : 0);
     if (n0 >= n1) return;
     int in = n0;  // list entry whose loads are issued next
 #pragma unroll 1
@@ -1503,7 +1554,13 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
     for (int n = n0; n < n1; ++n, ++in) {
       const IssueCtx ic = prepare_issue(in, n1);
       uint64_t vis = 0;
-      if constexpr (decltype(msk_c)::value) {
+      if constexpr (decltype(msk_c)::value && NODES) {
+        // the positions in front of the group, and those of the row's own node up to its own
+        auto first_bits = [](int c) { return c >= 64 ? ~0ull : c <= 0 ? 0ull : (1ull << c) - 1; };
+        const int own = anc + iq_row - n * BN;  // the row's position inside the tile
+        vis = first_bits(anc - n * BN) | (first_bits(own + 1) & ~first_bits(own - depth));
+        vis = row_ok ? vis >> (4 * H) : 0ull;
+      } else if constexpr (decltype(msk_c)::value) {
         // the keys of the tile that this lane's row sees: own node up to the row itself
         // (WIDE: none at all when the wave pair's own query tile does not see the key tile -- the
         // few such tiles along the diagonal are multiplied through with zeros)
@@ -1526,9 +1583,13 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   dq_store<D>(a, me, H, dQ);
 }
 template <bool WIDE>
-__global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE>(a); }
+__global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE, false>(a); }
 template <bool WIDE>
-__global__ void __launch_bounds__(256, 2) k_bwd64_dq(BwdArgs a) { dq_ring_body<64, WIDE>(a); }
+__global__ void __launch_bounds__(256, 2) k_bwd64_dq(BwdArgs a) { dq_ring_body<64, WIDE, false>(a); }
+template <bool WIDE>
+__global__ void __launch_bounds__(512) k_nodes_dq2(BwdArgs a) { dq_ring_body<128, WIDE, true>(a); }
+template <bool WIDE>
+__global__ void __launch_bounds__(256, 2) k_nodes64_dq(BwdArgs a) { dq_ring_body<64, WIDE, true>(a); }
 
 template <int D, int HG>
 int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
@@ -1559,22 +1620,26 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
   constexpr int RPB = 256 / (D / 8);  // rows per workgroup of k_bwd_delta
   hipLaunchKernelGGL((k_bwd_delta<D>), dim3((unsigned)((a.total_rows + RPB - 1) / RPB)), dim3(256), 0, stream, a);
   const int total_tokens = (int)(a.total_rows / a.hq);
-  hipLaunchKernelGGL(k_bwd_tokvis, dim3((unsigned)((total_tokens + 255) / 256)), dim3(256), 0, stream, a, total_tokens);
+  if (!a.runs || bwd_first_version())
+    hipLaunchKernelGGL(k_bwd_tokvis, dim3((unsigned)((total_tokens + 255) / 256)), dim3(256), 0, stream, a, total_tokens);
   DAG_LAUNCH_CHECK();
   int rc;
   if (!bwd_first_version()) {
     // the heads left over by the groups of NPAIR take NPAIR query tiles each
     constexpr int NPAIR = Dq<D>::NPAIR, sm2 = Dq<D>::NST * Dq<D>::STAGEB;
     const int wide = a.G - a.dq_narrow;
-    auto* const one_tile = D == 128 ? k_bwd_dq2<false> : k_bwd64_dq<false>;
-    auto* const many_tiles = D == 128 ? k_bwd_dq2<true> : k_bwd64_dq<true>;
+    const bool nodes = a.runs != nullptr;
+    auto* const one_tile = D == 128 ? (nodes ? k_nodes_dq2<false> : k_bwd_dq2<false>) : nodes ? k_nodes64_dq<false> : k_bwd64_dq<false>;
+    auto* const many_tiles = D == 128 ? (nodes ? k_nodes_dq2<true> : k_bwd_dq2<true>) : nodes ? k_nodes64_dq<true> : k_bwd64_dq<true>;
     if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
         hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
     if (a.dq_narrow > 0)
-      hipLaunchKernelGGL(one_tile, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)((a.dq_narrow + NPAIR - 1) / NPAIR)),
+      hipLaunchKernelGGL(one_tile, dim3((unsigned)(nodes ? a.chunk_slots[0] : total_qtiles), (unsigned)a.hkv, (unsigned)((a.dq_narrow + NPAIR - 1) / NPAIR)),
                          dim3(128 * NPAIR), sm2, stream, a);
-    if (wide > 0) {
+    if (wide > 0 && nodes) {
+      hipLaunchKernelGGL(many_tiles, dim3((unsigned)a.chunk_slots[1], (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
+    } else if (wide > 0) {
       hipLaunchKernelGGL(k_bwd_wide_rows<NPAIR>, dim3((unsigned)total_qtiles), dim3(64), 0, stream, a);
       const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
       hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
@@ -1807,6 +1872,26 @@ extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t h
   return n + bwd_wide_list_bytes(m, hq, hkv, head_dim);
 }
 
+// dQ on query chunks (see launch_d of the forward for where they pay).  Their tables are built in dK, which the
+// dQ kernels neither read nor write and the dK / dV kernels, started behind them, overwrite whole.
+static bool bwd_dq_on_chunks(const dag_meta_t* m, const BwdArgs& a, int32_t head_dim) {
+  const int64_t T = m->sizes.total_tokens, n = m->sizes.total_nodes;
+  if (!m->node_tok_start || !m->node_pos_start || !m->pos_ids || n < 1 || m->words_per_node > 2 || bwd_first_version()) return false;
+  const size_t dk_bytes = (size_t)T * a.hkv * head_dim * 2;
+  if (dk_bytes > UINT32_MAX || DAG_SCHED_INTS * 4 + prefill_node_table_bytes(T, n) > dk_bytes) return false;  // (row offsets are 32-bit)
+  auto apart = [&](const void* p, size_t bytes) {
+    return (const char*)p + bytes <= (const char*)a.dk || (const char*)a.dk + dk_bytes <= (const char*)p;
+  };
+  const size_t q_bytes = (size_t)a.total_rows * head_dim * 2;
+  if (!apart(a.q, q_bytes) || !apart(a.dout, q_bytes) || !apart(a.out, q_bytes) || !apart(a.dq, q_bytes) ||
+      !apart(a.k, dk_bytes) || !apart(a.v, dk_bytes) || !apart(a.lse, (size_t)a.total_rows * 4))
+    return false;
+  // Forward and backward of 4 x 64 nodes of 24 / 32 / 64 / 144 tokens on average, block map : chunks: 32 / 8 heads of
+  // dimension 128 1.06 / 1.05 / 1.06 / 1.05, 16 / 8 heads 0.93 / 0.90 / 1.00 / 1.08 (chunks of 256 rows), 16 / 8
+  // heads of dimension 64 1.09 / 1.05 / 1.10 / 1.07.
+  return T >= (head_dim == 128 && a.dq_narrow < a.G ? 64 : 16) * n;
+}
+
 extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const void* k, const void* v, const void* out,
                                     const void* dout, const float* lse, void* dq, void* dk, void* dv, int32_t hq,
                                     int32_t hkv, int32_t head_dim, float softmax_scale, dag_dtype_t dtype, void* ws,
@@ -1872,6 +1957,26 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.total_rows = (long)m->sizes.total_tokens * hq;
   a.scale = softmax_scale; a.sc = softmax_scale * LOG2E;
   hipStream_t s = (hipStream_t)stream;
+  a.runs = nullptr;
+  if (bwd_dq_on_chunks(m, a, head_dim)) {
+    PrefillArgs p = {};
+    p.n_seqs = m->n_seqs; p.W = m->words_per_node;
+    p.total_tokens = m->sizes.total_tokens; p.total_nodes = m->sizes.total_nodes;
+    p.cu_seqlens = m->cu_seqlens; p.node_start = m->node_start; p.tok_node = m->tok_node; p.node_vis = m->node_vis;
+    p.node_tok_start = m->node_tok_start; p.node_pos_start = m->node_pos_start;
+    p.sched = (int32_t*)dk;
+    prefill_node_tables(p, p.sched + DAG_SCHED_INTS);
+    const int wide = head_dim == 128 ? 2 : 1;  // chunks of NPAIR x 64 rows
+    int rc = a.dq_narrow > 0 ? launch_chunk_tables(p, 0, s) : DAG_OK;
+    if (rc == DAG_OK && a.dq_narrow < a.G) rc = launch_chunk_tables(p, wide, s);
+    if (rc != DAG_OK) return rc;
+    for (int i = 0; i < 2; ++i) {
+      a.chunk[i] = p.chunk[i ? wide : 0];
+      a.chunk_slots[i] = chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[i ? wide : 0]);
+    }
+    a.runs = p.node_runs;
+    a.pos_ids = m->pos_ids;
+  }
   return head_dim == 128 ? launch_bwd<128>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
                          : launch_bwd<64>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
 }

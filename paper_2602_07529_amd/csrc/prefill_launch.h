@@ -67,6 +67,17 @@ inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes
   return n;
 }
 
+// Points the node tables of `a` into the memory at t (8-byte aligned, prefill_node_table_bytes of it).
+inline void prefill_node_tables(PrefillArgs& a, int32_t* t) {
+  a.node_runs = t;
+  t += a.total_nodes * 128;
+  for (int i = 0; i < DAG_CHUNK_SIZES; ++i) {
+    const int64_t n = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[i]);
+    a.chunk[i] = {t, t + 62, t + 62 + n, t + 62 + 9 * n};
+    t += 62 + 17 * n;
+  }
+}
+
 // Workspace of the bf16 path behind the transposed V: counters, then the tables above.
 inline size_t prefill_bf16_table_bytes(int64_t total_qtiles, int64_t csr_capacity) {
   return (size_t)(DAG_SCHED_INTS + 64 + 17 * total_qtiles + csr_capacity) * 4;
@@ -81,6 +92,8 @@ struct PagedPrefillArgs {
   const int32_t *q_off, *ctx_page_off, *ctx_pages, *ctx_page_len, *own_page, *own_len;
 };
 int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream);
+
+int launch_chunk_tables(const PrefillArgs& a, int i, hipStream_t stream);  // of the chunks of DAG_CHUNK_ROWS[i] rows
 
 int launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t stream);
 int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_t stream);  // V -> workspace copy

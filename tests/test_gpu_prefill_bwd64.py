@@ -29,6 +29,19 @@ def test_bwd_head_dim_64_head_groupings(hq, hkv):
     _check_against_oracle(dag_list, inputs, grads)
 
 
+# nodes long enough for query chunks, lists of runs over one and two visibility words
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_nodes,hq,hkv,d", [(20, 5, 1, 128), (64, 4, 1, 64), (65, 3, 1, 64), (100, 6, 1, 128), (128, 2, 1, 64)])
+def test_bwd_dq_on_chunks(n_nodes, hq, hkv, d):
+    rng = np.random.Generator(np.random.PCG64(6800 + n_nodes))
+    alternating = [[u for u in range(v) if u % 2 == v % 2] for v in range(n_nodes)]
+    dag_list = [(np.asarray(rng.integers(17, 30, n_nodes), dtype=np.int32), dags.bits_from_sets(alternating)),
+                dags.random_dag(rng, n_nodes=n_nodes, depth=6, len_lo=10, len_hi=50)[:2],
+                dags.fork_join(130, [40, 64, 3, 150, 63], 70)]
+    inputs, grads = _forward_backward(dag_list, hq, hkv, d, 6900 + n_nodes)
+    _check_against_oracle(dag_list, inputs, grads)
+
+
 # a workspace without room for the tile lists of left-over heads is still taken
 @pytest.mark.gpu
 @pytest.mark.parametrize("hq,hkv", [(1, 1), (5, 1), (6, 2)])
@@ -57,6 +70,17 @@ def test_bwd_visibility_words(n_nodes, hq, hkv, d):
     dag_list = [dags.random_dag(rng, n_nodes=n_nodes, depth=7, len_lo=1, len_hi=6)[:2], dags.fork_join(90, [30] * 3, 20)]
     inputs, grads = _forward_backward(dag_list, hq, hkv, d, 6700 + n_nodes + hq)
     _check_against_oracle(dag_list, inputs, grads)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_generated_code_of_the_chunk_kernels(tmp_path):
+    seen = 0
+    for name, lines in _kernels(_assembly("prefill_bwd", tmp_path), "k_nodes"):
+        _, bad = _conflicts_of_kernel(lines)
+        assert not bad, "%s: %s" % (name, bad[:3])
+        assert not any("scratch_" in l for l in lines), name
+        seen += 1
+    assert seen == 4
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
