@@ -18,6 +18,8 @@
 //                 head) = 64 slots (described at the kernel); nothing is accumulated through
 //                 atomics, so the results do not depend on the order of execution
 //   k_bwd64_dq, k_bwd64_dkv   the same two for head dimension 64
+//   k_nodes_dq2, k_nodes64_dq   dQ on the forward's query chunks instead of the block map's tiles
+//   k_nodes_dkv2, k_nodes64_dkv   dK/dV with the query rows that see the keys as one compact stream
 //   k_bwd_dq, k_bwd_dkv   the first versions (tiles staged through registers, compiler-scheduled),
 //                 reached by a development switch only
 // Register layout of a 32x32 MFMA result C = A B:  lane (L, H) = (lane % 32, lane / 32) holds
@@ -72,6 +74,9 @@ struct BwdArgs {
   ChunkTables chunk[2];
   int64_t chunk_slots[2];
   const int32_t *runs, *pos_ids;
+  // dK / dV on streams of query rows
+  bool dkv_stream;
+  const int32_t* node_tok_start;
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -858,7 +863,12 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int D>
+// NODES: the query rows come as one compact stream instead of the block map's query tiles: the rows of the nodes
+// that see every node of the workgroup's 128 keys (and of the last key's node the rows behind the keys), then
+// the rows of the other nodes that see one of them, the keys' own among them, each part in token order,
+// gathered row by row.  The tiles made of the first part alone run without tests.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of dimension
+// 64: 571 us on the block map's tiles, 529 so; 4 x 4608 fork-join, 32 / 8 heads of dimension 128: 1381 -> 1303 us.
+template <int D, bool NODES>
 __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   using C = Dkv<D>;
   using R = RingTile<D>;
@@ -870,8 +880,8 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   typedef short v8i16 __attribute__((ext_vector_type(8)));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int KIND_WORDS = (MAX_QT_LDS + 63) / 64;
-  __shared__ uint8_t sFlag[MAX_QT_LDS];  // block-map column of the pair: flag of tile 0 | flag of tile 1 << 2
-  __shared__ uint64_t sKind[2][KIND_WORDS];
+  __shared__ uint8_t sFlag[NODES ? 1 : MAX_QT_LDS];  // block-map column of the pair: flag of tile 0 | flag of tile 1 << 2
+  __shared__ uint64_t sKind[2][NODES ? 1 : KIND_WORDS];
   const int hk = blockIdx.x % a.hkv, kt = a.kt_order[blockIdx.x / a.hkv];  // heaviest pairs first
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int ktl = kt - a.ktile_start[b];
@@ -897,7 +907,10 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   // i.e. the key's column of the sequence's visibility matrix (the first 128 nodes of it; sequences
   // with more take every word they need from memory)
   uint64_t seen_by[2] = {0, 0};
-  if (a.W <= 2) {
+  // NODES: the stream as runs of consecutive tokens {first position, token - position} (at most 129); its length and that of its first part, its tiles without tests; the position of this lane's key in it
+  __shared__ int2 sRun[NODES ? 144 : 1];  // (1152 bytes: the ring behind it stays on a multiple of 128; 16 bytes off it cost 5 %)
+  int n_pos = 0, n_first = 0, n_fast = 0, key_pos = 0, n_runs = 0;
+  if (NODES || a.W <= 2) {
     const int n_nodes = a.node_start[b + 1] - nbase;
     uint64_t word[2][2];  // word y of node 64 x + lane
 #pragma unroll
@@ -914,6 +927,62 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         const uint64_t column = __builtin_amdgcn_ballot_w64(((n < 64 ? word[x][0] : word[x][1]) >> (n & 63)) & 1ull);
         if (nj == n) seen_by[x] = column;
       }
+    }
+    if constexpr (NODES) {
+      const int u0 = a.tok_node[cu + ktl * BN], u1 = a.tok_node[cu + min(ktl * BN + 2 * BN, T) - 1];  // the keys' nodes
+      const int key0 = ktl * BN, key1 = min(key0 + 2 * BN, T);
+      // Rows [from, to) of node 64 x + lane in either part.  Of the keys' own nodes the rows in front of the
+      // first key see none of them, and those behind the last key what their node sees.
+      int from[2][2], to[2][2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const int n = 64 * x + lane;
+        const int first = n < n_nodes ? a.node_tok_start[nbase + n] : T, end = n + 1 < n_nodes ? a.node_tok_start[nbase + n + 1] : T;
+        // bits u0 .. u1 of the node's words
+        uint64_t hit = 0, miss = 0;
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const int lo = max(u0 - 64 * y, 0), hi = min(u1 - 64 * y, 63);
+          const uint64_t range = lo <= hi ? (~0ull >> (63 - hi)) & (~0ull << lo) : 0ull;
+          hit |= word[x][y] & range;
+          miss |= ~word[x][y] & range;
+        }
+        const int begin = max(first, key0), stop = n < n_nodes && hit != 0 ? end : begin;
+        const int split = miss != 0 || n < u1 ? stop : n == u1 ? min(key1, stop) : begin;  // the second part's rows lie in front of it
+        from[0][x] = split, to[0][x] = stop;
+        from[1][x] = begin, to[1][x] = split;
+      }
+#pragma unroll
+      for (int part = 0; part < 2; ++part) {
+        int end_before = -1;  // of the part's last node in the word in front
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const int mine = to[part][x] - from[part][x];
+          int incl = mine;
+          for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+          }
+          const int pos = n_pos + incl - mine;
+          n_pos += __builtin_amdgcn_readlane(incl, 63);
+          const int my_end = mine > 0 ? to[part][x] : -1;
+          int prev = __shfl_up(my_end, 1);
+          if (lane == 0) prev = end_before;
+          end_before = __builtin_amdgcn_readlane(my_end, 63);
+          const uint64_t starts = __builtin_amdgcn_ballot_w64(mine > 0 && prev != from[part][x]);
+          const int own = __shfl(pos - from[part][x], nj & 63);
+          if (part == 1 && nj >> 6 == x) key_pos = own + jc;
+          if (w == 0 && (starts >> lane) & 1)
+            sRun[n_runs + __builtin_popcountll(starts & ((1ull << lane) - 1))] = int2{pos, cu + from[part][x] - pos};
+          n_runs += __builtin_popcountll(starts);
+        }
+        if (part == 0) {
+          n_first = n_pos;
+          n_fast = n_pos / BM;
+        }
+      }
+      // every key of the pair exists in a tile without tests (else the words of the lanes say so)
+      if ((ktl + 2) * BN > T) n_fast = 0;
     }
   }
   auto word_of = [&](uint32_t n) __attribute__((always_inline)) -> uint64_t {  // (n is wave-uniform)
@@ -939,7 +1008,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   // The column is kept in LDS as the flags and as one bitmap per kind of iteration (bit qt % 64 of
   // word qt / 64: tile qt has a visible pair and is of that kind), so that a walk finds its next
   // tile with one 64-bit read per 64 tiles instead of one probe per tile.
-  const bool flags_in_lds = QT <= MAX_QT_LDS;
+  const bool flags_in_lds = !NODES && QT <= MAX_QT_LDS;
   if (flags_in_lds) {
     for (int x0 = 0; x0 < QT; x0 += 256) {
       const int x = x0 + tid;
@@ -1014,8 +1083,54 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     uint32_t voff[NPB];        // element offset of this lane's chunk in block w + 4 i (rows past the sequence end re-read its last row)
     const float* rd;           // this lane's row-data word
   };
+  // NODES: the tile whose loads are issued next: element offsets of this lane's chunks, the token of its row
+  // data, where the tile is in the runs
+  uint32_t it_voff[NPB];
+  int it_tok = cu, run_at = 0, run_beg = 0, run_d = 0;
+  auto run_of = [&](int e) __attribute__((always_inline)) {  // (inline assembly for the reason given at pair_flag)
+    uint64_t v;
+    asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(sRun) + 8u * (uint32_t)e) : "memory");
+    return int2{__builtin_amdgcn_readfirstlane((int)(uint32_t)v), __builtin_amdgcn_readfirstlane((int)(v >> 32))};
+  };
+  auto enter_run = [&](int e) __attribute__((always_inline)) {
+    const int2 run = run_of(e);
+    run_at = e;
+    run_beg = run.x;
+    run_d = run.y;
+  };
+  // (tiles are entered in descending order, from run n_runs - 1 at the start of a walk)
+  auto enter_tile = [&](int n) __attribute__((always_inline)) {
+    const int p0 = n * BM, last = min(p0 + BM, n_pos) - 1;
+    while (run_beg > last) enter_run(run_at - 1);
+    int pos[NPB], tok[NPB];
+    const int rd_pos = min(p0 + lane, last);  // (positions past the end re-read the last one and are masked)
+    it_tok = rd_pos + run_d;
+#pragma unroll
+    for (int i = 0; i < NPB; ++i) {
+      pos[i] = min(p0 + R::RPB * (w + 4 * i) + rsub, last);
+      tok[i] = pos[i] + run_d;
+    }
+    while (run_beg > p0) {  // (wave-uniform) the tile begins in the run in front
+      const int to = run_beg;
+      enter_run(run_at - 1);
+      it_tok = rd_pos < to ? rd_pos + run_d : it_tok;
+#pragma unroll
+      for (int i = 0; i < NPB; ++i) tok[i] = pos[i] < to ? pos[i] + run_d : tok[i];
+    }
+#pragma unroll
+    for (int i = 0; i < NPB; ++i) it_voff[i] = (uint32_t)tok[i] * row_stride + chunk8;
+  };
   auto prepare_issue = [&](int qt, int g) __attribute__((always_inline)) {
     IssueCtx c;
+    if constexpr (NODES) {  // (past the end of the walk: its last tile once more, never consumed)
+      const int h = hk * a.G + g;
+      c.qb = a.q + h * D;
+      c.dob = a.dout + h * D;
+#pragma unroll
+      for (int i = 0; i < NPB; ++i) c.voff[i] = it_voff[i];
+      c.rd = rd_src + ((size_t)it_tok * rd_mul + rd_hmul * h);
+      return c;
+    }
     const int qv = max(qt, 0);
     const int r0 = qv * BM, n_in = min(BM, T - r0), h = hk * a.G + g;
     const size_t slab = ((size_t)(cu + r0) * a.hq + h) * D;
@@ -1143,19 +1258,32 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     });
   };
 
-  // ---- the walk of one kind of iteration: query tiles from the last one down, the heads of the group inside
+  // ---- the walk of one kind of iteration: query tiles from the last one down (as do the other workgroups of the
+  // KV head: they share the rows of the sequence's end in L2), the heads of the group inside
   auto ring_loop = [&](auto msk_c) __attribute__((always_inline)) {
     constexpr int KIND = decltype(msk_c)::value ? 1 : 0;
+    const int n0 = KIND == 0 ? 0 : n_fast, n1 = KIND == 0 ? n_fast : (n_pos + BM - 1) / BM;  // (NODES)
     auto next_tile = [&](int qt) { return last_of_kind(KIND, qt); };
     auto advance = [&](int& qt, int& g) {
+      if constexpr (NODES) {
+        if (++g == a.G) {
+          g = 0;
+          if (--qt >= n0) enter_tile(qt);
+        }
+        return;
+      }
       if (qt < 0) return;
       if (++g == a.G) {
         g = 0;
         qt = next_tile(qt - 1);
       }
     };
-    int cq = next_tile(QT - 1), cg = 0;  // the iteration being computed
-    if (cq < 0) return;
+    int cq = NODES ? n1 - 1 : next_tile(QT - 1);  // the tile being computed
+    if (NODES ? n0 >= n1 : cq < 0) return;
+    if constexpr (NODES) {
+      enter_run(n_runs - 1);
+      enter_tile(cq);
+    }
     int iq = cq, ig = 0;                 // the iteration whose loads are issued next
 #pragma unroll 1
     for (int st = 0; st < NST - 1; ++st) {
@@ -1171,10 +1299,17 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     // (register classes, at the top of every iteration: the dK / dV accumulators stay in the
     // accumulation registers over the whole loop; without the hint the allocator moves three of
     // the eight back and forth every iteration)
-    while (cq >= 0) {  // one query tile: (with masks) its visibility word once, then an iteration per head
+    while (NODES ? cq >= n0 : cq >= 0) {  // one query tile: (with masks) its visibility word once, then an iteration per head
       bool active = true;  // a visible pair in this wave's key tile
       uint64_t vis = 0;
-      if constexpr (KIND == 1) {
+      if constexpr (KIND == 1 && NODES) {
+        const int at = key_pos - cq * BM;  // the key's own row in the tile: the rows of its node see it from there on
+        const int sure = n_first - cq * BM;    // rows of the first part: every key sees them
+        const uint64_t own = (at <= 0 ? ~0ull : at >= 64 ? 0ull : ~0ull << at) | (sure >= 64 ? ~0ull : sure <= 0 ? 0ull : (1ull << sure) - 1);
+        vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + RD + 512, lane, (uint32_t)nj, own, n_pos - cq * BM, word_of);
+        active = __builtin_amdgcn_ballot_w64(key_ok && vis != 0) != 0;
+        vis = key_ok ? vis >> (4 * H) : 0ull;
+      } else if constexpr (KIND == 1) {
         active = ((pair_flag(cq) >> (2 * (w >> 1))) & 3) != 0;
         if (active) {
           // the rows of tile cq that this lane's key is visible to: own node from the key's row on
@@ -1201,7 +1336,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         cs = cs + 1 == NST ? 0 : cs + 1;
         is = is + 1 == NST ? 0 : is + 1;
       }
-      cq = next_tile(cq - 1);
+      cq = NODES ? cq - 1 : next_tile(cq - 1);
     }
     wait_vmcnt_only<0>();  // (the loads past the end of the walk)
     __builtin_amdgcn_s_barrier();  // every wave is done with the ring before the next loop refills it
@@ -1214,8 +1349,10 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   const int j_out = ktl * BN + key;
   dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < T, H, dK, dV);
 }
-__global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) { dkv_ring_body<128>(a); }
-__global__ void __launch_bounds__(256, 2) k_bwd64_dkv(BwdArgs a) { dkv_ring_body<64>(a); }
+__global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) { dkv_ring_body<128, false>(a); }
+__global__ void __launch_bounds__(256, 2) k_bwd64_dkv(BwdArgs a) { dkv_ring_body<64, false>(a); }
+__global__ void __launch_bounds__(256) k_nodes_dkv2(BwdArgs a) { dkv_ring_body<128, true>(a); }
+__global__ void __launch_bounds__(256, 2) k_nodes64_dkv(BwdArgs a) { dkv_ring_body<64, true>(a); }
 
 // Tile lists of the dQ workgroups that take one query head on a group of NQ = four (head dimension
 // 128) or two query tiles (the heads that do not fill a workgroup on one tile): one wave per query
@@ -1659,7 +1796,7 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
   DAG_LAUNCH_CHECK();
   if (!bwd_first_version()) {
     constexpr int sm2 = Dkv<D>::NST * Dkv<D>::STAGEB;
-    auto* const ring = D == 128 ? k_bwd_dkv2 : k_bwd64_dkv;
+    auto* const ring = D == 128 ? (a.dkv_stream ? k_nodes_dkv2 : k_bwd_dkv2) : a.dkv_stream ? k_nodes64_dkv : k_bwd64_dkv;
     if (hipFuncSetAttribute((const void*)ring, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
     hipLaunchKernelGGL(ring, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
@@ -1957,6 +2094,11 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.total_rows = (long)m->sizes.total_tokens * hq;
   a.scale = softmax_scale; a.sc = softmax_scale * LOG2E;
   hipStream_t s = (hipStream_t)stream;
+  a.node_tok_start = m->node_tok_start;
+  // Forward and backward, block map : streams, nodes of 16 / 24 / 32 / 64 / 144 tokens on average: 32 / 8 heads of
+  // dimension 128 1.00 / 1.02 / 1.02 / 1.06 / 1.08, 16 / 8 heads of dimension 64 1.00 / 1.05 / 1.06 / 1.07 / 1.07.
+  a.dkv_stream = m->node_tok_start && m->words_per_node <= 2 && a.total_rows * head_dim <= (long)UINT32_MAX &&
+                 m->sizes.total_tokens >= 16 * m->sizes.total_nodes;  // (row offsets are 32-bit)
   a.runs = nullptr;
   if (bwd_dq_on_chunks(m, a, head_dim)) {
     PrefillArgs p = {};

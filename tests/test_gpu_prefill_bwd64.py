@@ -32,7 +32,7 @@ def test_bwd_head_dim_64_head_groupings(hq, hkv):
 # nodes long enough for query chunks, lists of runs over one and two visibility words
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_nodes,hq,hkv,d", [(20, 5, 1, 128), (64, 4, 1, 64), (65, 3, 1, 64), (100, 6, 1, 128), (128, 2, 1, 64)])
-def test_bwd_dq_on_chunks(n_nodes, hq, hkv, d):
+def test_bwd_on_chunks_and_streams(n_nodes, hq, hkv, d):
     rng = np.random.Generator(np.random.PCG64(6800 + n_nodes))
     alternating = [[u for u in range(v) if u % 2 == v % 2] for v in range(n_nodes)]
     dag_list = [(np.asarray(rng.integers(17, 30, n_nodes), dtype=np.int32), dags.bits_from_sets(alternating)),
@@ -80,7 +80,7 @@ def test_generated_code_of_the_chunk_kernels(tmp_path):
         assert not bad, "%s: %s" % (name, bad[:3])
         assert not any("scratch_" in l for l in lines), name
         seen += 1
-    assert seen == 4
+    assert seen == 6
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
