@@ -160,16 +160,71 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   }
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
+  // A hidden key goes through the products with probability zero, and 0 x Inf or NaN is NaN: where a visited
+  // tile holds a V row that is not finite, rows that do not see it would be lost.  So a wave whose outputs
+  // are not numbers although its row sums are goes over its rows again, key by key, with nothing but the
+  // visible ones (o: this lane's dimensions 64 x + 16 g + 4 e0 .., o[x][e][c], before the division; as long as
+  // every output is a number this costs one comparison for two of them).
+  auto lost = [&](const auto& o, float l_row) __attribute__((always_inline)) {
+    bool nan = false;
+#pragma unroll
+    for (int x = 0; x < X; ++x)
+#pragma unroll
+      for (int e = 0; e < (int)(sizeof(o[0]) / sizeof(f32x4)); ++e)
+        nan |= __builtin_isunordered(o[x][e][0], o[x][e][1]) | __builtin_isunordered(o[x][e][2], o[x][e][3]);
+    return __builtin_amdgcn_ballot_w64(nan && l_row < INFINITY) != 0;
+  };
+  auto visible_keys_only = [&](auto& o, int e0, float m_row) __attribute__((always_inline)) {
+    constexpr int NE = sizeof(o[0]) / sizeof(f32x4);
+#pragma unroll
+    for (int x = 0; x < X; ++x)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) o[x][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int n = 0; n < n_tiles; ++n) {
+      const int j0 = a.col[c0 + n] * TN, j1 = min(j0 + TN, T);
+#pragma unroll 1
+      for (int j = j0; j < j1; ++j) {
+        const int nj = a.tok_node[cu + j];
+        const bool ok = j <= i && ((vis_row[nj >> 6] >> (nj & 63)) & 1);
+        const float* kp = kbase + (size_t)j * stride;
+        const float* vp = (const float*)a.v + ((size_t)(cu + j) * a.hkv + hk) * D + 16 * g + 4 * e0;
+        float s = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT4; ++t) {
+          const f32x4 k4 = *(const f32x4*)(kp + 16 * t);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) s = fmaf(k4[c], q[t][c], s);
+        }
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        const float p = expf(s * a.scale - m_row);
+#pragma unroll
+        for (int x = 0; x < X; ++x)
+#pragma unroll
+          for (int e = 0; e < NE; ++e) {
+            const f32x4 v4 = *(const f32x4*)(vp + 64 * x + 4 * e);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[x][e][c] = ok ? fmaf(p, v4[c], o[x][e][c]) : o[x][e][c];
+          }
+      }
+    }
+  };
   // register e of accumulator (x, c): dimension 64 x + 16 g + 4 e + c of row L
   float* out = (float*)a.out + ((size_t)(cu + ic) * a.hq + head) * D + 16 * g;
   if constexpr (SPLIT == 1) {
+    f32x4 o[X][4];
+#pragma unroll
+    for (int x = 0; x < X; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[x][e] = f32x4{O[x][0][e], O[x][1][e], O[x][2][e], O[x][3][e]};
+    if (lost(o, l)) visible_keys_only(o, 0, m);
     if (i < T) {
       const float inv = 1.f / l;
 #pragma unroll
       for (int x = 0; x < X; ++x)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          *(f32x4*)(out + 64 * x + 4 * e) = f32x4{O[x][0][e] * inv, O[x][1][e] * inv, O[x][2][e] * inv, O[x][3][e] * inv};
+        for (int e = 0; e < 4; ++e) *(f32x4*)(out + 64 * x + 4 * e) = o[x][e] * inv;
       if (a.lse && g == 0) a.lse[(size_t)(cu + i) * a.hq + head] = m + logf(l);
     }
   } else {
@@ -192,14 +247,17 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
       lt += f[y] * sL[y][L];
     }
     const float inv = 1.f / lt;
+    f32x4 o[X][1];
+#pragma unroll
+    for (int x = 0; x < X; ++x) {  // wave w writes dimensions 64 x + 16 g + 4 w ..
+      o[x][0] = f[0] * sO[0][4 * x + w][lane];
+#pragma unroll
+      for (int y = 1; y < 4; ++y) o[x][0] += f[y] * sO[y][4 * x + w][lane];
+    }
+    if (lost(o, lt)) visible_keys_only(o, w, M);
     if (i < T) {
 #pragma unroll
-      for (int x = 0; x < X; ++x) {  // wave w writes dimensions 64 x + 16 g + 4 w ..
-        f32x4 o = f[0] * sO[0][4 * x + w][lane];
-#pragma unroll
-        for (int y = 1; y < 4; ++y) o += f[y] * sO[y][4 * x + w][lane];
-        *(f32x4*)(out + 64 * x + 4 * w) = o * inv;
-      }
+      for (int x = 0; x < X; ++x) *(f32x4*)(out + 64 * x + 4 * w) = o[x][0] * inv;
       if (a.lse && g == 0 && w == 0) a.lse[(size_t)(cu + i) * a.hq + head] = M + logf(lt);
     }
   }

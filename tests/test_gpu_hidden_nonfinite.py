@@ -1,0 +1,69 @@
+"""GPU: what Eq. 3 hides from a row does not reach it, also where it is Inf or NaN and shares a key tile with
+what the row sees.  The rows that do not see such a token are compared with the oracle on clean inputs; the
+rows that see one are not numbers."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dag_oracle as orc
+from paper_2602_07529_amd import binding as B
+from workloads import dags
+from tests.gpu_util import DEV, TOL, build_meta, oracle_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(seed):
+    """Siblings that share key tiles, nodes that start and end inside a tile, rows in front of a bad token of their
+    own node; and the bad tokens: a whole branch, single tokens, the last token of a sequence."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    dag_list = [dags.fork_join(64, [32, 32, 32, 32], 40), dags.fork_join(130, [40, 64, 33, 150, 63], 70),
+                dags.random_dag(rng, n_nodes=24, depth=5, len_lo=20, len_hi=90)[:2], dags.linear_chain([200, 77])]
+    at = np.cumsum([0] + [int(np.sum(L)) for L, _ in dag_list])
+    bad = list(range(64, 96)) + [at[0] + 64 + 32 + 17]                 # first branch of the first sequence, a token of the second
+    bad += [at[1] + 130 + 40 + 63, at[1] + 130 + 40 + 64 + 5]          # two branches of the second
+    bad += [at[2] + int(np.sum(dag_list[2][0])) // 2, at[3] + 150, at[4] - 1]
+    return dag_list, np.asarray(bad), int(at[-1])
+
+
+def _sees_bad(dag_list, bad, T):
+    out, t0 = np.zeros(T, dtype=bool), 0
+    for L, anc in dag_list:
+        Tb = int(np.sum(L))
+        here = bad[(bad >= t0) & (bad < t0 + Tb)] - t0
+        out[t0:t0 + Tb] = orc.explicit_mask(L, anc)[:, here].any(axis=1)
+        t0 += Tb
+    return out
+
+
+def _spoil(v, bad):
+    v = v.clone()
+    for x, t in enumerate(bad):
+        v[t] = (float("nan"), float("inf"), float("-inf"))[x % 3]
+    return v
+
+
+def _check(got, ref, rows, tol):
+    g, r = got.cpu().double().numpy()[rows], ref[rows]
+    assert np.isfinite(g).all(), "%d rows lost" % int((~np.isfinite(g)).reshape(len(g), -1).any(axis=1).sum())
+    scale = max(1.0, float(np.abs(r).max()))
+    assert np.abs(g - r).max() <= tol[0] * scale and np.linalg.norm(g - r) <= tol[1] * np.linalg.norm(r)
+
+
+# fp32: both cuts of the work
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(2, 1, 64, torch.float32), (3, 1, 128, torch.float32), (24, 2, 64, torch.float32),
+                                            (24, 4, 128, torch.float32)])
+def test_hidden_values(hq, hkv, d, dtype):
+    dag_list, bad, T = _batch(hq + d)
+    q, k, v = dags.make_qkv(60 + hq, T, hq, hkv, d, 0.5 if dtype == torch.bfloat16 else 1.0, dtype)
+    ref, ref_lse, _ = oracle_prefill(dag_list, q, k, v, 1e4)
+    _, meta = build_meta(dag_list, hq, hkv, d, dtype)
+    qd, kd, vd = q.to(DEV).clone(), k.to(DEV).clone(), _spoil(v, bad).to(DEV)
+    B.dag_rope_qk(meta.get("pos_ids"), qd, kd, 1e4)
+    out, lse = torch.empty_like(qd), torch.empty(T, hq, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, qd, kd, vd, out, lse)
+    sees = _sees_bad(dag_list, bad, T)
+    assert not torch.isfinite(out[torch.from_numpy(sees).to(DEV)].float()).any(dim=-1).any()
+    _check(out, ref, ~sees, TOL[dtype])
+    assert np.abs(lse.cpu().double().numpy() - ref_lse).max() < (1e-4 if dtype == torch.float32 else 2e-2)
+
