@@ -1657,6 +1657,69 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     TACC(8, t_loop, te0);
     TACC(9, te0, te1);
     TACC(3, te1, te2);
+    // ---- A hidden key goes through the products with probability zero, and 0 x Inf or NaN is NaN: on chunks
+    // the last tiles of an item hold tokens that not all of their rows see (rows of the same chunk further
+    // on, siblings), wherever the nodes begin.  So a wave whose outputs are not numbers although its row
+    // sums are goes over its rows again, key by key, with nothing but the visible ones.  As long as every
+    // output is a number this costs one comparison for two of them; where a visible V is not finite the
+    // outputs stay what they are, and the walk ends once no number is left in the wave.
+    if constexpr (NODES) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        float any = 0.f;  // (maximum, unlike fmaxf, hands a NaN on)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; e += 2)
+            any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(O[r][db][e], O[r][db][e + 1]), any);
+        if (__builtin_amdgcn_ballot_w64(any != any && l[r] + __shfl_xor(l[r], 32) < INFINITY) == 0) continue;
+        u32x4 qr[KSTEPS];  // the row as load_q and scale_q left it (qf holds the next item's by now)
+        const uint16_t* qp = qg + ((size_t)token_of(cur, r) * a.hq + head_of(cur)) * D + 8 * H;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) {
+          const u32x4 raw = *(const u32x4*)(qp + 16 * s);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) qr[s][e] = dag_pack_bf2(dag_bf_lo(raw[e]) * sc, dag_bf_hi(raw[e]) * sc);
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) O[r][db][e] = 0.f;
+        const int own = cur.nstart + min(row_of(cur, r), cur.T - 1);       // the row's own position
+        const int end = cur.nstart + min(cur.row0 + 32 * NRG, cur.T);      // (wave-uniform)
+        int run = 0;
+#pragma unroll 1
+        for (int p = 0; p < end; ++p) {
+          while (run < 63 && a.col[(size_t)(cur.c0 + run + 1) * 2] <= p) ++run;
+          const size_t at = (size_t)(p + a.col[(size_t)(cur.c0 + run) * 2 + 1]) * rowbytes + cur.hk * (D * 2);
+          float s = 0.f;
+#pragma unroll
+          for (int x = 0; x < KSTEPS; ++x) {
+            const u32x4 kr = *(const u32x4*)(kg + at + 32 * x + 16 * H);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = fmaf(dag_bf_hi(kr[e]), dag_bf_hi(qr[x][e]), fmaf(dag_bf_lo(kr[e]), dag_bf_lo(qr[x][e]), s));
+          }
+          s += __shfl_xor(s, 32);
+          const bool ok = p < cur.nstart || (p <= own && p >= own - rdepth[r]);
+          const float pr = __builtin_amdgcn_exp2f(s - M[r]);
+          bool number = false;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {  // dimensions 32 db + 8 r4 + 4 H .. + 3
+              const u32x2 vr = *(const u32x2*)(vtg + at + 64 * db + 16 * r4 + 8 * H);
+              const float v4[4] = {dag_bf_lo(vr[0]), dag_bf_hi(vr[0]), dag_bf_lo(vr[1]), dag_bf_hi(vr[1])};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float before = O[r][db][4 * r4 + e], o = ok ? fmaf(pr, v4[e], before) : before;
+                O[r][db][4 * r4 + e] = o;
+                number |= o == o;
+              }
+            }
+          if (__builtin_amdgcn_ballot_w64(number) == 0) break;
+        }
+      }
+    }
     // ---- output.  A lane holds one row in 8-byte pieces (four consecutive dimensions).  Stored
     // as they are, a store instruction writes 16 bytes of each of 32 rows, 4096 such fragments per
     // item, and the stores took 3.7 us of the item (the compute units take the fragments one by

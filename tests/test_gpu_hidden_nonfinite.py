@@ -50,9 +50,10 @@ def _check(got, ref, rows, tol):
     assert np.abs(g - r).max() <= tol[0] * scale and np.linalg.norm(g - r) <= tol[1] * np.linalg.norm(r)
 
 
-# fp32: both cuts of the work
+# fp32: both cuts of the work; bf16: every launch shape on query chunks (nodes of 16 tokens and more)
 @pytest.mark.parametrize("hq,hkv,d,dtype", [(2, 1, 64, torch.float32), (3, 1, 128, torch.float32), (24, 2, 64, torch.float32),
-                                            (24, 4, 128, torch.float32)])
+                                            (24, 4, 128, torch.float32), (4, 1, 128, torch.bfloat16), (7, 1, 128, torch.bfloat16),
+                                            (56, 8, 128, torch.bfloat16), (7, 1, 64, torch.bfloat16), (56, 8, 64, torch.bfloat16)])
 def test_hidden_values(hq, hkv, d, dtype):
     dag_list, bad, T = _batch(hq + d)
     q, k, v = dags.make_qkv(60 + hq, T, hq, hkv, d, 0.5 if dtype == torch.bfloat16 else 1.0, dtype)
