@@ -22,6 +22,8 @@
 // 448 tokens, 4 heads, D 64: 184 -> 15 us; 1024 tokens, 32 heads, D 128: 1588 -> 160 us; 3328
 // tokens, 32 heads, D 128: 9180 -> 898 us = 94 TFLOP/s (a large fp32 matrix product reaches 154).
 // What is left: the softmax between the two products, two waves per SIMD at 254 registers.
+#include <type_traits>
+
 #include "common.h"
 #include "prefill_launch.h"
 
@@ -163,23 +165,27 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   // A hidden key goes through the products with probability zero, and 0 x Inf or NaN is NaN: where a visited
   // tile holds a V row that is not finite, rows that do not see it would be lost.  So a wave whose outputs
   // are not numbers although its row sums are goes over its rows again, key by key, with nothing but the
-  // visible ones (o: this lane's dimensions 64 x + 16 g + 4 e0 .., o[x][e][c], before the division; as long as
-  // every output is a number this costs one comparison for two of them).
-  auto lost = [&](const auto& o, float l_row) __attribute__((always_inline)) {
-    bool nan = false;
+  // visible ones; as long as every output is a number this costs a maximum over them (one that, unlike
+  // fmaxf, hands a NaN on).  o(x, e, c): this lane's output dimension 64 x + 16 g + 4 (e0 + e) + c before the
+  // division, set(x, e, c, value) replaces it.
+  auto nan_among = [&](auto ne, auto&& o) __attribute__((always_inline)) {
+    float any = 0.f;
 #pragma unroll
     for (int x = 0; x < X; ++x)
 #pragma unroll
-      for (int e = 0; e < (int)(sizeof(o[0]) / sizeof(f32x4)); ++e)
-        nan |= __builtin_isunordered(o[x][e][0], o[x][e][1]) | __builtin_isunordered(o[x][e][2], o[x][e][3]);
-    return __builtin_amdgcn_ballot_w64(nan && l_row < INFINITY) != 0;
+      for (int e = 0; e < decltype(ne)::value; ++e)
+#pragma unroll
+        for (int c = 0; c < 4; c += 2) any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(o(x, e, c), o(x, e, c + 1)), any);
+    return any != any;
   };
-  auto visible_keys_only = [&](auto& o, int e0, float m_row) __attribute__((always_inline)) {
-    constexpr int NE = sizeof(o[0]) / sizeof(f32x4);
+  auto visible_keys_only = [&](auto ne, int e0, float m_row, auto&& o, auto&& set) __attribute__((always_inline)) {
+    constexpr int NE = decltype(ne)::value;
 #pragma unroll
     for (int x = 0; x < X; ++x)
 #pragma unroll
-      for (int e = 0; e < NE; ++e) o[x][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) set(x, e, c, 0.f);
 #pragma unroll 1
     for (int n = 0; n < n_tiles; ++n) {
       const int j0 = a.col[c0 + n] * TN, j1 = min(j0 + TN, T);
@@ -205,7 +211,7 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
           for (int e = 0; e < NE; ++e) {
             const f32x4 v4 = *(const f32x4*)(vp + 64 * x + 4 * e);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) o[x][e][c] = ok ? fmaf(p, v4[c], o[x][e][c]) : o[x][e][c];
+            for (int c = 0; c < 4; ++c) set(x, e, c, ok ? fmaf(p, v4[c], o(x, e, c)) : o(x, e, c));
           }
       }
     }
@@ -213,18 +219,17 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   // register e of accumulator (x, c): dimension 64 x + 16 g + 4 e + c of row L
   float* out = (float*)a.out + ((size_t)(cu + ic) * a.hq + head) * D + 16 * g;
   if constexpr (SPLIT == 1) {
-    f32x4 o[X][4];
-#pragma unroll
-    for (int x = 0; x < X; ++x)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[x][e] = f32x4{O[x][0][e], O[x][1][e], O[x][2][e], O[x][3][e]};
-    if (lost(o, l)) visible_keys_only(o, 0, m);
+    auto o = [&](int x, int e, int c) __attribute__((always_inline)) { return O[x][c][e]; };
+    const std::integral_constant<int, 4> ne;
+    if (__builtin_amdgcn_ballot_w64(nan_among(ne, o) && l < INFINITY) != 0)
+      visible_keys_only(ne, 0, m, o, [&](int x, int e, int c, float value) __attribute__((always_inline)) { O[x][c][e] = value; });
     if (i < T) {
       const float inv = 1.f / l;
 #pragma unroll
       for (int x = 0; x < X; ++x)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) *(f32x4*)(out + 64 * x + 4 * e) = o[x][e] * inv;
+        for (int e = 0; e < 4; ++e)
+          *(f32x4*)(out + 64 * x + 4 * e) = f32x4{O[x][0][e] * inv, O[x][1][e] * inv, O[x][2][e] * inv, O[x][3][e] * inv};
       if (a.lse && g == 0) a.lse[(size_t)(cu + i) * a.hq + head] = m + logf(l);
     }
   } else {
@@ -247,17 +252,20 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
       lt += f[y] * sL[y][L];
     }
     const float inv = 1.f / lt;
-    f32x4 o[X][1];
+    f32x4 part[X];
 #pragma unroll
     for (int x = 0; x < X; ++x) {  // wave w writes dimensions 64 x + 16 g + 4 w ..
-      o[x][0] = f[0] * sO[0][4 * x + w][lane];
+      part[x] = f[0] * sO[0][4 * x + w][lane];
 #pragma unroll
-      for (int y = 1; y < 4; ++y) o[x][0] += f[y] * sO[y][4 * x + w][lane];
+      for (int y = 1; y < 4; ++y) part[x] += f[y] * sO[y][4 * x + w][lane];
     }
-    if (lost(o, lt)) visible_keys_only(o, w, M);
+    auto o = [&](int x, int, int c) __attribute__((always_inline)) { return part[x][c]; };
+    const std::integral_constant<int, 1> ne;
+    if (__builtin_amdgcn_ballot_w64(nan_among(ne, o) && lt < INFINITY) != 0)
+      visible_keys_only(ne, w, M, o, [&](int x, int, int c, float value) __attribute__((always_inline)) { part[x][c] = value; });
     if (i < T) {
 #pragma unroll
-      for (int x = 0; x < X; ++x) *(f32x4*)(out + 64 * x + 4 * w) = o[x][0] * inv;
+      for (int x = 0; x < X; ++x) *(f32x4*)(out + 64 * x + 4 * w) = part[x] * inv;
       if (a.lse && g == 0 && w == 0) a.lse[(size_t)(cu + i) * a.hq + head] = M + logf(lt);
     }
   }
