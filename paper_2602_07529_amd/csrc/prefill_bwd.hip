@@ -1629,9 +1629,9 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
     };
     auto score = [&](auto hc, auto ec) __attribute__((always_inline)) {  // dS of key e of half h (this lane's row), packed in pairs
       constexpr int h = decltype(hc)::value, e = decltype(ec)::value;
-      float p = __builtin_amdgcn_exp2f(fmaf(S[h][e], sc, nl));
-      if constexpr (MSK) p = keep_if_bit<8 * (e >> 2) + (e & 3)>(p, h == 0 ? vis_lo : vis_hi);  // Eq. 3 and the end of the sequence
-      dt[h][e] = p * (dP[h][e] - dl);
+      dt[h][e] = __builtin_amdgcn_exp2f(fmaf(S[h][e], sc, nl)) * (dP[h][e] - dl);
+      // Eq. 3 and the end of the sequence (behind the product: V of a hidden key may be anything)
+      if constexpr (MSK) dt[h][e] = keep_if_bit<8 * (e >> 2) + (e & 3)>(dt[h][e], h == 0 ? vis_lo : vis_hi);
       if constexpr ((e & 1) == 1) {
         typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
         const bf16x2 pk = __builtin_bit_cast(bf16x2, dag_pack_bf2(dt[h][e - 1], dt[h][e]));

@@ -68,3 +68,22 @@ def test_hidden_values(hq, hkv, d, dtype):
     _check(out, ref, ~sees, TOL[dtype])
     assert np.abs(lse.cpu().double().numpy() - ref_lse).max() < (1e-4 if dtype == torch.float32 else 2e-2)
 
+
+# dQ with one and two visibility words, on query chunks (first two) and on the block map's tiles (shorter nodes)
+@pytest.mark.parametrize("hq,hkv,d,n_nodes,longest", [(2, 1, 64, 24, 90), (4, 1, 128, 70, 60), (3, 1, 64, 40, 14), (4, 1, 128, 100, 14)])
+def test_hidden_values_backward_dq(hq, hkv, d, n_nodes, longest):
+    rng = np.random.Generator(np.random.PCG64(700 + n_nodes))
+    dag_list = [dags.random_dag(rng, n_nodes=n_nodes, depth=5, len_lo=longest // 2, len_hi=longest)[:2]]
+    T = int(np.sum(dag_list[0][0]))
+    bad = np.asarray([T // 3, T // 2, T - 1])
+    q, k, v = dags.make_qkv(80 + hq, T, hq, hkv, d, 0.7, torch.bfloat16)
+    dout = dags.make_qkv(81 + hq, T, hq, hkv, d, 1.0, torch.bfloat16)[0]
+    _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
+    qd, kd, dod = q.to(DEV), k.to(DEV), dout.to(DEV)
+    vd = v.to(DEV)
+    out, lse = torch.empty_like(qd), torch.empty(T, hq, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, qd, kd, vd, out, lse)
+    dq, dk, dv = torch.empty_like(qd), torch.empty_like(kd), torch.empty_like(kd)
+    B.dag_attn_prefill_bwd(meta, qd, kd, _spoil(v, bad).to(DEV), out, dod, lse, dq, dk, dv)
+    ref = orc.attn_prefill_bwd(dags.to_f64(q), dags.to_f64(k), dags.to_f64(v), dags.to_f64(dout), *dag_list[0])[0]
+    _check(dq, ref, ~_sees_bad(dag_list, bad, T), TOL[torch.bfloat16])
