@@ -56,12 +56,10 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   a->wide_desc = need > 0 ? a->wide_pre + 8 * m->sizes.total_qtiles : nullptr;
   a->wide_col = need > 0 ? a->wide_desc + 8 * m->sizes.total_qtiles : nullptr;
   a->node_tok_start = m->node_tok_start;
-  a->node_pos_start = m->node_pos_start;
-  a->pos_ids = m->pos_ids;
   a->total_tokens = m->sizes.total_tokens;
   a->total_nodes = m->sizes.total_nodes;
   a->node_runs = nullptr;
-  if (need > 0 && m->node_tok_start && m->node_pos_start && m->pos_ids && a->total_nodes > 0 && m->words_per_node <= 2 &&
+  if (need > 0 && m->node_tok_start && a->total_nodes > 0 && m->words_per_node <= 2 &&
       prefill_node_table_bytes(a->total_tokens, a->total_nodes) <=
           (size_t)m->sizes.total_ktiles * hkv * head_dim * m->tile_n * 2) {
     prefill_node_tables(*a, (int32_t*)a->vt);

@@ -308,7 +308,6 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
                                           const int32_t* __restrict__ cu_seqlens,
                                           const int32_t* __restrict__ tok_node,
                                           const int32_t* __restrict__ node_tok_start,
-                                          const int32_t* __restrict__ node_pos_start,
                                           const uint64_t* __restrict__ node_vis,
                                           int32_t* __restrict__ runs, const ChunkTables& t) {
   const int lane = threadIdx.x & 63;
@@ -374,29 +373,42 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
     d[4] = (anc + row_end + TN - 1) / TN;
     d[5] = (row_end <= u1 - u0 ? anc + row0 + 1 : anc) / TN;  // tiles whose 64 positions every row sees
     d[6] = anc;
-    d[7] = node_pos_start[gv];  // position id of the first token of every node of the group
+    d[7] = 0;
   }
 }
 
+// Tokens of its own node in front of a token, for the 1024 tokens from t0 on (not from the position ids: those
+// are the caller's to shift).
+__device__ __forceinline__ void token_depths(const PrefillArgs& a, int64_t t0) {
+  for (int64_t t = t0 + threadIdx.x; t < min(t0 + 1024, a.total_tokens); t += blockDim.x) {
+    const int b = dag_find_segment(a.cu_seqlens, a.n_seqs, (int)t);
+    a.tok_depth[t] = (int)t - a.cu_seqlens[b] - a.node_tok_start[a.node_start[b] + a.tok_node[t]];
+  }
+}
+
+// Four nodes a block, then blocks of 1024 tokens.
 template <int W>
 __global__ void __launch_bounds__(256) k_node_rows(int rows, int64_t n_slots, PrefillArgs a, ChunkTables t) {
+  const int node_blocks = ((int)a.total_nodes + 3) / 4;
+  if ((int)blockIdx.x >= node_blocks) return token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 1024);
   const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (blockIdx.x == 0 && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;  // work counters of the attention kernel
   if (gv < a.total_nodes)
     node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
-                 a.node_pos_start, a.node_vis, a.node_runs, t);
+                 a.node_vis, a.node_runs, t);
 }
-// Few nodes: the tables and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2).
+// Few nodes: the tables and their order in one workgroup, and blocks of 1024 tokens as above (15 slots: 4.0 us instead of 3.8 + 2.2).
 constexpr int SMALL_NODES = 64, SMALL_SLOTS = 128;
 template <int W>
 __global__ void __launch_bounds__(1024) k_node_rows_small(int rows, int n_slots, PrefillArgs a, ChunkTables t) {
+  if (blockIdx.x > 0) return token_depths(a, (int64_t)(blockIdx.x - 1) * 1024);
   __shared__ int32_t s_cnt[SMALL_SLOTS], s_pre[SMALL_SLOTS * 8];
   const int w = threadIdx.x >> 6;
   if (threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
   const ChunkTables local = {t.count, s_cnt, s_pre, t.desc};
   for (int gv = w; gv < a.total_nodes; gv += 16)
     node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
-                 a.node_pos_start, a.node_vis, a.node_runs, local);
+                 a.node_vis, a.node_runs, local);
   __syncthreads();
   for (int i = w; i < n_slots; i += 16) wide_order(i, n_slots, s_cnt, s_pre, t.desc, t.count);
 }
@@ -1121,15 +1133,14 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
   // Row data for the mask: node of each row (rnode), word 0 of that node's visibility bitset
   // (vis0), and the nodes of the next item's rows, fetched one item ahead so that the dependent
   // vis0 load can go out together with the next Q rows.
-  // NODES: how many tokens of its own node come before the row (siblings start at the same position).
-  int rnode[RB], rnode_nxt[RB], rdepth[RB];
+  // NODES: how many tokens of its own node come before the row, instead of the node.
+  int rnode[RB], rnode_nxt[RB];
   uint64_t vis0[RB];
-  auto row_data = [&](const Item& I, int r) __attribute__((always_inline)) { return (NODES ? a.pos_ids : a.tok_node)[token_of(I, r)]; };
+  auto row_data = [&](const Item& I, int r) __attribute__((always_inline)) { return (NODES ? a.tok_depth : a.tok_node)[token_of(I, r)]; };
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
     rnode[r] = PAGED ? 0 : row_data(cur, r);
     rnode_nxt[r] = !PAGED && has_next ? row_data(nxt, r) : 0;
-    rdepth[r] = NODES ? rnode[r] - cur.ktb : 0;
   }
 #pragma unroll
   for (int r = 0; r < RB; ++r) vis0[r] = STREAM != STREAM_TILES ? 0 : a.node_vis[(int64_t)(cur.nstart + rnode[r]) * a.W];
@@ -1190,7 +1201,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
           const int own = cur.nstart + min(row_of(cur, r), cur.T - 1) - n * TN;  // the row's own position inside the tile
-          rm[r] = (first_bits(cur.nstart - n * TN) | (first_bits(own + 1) & ~first_bits(own - rdepth[r]))) >> (8 * H);
+          rm[r] = (first_bits(cur.nstart - n * TN) | (first_bits(own + 1) & ~first_bits(own - rnode[r]))) >> (8 * H);
         }
         return;
       }
@@ -1700,7 +1711,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
             for (int e = 0; e < 4; ++e) s = fmaf(dag_bf_hi(kr[e]), dag_bf_hi(qr[x][e]), fmaf(dag_bf_lo(kr[e]), dag_bf_lo(qr[x][e]), s));
           }
           s += __shfl_xor(s, 32);
-          const bool ok = p < cur.nstart || (p <= own && p >= own - rdepth[r]);
+          const bool ok = p < cur.nstart || (p <= own && p >= own - rnode[r]);
           const float pr = __builtin_amdgcn_exp2f(s - M[r]);
           bool number = false;
 #pragma unroll
@@ -1782,7 +1793,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       rnode[r] = rnode_nxt[r];
-      rdepth[r] = NODES ? rnode[r] - cur.ktb : 0;
       if (!PAGED && has_next) rnode_nxt[r] = row_data(nxt, r);
     }
     if (iss_next) iss_next = 0;     // the cursor was already in what is now the current item
@@ -1955,14 +1965,15 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
 // The chunk tables of one chunk size: descriptors, then launch order (by descending tile count).
 int build_chunks(const PrefillArgs& a, int i, hipStream_t stream) {
   const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[i]);
+  const unsigned token_blocks = (unsigned)dag_ceil_div(a.total_tokens, 1024);
   if (a.total_nodes <= SMALL_NODES && slots <= SMALL_SLOTS) {
-    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(1), dim3(1024), 0, stream, DAG_CHUNK_ROWS[i],
+    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(1 + token_blocks), dim3(1024), 0, stream, DAG_CHUNK_ROWS[i],
                        (int)slots, a, a.chunk[i]);
     DAG_LAUNCH_CHECK();
     return DAG_OK;
   }
-  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream,
-                     DAG_CHUNK_ROWS[i], slots, a, a.chunk[i]);
+  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4) + token_blocks), dim3(256), 0,
+                     stream, DAG_CHUNK_ROWS[i], slots, a, a.chunk[i]);
   hipLaunchKernelGGL(k_wide_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, (int)slots, a.chunk[i].cnt,
                      a.chunk[i].pre, a.chunk[i].desc, a.chunk[i].count);
   DAG_LAUNCH_CHECK();

@@ -73,7 +73,7 @@ struct BwdArgs {
   // dQ on query chunks (k_node_rows): the chunk tables of 64 and of 64 NQ rows, the nodes' runs
   ChunkTables chunk[2];
   int64_t chunk_slots[2];
-  const int32_t *runs, *pos_ids;
+  const int32_t *runs, *tok_depth;
   // dK / dV on streams of query rows
   bool dkv_stream;
   const int32_t* node_tok_start;
@@ -1484,11 +1484,10 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   const int pair = w >> 1;  // (WIDE) which of the query tiles
   DqTile t;
   int64_t wide_base = 0;
-  int pos0 = 0;
   if constexpr (NODES) {
     if ((int)blockIdx.x >= *a.chunk[WIDE].count) return;  // (the launch is sized by a bound)
     const int32_t* d = a.chunk[WIDE].desc + (size_t)blockIdx.x * 8;
-    t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6], pos0 = d[7];
+    t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
   } else if constexpr (!WIDE) {
     t = dq_tile(a);
   } else {
@@ -1526,7 +1525,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
     const int2 run = ((const int2*)a.runs)[t.c0 + lane];
     run_pos = run.x;
     run_delta = run.y;
-    depth = a.pos_ids[cu + min(me.i, T - 1)] - pos0;
+    depth = a.tok_depth[cu + min(me.i, T - 1)];
     asm volatile("" ::"v"(run_pos), "v"(run_delta), "v"(depth));
     run_d = __builtin_amdgcn_readlane(run_delta, 0);
     run_end = __builtin_amdgcn_readlane(run_pos, 1);
@@ -2013,7 +2012,7 @@ extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t h
 // dQ kernels neither read nor write and the dK / dV kernels, started behind them, overwrite whole.
 static bool bwd_dq_on_chunks(const dag_meta_t* m, const BwdArgs& a, int32_t head_dim) {
   const int64_t T = m->sizes.total_tokens, n = m->sizes.total_nodes;
-  if (!m->node_tok_start || !m->node_pos_start || !m->pos_ids || n < 1 || m->words_per_node > 2 || bwd_first_version()) return false;
+  if (!m->node_tok_start || n < 1 || m->words_per_node > 2 || bwd_first_version()) return false;
   const size_t dk_bytes = (size_t)T * a.hkv * head_dim * 2;
   if (dk_bytes > UINT32_MAX || DAG_SCHED_INTS * 4 + prefill_node_table_bytes(T, n) > dk_bytes) return false;  // (row offsets are 32-bit)
   auto apart = [&](const void* p, size_t bytes) {
@@ -2105,7 +2104,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     p.n_seqs = m->n_seqs; p.W = m->words_per_node;
     p.total_tokens = m->sizes.total_tokens; p.total_nodes = m->sizes.total_nodes;
     p.cu_seqlens = m->cu_seqlens; p.node_start = m->node_start; p.tok_node = m->tok_node; p.node_vis = m->node_vis;
-    p.node_tok_start = m->node_tok_start; p.node_pos_start = m->node_pos_start;
+    p.node_tok_start = m->node_tok_start;
     p.sched = (int32_t*)dk;
     prefill_node_tables(p, p.sched + DAG_SCHED_INTS);
     const int wide = head_dim == 128 ? 2 : 1;  // chunks of NPAIR x 64 rows
@@ -2117,7 +2116,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
       a.chunk_slots[i] = chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[i ? wide : 0]);
     }
     a.runs = p.node_runs;
-    a.pos_ids = m->pos_ids;
+    a.tok_depth = p.tok_depth;
   }
   return head_dim == 128 ? launch_bwd<128>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
                          : launch_bwd<64>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s);

@@ -52,17 +52,18 @@ struct PrefillArgs {
   int32_t* wide_desc;   // [total_qtiles][8] descriptors in launch order (wide_count of them)
   int32_t* wide_col;    // [csr_capacity] key tiles of the rows, row of tile qt at rowptr[qt]
   // bf16 path, workspace: what every node sees, as runs of consecutive tokens (see k_node_rows)
-  const int32_t *node_tok_start, *node_pos_start, *pos_ids;
+  const int32_t* node_tok_start;
   int64_t total_tokens, total_nodes;
   int32_t* node_runs;  // [total_nodes][64][2], null when the workspace has no room for them
+  int32_t* tok_depth;  // [total_tokens] tokens of its own node in front of every token
   ChunkTables chunk[DAG_CHUNK_SIZES];
 };
 
 // The node tables hold 64 runs per node, the most that 128 nodes can have.  They take the place of the
-// transposed V, which is not needed with them: 716 bytes a node and 1.9 a token against at least 128 a
+// transposed V, which is not needed with them: 716 bytes a node and 5.9 a token against at least 128 a
 // token, so that they fit wherever a node has six tokens on average.
 inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes) {
-  size_t n = (size_t)total_nodes * 128 * 4;
+  size_t n = (size_t)total_nodes * 128 * 4 + (size_t)total_tokens * 4;
   for (int i = 0; i < DAG_CHUNK_SIZES; ++i) n += (size_t)(62 + 17 * chunk_slots(total_tokens, total_nodes, DAG_CHUNK_ROWS[i])) * 4;
   return n;
 }
@@ -76,6 +77,7 @@ inline void prefill_node_tables(PrefillArgs& a, int32_t* t) {
     a.chunk[i] = {t, t + 62, t + 62 + n, t + 62 + 9 * n};
     t += 62 + 17 * n;
   }
+  a.tok_depth = t;
 }
 
 // Workspace of the bf16 path behind the transposed V: counters, then the tables above.

@@ -6,8 +6,9 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2602_07529_amd import binding as B
 from workloads import dags
-from tests.gpu_util import check_close, oracle_prefill, run_prefill
+from tests.gpu_util import DEV, build_meta, check_close, oracle_prefill, run_prefill
 from tests.test_asm_lds_reads import HIPCC, _assembly, _conflicts_of_kernel, _kernels
 
 
@@ -42,6 +43,28 @@ def test_chunks_many_nodes_and_runs(n_nodes):
     dag_list = [(np.asarray(rng.integers(4, 40, n_nodes), dtype=np.int32), dags.bits_from_sets(alternating)),
                 dags.random_dag(rng, n_nodes=n_nodes, depth=6, len_lo=10, len_hi=40)[:2]]
     _check(dag_list, 4, 1, 128, 8600 + n_nodes)
+
+
+# a prompt that starts at an offset: its positions are shifted in place, the mask stays what it was
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (3, 1, 64)])
+def test_mask_does_not_depend_on_the_positions(hq, hkv, d):
+    dag_list = [dags.fork_join(130, [40, 64, 33, 150, 63], 70), dags.linear_chain([65, 190])]
+    T = int(sum(int(np.sum(L)) for L, _ in dag_list))
+    q, k, v = (x.to(DEV) for x in dags.make_qkv(8500 + d, T, hq, hkv, d, 0.5, torch.bfloat16))
+    dout = dags.make_qkv(8501 + d, T, hq, hkv, d, 1.0, torch.bfloat16)[0].to(DEV)
+    results = []
+    for shift in (0, 1000):
+        _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
+        meta.t["pos_ids"] += shift
+        meta.t["node_pos_start"] += shift // 2
+        out, lse = torch.empty_like(q), torch.empty(T, hq, dtype=torch.float32, device=DEV)
+        B.dag_attn_prefill(meta, q, k, v, out, lse)
+        grads = [torch.empty_like(x) for x in (q, k, v)]
+        B.dag_attn_prefill_bwd(meta, q, k, v, out, dout, lse, *grads)
+        results.append([out, lse] + grads)
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
