@@ -159,10 +159,11 @@ int dag_attn_prefill(const dag_meta_t* meta, const void* q, const void* k, const
 /* The two halves of dag_attn_prefill (Eq. 2 + Eq. 3), for callers that want them as separate
  * launches, e.g. to time the attention kernel alone or to prepare V while Q and K are still being
  * produced.  dag_prefill_prepare_v writes into `ws` what the attention kernel works from -- its work
- * list or, where it needs one, a key-tile-wise transposed copy of v [T][hkv][head_dim] -- (a no-op for
+ * lists or a key-tile-wise transposed copy of v [T][hkv][head_dim] -- (a no-op for
  * DAG_F32); dag_attn_prefill_prepared is dag_attn_prefill without that
- * step: it expects `ws` as dag_prefill_prepare_v left it for the same meta, v, hq, hkv, head_dim and
- * dtype.  Arguments, layouts, errors and the workspace size are those of dag_attn_prefill.
+ * step: it expects `ws` as dag_prefill_prepare_v left it for the same meta, v, hkv, head_dim and
+ * dtype and an hq with the same remainder of hq / hkv modulo 4, and v as it was then.
+ * Arguments, layouts, errors and the workspace size are those of dag_attn_prefill.
  * The workspace also holds the attention kernel's work-distribution counters: dag_prefill_prepare_v
  * zeroes them and every attention launch leaves them zeroed, so a workspace must go through
  * dag_prefill_prepare_v (or dag_attn_prefill) once before dag_attn_prefill_prepared uses it, and

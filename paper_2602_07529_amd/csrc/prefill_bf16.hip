@@ -338,7 +338,7 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
     before += __shfl(incl, 63);
     if (v / 64 == x) anc = __shfl(pos, v % 64);
     const uint64_t starts = sees[x] & ~(sees[x] << 1 | (x > 0 ? sees[x > 0 ? x - 1 : 0] >> 63 : 0));  // a run starts where the node in front is not visible
-    if ((starts >> lane) & 1) out[n_runs + __popcll(starts & below)] = int2{pos, cu + first - pos};
+    if (runs && (starts >> lane) & 1) out[n_runs + __popcll(starts & below)] = int2{pos, cu + first - pos};
     n_runs += __popcll(starts);
     bool eq = u < n;
 #pragma unroll
@@ -348,7 +348,7 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
     }
     same[x] = __ballot(eq);
   }
-  if (lane >= n_runs) out[lane] = int2{INT32_MAX, 0};
+  if (runs && lane >= n_runs) out[lane] = int2{INT32_MAX, 0};
   auto is_same = [&](int u) { return ((W > 1 && u >= 64 ? same[W - 1] : same[0]) >> (u & 63)) & 1; };
   if (v > 0 && is_same(v - 1)) return;  // the first node of the group writes its chunks
   int end = v + 1;                      // first node behind the group
@@ -386,31 +386,59 @@ __device__ __forceinline__ void token_depths(const PrefillArgs& a, int64_t t0) {
   }
 }
 
-// Four nodes a block, then blocks of 1024 tokens.
-template <int W>
-__global__ void __launch_bounds__(256) k_node_rows(int rows, int64_t n_slots, PrefillArgs a, ChunkTables t) {
-  const int node_blocks = ((int)a.total_nodes + 3) / 4;
-  if ((int)blockIdx.x >= node_blocks) return token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 1024);
-  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (blockIdx.x == 0 && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;  // work counters of the attention kernel
-  if (gv < a.total_nodes)
-    node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
-                 a.node_vis, a.node_runs, t);
+// The tables of several chunk sizes are built together (bit i of `sizes`: those of DAG_CHUNK_ROWS[i] rows;
+// blockIdx.y, in the small form blockIdx.x, counts the set bits).  The prefill builds all of them whatever the
+// launch behind it takes: the head counts of a call may differ from those that its workspace was prepared for.
+// What the sizes share by the blocks of the first one: the runs, the work counters of the attention kernel,
+// the depths.
+__device__ __forceinline__ int nth_size(int sizes, int n) {
+  for (; n > 0; --n) sizes &= sizes - 1;
+  return __builtin_ctz(sizes);
 }
-// Few nodes: the tables and their order in one workgroup, and blocks of 1024 tokens as above (15 slots: 4.0 us instead of 3.8 + 2.2).
+__device__ __forceinline__ ChunkTables tables_of(const PrefillArgs& a, int i) { return i == 0 ? a.chunk[0] : i == 1 ? a.chunk[1] : a.chunk[2]; }
+__device__ __forceinline__ int rows_of(int i) { return DAG_CHUNK_ROWS[0] << i; }
+__device__ __forceinline__ int slots_of(const PrefillArgs& a, int i) {  // = chunk_slots
+  return (int)(a.total_tokens >> (__builtin_ctz(DAG_CHUNK_ROWS[0]) + i)) + (int)a.total_nodes;
+}
+// Four nodes a block, then (of the first size) blocks of 1024 tokens.
+template <int W>
+__global__ void __launch_bounds__(256) k_node_rows(PrefillArgs a, int sizes) {
+  const int node_blocks = ((int)a.total_nodes + 3) / 4, i = nth_size(sizes, blockIdx.y), rows = rows_of(i);
+  const bool first = blockIdx.y == 0;
+  if ((int)blockIdx.x >= node_blocks) {
+    if (first) token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 1024);
+    return;
+  }
+  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (blockIdx.x == 0 && first && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
+  if (gv < a.total_nodes)
+    node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, slots_of(a, i), a.node_start,
+                 a.cu_seqlens, a.tok_node, a.node_tok_start, a.node_vis, first ? a.node_runs : nullptr, tables_of(a, i));
+}
+__global__ void __launch_bounds__(256) k_chunk_order(PrefillArgs a, int sizes) {
+  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), i = nth_size(sizes, blockIdx.y);
+  const int n_slots = slots_of(a, i);
+  const ChunkTables t = tables_of(a, i);
+  if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
+}
+// Few nodes: the tables of a size and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2), and
+// blocks of 1024 tokens as above.
 constexpr int SMALL_NODES = 64, SMALL_SLOTS = 128;
 template <int W>
-__global__ void __launch_bounds__(1024) k_node_rows_small(int rows, int n_slots, PrefillArgs a, ChunkTables t) {
-  if (blockIdx.x > 0) return token_depths(a, (int64_t)(blockIdx.x - 1) * 1024);
+__global__ void __launch_bounds__(1024) k_node_rows_small(PrefillArgs a, int sizes) {
   __shared__ int32_t s_cnt[SMALL_SLOTS], s_pre[SMALL_SLOTS * 8];
-  const int w = threadIdx.x >> 6;
-  if (threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
-  const ChunkTables local = {t.count, s_cnt, s_pre, t.desc};
+  const int n_sizes = __builtin_popcount(sizes);
+  if ((int)blockIdx.x >= n_sizes) return token_depths(a, (int64_t)(blockIdx.x - n_sizes) * 1024);
+  const bool first = blockIdx.x == 0;
+  const int w = threadIdx.x >> 6, i = nth_size(sizes, blockIdx.x), rows = rows_of(i);
+  const int n_slots = slots_of(a, i);
+  const ChunkTables t = tables_of(a, i), local = {t.count, s_cnt, s_pre, t.desc};
+  if (first && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
   for (int gv = w; gv < a.total_nodes; gv += 16)
     node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
-                 a.node_vis, a.node_runs, local);
+                 a.node_vis, first ? a.node_runs : nullptr, local);
   __syncthreads();
-  for (int i = w; i < n_slots; i += 16) wide_order(i, n_slots, s_cnt, s_pre, t.desc, t.count);
+  for (int x = w; x < n_slots; x += 16) wide_order(x, n_slots, s_cnt, s_pre, t.desc, t.count);
 }
 
 // Work items of the paged prefill (section 4.3, phase II: the new tokens of a node are prefilled
@@ -1962,39 +1990,28 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
   return rc;
 }
 
-// The chunk tables of one chunk size: descriptors, then launch order (by descending tile count).
-int build_chunks(const PrefillArgs& a, int i, hipStream_t stream) {
-  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[i]);
-  const unsigned token_blocks = (unsigned)dag_ceil_div(a.total_tokens, 1024);
+}  // namespace
+
+// The nodes' runs and the chunk tables of the sizes asked for: descriptors, then launch order (by descending tile count).
+int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream) {
+  const unsigned n_sizes = (unsigned)__builtin_popcount((unsigned)sizes), token_blocks = (unsigned)dag_ceil_div(a.total_tokens, 1024);
+  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[__builtin_ctz(sizes)]);  // (the larger sizes have fewer)
   if (a.total_nodes <= SMALL_NODES && slots <= SMALL_SLOTS) {
-    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(1 + token_blocks), dim3(1024), 0, stream, DAG_CHUNK_ROWS[i],
-                       (int)slots, a, a.chunk[i]);
+    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(n_sizes + token_blocks), dim3(1024), 0, stream, a, sizes);
     DAG_LAUNCH_CHECK();
     return DAG_OK;
   }
-  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4) + token_blocks), dim3(256), 0,
-                     stream, DAG_CHUNK_ROWS[i], slots, a, a.chunk[i]);
-  hipLaunchKernelGGL(k_wide_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, (int)slots, a.chunk[i].cnt,
-                     a.chunk[i].pre, a.chunk[i].desc, a.chunk[i].count);
+  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4) + token_blocks, n_sizes),
+                     dim3(256), 0, stream, a, sizes);
+  hipLaunchKernelGGL(k_chunk_order, dim3((unsigned)((slots + 3) / 4), n_sizes), dim3(256), 0, stream, a, sizes);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
 
-}  // namespace
-
-int launch_chunk_tables(const PrefillArgs& a, int i, hipStream_t stream) { return build_chunks(a, i, stream); }
-
 template <int D>
 int launch_prepare_v(const PrefillArgs& a, hipStream_t stream) {
-  const bool chunks = on_chunks(a, D);
-  const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
-  if (chunks) {  // V is read as it is
-    if (heads_of_small_batch(a, D) > 0) return build_chunks(a, 0, stream);
-    int rc = h.four > 0 || (h.two > 0 && D == 64) ? build_chunks(a, 0, stream) : DAG_OK;
-    if (rc == DAG_OK && ((h.two > 0 && D == 128) || (h.one > 0 && D == 64))) rc = build_chunks(a, 1, stream);
-    if (rc == DAG_OK && h.one > 0 && D == 128) rc = build_chunks(a, 2, stream);
-    return rc;
-  }
+  if (on_chunks(a, D)) return launch_chunk_tables(a, (1 << DAG_CHUNK_SIZES) - 1, stream);  // V is read as it is
+  const HeadSplit h = split_heads(a.hq / a.hkv, false);
   hipLaunchKernelGGL((k_vt_prepare<D>), dim3((unsigned)a.total_ktiles, (unsigned)a.hkv), dim3(256), 0, stream,
                      (const uint16_t*)a.v, (uint16_t*)a.vt, a.ktile_start, a.cu_seqlens, a.n_seqs, a.hkv, a.sched);
   DAG_LAUNCH_CHECK();

@@ -2108,8 +2108,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     p.sched = (int32_t*)dk;
     prefill_node_tables(p, p.sched + DAG_SCHED_INTS);
     const int wide = head_dim == 128 ? 2 : 1;  // chunks of NPAIR x 64 rows
-    int rc = a.dq_narrow > 0 ? launch_chunk_tables(p, 0, s) : DAG_OK;
-    if (rc == DAG_OK && a.dq_narrow < a.G) rc = launch_chunk_tables(p, wide, s);
+    const int rc = launch_chunk_tables(p, (a.dq_narrow > 0) | (a.dq_narrow < a.G) << wide, s);
     if (rc != DAG_OK) return rc;
     for (int i = 0; i < 2; ++i) {
       a.chunk[i] = p.chunk[i ? wide : 0];

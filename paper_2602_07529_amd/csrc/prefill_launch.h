@@ -8,7 +8,7 @@ constexpr int DAG_SCHED_INTS = 128;  // [0..63] item counters, [64] finished wor
 // the group of siblings that starts with node v (of the batch) and token t owns the slots from
 // t / rows + v on.
 constexpr int DAG_CHUNK_SIZES = 3;
-constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};
+constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};  // (each twice the one in front)
 struct ChunkTables {
   int32_t* count;  // [1] number of chunks
   int32_t* cnt;    // [slots] key tiles of the chunk, -1: no chunk here
@@ -95,7 +95,7 @@ struct PagedPrefillArgs {
 };
 int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream);
 
-int launch_chunk_tables(const PrefillArgs& a, int i, hipStream_t stream);  // of the chunks of DAG_CHUNK_ROWS[i] rows
+int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream);  // bit i of sizes: chunks of DAG_CHUNK_ROWS[i] rows
 
 int launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t stream);
 int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_t stream);  // V -> workspace copy
