@@ -91,6 +91,15 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   return DAG_OK;
 }
 
+// Whether the call writes to where V lies.  On query chunks V is read while rows are written; the block map's
+// tiles work from a copy of V made in a launch before, and take such a call.
+bool writes_v(const PrefillArgs& a, int32_t head_dim) {
+  const char* const v = (const char*)a.v;
+  const size_t rows = (size_t)a.total_tokens, v_bytes = rows * a.hkv * head_dim * 2;
+  auto meets = [&](const void* p, size_t bytes) { return p && (const char*)p < v + v_bytes && v < (const char*)p + bytes; };
+  return meets(a.out, rows * a.hq * head_dim * 2) || meets(a.lse, rows * a.hq * 4);
+}
+
 }  // namespace
 
 extern "C" int dag_prefill_prepare_v(const dag_meta_t* m, const void* v, int32_t hq, int32_t hkv, int32_t head_dim,
@@ -112,7 +121,13 @@ extern "C" int dag_attn_prefill_prepared(const dag_meta_t* m, const void* q, con
                               &empty);
   if (rc != DAG_OK || empty) return rc;
   hipStream_t stream = (hipStream_t)stream_;
-  return dtype == DAG_F32 ? launch_prefill_f32(a, head_dim, stream) : launch_prefill_bf16(a, head_dim, stream);
+  if (dtype == DAG_F32) return launch_prefill_f32(a, head_dim, stream);
+  if (!prefill_on_chunks(a, head_dim) || !writes_v(a, head_dim)) return launch_prefill_bf16(a, head_dim, stream);
+  PrefillArgs tiles = a;  // the copy of V first; behind it the workspace becomes again what it was
+  tiles.node_runs = nullptr;
+  int rp = launch_prefill_bf16_prepare_v(tiles, head_dim, stream);
+  if (rp == DAG_OK) rp = launch_prefill_bf16(tiles, head_dim, stream);
+  return rp == DAG_OK ? launch_prefill_bf16_prepare_v(a, head_dim, stream) : rp;
 }
 
 extern "C" int dag_attn_prefill(const dag_meta_t* m, const void* q, const void* k, const void* v, void* out,
@@ -125,6 +140,7 @@ extern "C" int dag_attn_prefill(const dag_meta_t* m, const void* q, const void* 
   if (rc != DAG_OK || empty) return rc;
   hipStream_t stream = (hipStream_t)stream_;
   if (dtype == DAG_F32) return launch_prefill_f32(a, head_dim, stream);
+  if (writes_v(a, head_dim)) a.node_runs = nullptr;
   const int rp = launch_prefill_bf16_prepare_v(a, head_dim, stream);
   return rp != DAG_OK ? rp : launch_prefill_bf16(a, head_dim, stream);
 }

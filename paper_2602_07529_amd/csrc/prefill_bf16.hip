@@ -1992,6 +1992,8 @@ int launch_d(const PrefillArgs& a, hipStream_t stream) {
 
 }  // namespace
 
+bool prefill_on_chunks(const PrefillArgs& a, int head_dim) { return on_chunks(a, head_dim); }
+
 // The nodes' runs and the chunk tables of the sizes asked for: descriptors, then launch order (by descending tile count).
 int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream) {
   const unsigned n_sizes = (unsigned)__builtin_popcount((unsigned)sizes), token_blocks = (unsigned)dag_ceil_div(a.total_tokens, 1024);

@@ -1,5 +1,5 @@
-"""GPU: dag_attn_prefill with buffers that are shared between calls in the ways it takes them: a workspace that was
-prepared once serves several head counts."""
+"""GPU: dag_attn_prefill with buffers that overlap or are shared between calls in the ways it takes them: the output
+on the memory of V or Q, and workspaces prepared once for several head counts."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +23,38 @@ def _close(got, ref):
     # two correct orders of the keys: bf16 probabilities and results
     assert torch.isfinite(got.float()).all()
     assert float((got.double() - ref.double()).norm()) <= 1e-2 * float(ref.double().norm())
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("hq,hkv,d", [(8, 8, 128), (16, 16, 64), (16, 8, 128)])
+def test_output_on_the_memory_of_v(hq, hkv, d, prepared):
+    q, k, v, meta = _batch(hq, hkv, d)
+    ref = torch.empty_like(q)
+    B.dag_attn_prefill(meta, q, k, v, ref)
+    ws = torch.empty(B.dag_prefill_workspace_bytes(meta, hkv, d, B.DAG_BF16), dtype=torch.uint8, device=DEV)
+    if prepared:
+        B.dag_prefill_prepare_v(meta, v, hq, workspace=ws)
+        again = torch.empty_like(q)
+        B.dag_attn_prefill(meta, q, k, v, again, workspace=ws, prepared=True)
+        assert torch.equal(again, ref)
+    memory = torch.empty(q.numel(), dtype=q.dtype, device=DEV)
+    v_in = memory[-v.numel():].view_as(v)   # (hq > hkv: on the last rows of the output)
+    v_in.copy_(v)
+    out = memory.view_as(q)
+    B.dag_attn_prefill(meta, q, k, v_in, out, workspace=ws, prepared=prepared)
+    _close(out, ref)
+    if prepared:   # and the workspace is what it was
+        B.dag_attn_prefill(meta, q, k, v, again, workspace=ws, prepared=True)
+        assert torch.equal(again, ref)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 8, 64)])
+def test_output_on_the_memory_of_q(hq, hkv, d):
+    q, k, v, meta = _batch(hq, hkv, d)
+    ref = torch.empty_like(q)
+    B.dag_attn_prefill(meta, q, k, v, ref)
+    B.dag_attn_prefill(meta, q, k, v, q)
+    assert torch.equal(q, ref)
 
 
 # the grouping the workspace was prepared for, the one it is used with: every launch shape finds its tables
