@@ -545,7 +545,7 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 #pragma unroll
       for (int n = 0; n < BATCH; ++n)
 #pragma unroll
-        for (int t = 0; t < PER; ++t) acc[t] += n < n_live ? w[n] * x[n][t] : 0.f;
+        for (int t = 0; t < PER; ++t) acc[t] = n < n_live ? fmaf(w[n], x[n][t], acc[t]) : acc[t];
     }
   }
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
