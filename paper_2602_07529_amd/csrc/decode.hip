@@ -978,9 +978,12 @@ __global__ void __launch_bounds__(256) k_kv_append(const int32_t* branch_page_of
 // from slot 5 on (the traffic takes 45 us at the rate of a large copy).  Few runs are divided over the
 // heads too, to about two workgroups a compute unit.
 // Entries from which on: with 8 heads runs of 512 take the same either way, 1024 take 10.3 -> 8.5 us, 4096 26 ->
-// 13 to 16; entries on pages of their own, 2048 to 4096 of them, lose 3 to 7 us (21 -> 24, 36 -> 43).
+// 13 to 16.  Entries on pages of their own lose 3 to 7 us up to 4096 (1024: 11.6 -> 15.6 us, 2048: 20.5 -> 23.4,
+// 4096: 36.6 -> 42.8) and gain beyond (8192: 189 -> 169).  A descriptor with sibling groups is a decode step, every
+// entry the newest token of a branch with pages of its own, and takes this kernel where those gain;
+// one without groups lists the tokens of prefilled nodes.
 constexpr int kRunRows = 16, kRunThreads = 256;
-constexpr int kAppendRunRows = 1024;
+constexpr int kAppendRunRows = 1024, kAppendRunBranches = 8192;
 __global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const int32_t* branch_page_off, const int32_t* branch_pages,
                                                        const int32_t* branch_len, const int32_t* branch_pos,
                                                        const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
@@ -1177,7 +1180,7 @@ extern "C" int dag_kv_append_rope(const dag_decode_desc_t* d, const void* k_new,
       !d->branch_pos)
     return DAG_ERR_NULL;
   const int64_t runs = dag_ceil_div(d->n_live, kRunRows), split = dag_ceil_div(512, runs);
-  if (d->n_live >= kAppendRunRows && dag_aligned16(k_new) && dag_aligned16(v_new) && dag_aligned16(k_pool) && dag_aligned16(v_pool))
+  if (d->n_live >= (d->n_groups > 0 ? kAppendRunBranches : kAppendRunRows) && dag_aligned16(k_new) && dag_aligned16(v_new) && dag_aligned16(k_pool) && dag_aligned16(v_pool))
     hipLaunchKernelGGL(k_kv_append_run, dim3((unsigned)runs, (unsigned)(split < hkv ? split : hkv)), dim3(kRunThreads), 0, (hipStream_t)stream_,
                        d->n_live, d->branch_page_off, d->branch_pages, d->branch_len, d->branch_pos,
                        (const uint16_t*)k_new, (const uint16_t*)v_new, (uint16_t*)k_pool, (uint16_t*)v_pool, hkv,
