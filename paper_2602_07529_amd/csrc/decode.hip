@@ -856,16 +856,20 @@ __global__ void __launch_bounds__(WIDE_MAX_THREADS) __attribute__((amdgpu_waves_
 
 // One wave per (branch, query head): log-sum-exp combination of its partials.  What it costs is the chain
 // of dependent loads (a binary search for the group, then the partials four at a time: 7.8 us for
-// 16 partials), so the group is found with one load per lane, and the outputs of the first 16
-// partials are on their way together with the maxima and sums: 4.7 us.
+// 16 partials), so the group is found with one load per lane for every factor of 64 in their number, and the
+// outputs of the first 16 partials are on their way together with the maxima and sums: 4.7 us. 
 template <int D>
 __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   const int r = blockIdx.x / a.hq, head = blockIdx.x % a.hq;
   const int hk = head / a.G, j = head % a.G;
   const int lane = threadIdx.x;
-  int g = -1;  // the last group that starts at or before r
-  for (int g0 = 0; g0 < a.n_groups; g0 += 64)
-    g += __popcll(__ballot(g0 + lane < a.n_groups && a.group_branch_off[min(g0 + lane, a.n_groups)] <= r));
+  int g = 0;  // the last group that starts at or before r, one of the n from g on
+  for (int n = a.n_groups; n > 1;) {
+    const int step = (n + 63) / 64, at = min(lane * step, n - 1);
+    const int before = __popcll(__ballot(lane * step < n && a.group_branch_off[g + at] <= r)) - 1;
+    g += max(before, 0) * step;
+    n = min(step, n - max(before, 0) * step);
+  }
   const int row = (r - a.group_branch_off[g]) * a.G + j;
   const int rb = row >> 5, rr = row & 31;
   const size_t ia0 = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a;
@@ -879,53 +883,61 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   auto o_of = [&](int p) {
     return p < a.splits_a ? a.part_o_a + ((ia0 + p) * 32 + rr) * D : a.part_o_b + ((ib0 + (p - a.splits_a)) * a.G + j) * D;
   };
-  constexpr int BATCH = 16;
-  float x[BATCH][PER], acc[PER];
-  auto fetch = [&](int p0) __attribute__((always_inline)) {
+  float acc[PER], lsum = 0.f;
+  auto merge = [&](auto batch_c) __attribute__((always_inline)) {  // BATCH partial outputs in flight
+    constexpr int BATCH = decltype(batch_c)::value;
+    float x[BATCH][PER];
+    auto fetch = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const float* o = o_of(min(p0 + i, np - 1)) + lane * PER;
+      for (int i = 0; i < BATCH; ++i) {
+        const float* o = o_of(min(p0 + i, np - 1)) + lane * PER;
 #pragma unroll
-      for (int e = 0; e < PER; ++e) x[i][e] = o[e];
+        for (int e = 0; e < PER; ++e) x[i][e] = o[e];
+      }
+    };
+    fetch(0);
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+    // The reference maximum first (64 partials at a time, one per lane, so that their loads are in
+    // flight together), then the weighted sums in the fixed order of the partials: the weights of
+    // a group of 64 come from the lanes, and the loads of the partial outputs do not depend on
+    // each other (a partial without a visible key has l = 0 and weight 0; what it holds is read
+    // and dropped).
+    float mx = -1e30f;
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      const float mv = p0 + lane < np ? ml_of(p0 + lane)[0] : -1e30f;
+      mx = fmaxf(mx, mv);
+    }
+#pragma unroll
+    for (int off = 32; off; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      float wl = 0.f, wgt = 0.f;
+      if (p0 + lane < np) {
+        const float* ml = ml_of(p0 + lane);
+        const float ls = ml[1];
+        if (ls > 0.f) {
+          wgt = __builtin_amdgcn_exp2f((ml[0] - mx) * a.sc);
+          wl = ls * wgt;
+        }
+      }
+      for (int b0 = p0; b0 < min(p0 + 64, np); b0 += BATCH) {
+        if (b0 > 0) fetch(b0);
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {  // (the weight of a partial past the last one is zero)
+          const float wi = __shfl(wgt, b0 - p0 + i);
+          lsum += __shfl(wl, b0 - p0 + i);
+#pragma unroll
+          for (int e = 0; e < PER; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
+        }
+      }
     }
   };
-  fetch(0);
-#pragma unroll
-  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  // The reference maximum first (64 partials at a time, one per lane, so that their loads are in
-  // flight together), then the weighted sums in the fixed order of the partials: the weights of
-  // a group of 64 come from the lanes, and the loads of the partial outputs do not depend on
-  // each other (a partial without a visible key has l = 0 and weight 0; what it holds is read
-  // and dropped).
-  float mx = -1e30f;
-  for (int p0 = 0; p0 < np; p0 += 64) {
-    const float mv = p0 + lane < np ? ml_of(p0 + lane)[0] : -1e30f;
-    mx = fmaxf(mx, mv);
-  }
-#pragma unroll
-  for (int off = 32; off; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  float lsum = 0.f;
-  for (int p0 = 0; p0 < np; p0 += 64) {
-    float wl = 0.f, wgt = 0.f;
-    if (p0 + lane < np) {
-      const float* ml = ml_of(p0 + lane);
-      const float ls = ml[1];
-      if (ls > 0.f) {
-        wgt = __builtin_amdgcn_exp2f((ml[0] - mx) * a.sc);
-        wl = ls * wgt;
-      }
-    }
-    for (int b0 = p0; b0 < min(p0 + 64, np); b0 += BATCH) {
-      if (b0 > 0) fetch(b0);
-#pragma unroll
-      for (int i = 0; i < BATCH; ++i) {  // (the weight of a partial past the last one is zero)
-        const float wi = __shfl(wgt, b0 - p0 + i);
-        lsum += __shfl(wl, b0 - p0 + i);
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
-      }
-    }
-  }
+  // (what is read beyond the last partial is that one again: 4096 groups of one branch with a few partials take
+  // 59 us with sixteen in flight, 51 so)
+  if (np <= 2) merge(std::integral_constant<int, 2>{});
+  else if (np <= 4) merge(std::integral_constant<int, 4>{});
+  else if (np <= 8) merge(std::integral_constant<int, 8>{});
+  else merge(std::integral_constant<int, 16>{});
   const float inv = 1.f / lsum;
   uint16_t* o = a.out + ((size_t)r * a.hq + head) * D + lane * PER;
   if (PER == 2) {
