@@ -148,13 +148,13 @@ class PrefillWork:
         if ev:
             ev[1].record()
         # dag_attn_prefill = prepare_v + this call; launched separately here so that the events
-        # bracket exactly one kernel (k_prefill_bf16), the one the roofline is quoted on
+        # bracket exactly the attention kernel, the one the roofline is quoted on
         B.dag_attn_prefill(self.meta, self.q, self.k, self.v, self.out, prepared=True)
         if ev:
             ev[2].record()
 
     def algorithmic_bytes(self):
-        """Q read and out written once, K and the transposed V read once."""
+        """Q read and out written once, K and V read once."""
         c = self.cfg
         return (2 * self.T * c["hq"] + 2 * self.T * c["hkv"]) * c["d"] * 2
 
@@ -323,12 +323,35 @@ def backward_timing(pw, dev, calls, warmup):
     return ms, 2.5 * flops / (ms * 1e-3) / 1e12
 
 
-def bwd_kernels(G):
-    """The launches of dag_attn_prefill_bwd at head dimension 128 with G query heads per KV head: groups of
-    four heads on one query tile (k_bwd_dq2<false>), the left-over heads on four query tiles each."""
-    wide = G % 4
-    dq = (("k_bwd_dq2<false>",) if G - wide > 0 else ()) + (("k_bwd_wide_rows", "k_bwd_dq2<true>") if wide else ())
-    return ("k_bwd_delta<128>", "k_bwd_tokvis") + dq + ("k_bwd_weights", "k_bwd_order", "k_bwd_dkv2")
+def _shape(pw):
+    """What the library's rules on the route of a prefill look at (head dimension 128): tokens, nodes, visibility
+    words, query heads per KV head."""
+    return (pw.T, sum(len(L) for L, _ in pw.dag_list), max(a.shape[1] for _, a in pw.dag_list),
+            pw.cfg["hq"] // pw.cfg["hkv"])
+
+
+def prefill_kernels(pw):
+    """The attention launches of dag_attn_prefill at head dimension 128 (bf16, batches that fill the device): on query
+    chunks items of four heads on 64 rows, pairs on 128, single heads on 256; on the block map's tiles four heads
+    on 64 rows, the others one by one on 256."""
+    T, nodes, words, G = _shape(pw)
+    rest = G % 4
+    if words <= 2 and T >= (32 if G % 2 else 16) * nodes:
+        return (["k_prefill_nodes<128,4,2>"] if G > rest else []) + (["k_prefill_nodes<128,2,4>"] if rest & 2 else []) + \
+               (["k_prefill_nodes<128,1,8>"] if rest & 1 else [])
+    return (["k_prefill_bf16<128,4,2,false>"] if G > rest else []) + (["k_prefill_bf16<128,1,8,false>"] if rest else [])
+
+
+def bwd_kernels(pw):
+    """The launches of dag_attn_prefill_bwd at head dimension 128: dQ for groups of four heads on one chunk or query tile
+    (<false>), for the left-over heads one by one on 256 rows (<true>); dK / dV."""
+    T, nodes, words, G = _shape(pw)
+    rest = G % 4
+    chunks = words <= 2 and T >= (64 if rest else 16) * nodes
+    dq = "k_nodes_dq2" if chunks else "k_bwd_dq2"
+    return ("k_bwd_delta<128>",) + (("k_node_rows<%d>" % words, "k_chunk_order") if chunks else ("k_bwd_tokvis",)) + \
+        ((dq + "<false>",) if G > rest else ()) + ((() if chunks else ("k_bwd_wide_rows",)) + (dq + "<true>",) if rest else ()) + \
+        ("k_bwd_weights", "k_bwd_order", "k_nodes_dkv2" if words <= 2 and T >= 16 * nodes else "k_bwd_dkv2")
 
 
 def prefill_leg(cfg, dev, launches, warmup, workload_key, with_bwd=False):
@@ -349,19 +372,15 @@ def prefill_leg(cfg, dev, launches, warmup, workload_key, with_bwd=False):
     tf = flops / (ms_attn * 1e-3) / 1e12
     bmap = pw.meta.get("block_map")
     census = {"full": int((bmap == B.TILE_FULL).sum().item()), "partial": int((bmap == B.TILE_PARTIAL).sum().item())}
-    # the launches of one call: four-head items on 64-row tiles, left-over heads (one or two) on 256-row tiles
-    g = cfg["hq"] // cfg["hkv"]
-    wide = g % 4 if g % 4 < 3 else 0
-    kerns = (["k_prefill_bf16<%d,4,2,false>" % cfg["d"]] if g > wide else []) + \
-            (["k_prefill_bf16<%d,1,8,false>" % cfg["d"]] if wide else [])
+    kerns, bwd_k = prefill_kernels(pw), bwd_kernels(pw)
     bwd = None
     if with_bwd:
         ms_bwd, tf_bwd = backward_timing(pw, dev, 3, 1)
         bwd = {"metric": "dag_attn_prefill_bwd_useful_tflops", "value": tf_bwd, "unit": "TFLOP/s", "ms_per_call": ms_bwd,
-               "calls": 3, "roofline": {"bound": "mfma", "kernel": "+".join(bwd_kernels(cfg["hq"] // cfg["hkv"])), "achieved": tf_bwd,
+               "calls": 3, "roofline": {"bound": "mfma", "kernel": "+".join(bwd_k), "achieved": tf_bwd,
                                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                                         "frac": tf_bwd / MFMA_BF16_PEAK_TFLOPS,
-                                        "traffic": traffic_of(workload_key, *bwd_kernels(cfg["hq"] // cfg["hkv"]))}}
+                                        "traffic": traffic_of(workload_key, *bwd_k)}}
     return {"metric": "dag_attn_prefill_useful_tflops", "value": flops / (ms_path * 1e-3) / 1e12, "unit": "TFLOP/s",
             "prefill_bwd": bwd,
             "launches": launches, "ms_prefill_path(meta+rope+attn)": ms_path, "ms_attn_kernel": ms_attn,
@@ -518,7 +537,7 @@ def main():
     tflops_kernel = flops / (ms_attn * 1e-3) / 1e12
     dec_gbs = dw.bytes / (ms_deck * 1e-3) / 1e9
     cfg = pw.cfg
-    bwd_k = bwd_kernels(cfg["hq"] // cfg["hkv"])
+    kerns, bwd_k = prefill_kernels(pw), bwd_kernels(pw)
     res = {
         "metric": "dag_attn_prefill_useful_tflops",
         "value": tflops_seg,
@@ -534,9 +553,9 @@ def main():
         "segments_ms": {"prefill_path(meta+rope+attn)": ms_pre, "prefill_attn_kernel": ms_attn,
                         "decode_path(append+attn+merge)": ms_dec, "decode_attn_kernels": ms_deck,
                         "min_prefill_attn_kernel": float(np.min(attn_ms)), "min_decode_attn_kernels": float(np.min(deck_ms))},
-        "roofline": {"bound": "mfma", "kernel": "k_prefill_bf16<128,4,2,false>", "achieved": tflops_kernel,
+        "roofline": {"bound": "mfma", "kernel": "+".join(kerns), "achieved": tflops_kernel,
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tflops_kernel / MFMA_BF16_PEAK_TFLOPS,
-                     "traffic": traffic_of("main", "k_prefill_bf16<128,4,2,false>"), "algorithmic_bytes": pw.algorithmic_bytes()},
+                     "traffic": traffic_of("main", *kerns), "algorithmic_bytes": pw.algorithmic_bytes()},
         "decode": {"metric": "branch_decode_tok_per_s_one_attention_layer",
                    "value": dw.n_live / (ms_dec * 1e-3), "unit": "tok/s", "ms_per_decode_step": ms_dec,
                    "config": {"workload": dw.cfg["name"], "n_seqs": dw.cfg["n_seqs"], "live_branches": dw.n_live,

@@ -22,7 +22,8 @@
  *   - Process-wide state: none that a result depends on.  What the library keeps until the
  *     process ends is (a) per device, the address of the scratch array of
  *     dag_attn_decode_static (see there), (b) attributes set on its own kernels, and (c) the
- *     development knobs of the decode split sizes, read from the environment once.  It creates no streams and no events.  Calls on different streams may
+ *     development knobs of the decode split sizes and of the backward's first kernels, read from
+ *     the environment once.  It creates no streams and no events.  Calls on different streams may
  *     overlap if their buffers (workspaces included) do not.
  */
 #ifndef DAGATTN_H
@@ -144,13 +145,22 @@ int dag_rope_qk(const int32_t* pos_ids, int64_t n_tokens, void* q, void* k, int3
 
 /* Eq. 2 + Eq. 3: out[i] = sum_j softmax_j(q_i . k_j * softmax_scale + M_ij) v_j, where M is the
  * DAG mask described by `meta`.  q/out [T][hq][head_dim], k/v [T][hkv][head_dim] DEVICE, already
- * rotated; lse (nullable) [T][hq] fp32 receives log sum exp of the scaled scores.  Fully masked
- * tiles are skipped through the block map; only PARTIAL tiles evaluate per-token masks.
+ * rotated; lse (nullable) [T][hq] fp32 receives log sum exp of the scaled scores.
+ * Two routes.  DAG_F32, and DAG_BF16 with nodes too short for the other one, more than 128 nodes in
+ * a sequence or a `k` of 4 GiB and more: query tiles of 64 rows on the block map, which skips what is
+ * fully masked; only PARTIAL tiles evaluate per-token masks.  Otherwise DAG_BF16: chunks of query
+ * rows that begin where a node (or a run of siblings) begins, each with the keys that its node sees
+ * as one list, so that only the last tiles of a chunk take a mask.  The positions (pos_ids,
+ * node_pos_start) are read by neither.
+ * What a row does not see may hold anything in DAG_F32 and on chunks.  On the block map's bf16 tiles
+ * an Inf or NaN in v of a hidden token turns rows into NaN that share a PARTIAL 64 x 64 tile with it.
+ * `out` may be `q` itself; in DAG_BF16 `out` and `lse` may also lie on the memory of `v` (such a call
+ * takes the block map's tiles, which work from a copy of v).
  * Supported: DAG_BF16 with head_dim 64 or 128 (MFMA path, fp32 accumulation); DAG_F32 with
  * head_dim 64 or 128; hq a multiple of hkv.  meta->tile_m/tile_n must equal
  * dag_prefill_tile_shape() for the same configuration.  `ws` is DEVICE scratch of at least
- * dag_prefill_workspace_bytes() bytes, 256-byte aligned (the bf16 path keeps a key-tile-wise
- * transposed copy of V there); it may be NULL when that size is 0. */
+ * dag_prefill_workspace_bytes() bytes, 256-byte aligned (the bf16 path keeps the work lists of the
+ * chunks or a key-tile-wise transposed copy of V there); it may be NULL when that size is 0. */
 int dag_attn_prefill(const dag_meta_t* meta, const void* q, const void* k, const void* v,
                      void* out, float* lse, int32_t hq, int32_t hkv, int32_t head_dim,
                      float softmax_scale, dag_dtype_t dtype, void* ws, size_t ws_bytes,
@@ -186,12 +196,18 @@ size_t dag_prefill_workspace_bytes(const dag_meta_t* meta, int32_t hkv, int32_t 
  *   dq [T][hq][head_dim], dk and dv [T][hkv][head_dim]   (gradients w.r.t. the rotated q and k; a KV
  *   head's gradient is the sum over its query heads)
  * with P recomputed from lse: dV = P^T dO, dS = P o (dO V^T - rowsum(dO o O)), dQ = scale dS K,
- * dK = scale dS^T Q, only over the tiles the block map marks visible.  DAG_BF16 (MFMA, fp32
+ * dK = scale dS^T Q, only where the mask lets a pair through.  DAG_BF16 (MFMA, fp32
  * accumulation; gradients bf16) or DAG_F32 (plain fp32 arithmetic, the accuracy path; gradients
  * fp32), head_dim 128 or 64; all tensors DEVICE, 16-byte aligned; `ws` DEVICE scratch of
- * dag_prefill_bwd_workspace_bytes.  `meta` is the one dag_build_meta filled for the forward: the
- * bf16 path reads its block map, launch order, tile descriptors and FULL-first CSR.  No atomics:
- * results are bit-identical from run to run.  Errors as dag_attn_prefill. */
+ * dag_prefill_bwd_workspace_bytes.  `meta` is the one dag_build_meta filled for the forward.  In
+ * bf16 dQ works on the forward's chunks or on the block map's tiles (launch order, tile descriptors,
+ * FULL-first CSR), dK / dV on the rows that see 128 keys or on the block map's columns, by rules of
+ * their own on node lengths and sizes.  `dk` is scratch during the call (the work lists of the chunks
+ * are built there before it is written), except where it overlaps an input or dq: dq then takes the
+ * block map's tiles, so that dk and dv may lie on the memory of k and v.
+ * An Inf or NaN in v of a hidden token does not reach dq of the rows that do not see it; one in k, q or
+ * dout of a hidden token may turn gradients into NaN that share a masked tile with it.
+ * No atomics: results are bit-identical from run to run.  Errors as dag_attn_prefill. */
 size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* meta, int32_t hq, int32_t hkv, int32_t head_dim);
 int dag_attn_prefill_bwd(const dag_meta_t* meta, const void* q, const void* k, const void* v,
                          const void* out, const void* dout, const float* lse, void* dq, void* dk,

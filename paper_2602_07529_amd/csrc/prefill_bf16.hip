@@ -1700,7 +1700,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // the last tiles of an item hold tokens that not all of their rows see (rows of the same chunk further
     // on, siblings), wherever the nodes begin.  So a wave whose outputs are not numbers although its row
     // sums are goes over its rows again, key by key, with nothing but the visible ones.  As long as every
-    // output is a number this costs one comparison for two of them; where a visible V is not finite the
+    // output is a number this costs a maximum over them; where a visible V is not finite the
     // outputs stay what they are, and the walk ends once no number is left in the wave.
     if constexpr (NODES) {
 #pragma unroll

@@ -395,8 +395,8 @@ __global__ void __launch_bounds__(64) k_bwd_weights(BwdArgs a) {
   for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
   if (lane == 0) a.kt_weight[kt] = (ktl & 1) ? -1 : n;
 }
-// First visibility word of every token's node, so that the dK/dV kernel can fetch it for the rows
-// of a tile without a load that depends on another load.
+// First visibility word of every token's node, so that the dQ kernels on the block map's tiles can fetch it for
+// their rows without a load that depends on another load.
 __global__ void __launch_bounds__(256) k_bwd_tokvis(BwdArgs a, int total_tokens) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= total_tokens) return;
@@ -1787,9 +1787,6 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
                   : a.G == 2 ? launch_dq<D, 2>(a, total_qtiles, stream) : launch_dq<D, 1>(a, total_qtiles, stream);
   }
   if (rc != DAG_OK) return rc;
-  constexpr int sm = dkv_smem_bytes<D>();
-  if (hipFuncSetAttribute((const void*)k_bwd_dkv<D>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
-    return DAG_ERR_HIP;
   hipLaunchKernelGGL(k_bwd_weights, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
   hipLaunchKernelGGL(k_bwd_order, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
   DAG_LAUNCH_CHECK();
@@ -1800,6 +1797,9 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
       return DAG_ERR_HIP;
     hipLaunchKernelGGL(ring, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
   } else {
+    constexpr int sm = dkv_smem_bytes<D>();
+    if (hipFuncSetAttribute((const void*)k_bwd_dkv<D>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
+      return DAG_ERR_HIP;
     hipLaunchKernelGGL((k_bwd_dkv<D>), dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm, stream, a);
   }
   DAG_LAUNCH_CHECK();
