@@ -14,7 +14,7 @@
 // order of what its node sees: all but its last tiles are free of masks, and V is read as it is
 // through the transposing LDS load.  Random DAGs of 8 x 64 nodes of 32 to 256 tokens, 32 / 8 heads: 62 %
 // of the block map's tiles are PARTIAL and 34 % of what they compute is masked; 1770 + 83 (V^T) us on
-// them, 1357 + 13 (tables) on chunks.  2048 -> 8 x 256 -> 512: 618 -> 598 us for the whole prefill, the
+// them, 1357 + 14 (tables) on chunks.  2048 -> 8 x 256 -> 512: 618 -> 598 us for the whole prefill, the
 // V^T pre-pass being gone; the same fork-join 16 times as long: 38.6 -> 37.7 ms.
 // On the block map's tiles (k_prefill_bf16) for nodes too short for chunks, more than 128 nodes, and
 // (PAGED) paged contexts:

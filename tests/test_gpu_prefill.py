@@ -84,10 +84,11 @@ def test_config4_random_multilevel_full_size_sampled_rows():
 @pytest.mark.parametrize("hq,hkv,d", [(5, 1, 128), (6, 1, 128), (2, 2, 64), (9, 1, 64)])
 def test_left_over_heads_on_256_row_tiles_ragged_multilevel_dags(hq, hkv, d):
     """Head groups of 5, 6, 1 and 9 (one or two heads beside the four-head items, or alone) on
-    sequences of 1 to 19 query tiles whose lengths leave a ragged 256-row tile: the rows of those
-    tiles over the key tiles are derived from the 64 x 64 block map on the device (mixed SKIP / FULL
-    / PARTIAL quartets, fully hidden 32-row blocks inside a visited tile); sampled rows of every
-    sequence and every head."""
+    sequences of 1 to 19 query tiles whose lengths leave a ragged 256-row tile; sampled rows of every
+    sequence and every head.  The group of 5 runs on the block map's tiles, the rows of its
+    256-row tiles over the key tiles derived from the 64 x 64 block map on the device (mixed SKIP / FULL
+    / PARTIAL quartets, fully hidden 32-row blocks inside a visited tile); the others run on query chunks
+    (tests/test_gpu_prefill_routes.py has every group on either route)."""
     rng = np.random.Generator(np.random.PCG64(4000 + hq + d))
     dag_list = [dags.random_dag(rng, n_nodes=40, depth=5, len_lo=1, len_hi=60)[:2],
                 dags.fork_join(517, [64, 190, 3], 131),
@@ -229,8 +230,8 @@ def test_config4_one_sequence_every_row_of_one_kv_group():
 
 
 def test_bf16_two_visibility_words_many_tiles():
-    """More than 64 nodes (two visibility words per node) at several thousand tokens: the masked
-    tiles fetch their visibility word inside the pipeline, here with dozens of tiles per row."""
+    """More than 64 nodes (two visibility words per node) at several thousand tokens, on query chunks with lists of
+    runs over two words (the block map's tiles with two and three words: tests/test_gpu_prefill_routes.py)."""
     rng = np.random.Generator(np.random.PCG64(177))
     L, anc, _, _ = dags.random_dag(rng, n_nodes=100, depth=7, len_lo=16, len_hi=80)
     assert anc.shape[1] == 2 and int(np.sum(L)) >= 4000

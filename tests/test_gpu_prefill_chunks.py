@@ -21,7 +21,8 @@ def _check(dag_list, hq, hkv, d, seed):
     assert np.abs(lse.cpu().double().numpy() - ref_lse).max() < 2e-2
 
 
-# every launch shape: items of four heads, pairs, single heads
+# every head split: items of four heads, pairs, single heads (the one- and two-head items of batches that leave compute
+# units idle: tests/test_gpu_prefill_routes.py)
 @pytest.mark.gpu
 @pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (2, 1, 128), (1, 1, 128), (7, 1, 128), (10, 2, 128),
                                       (4, 1, 64), (2, 1, 64), (1, 1, 64), (7, 1, 64), (12, 2, 64)])
