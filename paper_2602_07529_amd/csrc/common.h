@@ -44,6 +44,19 @@ __device__ __forceinline__ uint32_t dag_pack_bf2(float lo, float hi) {
 __device__ __forceinline__ float dag_bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float dag_bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// Whether a row of D bf16 (16-byte aligned) holds an Inf or NaN.
+template <int D>
+__device__ __forceinline__ bool dag_row_not_finite(const void* row) {
+  bool bad = false;
+#pragma unroll
+  for (int s = 0; s < D / 8; ++s) {
+    const u32x4 x = ((const u32x4*)row)[s];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad |= (x[e] & 0x7f80u) == 0x7f80u || (x[e] & 0x7f800000u) == 0x7f800000u;
+  }
+  return bad;
+}
+
 // Largest sequence index b with start[b] <= x, for a non-decreasing array start[0..n] (start[0] = 0).
 template <typename T>
 __device__ __forceinline__ int dag_find_segment(const T* start, int n, T x) {

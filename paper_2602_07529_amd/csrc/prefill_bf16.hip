@@ -1699,9 +1699,9 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // ---- A hidden key goes through the products with probability zero, and 0 x Inf or NaN is NaN: on chunks
     // the last tiles of an item hold tokens that not all of their rows see (rows of the same chunk further
     // on, siblings), wherever the nodes begin.  So a wave whose outputs are not numbers although its row
-    // sums are goes over its rows again, key by key, with nothing but the visible ones.  As long as every
-    // output is a number this costs a maximum over them; where a visible V is not finite the
-    // outputs stay what they are, and the walk ends once no number is left in the wave.
+    // sums are, and whose masked tiles hold a V row that is not finite, goes over its rows again, key by key, with
+    // nothing but the visible ones (until no number is left in the wave).  As long as every output is
+    // a number this costs a maximum over them.
     if constexpr (NODES) {
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
@@ -1712,6 +1712,20 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
           for (int e = 0; e < 16; e += 2)
             any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(O[r][db][e], O[r][db][e + 1]), any);
         if (__builtin_amdgcn_ballot_w64(any != any && l[r] + __shfl_xor(l[r], 32) < INFINITY) == 0) continue;
+        const int end = cur.nstart + min(cur.row0 + 32 * NRG, cur.T);      // (wave-uniform)
+        bool suspect = false;
+#pragma unroll 1
+        for (int p0 = cur.nfast * TN; p0 < end && !suspect; p0 += 64) {  // a position per lane
+          const int p = min(p0 + lane, end - 1);
+          int tok = cur.cu;
+          for (int e = 0; e < 64; ++e) {
+            const int2 run = ((const int2*)a.col)[cur.c0 + e];
+            if (run.x >= p0 + 64) break;
+            tok = p >= run.x ? p + run.y : tok;
+          }
+          suspect = __builtin_amdgcn_ballot_w64(dag_row_not_finite<D>(vtg + (size_t)tok * rowbytes + cur.hk * (D * 2))) != 0;
+        }
+        if (!suspect) continue;
         u32x4 qr[KSTEPS];  // the row as load_q and scale_q left it (qf holds the next item's by now)
         const uint16_t* qp = qg + ((size_t)token_of(cur, r) * a.hq + head_of(cur)) * D + 8 * H;
 #pragma unroll
@@ -1725,7 +1739,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) O[r][db][e] = 0.f;
         const int own = cur.nstart + min(row_of(cur, r), cur.T - 1);       // the row's own position
-        const int end = cur.nstart + min(cur.row0 + 32 * NRG, cur.T);      // (wave-uniform)
         int run = 0;
 #pragma unroll 1
         for (int p = 0; p < end; ++p) {

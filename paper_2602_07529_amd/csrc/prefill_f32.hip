@@ -164,9 +164,9 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   l += __shfl_xor(l, 32);
   // A hidden key goes through the products with probability zero, and 0 x Inf or NaN is NaN: where a visited
   // tile holds a V row that is not finite, rows that do not see it would be lost.  So a wave whose outputs
-  // are not numbers although its row sums are goes over its rows again, key by key, with nothing but the
-  // visible ones; as long as every output is a number this costs a maximum over them (one that, unlike
-  // fmaxf, hands a NaN on).  o(x, e, c): this lane's output dimension 64 x + 16 g + 4 (e0 + e) + c before the
+  // are not numbers although its row sums are, and whose tiles with a mask hold such a V row, goes over its
+  // rows again, key by key, with nothing but the visible ones; as long as every output is a number this
+  // costs a maximum over them (one that, unlike fmaxf, hands a NaN on).  o(x, e, c): this lane's output dimension 64 x + 16 g + 4 (e0 + e) + c before the
   // division, set(x, e, c, value) replaces it.
   auto nan_among = [&](auto ne, auto&& o) __attribute__((always_inline)) {
     float any = 0.f;
@@ -180,6 +180,22 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   };
   auto visible_keys_only = [&](auto ne, int e0, float m_row, auto&& o, auto&& set) __attribute__((always_inline)) {
     constexpr int NE = decltype(ne)::value;
+    bool suspect = false;
+#pragma unroll 1
+    for (int n = 0; n < n_tiles && !suspect; ++n) {  // a key per lane
+      const int j0 = a.col[c0 + n] * TN;
+      if (a.flag[c0 + n] == DAG_TILE_FULL && j0 + TN <= T) continue;
+      const float* vp = (const float*)a.v + ((size_t)(cu + min(j0 + lane, T - 1)) * a.hkv + hk) * D;
+      bool bad = false;
+#pragma unroll 4
+      for (int d = 0; d < D; d += 4) {
+        const f32x4 v4 = *(const f32x4*)(vp + d);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bad |= !(fabsf(v4[c]) < INFINITY);
+      }
+      suspect = __builtin_amdgcn_ballot_w64(bad) != 0;
+    }
+    if (!suspect) return;
 #pragma unroll
     for (int x = 0; x < X; ++x)
 #pragma unroll
