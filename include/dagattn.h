@@ -205,8 +205,10 @@ size_t dag_prefill_workspace_bytes(const dag_meta_t* meta, int32_t hkv, int32_t 
  * their own on node lengths and sizes.  `dk` is scratch during the call (the work lists of the chunks
  * are built there before it is written), except where it overlaps an input or dq: dq then takes the
  * block map's tiles, so that dk and dv may lie on the memory of k and v.
- * An Inf or NaN in v of a hidden token does not reach dq of the rows that do not see it; one in k, q or
- * dout of a hidden token may turn gradients into NaN that share a masked tile with it.
+ * On chunks and streams of rows, too, what a row does not see does not reach its dq, nor a row that does not
+ * see a key that key's dk and dv, whatever it holds (dk and dv only where they overlap no input).  On the
+ * block map's tiles an Inf or NaN in k, q or dout of a hidden token may turn gradients into NaN
+ * that share a masked tile with it.
  * No atomics: results are bit-identical from run to run.  Errors as dag_attn_prefill. */
 size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* meta, int32_t hq, int32_t hkv, int32_t head_dim);
 int dag_attn_prefill_bwd(const dag_meta_t* meta, const void* q, const void* k, const void* v,

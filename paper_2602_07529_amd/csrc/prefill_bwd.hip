@@ -67,6 +67,7 @@ struct BwdArgs {
   // the list of the tiles NQ c .. of a sequence lies where row NQ c of its dense block map does
   int dq_narrow;
   int total_qtiles;
+  int32_t* kt_again;  // [total key tiles] set where k_dkv_again has to look (in the place of tok_vis0, which dQ has read by then)
   int32_t* wide_col;    // [dense map] key tiles that one of the query tiles sees, those that all of them see in full first
   int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every NQ-th tile)
   int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups, sequence after sequence; last element: their number
@@ -414,6 +415,7 @@ __global__ void __launch_bounds__(64) k_bwd_order(BwdArgs a) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) rank += __shfl_xor(rank, o);
   if (lane == 0) a.kt_order[rank] = kt;
+  if (lane == 0 && a.dkv_stream) a.kt_again[kt] = 0;
 }
 
 template <int D>
@@ -1348,11 +1350,105 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   asm volatile("" : "+v"(key));  // (recomputed here: its offsets need no registers across the loops)
   const int j_out = ktl * BN + key;
   dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < T, H, dK, dV);
+  if constexpr (NODES) {  // sums that are not numbers: k_dkv_again looks into it
+    float any = 0.f;  // (maximum, unlike fmaxf, hands a NaN on)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(dK[db][e], dV[db][e]), any);
+    if (any != any) a.kt_again[kt] = 1;
+  }
 }
 __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) { dkv_ring_body<128, false>(a); }
 __global__ void __launch_bounds__(256, 2) k_bwd64_dkv(BwdArgs a) { dkv_ring_body<64, false>(a); }
 __global__ void __launch_bounds__(256) k_nodes_dkv2(BwdArgs a) { dkv_ring_body<128, true>(a); }
 __global__ void __launch_bounds__(256, 2) k_nodes64_dkv(BwdArgs a) { dkv_ring_body<64, true>(a); }
+
+// Behind the streams: their masked tiles multiply a hidden row's Q and dO by zero, and 0 x Inf or NaN is NaN.  A
+// wave of a workgroup whose sums are not numbers, and whose keys some row that is not finite does not see (at
+// least one of them), takes its keys again, row by row with nothing but the visible ones, until no number is
+// left.  A kernel of its own, because the streams have no register left for it (a few of them spilled, in the
+// loop, wherever this went); with nothing to do it takes 3 us of 900.
+template <int D>
+__device__ void dkv_again(const BwdArgs& a, int kt, int hk) {
+  const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
+  const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu, nbase = a.node_start[b];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, H = lane >> 5;
+  const int j0 = (kt - a.ktile_start[b]) * BN + 32 * w, j = j0 + (lane & 31), jc = min(j, T - 1);
+  if (j0 >= T) return;
+  const bool key_ok = j < T;
+  const int node = a.tok_node[cu + jc], u0 = a.tok_node[cu + j0], j1 = min(j0 + 31, T - 1), u1 = a.tok_node[cu + j1];
+  auto sees = [&](int ni, int u) { return ((a.node_vis[(int64_t)(nbase + ni) * a.W + (u >> 6)] >> (u & 63)) & 1) != 0; };
+  bool suspect = false;
+  for (int i0 = (kt - a.ktile_start[b]) * BN; i0 < T && !suspect; i0 += 64) {  // a row per lane
+    const int i = min(i0 + lane, T - 1), ni = a.tok_node[cu + i];
+    bool all = i >= j1;
+    for (int u = u0; u <= u1; ++u) all = all && sees(ni, u);
+    bool bad = false;
+    if (!all)
+      for (int g = 0; g < a.G; ++g) {
+        const size_t row = (size_t)(cu + i) * a.hq + hk * a.G + g;
+        bad |= dag_row_not_finite<D>(a.q + row * D) || dag_row_not_finite<D>(a.dout + row * D) || !(fabsf(a.nlse2[row]) < INFINITY) ||
+               !(fabsf(a.delta[row]) < INFINITY);
+      }
+    suspect = __builtin_amdgcn_ballot_w64(bad) != 0;
+  }
+  if (!suspect) return;
+  f32x16 dK[D / 32], dV[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) dK[db][e] = dV[db][e] = 0.f;
+  const size_t koff = ((size_t)(cu + jc) * a.hkv + hk) * D;
+#pragma unroll 1
+  for (int i = j0; i < T; ++i) {
+    const int ni = a.tok_node[cu + i];
+    const bool ok = key_ok && (ni == node ? j <= i : sees(ni, node));
+    bool number = false;
+#pragma unroll 1
+    for (int g = 0; g < a.G; ++g) {
+      const size_t row = (size_t)(cu + i) * a.hq + hk * a.G + g;
+      const uint16_t *qp = a.q + row * D, *dop = a.dout + row * D;
+      float s = 0.f, dp = 0.f;
+#pragma unroll
+      for (int x = 0; x < D / 16; ++x) {
+        const u32x4 qr = *(const u32x4*)(qp + 16 * x + 8 * H), dr = *(const u32x4*)(dop + 16 * x + 8 * H);
+        const u32x4 kr = *(const u32x4*)(a.k + koff + 16 * x + 8 * H), vr = *(const u32x4*)(a.v + koff + 16 * x + 8 * H);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s = fmaf(dag_bf_hi(kr[e]), dag_bf_hi(qr[e]), fmaf(dag_bf_lo(kr[e]), dag_bf_lo(qr[e]), s));
+          dp = fmaf(dag_bf_hi(vr[e]), dag_bf_hi(dr[e]), fmaf(dag_bf_lo(vr[e]), dag_bf_lo(dr[e]), dp));
+        }
+      }
+      s += __shfl_xor(s, 32);
+      dp += __shfl_xor(dp, 32);
+      const float pe = __builtin_amdgcn_exp2f(fmaf(s, a.sc, a.nlse2[row])), ds = pe * (dp - a.delta[row]);
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {  // dimensions 32 db + 8 e4 + 4 H .. + 3
+          const u32x2 qr = *(const u32x2*)(qp + 32 * db + 8 * e4 + 4 * H), dr = *(const u32x2*)(dop + 32 * db + 8 * e4 + 4 * H);
+          const float q4[4] = {dag_bf_lo(qr[0]), dag_bf_hi(qr[0]), dag_bf_lo(qr[1]), dag_bf_hi(qr[1])};
+          const float d4[4] = {dag_bf_lo(dr[0]), dag_bf_hi(dr[0]), dag_bf_lo(dr[1]), dag_bf_hi(dr[1])};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float k0 = dK[db][4 * e4 + e], v0 = dV[db][4 * e4 + e];
+            const float k1 = ok ? fmaf(ds, q4[e], k0) : k0, v1 = ok ? fmaf(pe, d4[e], v0) : v0;
+            dK[db][4 * e4 + e] = k1;
+            dV[db][4 * e4 + e] = v1;
+            number |= k1 == k1 || v1 == v1;
+          }
+        }
+    }
+    if (__builtin_amdgcn_ballot_w64(key_ok && number) == 0) break;
+  }
+  dkv_store<D>(a, koff, key_ok, H, dK, dV);
+}
+template <int D>
+__global__ void __launch_bounds__(256) k_dkv_again(BwdArgs a) {
+  if (a.kt_again[blockIdx.x] == 0) return;
+  for (int hk = 0; hk < a.hkv; ++hk) dkv_again<D>(a, blockIdx.x, hk);
+}
 
 // Tile lists of the dQ workgroups that take one query head on a group of NQ = four (head dimension
 // 128) or two query tiles (the heads that do not fill a workgroup on one tile): one wave per query
@@ -1716,6 +1812,70 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   };
   ring_loop(std::false_type{}, 0, NF);
   ring_loop(std::true_type{}, NF, t.N);  // the masked and the ragged tiles
+  // The masked tiles of a chunk multiply a hidden key's K by zero, and 0 x Inf or NaN is NaN: as in dK / dV above
+  // the dQ rows of such a wave are taken again from the visible keys.
+  if constexpr (NODES) {
+    float any = 0.f;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(dQ[db][e], dQ[db][e + 1]), any);
+    const int2* const runs = (const int2*)a.runs + t.c0;
+    bool suspect = false;
+    if (__builtin_amdgcn_ballot_w64(row_ok && any != any) != 0) {
+#pragma unroll 1
+      for (int p0 = NF * BN; p0 < n_pos && !suspect; p0 += 64) {  // a key per lane
+        const int p = min(p0 + lane, n_pos - 1);
+        int tok = cu;
+        for (int e = 0; e < 64 && runs[e].x < p0 + 64; ++e) tok = p >= runs[e].x ? p + runs[e].y : tok;
+        suspect = __builtin_amdgcn_ballot_w64(dag_row_not_finite<D>(a.k + ((size_t)tok * a.hkv + hk) * D)) != 0;
+      }
+    }
+    if (suspect) {
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dQ[db][e] = 0.f;
+      const int own = anc + iq_row;
+      int run = 0;
+#pragma unroll 1
+      for (int p = 0; p < n_pos; ++p) {
+        while (run < 63 && runs[run + 1].x <= p) ++run;
+        const size_t row = (size_t)(p + runs[run].y) * a.hkv + hk;
+        const uint16_t *kp = a.k + row * D, *vp = a.v + row * D;
+        const bool ok = row_ok && (p < anc || (p <= own && p >= own - depth));
+        float s = 0.f, dp = 0.f;
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x) {
+          const u32x4 kr = *(const u32x4*)(kp + 16 * x + 8 * H), vr = *(const u32x4*)(vp + 16 * x + 8 * H);
+          const u32x4 qr = __builtin_bit_cast(u32x4, me.qf[x]), dr = __builtin_bit_cast(u32x4, me.dof[x]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            s = fmaf(dag_bf_hi(kr[e]), dag_bf_hi(qr[e]), fmaf(dag_bf_lo(kr[e]), dag_bf_lo(qr[e]), s));
+            dp = fmaf(dag_bf_hi(vr[e]), dag_bf_hi(dr[e]), fmaf(dag_bf_lo(vr[e]), dag_bf_lo(dr[e]), dp));
+          }
+        }
+        s += __shfl_xor(s, 32);
+        dp += __shfl_xor(dp, 32);
+        const float ds = __builtin_amdgcn_exp2f(fmaf(s, sc, nl)) * (dp - dl);
+        bool number = false;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) {
+            const u32x2 kr = *(const u32x2*)(kp + 32 * db + 8 * e4 + 4 * H);
+            const float k4[4] = {dag_bf_lo(kr[0]), dag_bf_hi(kr[0]), dag_bf_lo(kr[1]), dag_bf_hi(kr[1])};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float before = dQ[db][4 * e4 + e], after = ok ? fmaf(ds, k4[e], before) : before;
+              dQ[db][4 * e4 + e] = after;
+              number |= after == after;
+            }
+          }
+        if (__builtin_amdgcn_ballot_w64(row_ok && number) == 0) break;
+      }
+    }
+  }
   dq_store<D>(a, me, H, dQ);
 }
 template <bool WIDE>
@@ -1796,6 +1956,16 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
     if (hipFuncSetAttribute((const void*)ring, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
     hipLaunchKernelGGL(ring, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
+    // (it reads K, V, Q and dO once more: not where the gradients have been written over them)
+    const size_t q_bytes = (size_t)a.total_rows * D * 2, k_bytes = q_bytes / a.G;
+    auto apart = [&](const void* p, size_t p_bytes, const void* out) {
+      return (const char*)p + p_bytes <= (const char*)out || (const char*)out + k_bytes <= (const char*)p;
+    };
+    bool again = a.dkv_stream;
+    for (const void* out : {(const void*)a.dk, (const void*)a.dv})
+      again = again && apart(a.q, q_bytes, out) && apart(a.dout, q_bytes, out) && apart(a.k, k_bytes, out) && apart(a.v, k_bytes, out);
+    if (again)
+      hipLaunchKernelGGL(k_dkv_again<D>, dim3((unsigned)total_ktiles), dim3(256), 0, stream, a);
   } else {
     constexpr int sm = dkv_smem_bytes<D>();
     if (hipFuncSetAttribute((const void*)k_bwd_dkv<D>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
@@ -2082,6 +2252,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.wide_n = (int32_t*)((char*)a.wide_col + dag_align_up((size_t)m->sizes.total_tiles * 4, 256));
   a.wide_nfast = a.wide_n + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
   a.wide_list = a.wide_nfast + dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256) / 4;
+  a.kt_again = (int32_t*)a.tok_vis0;  // (eight bytes a token against four a key tile)
   a.total_qtiles = (int)m->sizes.total_qtiles;
   a.dq_narrow = hq / hkv - (lists ? bwd_wide_heads(hq / hkv, head_dim) : 0);
   a.cu_seqlens = m->cu_seqlens; a.node_start = m->node_start; a.tok_node = m->tok_node;
@@ -2096,7 +2267,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.node_tok_start = m->node_tok_start;
   // Forward and backward, block map : streams, nodes of 16 / 24 / 32 / 64 / 144 tokens on average: 32 / 8 heads of
   // dimension 128 1.00 / 1.02 / 1.02 / 1.06 / 1.08, 16 / 8 heads of dimension 64 1.00 / 1.05 / 1.06 / 1.07 / 1.07.
-  a.dkv_stream = m->node_tok_start && m->words_per_node <= 2 && a.total_rows * head_dim <= (long)UINT32_MAX &&
+  a.dkv_stream = !bwd_first_version() && m->node_tok_start && m->words_per_node <= 2 && a.total_rows * head_dim <= (long)UINT32_MAX &&
                  m->sizes.total_tokens >= 16 * m->sizes.total_nodes;  // (row offsets are 32-bit)
   a.runs = nullptr;
   if (bwd_dq_on_chunks(m, a, head_dim)) {

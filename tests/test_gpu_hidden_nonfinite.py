@@ -87,3 +87,37 @@ def test_hidden_values_backward_dq(hq, hkv, d, n_nodes, longest):
     B.dag_attn_prefill_bwd(meta, qd, kd, _spoil(v, bad).to(DEV), out, dod, lse, dq, dk, dv)
     ref = orc.attn_prefill_bwd(dags.to_f64(q), dags.to_f64(k), dags.to_f64(v), dags.to_f64(dout), *dag_list[0])[0]
     _check(dq, ref, ~_sees_bad(dag_list, bad, T), TOL[torch.bfloat16])
+
+
+# a branch and the last token of another one hold nothing but Inf and NaN, in every input: the siblings' gradients, and those
+# of the tokens in front of the fork for the rows' part, are what they are without them
+@pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (3, 1, 64), (4, 1, 128), (5, 1, 128)])
+@pytest.mark.parametrize("prefix,branches", [(128, [64, 64, 64, 64]), (77, [40, 100, 64, 90, 130])])
+def test_hidden_tokens_backward(prefix, branches, hq, hkv, d):
+    dag_list = [dags.fork_join(prefix, branches, None), dags.linear_chain([200, 77])]
+    L, anc = dag_list[0]
+    T = int(sum(int(np.sum(x)) for x, _ in dag_list))
+    start = prefix + branches[0]
+    bad = np.concatenate([np.arange(start, start + branches[1]), [prefix + sum(branches[:3]) - 1]])
+    q, k, v = dags.make_qkv(90 + hq, T, hq, hkv, d, 0.7, torch.bfloat16)
+    dout = dags.make_qkv(91 + hq, T, hq, hkv, d, 1.0, torch.bfloat16)[0]
+    _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
+    qd, kd, vd, dod = (_spoil(x, bad).to(DEV) for x in (q, k, v, dout))
+    out, lse = torch.empty_like(qd), torch.empty(T, hq, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, qd, kd, vd, out, lse)
+    dq, dk, dv = torch.empty_like(qd), torch.empty_like(kd), torch.empty_like(vd)
+    B.dag_attn_prefill_bwd(meta, qd, kd, vd, out, dod, lse, dq, dk, dv)
+    ref, t0 = [], 0
+    for x, y in dag_list:
+        sl = slice(t0, t0 + int(np.sum(x)))
+        ref.append(orc.attn_prefill_bwd(*(dags.to_f64(z[sl]) for z in (q, k, v, dout)), x, y))
+        t0 = sl.stop
+    dq_ref, dk_ref, dv_ref = (np.concatenate(z) for z in zip(*ref))
+    lost_rows = _sees_bad(dag_list, bad, T)                 # (a bad row sees itself)
+    lost_keys, n = np.zeros(T, dtype=bool), int(np.sum(L))
+    lost_keys[:n] = orc.explicit_mask(L, anc)[lost_rows[:n]].any(axis=0)
+    assert not lost_keys.all() and lost_keys[:prefix].all()
+    _check(dq, dq_ref, ~lost_rows, TOL[torch.bfloat16])
+    _check(dk, dk_ref, ~lost_keys, TOL[torch.bfloat16])
+    _check(dv, dv_ref, ~lost_keys, TOL[torch.bfloat16])
+    assert not torch.isfinite(dv[:prefix].float()).all(dim=-1).any()
