@@ -351,7 +351,7 @@ def bwd_kernels(pw):
     dq = "k_nodes_dq2" if chunks else "k_bwd_dq2"
     return ("k_bwd_delta<128>",) + (("k_node_rows<%d>" % words, "k_chunk_order") if chunks else ("k_bwd_tokvis",)) + \
         ((dq + "<false>",) if G > rest else ()) + ((() if chunks else ("k_bwd_wide_rows",)) + (dq + "<true>",) if rest else ()) + \
-        ("k_bwd_weights", "k_bwd_order", "k_nodes_dkv2" if words <= 2 and T >= 16 * nodes else "k_bwd_dkv2")
+        ("k_bwd_weights", "k_bwd_order") + (("k_nodes_dkv2", "k_dkv_again<128>") if words <= 2 and T >= 16 * nodes else ("k_bwd_dkv2",))
 
 
 def prefill_leg(cfg, dev, launches, warmup, workload_key, with_bwd=False):
