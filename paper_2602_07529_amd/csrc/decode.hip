@@ -22,6 +22,7 @@
 #include <stdlib.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -51,6 +52,8 @@ struct DecodeArgs {
   int items_a, items_b;
   int item_base;     // first work item of this launch (k_decode)
   int wide_shared;   // k_decode_wide: workgroups that take shared items (the rest take own pages)
+  int wide_first;    // k_decode_wide: workgroups with own pages that are launched before them
+  int wide_own;      // k_decode_wide: waves of a workgroup that share an own item
   float sc;          // softmax_scale * log2(e)
   float th;          // 8 / sc: how far a score may exceed the reference maximum before it is raised
   float scale;
@@ -564,299 +567,563 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
   }
 }
 
-// Shared items of wide sibling groups (more than 32 stacked query rows per KV head, e.g. 32 siblings
-// x 5 query heads): one workgroup per (group, kv head, page split) with one wave per 32-row
-// block.  The waves share the K/V blocks through a ring in LDS (global -> LDS directly, 16 bytes
-// per lane; a page of the pools is already the operand image), so the shared pages are streamed
-// once per group whatever the number of rows, and up to RING blocks are in flight per workgroup
-// instead of one per wave.  A row block is served by `nsub` waves that take the key blocks in
-// turn (wave `sub` of a row block computes blocks sub, sub + nsub, ...), each with accumulators
-// of its own that are put together through LDS at the end: a wave's chain of LDS reads, score
-// MFMAs, softmax arithmetic and P V MFMAs is long and serial, so a SIMD needs two or three of
-// them to stay busy.  The workgroup meets at a barrier once per round of nsub blocks.  Writes the
-// same partials as the shared items of k_decode.
-constexpr int WIDE_RING = 6;                    // 32-key blocks in the ring (96 KiB of LDS at head_dim 128; behind it the query operands)
-constexpr int WIDE_MAX_WAVES = 8;               // row blocks of a workgroup
-constexpr int WIDE_MAX_THREADS = 768;           // three waves per SIMD (the register budget is set for that)
-constexpr int WIDE_OWN_WAVES = WIDE_RING / 2;   // waves that share the own pages of a branch
-template <int D>
-constexpr int wide_block_bytes() { return 4 * PAGE * D * 2; }  // K and V of two pages
-// waves per row block: as many as fit into twelve waves, and their accumulators (64 lanes x
-// (D / 2 + 4) floats per wave) into the ring for the final combination
-// (a round's blocks are issued a round ahead, so the ring holds two rounds)
-inline int wide_nsub(int rb_max, int D) {
-  int n = (WIDE_MAX_THREADS / 64) / rb_max;
-  if (n > WIDE_RING / 2) n = WIDE_RING / 2;
-  while (n > 1 && (size_t)(n - 1) * rb_max * 64 * (D / 2 + 4) * 4 > (size_t)WIDE_RING * 4 * PAGE * D * 2) --n;
-  return n < 1 ? 1 : n;
+// Wide sibling groups (more than 32 stacked query rows per KV head, e.g. 32 siblings x 5 query heads).
+//
+// Shared items: a workgroup of eight waves per (group, kv head, page slice), a wave per 32-row block, so that the
+// shared pages are streamed once per group whatever the number of rows.  The waves read the same K/V tiles of 64
+// keys (four pages) from rings in LDS that are filled directly from the pools (a page is the operand image).  Up to
+// four row blocks are served by two waves each, one for either half of every tile, with accumulators of
+// their own that are put together at the end.
+// A wave walks its 32-key units in a pipeline: in one run of slots it takes the scores of unit u, the
+// exponentials of unit u - 1 and the P V product of unit u - 2, a slot being one operand read, one MFMA and a share
+// of the exponentials; the two products alternate, so that consecutive MFMAs do not depend on each other.
+// The reference maximum is not looked after before the exponentials: a lane's sum of 16 probabilities
+// tells afterwards whether a score left the range.
+// Own items: (branch, kv head, page slice) in workgroups of the same launch; every wave streams a part of an item's
+// pages as k_decode does and the partials are put together in LDS.
+// Five and six row blocks: a tile takes as long as the SIMD with the most to do, and four waves with
+// two units of a tile each leave the others a unit or none.  Four row blocks have a wave each; the waves
+// 4 .. 7 share what is left, one half of every tile each (six) or of every second one (five): 105 -> 99 us.
+// 2 groups of 32 siblings x 5 heads on 8 KV heads, 32 K shared and 640 own tokens (436 MB): 128 us with units in
+// read - wait - multiply phases by ten waves, 93 us so = 4.7 TB/s; the matrix pipes need 17 us of it.
+constexpr int WIDE_WAVES = 8;        // of a workgroup: two per SIMD
+constexpr int WIDE_MAX_BLOCKS = 8;   // row blocks of a workgroup
+constexpr int WIDE_TILE_PAGES = 4;
+constexpr int WIDE_RING = 4;         // tiles in the K ring and in the V ring
+constexpr int WIDE_MAX_PAGES = 128;  // of a shared slice: its page ids sit in two registers
+// dynamic LDS of a launch: the rings, or the query operands and the partials of the own items
+inline int wide_own_bytes(int G, int D, int own) { return WIDE_WAVES / own * (D / 16 * 1024) + WIDE_WAVES * G * (D + 6) * 4; }
+inline int wide_lds_bytes(int G, int D, int own) {
+  const int rings = 2 * WIDE_RING * WIDE_TILE_PAGES * PAGE * D * 2, bytes = wide_own_bytes(G, D, own);
+  return rings > bytes ? rings : bytes;
 }
-// dynamic LDS of a launch: the ring, then the query operands of every row block
-inline int wide_lds_bytes(int rb_max, int D) { return WIDE_RING * 4 * PAGE * D * 2 + rb_max * (D / 16) * 1024; }
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {  // s_waitcnt vmcnt(n), n <= 56, wave-uniform
-  // vmcnt is split over bits 3:0 and 15:14 of the immediate (gfx9 encoding)
-  switch (n >> 2) {
-#define DAG_VM_CASE(q)                                                                         \
-  case q:                                                                                       \
-    switch (n & 3) {                                                                            \
-      case 0: __builtin_amdgcn_s_waitcnt(0x0F70 | ((4 * q + 0) & 15) | (((4 * q + 0) >> 4) << 14)); break; \
-      case 1: __builtin_amdgcn_s_waitcnt(0x0F70 | ((4 * q + 1) & 15) | (((4 * q + 1) >> 4) << 14)); break; \
-      case 2: __builtin_amdgcn_s_waitcnt(0x0F70 | ((4 * q + 2) & 15) | (((4 * q + 2) >> 4) << 14)); break; \
-      default: __builtin_amdgcn_s_waitcnt(0x0F70 | ((4 * q + 3) & 15) | (((4 * q + 3) >> 4) << 14)); break; \
-    }                                                                                           \
-    break;
-    DAG_VM_CASE(0) DAG_VM_CASE(1) DAG_VM_CASE(2) DAG_VM_CASE(3) DAG_VM_CASE(4) DAG_VM_CASE(5) DAG_VM_CASE(6)
-    DAG_VM_CASE(7) DAG_VM_CASE(8) DAG_VM_CASE(9) DAG_VM_CASE(10) DAG_VM_CASE(11) DAG_VM_CASE(12) DAG_VM_CASE(13)
-#undef DAG_VM_CASE
-    default: __builtin_amdgcn_s_waitcnt(0x0F70); break;  // vmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {  // s_waitcnt vmcnt(N) only (gfx9 encoding)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() { __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8)); }
+// f(integral_constant<int, I>) for I = A .. B - 1, each a separate instantiation
+template <int A, int B, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    static_for<A + 1, B>(f);
   }
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {  // byte address inside LDS of a __shared__ pointer
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-template <int D>
-__global__ void __launch_bounds__(WIDE_MAX_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) k_decode_wide(DecodeArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];
-  constexpr int BB = wide_block_bytes<D>();       // bytes of a block in the ring: K page 0, K page 1, V page 0, V page 1
-  constexpr int PB = PAGE * D * 2;                // bytes of one page of one kv head in a pool
-  constexpr int LOADS = BB / 1024;                // wave-level loads per block
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+// One shared item.  pages: the np pages of the slice, ntok: the tokens they hold; qrow: this lane's query row.
+// On return (O, m, l) hold the un-normalised partial of the units this wave took (l of this lane's half of the keys only).
+// HALVES 2: units of key half `sub` of every tile.  HALVES 1: all units; parts 2: key half `sub` of every
+// tile, parts 4: key half sub % 2 of every second tile from sub / 2 on.
+template <int D, int HALVES, typename A>
+__device__ __forceinline__ void wide_item(const A& a, unsigned char* smem, const int32_t* pages, int np, int ntok, int hk,
+                                          const uint16_t* qrow, int w, int lane, int sub, int parts, bool active, f32x16* O,
+                                          float& m, float& l) {
+  constexpr int PB = PAGE * D * 2, TB = WIDE_TILE_PAGES * PB;  // bytes of a page, a tile of one pool
+  constexpr int KS = D / 16, DB = D / 32, NS = KS + 2 * DB;    // slots of a unit
+  constexpr int IP = PB / 1024 / 2;                            // 1 KiB pieces of a page that a wave fetches
+  constexpr int LPG = 2 * IP;                                  // a wave's loads per group
+  constexpr int LAG = HALVES;                                  // V is read so many tiles behind K
+  constexpr int PF = 3, OPR = 4;                               // operand reads in flight ahead, their registers
   const int L = lane & 31, H = lane >> 5;
-  // The first wide_shared workgroups take the shared items; the ones after them take the own
-  // pages of one (branch, kv head, split) each, as a single row block whose waves (six at most,
-  // the others leave at once) take the key blocks in turn: they follow the shared items in the
-  // same launch and fill the compute units as those run out.
-  const bool own = (int)blockIdx.x >= a.wide_shared;
-#ifdef DAGATTN_ABL_NOOWN  // (development: timing of the shared items alone; results are wrong)
-  if (own) return;
-#endif
-#ifdef DAGATTN_ABL_NOSHARED
-  if (!own) return;
-#endif
-  int nw, nsub, rb, sub, split, hk, branch0, nrows, len, chunk;
-  const int32_t* pages;
-  float *po, *pml;
-  if (!own) {
-    nw = blockDim.x >> 6;
-    nsub = nw / a.rb_max; rb = w % a.rb_max; sub = w / a.rb_max;
-    int x = blockIdx.x;
-    split = x % a.splits_a; x /= a.splits_a;
-    hk = x % a.hkv;
-    const int g = x / a.hkv;
-    branch0 = a.group_branch_off[g];
-    nrows = (a.group_branch_off[g + 1] - branch0) * a.G;
-    pages = a.shared_pages + a.shared_page_off[g];
-    len = a.shared_len[g];
-    chunk = a.chunk_a;
-    const size_t item = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a + split;
-    po = a.part_o_a + (item * 32 + L) * D;
-    pml = a.part_ml_a + (item * 32 + L) * 2;
-  } else {
-    nw = min((int)(blockDim.x >> 6), WIDE_OWN_WAVES);
-    if (w >= nw) return;
-    nsub = nw; rb = 0; sub = w;
-    int x = (int)blockIdx.x - a.wide_shared;
-    const size_t item = (size_t)x;  // the order of k_decode's own items: (branch, kv head, split)
-    split = x % a.splits_b; x /= a.splits_b;
-    hk = x % a.hkv;
-    branch0 = x / a.hkv;
-    nrows = a.G;
-    pages = a.branch_pages + a.branch_page_off[branch0];
-    len = a.branch_len[branch0];
-    chunk = a.chunk_b;
-    po = a.part_o_b + (item * a.G + L) * D;
-    pml = a.part_ml_b + (item * a.G + L) * 2;
-  }
-  const int npages = (len + PAGE - 1) / PAGE;
-  const int p0 = split * chunk, p1 = min(p0 + chunk, npages);
-  const int row = 32 * rb + L;
-  const bool row_ok = row < nrows;
-  const int rbm = own ? 1 : a.rb_max;  // row blocks of the workgroup
-  if (p0 >= p1) {  // empty slice (the same for every wave of the workgroup): neutral partials
-    if (row_ok && H == 0 && sub == 0) {
-      pml[0] = -1e30f;
-      pml[1] = 0.f;
+  unsigned char *const Kring = smem, *const Vring = smem + WIDE_RING * TB;
+
+  const int pg_a = pages[min(lane, np - 1)], pg_b = pages[min(lane + 64, np - 1)];
+  bf16x8 qf[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) qf[s] = *(const bf16x8*)(qrow + 8 * H + 16 * s);
+  // (arrived: a wait for them further down would also wait for the tiles in flight)
+  asm volatile("" ::"v"(pg_a), "v"(pg_b));
+#pragma unroll
+  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
+
+  // Group g of the stream: K tile g and V tile g - LAG, in slots g % RING and (g - LAG) % RING of their rings.  Wave w
+  // fetches the pieces IP (w % 2) .. of page w / 2 of either tile; what lies outside the slice re-reads a tile
+  // of it (never used).  A V piece (32 dimensions x 16 keys) is fetched so that the 16 lanes which read an operand together
+  // find it in 256 consecutive bytes: LDS position u of it holds dimension 16 (u / 32) + u % 16, key half (u / 16) % 2.
+  const int nt = (np + WIDE_TILE_PAGES - 1) / WIDE_TILE_PAGES, ng = nt + LAG;
+  const int F = ntok / (WIDE_TILE_PAGES * PAGE * HALVES) * HALVES;  // tiles in the pipeline
+  const uint32_t vsrc = (2 * (16 * (lane / 32) + lane % 16) + (lane / 16) % 2) * 16;
+  const unsigned char *p_k = nullptr, *p_v = nullptr;
+  unsigned char *p_kl = nullptr, *p_vl = nullptr;
+  auto group_setup = [&](int g) __attribute__((always_inline)) {
+    auto page = [&](int tile) __attribute__((always_inline)) {
+      const int i = min(WIDE_TILE_PAGES * min(max(tile, 0), nt - 1) + w / 2, np - 1);
+      const int id = __builtin_amdgcn_readlane(i < 64 ? pg_a : pg_b, i & 63);
+      return ((size_t)id * a.hkv + hk) * (size_t)PB + (w % 2) * IP * 1024;
+    };
+    const uint32_t at = (w / 2) * PB + (w % 2) * IP * 1024;
+    p_k = (const unsigned char*)a.k_pool + page(g);
+    p_v = (const unsigned char*)a.v_pool + page(g - LAG);
+    p_kl = Kring + (g % WIDE_RING) * TB + at;
+    p_vl = Vring + ((g + WIDE_RING - LAG) % WIDE_RING) * TB + at;
+  };
+  auto group_load = [&](auto xc) __attribute__((always_inline)) {
+    constexpr int x = decltype(xc)::value;
+    const unsigned char* src = x < IP ? p_k + x * 1024 + lane * 16 : p_v + (x - IP) * 1024 + vsrc;
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)src,
+                                     (__attribute__((address_space(3))) void*)(x < IP ? p_kl + x * 1024 : p_vl + (x - IP) * 1024), 16, 0, 0);
+  };
+  auto issue = [&](int g) __attribute__((always_inline)) {
+    if (g >= ng) return;
+    group_setup(g);
+    static_for<0, LPG>(group_load);
+  };
+  // Group t is there for everybody, and everybody is past what group t - 1 was needed for: the slots of group t + 3 are free.
+  auto arrive = [&](int t) __attribute__((always_inline)) {
+    if (t + 3 <= ng) wait_vmcnt<2 * LPG>();
+    else if (t + 2 <= ng) wait_vmcnt<LPG>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  for (int g = 0; g < 3; ++g) issue(g);
+
+  if (!active) {  // (no rows for this wave: its share of the loads)
+    for (int t = 0; t < ng; ++t) {
+      arrive(t);
+      issue(t + 3);
     }
     return;
   }
-
-  // The query operands of the row block live in LDS behind the ring (operand s of lane i at
-  // (s 64 + i) 16 bytes), written by the block's first wave and read again for every key block:
-  // with them in registers three waves would not fit on a SIMD.
-  const uint32_t qbase = WIDE_RING * BB + rb * (D / 16) * 1024;
-  if (sub == 0) {
-    const int rr = row_ok ? row : 0;
-    const int br = branch0 + rr / a.G, head = hk * a.G + rr % a.G;
-    const uint16_t* qp = a.q + ((size_t)br * a.hq + head) * D + 8 * H;
-    bf16x8 qreg[D / 16];
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) qreg[s] = *(const bf16x8*)(qp + 16 * s);
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) *(bf16x8*)(ring + qbase + (s * 64 + lane) * 16) = qreg[s];
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // (written before the first barrier of the block loop, which every wave passes before it reads them)
-
-  // Loads of a block: piece j (0 .. LOADS - 1) = 1 KiB number j % (LOADS / 4) of {K page 0, K page 1,
-  // V page 0, V page 1}[j / (LOADS / 4)]; wave w issues the pieces w, w + nw, ...  Every wave
-  // issues the same number of loads per block (the last ones of some waves repeat a piece), so
-  // that the number of loads a wave may leave in flight is the same for all.
-  const int lpw = (LOADS + nw - 1) / nw;
-  const int np = p1 - p0, nblk = (np + 1) / 2;
-  int pgv = pages[p0 + min(lane, np - 1)];  // page ids, a 64-page window per register (as in k_decode)
-  asm volatile("" ::"v"(pgv));             // arrived (a wait for it inside the loops would drain the ring's loads)
-  int pgv_first = 0;                        // first page (relative) of the window in pgv
-  // A V piece (32 dimensions x 16 keys) is fetched so that the 16 lanes which read an operand
-  // together find it in 256 consecutive bytes: LDS position u of the piece holds dimension
-  // 16 (u / 32) + u % 16, key half (u / 16) % 2 (a row of the pool has 32 bytes: read as it lies,
-  // those lanes would hit every bank twice).
-  const uint32_t vsrc = (2 * (16 * (lane / 32) + lane % 16) + (lane / 16) % 2) * 16;
-  auto issue_block = [&](int b) {
-    const int pr = 2 * b;
-    if (pr - pgv_first >= 64) {  // next window (blocks are issued in order)
-      pgv_first += 64;
-      pgv = pages[p0 + min(pgv_first + lane, np - 1)];
-      asm volatile("" ::"v"(pgv));
-    }
-    const int pg0 = __builtin_amdgcn_readlane(pgv, (pr - pgv_first) & 63);
-    const int pg1 = __builtin_amdgcn_readlane(pgv, (min(pr + 1, np - 1) - pgv_first) & 63);
-    const size_t base0 = ((size_t)pg0 * a.hkv + hk) * (size_t)PB, base1 = ((size_t)pg1 * a.hkv + hk) * (size_t)PB;
-    unsigned char* slot = ring + (b % WIDE_RING) * BB;
-    for (int i = 0; i < lpw; ++i) {
-      const int j = min(w + i * nw, LOADS - 1);
-      const int part = j / (LOADS / 4), piece = j % (LOADS / 4);
-      const unsigned char* src = (const unsigned char*)(part < 2 ? a.k_pool : a.v_pool) + ((part & 1) ? base1 : base0) +
-                                 piece * 1024 + (part < 2 ? lane * 16 : vsrc);
-      __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)src,
-                                       (__attribute__((address_space(3))) void*)(slot + j * 1024), 16, 0, 0);
-    }
-  };
-
   const int kr = key_of_row(L);
-  // operand addresses inside a block: K[s] = chunk 2 s + H of key pi(L); V[page][db] = keys 8 H .. of
-  // dimension 32 db + L, which lies at position 32 (L / 16) + 16 H + L % 16 of its 1 KiB piece
-  const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)ring;
-  const uint32_t koff = (kr >> 4) * PB + H * (PAGE * 16) + (kr & 15) * 16;
-  const uint32_t voff = 2 * PB + (L / 16) * 512 + H * 256 + (L % 16) * 16;
+  const uint32_t half0 = HALVES == 2 || parts > 1 ? (sub & 1) * 2 * PB : 0;
+  const uint32_t koff = lds_addr(Kring) + half0 + (kr >> 4) * PB + H * 256 + (kr & 15) * 16;
+  const uint32_t voff = lds_addr(Vring) + half0 + (L / 16) * 512 + H * 256 + (L % 16) * 16;
+  auto Ka = [&](int t) __attribute__((always_inline)) { return koff + (uint32_t)(t % WIDE_RING) * TB; };
+  auto Va = [&](int t) __attribute__((always_inline)) { return voff + (uint32_t)(t % WIDE_RING) * TB; };
 
-  f32x16 O[D / 32];
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) O[db][r] = 0.f;
-  float m = -1e30f, l = 0.f;
-  bf16x8 qcur[D / 16];
-  auto qop = [&](int s) { return qcur[s]; };
+  m = -1e30f;
+  l = 0.f;
+  float msc = m * a.sc;
+  f32x16 SA, SB;
+  bf16x8 P0[2], P1[2];
 
-  // Operands come from LDS right before their product (inline assembly: for plain LDS reads the
-  // compiler would first wait for every global-to-LDS load in flight).  Nothing else happens
-  // between a read and its wait: the compiler does not know that the registers are not there yet
-  // (it might spill one in between).
-  bf16x8 pb0, pb1;
-  auto score_phase = [&](int b) __attribute__((always_inline)) {  // scores and probabilities of block b
-    const uint32_t sb = ring0 + (b % WIDE_RING) * BB;
-    bf16x8 kop[D / 16];
+  // The pieces of a unit by themselves (first and last units, the ragged tile): operand reads, wait, products.
+  auto scores = [&](uint32_t ka, auto half_c, f32x16& S) __attribute__((always_inline)) {
+    constexpr int HF = decltype(half_c)::value;
+    bf16x8 kop[KS];
+    const uint32_t ka_ = ka;
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s)
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(kop[s]) : "v"(sb + koff), "n"(s * 2 * PAGE * 16));
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s)
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(qcur[s]) : "v"(ring0 + qbase + lane * 16), "n"(s * 1024));
+    for (int s = 0; s < KS; ++s) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(kop[s]) : "v"(ka_), "n"(HF * 2 * PB + s * 512));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) asm volatile("" : "+v"(kop[s]), "+v"(qcur[s]));
-    block_scores<D>(kop, qop, O, m, l, a.sc, a.th, (p0 + 2 * b) * PAGE, len, len, H, pb0, pb1);
-  };
-  auto value_phase = [&](int b) __attribute__((always_inline)) {  // O += V^T P^T of block b
-    const uint32_t sb = ring0 + (b % WIDE_RING) * BB;
-    bf16x8 v0[D / 32], v1[D / 32];
+    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(kop[s]));
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v0[db]) : "v"(sb + voff), "n"(db * 32 * PAGE * 2));
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v1[db]) : "v"(sb + voff), "n"(PB + db * 32 * PAGE * 2));
+    for (int r = 0; r < 16; ++r) S[r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) S = mfma32(kop[s], qf[s], S);
+  };
+  auto values = [&](uint32_t va, auto half_c, const bf16x8* P, int key0) __attribute__((always_inline)) {  // key0 + 32 > ntok: ragged
+    constexpr int HF = decltype(half_c)::value;
+    bf16x8 v0[DB], v1[DB];
+    const uint32_t va_ = va;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v0[db]) : "v"(va_), "n"(HF * 2 * PB + db * 1024));
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v1[db]) : "v"(va_), "n"(HF * 2 * PB + PB + db * 1024));
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) asm volatile("" : "+v"(v0[db]), "+v"(v1[db]));
-    if ((p0 + 2 * b) * PAGE + 32 > len) clear_unused_values<D>(v0, v1, (p0 + 2 * b) * PAGE, len, H);
-    block_pv<D>(v0, v1, pb0, pb1, O);
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(v0[db]), "+v"(v1[db]));
+    if (key0 + 32 > ntok) clear_unused_values<D>(v0, v1, key0, ntok, H);
+    block_pv<D>(v0, v1, P[0], P[1], O);
   };
-  // The barrier of a round puts every wave at the same point, and waves that then all read LDS,
-  // all run their score MFMAs, all do the softmax arithmetic at the same time leave each of those
-  // units idle for most of the round.  When the ring holds three rounds, the waves with an odd
-  // `sub` therefore run half a block behind: after the barrier they first finish the block of the
-  // round before (its values), then take the scores of their new block, while the others do it
-  // the usual way round; a round's slots are then refilled a round later.
-  const bool skew = WIDE_RING >= 3 * nsub;
-  const bool late = skew && (sub & 1);
-  const int keep = skew ? 1 : 0;  // rounds before the current one whose blocks are still read
-  int issued = 0;
-  for (; issued < nblk && issued < WIDE_RING - keep * nsub; ++issued) issue_block(issued);
-  const int nrounds = (nblk + nsub - 1) / nsub;
-  auto round_sync = [&](int r) __attribute__((always_inline)) {
-    // this wave's loads of the round's blocks have landed when at most the loads of the blocks after them are in flight
-    wait_vmcnt_dyn(max(issued - min((r + 1) * nsub, nblk), 0) * lpw);
-    __builtin_amdgcn_s_barrier();  // the round's blocks are complete; every wave has finished the round before (late ones: its scores)
-    asm volatile("" ::: "memory");
-    // the next loads, into the slots that nobody reads any more
-    for (; issued < nblk && issued - (r - keep) * nsub < WIDE_RING; ++issued) issue_block(issued);
+  auto row_max = [&](const f32x16& S) __attribute__((always_inline)) {
+    float bm = S[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) bm = fmaxf(bm, S[r]);
+    return fmaxf(bm, __shfl_xor(bm, 32));
   };
-  // (every wave passes one barrier per round, the late ones between the two halves of a block)
-  round_sync(0);
-  for (int r = 0; r < nrounds; ++r) {
-    const int b = r * nsub + sub;
-    const bool mine = b < nblk;
-    if (mine) score_phase(b);
-    if (late && r + 1 < nrounds) round_sync(r + 1);
-    if (mine) value_phase(b);
-    if (!late && r + 1 < nrounds) round_sync(r + 1);
+  auto raise = [&](float bm) __attribute__((always_inline)) {  // the reference maximum to at least bm
+    const float m_new = fmaxf(m, bm), alpha = __builtin_amdgcn_exp2f((m - m_new) * a.sc);
+    m = m_new;
+    msc = m * a.sc;
+    l *= alpha;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) O[db][r] *= alpha;
+  };
+  auto probs = [&](const f32x16& S, bf16x8* P) __attribute__((always_inline)) {
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      const float pa = __builtin_amdgcn_exp2f(fmaf(S[e], a.sc, -msc)), pb = __builtin_amdgcn_exp2f(fmaf(S[e + 1], a.sc, -msc));
+      sum += pa + pb;
+      P[e >> 3][e & 7] = (__bf16)pa;
+      P[e >> 3][(e & 7) + 1] = (__bf16)pb;
+    }
+    return sum;
+  };
+  // Probabilities of S once more, with the reference raised, where they have left the range (what
+  // else is under way are scores, which know no reference).
+  auto settle = [&](const f32x16& S, bf16x8* P, float& sum) __attribute__((always_inline)) {
+    if (__builtin_amdgcn_ballot_w64(!(sum < 1024.f)) == 0) return;
+    raise(row_max(S));
+    sum = probs(S, P);
+  };
+  auto first_part = [&](int t, auto half_c, int key0, bf16x8* P) __attribute__((always_inline)) {  // scores and probabilities
+    f32x16 S;
+    scores(Ka(t), half_c, S);
+    if (key0 + 32 > ntok) {  // masked at the end of the list
+#pragma unroll
+      for (int r = 0; r < 16; ++r) S[r] = key0 + 16 * (r >> 3) + 8 * H + (r & 7) < ntok ? S[r] : -INFINITY;
+    }
+    const float bm = row_max(S);
+    if (__builtin_amdgcn_ballot_w64(bm > m + a.th) != 0) raise(bm);
+    l += probs(S, P);
+  };
+  auto general = [&](int t, auto half_c, int half) __attribute__((always_inline)) {  // a unit by itself
+    bf16x8 P[2];
+    const int key0 = t * WIDE_TILE_PAGES * PAGE + 32 * half;
+    first_part(t, half_c, key0, P);
+    values(Va(t), half_c, P, key0);
+  };
+  typedef std::integral_constant<int, 0> h0_t;
+  typedef std::integral_constant<int, 1> h1_t;
+
+  if constexpr (HALVES == 1) {
+    if (parts > 1) {  // the values of a unit a tile behind its scores: the two waves of a SIMD take turns with the matrix pipe
+      bool pending = false;
+      int key0 = 0;
+#pragma unroll 1
+      for (int t = 0; t < ng; ++t) {
+        arrive(t);
+        issue(t + 3);
+        if (pending) values(Va(t + WIDE_RING - 1), h0_t{}, P0, key0);
+        pending = t < nt && (parts == 2 || (t & 1) == sub >> 1);
+        key0 = t * WIDE_TILE_PAGES * PAGE + 32 * (sub & 1);
+        if (pending) first_part(t, h0_t{}, key0, P0);
+      }
+      return;
+    }
   }
 
-  // The waves of a row block put their accumulators together: waves 1 .. nsub - 1 leave theirs in
-  // LDS (the ring is free once every load has landed and every wave is past its last block), lane
-  // by lane, and wave 0 adds them in the order of `sub` with the usual change of reference maximum.
-  if (nsub > 1) {
-    wait_vmcnt_dyn(0);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    float* const slot = (float*)ring + ((size_t)((sub - 1) * rbm + rb) * 64 + lane) * (D / 2 + 4);
-    if (sub > 0) {
+  // A tile in the steady state: 2 / HALVES units.  Unit u takes scores into SA (u even) or SB.
+  auto steady = [&](int t, auto par_c) __attribute__((always_inline)) {
+    constexpr int PAR = decltype(par_c)::value, STEPS = 2 / HALVES, NT = STEPS * NS;
+    const uint32_t ka = Ka(t), va = Va(t + WIDE_RING - LAG);
+    bf16x8 opr[OPR];
+    float sum = 0.f, even = 0.f, last = 0.f;
+    auto fetch = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value, st = i / NS, j = i % NS;
+      bf16x8* const op = opr;
+      const uint32_t ka_ = ka, va_ = va;
+      if constexpr (i < NT) {
+        if constexpr (j % 2 == 0) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(op[i % OPR]) : "v"(ka_), "n"(st * 2 * PB + j / 2 * 512));
+        else
+          asm volatile("ds_read_b128 %0, %1 offset:%2"
+                       : "=v"(op[i % OPR])
+                       : "v"(va_), "n"(st * 2 * PB + j / 2 / DB * PB + j / 2 % DB * 1024));
+      }
+    };
+    static_for<0, PF>(fetch);
+    if (t + 3 < ng) group_setup(t + 3);  // (none left: the last group once more, the same bytes into the same places)
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NT>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value, st = i / NS, j = i % NS, x = j / 2;
+      fetch(std::integral_constant<int, i + PF>{});
+      wait_lgkmcnt<(i + PF < NT ? PF : NT - 1 - i)>();
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr bool odd = (PAR + st) % 2 != 0;
+      f32x16& Sn = odd ? SB : SA;
+      const f32x16& Sc = odd ? SA : SB;
+      bf16x8* const Pp = odd ? P1 : P0;
+      bf16x8* const Pc = odd ? P0 : P1;
+      if constexpr (j % 2 == 0) {
+        if constexpr (j == 0) Sn = mfma32(opr[i % OPR], qf[0], f32x16{});
+        else Sn = mfma32(opr[i % OPR], qf[x], Sn);
+      } else {
+        O[x % DB] = mfma32(opr[i % OPR], Pp[x / DB], O[x % DB]);
+      }
+      if constexpr (st == STEPS - 1 && j % (NS / LPG) == 1) {  // a load of the group three tiles ahead
+        group_load(std::integral_constant<int, j / (NS / LPG)>{});
+      }
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          *(f32x4*)(slot + 16 * db + 4 * r4) = f32x4{O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
-      slot[D / 2] = m;
-      slot[D / 2 + 1] = l;
+      for (int e = j * 16 / NS; e < (j + 1) * 16 / NS; ++e) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(Sc[e], a.sc, -msc));
+        sum += last;  // (the one before: its result is there, this one's is not yet)
+        last = p;
+        asm volatile("" : "+v"(sum));  // keep the running sum
+        if (e & 1) {
+          Pc[e >> 3][(e & 7) - 1] = (__bf16)even;
+          Pc[e >> 3][e & 7] = (__bf16)p;
+        } else {
+          even = p;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (j == NS - 1) {
+        sum += last;
+        settle(Sc, Pc, sum);
+        l += sum;
+        sum = last = 0.f;
+      }
+    });
+  };
+
+  int t = 0;
+  if (F > 0) {
+    // units 0 and 1
+    arrive(0);
+    scores(Ka(0), h0_t{}, SA);
+    raise(row_max(SA));
+    issue(3);
+    if constexpr (HALVES == 1) {
+      scores(Ka(0), h1_t{}, SB);
+    } else {
+      arrive(1);
+      scores(Ka(1), h0_t{}, SB);
+      issue(4);
     }
-    __syncthreads();
-    if (sub > 0) return;
-    for (int s2 = 1; s2 < nsub; ++s2) {
-      const float* const other = (const float*)ring + ((size_t)((s2 - 1) * rbm + rb) * 64 + lane) * (D / 2 + 4);
-      const float m2 = other[D / 2], l2 = other[D / 2 + 1];
-      const float m_new = fmaxf(m, m2);
+    l += probs(SA, P0);
+#pragma unroll 1
+    for (t = LAG; t < F; t += HALVES) {
+      arrive(t);
+      steady(t, h0_t{});
+      if constexpr (HALVES == 2) {
+        arrive(t + 1);
+        steady(t + 1, h1_t{});
+      }
+    }
+    // probabilities of the last unit, products of the last two
+    arrive(F);
+    issue(F + 3);
+    values(Va(F - LAG), h0_t{}, P0, 0);
+    float sum = probs(SB, P1);
+    settle(SB, P1, sum);
+    l += sum;
+    if constexpr (HALVES == 2) {
+      arrive(F + 1);
+      values(Va(F - 1), h0_t{}, P1, 0);
+    } else {
+      values(Va(F - 1), h1_t{}, P1, 0);
+    }
+    t = F + LAG;
+  }
+  // what is left, two tiles at most: one that ends inside, and in front of it the odd one of a wave that takes halves
+#pragma unroll 1
+  for (int g = t; g < ng; ++g) {
+    arrive(g);
+    issue(g + 3);
+  }
+#pragma unroll 1
+  for (t = F; t < nt; ++t) {
+    general(t, h0_t{}, HALVES == 2 ? sub : 0);
+    if constexpr (HALVES == 1) general(t, h1_t{}, 1);
+  }
+}
+
+template <int D>
+__global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int L = lane & 31, H = lane >> 5;
+  f32x16 O[D / 32];
+  float m, l;
+  // Workgroups in launch order: a.wide_first with own items, the shared items, the other own items.
+  const int first = (int)blockIdx.x - a.wide_first;
+  if (first >= 0 && first < a.wide_shared) {
+    const bool halves = a.rb_max <= WIDE_WAVES / 2;
+    int rb = w % a.rb_max, sub = w / a.rb_max, parts = halves ? 2 : 1;
+    if (a.rb_max == 5 || a.rb_max == 6) {
+      const int left = a.rb_max - 4;
+      rb = w < 4 ? w : 4 + (w - 4) % left;
+      sub = w < 4 ? 0 : (w - 4) / left;
+      parts = w < 4 ? 1 : 4 / left;
+    }
+    int x = first;
+    const int split = x % a.splits_a; x /= a.splits_a;
+    const int hk = x % a.hkv, g = x / a.hkv;
+    const int branch0 = a.group_branch_off[g], nrows = (a.group_branch_off[g + 1] - branch0) * a.G;
+    const int len = a.shared_len[g], npages = (len + PAGE - 1) / PAGE;
+    const int p0 = split * a.chunk_a, p1 = min(p0 + a.chunk_a, npages);
+    const int row = 32 * rb + L;
+    const bool row_ok = row < nrows, active = sub < parts && 32 * rb < nrows;
+    const size_t item = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a + split;
+    float* const pml = a.part_ml_a + (item * 32 + L) * 2;
+    if (p0 >= p1) {  // empty slice (the same for every wave of the workgroup): neutral partials
+      if (row_ok && H == 0 && sub == 0) {
+        pml[0] = -1e30f;
+        pml[1] = 0.f;
+      }
+      return;
+    }
+    const int rr = row_ok ? row : 0;
+    const uint16_t* qrow = a.q + (active ? ((size_t)(branch0 + rr / a.G) * a.hq + hk * a.G + rr % a.G) * D : 0);
+    const int32_t* pages = a.shared_pages + a.shared_page_off[g] + p0;
+    const int np = p1 - p0, ntok = min(len - p0 * PAGE, np * PAGE);
+    if (halves) wide_item<D, 2>(a, smem, pages, np, ntok, hk, qrow, w, lane, sub, parts, active, O, m, l);
+    else wide_item<D, 1>(a, smem, pages, np, ntok, hk, qrow, w, lane, sub, parts, active, O, m, l);
+    int db0 = 0, db1 = D / 32;
+    if (halves) {
+      // The two waves of a row block exchange halves of their accumulators through the rings (every load has landed, and
+      // every wave is past its last operand) and each puts one half of the output dimensions together.
+      constexpr int HD = D / 64;  // accumulator blocks of a half
+      float* const slots = (float*)smem;
+      auto slot = [&](int s2) { return slots + ((size_t)(rb * 2 + s2) * 64 + lane) * (16 * HD + 4); };
+      __syncthreads();
+      if (active) {
+        float* const mine = slot(sub);
+#pragma unroll
+        for (int db = 0; db < HD; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; r += 4) {
+            const f32x16& give = sub ? O[db] : O[HD + db];
+            *(f32x4*)(mine + 16 * db + r) = f32x4{give[r], give[r + 1], give[r + 2], give[r + 3]};
+          }
+        mine[16 * HD] = m;
+        mine[16 * HD + 1] = l;
+      }
+      __syncthreads();
+      if (!active) return;
+      const float* const other = slot(1 - sub);
+      const float m2 = other[16 * HD], l2 = other[16 * HD + 1], m_new = fmaxf(m, m2);
       const float a1 = __builtin_amdgcn_exp2f((m - m_new) * a.sc), a2 = __builtin_amdgcn_exp2f((m2 - m_new) * a.sc);
       m = m_new;
       l = l * a1 + l2 * a2;
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db)
+      for (int db = 0; db < HD; ++db)
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const f32x4 o2 = *(const f32x4*)(other + 16 * db + 4 * r4);
+        for (int r = 0; r < 16; r += 4) {
+          const f32x4 o2 = *(const f32x4*)(other + 16 * db + r);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) O[db][4 * r4 + e] = O[db][4 * r4 + e] * a1 + o2[e] * a2;
+          for (int e = 0; e < 4; ++e) {
+            const float own = sub ? O[HD + db][r + e] : O[db][r + e];
+            O[db][r + e] = own * a1 + o2[e] * a2;
+          }
         }
+      db0 = sub ? HD : 0;
+      db1 = HD;  // (O[0 ..] hold the wave's half now)
     }
-  }
-
-  const float l_tot = l + __shfl_xor(l, 32);
-  if (row_ok) {
+    if (a.rb_max == 5 || a.rb_max == 6) {
+      // The waves that share a row block leave their accumulators in the rings and each puts some output dimensions together.
+      constexpr int DB = D / 32;
+      float* const slots = (float*)smem;
+      auto slot = [&](int wave) { return slots + ((size_t)(wave - 4) * 64 + lane) * (16 * DB + 4); };
+      __syncthreads();
+      if (active && parts > 1) {
+        float* const mine = slot(w);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; r += 4) *(f32x4*)(mine + 16 * db + r) = f32x4{O[db][r], O[db][r + 1], O[db][r + 2], O[db][r + 3]};
+        mine[16 * DB] = m;
+        mine[16 * DB + 1] = l;
+      }
+      __syncthreads();
+      if (!active) return;
+      if (parts > 1) {
+        const int left = a.rb_max - 4, first_wave = rb;  // the waves rb, rb + left, ..
+        db0 = sub * DB / parts;
+        const int n = max((sub + 1) * DB / parts - db0, 0);
+        float mx = -1e30f, ls = 0.f;
+        for (int p = 0; p < parts; ++p) mx = fmaxf(mx, slot(first_wave + p * left)[16 * DB]);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) O[db][r] = 0.f;
+        for (int p = 0; p < parts; ++p) {
+          const float* const theirs = slot(first_wave + p * left);
+          const float wgt = __builtin_amdgcn_exp2f((theirs[16 * DB] - mx) * a.sc);
+          ls += theirs[16 * DB + 1] * wgt;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+            if (db < n)
+#pragma unroll
+              for (int r = 0; r < 16; r += 4) {
+                const f32x4 o = *(const f32x4*)(theirs + 16 * (db0 + db) + r);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) O[db][r + e] += o[e] * wgt;
+              }
+        }
+        m = mx;
+        l = ls;
+        db1 = n;
+      }
+    }
+    if (!active) return;
+    const float l_tot = l + __shfl_xor(l, 32);
+    if (!row_ok) return;
+    float* const po = a.part_o_a + (item * 32 + L) * D + 32 * db0 + 4 * H;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
+      if (db < db1)
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        f32x4 o = {O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
-        *(f32x4*)(po + 32 * db + 8 * r4 + 4 * H) = o;
-      }
-    if (H == 0) {
+        for (int r4 = 0; r4 < 4; ++r4)
+          *(f32x4*)(po + 32 * db + 8 * r4) = f32x4{O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
+    if (H == 0 && sub == 0) {
       pml[0] = m;
       pml[1] = l_tot;
+    }
+    return;
+  }
+
+  // Own pages of a (branch, kv head, slice) for every wide_own waves, in the order of k_decode's own items.
+  const int ow = a.wide_own, G = a.G, slot = w / ow, sub = w % ow;
+  const int item0 = (first < 0 ? (int)blockIdx.x : (int)blockIdx.x - a.wide_shared) * (WIDE_WAVES / ow), item = min(item0 + slot, a.items_b - 1);
+  int x = item;
+  const int split = x % a.splits_b; x /= a.splits_b;
+  const int hk = x % a.hkv, branch = x / a.hkv;
+  const int len = a.branch_len[branch], npages = (len + PAGE - 1) / PAGE;
+  const int p0 = split * a.chunk_b, p1 = min(p0 + a.chunk_b, npages);
+  const int per = ((max(p1 - p0, 0) + ow - 1) / ow + 1) & ~1;  // pages of a wave (a 32-key block never straddles two)
+  const int w0 = p0 + sub * per, w1 = min(w0 + per, p1);
+  bf16x8* const qs = (bf16x8*)smem;                                                   // [slot][operand][lane]
+  float* const po_lds = (float*)(smem + WIDE_WAVES / ow * (D / 16) * 1024);           // [wave][row][D + 4]
+  float* const ml_lds = po_lds + WIDE_WAVES * G * (D + 4);                            // [wave][row][2]
+  const bf16x8* const qf = qs + slot * (D / 16) * 64 + lane;
+  for (int s = sub; s < D / 16; s += ow)
+    qs[(slot * (D / 16) + s) * 64 + lane] = *(const bf16x8*)(a.q + ((size_t)branch * a.hq + hk * G + min(L, G - 1)) * D + 8 * H + 16 * s);
+  __syncthreads();
+  m = -1e30f;
+  float l_tot = 0.f;
+  if (w0 < w1) {
+    auto qop = [&](int s) { return qf[s * 64]; };
+    stream_slice<D>(a, a.branch_pages + a.branch_page_off[branch], w0, w1, len, len, len, hk, lane, qop, O, m, l);
+    l_tot = l + __shfl_xor(l, 32);
+    if (L < G) {
+      float* const po = po_lds + (w * G + L) * (D + 4) + 4 * H;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          *(f32x4*)(po + 32 * db + 8 * r4) = f32x4{O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
+    }
+  }
+  if (L < G && H == 0) {
+    ml_lds[(w * G + L) * 2] = m;
+    ml_lds[(w * G + L) * 2 + 1] = l_tot;
+  }
+  __syncthreads();
+  if (item0 + slot >= a.items_b) return;
+  const int used = p1 > p0 ? (p1 - p0 + per - 1) / per : 0;
+  for (int i = sub * 64 + lane; i < G * D / 4; i += 64 * ow) {
+    const int r = i / (D / 4), c = i % (D / 4) * 4;
+    float mx = -1e30f, ls = 0.f;
+    for (int p = 0; p < used; ++p) mx = fmaxf(mx, ml_lds[((slot * ow + p) * G + r) * 2]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < used; ++p) {
+      const int at = (slot * ow + p) * G + r;
+      const float wgt = __builtin_amdgcn_exp2f((ml_lds[at * 2] - mx) * a.sc);
+      const f32x4 o = *(const f32x4*)(po_lds + at * (D + 4) + c);
+      ls += ml_lds[at * 2 + 1] * wgt;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += o[e] * wgt;
+    }
+    *(f32x4*)(a.part_o_b + ((size_t)item * G + r) * D + c) = acc;
+    if (c == 0) {
+      a.part_ml_b[((size_t)item * G + r) * 2] = mx;
+      a.part_ml_b[((size_t)item * G + r) * 2 + 1] = ls;
     }
   }
 }
@@ -1153,7 +1420,8 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
   int ca = knobs.chunk_a ? knobs.chunk_a : 128, cb = knobs.chunk_b ? knobs.chunk_b : 64;
   ca += ca & 1;
   cb += cb & 1;
-  p->wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_WAVES;
+  p->wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_BLOCKS;
+  if (p->wide && ca > WIDE_MAX_PAGES) ca = WIDE_MAX_PAGES;
   if (!knobs.chunk_a) {
     if (p->wide)  // about one workgroup per compute unit
       while (ca > 8 && (int64_t)d->n_groups * hkv * dag_ceil_div(d->max_shared_pages, ca) < 256) ca /= 2;
@@ -1238,6 +1506,11 @@ int static_scratch(void** out) {
   return DAG_OK;
 }
 
+int compute_units() {  // of the current device; 0: it cannot be asked
+  int dev = 0, n = 0;
+  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+}
+
 // static_ws: the partials go to the library's own scratch array (ws / ws_bytes ignored).
 int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, const void* v_pool, void* out,
                 int32_t hq, int32_t hkv, int32_t head_dim, float softmax_scale, void* ws, size_t ws_bytes,
@@ -1302,17 +1575,29 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
     // shared items first (one workgroup streams a slice of the shared pages once for all rows),
     // the own items behind them.
     const unsigned shared_wgs = (unsigned)(d->n_groups * hkv * p.splits_a);
-    const unsigned threads = 64u * (unsigned)(p.rb_max * wide_nsub(p.rb_max, head_dim));
-    const int sm = wide_lds_bytes(p.rb_max, head_dim);
+    const unsigned threads = 64u * WIDE_WAVES;
+    // Waves to an own item: as many as leave a workgroup for every compute unit (512 items of 40 pages by
+    // themselves: eight waves each 30.5 us, four 27.9).
+    const int n_cu = compute_units();
+    if (n_cu < 1) return DAG_ERR_HIP;
+    a.wide_own = WIDE_WAVES;
+    while (a.wide_own > 1 && (int64_t)p.items_b * a.wide_own > (int64_t)WIDE_WAVES * n_cu &&
+           wide_own_bytes(a.G, head_dim, a.wide_own / 2) <= 160 * 1024)
+      a.wide_own /= 2;
+    const unsigned own_wgs = (unsigned)dag_ceil_div(p.items_b, WIDE_WAVES / a.wide_own);
+    // Half of the compute units start with own pages: an item keeps the memory idle for its first 6 us (lengths, page ids, pages), which all
+    // of them at once waste and half of them leave to the others (2 x 32 siblings over 32 K: 98 -> 89 us).
+    a.wide_first = (int)own_wgs < n_cu / 2 ? (int)own_wgs : n_cu / 2;
+    const int sm = wide_lds_bytes(a.G, head_dim, a.wide_own);
     a.wide_shared = (int)shared_wgs;
     if (head_dim == 128) {
       if (hipFuncSetAttribute((const void*)k_decode_wide<128>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
         return DAG_ERR_HIP;
-      hipLaunchKernelGGL(k_decode_wide<128>, dim3(shared_wgs + (unsigned)p.items_b), dim3(threads), sm, stream, a);
+      hipLaunchKernelGGL(k_decode_wide<128>, dim3(shared_wgs + own_wgs), dim3(threads), sm, stream, a);
     } else {
       if (hipFuncSetAttribute((const void*)k_decode_wide<64>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
         return DAG_ERR_HIP;
-      hipLaunchKernelGGL(k_decode_wide<64>, dim3(shared_wgs + (unsigned)p.items_b), dim3(threads), sm, stream, a);
+      hipLaunchKernelGGL(k_decode_wide<64>, dim3(shared_wgs + own_wgs), dim3(threads), sm, stream, a);
     }
     DAG_LAUNCH_CHECK();
     items = 0;
