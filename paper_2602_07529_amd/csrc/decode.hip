@@ -1129,14 +1129,17 @@ __global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a
 }
 
 // One wave per (branch, query head): log-sum-exp combination of its partials.  What it costs is the chain
-// of dependent loads (a binary search for the group, then the partials four at a time: 7.8 us for
-// 16 partials), so the group is found with one load per lane for every factor of 64 in their number, and the
-// outputs of the first 16 partials are on their way together with the maxima and sums: 4.7 us. 
+// of dependent loads, so the group is found with one load per lane for every factor of 64 in their number, and the
+// outputs of the first partials are on their way together with the maxima and sums.  A lane has four output
+// dimensions of every second partial (every fourth at head dimension 64).
+constexpr int MERGE_THREADS = 256;  // four rows to a workgroup
 template <int D>
-__global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
-  const int r = blockIdx.x / a.hq, head = blockIdx.x % a.hq;
+__global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
+  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (MERGE_THREADS / 64) + (threadIdx.x >> 6));
+  const int r = wid / a.hq, head = wid % a.hq;
+  if (r >= a.n_live) return;
   const int hk = head / a.G, j = head % a.G;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   int g = 0;  // the last group that starts at or before r, one of the n from g on
   for (int n = a.n_groups; n > 1;) {
     const int step = (n + 63) / 64, at = min(lane * step, n - 1);
@@ -1148,7 +1151,8 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   const int rb = row >> 5, rr = row & 31;
   const size_t ia0 = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a;
   const size_t ib0 = ((size_t)r * a.hkv + hk) * a.splits_b;
-  constexpr int PER = D / 64;  // output elements per lane
+  constexpr int ROW = D / 4, SETS = 64 / ROW;  // lanes to a partial, partials to a load
+  const int set = lane / ROW, c = lane % ROW * 4;
   const int np = a.splits_a + a.splits_b;
   // partial p of this (branch, head): shared split p, then own split p - splits_a
   auto ml_of = [&](int p) {
@@ -1157,21 +1161,16 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
   auto o_of = [&](int p) {
     return p < a.splits_a ? a.part_o_a + ((ia0 + p) * 32 + rr) * D : a.part_o_b + ((ib0 + (p - a.splits_a)) * a.G + j) * D;
   };
-  float acc[PER], lsum = 0.f;
-  auto merge = [&](auto batch_c) __attribute__((always_inline)) {  // BATCH partial outputs in flight
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float lsum = 0.f;
+  auto merge = [&](auto batch_c) __attribute__((always_inline)) {  // BATCH loads of SETS partial outputs in flight
     constexpr int BATCH = decltype(batch_c)::value;
-    float x[BATCH][PER];
+    f32x4 x[BATCH];
     auto fetch = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) {
-        const float* o = o_of(min(p0 + i, np - 1)) + lane * PER;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) x[i][e] = o[e];
-      }
+      for (int i = 0; i < BATCH; ++i) x[i] = *(const f32x4*)(o_of(min(p0 + i * SETS + set, np - 1)) + c);
     };
     fetch(0);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
     // The reference maximum first (64 partials at a time, one per lane, so that their loads are in
     // flight together), then the weighted sums in the fixed order of the partials: the weights of
     // a group of 64 come from the lanes, and the loads of the partial outputs do not depend on
@@ -1194,31 +1193,33 @@ __global__ void __launch_bounds__(64) k_decode_merge(DecodeArgs a) {
           wl = ls * wgt;
         }
       }
-      for (int b0 = p0; b0 < min(p0 + 64, np); b0 += BATCH) {
+      for (int b0 = p0; b0 < min(p0 + 64, np); b0 += BATCH * SETS) {
         if (b0 > 0) fetch(b0);
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {  // (the weight of a partial past the last one is zero)
-          const float wi = __shfl(wgt, b0 - p0 + i);
-          lsum += __shfl(wl, b0 - p0 + i);
+          const float wi = __shfl(wgt, b0 - p0 + i * SETS + set);
+          lsum += __shfl(wl, b0 - p0 + i * SETS + set);
 #pragma unroll
-          for (int e = 0; e < PER; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
+          for (int e = 0; e < 4; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
         }
       }
     }
   };
-  // (what is read beyond the last partial is that one again: 4096 groups of one branch with a few partials take
-  // 59 us with sixteen in flight, 51 so)
-  if (np <= 2) merge(std::integral_constant<int, 2>{});
-  else if (np <= 4) merge(std::integral_constant<int, 4>{});
-  else if (np <= 8) merge(std::integral_constant<int, 8>{});
+  // (what is read beyond the last partial is that one again)
+  if (np <= SETS) merge(std::integral_constant<int, 1>{});
+  else if (np <= 3 * SETS) merge(std::integral_constant<int, 3>{});
+  else if (np <= 9 * SETS) merge(std::integral_constant<int, 9>{});
   else merge(std::integral_constant<int, 16>{});
-  const float inv = 1.f / lsum;
-  uint16_t* o = a.out + ((size_t)r * a.hq + head) * D + lane * PER;
-  if (PER == 2) {
-    *(uint32_t*)o = dag_pack_bf2(acc[0] * inv, acc[PER - 1] * inv);
-  } else {
-    o[0] = (uint16_t)dag_f2bf(acc[0] * inv);
+#pragma unroll
+  for (int off = ROW; off < 64; off <<= 1) {
+    lsum += __shfl_xor(lsum, off);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
   }
+  if (set != 0) return;
+  const float inv = 1.f / lsum;
+  uint16_t* o = a.out + ((size_t)r * a.hq + head) * D + c;
+  *(u32x2*)o = u32x2{dag_pack_bf2(acc[0] * inv, acc[1] * inv), dag_pack_bf2(acc[2] * inv, acc[3] * inv)};
 }
 
 // One block per live branch: rotate the new key at the branch's adaptive position and scatter
@@ -1567,7 +1568,7 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
   a.sc = softmax_scale * 1.4426950408889634f;
   a.th = 8.f / a.sc;
   hipStream_t stream = (hipStream_t)stream_;
-  const unsigned nout = (unsigned)(d->n_live * hq);
+  const unsigned nout = (unsigned)dag_ceil_div((int64_t)d->n_live * hq, MERGE_THREADS / 64);
   a.item_base = 0;
   unsigned items = (unsigned)(p.items_a + p.items_b);
   if (p.wide && p.items_a > 0) {
@@ -1607,8 +1608,8 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
     else hipLaunchKernelGGL(k_decode<64>, dim3(items), dim3(64), 0, stream, a);
     DAG_LAUNCH_CHECK();
   }
-  if (head_dim == 128) hipLaunchKernelGGL(k_decode_merge<128>, dim3(nout), dim3(64), 0, stream, a);
-  else hipLaunchKernelGGL(k_decode_merge<64>, dim3(nout), dim3(64), 0, stream, a);
+  if (head_dim == 128) hipLaunchKernelGGL(k_decode_merge<128>, dim3(nout), dim3(MERGE_THREADS), 0, stream, a);
+  else hipLaunchKernelGGL(k_decode_merge<64>, dim3(nout), dim3(MERGE_THREADS), 0, stream, a);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
