@@ -385,12 +385,7 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
       rbs = min((nr * a.G + 31) / 32, a.rb_max);
     }
     const int cnt = nsp * rbs;
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
-    }
+    const int incl = dag_wave_scan(cnt);
     if (lane == 63) s_wave[w] = incl;
     __syncthreads();
     int start = s_carry + incl - cnt;
@@ -515,16 +510,10 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
         }
       }
     }
-    float cm = ms;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) cm = fmaxf(cm, __shfl_xor(cm, o));
-    const float mn = fmaxf(mx, cm);
+    const float mn = fmaxf(mx, dag_wave_max(ms));
     const float keep = __builtin_amdgcn_exp2f((mx - mn) * a.sc);
     const float wgt = ls > 0.f ? __builtin_amdgcn_exp2f((ms - mn) * a.sc) : 0.f;
-    float part = ls * wgt;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-    lsum = lsum * keep + part;
+    lsum = lsum * keep + dag_wave_sum(ls * wgt);
     mx = mn;
 #pragma unroll
     for (int t = 0; t < PER; ++t) acc[t] *= keep;
@@ -1181,8 +1170,7 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
       const float mv = p0 + lane < np ? ml_of(p0 + lane)[0] : -1e30f;
       mx = fmaxf(mx, mv);
     }
-#pragma unroll
-    for (int off = 32; off; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    mx = dag_wave_max(mx);
     for (int p0 = 0; p0 < np; p0 += 64) {
       float wl = 0.f, wgt = 0.f;
       if (p0 + lane < np) {
@@ -1228,34 +1216,45 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
 __global__ void __launch_bounds__(256) k_kv_append(const int32_t* branch_page_off, const int32_t* branch_pages,
                                                    const int32_t* branch_len, const int32_t* branch_pos,
                                                    const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
-                                                   uint16_t* v_pool, int hkv, int D, float theta) {
+                                                   uint16_t* v_pool, int hkv, int D, RopeTheta theta) {
   __shared__ float s_cos[64], s_sin[64];  // D / 2 <= 64 (the entry point admits head_dim 64 and 128 only)
-  const int r = blockIdx.x;
+  constexpr int KEEP = 2;                 // a thread's first pairs are on their way while the angles are computed
+  const int r = blockIdx.x, half = D / 2, n = hkv * half;
+  struct Pair {
+    uint16_t k0, k1, v0, v1;
+  };
+  auto load = [&](int x) __attribute__((always_inline)) {
+    const size_t src = ((size_t)r * hkv + x / half) * D + x % half;
+    return Pair{k_new[src], k_new[src + half], v_new[src], v_new[src + half]};
+  };
+  Pair keep[KEEP];
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) keep[i] = load(min((int)threadIdx.x + 256 * i, n - 1));
   const int idx = branch_len[r] - 1;
   if (idx < 0) return;
   const int page = branch_pages[branch_page_off[r] + idx / PAGE];
   const int slot = idx % PAGE;
-  const int half = D / 2;
   if ((int)threadIdx.x < half) {
     double sn, cs;
-    sincos((double)branch_pos[r] * pow((double)theta, -2.0 * (double)threadIdx.x / (double)D), &sn, &cs);
+    sincos((double)branch_pos[r] * dag_rope_freq(theta, threadIdx.x, D), &sn, &cs);
     s_cos[threadIdx.x] = (float)cs;
     s_sin[threadIdx.x] = (float)sn;
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < hkv * half; x += blockDim.x) {
-    const int h = x / half, mi = x % half;
-    const size_t src = ((size_t)r * hkv + h) * D;
-    const float lo = __uint_as_float((uint32_t)k_new[src + mi] << 16);
-    const float hi = __uint_as_float((uint32_t)k_new[src + mi + half] << 16);
-    const float c = s_cos[mi], s = s_sin[mi];  // (the products are rounded alike in k_kv_append_run)
+  auto store = [&](int x, const Pair& p) __attribute__((always_inline)) {
+    const int h = x / half, d0 = x % half, d1 = d0 + half;
+    const float lo = __uint_as_float((uint32_t)p.k0 << 16), hi = __uint_as_float((uint32_t)p.k1 << 16);
+    const float c = s_cos[d0], s = s_sin[d0];  // (the products are rounded alike in k_kv_append_run)
     const size_t pb = ((size_t)page * hkv + h) * (size_t)(D * PAGE);
-    const int d0 = mi, d1 = mi + half;
     k_pool[pb + (size_t)(d0 >> 3) * (PAGE * 8) + slot * 8 + (d0 & 7)] = (uint16_t)dag_f2bf(fmaf(lo, c, -(hi * s)));
     k_pool[pb + (size_t)(d1 >> 3) * (PAGE * 8) + slot * 8 + (d1 & 7)] = (uint16_t)dag_f2bf(fmaf(lo, s, hi * c));
-    v_pool[pb + (size_t)d0 * PAGE + slot] = v_new[src + d0];
-    v_pool[pb + (size_t)d1 * PAGE + slot] = v_new[src + d1];
-  }
+    v_pool[pb + (size_t)d0 * PAGE + slot] = p.v0;
+    v_pool[pb + (size_t)d1 * PAGE + slot] = p.v1;
+  };
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i)
+    if ((int)threadIdx.x + 256 * i < n) store(threadIdx.x + 256 * i, keep[i]);
+  for (int x = threadIdx.x + 256 * KEEP; x < n; x += 256) store(x, load(x));
 }
 
 // The same for many entries (the new tokens of prefilled nodes), kRunRows at a time.  Consecutive entries mostly are
@@ -1274,7 +1273,7 @@ constexpr int kAppendRunRows = 1024, kAppendRunBranches = 8192;
 __global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const int32_t* branch_page_off, const int32_t* branch_pages,
                                                        const int32_t* branch_len, const int32_t* branch_pos,
                                                        const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
-                                                       uint16_t* v_pool, int hkv, int D, float theta) {
+                                                       uint16_t* v_pool, int hkv, int D, RopeTheta theta) {
   __shared__ __attribute__((aligned(16))) float s_cos[kRunRows][64], s_sin[kRunRows][64];
   __shared__ int s_page[kRunRows], s_slot[kRunRows], s_whole[kRunRows], s_one[kRunRows], s_wholes, s_ones;  // slot -1: nothing to store
   const int r0 = blockIdx.x * kRunRows, tid = threadIdx.x, half = D / 2;
@@ -1311,7 +1310,7 @@ __global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const
     }
   }
   {
-    const double freq = pow((double)theta, -2.0 * (double)(tid % half) / (double)D);  // (half divides the block)
+    const double freq = dag_rope_freq(theta, tid % half, D);  // (half divides the block)
     for (int i = tid / half; i < kRunRows; i += kRunThreads / half) {
       double sn = 0., cs = 1.;
       if (r0 + i < n_live) sincos((double)branch_pos[r0 + i] * freq, &sn, &cs);
@@ -1472,11 +1471,11 @@ extern "C" int dag_kv_append_rope(const dag_decode_desc_t* d, const void* k_new,
     hipLaunchKernelGGL(k_kv_append_run, dim3((unsigned)runs, (unsigned)(split < hkv ? split : hkv)), dim3(kRunThreads), 0, (hipStream_t)stream_,
                        d->n_live, d->branch_page_off, d->branch_pages, d->branch_len, d->branch_pos,
                        (const uint16_t*)k_new, (const uint16_t*)v_new, (uint16_t*)k_pool, (uint16_t*)v_pool, hkv,
-                       head_dim, theta);
+                       head_dim, dag_rope_theta(theta));
   else
     hipLaunchKernelGGL(k_kv_append, dim3(d->n_live), dim3(256), 0, (hipStream_t)stream_, d->branch_page_off,
                      d->branch_pages, d->branch_len, d->branch_pos, (const uint16_t*)k_new, (const uint16_t*)v_new,
-                     (uint16_t*)k_pool, (uint16_t*)v_pool, hkv, head_dim, theta);
+                     (uint16_t*)k_pool, (uint16_t*)v_pool, hkv, head_dim, dag_rope_theta(theta));
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }

@@ -118,11 +118,6 @@ struct MetaOut {  // what the kernels write, see dag_meta_t
   int64_t* useful_pairs;
 };
 
-__device__ __forceinline__ int wave_sum(int x) {
-  for (int off = 32; off; off >>= 1) x += __shfl_xor(x, off);
-  return x;
-}
-
 // Whole block: per-sequence token counts and the prefix sums over sequences, a wave per sequence, then a scan
 // over 64 sequences at a time.
 __device__ __forceinline__ void seq_sums(int n_seqs, const int32_t* node_off, const int32_t* node_len, int tile_m, int tile_n,
@@ -133,7 +128,7 @@ __device__ __forceinline__ void seq_sums(int n_seqs, const int32_t* node_off, co
   for (int b = threadIdx.x >> 6; b < n_seqs; b += blockDim.x >> 6) {
     int t = 0;
     for (int v = node_off[b] + lane; v < node_off[b + 1]; v += 64) t += node_len[v];
-    t = wave_sum(t);
+    t = dag_wave_sum(t);
     if (lane == 0) cu_seqlens[b + 1] = t;  // turned into a prefix sum below
   }
   __syncthreads();
@@ -150,27 +145,21 @@ __device__ __forceinline__ void seq_sums(int n_seqs, const int32_t* node_off, co
     const int b = b0 + lane;
     int t = b < n_seqs ? cu_seqlens[b + 1] : 0;
     int qt = (t + tile_m - 1) / tile_m, kt = (t + tile_n - 1) / tile_n;
-    long long m = (long long)qt * kt;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int yt = __shfl_up(t, off), yq = __shfl_up(qt, off), yk = __shfl_up(kt, off);
-      const long long ym = __shfl_up(m, off);
-      if (lane >= off) {
-        t += yt;
-        qt += yq;
-        kt += yk;
-        m += ym;
-      }
-    }
+    int64_t m = (int64_t)qt * kt;
+    t = dag_wave_scan(t);
+    qt = dag_wave_scan(qt);
+    kt = dag_wave_scan(kt);
+    m = dag_wave_scan(m);
     if (b < n_seqs) {
       cu_seqlens[b + 1] = cu + t;
       qtile_start[b + 1] = qs + qt;
       ktile_start[b + 1] = ks + kt;
       block_map_off[b + 1] = mo + m;
     }
-    cu += __shfl(t, 63);
-    qs += __shfl(qt, 63);
-    ks += __shfl(kt, 63);
-    mo += __shfl(m, 63);
+    cu += __builtin_amdgcn_readlane(t, 63);
+    qs += __builtin_amdgcn_readlane(qt, 63);
+    ks += __builtin_amdgcn_readlane(kt, 63);
+    mo += dag_readlane(m, 63);
   }
 }
 
@@ -184,17 +173,13 @@ __device__ __forceinline__ int64_t node_walk(int n, int W, const int32_t* len, c
                                              int32_t* tok_start, int32_t* pos_start) {
   const int lane = threadIdx.x & 63;
   int run = 0;
-  long long pairs = 0;
+  int64_t pairs = 0;
   for (int c = 0; c < n; c += 64) {
     const int v = c + lane;
     const int x = v < n ? len[v] : 0;
-    int incl = x;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
-    }
+    const int incl = dag_wave_scan(x);
     if (v < n) tok_start[v] = run + incl - x;
-    run += __shfl(incl, 63);
+    run += __builtin_amdgcn_readlane(incl, 63);
     int best = -1;  // largest ancestor end position seen so far
     long long tokens = 0;
     for (int w = 0; w < c / 64; ++w) {
@@ -217,12 +202,11 @@ __device__ __forceinline__ int64_t node_walk(int n, int W, const int32_t* len, c
     if (v < n) {
       pos_start[v] = best + 1;
       pos_end[v] = best + x;
-      pairs += (long long)x * tokens + (long long)x * (x + 1) / 2;
+      pairs += (int64_t)x * tokens + (int64_t)x * (x + 1) / 2;
     }
     __threadfence_block();
   }
-  for (int off = 32; off; off >>= 1) pairs += __shfl_xor(pairs, off);
-  return pairs;
+  return dag_wave_sum(pairs);
 }
 
 // Visible pairs among the rows i0 .. i1 - 1 and keys j0 .. j1 - 1 of a sequence => SKIP / PARTIAL / FULL.
@@ -230,8 +214,20 @@ __device__ __forceinline__ int64_t node_walk(int n, int W, const int32_t* len, c
 __device__ __forceinline__ uint8_t tile_state(int T, int n, const int32_t* tok_start, const uint64_t* vis, int W, int i0,
                                               int i1, int j0, int j1, int sub = 0, int lanes = 1) {
   if (j0 > i1 - 1) return DAG_TILE_SKIP;  // entirely in the future of every row
-  const int u_lo = dag_find_segment(tok_start, n, i0), u_hi = dag_find_segment(tok_start, n, i1 - 1);
-  const int w_lo = dag_find_segment(tok_start, n, j0), w_hi = dag_find_segment(tok_start, n, j1 - 1);
+  // the nodes of the first and last row and key: four searches (dag_find_segment) with their loads in flight together
+  const int at[4] = {i0, i1 - 1, j0, j1 - 1};
+  int lo[4] = {0, 0, 0, 0}, hi[4] = {n, n, n, n};
+  for (int left = n; left > 1; left = (left + 1) / 2) {
+    int start[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) start[i] = tok_start[(lo[i] + hi[i]) >> 1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int mid = (lo[i] + hi[i]) >> 1;
+      if (start[i] <= at[i]) lo[i] = mid; else hi[i] = mid;
+    }
+  }
+  const int u_lo = lo[0], u_hi = lo[1], w_lo = lo[2], w_hi = lo[3];
   int allowed = 0;  // (at most 1024 x 1024)
   const int nw = w_hi - w_lo + 1;
   int u = u_lo, w = w_lo + sub;
@@ -254,7 +250,12 @@ __device__ __forceinline__ uint8_t tile_state(int T, int n, const int32_t* tok_s
     }
     w += lanes;
   }
-  for (int off = lanes / 2; off; off >>= 1) allowed += __shfl_xor(allowed, off);
+  if (lanes > 1) allowed = dag_wave_sum<1>(allowed);  // (in steps: the lanes of a group are neighbours)
+  if (lanes > 2) allowed += (int)dag_other_group<2>((uint32_t)allowed);
+  if (lanes > 4) allowed += (int)dag_other_group<4>((uint32_t)allowed);
+  if (lanes > 8) allowed += (int)dag_other_group<8>((uint32_t)allowed);
+  if (lanes > 16) allowed += (int)dag_other_group<16>((uint32_t)allowed);
+  if (lanes > 32) allowed += (int)dag_other_group<32>((uint32_t)allowed);
   return allowed == 0 ? DAG_TILE_SKIP : allowed == (i1 - i0) * (j1 - j0) ? DAG_TILE_FULL : DAG_TILE_PARTIAL;
 }
 
@@ -281,8 +282,8 @@ __device__ __forceinline__ void csr_row(int qt, int n_seqs, int total_qtiles, in
     oi += (x > mine) || (x == mine && j < qt);
     c0 += j < qt ? x : 0;
   }
-  oi = wave_sum(oi);
-  c0 = wave_sum(c0);
+  oi = dag_wave_sum(oi);
+  c0 = dag_wave_sum(c0);
   const int b = dag_find_segment(qtile_start, n_seqs, qt);
   const int T = cu_seqlens[b + 1] - cu_seqlens[b];
   const int KT = (T + tile_n - 1) / tile_n;
@@ -455,10 +456,10 @@ __global__ void __launch_bounds__(1024) k_meta_small(int n_seqs, NodeTable table
     o.node_tok_start[v] = s_tok[v];
     o.node_pos_start[v] = s_pos[v];
   }
-  int lanes = 1;  // of a tile: few tiles with many short nodes are shared by several lanes
-  while (lanes < 64 && 2 * lanes * total_tiles <= 1024) lanes *= 2;
-  const int sub = tid & (lanes - 1);
-  for (int idx = tid / lanes; idx < total_tiles; idx += 1024 / lanes) {
+  int shift = 0;  // 1 << shift lanes of a tile: few tiles with many short nodes are shared by several lanes
+  while (shift < 6 && total_tiles << (shift + 1) <= 1024) ++shift;
+  const int lanes = 1 << shift, sub = tid & (lanes - 1);
+  for (int idx = tid >> shift; idx < total_tiles; idx += 1024 >> shift) {
     const int b = dag_find_segment(s_mo, n_seqs, (int64_t)idx);
     const int T = s_cu[b + 1] - s_cu[b], KT = (T + tile_n - 1) / tile_n, loc = idx - (int)s_mo[b];
     const int a = loc / KT, kb = loc % KT, n0 = s_node[b];

@@ -276,10 +276,8 @@ __device__ __forceinline__ void wide_order(int qt, int total_qtiles, const int32
     oi += (o > mine) || (o == mine && j < qt);
     n += o >= 0;
   }
-  for (int off = 32; off; off >>= 1) {
-    oi += __shfl_xor(oi, off);
-    n += __shfl_xor(n, off);
-  }
+  oi = dag_wave_sum(oi);
+  n = dag_wave_sum(n);
   if (mine >= 0 && lane < 8) wide_desc[(int64_t)oi * 8 + lane] = wide_pre[(int64_t)qt * 8 + lane];
   if (qt == 0 && lane == 0) *wide_count = n;
 }
@@ -329,14 +327,10 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
     const int u = 64 * x + lane;
     const int first = u < n ? node_tok_start[n0 + u] : T, len = (u + 1 < n ? node_tok_start[n0 + u + 1] : T) - first;
     const int seen = (sees[x] >> lane) & 1 ? len : 0;
-    int incl = seen;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
-    }
+    const int incl = dag_wave_scan(seen);
     const int pos = before + incl - seen;
-    before += __shfl(incl, 63);
-    if (v / 64 == x) anc = __shfl(pos, v % 64);
+    before += __builtin_amdgcn_readlane(incl, 63);
+    if (v / 64 == x) anc = __builtin_amdgcn_readlane(pos, v % 64);
     const uint64_t starts = sees[x] & ~(sees[x] << 1 | (x > 0 ? sees[x > 0 ? x - 1 : 0] >> 63 : 0));  // a run starts where the node in front is not visible
     if (runs && (starts >> lane) & 1) out[n_runs + __popcll(starts & below)] = int2{pos, cu + first - pos};
     n_runs += __popcll(starts);

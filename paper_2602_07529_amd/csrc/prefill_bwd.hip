@@ -393,8 +393,7 @@ __global__ void __launch_bounds__(64) k_bwd_weights(BwdArgs a) {
   if (!(ktl & 1))
     for (int qt = lane; qt < QT; qt += 64)
       n += (bm[(int64_t)qt * KT + ktl] | (ktl + 1 < KT ? bm[(int64_t)qt * KT + ktl + 1] : 0)) != 0;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
+  n = dag_wave_sum(n);
   if (lane == 0) a.kt_weight[kt] = (ktl & 1) ? -1 : n;
 }
 // First visibility word of every token's node, so that the dQ kernels on the block map's tiles can fetch it for
@@ -413,8 +412,7 @@ __global__ void __launch_bounds__(64) k_bwd_order(BwdArgs a) {
     const int w = a.kt_weight[x];
     rank += w > mine || (w == mine && x < kt);
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) rank += __shfl_xor(rank, o);
+  rank = dag_wave_sum(rank);
   if (lane == 0) a.kt_order[rank] = kt;
   if (lane == 0 && a.dkv_stream) a.kt_again[kt] = 0;
 }

@@ -94,9 +94,30 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
   if (it < n_tiles) {
     int kt = __builtin_amdgcn_readfirstlane(a.col[c0 + it]);
     load_k(kt * TN);
+    int node_of_lane = a.tok_node[cu + min(kt * TN + lane, T - 1)];  // of the tile's keys, one per lane
     while (it < n_tiles) {
       const int full = __builtin_amdgcn_readfirstlane(a.flag[c0 + it]) == DAG_TILE_FULL;
       const int kt_next = it + STEP < n_tiles ? __builtin_amdgcn_readfirstlane(a.col[c0 + it + STEP]) : kt;
+      // Keys of the tile that this lane's row sees, bit j for key kt TN + j: the tile is a few runs of one node each, every one
+      // switched on as a whole (a test per element took 2 us a tile).
+      const bool masked = !full || kt * TN + TN > T;
+      uint64_t sees = ~0ull;
+      if (masked) {
+        auto first_bits = [](int n) { return n >= 64 ? ~0ull : n <= 0 ? 0ull : (1ull << n) - 1; };
+        if (!full) {
+          sees = 0;
+          const int prev = __shfl_up(node_of_lane, 1);
+          uint64_t starts = __builtin_amdgcn_ballot_w64(lane == 0 || node_of_lane != prev);
+          while (starts != 0) {
+            const int s0 = __builtin_ctzll(starts);
+            starts &= starts - 1;
+            const int n = __builtin_amdgcn_readlane(node_of_lane, s0);
+            const uint64_t word = a.W == 1 ? vis0 : vis_row[n >> 6];
+            if ((word >> (n & 63)) & 1) sees |= first_bits(starts != 0 ? __builtin_ctzll(starts) : 64) & ~first_bits(s0);
+          }
+        }
+        sees &= first_bits((full ? T : ic + 1) - kt * TN);
+      }
 #pragma unroll 1
       for (int u = 0; u < UPT; ++u) {
         const int j0 = kt * TN + u * UK;
@@ -111,21 +132,17 @@ __global__ void __launch_bounds__(256, 2) k_prefill_f32(PrefillArgs a) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) S[b] = mfma16(kf[b][t][c], q[t][c], S[b]);
         load_k(u + 1 < UPT ? j0 + UK : kt_next * TN);
+        if (u + 1 == UPT) node_of_lane = a.tok_node[cu + min(kt_next * TN + lane, T - 1)];
 #pragma unroll
         for (int b = 0; b < NB; ++b) S[b] *= a.scale;
-        if (!full || j0 + UK > T) {
+        if (masked) {
+          const uint32_t lo = (uint32_t)(sees >> (4 * g)), hi = (uint32_t)(sees >> (4 * g + 32));
 #pragma unroll
           for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int j = j0 + 16 * b + 4 * g + e;
-              bool ok = j < T;
-              if (!full) {
-                const int nj = a.tok_node[cu + min(j, T - 1)];
-                const uint64_t word = a.W == 1 ? vis0 : vis_row[nj >> 6];
-                ok = j <= i && ((word >> (nj & 63)) & 1);
-              }
-              S[b][e] = ok ? S[b][e] : -INFINITY;
+            for (int e = 0; e < 4; ++e) {  // this lane's key u UK + 16 b + 4 g + e of the tile
+              const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)((UK == 64 ? b > 1 : u > 0) ? hi : lo), 16 * (b & 1) + e, 1);
+              S[b][e] = __uint_as_float((__float_as_uint(S[b][e]) & keep) | (0xff800000u & ~keep));
             }
         }
         float mx = -INFINITY;
