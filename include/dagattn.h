@@ -199,7 +199,8 @@ size_t dag_prefill_workspace_bytes(const dag_meta_t* meta, int32_t hkv, int32_t 
  * dK = scale dS^T Q, only where the mask lets a pair through.  DAG_BF16 (MFMA, fp32
  * accumulation; gradients bf16) or DAG_F32 (plain fp32 arithmetic, the accuracy path; gradients
  * fp32), head_dim 128 or 64; all tensors DEVICE, 16-byte aligned; `ws` DEVICE scratch of
- * dag_prefill_bwd_workspace_bytes.  `meta` is the one dag_build_meta filled for the forward.  In
+ * dag_prefill_bwd_workspace_bytes (less is taken where it only leaves out room for the sums of dk and dv in
+ * pieces: the rows that see 128 keys are then one workgroup's).  `meta` is the one dag_build_meta filled for the forward.  In
  * bf16 dQ works on the forward's chunks or on the block map's tiles (launch order, tile descriptors,
  * FULL-first CSR), dK / dV on the rows that see 128 keys or on the block map's columns, by rules of
  * their own on node lengths and sizes.  `dk` is scratch during the call (the work lists of the chunks

@@ -20,7 +20,8 @@
 //   k_bwd64_dq, k_bwd64_dkv   the same two for head dimension 64
 //   k_nodes_dq2, k_nodes64_dq   dQ on the forward's query chunks instead of the block map's tiles
 //   k_nodes_dkv2, k_nodes64_dkv   dK/dV with the query rows that see the keys as one compact stream;
-//                 k_dkv_again behind them for keys that a hidden Inf or NaN has reached
+//                 k_dkv_finish behind them for streams in pieces and for keys that a
+//                 hidden Inf or NaN has reached
 //   k_bwd_dq, k_bwd_dkv   the first versions (tiles staged through registers, compiler-scheduled),
 //                 reached by a development switch only
 // Register layout of a 32x32 MFMA result C = A B:  lane (L, H) = (lane % 32, lane / 32) holds
@@ -68,7 +69,7 @@ struct BwdArgs {
   // the list of the tiles NQ c .. of a sequence lies where row NQ c of its dense block map does
   int dq_narrow;
   int total_qtiles;
-  int32_t* kt_again;  // [total key tiles] set where k_dkv_again has to look (in the place of tok_vis0, which dQ has read by then)
+  int32_t* kt_again;  // [total key tiles] set where k_dkv_finish has to look (in the place of tok_vis0, which dQ has read by then)
   int32_t* wide_col;    // [dense map] key tiles that one of the query tiles sees, those that all of them see in full first
   int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every NQ-th tile)
   int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups, sequence after sequence; last element: their number
@@ -79,6 +80,14 @@ struct BwdArgs {
   // dK / dV on streams of query rows
   bool dkv_stream;
   const int32_t* node_tok_start;
+  // streams cut into pieces (see k_bwd_order): {key tile, piece | pieces of the pair << 16} in launch order, their number, the
+  // sums of the pieces that share a pair; null: a workgroup takes the whole stream of its pair
+  int2* pieces;
+  int32_t* split_first;  // [max_split / 2] first piece of every split pair
+  int32_t* n_pieces;     // [2] pieces, split pairs
+  f32x4* part;    // [split piece][hkv][4 waves][dK, dV: 32 dims][4][64 lanes]
+  int max_split;  // room for this many pieces of split pairs (a KV head)
+  bool again;     // k_dkv_finish may read the inputs once more
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -404,17 +413,46 @@ __global__ void __launch_bounds__(256) k_bwd_tokvis(BwdArgs a, int total_tokens)
   const int b = dag_find_segment(a.cu_seqlens, a.n_seqs, t);
   a.tok_vis0[t] = a.node_vis[(int64_t)(a.node_start[b] + a.tok_node[t]) * a.W];
 }
+// Pairs that many rows see are cut into pieces, each a range of the stream and a workgroup of its own, summed by
+// k_dkv_finish: the root of a plan is seen by all of its rows, and its one workgroup ran on when all others were done
+// (4 x 75 nodes, five heads of dimension 64 on one KV head: 1020 of 1280 us, in pieces 127 + 15; 4 x 64 nodes, 16 / 8
+// heads: 513, in pieces 420).  A piece has at most the tiles that a workgroup gets where all are shared out evenly, and
+// at least DKV_MIN_STEPS iterations (a piece starts and ends in about five, its sums are 128 KiB at dimension 128).  w >
+// cap tiles make ceil(w / cap) < 2 w / cap pieces, so 2 W / cap slots hold those of all W tiles.  Split pairs are the
+// heaviest: their pieces come first in the launch order.  Forward and backward of 28 shapes with nodes of 50 to 500
+// tokens, 1 to 8 KV heads, against whole streams: 1.63 times as fast (0.99 to 4.7); pieces of a third, half and twice
+// the even share 1.60, 1.61, 1.53; of 16 iterations at least 1.60; none in pairs below 1.25 times the even share 1.59.
+constexpr int DKV_MIN_STEPS = 8;
+__device__ __forceinline__ int dkv_pieces(int w, int cap) { return w > cap ? (w + cap - 1) / cap : 1; }
 __global__ void __launch_bounds__(64) k_bwd_order(BwdArgs a) {
   const int kt = blockIdx.x, lane = threadIdx.x;
   const int mine = a.kt_weight[kt];
-  int rank = 0;
+  int rank = 0, sum = 0;
   for (int x = lane; x < a.total_ktiles; x += 64) {
     const int w = a.kt_weight[x];
     rank += w > mine || (w == mine && x < kt);
+    sum += max(w, 0);
   }
   rank = dag_wave_sum(rank);
   if (lane == 0) a.kt_order[rank] = kt;
   if (lane == 0 && a.dkv_stream) a.kt_again[kt] = 0;
+  if (!a.pieces) return;
+  const int total = dag_wave_sum(sum);
+  const int cap = max((DKV_MIN_STEPS + a.G - 1) / a.G, (int)((2 * (int64_t)total + a.max_split - 1) / a.max_split));
+  int first = 0, all = 0, pairs = 0;
+  for (int x = lane; x < a.total_ktiles; x += 64) {
+    const int w = a.kt_weight[x], n = w >= 0 ? dkv_pieces(w, cap) : 0;
+    all += n;
+    pairs += n > 1;
+    first += w > mine || (w == mine && x < kt) ? n : 0;
+  }
+  first = dag_wave_sum(first);
+  all = dag_wave_sum(all);
+  pairs = dag_wave_sum(pairs);
+  if (kt == 0 && lane == 0) a.n_pieces[0] = all, a.n_pieces[1] = pairs;
+  const int n = mine >= 0 ? dkv_pieces(mine, cap) : 0;
+  for (int p = lane; p < n; p += 64) a.pieces[first + p] = int2{kt, p | n << 16};
+  if (lane == 0 && n > 1) a.split_first[rank] = first;
 }
 
 template <int D>
@@ -883,7 +921,15 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   constexpr int KIND_WORDS = (MAX_QT_LDS + 63) / 64;
   __shared__ uint8_t sFlag[NODES ? 1 : MAX_QT_LDS];  // block-map column of the pair: flag of tile 0 | flag of tile 1 << 2
   __shared__ uint64_t sKind[2][NODES ? 1 : KIND_WORDS];
-  const int hk = blockIdx.x % a.hkv, kt = a.kt_order[blockIdx.x / a.hkv];  // heaviest pairs first
+  const int hk = blockIdx.x % a.hkv, slot = blockIdx.x / a.hkv;  // heaviest pairs first
+  int2 piece = {0, 1 << 16};
+  if (NODES && a.pieces) {
+    if (slot >= a.n_pieces[0]) return;
+    piece = a.pieces[slot];
+  } else {
+    piece.x = a.kt_order[slot];
+  }
+  const int kt = piece.x;
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int ktl = kt - a.ktile_start[b];
   if (ktl & 1) return;  // the workgroup of the even tile takes the pair
@@ -1261,9 +1307,11 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
 
   // ---- the walk of one kind of iteration: query tiles from the last one down (as do the other workgroups of the
   // KV head: they share the rows of the sequence's end in L2), the heads of the group inside
+  const int n_tiles = (n_pos + BM - 1) / BM, cuts = piece.y >> 16, cut = piece.y & 0xffff;  // (NODES)
+  const int tile0 = cut * (n_tiles / cuts) + min(cut, n_tiles % cuts), tile1 = tile0 + n_tiles / cuts + (cut < n_tiles % cuts);
   auto ring_loop = [&](auto msk_c) __attribute__((always_inline)) {
     constexpr int KIND = decltype(msk_c)::value ? 1 : 0;
-    const int n0 = KIND == 0 ? 0 : n_fast, n1 = KIND == 0 ? n_fast : (n_pos + BM - 1) / BM;  // (NODES)
+    const int n0 = KIND == 0 ? tile0 : max(tile0, n_fast), n1 = KIND == 0 ? min(tile1, n_fast) : tile1;  // (NODES)
     auto next_tile = [&](int qt) { return last_of_kind(KIND, qt); };
     auto advance = [&](int& qt, int& g) {
       if constexpr (NODES) {
@@ -1348,8 +1396,19 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   int key = 32 * w + L;
   asm volatile("" : "+v"(key));  // (recomputed here: its offsets need no registers across the loops)
   const int j_out = ktl * BN + key;
+  if (NODES && cuts > 1) {
+    f32x4* to = a.part + ((size_t)(slot * a.hkv + hk) * 4 + w) * (8 * DB * 64) + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        to[(4 * db + e4) * 64] = f32x4{dK[db][4 * e4], dK[db][4 * e4 + 1], dK[db][4 * e4 + 2], dK[db][4 * e4 + 3]};
+        to[(4 * DB + 4 * db + e4) * 64] = f32x4{dV[db][4 * e4], dV[db][4 * e4 + 1], dV[db][4 * e4 + 2], dV[db][4 * e4 + 3]};
+      }
+    return;
+  }
   dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < T, H, dK, dV);
-  if constexpr (NODES) {  // sums that are not numbers: k_dkv_again looks into it
+  if constexpr (NODES) {  // sums that are not numbers: k_dkv_finish looks into it
     float any = 0.f;  // (maximum, unlike fmaxf, hands a NaN on)
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -1369,10 +1428,10 @@ __global__ void __launch_bounds__(256, 2) k_nodes64_dkv(BwdArgs a) { dkv_ring_bo
 // left.  A kernel of its own, because the streams have no register left for it (a few of them spilled, in the
 // loop, wherever this went); with nothing to do it takes 4.5 us of 890 (4 x 64 random nodes, 16 / 8 heads of dimension 64).
 template <int D>
-__device__ void dkv_again(const BwdArgs& a, int kt, int hk) {
+__device__ void dkv_again(const BwdArgs& a, int kt, int hk, int w) {
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu, nbase = a.node_start[b];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, H = lane >> 5;
+  const int lane = threadIdx.x & 63, H = lane >> 5;
   const int j0 = (kt - a.ktile_start[b]) * BN + 32 * w, j = j0 + (lane & 31), jc = min(j, T - 1);
   if (j0 >= T) return;
   const bool key_ok = j < T;
@@ -1443,10 +1502,50 @@ __device__ void dkv_again(const BwdArgs& a, int kt, int hk) {
   }
   dkv_store<D>(a, koff, key_ok, H, dK, dV);
 }
+// The workgroups behind those of the key tiles add up the pieces of the split pairs, in the order of the stream (32 keys
+// each, dK and dV in four parts).
 template <int D>
-__global__ void __launch_bounds__(256) k_dkv_again(BwdArgs a) {
-  if (a.kt_again[blockIdx.x] == 0) return;
-  for (int hk = 0; hk < a.hkv; ++hk) dkv_again<D>(a, blockIdx.x, hk);
+__global__ void __launch_bounds__(256) k_dkv_finish(BwdArgs a) {
+  constexpr int NR = D / 16;  // sums of four dimensions that a lane adds up
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, L = lane & 31, H = lane >> 5;
+  int kt = blockIdx.x, hk = 0, hk_end = a.hkv, group = w;
+  if (kt < a.total_ktiles) {
+    if (!a.again || a.kt_again[kt] == 0) return;
+  } else {
+    const int x = blockIdx.x - a.total_ktiles, pair = (x >> 2) / a.hkv;
+    group = x & 3;
+    hk = (x >> 2) % a.hkv;
+    hk_end = hk + 1;
+    if (pair >= a.n_pieces[1]) return;
+    const int slot = a.split_first[pair];
+    const int2 piece = a.pieces[slot];
+    kt = piece.x;
+    const int n = piece.y >> 16;
+    const size_t step = (size_t)a.hkv * 4 * (D / 4 * 64);
+    const f32x4* from = a.part + ((size_t)(slot * a.hkv + hk) * 4 + group) * (D / 4 * 64) + w * NR * 64 + lane;
+    f32x4 sum[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) sum[r] = from[r * 64];
+#pragma unroll 4
+    for (int p = 1; p < n; ++p) {
+      from += step;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) sum[r] += from[r * 64];
+    }
+    const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
+    const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu, j = (kt - a.ktile_start[b]) * BN + 32 * group + L;
+    const float scale = w < 2 ? a.scale : 1.f;
+    uint16_t* to = (w < 2 ? a.dk : a.dv) + ((size_t)(cu + min(j, T - 1)) * a.hkv + hk) * D + (w & 1) * (D / 2) + 4 * H;
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      bad |= sum[r][0] != sum[r][0] || sum[r][1] != sum[r][1] || sum[r][2] != sum[r][2] || sum[r][3] != sum[r][3];
+      const u32x2 o = {dag_pack_bf2(sum[r][0] * scale, sum[r][1] * scale), dag_pack_bf2(sum[r][2] * scale, sum[r][3] * scale)};
+      if (j < T) *(u32x2*)(to + 8 * r) = o;
+    }
+    if (!__syncthreads_or(bad) || !a.again || w != 0) return;
+  }
+  for (; hk < hk_end; ++hk) dkv_again<D>(a, kt, hk, group);
 }
 
 // Tile lists of the dQ workgroups that take one query head on a group of NQ = four (head dimension
@@ -1954,17 +2053,18 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
     auto* const ring = D == 128 ? (a.dkv_stream ? k_nodes_dkv2 : k_bwd_dkv2) : a.dkv_stream ? k_nodes64_dkv : k_bwd64_dkv;
     if (hipFuncSetAttribute((const void*)ring, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    hipLaunchKernelGGL(ring, dim3((unsigned)(total_ktiles * a.hkv)), dim3(256), sm2, stream, a);
+    const long pairs = a.pieces ? (total_ktiles + a.n_seqs) / 2 : total_ktiles;
+    hipLaunchKernelGGL(ring, dim3((unsigned)((pairs + a.max_split) * a.hkv)), dim3(256), sm2, stream, a);
     // (it reads K, V, Q and dO once more: not where the gradients have been written over them)
     const size_t q_bytes = (size_t)a.total_rows * D * 2, k_bytes = q_bytes / a.G;
     auto apart = [&](const void* p, size_t p_bytes, const void* out) {
       return (const char*)p + p_bytes <= (const char*)out || (const char*)out + k_bytes <= (const char*)p;
     };
-    bool again = a.dkv_stream;
+    a.again = a.dkv_stream;
     for (const void* out : {(const void*)a.dk, (const void*)a.dv})
-      again = again && apart(a.q, q_bytes, out) && apart(a.dout, q_bytes, out) && apart(a.k, k_bytes, out) && apart(a.v, k_bytes, out);
-    if (again)
-      hipLaunchKernelGGL(k_dkv_again<D>, dim3((unsigned)total_ktiles), dim3(256), 0, stream, a);
+      a.again = a.again && apart(a.q, q_bytes, out) && apart(a.dout, q_bytes, out) && apart(a.k, k_bytes, out) && apart(a.v, k_bytes, out);
+    if (a.again || a.pieces)
+      hipLaunchKernelGGL(k_dkv_finish<D>, dim3((unsigned)(total_ktiles + (long)(a.max_split / 2) * a.hkv * 4)), dim3(256), 0, stream, a);
   } else {
     constexpr int sm = dkv_smem_bytes<D>();
     if (hipFuncSetAttribute((const void*)k_bwd_dkv<D>, hipFuncAttributeMaxDynamicSharedMemorySize, sm) != hipSuccess)
@@ -2166,6 +2266,28 @@ static size_t bwd_wide_list_bytes(const dag_meta_t* m, int32_t hq, int32_t hkv, 
          3 * dag_align_up((size_t)(m->sizes.total_qtiles + 1) * 4, 256);
 }
 
+// Forward and backward, block map : streams, nodes of 16 / 24 / 32 / 64 / 144 tokens on average: 32 / 8 heads of
+// dimension 128 1.00 / 1.02 / 1.02 / 1.06 / 1.08, 16 / 8 heads of dimension 64 1.00 / 1.05 / 1.06 / 1.07 / 1.07.
+static bool bwd_dkv_on_stream(const dag_meta_t* m, int32_t hq, int32_t head_dim) {
+  return !bwd_first_version() && m->node_tok_start && m->words_per_node <= 2 && m->sizes.total_tokens * hq * head_dim <= (int64_t)UINT32_MAX &&
+         m->sizes.total_tokens >= 16 * m->sizes.total_nodes;  // (row offsets are 32-bit)
+}
+
+// Pieces of split pairs a KV head (see k_bwd_order): what an even share of the tiles asks for on 256 compute units (two
+// workgroups on each at head dimension 64), or what all tiles of the block map can give.
+static int64_t bwd_max_split(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
+  if (hq % hkv != 0 || !bwd_dkv_on_stream(m, hq, head_dim) || m->sizes.total_tiles < 0) return 0;
+  const int64_t G = hq / hkv, most = (m->sizes.total_tiles + m->sizes.total_qtiles) / 2;  // tiles of all pairs
+  const int64_t even = ((head_dim == 128 ? 256 : 512) * 2 + hkv - 1) / hkv;
+  const int64_t cap = (DKV_MIN_STEPS + G - 1) / G;
+  return m->sizes.total_qtiles > cap ? std::min(even, 2 * most / cap) : 0;  // (a pair has as many tiles as its sequence at most)
+}
+static int64_t bwd_piece_slots(const dag_meta_t* m, int64_t max_split) { return (m->sizes.total_ktiles + m->n_seqs) / 2 + max_split; }
+static size_t bwd_piece_bytes(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
+  const int64_t n = bwd_max_split(m, hq, hkv, head_dim);
+  return n == 0 ? 0 : dag_align_up((size_t)bwd_piece_slots(m, n) * 8 + (size_t)n * 4 + 8, 256) + (size_t)n * hkv * (2 * BN) * head_dim * 2 * 4;
+}
+
 extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
   if (!m || hq < 1 || hkv < 1 || head_dim < 1 || m->sizes.total_tokens < 0 || m->sizes.total_qtiles < 0 ||
       m->sizes.total_ktiles < 0)
@@ -2174,7 +2296,7 @@ extern "C" size_t dag_prefill_bwd_workspace_bytes(const dag_meta_t* m, int32_t h
   size_t n = 2 * dag_align_up((size_t)m->sizes.total_tokens * hq * 4, 256) +
              2 * dag_align_up((size_t)m->sizes.total_ktiles * 4, 256) +
              dag_align_up((size_t)m->sizes.total_tokens * 8, 256) + 256;
-  return n + bwd_wide_list_bytes(m, hq, hkv, head_dim);
+  return n + bwd_wide_list_bytes(m, hq, hkv, head_dim) + bwd_piece_bytes(m, hq, hkv, head_dim);
 }
 
 // dQ on query chunks (see launch_d of the forward for where they pay).  Their tables are built in dK, which the
@@ -2216,7 +2338,11 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     return DAG_ERR_ALIGN;
   if (m->sizes.total_tokens * (int64_t)hq > INT32_MAX) return DAG_ERR_UNSUPPORTED;
   if (m->sizes.total_qtiles != m->sizes.total_ktiles) return DAG_ERR_BAD_LEN;  // (both tilings are 64 rows)
-  const size_t need = dag_prefill_bwd_workspace_bytes(m, hq, hkv, head_dim);
+  // (a workspace without room for the pieces is taken, too: every pair is then one workgroup's)
+  size_t need = dag_prefill_bwd_workspace_bytes(m, hq, hkv, head_dim);
+  const size_t piece_bytes = bwd_piece_bytes(m, hq, hkv, head_dim);
+  const bool in_pieces = piece_bytes > 0 && ws_bytes >= need;
+  need -= piece_bytes;
   // (the lists came later at head dimension 64: a workspace without them is taken, the heads left over then
   // run on one query tile, half of their workgroup idle)
   const bool lists = ws_bytes >= need;
@@ -2264,10 +2390,18 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.scale = softmax_scale; a.sc = softmax_scale * LOG2E;
   hipStream_t s = (hipStream_t)stream;
   a.node_tok_start = m->node_tok_start;
-  // Forward and backward, block map : streams, nodes of 16 / 24 / 32 / 64 / 144 tokens on average: 32 / 8 heads of
-  // dimension 128 1.00 / 1.02 / 1.02 / 1.06 / 1.08, 16 / 8 heads of dimension 64 1.00 / 1.05 / 1.06 / 1.07 / 1.07.
-  a.dkv_stream = !bwd_first_version() && m->node_tok_start && m->words_per_node <= 2 && a.total_rows * head_dim <= (long)UINT32_MAX &&
-                 m->sizes.total_tokens >= 16 * m->sizes.total_nodes;  // (row offsets are 32-bit)
+  a.dkv_stream = bwd_dkv_on_stream(m, hq, head_dim);
+  a.pieces = nullptr;
+  a.max_split = 0;
+  a.again = false;
+  if (in_pieces) {
+    a.max_split = (int)bwd_max_split(m, hq, hkv, head_dim);
+    char* const at = (char*)a.delta + need - 256;  // (the first 256 bytes of the need are for the alignment of ws)
+    a.pieces = (int2*)at;
+    a.n_pieces = (int32_t*)(a.pieces + bwd_piece_slots(m, a.max_split));
+    a.split_first = a.n_pieces + 2;
+    a.part = (f32x4*)(at + piece_bytes - (size_t)a.max_split * hkv * (2 * BN) * head_dim * 2 * 4);
+  }
   a.runs = nullptr;
   if (bwd_dq_on_chunks(m, a, head_dim)) {
     PrefillArgs p = {};
