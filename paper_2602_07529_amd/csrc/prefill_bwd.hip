@@ -4,15 +4,15 @@
 //     dQ = scale dS K,   dK = scale dS^T Q        (a KV head sums over its query heads).
 // P is recomputed from the forward's log-sum-exp; the block map of the forward skips the tiles
 // without a visible pair.  bf16 operands on the 32x32x16 MFMA, fp32 accumulation.  The kernels:
-//   k_bwd_delta   delta and -lse log2(e) per (token, query head)
-//   k_bwd_tokvis, k_bwd_weights, k_bwd_order   small tables: first visibility word per token; weight
-//                 and launch rank of the key-tile pairs (the dK/dV workgroups start heaviest first)
+//   k_bwd_delta_tables   delta and -lse log2(e) per (token, query head), and small tables: the query chunks
+//                 or the first visibility word of every token, weights of the key-tile pairs
+//   k_bwd_orders  launch orders of the chunks and of the dK/dV workgroups (heaviest pairs first)
 //   k_bwd_dq2     one workgroup per (64-row query tile, KV head, four of its query heads), eight
 //                 waves; the K / V tiles of the tile's row of the forward's FULL-first CSR stream
 //                 through an LDS ring and every tile is a fixed sequence of 48 slots (described at
 //                 the kernel).  The heads that the groups of four leave over (G not a multiple of
 //                 four) run as k_bwd_dq2<true>: one head on four consecutive query tiles per
-//                 workgroup, with tile lists from k_bwd_wide_rows
+//                 workgroup, with tile lists from bwd_wide_rows
 //   k_bwd_dkv2    one workgroup per (pair of 64-key tiles, KV head), four waves; the Q / dO tiles of
 //                 the query tiles that see the pair stream through an LDS ring, one (tile, query
 //                 head) = 64 slots (described at the kernel); nothing is accumulated through
@@ -35,6 +35,7 @@
 #include <stdlib.h>
 #include <type_traits>
 
+#include "chunk_tables.h"
 #include "common.h"
 #include "prefill_launch.h"
 
@@ -65,7 +66,7 @@ struct BwdArgs {
   long total_rows;  // T * hq
   float scale, sc;  // sc = scale * log2(e)
   // dQ: heads 0 .. dq_narrow - 1 of a KV head run NQ = four (head dimension 64: two) at a time on one
-  // query tile, the others one at a time on NQ query tiles, whose tile lists k_bwd_wide_rows writes:
+  // query tile, the others one at a time on NQ query tiles, whose tile lists bwd_wide_rows writes:
   // the list of the tiles NQ c .. of a sequence lies where row NQ c of its dense block map does
   int dq_narrow;
   int total_qtiles;
@@ -80,7 +81,7 @@ struct BwdArgs {
   // dK / dV on streams of query rows
   bool dkv_stream;
   const int32_t* node_tok_start;
-  // streams cut into pieces (see k_bwd_order): {key tile, piece | pieces of the pair << 16} in launch order, their number, the
+  // streams cut into pieces (see bwd_order): {key tile, piece | pieces of the pair << 16} in launch order, their number, the
   // sums of the pieces that share a pair; null: a workgroup takes the whole stream of its pair
   int2* pieces;
   int32_t* split_first;  // [max_split / 2] first piece of every split pair
@@ -139,27 +140,6 @@ __device__ __forceinline__ bf16x8 read_transposed(const uint16_t* tile, int lane
   typedef short v8i16 __attribute__((ext_vector_type(8)));
   const v8i16 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   return __builtin_bit_cast(bf16x8, x);
-}
-
-template <int D>
-__global__ void __launch_bounds__(256) k_bwd_delta(BwdArgs a) {
-  // D / 8 lanes per (token, query head) row, 16 bytes of out and of dout per lane
-  constexpr int LPR = D / 8, RPB = 256 / LPR;
-  const long row = (long)blockIdx.x * RPB + threadIdx.x / LPR;
-  const int part = threadIdx.x % LPR;
-  float s = 0.f;
-  if (row < a.total_rows) {
-    const u32x4 o = *(const u32x4*)(a.out + (size_t)row * D + part * 8);
-    const u32x4 g = *(const u32x4*)(a.dout + (size_t)row * D + part * 8);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s += dag_bf_lo(o[e]) * dag_bf_lo(g[e]) + dag_bf_hi(o[e]) * dag_bf_hi(g[e]);
-  }
-#pragma unroll
-  for (int o = LPR / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  if (part == 0 && row < a.total_rows) {
-    a.delta[row] = s;
-    a.nlse2[row] = -a.lse[row] * LOG2E;
-  }
 }
 
 // The per-wave state of a dQ workgroup (64-row query tile x KV head x up to 4 of its query heads;
@@ -386,13 +366,33 @@ __global__ void __launch_bounds__(128 * HG) k_bwd_dq(BwdArgs a) {
   dq_store<D>(a, me, (threadIdx.x & 63) >> 5, dQ);
 }
 
+template <int D>
+__device__ __forceinline__ void bwd_delta(const BwdArgs& a, int block) {
+  // D / 8 lanes per (token, query head) row, 16 bytes of out and of dout per lane
+  constexpr int LPR = D / 8, RPB = 256 / LPR;
+  const long row = (long)block * RPB + threadIdx.x / LPR;
+  const int part = threadIdx.x % LPR;
+  float s = 0.f;
+  if (row < a.total_rows) {
+    const u32x4 o = *(const u32x4*)(a.out + (size_t)row * D + part * 8);
+    const u32x4 g = *(const u32x4*)(a.dout + (size_t)row * D + part * 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s += dag_bf_lo(o[e]) * dag_bf_lo(g[e]) + dag_bf_hi(o[e]) * dag_bf_hi(g[e]);
+  }
+#pragma unroll
+  for (int o = LPR / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  if (part == 0 && row < a.total_rows) {
+    a.delta[row] = s;
+    a.nlse2[row] = -a.lse[row] * LOG2E;
+  }
+}
+
 // Launch order of the dK/dV workgroups: heaviest first.  A workgroup takes a pair of key tiles
 // (the even tile of a sequence and its successor); its weight is the number of query tiles that
 // see the pair (the prefix keys of a plan are seen by every later tile, the keys of a branch by a
 // few), odd tiles get -1 and sort last.  One wave per key tile, twice: weights, then ranks by
 // counting (ties by index), which is fine for the few thousand tiles of a batch.
-__global__ void __launch_bounds__(64) k_bwd_weights(BwdArgs a) {
-  const int kt = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void bwd_weight(const BwdArgs& a, int kt, int lane) {
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int ktl = kt - a.ktile_start[b];
   const int T = a.cu_seqlens[b + 1] - a.cu_seqlens[b];
@@ -407,12 +407,49 @@ __global__ void __launch_bounds__(64) k_bwd_weights(BwdArgs a) {
 }
 // First visibility word of every token's node, so that the dQ kernels on the block map's tiles can fetch it for
 // their rows without a load that depends on another load.
-__global__ void __launch_bounds__(256) k_bwd_tokvis(BwdArgs a, int total_tokens) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= total_tokens) return;
+__device__ __forceinline__ void bwd_token_vis(const BwdArgs& a, int t) {
   const int b = dag_find_segment(a.cu_seqlens, a.n_seqs, t);
   a.tok_vis0[t] = a.node_vis[(int64_t)(a.node_start[b] + a.tok_node[t]) * a.W];
 }
+
+// What the other kernels read, as far as it comes from the inputs alone: the chunks of dQ (tables of the sizes in `sizes`) or the
+// words of its rows on the block map's tiles, the weights of the key tiles, delta.  One launch, because none of
+// them waits for another and a launch of any of them costs 4.6 us, however little it does; the longest chains
+// first.  Five launches were 23 us of the 114 that 33 nodes of 80 tokens take forward and backward.
+struct PrepareBlocks {
+  int nodes, sizes, tokens, weights, delta;  // blocks of a size, sizes of chunks, and blocks of each of the rest
+};
+template <int D>
+__global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs p, int sizes, PrepareBlocks n) {
+  int x = blockIdx.x;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (x < n.nodes * n.sizes) {
+    const int i = nth_size(sizes, x / n.nodes), gv = x % n.nodes * 4 + w;
+    int32_t* const runs = x < n.nodes ? p.node_runs : nullptr;
+    if (gv >= p.total_nodes) return;
+    if (a.W == 1)
+      node_rows<1>(gv, p.n_seqs, (int)p.total_nodes, rows_of(i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+    else
+      node_rows<2>(gv, p.n_seqs, (int)p.total_nodes, rows_of(i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+    return;
+  }
+  x -= n.nodes * n.sizes;
+  if (x < n.tokens) {
+    if (a.runs) {
+      token_depths(p, (int64_t)x * 1024);
+    } else {
+      for (int64_t t = (int64_t)x * 1024 + threadIdx.x; t < min((int64_t)x * 1024 + 1024, a.total_rows / a.hq); t += 256) bwd_token_vis(a, (int)t);
+    }
+    return;
+  }
+  x -= n.tokens;
+  if (x < n.weights) {
+    if (4 * x + w < a.total_ktiles) bwd_weight(a, 4 * x + w, lane);
+    return;
+  }
+  bwd_delta<D>(a, x - n.weights);
+}
+
 // Pairs that many rows see are cut into pieces, each a range of the stream and a workgroup of its own, summed by
 // k_dkv_finish: the root of a plan is seen by all of its rows, and its one workgroup ran on when all others were done
 // (4 x 75 nodes, five heads of dimension 64 on one KV head: 1020 of 1280 us, in pieces 127 + 15; 4 x 64 nodes, 16 / 8
@@ -424,8 +461,7 @@ __global__ void __launch_bounds__(256) k_bwd_tokvis(BwdArgs a, int total_tokens)
 // the even share 1.60, 1.61, 1.53; of 16 iterations at least 1.60; none in pairs below 1.25 times the even share 1.59.
 constexpr int DKV_MIN_STEPS = 8;
 __device__ __forceinline__ int dkv_pieces(int w, int cap) { return w > cap ? (w + cap - 1) / cap : 1; }
-__global__ void __launch_bounds__(64) k_bwd_order(BwdArgs a) {
-  const int kt = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void bwd_order(const BwdArgs& a, int kt, int lane) {
   const int mine = a.kt_weight[kt];
   int rank = 0, sum = 0;
   for (int x = lane; x < a.total_ktiles; x += 64) {
@@ -434,9 +470,11 @@ __global__ void __launch_bounds__(64) k_bwd_order(BwdArgs a) {
     sum += max(w, 0);
   }
   rank = dag_wave_sum(rank);
-  if (lane == 0) a.kt_order[rank] = kt;
   if (lane == 0 && a.dkv_stream) a.kt_again[kt] = 0;
-  if (!a.pieces) return;
+  if (!a.pieces) {
+    if (lane == 0) a.kt_order[rank] = kt;
+    return;
+  }
   const int total = dag_wave_sum(sum);
   const int cap = max((DKV_MIN_STEPS + a.G - 1) / a.G, (int)((2 * (int64_t)total + a.max_split - 1) / a.max_split));
   int first = 0, all = 0, pairs = 0;
@@ -1554,8 +1592,7 @@ __global__ void __launch_bounds__(256) k_dkv_finish(BwdArgs a) {
 // NQ c + NQ - 1 holds every key tile that one of them sees; the key tiles that all of them see in full, with all their rows and keys inside the sequence, come
 // first (they run without tests), both parts ascending.
 template <int NQ>
-__global__ void __launch_bounds__(64) k_bwd_wide_rows(BwdArgs a) {
-  const int x = blockIdx.x, lane = threadIdx.x;
+__device__ void bwd_wide_rows(const BwdArgs& a, int x, int lane) {
   const int b = dag_find_segment(a.qtile_start, a.n_seqs, x);
   const int qt = x - a.qtile_start[b];
   if (qt % NQ) return;
@@ -1602,6 +1639,30 @@ __global__ void __launch_bounds__(64) k_bwd_wide_rows(BwdArgs a) {
     a.wide_list[before + qt / NQ] = x;
     if (qt == 0 && a.qtile_start[b + 1] == a.total_qtiles) a.wide_list[a.total_qtiles] = before + (QT + NQ - 1) / NQ;  // (the last sequence with tokens)
   }
+}
+
+// The tables that need those of the launch in front, a wave each: launch order of the chunks, of the dK / dV workgroups, and
+// (with it for the same reason) the lists above.
+struct OrderBlocks {
+  int chunks, sizes, wide, order;
+};
+template <int NQ>
+__global__ void __launch_bounds__(256) k_bwd_orders(BwdArgs a, PrefillArgs p, int sizes, OrderBlocks n) {
+  int x = blockIdx.x;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (x < n.order) {
+    if (4 * x + w < a.total_ktiles) bwd_order(a, 4 * x + w, lane);
+    return;
+  }
+  x -= n.order;
+  if (x < n.wide) {
+    if (4 * x + w < a.total_qtiles) bwd_wide_rows<NQ>(a, 4 * x + w, lane);
+    return;
+  }
+  x -= n.wide;
+  const int i = nth_size(sizes, x / n.chunks), slot = x % n.chunks * 4 + w, n_slots = slots_of(p, i);
+  const ChunkTables t = tables_of(p, i);
+  if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1657,7 +1718,7 @@ struct Dq {
 
 // WIDE: the same workgroup turned by ninety degrees -- one query head on four (two) consecutive query
 // tiles (wave pair p takes tile 4 c + p), for the heads that do not fill a group: the waves still
-// share every staged K / V tile.  The tile list is the one k_bwd_wide_rows wrote.
+// share every staged K / V tile.  The tile list is the one bwd_wide_rows wrote.
 // NODES: on query chunks instead of query tiles (the forward's tables, k_node_rows): the keys of a chunk stream
 // in the order of what its node sees, gathered row by row, so that only its last tiles take a mask, and
 // that mask is arithmetic on positions.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of
@@ -2009,13 +2070,18 @@ bool bwd_first_version() {
 }
 
 template <int D>
-int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStream_t stream) {
+int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_qtiles, long total_ktiles, hipStream_t stream) {
   BwdArgs a = args;
-  constexpr int RPB = 256 / (D / 8);  // rows per workgroup of k_bwd_delta
-  hipLaunchKernelGGL((k_bwd_delta<D>), dim3((unsigned)((a.total_rows + RPB - 1) / RPB)), dim3(256), 0, stream, a);
-  const int total_tokens = (int)(a.total_rows / a.hq);
-  if (!a.runs || bwd_first_version())
-    hipLaunchKernelGGL(k_bwd_tokvis, dim3((unsigned)((total_tokens + 255) / 256)), dim3(256), 0, stream, a, total_tokens);
+  constexpr int RPB = 256 / (D / 8), NQ = Dq<D>::NPAIR;  // rows per workgroup of bwd_delta
+  const int n_sizes = __builtin_popcount((unsigned)sizes), waves4 = (int)((total_ktiles + 3) / 4);
+  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 1023) / 1024), waves4, (int)((a.total_rows + RPB - 1) / RPB)};
+  hipLaunchKernelGGL((k_bwd_delta_tables<D>), dim3((unsigned)(pre.nodes * pre.sizes + pre.tokens + pre.weights + pre.delta)), dim3(256), 0, stream, a, p, sizes, pre);
+  // (without pieces the flags of k_dkv_finish lie where dQ on the block map's tiles reads the words of its rows)
+  const bool order_now = a.pieces || a.runs || !a.dkv_stream;
+  const OrderBlocks ord = {a.runs ? (int)((chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[__builtin_ctz(sizes)]) + 3) / 4) : 0, n_sizes,
+                           !a.runs && a.dq_narrow < a.G && !bwd_first_version() ? (int)((total_qtiles + 3) / 4) : 0, order_now ? waves4 : 0};
+  if (ord.chunks * ord.sizes + ord.wide + ord.order > 0)
+    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)(ord.chunks * ord.sizes + ord.wide + ord.order)), dim3(256), 0, stream, a, p, sizes, ord);
   DAG_LAUNCH_CHECK();
   int rc;
   if (!bwd_first_version()) {
@@ -2034,7 +2100,6 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
     if (wide > 0 && nodes) {
       hipLaunchKernelGGL(many_tiles, dim3((unsigned)a.chunk_slots[1], (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
     } else if (wide > 0) {
-      hipLaunchKernelGGL(k_bwd_wide_rows<NPAIR>, dim3((unsigned)total_qtiles), dim3(64), 0, stream, a);
       const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
       hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
     }
@@ -2045,9 +2110,10 @@ int launch_bwd(const BwdArgs& args, long total_qtiles, long total_ktiles, hipStr
                   : a.G == 2 ? launch_dq<D, 2>(a, total_qtiles, stream) : launch_dq<D, 1>(a, total_qtiles, stream);
   }
   if (rc != DAG_OK) return rc;
-  hipLaunchKernelGGL(k_bwd_weights, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
-  hipLaunchKernelGGL(k_bwd_order, dim3((unsigned)total_ktiles), dim3(64), 0, stream, a);
-  DAG_LAUNCH_CHECK();
+  if (!order_now) {
+    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)waves4), dim3(256), 0, stream, a, p, 0, OrderBlocks{0, 0, 0, waves4});
+    DAG_LAUNCH_CHECK();
+  }
   if (!bwd_first_version()) {
     constexpr int sm2 = Dkv<D>::NST * Dkv<D>::STAGEB;
     auto* const ring = D == 128 ? (a.dkv_stream ? k_nodes_dkv2 : k_bwd_dkv2) : a.dkv_stream ? k_nodes64_dkv : k_bwd64_dkv;
@@ -2273,7 +2339,7 @@ static bool bwd_dkv_on_stream(const dag_meta_t* m, int32_t hq, int32_t head_dim)
          m->sizes.total_tokens >= 16 * m->sizes.total_nodes;  // (row offsets are 32-bit)
 }
 
-// Pieces of split pairs a KV head (see k_bwd_order): what an even share of the tiles asks for on 256 compute units (two
+// Pieces of split pairs a KV head (see bwd_order): what an even share of the tiles asks for on 256 compute units (two
 // workgroups on each at head dimension 64), or what all tiles of the block map can give.
 static int64_t bwd_max_split(const dag_meta_t* m, int32_t hq, int32_t hkv, int32_t head_dim) {
   if (hq % hkv != 0 || !bwd_dkv_on_stream(m, hq, head_dim) || m->sizes.total_tiles < 0) return 0;
@@ -2395,6 +2461,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.max_split = 0;
   a.again = false;
   if (in_pieces) {
+    a.kt_again = a.kt_order;  // (the pieces have their own order)
     a.max_split = (int)bwd_max_split(m, hq, hkv, head_dim);
     char* const at = (char*)a.delta + need - 256;  // (the first 256 bytes of the need are for the alignment of ws)
     a.pieces = (int2*)at;
@@ -2403,8 +2470,9 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     a.part = (f32x4*)(at + piece_bytes - (size_t)a.max_split * hkv * (2 * BN) * head_dim * 2 * 4);
   }
   a.runs = nullptr;
+  PrefillArgs p = {};
+  int sizes = 0;
   if (bwd_dq_on_chunks(m, a, head_dim)) {
-    PrefillArgs p = {};
     p.n_seqs = m->n_seqs; p.W = m->words_per_node;
     p.total_tokens = m->sizes.total_tokens; p.total_nodes = m->sizes.total_nodes;
     p.cu_seqlens = m->cu_seqlens; p.node_start = m->node_start; p.tok_node = m->tok_node; p.node_vis = m->node_vis;
@@ -2412,8 +2480,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     p.sched = (int32_t*)dk;
     prefill_node_tables(p, p.sched + DAG_SCHED_INTS);
     const int wide = head_dim == 128 ? 2 : 1;  // chunks of NPAIR x 64 rows
-    const int rc = launch_chunk_tables(p, (a.dq_narrow > 0) | (a.dq_narrow < a.G) << wide, s);
-    if (rc != DAG_OK) return rc;
+    sizes = (a.dq_narrow > 0) | (a.dq_narrow < a.G) << wide;
     for (int i = 0; i < 2; ++i) {
       a.chunk[i] = p.chunk[i ? wide : 0];
       a.chunk_slots[i] = chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[i ? wide : 0]);
@@ -2421,6 +2488,6 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     a.runs = p.node_runs;
     a.tok_depth = p.tok_depth;
   }
-  return head_dim == 128 ? launch_bwd<128>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
-                         : launch_bwd<64>(a, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
+  return head_dim == 128 ? launch_bwd<128>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
+                         : launch_bwd<64>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
 }

@@ -95,8 +95,6 @@ struct PagedPrefillArgs {
 };
 int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream);
 
-int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream);  // bit i of sizes: chunks of DAG_CHUNK_ROWS[i] rows
-
 bool prefill_on_chunks(const PrefillArgs& a, int head_dim);  // bf16: query chunks or the block map's tiles
 int launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t stream);
 int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_t stream);  // V -> workspace copy
