@@ -159,7 +159,7 @@ extern "C" size_t dag_prefill_paged_workspace_bytes(const dag_paged_prefill_desc
   int64_t slots, nt_max;
   if (!paged_dims(d, &slots, &nt_max)) return 0;
   // counters, item count, per slot: tile count, two descriptors, its row of tile entries
-  return (size_t)(DAG_SCHED_INTS + 64 + slots * (17 + 8 * nt_max)) * 4 + 256;
+  return (size_t)(DAG_SCHED_INTS + 64 + slots * (17 + 8 * nt_max)) * 4 + 256 + paged_piece_bytes(slots, nt_max);
 }
 
 extern "C" int dag_attn_prefill_paged(const dag_paged_prefill_desc_t* d, const void* q, const void* k_pool,
@@ -178,7 +178,8 @@ extern "C" int dag_attn_prefill_paged(const dag_paged_prefill_desc_t* d, const v
       !d->own_page || !d->own_len)
     return DAG_ERR_NULL;
   if (!dag_aligned16(q) || !dag_aligned16(k_pool) || !dag_aligned16(v_pool) || !dag_aligned16(out)) return DAG_ERR_ALIGN;
-  if (!ws || ws_bytes < dag_prefill_paged_workspace_bytes(d)) return DAG_ERR_WORKSPACE;
+  const size_t need = dag_prefill_paged_workspace_bytes(d), piece_bytes = paged_piece_bytes(slots, nt_max);
+  if (!ws || ws_bytes < need - piece_bytes) return DAG_ERR_WORKSPACE;  // (without room for pieces every row of tiles is one item)
   PagedPrefillArgs pa = {};
   PrefillArgs& a = pa.a;
   a.q = q;
@@ -192,6 +193,10 @@ extern "C" int dag_attn_prefill_paged(const dag_paged_prefill_desc_t* d, const v
   a.wide_pre = a.wide_cnt + slots;
   a.wide_desc = a.wide_pre + 8 * slots;
   a.wide_col = a.wide_desc + 8 * slots;
+  if (piece_bytes > 0 && ws_bytes >= need) {
+    pa.piece_tables = (int32_t*)dag_align_up((size_t)(uintptr_t)(a.wide_col + 8 * nt_max * slots), 256);
+    a.part = (float*)(pa.piece_tables + 17 * PAGED_MAX_ITEMS);
+  }
   a.W = 1;
   a.hq = hq;
   a.hkv = hkv;
@@ -199,7 +204,7 @@ extern "C" int dag_attn_prefill_paged(const dag_paged_prefill_desc_t* d, const v
   a.heads = hq / hkv;
   a.scale = softmax_scale;
   pa.n_nodes = d->n_nodes;
-  pa.qt_max = (d->max_new + 63) / 64;
+  pa.max_new = d->max_new;
   pa.nt_max = (int)nt_max;
   pa.n_pages = n_pages;
   pa.q_off = d->q_off;

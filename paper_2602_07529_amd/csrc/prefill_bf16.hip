@@ -57,6 +57,7 @@
 // only raised when some row of the wave exceeds it by more than 2^8 (general step) or when a row's
 // probabilities of a half sum to 2^10 or more (steady state, found afterwards); probabilities may
 // exceed 1 by such a factor, which fp32 accumulation and the final division absorb exactly.
+#include <algorithm>
 #include <type_traits>
 
 #include "chunk_tables.h"
@@ -155,6 +156,9 @@ __device__ __forceinline__ bf16x8 join_halves(v4i16_t lo, v4i16_t hi) {
 // Workgroups of the attention kernel on a compute unit: at head dimension 64 the rings of two of four waves
 // fit into its LDS.
 constexpr int wgs_per_cu(int D, int waves) { return D == 64 && waves == 4 ? 2 : 1; }
+
+// Floats of a wave's partial result (paged prefill): 32 rows of D sums, their reference maxima, their row sums.
+__host__ __device__ constexpr int paged_part(int D) { return 32 * D + 64; }
 
 struct Item {  // wave-uniform description of a work item
   int cu, T, row0, c0, N, nfast, nstart, ktb, hk, hs;
@@ -319,8 +323,11 @@ __global__ void __launch_bounds__(1024) k_node_rows_small(PrefillArgs a, int siz
 // row of a query tile lists the tiles up to the last row's own position, those that need no mask
 // first (four full pages, all in front of the first row's position).  An entry is {four page
 // ids, their token counts (one byte each), tile index, 0, 0}; pages past the end of the context
-// repeat its first page with a count of zero, page ids are clamped to the pool.
-__global__ void __launch_bounds__(256) k_paged_rows(int n_nodes, int qt_max, int nt_max, int n_pages,
+// repeat its first page with a count of zero, page ids are clamped to the pool.  With `pieces` > 1 the row is cut
+// into up to that many items of at least PAGED_PIECE tiles where it has PAGED_CUT_TILES, each with a descriptor (the last word: its place
+// among the partial results + 1, and the number of pieces in the upper half; 0: the item is the whole row).
+constexpr int PAGED_PIECE = 4;
+__global__ void __launch_bounds__(256) k_paged_rows(int n_nodes, int qt_max, int rows, int nt_max, int pieces, int n_pages,
                                                     const int32_t* __restrict__ q_off,
                                                     const int32_t* __restrict__ ctx_page_off,
                                                     const int32_t* __restrict__ ctx_pages,
@@ -335,12 +342,12 @@ __global__ void __launch_bounds__(256) k_paged_rows(int n_nodes, int qt_max, int
   const int node = slot / qt_max, qt = slot % qt_max;
   const int n = q_off[node + 1] - q_off[node];
   const int p0 = ctx_page_off[node], np = ctx_page_off[node + 1] - p0;
-  if (qt * TM >= n || np < 1) {
-    if (lane == 0) cnt_out[slot] = -1;
+  if (qt * rows >= n || np < 1) {
+    if (lane < pieces) cnt_out[slot * pieces + lane] = -1;
     return;
   }
   const int nstart = own_page[node] * 16 + own_len[node] - n;  // context slot of the node's first new token
-  const int lim_first = nstart + qt * TM, lim_last = nstart + min(qt * TM + TM - 1, n - 1);
+  const int lim_first = nstart + qt * rows, lim_last = nstart + min(qt * rows + rows - 1, n - 1);
   const int NT = min(min(lim_last / TN + 1, (np + 3) / 4), nt_max);
   int32_t* const row = tiles + (int64_t)slot * nt_max * 8;
   int out = 0, nf = 0;
@@ -368,17 +375,19 @@ __global__ void __launch_bounds__(256) k_paged_rows(int n_nodes, int qt_max, int
     }
     if (pass == 0) nf = out;
   }
-  if (lane != 0) return;
-  cnt_out[slot] = out;
-  int32_t* d = pre + (int64_t)slot * 8;
+  if (lane >= pieces) return;
+  const int cuts = out < PAGED_CUT_TILES ? 1 : min(pieces, out / PAGED_PIECE), at = slot * pieces + lane;
+  const int t0 = lane * (out / cuts) + min(lane, out % cuts), t1 = t0 + out / cuts + (lane < out % cuts);
+  cnt_out[at] = lane < cuts ? t1 - t0 : -1;
+  int32_t* d = pre + (int64_t)at * 8;
   d[0] = q_off[node];
   d[1] = n;
-  d[2] = qt * TM;
-  d[3] = slot * nt_max;
-  d[4] = out;
-  d[5] = nf;
+  d[2] = qt * rows;
+  d[3] = slot * nt_max + t0;
+  d[4] = t1 - t0;
+  d[5] = min(max(nf - t0, 0), t1 - t0);
   d[6] = nstart;
-  d[7] = 0;
+  d[7] = cuts > 1 ? cuts << 16 | (at + 1) : 0;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1652,6 +1661,18 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // every tile load in flight); the piece belongs to this wave, so no barrier is involved.
     const int head = head_of(cur);
     const bool store = head_is_mine(cur);
+    if (PAGED && cur.ktb != 0) {  // a piece of a row of tiles: the sums as they are, for k_paged_merge
+      float* const to = a.part + (((size_t)((cur.ktb & 0xffff) - 1) * nhw + cur.hk * HS + cur.hs) * NW + w) * paged_part(D);
+      const float l_tot = l[0] + __shfl_xor(l[0], 32);
+      if (store) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4)
+            ((f32x4*)to)[(4 * db + r4) * 64 + lane] = f32x4{O[0][db][4 * r4], O[0][db][4 * r4 + 1], O[0][db][4 * r4 + 2], O[0][db][4 * r4 + 3]};
+        to[32 * D + lane] = H == 0 ? M[0] : l_tot;
+      }
+    } else
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       const float l_tot = l[r] + __shfl_xor(l[r], 32);
@@ -1764,6 +1785,66 @@ __global__ void __launch_bounds__(64 * HG * NRG, wgs_per_cu(D, HG * NRG)) k_pref
   prefill_body<D, HG, NRG, STREAM_NODES>(a);
 }
 
+// (heads of the paged prefill that do not fill items of four)
+template <int D, int HG, int NRG>
+__global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_pages(PrefillArgs a) {
+  prefill_body<D, HG, NRG, STREAM_PAGES>(a);
+}
+
+// Adds up the pieces of a row of tiles (paged prefill), in order: a wave per eight output dimensions of a wave of the
+// attention kernel.  `n_slots` rows of tiles, `pieces` descriptors each.  The partial results come from other XCDs, a
+// round trip of 2 us, so that everything of eight pieces is fetched at once: one wave for all dimensions, piece after
+// piece, took 16 us for 7 pieces and 43 us for 12 (dimension 128).
+template <int D>
+__global__ void __launch_bounds__(256) k_paged_merge(PrefillArgs a, int n_slots, int pieces, int HG) {
+  constexpr int NW = 8, PARTS = D / 16, AT_ONCE = 8;
+  const int HS = (a.heads + HG - 1) / HG, nhw = a.hkv * HS;
+  const int x = blockIdx.x * 4 + (threadIdx.x >> 6), part = x % PARTS, w = x / PARTS % NW, hw = x / (PARTS * NW) % nhw, slot = x / (PARTS * NW) / nhw;
+  if (slot >= n_slots || a.wide_cnt[slot * pieces] < 0) return;
+  const int32_t* const d = a.wide_pre + (size_t)slot * pieces * 8;
+  const int n = d[7] >> 16, hj = w % HG, lane = threadIdx.x & 63, L = lane & 31, H = lane >> 5;
+  if (n < 2 || hw % HS * HG + hj >= a.heads) return;
+  const size_t step = (size_t)nhw * NW * paged_part(D);
+  const float* const from = a.part + ((size_t)slot * pieces * nhw + hw) * NW * paged_part(D) + (size_t)w * paged_part(D);
+  float mx = -INFINITY, l = 0.f, O[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int p0 = 0; p0 < n; p0 += AT_ONCE) {
+    float m[AT_ONCE], s[AT_ONCE];
+    f32x4 o[AT_ONCE][2];
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i) {
+      const float* const p = from + min(p0 + i, n - 1) * step;
+      m[i] = p[32 * D + L];
+      s[i] = p[32 * D + 32 + L];
+      o[i][0] = ((const f32x4*)p)[(2 * part) * 64 + lane];
+      o[i][1] = ((const f32x4*)p)[(2 * part + 1) * 64 + lane];
+    }
+    float top = mx;
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i) top = p0 + i < n && s[i] > 0.f ? fmaxf(top, m[i]) : top;
+    const float keep = l == 0.f ? 0.f : __builtin_amdgcn_exp2f(mx - top);
+    mx = top;
+    l *= keep;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) O[e] *= keep;
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i) {
+      if (p0 + i >= n || s[i] == 0.f) continue;  // (a piece that the row does not see has the reference 0)
+      const float wgt = __builtin_amdgcn_exp2f(m[i] - mx);
+      l = fmaf(s[i], wgt, l);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) O[e] = fmaf(o[i][e >> 2][e & 3], wgt, O[e]);
+    }
+  }
+  const int row = d[2] + 32 * (w / HG) + L, head = hw / HS * (a.hq / a.hkv) + a.head0 + hw % HS * HG + hj;
+  if (row >= d[1]) return;
+  const size_t at = (size_t)(d[0] + row) * a.hq + head;
+  if (a.lse && H == 0 && part == 0) a.lse[at] = mx * 0.6931471805599453f + logf(l);
+  const float inv = 1.f / l;
+  uint16_t* const to = (uint16_t*)a.out + at * D + 16 * part + 4 * H;
+  *(u32x2*)to = u32x2{dag_pack_bf2(O[0] * inv, O[1] * inv), dag_pack_bf2(O[2] * inv, O[3] * inv)};
+  *(u32x2*)(to + 8) = u32x2{dag_pack_bf2(O[4] * inv, O[5] * inv), dag_pack_bf2(O[6] * inv, O[7] * inv)};
+}
+
 // How the launches divide a KV head's G query heads.
 //   four: heads in items of four heads x 64 rows;  two: a pair in an item of its own;
 //   one:  heads one at a time in items of 256 (on chunks at head dimension 64: 128) rows.
@@ -1815,6 +1896,7 @@ int launch_one(const PrefillArgs& a, long max_tiles, hipStream_t stream) {
   static_assert(PER_CU * sm <= 160 * 1024, "LDS of a compute unit");
   void (*kernel)(PrefillArgs);
   if constexpr (STREAM == STREAM_NODES) kernel = k_prefill_nodes<D, HG, NRG>;
+  else if constexpr (STREAM == STREAM_PAGES && HG != 4) kernel = k_prefill_pages<D, HG, NRG>;
   else kernel = k_prefill_bf16<D, HG, NRG, STREAM == STREAM_PAGES>;
   if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess) return DAG_ERR_HIP;
   const int n_cu = compute_units();
@@ -1918,23 +2000,55 @@ int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_
   return head_dim == 128 ? launch_prepare_v<128>(a, stream) : launch_prepare_v<64>(a, stream);
 }
 
-int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream) {
-  const int slots = pa.n_nodes * pa.qt_max;
-  const unsigned nblk = (unsigned)((slots + 3) / 4);
+// Rows of tiles that leave compute units idle are cut into pieces, so many that the items fill the device (3 nodes of 62
+// tokens against 3100, 8 / 2 heads: 83.5 -> 35 us with the append; 6 nodes of 57 against 3750, 16 / 4: 98 -> 49.5; 28
+// shapes of 20 to 700 new tokens 1.29 times as fast on average, those of less than 24 tiles, which stay whole, 1.00).  Items take four heads of a KV head on 64 rows, one padded where the heads
+// are no multiple of four; where there are more of them than compute units, two heads on 128 or one on 256
+// rows if that makes fewer items.
+template <int D>
+int launch_paged(const PagedPrefillArgs& pa, hipStream_t stream) {
   const PrefillArgs& a = pa.a;
-  hipLaunchKernelGGL(k_paged_rows, dim3(nblk), dim3(256), 0, stream, pa.n_nodes, pa.qt_max, pa.nt_max, pa.n_pages,
-                     pa.q_off, pa.ctx_page_off, pa.ctx_pages, pa.ctx_page_len, pa.own_page, pa.own_len, a.sched,
-                     a.wide_cnt, a.wide_pre, a.wide_col);
-  DAG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_wide_order, dim3(nblk), dim3(256), 0, stream, slots, a.wide_cnt, a.wide_pre, a.wide_desc,
-                     a.wide_count);
-  DAG_LAUNCH_CHECK();
+  const int64_t n_cu = compute_units();
+  if (n_cu < 1) return DAG_ERR_HIP;
+  auto tiles = [&](int hg) { return (pa.max_new + 256 / hg - 1) / (256 / hg); };   // of a node
+  auto heads = [&](int hg) { return (a.heads + hg - 1) / hg; };                    // items of a KV head
+  int hg = 4;
+  if ((int64_t)pa.n_nodes * tiles(4) * a.hkv * heads(4) > n_cu)
+    for (int x : {2, 1})
+      if (tiles(x) * heads(x) < tiles(hg) * heads(hg)) hg = x;
+  const int rows = 256 / hg, slots = pa.n_nodes * tiles(hg);
+  const int64_t items = (int64_t)slots * a.hkv * heads(hg);
   PrefillArgs b = a;
-  b.col = a.wide_col;
-  b.qtile_desc = a.wide_desc;
-  b.n_tiles_dev = a.wide_count;
-  // (query heads in items of four, the last item padded)
-  return head_dim == 128 ? launch_one<128, 4, 2, STREAM_PAGES>(b, slots, stream) : launch_one<64, 4, 2, STREAM_PAGES>(b, slots, stream);
+  int pieces = 1;
+  if (a.part) {
+    pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(n_cu, PAGED_MAX_ITEMS) / items, pa.nt_max / PAGED_PIECE));
+    pieces = std::min(pieces, PAGED_MAX_CUTS);
+  }
+  if (pieces > 1) {  // the descriptors are more than the workspace holds elsewhere
+    b.wide_cnt = pa.piece_tables;
+    b.wide_pre = b.wide_cnt + PAGED_MAX_ITEMS;
+    b.wide_desc = b.wide_pre + 8 * PAGED_MAX_ITEMS;
+  }
+  hipLaunchKernelGGL(k_paged_rows, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, pa.n_nodes, tiles(hg), rows, pa.nt_max,
+                     pieces, pa.n_pages, pa.q_off, pa.ctx_page_off, pa.ctx_pages, pa.ctx_page_len, pa.own_page, pa.own_len, b.sched,
+                     b.wide_cnt, b.wide_pre, b.wide_col);
+  DAG_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_wide_order, dim3((unsigned)((slots * pieces + 3) / 4)), dim3(256), 0, stream, slots * pieces, b.wide_cnt, b.wide_pre,
+                     b.wide_desc, b.wide_count);
+  DAG_LAUNCH_CHECK();
+  b.col = b.wide_col;
+  b.qtile_desc = b.wide_desc;
+  b.n_tiles_dev = b.wide_count;
+  const int rc = hg == 4   ? launch_one<D, 4, 2, STREAM_PAGES>(b, slots * pieces, stream)
+                 : hg == 2 ? launch_one<D, 2, 4, STREAM_PAGES>(b, slots * pieces, stream) : launch_one<D, 1, 8, STREAM_PAGES>(b, slots * pieces, stream);
+  if (rc != DAG_OK || pieces == 1) return rc;
+  hipLaunchKernelGGL((k_paged_merge<D>), dim3((unsigned)(items * (D / 8))), dim3(256), 0, stream, b, slots, pieces, hg);
+  DAG_LAUNCH_CHECK();
+  return DAG_OK;
+}
+
+int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream) {
+  return head_dim == 128 ? launch_paged<128>(pa, stream) : launch_paged<64>(pa, stream);
 }
 
 int launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t stream) {

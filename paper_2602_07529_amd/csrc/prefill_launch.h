@@ -57,6 +57,7 @@ struct PrefillArgs {
   int32_t* node_runs;  // [total_nodes][64][2], null when the workspace has no room for them
   int32_t* tok_depth;  // [total_tokens] tokens of its own node in front of every token
   ChunkTables chunk[DAG_CHUNK_SIZES];
+  float* part;  // paged prefill: partial results of the pieces of its rows of tiles, null: no room for them
 };
 
 // The node tables hold 64 runs per node, the most that 128 nodes can have.  They take the place of the
@@ -88,9 +89,17 @@ inline size_t prefill_bf16_table_bytes(int64_t total_qtiles, int64_t csr_capacit
 // Paged prefill: the kernel argument block (q, k = K pool, vt = V pool, out, lse, sched, hq, hkv,
 // scale, head0 / heads, and the five table pointers, of which wide_col holds the tile entries)
 // plus what the table kernel reads.
+constexpr int PAGED_MAX_ITEMS = 256;  // at most this many items (of one KV head and HG heads) are pieces
+constexpr int PAGED_MAX_CUTS = 32;    // of one row of tiles
+constexpr int PAGED_CUT_TILES = 24;   // shorter rows of tiles are not cut: the partial results of a full device are 34 MB, 15 us written and read
+// (a piece has 256 rows of sums, with two words a row; items are at least as many as rows of tiles)
+inline size_t paged_piece_bytes(int64_t slots, int64_t nt_max) {
+  return slots > PAGED_MAX_ITEMS / 2 || nt_max < PAGED_CUT_TILES ? 0 : (size_t)PAGED_MAX_ITEMS * (17 * 4 + 8 * (32 * 128 + 64) * 4) + 256;
+}
 struct PagedPrefillArgs {
   PrefillArgs a;
-  int n_nodes, qt_max, nt_max, n_pages;
+  int n_nodes, max_new, nt_max, n_pages;
+  int32_t* piece_tables;  // room for the count and the two descriptors of PAGED_MAX_ITEMS items, where a.part is not null
   const int32_t *q_off, *ctx_page_off, *ctx_pages, *ctx_page_len, *own_page, *own_len;
 };
 int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream);
