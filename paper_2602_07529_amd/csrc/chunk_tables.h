@@ -108,10 +108,11 @@ __device__ __forceinline__ void node_rows(int gv, int n_seqs, int total_nodes, i
   }
 }
 
-// Tokens of its own node in front of a token, for the 1024 tokens from t0 on (not from the position ids: those
+// Tokens of its own node in front of a token, for as many tokens as the block has threads, from t0 on (not from the position ids: those
 // are the caller's to shift).
 __device__ __forceinline__ void token_depths(const PrefillArgs& a, int64_t t0) {
-  for (int64_t t = t0 + threadIdx.x; t < min(t0 + 1024, a.total_tokens); t += blockDim.x) {
+  const int64_t t = t0 + threadIdx.x;
+  if (t < a.total_tokens) {
     const int b = dag_find_segment(a.cu_seqlens, a.n_seqs, (int)t);
     a.tok_depth[t] = (int)t - a.cu_seqlens[b] - a.node_tok_start[a.node_start[b] + a.tok_node[t]];
   }

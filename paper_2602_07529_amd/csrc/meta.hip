@@ -364,44 +364,76 @@ __global__ void __launch_bounds__(256) k_seq_node(int n_seqs, Table table, const
   if (threadIdx.x == 0) o.useful_pairs[b] = pairs;
 }
 
-// The first blocks: one thread per (query tile, key tile), its state in the block map.  Also adds up the
+// The first blocks: one thread, or LANES of them, per (query tile, key tile), its state in the block map.  Also adds up the
 // non-skip tiles of every query tile's row (cnt, zeroed before): tiles are numbered row after row, so
 // a block touches at most blockDim.x consecutive rows; it counts them in LDS and adds each row's
-// share to cnt once.  The remaining blocks, 1024 tokens each: node and position of every token.
+// share to cnt once.  The remaining blocks, 256 tokens each: node and position of every token.
+// A thread is a chain of some fifteen loads, each of which waits for the one in front (which sequence, which nodes, do they
+// see each other): with STAGED the tables of the whole batch are in LDS first, one load and a barrier, where they are small.
+// A tile of short nodes is many pairs of nodes (64 of eight tokens each): LANES neighbouring threads share a tile's, up to as
+// many tiles as then still fit the device at once.  70 nodes of 23 to 129 tokens 9.4 -> 5.1 us, 2 x 68 nodes of 21 to 185
+// 9.9 -> 5.5 (the copies alone 9.2 and 8.6), 4 x 4608 fork-join 5.6 -> 4.8; 8 x 64 nodes of 144, one thread a tile, 11.6 -> 10.8.
+constexpr int kStagedNodes = 512, kStagedSeqs = 64;
+constexpr int64_t kSharedTiles = 1 << 16;
+template <bool STAGED, int LANES>
 __global__ void __launch_bounds__(256) k_tiles(int n_seqs, int64_t total_tiles, int tile_blocks, int total_tokens, int W,
-                                               int tile_m, int tile_n, MetaOut o, int32_t* cnt) {
-  if ((int)blockIdx.x >= tile_blocks) {
-    const int t0 = (blockIdx.x - tile_blocks) * 1024;
-    for (int t = t0 + threadIdx.x; t < min(t0 + 1024, total_tokens); t += 256) {
-      const int b = dag_find_segment(o.cu_seqlens, n_seqs, t);
-      const int n0 = o.node_start[b], i = t - o.cu_seqlens[b];
-      const int v = dag_find_segment(o.node_tok_start + n0, o.node_start[b + 1] - n0, i);
+                                               int tile_m, int tile_n, MetaOut o, int32_t* cnt, int total_nodes) {
+  __shared__ int32_t s_tok[STAGED ? kStagedNodes : 1], s_cu[STAGED ? kStagedSeqs + 1 : 1], s_node[STAGED ? kStagedSeqs + 1 : 1];
+  __shared__ int32_t s_qs[STAGED ? kStagedSeqs + 1 : 1];
+  __shared__ int64_t s_off[STAGED ? kStagedSeqs + 1 : 1];
+  __shared__ uint64_t s_vis[STAGED ? 2 * kStagedNodes : 1];
+  const bool tokens = (int)blockIdx.x >= tile_blocks;
+  if constexpr (STAGED) {
+    for (int i = threadIdx.x; i < total_nodes; i += 256) s_tok[i] = o.node_tok_start[i];
+    if (!tokens)
+      for (int i = threadIdx.x; i < total_nodes * W; i += 256) s_vis[i] = o.node_vis[i];
+    if ((int)threadIdx.x <= n_seqs) {
+      s_cu[threadIdx.x] = o.cu_seqlens[threadIdx.x];
+      s_node[threadIdx.x] = o.node_start[threadIdx.x];
+      s_qs[threadIdx.x] = o.qtile_start[threadIdx.x];
+      s_off[threadIdx.x] = o.block_map_off[threadIdx.x];
+    }
+    __syncthreads();
+  }
+  const int32_t* const tok_start = STAGED ? s_tok : o.node_tok_start;
+  const int32_t* const cu_seqlens = STAGED ? s_cu : o.cu_seqlens;
+  const int32_t* const node_start = STAGED ? s_node : o.node_start;
+  const int32_t* const qtile_start = STAGED ? s_qs : o.qtile_start;
+  const int64_t* const block_map_off = STAGED ? s_off : o.block_map_off;
+  const uint64_t* const vis = STAGED ? s_vis : o.node_vis;
+  if (tokens) {
+    const int t = (blockIdx.x - tile_blocks) * 256 + threadIdx.x;
+    if (t < total_tokens) {
+      const int b = dag_find_segment(cu_seqlens, n_seqs, t);
+      const int n0 = node_start[b], i = t - cu_seqlens[b];
+      const int v = dag_find_segment(tok_start + n0, node_start[b + 1] - n0, i);
       o.tok_node[t] = v;
-      o.pos_ids[t] = o.node_pos_start[n0 + v] + i - o.node_tok_start[n0 + v];
+      o.pos_ids[t] = o.node_pos_start[n0 + v] + i - tok_start[n0 + v];
     }
     return;
   }
   __shared__ int s_rows[256];
   __shared__ int s_first;
   s_rows[threadIdx.x] = 0;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LANES;
+  const int sub = threadIdx.x % LANES;
   int gq = 0;  // query tile (row of the block map) over the whole batch
   uint8_t state = DAG_TILE_SKIP;
   if (idx < total_tiles) {
-    const int b = dag_find_segment(o.block_map_off, n_seqs, idx);
-    const int T = o.cu_seqlens[b + 1] - o.cu_seqlens[b];
+    const int b = dag_find_segment(block_map_off, n_seqs, idx);
+    const int T = cu_seqlens[b + 1] - cu_seqlens[b];
     const int KT = (T + tile_n - 1) / tile_n;
-    const int64_t loc = idx - o.block_map_off[b];
+    const int64_t loc = idx - block_map_off[b];
     const int a = (int)(loc / KT), kb = (int)(loc % KT);
-    gq = o.qtile_start[b] + a;
-    const int n0 = o.node_start[b];
-    state = tile_state(T, o.node_start[b + 1] - n0, o.node_tok_start + n0, o.node_vis + (int64_t)n0 * W, W, a * tile_m,
-                       min(T, (a + 1) * tile_m), kb * tile_n, min(T, (kb + 1) * tile_n));
-    o.block_map[idx] = state;
+    gq = qtile_start[b] + a;
+    const int n0 = node_start[b];
+    state = tile_state(T, node_start[b + 1] - n0, tok_start + n0, vis + (int64_t)n0 * W, W, a * tile_m,
+                       min(T, (a + 1) * tile_m), kb * tile_n, min(T, (kb + 1) * tile_n), sub, LANES);
+    if (sub == 0) o.block_map[idx] = state;
   }
   if (threadIdx.x == 0) s_first = gq;  // thread 0 is always valid (the grid covers total_tiles)
   __syncthreads();
-  if (state != DAG_TILE_SKIP) atomicAdd(&s_rows[gq - s_first], 1);
+  if (state != DAG_TILE_SKIP && sub == 0) atomicAdd(&s_rows[gq - s_first], 1);
   __syncthreads();
   if (s_rows[threadIdx.x] != 0) atomicAdd(cnt + s_first + threadIdx.x, s_rows[threadIdx.x]);
 }
@@ -587,9 +619,12 @@ extern "C" int dag_build_meta(const dag_desc_t* d, const dag_meta_t* m, void* ws
   }
   DAG_LAUNCH_CHECK();
   if (s.total_tokens == 0) return DAG_OK;
-  const int64_t tile_blocks = dag_ceil_div(s.total_tiles, 256);
-  hipLaunchKernelGGL(k_tiles, dim3((unsigned)(tile_blocks + dag_ceil_div(s.total_tokens, 1024))), dim3(256), 0, stream,
-                     d->n_seqs, s.total_tiles, (int)tile_blocks, (int)s.total_tokens, W, d->tile_m, d->tile_n, o, d_cnt);
+  const bool shared = s.total_tiles <= kSharedTiles;
+  const int64_t tile_blocks = dag_ceil_div(s.total_tiles * (shared ? 4 : 1), 256);
+  const bool staged = s.total_nodes <= kStagedNodes && d->n_seqs <= kStagedSeqs && W <= 2;
+  auto* const tiles = staged ? (shared ? k_tiles<true, 4> : k_tiles<true, 1>) : shared ? k_tiles<false, 4> : k_tiles<false, 1>;
+  hipLaunchKernelGGL(tiles, dim3((unsigned)(tile_blocks + dag_ceil_div(s.total_tokens, 256))), dim3(256), 0, stream,
+                     d->n_seqs, s.total_tiles, (int)tile_blocks, (int)s.total_tokens, W, d->tile_m, d->tile_n, o, d_cnt, (int)s.total_nodes);
   DAG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_csr_order_desc, dim3((unsigned)((QT + 3) / 4)), dim3(256), 0, stream, d->n_seqs, QT, d->tile_m,
                      d->tile_n, d_cnt, o);

@@ -275,13 +275,13 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
   if (qt < total_qtiles) wide_order(qt, total_qtiles, wide_cnt, wide_pre, wide_desc, wide_count);
 }
 
-// Four nodes a block, then (of the first size) blocks of 1024 tokens.
+// Four nodes a block, then (of the first size) blocks of 256 tokens.
 template <int W>
 __global__ void __launch_bounds__(256) k_node_rows(PrefillArgs a, int sizes) {
   const int node_blocks = ((int)a.total_nodes + 3) / 4, i = nth_size(sizes, blockIdx.y), rows = rows_of(i);
   const bool first = blockIdx.y == 0;
   if ((int)blockIdx.x >= node_blocks) {
-    if (first) token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 1024);
+    if (first) token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 256);
     return;
   }
   const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(256) k_chunk_order(PrefillArgs a, int sizes) {
   if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
 }
 // Few nodes: the tables of a size and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2), and
-// blocks of 1024 tokens as above.
+// blocks of 1024 tokens.
 constexpr int SMALL_NODES = 64, SMALL_SLOTS = 128;
 template <int W>
 __global__ void __launch_bounds__(1024) k_node_rows_small(PrefillArgs a, int sizes) {
@@ -1962,14 +1962,14 @@ bool prefill_on_chunks(const PrefillArgs& a, int head_dim) { return on_chunks(a,
 
 // The nodes' runs and the chunk tables of the sizes asked for: descriptors, then launch order (by descending tile count).
 static int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream) {
-  const unsigned n_sizes = (unsigned)__builtin_popcount((unsigned)sizes), token_blocks = (unsigned)dag_ceil_div(a.total_tokens, 1024);
+  const unsigned n_sizes = (unsigned)__builtin_popcount((unsigned)sizes);
   const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[__builtin_ctz(sizes)]);  // (the larger sizes have fewer)
   if (a.total_nodes <= SMALL_NODES && slots <= SMALL_SLOTS) {
-    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(n_sizes + token_blocks), dim3(1024), 0, stream, a, sizes);
+    hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(n_sizes + (unsigned)dag_ceil_div(a.total_tokens, 1024)), dim3(1024), 0, stream, a, sizes);
     DAG_LAUNCH_CHECK();
     return DAG_OK;
   }
-  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4) + token_blocks, n_sizes),
+  hipLaunchKernelGGL(a.W == 1 ? k_node_rows<1> : k_node_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4 + dag_ceil_div(a.total_tokens, 256)), n_sizes),
                      dim3(256), 0, stream, a, sizes);
   hipLaunchKernelGGL(k_chunk_order, dim3((unsigned)((slots + 3) / 4), n_sizes), dim3(256), 0, stream, a, sizes);
   DAG_LAUNCH_CHECK();

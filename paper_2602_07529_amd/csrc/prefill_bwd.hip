@@ -436,9 +436,10 @@ __global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs
   x -= n.nodes * n.sizes;
   if (x < n.tokens) {
     if (a.runs) {
-      token_depths(p, (int64_t)x * 1024);
+      token_depths(p, (int64_t)x * 256);
     } else {
-      for (int64_t t = (int64_t)x * 1024 + threadIdx.x; t < min((int64_t)x * 1024 + 1024, a.total_rows / a.hq); t += 256) bwd_token_vis(a, (int)t);
+      const int64_t t = (int64_t)x * 256 + threadIdx.x;
+      if (t < a.total_rows / a.hq) bwd_token_vis(a, (int)t);
     }
     return;
   }
@@ -2074,7 +2075,7 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_
   BwdArgs a = args;
   constexpr int RPB = 256 / (D / 8), NQ = Dq<D>::NPAIR;  // rows per workgroup of bwd_delta
   const int n_sizes = __builtin_popcount((unsigned)sizes), waves4 = (int)((total_ktiles + 3) / 4);
-  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 1023) / 1024), waves4, (int)((a.total_rows + RPB - 1) / RPB)};
+  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 255) / 256), waves4, (int)((a.total_rows + RPB - 1) / RPB)};
   hipLaunchKernelGGL((k_bwd_delta_tables<D>), dim3((unsigned)(pre.nodes * pre.sizes + pre.tokens + pre.weights + pre.delta)), dim3(256), 0, stream, a, p, sizes, pre);
   // (without pieces the flags of k_dkv_finish lie where dQ on the block map's tiles reads the words of its rows)
   const bool order_now = a.pieces || a.runs || !a.dkv_stream;
