@@ -89,6 +89,7 @@ struct BwdArgs {
   f32x4* part;    // [split piece][hkv][4 waves][dK, dV: 32 dims][4][64 lanes]
   int max_split;  // room for this many pieces of split pairs (a KV head)
   bool again;     // k_dkv_finish may read the inputs once more
+  int dq_pieces;  // dQ on chunks: workgroups that may share a chunk, set per launch (see dq_cuts)
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -1724,6 +1725,10 @@ struct Dq {
 // in the order of what its node sees, gathered row by row, so that only its last tiles take a mask, and
 // that mask is arithmetic on positions.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of
 // dimension 64: 336 us on the block map's tiles, 240 on chunks.
+// Few chunks leave compute units idle, and a chunk is a chain of 2 us a tile: its tiles are then shared out over up to
+// `pieces` workgroups of at least DQ_PIECE tiles, whose sums k_dq_sum adds up (2214 tokens of one head 70 -> 33 + 5 us, 3515 tokens, 8 / 2 heads: 106 -> 42 + 5).
+constexpr int DQ_PIECE = 6, DQ_MAX_PIECES = 16;
+__device__ __forceinline__ int dq_cuts(int tiles, int pieces) { return max(min(pieces, tiles / DQ_PIECE), 1); }
 template <int D, bool WIDE, bool NODES>
 __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   using C = Dq<D>;
@@ -1740,10 +1745,16 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   const int pair = w >> 1;  // (WIDE) which of the query tiles
   DqTile t;
   int64_t wide_base = 0;
+  int cuts = 1, tile0 = 0, tile1 = 0;
   if constexpr (NODES) {
-    if ((int)blockIdx.x >= *a.chunk[WIDE].count) return;  // (the launch is sized by a bound)
-    const int32_t* d = a.chunk[WIDE].desc + (size_t)blockIdx.x * 8;
+    const int chunk = blockIdx.x / a.dq_pieces, cut = blockIdx.x % a.dq_pieces;
+    if (chunk >= *a.chunk[WIDE].count) return;  // (the launch is sized by a bound)
+    const int32_t* d = a.chunk[WIDE].desc + (size_t)chunk * 8;
     t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
+    cuts = dq_cuts(t.N, a.dq_pieces);
+    if (cut >= cuts) return;
+    tile0 = cut * (t.N / cuts) + min(cut, t.N % cuts);
+    tile1 = tile0 + t.N / cuts + (cut < t.N % cuts);
   } else if constexpr (!WIDE) {
     t = dq_tile(a);
   } else {
@@ -1970,8 +1981,9 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
     __builtin_amdgcn_s_barrier();  // every wave is done with the ring before it is filled again
     asm volatile("" ::: "memory");
   };
-  ring_loop(std::false_type{}, 0, NF);
-  ring_loop(std::true_type{}, NF, t.N);  // the masked and the ragged tiles
+  if constexpr (!NODES) tile1 = t.N;
+  ring_loop(std::false_type{}, tile0, min(NF, tile1));
+  ring_loop(std::true_type{}, max(NF, tile0), tile1);  // the masked and the ragged tiles
   // The masked tiles of a chunk multiply a hidden key's K by zero, and 0 x Inf or NaN is NaN: as in dK / dV above
   // the dQ rows of such a wave are taken again from the visible keys.
   if constexpr (NODES) {
@@ -1981,11 +1993,12 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
 #pragma unroll
       for (int e = 0; e < 16; e += 2) any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(dQ[db][e], dQ[db][e + 1]), any);
     const int2* const runs = (const int2*)a.runs + t.c0;
+    const int pos_end = min(tile1 * BN, n_pos);
     bool suspect = false;
     if (__builtin_amdgcn_ballot_w64(row_ok && any != any) != 0) {
 #pragma unroll 1
-      for (int p0 = NF * BN; p0 < n_pos && !suspect; p0 += 64) {  // a key per lane
-        const int p = min(p0 + lane, n_pos - 1);
+      for (int p0 = max(NF, tile0) * BN; p0 < pos_end && !suspect; p0 += 64) {  // a key per lane
+        const int p = min(p0 + lane, pos_end - 1);
         int tok = cu;
         for (int e = 0; e < 64 && runs[e].x < p0 + 64; ++e) tok = p >= runs[e].x ? p + runs[e].y : tok;
         suspect = __builtin_amdgcn_ballot_w64(dag_row_not_finite<D>(a.k + ((size_t)tok * a.hkv + hk) * D)) != 0;
@@ -1999,7 +2012,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
       const int own = anc + iq_row;
       int run = 0;
 #pragma unroll 1
-      for (int p = 0; p < n_pos; ++p) {
+      for (int p = tile0 * BN; p < pos_end; ++p) {
         while (run < 63 && runs[run + 1].x <= p) ++run;
         const size_t row = (size_t)(p + runs[run].y) * a.hkv + hk;
         const uint16_t *kp = a.k + row * D, *vp = a.v + row * D;
@@ -2036,7 +2049,52 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
       }
     }
   }
+  if (NODES && cuts > 1) {
+    f32x4* const to = a.part + ((((size_t)blockIdx.x * a.hkv + hk) * gridDim.z + blockIdx.z) * NW + w) * (D / 4 * 32) + lane;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4)
+        to[(4 * db + e4) * 64] = f32x4{dQ[db][4 * e4], dQ[db][4 * e4 + 1], dQ[db][4 * e4 + 2], dQ[db][4 * e4 + 3]};
+    return;
+  }
   dq_store<D>(a, me, H, dQ);
+}
+// Sums of the chunks whose tiles several workgroups share, in the order of the tiles: a wave per sixteen dimensions of a wave of
+// the dQ kernel, everything of eight pieces fetched at once.
+template <int D, bool WIDE>
+__global__ void __launch_bounds__(256) k_dq_sum(BwdArgs a, int nz) {
+  constexpr int NPAIR = Dq<D>::NPAIR, NW = 2 * NPAIR, PARTS = D / 16, AT_ONCE = 8;
+  const int x = blockIdx.x * 4 + (threadIdx.x >> 6), part = x % PARTS, w = x / PARTS % NW, z = x / (PARTS * NW) % nz;
+  const int hk = x / (PARTS * NW) / nz % a.hkv, chunk = x / (PARTS * NW) / nz / a.hkv;
+  const int lane = threadIdx.x & 63, L = lane & 31, H = lane >> 5;
+  if (chunk >= *a.chunk[WIDE].count) return;
+  const int32_t* const d = a.chunk[WIDE].desc + (size_t)chunk * 8;
+  const int n = dq_cuts(d[4], a.dq_pieces), g = WIDE ? a.dq_narrow + z : z * NPAIR + (w >> 1);
+  if (n < 2 || (!WIDE && g >= a.dq_narrow)) return;
+  const size_t step = (size_t)a.hkv * nz * NW * (D / 4 * 32);
+  const f32x4* const from = a.part + (size_t)chunk * a.dq_pieces * step + (((size_t)hk * nz + z) * NW + w) * (D / 4 * 32) + 2 * part * 64 + lane;
+  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+  for (int p0 = 0; p0 < n; p0 += AT_ONCE) {
+    f32x4 v[AT_ONCE][2];
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i) {
+      const f32x4* const at = from + min(p0 + i, n - 1) * step;
+      v[i][0] = at[0];
+      v[i][1] = at[64];
+    }
+#pragma unroll
+    for (int i = 0; i < AT_ONCE; ++i)
+      if (p0 + i < n) {
+        s0 += v[i][0];
+        s1 += v[i][1];
+      }
+  }
+  const int row = d[2] + (WIDE ? BM * (w >> 1) : 0) + 32 * (w & 1) + L;
+  if (row >= d[1]) return;
+  uint16_t* const to = a.dq + ((size_t)(d[0] + row) * a.hq + hk * a.G + g) * D + 16 * part + 4 * H;
+  *(u32x2*)to = u32x2{dag_pack_bf2(s0[0] * a.scale, s0[1] * a.scale), dag_pack_bf2(s0[2] * a.scale, s0[3] * a.scale)};
+  *(u32x2*)(to + 8) = u32x2{dag_pack_bf2(s1[0] * a.scale, s1[1] * a.scale), dag_pack_bf2(s1[2] * a.scale, s1[3] * a.scale)};
 }
 template <bool WIDE>
 __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE, false>(a); }
@@ -2095,11 +2153,28 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_
     if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
         hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    if (a.dq_narrow > 0)
-      hipLaunchKernelGGL(one_tile, dim3((unsigned)(nodes ? a.chunk_slots[0] : total_qtiles), (unsigned)a.hkv, (unsigned)((a.dq_narrow + NPAIR - 1) / NPAIR)),
+    // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
+    // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
+    auto pieces_of = [&](int64_t slots, int nz) {
+      const int64_t items = slots * a.hkv * nz, fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
+      return a.pieces && total_qtiles >= 16 * a.n_seqs ? (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES)) : 1;
+    };
+    auto sum_pieces = [&](auto wide_c, int64_t slots, int nz) {
+      if (a.dq_pieces > 1)
+        hipLaunchKernelGGL((k_dq_sum<D, decltype(wide_c)::value>), dim3((unsigned)(slots * a.hkv * nz * 2 * NPAIR * (D / 16) / 4)), dim3(256), 0, stream, a, nz);
+    };
+    a.dq_pieces = 1;
+    if (a.dq_narrow > 0) {
+      const int nz = (a.dq_narrow + NPAIR - 1) / NPAIR;
+      if (nodes) a.dq_pieces = pieces_of(a.chunk_slots[0], nz);
+      hipLaunchKernelGGL(one_tile, dim3((unsigned)(nodes ? a.chunk_slots[0] * a.dq_pieces : total_qtiles), (unsigned)a.hkv, (unsigned)nz),
                          dim3(128 * NPAIR), sm2, stream, a);
+      sum_pieces(std::false_type{}, a.chunk_slots[0], nz);
+    }
     if (wide > 0 && nodes) {
-      hipLaunchKernelGGL(many_tiles, dim3((unsigned)a.chunk_slots[1], (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
+      a.dq_pieces = pieces_of(a.chunk_slots[1], wide);
+      hipLaunchKernelGGL(many_tiles, dim3((unsigned)(a.chunk_slots[1] * a.dq_pieces), (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
+      sum_pieces(std::true_type{}, a.chunk_slots[1], wide);
     } else if (wide > 0) {
       const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
       hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
