@@ -1119,12 +1119,18 @@ __global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a
 
 // One wave per (branch, query head): log-sum-exp combination of its partials.  What it costs is the chain
 // of dependent loads, so the group is found with one load per lane for every factor of 64 in their number, and the
-// outputs of the first partials are on their way together with the maxima and sums.  A lane has four output
-// dimensions of every second partial (every fourth at head dimension 64).
-constexpr int MERGE_THREADS = 256;  // four rows to a workgroup
-template <int D>
-__global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
-  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (MERGE_THREADS / 64) + (threadIdx.x >> 6));
+// outputs of the first partials are on their way together with the maxima and sums.  Up to MERGE_FEW_ROWS rows a lane has four
+// output dimensions (PER) of every second partial (every fourth at head dimension 64) and a workgroup four rows: fewer loads in
+// the chain.  More rows are more waves than the device holds at once, and what counts is their number of instructions: a lane
+// then has the same D / 64 dimensions of every partial, at addresses that the wave computes once, and the partials need no sum over
+// lanes.  Few partials, first and second form: dimension 64, 4096 rows 4.2 and 5.1 us, 8192 rows 7.1 and 5.9, 16384 rows 12.6 and 9.1,
+// 65536 rows 46 and 33; dimension 128 4.2 and 4.5, 8.0 and 6.8, 12.0 and 10.2, 46 and 38.
+constexpr int64_t MERGE_FEW_ROWS = 4096;
+constexpr int merge_per(int D, bool few) { return few ? 4 : D / 64; }
+constexpr int merge_threads(bool few) { return few ? 256 : 64; }
+template <int D, bool FEW>
+__global__ void __launch_bounds__(merge_threads(FEW)) k_decode_merge(DecodeArgs a) {
+  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (merge_threads(FEW) / 64) + (threadIdx.x >> 6));
   const int r = wid / a.hq, head = wid % a.hq;
   if (r >= a.n_live) return;
   const int hk = head / a.G, j = head % a.G;
@@ -1140,8 +1146,9 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
   const int rb = row >> 5, rr = row & 31;
   const size_t ia0 = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a;
   const size_t ib0 = ((size_t)r * a.hkv + hk) * a.splits_b;
-  constexpr int ROW = D / 4, SETS = 64 / ROW;  // lanes to a partial, partials to a load
-  const int set = lane / ROW, c = lane % ROW * 4;
+  constexpr int PER = merge_per(D, FEW), ROW = D / PER, SETS = 64 / ROW;  // lanes to a partial, partials to a load
+  typedef __attribute__((ext_vector_type(PER))) float part_t;
+  const int set = SETS > 1 ? lane / ROW : 0, c = lane % ROW * PER;
   const int np = a.splits_a + a.splits_b;
   // partial p of this (branch, head): shared split p, then own split p - splits_a
   auto ml_of = [&](int p) {
@@ -1150,14 +1157,16 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
   auto o_of = [&](int p) {
     return p < a.splits_a ? a.part_o_a + ((ia0 + p) * 32 + rr) * D : a.part_o_b + ((ib0 + (p - a.splits_a)) * a.G + j) * D;
   };
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  part_t acc;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
   float lsum = 0.f;
   auto merge = [&](auto batch_c) __attribute__((always_inline)) {  // BATCH loads of SETS partial outputs in flight
     constexpr int BATCH = decltype(batch_c)::value;
-    f32x4 x[BATCH];
+    part_t x[BATCH];
     auto fetch = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) x[i] = *(const f32x4*)(o_of(min(p0 + i * SETS + set, np - 1)) + c);
+      for (int i = 0; i < BATCH; ++i) x[i] = *(const part_t*)(o_of(min(p0 + i * SETS + set, np - 1)) + c);
     };
     fetch(0);
     // The reference maximum first (64 partials at a time, one per lane, so that their loads are in
@@ -1188,26 +1197,35 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_decode_merge(DecodeArgs a) {
           const float wi = __shfl(wgt, b0 - p0 + i * SETS + set);
           lsum += __shfl(wl, b0 - p0 + i * SETS + set);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
+          for (int e = 0; e < PER; ++e) acc[e] += wi != 0.f ? wi * x[i][e] : 0.f;
         }
       }
     }
   };
   // (what is read beyond the last partial is that one again)
-  if (np <= SETS) merge(std::integral_constant<int, 1>{});
-  else if (np <= 3 * SETS) merge(std::integral_constant<int, 3>{});
-  else if (np <= 9 * SETS) merge(std::integral_constant<int, 9>{});
-  else merge(std::integral_constant<int, 16>{});
+  if constexpr (FEW) {
+    if (np <= SETS) merge(std::integral_constant<int, 1>{});
+    else if (np <= 3 * SETS) merge(std::integral_constant<int, 3>{});
+    else if (np <= 9 * SETS) merge(std::integral_constant<int, 9>{});
+    else merge(std::integral_constant<int, 16>{});
+  } else {
+    if (np <= 2) merge(std::integral_constant<int, 2>{});
+    else if (np <= 4) merge(std::integral_constant<int, 4>{});
+    else if (np <= 8) merge(std::integral_constant<int, 8>{});
+    else merge(std::integral_constant<int, 16>{});
+  }
 #pragma unroll
   for (int off = ROW; off < 64; off <<= 1) {
     lsum += __shfl_xor(lsum, off);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+    for (int e = 0; e < PER; ++e) acc[e] += __shfl_xor(acc[e], off);
   }
   if (set != 0) return;
   const float inv = 1.f / lsum;
   uint16_t* o = a.out + ((size_t)r * a.hq + head) * D + c;
-  *(u32x2*)o = u32x2{dag_pack_bf2(acc[0] * inv, acc[1] * inv), dag_pack_bf2(acc[2] * inv, acc[3] * inv)};
+  if constexpr (PER == 4) *(u32x2*)o = u32x2{dag_pack_bf2(acc[0] * inv, acc[1] * inv), dag_pack_bf2(acc[2] * inv, acc[3] * inv)};
+  else if constexpr (PER == 2) *(uint32_t*)o = dag_pack_bf2(acc[0] * inv, acc[1] * inv);
+  else *o = (uint16_t)dag_f2bf(acc[0] * inv);
 }
 
 // One block per live branch: rotate the new key at the branch's adaptive position and scatter
@@ -1567,7 +1585,6 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
   a.sc = softmax_scale * 1.4426950408889634f;
   a.th = 8.f / a.sc;
   hipStream_t stream = (hipStream_t)stream_;
-  const unsigned nout = (unsigned)dag_ceil_div((int64_t)d->n_live * hq, MERGE_THREADS / 64);
   a.item_base = 0;
   unsigned items = (unsigned)(p.items_a + p.items_b);
   if (p.wide && p.items_a > 0) {
@@ -1607,8 +1624,11 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
     else hipLaunchKernelGGL(k_decode<64>, dim3(items), dim3(64), 0, stream, a);
     DAG_LAUNCH_CHECK();
   }
-  if (head_dim == 128) hipLaunchKernelGGL(k_decode_merge<128>, dim3(nout), dim3(MERGE_THREADS), 0, stream, a);
-  else hipLaunchKernelGGL(k_decode_merge<64>, dim3(nout), dim3(MERGE_THREADS), 0, stream, a);
+  const int64_t rows = (int64_t)d->n_live * hq;
+  const bool few = rows <= MERGE_FEW_ROWS;
+  auto* const merge = head_dim == 128 ? (few ? k_decode_merge<128, true> : k_decode_merge<128, false>)
+                                      : few ? k_decode_merge<64, true> : k_decode_merge<64, false>;
+  hipLaunchKernelGGL(merge, dim3((unsigned)dag_ceil_div(rows, merge_threads(few) / 64)), dim3(merge_threads(few)), 0, stream, a);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }

@@ -29,3 +29,15 @@ def test_many_groups(n_groups):
     rows = np.unique(np.concatenate([[0, 1, 2 * n_groups - 2, 2 * n_groups - 1], rng.integers(0, 2 * n_groups, 60)]))
     ref = orc.attn_decode(st["desc"], dags.to_f64(st["q"]), dags.to_f64(kp), dags.to_f64(vp), branches=rows)
     check_close(out[rows], ref[rows], torch.bfloat16, "%d groups" % n_groups)
+
+
+# 4096 rows (branches x heads) take the merge of few rows, 4128 and 4160 that of many; 2, 6 and 17 partials to a row
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("groups,branches,hkv,shared,own", [(32, 4, 8, 17, 9), (43, 3, 8, 17, 9), (43, 3, 2, 2500, 200), (10, 13, 1, 12000, 700)])
+def test_merge_of_few_and_of_many_rows(groups, branches, hkv, shared, own, d):
+    hq, n = 32, groups * branches
+    st = dags.decode_state(900 + n + d, groups, branches, shared, 1, hq, hkv, d, branch_len_list=[max(1, own - 40 * (r % 5)) for r in range(n)])
+    out, kp, vp = _gpu_decode(st, hq, hkv, d, 1e4)
+    rows = np.array([0, 1, n // 2, n - 2, n - 1])
+    ref = orc.attn_decode(st["desc"], dags.to_f64(st["q"]), dags.to_f64(kp), dags.to_f64(vp), branches=rows)
+    check_close(out[rows], ref[rows], torch.bfloat16, "%d rows" % (n * hq))
