@@ -7,26 +7,26 @@
 namespace {
 
 // Tokens per block: four share the frequencies.  With fewer than kRopeFew tokens that leaves compute units
-// idle and every thread several rows one after another: 650 tokens of 40 heads take 8.3 us, with one token a block 7.0.
+// idle and every thread several rows one after another: 650 tokens of 40 heads take 6.2 us, with one token a block 5.2.
 // A block is a chain of frequencies, angles and rows: where a token has few pieces of rows and the batch many blocks, sixteen
-// tokens share the chain (2 / 2 heads of dimension 128: 15,000 tokens 12.4 -> 10.9 us, 76,000 48 -> 35; 96 pieces a token 17.0
-// -> 16.5, 5000 tokens of few pieces 5.6 -> 6.6).
+// tokens share the chain (four, sixteen: 2 / 2 heads of dimension 64, 16 pieces, 20,000 tokens 9.1, 7.6 us, 76,000 24.3, 18.6; 5 / 1
+// of 128, 48 pieces, 39.8, 39.1; 6 / 2, 64 pieces, 48.5, 50.4; 2 / 2 of 64, 8192 tokens 5.2, 5.1, 4000 4.2, 4.4).
 constexpr int kRopeTokens = 4, kRopeManyTokens = 16;
 constexpr int64_t kRopeFew = 2048, kRopeMany = 8192;
-constexpr int kRopeFewPieces = 64;
+constexpr int kRopeFewPieces = 48;
 constexpr int kRopeMaxHalf = 128;
 
 template <bool BF16, int TOKENS>
 __global__ void __launch_bounds__(256) k_rope(const int32_t* __restrict__ pos_ids, int64_t n_tokens,
                                               void* __restrict__ q, void* __restrict__ k, int hq, int hkv,
-                                              int D, float theta) {
+                                              int D, RopeTheta theta) {
   __shared__ double s_freq[kRopeMaxHalf];
   __shared__ float s_cos[TOKENS][kRopeMaxHalf];
   __shared__ float s_sin[TOKENS][kRopeMaxHalf];
   const int half = D / 2;
   const int64_t t0 = (int64_t)blockIdx.x * TOKENS;
   for (int m = threadIdx.x; m < half; m += blockDim.x)
-    s_freq[m] = pow((double)theta, -2.0 * (double)m / (double)D);
+    s_freq[m] = dag_rope_freq(theta, m, D);
   __syncthreads();
   for (int idx = threadIdx.x; idx < TOKENS * half; idx += blockDim.x) {
     const int tt = idx / half, m = idx % half;
@@ -102,7 +102,7 @@ extern "C" int dag_rope_qk(const int32_t* pos_ids, int64_t n_tokens, void* q, vo
   const int tokens = n_tokens < kRopeFew ? 1 : n_tokens >= kRopeMany && pieces <= kRopeFewPieces ? kRopeManyTokens : kRopeTokens;
   auto* const kernel = bf16 ? (tokens == 1 ? k_rope<true, 1> : tokens == 4 ? k_rope<true, kRopeTokens> : k_rope<true, kRopeManyTokens>)
                             : (tokens == 1 ? k_rope<false, 1> : tokens == 4 ? k_rope<false, kRopeTokens> : k_rope<false, kRopeManyTokens>);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)dag_ceil_div(n_tokens, tokens)), dim3(256), 0, stream, pos_ids, n_tokens, q, k, hq, hkv, head_dim, theta);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)dag_ceil_div(n_tokens, tokens)), dim3(256), 0, stream, pos_ids, n_tokens, q, k, hq, hkv, head_dim, dag_rope_theta(theta));
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }

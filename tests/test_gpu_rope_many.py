@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T", [8192, 8193, 8207])
-@pytest.mark.parametrize("hq,hkv,d,dtype", [(1, 1, 64, torch.bfloat16), (6, 2, 128, torch.bfloat16), (3, 1, 96, torch.bfloat16), (2, 1, 64, torch.float32)])
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(1, 1, 64, torch.bfloat16), (5, 1, 128, torch.bfloat16), (6, 2, 128, torch.bfloat16), (3, 1, 96, torch.bfloat16), (2, 1, 64, torch.float32)])
 def test_many_tokens_of_few_heads(T, hq, hkv, d, dtype):
     q, k, _ = dags.make_qkv(13, T, hq, hkv, d, 1.0, dtype)
     pos = np.random.Generator(np.random.PCG64(4)).integers(0, 60000, size=T).astype(np.int32)
