@@ -7,7 +7,7 @@ copy the register, or (once the value is dead) reuse it for something else, whil
 still in flight.  This test compiles the sources to assembly and checks, over the control-flow
 graph of every kernel, that no instruction touches a register whose read may be pending under the
 in-order return of LDS operations -- so that a compiler or source change that breaks the scheme is
-found on the CPU and not as wrong numbers now and then.  For the two pipelined backward kernels it
+found on the CPU and not as wrong numbers now and then.  For the pipelined backward kernels of head dimension 128 it
 also checks that an iteration is one straight-line block.
 """
 import os
@@ -23,9 +23,9 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 CAP = 24  # reads remembered per path (the hardware counter holds 15)
 
 # pipelined blocks of the backward kernels (one without masks, one with): LDS reads of each
-#   k_bwd_dkv2: 32 row operands + 32 transposed operands (two reads each) + 8 groups of row data (2 reads)
-#   k_bwd_dq2:  32 row operands + 16 transposed operands (two reads each)
-PIPELINED = {"k_bwd_dkv2": [112, 112], "k_bwd_dq2": [64, 64]}
+#   k_bwd_dkv2, k_nodes_dkv2: 32 row operands + 32 transposed operands (two reads each) + 8 groups of row data (2 reads)
+#   k_bwd_dq2, k_nodes_dq2:   32 row operands + 16 transposed operands (two reads each)
+PIPELINED = {"k_bwd_dkv2": [112, 112], "k_bwd_dq2": [64, 64], "k_nodes_dkv2": [112, 112], "k_nodes_dq2": [64, 64]}
 
 
 def _regs(text):
@@ -130,14 +130,20 @@ def _conflicts_of_kernel(lines):
     return blocks, bad
 
 
+_texts = {}
+
+
 def _assembly(name, tmp_path):
+    if name in _texts:
+        return _texts[name]
     asm = tmp_path / (name + ".s")
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fno-gpu-rdc", "-Xclang", "-target-feature", "-Xclang",
            "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
            "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-S", "--cuda-device-only", "-o", str(asm),
            os.path.join(CSRC, name + ".hip")]
     subprocess.run(cmd, check=True, capture_output=True, timeout=900)
-    return asm.read_text().split("\n")
+    _texts[name] = asm.read_text().split("\n")
+    return _texts[name]
 
 
 def _kernels(text, pattern):
@@ -147,8 +153,9 @@ def _kernels(text, pattern):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
-@pytest.mark.parametrize("source,pattern,n_kernels", [("prefill_bf16", "k_prefill_bf16", 6), ("prefill_bwd", "k_bwd_d", 17),
-                                                      ("decode", "k_decode", 12)])
+@pytest.mark.parametrize("source,pattern,n_kernels", [("prefill_bf16", "k_prefill_bf16", 6), ("prefill_bf16", "k_prefill_pages", 4),
+                                                      ("prefill_bf16", "k_prefill_nodes", 9), ("prefill_bwd", "k_bwd_d", 17),
+                                                      ("prefill_bwd", "k_nodes", 6), ("decode", "k_decode", 12)])
 def test_no_instruction_touches_a_register_with_a_read_in_flight(tmp_path, source, pattern, n_kernels):
     text = _assembly(source, tmp_path)
     seen = 0
