@@ -92,7 +92,8 @@ def test_hidden_values_backward_dq(hq, hkv, d, n_nodes, longest):
 # a branch and the last token of another one hold nothing but Inf and NaN, in every input: the siblings' gradients, and those
 # of the tokens in front of the fork for the rows' part, are what they are without them
 @pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (3, 1, 64), (4, 1, 128), (5, 1, 128)])
-@pytest.mark.parametrize("prefix,branches", [(128, [64, 64, 64, 64]), (77, [40, 100, 64, 90, 130])])
+@pytest.mark.parametrize("prefix,branches", [(128, [64, 64, 64, 64]), (77, [40, 100, 64, 90, 130]),
+                                             (2000, [64, 40, 100, 64])])  # (the last: chunks of 33 key tiles, shared by five workgroups)
 def test_hidden_tokens_backward(prefix, branches, hq, hkv, d):
     dag_list = [dags.fork_join(prefix, branches, None), dags.linear_chain([200, 77])]
     L, anc = dag_list[0]
