@@ -566,8 +566,8 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 // A wave walks its 32-key units in a pipeline: in one run of slots it takes the scores of unit u, the
 // exponentials of unit u - 1 and the P V product of unit u - 2, a slot being one operand read, one MFMA and a share
 // of the exponentials; the two products alternate, so that consecutive MFMAs do not depend on each other.
-// The reference maximum is not looked after before the exponentials: a lane's sum of 16 probabilities
-// tells afterwards whether a score left the range.
+// The reference maximum, that of the first two units, is not looked after before the exponentials: a lane's sum of 16
+// probabilities tells afterwards whether a score left the range.
 // Own items: (branch, kv head, page slice) in workgroups of the same launch; every wave streams a part of an item's
 // pages as k_decode does and the partials are put together in LDS.
 // Five and six row blocks: a tile takes as long as the SIMD with the most to do, and four waves with
@@ -865,7 +865,6 @@ __device__ __forceinline__ void wide_item(const A& a, unsigned char* smem, const
     // units 0 and 1
     arrive(0);
     scores(Ka(0), h0_t{}, SA);
-    raise(row_max(SA));
     issue(3);
     if constexpr (HALVES == 1) {
       scores(Ka(0), h1_t{}, SB);
@@ -874,6 +873,7 @@ __device__ __forceinline__ void wide_item(const A& a, unsigned char* smem, const
       scores(Ka(1), h0_t{}, SB);
       issue(4);
     }
+    raise(fmaxf(row_max(SA), row_max(SB)));  // (of 64 keys: the closer to the row's maximum, the smaller the rounding of its largest probabilities)
     l += probs(SA, P0);
 #pragma unroll 1
     for (t = LAG; t < F; t += HALVES) {
@@ -1078,6 +1078,7 @@ __global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a
   float l_tot = 0.f;
   if (w0 < w1) {
     auto qop = [&](int s) { return qf[s * 64]; };
+    a.th *= 0.125f;  // (raised by a factor of two: a wave may have a whole slice under the one reference)
     stream_slice<D>(a, a.branch_pages + a.branch_page_off[branch], w0, w1, len, len, len, hk, lane, qop, O, m, l);
     l_tot = l + __shfl_xor(l, 32);
     if (L < G) {

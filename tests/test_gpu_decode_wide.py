@@ -44,3 +44,34 @@ def test_wide_groups_at_every_number_of_row_blocks(nb, group, shared, d, growth)
     ref = orc.attn_decode(one, dags.to_f64(st["q"][:, heads]), dags.to_f64(st["k_pool"][:, head:head + 1]),
                           dags.to_f64(st["v_pool"][:, head:head + 1]), branches=list(range(g * nb, (g + 1) * nb)))
     check_close(out[rows, heads], ref[rows], torch.bfloat16, "%d branches x %d heads, %d tokens" % (nb, group, shared))
+
+
+# Probabilities are rounded to 16 bits relative to a reference maximum, and those just below a power of two, where the largest are
+# when the reference is their maximum, lose the least.  So the references have to stay near it: the error against 64 bits, as a
+# part of what probabilities relative to the row's maximum give, is 0.910, 0.925, 0.902, 0.941, 0.971 with the maximum of 64 keys in
+# the shared slices and the running one within a factor of two in the own pages; with that of 32 keys, and of the first 32 of an own
+# slice, 0.947, 0.961, 0.943, 0.993, 1.010.  `most` lies between.
+@pytest.mark.parametrize("groups,nb,shared,own,hq,hkv,d,most", [
+    (10, 10, 2021, 114, 8, 2, 64, 0.93), (4, 22, 526, 80, 2, 1, 128, 0.945), (6, 8, 3760, 258, 16, 2, 64, 0.925),
+    (10, 15, 141, 885, 5, 1, 128, 0.965), (15, 29, 104, 234, 10, 2, 128, 0.99)])
+def test_probabilities_are_rounded_near_the_maximum(groups, nb, shared, own, hq, hkv, d, most):
+    st = dags.decode_state(11, groups, nb, shared, own, hq, hkv, d)
+    dd = B.DecodeDesc(st["desc"], DEV)
+    q, out = st["q"].to(DEV), torch.empty_like(st["q"], device=DEV)
+    ws = torch.empty(B.dag_decode_workspace_bytes(dd, hq, hkv, d), dtype=torch.uint8, device=DEV)
+    B.dag_attn_decode(dd, q, st["k_pool"].to(DEV), st["v_pool"].to(DEV), out, ws)
+    torch.cuda.synchronize()
+    bf16 = lambda x: x.to(torch.bfloat16).double()  # noqa: E731
+    err = err_ref = 0.0
+    kp, vp = dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"])
+    for r in range(0, groups * nb, max(1, groups * nb // 48)):
+        for h in range(hkv):
+            k, v = (torch.from_numpy(np.ascontiguousarray(x)) for x in orc.gather_context(st["desc"], r, h, kp, vp))
+            rows = slice(h * hq // hkv, (h + 1) * hq // hkv)
+            s = st["q"][r, rows].double() @ k.T / d ** 0.5
+            p = torch.exp(s - s.max(dim=-1, keepdim=True).values)
+            total = p.sum(dim=-1, keepdim=True)
+            exact = p @ v / total
+            err += (out[r, rows].cpu().double() - exact).square().sum().item()
+            err_ref += (bf16(bf16(p) @ v / total) - exact).square().sum().item()
+    assert err < most ** 2 * err_ref, "%.4f of the error with the row's maximum" % (err / err_ref) ** 0.5
