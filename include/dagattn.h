@@ -199,8 +199,9 @@ size_t dag_prefill_workspace_bytes(const dag_meta_t* meta, int32_t hkv, int32_t 
  * dK = scale dS^T Q, only where the mask lets a pair through.  DAG_BF16 (MFMA, fp32
  * accumulation; gradients bf16) or DAG_F32 (plain fp32 arithmetic, the accuracy path; gradients
  * fp32), head_dim 128 or 64; all tensors DEVICE, 16-byte aligned; `ws` DEVICE scratch of
- * dag_prefill_bwd_workspace_bytes (less is taken where it only leaves out room for the sums of dk and dv in
- * pieces: the rows that see 128 keys are then one workgroup's).  `meta` is the one dag_build_meta filled for the forward.  In
+ * dag_prefill_bwd_workspace_bytes (less is taken where it only leaves out room for sums of pieces, about 67 MB
+ * and unused in DAG_F32: the rows that see 128 keys, and the keys that a chunk sees, are then one workgroup's, and
+ * the sums of dq, dk and dv are those of one piece).  `meta` is the one dag_build_meta filled for the forward.  In
  * bf16 dQ works on the forward's chunks or on the block map's tiles (launch order, tile descriptors,
  * FULL-first CSR), dK / dV on the rows that see 128 keys or on the block map's columns, by rules of
  * their own on node lengths and sizes.  `dk` is scratch during the call (the work lists of the chunks
@@ -355,8 +356,9 @@ typedef struct {
   const int32_t* own_len;      /* [n_nodes] tokens in the node's own pages, the new ones included */
 } dag_paged_prefill_desc_t;
 
-/* Bytes of DEVICE workspace dag_attn_prefill_paged needs (0 on bad arguments).  From contexts of 1,472 tokens on, with few
- * nodes, 34 MB of it are for contexts cut into pieces; a workspace without them is taken, the contexts then stay whole. */
+/* Bytes of DEVICE workspace dag_attn_prefill_paged needs (0 on bad arguments).  Where max_ctx_pages is 93 or more
+ * (contexts of more than 1,472 slots) and there are few nodes, 34 MB of it are for contexts cut into pieces; a workspace
+ * without them is taken, the contexts then stay whole. */
 size_t dag_prefill_paged_workspace_bytes(const dag_paged_prefill_desc_t* desc);
 
 /* q / out [q_off[n_nodes]][hq][head_dim] bf16 DEVICE (q already rotated), lse NULL or

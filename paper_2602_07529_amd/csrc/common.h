@@ -45,6 +45,11 @@ __device__ __forceinline__ uint32_t dag_pack_bf2(float lo, float hi) {
 __device__ __forceinline__ float dag_bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float dag_bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+static inline int dag_compute_units() {  // of the current device; 0: it cannot be asked
+  int dev = 0, n = 0;
+  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+}
+
 // Whether a row of D bf16 (16-byte aligned) holds an Inf or NaN.
 template <int D>
 __device__ __forceinline__ bool dag_row_not_finite(const void* row) {

@@ -559,7 +559,8 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 // Wide sibling groups (more than 32 stacked query rows per KV head, e.g. 32 siblings x 5 query heads).
 //
 // Shared items: a workgroup of eight waves per (group, kv head, page slice), a wave per 32-row block, so that the
-// shared pages are streamed once per group whatever the number of rows.  The waves read the same K/V tiles of 64
+// shared pages are streamed once per group whatever the number of rows (two row blocks leave four waves to the loads alone; with
+// six waves of the form before it 62 such shapes took 1.29 times as long).  The waves read the same K/V tiles of 64
 // keys (four pages) from rings in LDS that are filled directly from the pools (a page is the operand image).  Up to
 // four row blocks are served by two waves each, one for either half of every tile, with accumulators of
 // their own that are put together at the end.
@@ -1525,11 +1526,6 @@ int static_scratch(void** out) {
   return DAG_OK;
 }
 
-int compute_units() {  // of the current device; 0: it cannot be asked
-  int dev = 0, n = 0;
-  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
-}
-
 // static_ws: the partials go to the library's own scratch array (ws / ws_bytes ignored).
 int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, const void* v_pool, void* out,
                 int32_t hq, int32_t hkv, int32_t head_dim, float softmax_scale, void* ws, size_t ws_bytes,
@@ -1589,14 +1585,13 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
   a.item_base = 0;
   unsigned items = (unsigned)(p.items_a + p.items_b);
   if (p.wide && p.items_a > 0) {
-    // Wide sibling groups: one launch of workgroups that share their K/V blocks through LDS, the
-    // shared items first (one workgroup streams a slice of the shared pages once for all rows),
-    // the own items behind them.
+    // Wide sibling groups: one launch of workgroups with own items, of those that stream a slice of the shared pages
+    // once for all rows of a group, and of the other own items.
     const unsigned shared_wgs = (unsigned)(d->n_groups * hkv * p.splits_a);
     const unsigned threads = 64u * WIDE_WAVES;
     // Waves to an own item: as many as leave a workgroup for every compute unit (512 items of 40 pages by
     // themselves: eight waves each 30.5 us, four 27.9).
-    const int n_cu = compute_units();
+    const int n_cu = dag_compute_units();
     if (n_cu < 1) return DAG_ERR_HIP;
     a.wide_own = WIDE_WAVES;
     while (a.wide_own > 1 && (int64_t)p.items_b * a.wide_own > (int64_t)WIDE_WAVES * n_cu &&

@@ -1871,18 +1871,13 @@ bool on_chunks(const PrefillArgs& a, int head_dim) {
   return a.total_tokens >= shortest * a.total_nodes;
 }
 
-int compute_units() {  // of the current device; 0: it cannot be asked
-  int dev = 0, n = 0;
-  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
-}
-
 // Batches too small to give every compute unit an item of four heads take one or two heads to an item, all of
 // them in one launch (0: not such a batch, split_heads).  40 / 8 heads, 260 / 360 tokens: 49.5 / 56.7 ->
 // 33.2 / 36.6 us with meta and RoPE, 32 / 8 heads, 650 tokens: 43.3 -> 41.9 us, 4 / 2 heads, 2450 tokens:
 // 82.7 -> 79.2 us.  One or two heads of dimension 64 per KV head stay with their items (4 / 2 heads: 60
 // against 68 us).
 int heads_of_small_batch(const PrefillArgs& a, int head_dim) {
-  const int64_t chunks = chunk_slots(a.total_tokens, a.total_nodes, 64) * a.hkv, g = a.hq / a.hkv, n = compute_units();
+  const int64_t chunks = chunk_slots(a.total_tokens, a.total_nodes, 64) * a.hkv, g = a.hq / a.hkv, n = dag_compute_units();
   if (head_dim == 64 && g < 3) return 0;
   return chunks * g <= n ? 1 : chunks * ((g + 1) / 2) <= n ? 2 : 0;
 }
@@ -1899,7 +1894,7 @@ int launch_one(const PrefillArgs& a, long max_tiles, hipStream_t stream) {
   else if constexpr (STREAM == STREAM_PAGES && HG != 4) kernel = k_prefill_pages<D, HG, NRG>;
   else kernel = k_prefill_bf16<D, HG, NRG, STREAM == STREAM_PAGES>;
   if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess) return DAG_ERR_HIP;
-  const int n_cu = compute_units();
+  const int n_cu = dag_compute_units();
   if (n_cu < 1) return DAG_ERR_HIP;
   const long n_items = max_tiles * a.hkv * ((a.heads + HG - 1) / HG), n_wg = (long)n_cu * PER_CU;
   const unsigned grid = (unsigned)(n_items < n_wg ? n_items : n_wg);
@@ -2004,11 +1999,12 @@ int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_
 // tokens against 3100, 8 / 2 heads: 83.5 -> 35 us with the append; 6 nodes of 57 against 3750, 16 / 4: 98 -> 49.5; 28
 // shapes of 20 to 700 new tokens 1.29 times as fast on average, those of less than 24 tiles, which stay whole, 1.00).  Items take four heads of a KV head on 64 rows, one padded where the heads
 // are no multiple of four; where there are more of them than compute units, two heads on 128 or one on 256
-// rows if that makes fewer items.
+// rows if that makes fewer items: 24 such shapes, heads in fours always 0.70 times as fast (0.39 with one head to a KV head, 0.96 with
+// five).  Pieces of at least eight tiles instead of four: 0.99 over 30 shapes, 0.88 at worst.
 template <int D>
 int launch_paged(const PagedPrefillArgs& pa, hipStream_t stream) {
   const PrefillArgs& a = pa.a;
-  const int64_t n_cu = compute_units();
+  const int64_t n_cu = dag_compute_units();
   if (n_cu < 1) return DAG_ERR_HIP;
   auto tiles = [&](int hg) { return (pa.max_new + 256 / hg - 1) / (256 / hg); };   // of a node
   auto heads = [&](int hg) { return (a.heads + hg - 1) / hg; };                    // items of a KV head
