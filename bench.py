@@ -343,15 +343,15 @@ def prefill_kernels(pw):
 
 
 def bwd_kernels(pw):
-    """The launches of dag_attn_prefill_bwd at head dimension 128: dQ for groups of four heads on one chunk or query tile
-    (<false>), for the left-over heads one by one on 256 rows (<true>); dK / dV."""
+    """The launches of dag_attn_prefill_bwd at head dimension 128 (batches with more chunks than the device holds, so that
+    no chunk is shared and k_dq_sum not launched): delta and tables, orders, dQ for groups of four heads on one chunk or query
+    tile (<false>) and for the left-over heads one by one on 256 rows (<true>), dK / dV and the sums of its pieces."""
     T, nodes, words, G = _shape(pw)
     rest = G % 4
     chunks = words <= 2 and T >= (64 if rest else 16) * nodes
     dq = "k_nodes_dq2" if chunks else "k_bwd_dq2"
-    return ("k_bwd_delta<128>",) + (("k_node_rows<%d>" % words, "k_chunk_order") if chunks else ("k_bwd_tokvis",)) + \
-        ((dq + "<false>",) if G > rest else ()) + ((() if chunks else ("k_bwd_wide_rows",)) + (dq + "<true>",) if rest else ()) + \
-        ("k_bwd_weights", "k_bwd_order") + (("k_nodes_dkv2", "k_dkv_again<128>") if words <= 2 and T >= 16 * nodes else ("k_bwd_dkv2",))
+    return ("k_bwd_delta_tables<128>", "k_bwd_orders<4>") + ((dq + "<false>",) if G > rest else ()) + ((dq + "<true>",) if rest else ()) + \
+        (("k_nodes_dkv2", "k_dkv_finish<128>") if words <= 2 and T >= 16 * nodes else ("k_bwd_dkv2",))
 
 
 def prefill_leg(cfg, dev, launches, warmup, workload_key, with_bwd=False):
@@ -470,7 +470,7 @@ def main():
         extra["config5_prefill"] = prefill_leg(c5, dev, n5, min(args.warmup, 2), "config5", with_bwd=True)
         torch.cuda.empty_cache()
         extra["config5_decode"] = decode_leg(config5_decode_cfg(), dev, args.steps, args.warmup + 20, "config5",
-                                             ("k_decode_wide<128>", "k_decode_merge<128>"), copies=4)
+                                             ("k_decode_wide<128>", "k_decode_merge<128,true>"), copies=4)
     if args.only in ("all", "config4"):
         extra["config4_prefill"] = prefill_leg(dags.config(3), dev, max(1, min(args.steps, 20)),
                                                min(args.warmup, 5) + 10, "config4", with_bwd=True)
@@ -560,10 +560,10 @@ def main():
                    "value": dw.n_live / (ms_dec * 1e-3), "unit": "tok/s", "ms_per_decode_step": ms_dec,
                    "config": {"workload": dw.cfg["name"], "n_seqs": dw.cfg["n_seqs"], "live_branches": dw.n_live,
                               "shared_prefix": dw.cfg["shared"], "branch_len": dw.cfg["branch"], "page_size": 16},
-                   "roofline": {"bound": "hbm", "kernel": "k_decode<128>+k_decode_merge<128>", "achieved": dec_gbs,
+                   "roofline": {"bound": "hbm", "kernel": "k_decode<128>+k_decode_merge<128,true>", "achieved": dec_gbs,
                                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dec_gbs / HBM_PEAK_GBS,
                                 "algorithmic_bytes": dw.bytes,
-                                "traffic": traffic_of("main", "k_decode<128>", "k_decode_merge<128>")}},
+                                "traffic": traffic_of("main", "k_decode<128>", "k_decode_merge<128,true>")}},
         "decode_segments": {"metric": "segment_decode_tok_per_s_one_attention_layer",
                             "value": sw.n_live / (ms_seg * 1e-3), "unit": "tok/s", "ms_per_decode_step": ms_seg,
                             "config": {"workload": "three_level_frontier_bf16", "n_seqs": 16, "segments": sw.n_segments,
