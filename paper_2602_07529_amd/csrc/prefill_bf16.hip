@@ -712,9 +712,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
 #pragma unroll
   for (int r = 0; r < RB; ++r) rmsk[r] = 0;
   auto apply_mask = [&](f32x16* S, int half) __attribute__((always_inline)) {  // masked scores become -inf
-#ifdef DAGATTN_ABL_NOAPPLY  // (development: timing without the mask application; results are wrong)
-    return;
-#endif
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       const uint32_t word = half ? (uint32_t)(rmsk[r] >> 32) : (uint32_t)rmsk[r];
@@ -1098,11 +1095,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // node sees the segment's node (Eq. 3); the causal / length limit is one more AND.  Called
     // when tile n of the row (ring tile tc) has become visible, before its scores are masked.
     auto tile_mask = [&](int n, unsigned ring_tile, uint64_t* rm) __attribute__((always_inline)) {
-#ifdef DAGATTN_ABL_NOTILEMASK  // (development: timing without the mask construction; results are wrong)
-#pragma unroll
-      for (int r = 0; r < RB; ++r) rm[r] = ~0ull;
-      return;
-#endif
       if constexpr (NODES) {
         // a row sees the positions in front of `nstart` and those of its own node up to its own
         auto first_bits = [&](int c) __attribute__((always_inline)) { return c >= 64 ? ~0ull : (c <= 0 ? 0ull : ((1ull << c) - 1)); };
@@ -1389,7 +1381,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
                 }
               }
             }
-#ifndef DAGATTN_ABL_NOLOADS  // (development: timing without the steady state's loads; results are wrong)
             if constexpr (st == 1) {  // load x of the group (K first, then V^T) in slot x NS / LPT of the second half
               static_assert(LPT <= NS, "at most one load per slot");
               static_for<0, LPT>([&](auto xc) __attribute__((always_inline)) {
@@ -1406,16 +1397,11 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
                 }
               });
             }
-#endif
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
 #pragma unroll
               for (int e = j * 16 / NS; e < (j + 1) * 16 / NS; ++e) {
-#ifdef DAGATTN_ABL_NOEXP  // (development: timing without the exponentials; results are wrong)
-                const float pe = Sc[r][e];
-#else
                 const float pe = __builtin_amdgcn_exp2f(Sc[r][e]);
-#endif
                 rs[r] += plast[r];  // (the one before: its result is there, this one's is not yet)
                 plast[r] = pe;
                 asm volatile("" : "+v"(rs[r]));  // keep the running sum
@@ -1704,12 +1690,8 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
                      : "=&v"(x0), "=&v"(x1)
                      : "v"(ord), "n"(16 * OROW)
                      : "memory");
-#ifdef DAGATTN_ABL_NOSTORE  // (development: timing without the output stores; results are missing)
-        asm volatile("" ::"v"(x0), "v"(x1));
-#else
         if (omine[0]) *(u32x4*)(orow[0] + 32 * db) = x0;
         if (omine[1]) *(u32x4*)(orow[1] + 32 * db) = x1;
-#endif
       }
     }
     TSTAMP(t_o);
