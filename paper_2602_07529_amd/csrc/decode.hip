@@ -575,7 +575,7 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 // two units of a tile each leave the others a unit or none.  Four row blocks have a wave each; the waves
 // 4 .. 7 share what is left, one half of every tile each (six) or of every second one (five): 105 -> 99 us.
 // 2 groups of 32 siblings x 5 heads on 8 KV heads, 32 K shared and 640 own tokens (436 MB): 128 us with units in
-// read - wait - multiply phases by ten waves, 93 us so = 4.7 TB/s; the matrix pipes need 17 us of it.
+// read - wait - multiply phases by ten waves, 91 us so = 4.8 TB/s; the matrix pipes need 17 us of it.
 constexpr int WIDE_WAVES = 8;        // of a workgroup: two per SIMD
 constexpr int WIDE_MAX_BLOCKS = 8;   // row blocks of a workgroup
 constexpr int WIDE_TILE_PAGES = 4;
@@ -1599,7 +1599,7 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
       a.wide_own /= 2;
     const unsigned own_wgs = (unsigned)dag_ceil_div(p.items_b, WIDE_WAVES / a.wide_own);
     // Half of the compute units start with own pages: an item keeps the memory idle for its first 6 us (lengths, page ids, pages), which all
-    // of them at once waste and half of them leave to the others (2 x 32 siblings over 32 K: 98 -> 89 us).
+    // of them at once waste and half of them leave to the others (2 x 32 siblings over 32 K: 9 us of 98).
     a.wide_first = (int)own_wgs < n_cu / 2 ? (int)own_wgs : n_cu / 2;
     const int sm = wide_lds_bytes(a.G, head_dim, a.wide_own);
     a.wide_shared = (int)shared_wgs;
