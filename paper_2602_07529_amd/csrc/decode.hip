@@ -55,7 +55,8 @@ struct DecodeArgs {
   int wide_first;    // k_decode_wide: workgroups with own pages that are launched before them
   int wide_own;      // k_decode_wide: waves of a workgroup that share an own item
   float sc;          // softmax_scale * log2(e)
-  float th;          // 8 / sc: how far a score may exceed the reference maximum before it is raised
+  float th;          // how far a score may exceed the reference maximum before it is raised
+  float settle;      // k_decode_wide, shared pages: the sum of a lane's 16 probabilities from which on the reference is looked after
   float scale;
 };
 
@@ -757,7 +758,7 @@ __device__ __forceinline__ void wide_item(const A& a, unsigned char* smem, const
   // Probabilities of S once more, with the reference raised, where they have left the range (what
   // else is under way are scores, which know no reference).
   auto settle = [&](const f32x16& S, bf16x8* P, float& sum) __attribute__((always_inline)) {
-    if (__builtin_amdgcn_ballot_w64(!(sum < 1024.f)) == 0) return;
+    if (__builtin_amdgcn_ballot_w64(!(sum < a.settle)) == 0) return;
     raise(row_max(S));
     sum = probs(S, P);
   };
@@ -1401,6 +1402,7 @@ __global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const
 struct DecodePlan {
   int rb_max, chunk_a, splits_a, chunk_b, splits_b, items_a, items_b;
   bool wide;  // shared items by k_decode_wide (one workgroup per group, kv head and split)
+  float th, settle;  // log2 of how far a score may exceed the reference maximum; DecodeArgs::settle
   size_t off_o_a, off_ml_a, off_o_b, off_ml_b, bytes;
 };
 
@@ -1424,6 +1426,20 @@ const DecodeKnobs& decode_knobs() {
 // Split sizes: slices as long as the batch allows (every work item pays a start-up latency and
 // writes a partial, so fewer and longer items stream better) while still giving the GPU about two
 // waves per SIMD; both even so that a 32-key block never straddles a split.
+//
+// Wide groups, two to WIDE_MAX_BLOCKS row blocks of a KV head.  With little to read the single-wave items take them like any other
+// group, every row block reading the shared pages for itself: a workgroup of k_decode_wide costs 5 us before its first tile.  Pages
+// of 128 dimensions, shared ones once for each row block: up to 256 in a context, 5632 in all, and 6400 of the branches' own (96
+// random shapes, single waves : k_decode_wide below these lines 0.55 to 1.14, 0.87 on average, a step of 2 x 25 branches over 500
+// tokens 17.0 -> 12.6 us; above 5632 shared pages up to 2.5, above 256 in a context 1.04 to 1.25, above 6400 own ones 0.9 to 1.37).
+// What is left takes slices that make a hundred workgroups with shared pages and 256 with own ones, not 256 and 512:
+// each slice leaves 32 rows of sums that the merge reads (a group of 22 branches over 13,072 tokens, four KV heads: 103 slices of 8
+// pages 32.4 us, 26 of 32 pages 20.2; 135 random shapes of both kinds 1.09 times as fast, four of them 3 to 7 % slower).
+// Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
+// slices get longer it follows the maximum: always in single waves, in k_decode_wide when 16 probabilities add up to six (error
+// against 64 bits, 150 shapes, with : without longer slices 0.997 on average, 0.95 to 1.05; at a sum of 1024 as elsewhere 1.02).
+// The workspace keeps the size of the shorter slices: buffers sized by an earlier library stay as good as they were.
+constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES = 6400;
 int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p) {
   if (!d) return DAG_ERR_NULL;
   if (d->n_groups < 0 || d->n_live < 0 || d->max_shared_pages < 0 || d->max_branch_pages < 0 || d->max_group_size < 0)
@@ -1437,33 +1453,55 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
   const int64_t base_a = (int64_t)d->n_groups * hkv * p->rb_max;
   const int64_t base_b = (int64_t)d->n_live * hkv;
   const DecodeKnobs& knobs = decode_knobs();
-  int ca = knobs.chunk_a ? knobs.chunk_a : 128, cb = knobs.chunk_b ? knobs.chunk_b : 64;
-  ca += ca & 1;
-  cb += cb & 1;
   p->wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_BLOCKS;
-  if (p->wide && ca > WIDE_MAX_PAGES) ca = WIDE_MAX_PAGES;
-  if (!knobs.chunk_a) {
-    if (p->wide)  // about one workgroup per compute unit
-      while (ca > 8 && (int64_t)d->n_groups * hkv * dag_ceil_div(d->max_shared_pages, ca) < 256) ca /= 2;
-    else
-      while (ca > 8 && base_a * dag_ceil_div(d->max_shared_pages, ca) < 512) ca /= 2;
+  p->th = 8.f;
+  p->settle = 1024.f;
+  // slices of at least `least` pages, halved until there are `shared` / `own` workgroups or waves
+  auto slices = [&](bool wide, int64_t shared, int least, int64_t own) {
+    int ca = knobs.chunk_a ? knobs.chunk_a : 128, cb = knobs.chunk_b ? knobs.chunk_b : 64;
+    ca += ca & 1;
+    cb += cb & 1;
+    if (p->wide && ca > WIDE_MAX_PAGES) ca = WIDE_MAX_PAGES;
+    const int64_t base = wide ? (int64_t)d->n_groups * hkv : base_a;
+    if (!knobs.chunk_a)
+      while (ca > least && base * dag_ceil_div(d->max_shared_pages, ca) < shared) ca /= 2;
+    if (!knobs.chunk_b)
+      while (cb > 4 && base_b * dag_ceil_div(d->max_branch_pages, cb) < own) cb /= 2;
+    p->splits_a = d->max_shared_pages > 0 ? (int)dag_ceil_div(d->max_shared_pages, ca) : 0;
+    p->splits_b = d->max_branch_pages > 0 ? (int)dag_ceil_div(d->max_branch_pages, cb) : 0;
+    if (wide && !knobs.chunk_a && p->splits_a > 1) {  // slices of one length, unless that is more rounds of workgroups
+      const int same = ((d->max_shared_pages + p->splits_a - 1) / p->splits_a + 1) & ~1;
+      if (dag_ceil_div(base * p->splits_a, 256) * same <= dag_ceil_div(base * (p->splits_a - 1), 256) * ca) ca = same;
+    }
+    p->chunk_a = ca;
+    p->chunk_b = cb;
+    const int64_t ia = base_a * p->splits_a, ib = base_b * p->splits_b;
+    if (ia + ib > INT32_MAX) return DAG_ERR_UNSUPPORTED;
+    p->items_a = (int)ia;
+    p->items_b = (int)ib;
+    size_t off = 0;
+    p->off_o_a = off;  off += dag_align_up((size_t)ia * 32 * D * 4, 256);
+    p->off_ml_a = off; off += dag_align_up((size_t)ia * 32 * 2 * 4, 256);
+    p->off_o_b = off;  off += dag_align_up((size_t)ib * G * D * 4, 256);
+    p->off_ml_b = off; off += dag_align_up((size_t)ib * G * 2 * 4, 256);
+    p->bytes = off + 256;
+    return DAG_OK;
+  };
+  const int rc = slices(p->wide, p->wide ? 256 : 512, 8, p->wide ? 512 : 1024);
+  if (rc != DAG_OK || !p->wide) return rc;
+  const size_t bytes = p->bytes;  // (what follows has at most as many items of either kind)
+  const int shorter_a = p->chunk_a, shorter_b = p->chunk_b;
+  if (d->max_shared_pages <= NARROW_CONTEXT_PAGES && base_a * d->max_shared_pages * D <= NARROW_PAGES * 128 &&
+      base_b * d->max_branch_pages * D <= NARROW_OWN_PAGES * 128) {
+    slices(false, 512, 8, 512);
+    p->wide = false;
+    p->th = 0.f;
+  } else {
+    slices(true, 100, 16, 256);
+    if (p->chunk_a > shorter_a) p->settle = 6.f;
+    if (p->chunk_a > shorter_a || p->chunk_b > shorter_b) p->th = 0.f;
   }
-  if (!knobs.chunk_b)  // (wide: the own items are workgroups of several waves, about two per compute unit)
-    while (cb > 4 && base_b * dag_ceil_div(d->max_branch_pages, cb) < (p->wide ? 512 : 1024)) cb /= 2;
-  p->chunk_a = ca;
-  p->chunk_b = cb;
-  p->splits_a = d->max_shared_pages > 0 ? (int)dag_ceil_div(d->max_shared_pages, ca) : 0;
-  p->splits_b = d->max_branch_pages > 0 ? (int)dag_ceil_div(d->max_branch_pages, cb) : 0;
-  const int64_t ia = base_a * p->splits_a, ib = base_b * p->splits_b;
-  if (ia + ib > INT32_MAX) return DAG_ERR_UNSUPPORTED;
-  p->items_a = (int)ia;
-  p->items_b = (int)ib;
-  size_t off = 0;
-  p->off_o_a = off;  off += dag_align_up((size_t)ia * 32 * D * 4, 256);
-  p->off_ml_a = off; off += dag_align_up((size_t)ia * 32 * 2 * 4, 256);
-  p->off_o_b = off;  off += dag_align_up((size_t)ib * G * D * 4, 256);
-  p->off_ml_b = off; off += dag_align_up((size_t)ib * G * 2 * 4, 256);
-  p->bytes = off + 256;
+  p->bytes = bytes;
   return DAG_OK;
 }
 
@@ -1580,7 +1618,8 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
   a.items_b = p.items_b;
   a.scale = softmax_scale;
   a.sc = softmax_scale * 1.4426950408889634f;
-  a.th = 8.f / a.sc;
+  a.th = p.th / a.sc;
+  a.settle = p.settle;
   hipStream_t stream = (hipStream_t)stream_;
   a.item_base = 0;
   unsigned items = (unsigned)(p.items_a + p.items_b);
