@@ -63,7 +63,9 @@ struct DecodeArgs {
 // Decode over lists of KV segments: a segment is a page list with a token count and the set of
 // live branches that read it; a branch's context is the union of the segments it reads.
 struct SegItem {  // one work item: a slice of a segment's pages against one 32-row block of its readers' rows
-  int32_t page_off, len, e0, nrows, row0, split, pad0, pad1;
+  int32_t page_off, len, e0, nrows, row0;
+  int32_t p0, place;  // first page of the slice; place of its partial of reader e0
+  int32_t nsplit;     // slices of the segment, pages of a slice / 2 in the highest eight bits (unless SegArgs::fixed)
 };
 struct SegArgs {
   const int32_t* seg_page_off;
@@ -78,15 +80,18 @@ struct SegArgs {
   const uint16_t* k_pool;
   const uint16_t* v_pool;
   uint16_t* out;
-  float* part_o;   // [splits][total_readers][hq][D]
-  float* part_ml;  // [splits][total_readers][hq][2]
+  float* part_o;   // [splits * total_readers][hq][D]: the slices of every reader-list entry one after another
+  float* part_ml;  // [splits * total_readers][hq][2]
   SegItem* items;        // [item_cap] compact list of (segment, row block, slice), written by k_seg_plan
-  int32_t* item_total;   // number of list entries
-  int32_t* entry_nsplit; // [total_readers] slices of the segment of each reader-list entry
+  int32_t* totals;       // number of list entries, place behind the last partial, most slices of a segment
+  int32_t* entry_first;  // [total_readers] place of the first partial of each reader-list entry (the next one's: behind its last)
   int item_cap;
   int n_segments, n_live, hq, hkv, G;
   int rb_max;      // 32-row blocks per (segment, kv head)
-  int chunk, splits, total_readers;
+  int chunk, splits, total_readers;  // pages of a slice and slices of a segment that the workspace has room for
+  bool fixed;      // slices of `chunk` pages, whatever there is to read
+  bool few;        // the host's bounds leave less than SEG_PAGES_16 to read
+  float weight;    // of a page: hkv * D / 128
   float sc, th;
 };
 
@@ -101,6 +106,10 @@ __device__ __forceinline__ int key_of_row(int i) {
   const int a = i >> 3, hh = (i >> 2) & 1, c = i & 3;
   return 16 * (a >> 1) + 8 * hh + 4 * (a & 1) + c;
 }
+
+// Single-wave items: log2 of how far a score may exceed the reference maximum.  Probabilities lose less to 16 bits the nearer it is to
+// their maximum: error against 64 bits over 100 shapes 0.95 of that at 8, and the time of the largest steps the same (at 0: 0.93, and 0.2 %).
+constexpr float ITEM_TH = 1.f;
 
 template <int D>
 struct KVBlock {           // one 32-key block (2 pages) in operand layout
@@ -155,9 +164,8 @@ __device__ __forceinline__ void block_scores(const bf16x8 (&kop)[D / 16], QF&& q
 #pragma unroll
   for (int r = 1; r < 16; ++r) bm = fmaxf(bm, S[r]);
   bm = fmaxf(bm, __shfl_xor(bm, 32));
-  // The reference maximum m is raised only when some row of the wave exceeds it by more than 2^8
-  // (in the exponent's units); the rescale of the accumulators is then rare, and probabilities up
-  // to 2^8 are absorbed exactly by fp32 accumulation and the final division.
+  // The reference maximum m is raised only when some row of the wave exceeds it by more than th; the rescale of the accumulators
+  // is then rare, and probabilities above one are absorbed exactly by fp32 accumulation and the final division.
   if (__builtin_amdgcn_ballot_w64(bm > m + th) != 0) {
     const float m_new = fmaxf(m, bm);
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * sc);
@@ -367,43 +375,132 @@ __global__ void __launch_bounds__(64, 2) k_decode(DecodeArgs a) {
 // order and hold wave slots while their loads return).  One workgroup therefore writes the compact
 // list: for every segment, in the caller's order, its slices x row blocks (exclusive scan of the
 // counts), and for every reader-list entry the number of slices its segment has.
+//
+// The list also settles how long slices are.  The host knows the longest segment and takes every other one for as long, so its slices
+// are too long where one segment is; here all lengths are known.  Pages of 128 dimensions to be read (once for every row block) and
+// the slices that were fastest over 36 frontiers of 300 to 140,000 pages: 8 pages below 2,048, 16 below 9,216, 32 below 32,768,
+// 64 below 65,536, then 128 -- if the lists have room for so many, which have the sizes that the host's slices ask for: else twice
+// as long.  5 x 12 leaves under segments of 25 and 174 pages, 24 / 4 heads: 60 -> 38 us.  A segment's slices have one length, an
+// eighth more than that if this saves a slice (16 sequences of 254 to 258 | 2 x 126 to 130 | 8 x 63 to 67 pages: 227 -> 212 us).
 constexpr int PLAN_THREADS = 1024;
+constexpr int SEG_PAGES_16 = 2048, SEG_PAGES_32 = 9216, SEG_PAGES_64 = 32768, SEG_PAGES_128 = 65536;
 __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
-  __shared__ int s_wave[PLAN_THREADS / 64];
-  __shared__ int s_carry;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) s_carry = 0;
-  __syncthreads();
-  for (int base = 0; base < a.n_segments; base += PLAN_THREADS) {
-    const int s = base + tid;
-    int len = 0, e0 = 0, nr = 0, nsp = 0, rbs = 0;
+  __shared__ int s_wave[2][PLAN_THREADS / 64];
+  __shared__ float s_sum[2][2][PLAN_THREADS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, threads = blockDim.x, room = a.splits * a.total_readers;
+  struct Seg {
+    int len, e0, nr, npages, rbs;
+  };
+  auto segment = [&](int s) __attribute__((always_inline)) {
+    Seg g = {0, 0, 0, 0, 0};
     if (s < a.n_segments) {
-      len = max(a.seg_len[s], 0);
-      e0 = a.seg_reader_off[s];
-      nr = max(a.seg_reader_off[s + 1] - e0, 0);
-      const int npages = (len + PAGE - 1) / PAGE;
-      nsp = min((npages + a.chunk - 1) / a.chunk, a.splits);
-      rbs = min((nr * a.G + 31) / 32, a.rb_max);
+      g.len = max(a.seg_len[s], 0);
+      g.e0 = a.seg_reader_off[s];
+      g.nr = max(a.seg_reader_off[s + 1] - g.e0, 0);
+      g.npages = min((g.len + PAGE - 1) / PAGE, a.chunk * a.splits);
+      g.rbs = min((g.nr * a.G + 31) / 32, a.rb_max);
     }
-    const int cnt = nsp * rbs;
-    const int incl = dag_wave_scan(cnt);
-    if (lane == 63) s_wave[w] = incl;
-    __syncthreads();
-    int start = s_carry + incl - cnt;
-    for (int i = 0; i < w; ++i) start += s_wave[i];
+    return g;
+  };
+  const Seg mine = segment(tid);
+  int turn = 0;
+  struct Sums {
+    float x, y;
+  };
+  auto gather = [&](float x, float y, bool top) __attribute__((always_inline)) {  // sums over all threads (exact up to 2^24), of y the maximum if `top`
+    x = dag_wave_sum(x);
+    y = top ? dag_wave_max(y) : dag_wave_sum(y);
+    if (threads > 64) {
+      float(*const all)[PLAN_THREADS / 64] = s_sum[turn & 1];
+      ++turn;
+      if (lane == 0) {
+        all[0][w] = x;
+        all[1][w] = y;
+      }
+      __syncthreads();
+      x = y = 0.f;
+      for (int i = 0; i < threads / 64; ++i) {
+        x += all[0][i];
+        y = top ? fmaxf(y, all[1][i]) : y + all[1][i];
+      }
+    }
+    return Sums{x, y};
+  };
+  // pages of a segment's slices (even: a 32-key block never straddles two), at most c plus an eighth, all of them used
+  auto slice_of = [](int npages, int c) __attribute__((always_inline)) {
+    const int most = c + max(c / 8, 2), n = (npages + most - 1) / most;
+    return n > 0 ? ((npages + n - 1) / n + 1) & ~1 : 1;
+  };
+  auto fits = [](float n, int most) { return n < 16777216.f ? n <= (float)most : n * 1.001f < (float)most; };
+  int chunk = a.chunk, most = a.splits;  // slices of a segment
+  if (a.few) {
+    chunk = 8;
+  } else if (!a.fixed) {
+    float t = (float)mine.rbs * (float)mine.npages, longest = (float)mine.npages;
+    for (int s = tid + threads; s < a.n_segments; s += threads) {
+      const Seg g = segment(s);
+      t += (float)g.rbs * (float)g.npages;
+      longest = fmaxf(longest, (float)g.npages);
+    }
+    const Sums all = gather(t, longest, true);
+    const float pages = all.x * a.weight;
+    int c = pages < SEG_PAGES_16 ? 8 : pages < SEG_PAGES_32 ? 16 : pages < SEG_PAGES_64 ? 32 : pages < SEG_PAGES_128 ? 64 : 128;
+    for (; c < chunk; c *= 2) {
+      float items = 0.f, parts = 0.f;
+      for (int s = tid; s < a.n_segments; s += threads) {
+        const Seg g = s == tid ? mine : segment(s);
+        const int slice = slice_of(g.npages, c);
+        const float nsp = (float)((g.npages + slice - 1) / slice);
+        items += nsp * (float)g.rbs;
+        parts += nsp * (float)g.nr;
+      }
+      const Sums n = gather(items, parts, false);
+      if (fits(n.x, a.item_cap) && fits(n.y, room)) break;
+    }
+    chunk = c;
+    most = ((int)all.y + chunk - 1) / chunk;  // (at least; a segment of more than 2^24 pages is longer than any pool)
+  }
+  int start0 = 0, first0 = 0;  // items and partials of the segments in front
+  for (int base = 0; base < a.n_segments; base += threads) {
+    const int s = base + tid;
+    const Seg g = base == 0 ? mine : segment(s);
+    const int slice = a.fixed ? chunk : slice_of(g.npages, chunk);
+    const int nsp = (g.npages + slice - 1) / slice, cnt = nsp * g.rbs, parts = nsp * g.nr;
+    const int incl = dag_wave_scan(cnt), pincl = dag_wave_scan(parts);
+    int start = start0 + incl - cnt, first = first0 + pincl - parts;
+    if (threads > 64) {
+      if (lane == 63) {
+        s_wave[0][w] = incl;
+        s_wave[1][w] = pincl;
+      }
+      __syncthreads();
+      for (int i = 0; i < threads / 64; ++i) {
+        start += i < w ? s_wave[0][i] : 0;
+        first += i < w ? s_wave[1][i] : 0;
+        start0 += s_wave[0][i];
+        first0 += s_wave[1][i];
+      }
+      if (base + threads < a.n_segments) __syncthreads();
+    } else {
+      start0 += __builtin_amdgcn_readlane(incl, 63);
+      first0 += __builtin_amdgcn_readlane(pincl, 63);
+    }
     if (s < a.n_segments) {
       int k = start;
+      const int page_off = a.seg_page_off[s], code = a.fixed ? nsp : nsp | slice << 23;
       for (int sp = nsp - 1; sp >= 0; --sp)
-        for (int rb = 0; rb < rbs; ++rb, ++k)
-          if (k < a.item_cap) a.items[k] = SegItem{a.seg_page_off[s], len, e0, nr * a.G, rb * 32, sp, 0, 0};
-      for (int e = e0; e < e0 + nr; ++e)
-        if (e >= 0 && e < a.total_readers) a.entry_nsplit[e] = nsp;
+        for (int rb = 0; rb < g.rbs; ++rb, ++k)
+          if (k < a.item_cap) a.items[k] = SegItem{page_off, g.len, g.e0, g.nr * a.G, rb * 32, sp * slice, first + sp, code};
+      for (int e = 0; e < g.nr; ++e) {
+        if (g.e0 + e >= 0 && g.e0 + e < a.total_readers) a.entry_first[g.e0 + e] = first + e * nsp;
+        if (g.e0 + e == a.total_readers - 1) a.totals[1] = first + (e + 1) * nsp;
+      }
     }
-    __syncthreads();
-    if (tid == PLAN_THREADS - 1) s_carry = min(start + cnt, a.item_cap);
-    __syncthreads();
   }
-  if (tid == 0) *a.item_total = s_carry;
+  if (tid == 0) {
+    a.totals[0] = min(start0, a.item_cap);
+    a.totals[2] = most;
+  }
 }
 
 // Step 2: one wave per (work item, kv head).  Row j * G + g of a segment is query head hk * G + g
@@ -415,19 +512,20 @@ __global__ void __launch_bounds__(64, 2) k_decode_seg(SegArgs a) {
   __shared__ bf16x8 qs_all[(D / 16) * 64];
   const int lane = threadIdx.x, L = lane & 31, H = lane >> 5;
   const int hk = blockIdx.x % a.hkv, idx = blockIdx.x / a.hkv;
-  if (idx >= *a.item_total) return;
+  if (idx >= a.totals[0]) return;
   const SegItem it = a.items[idx];
-  const int len = it.len, e0 = it.e0, nrows = it.nrows, row0 = it.row0, split = it.split;
-  const int npages = (len + PAGE - 1) / PAGE;
-  const int p0 = split * a.chunk;
-  int p1 = min(p0 + a.chunk, npages);
+  const int len = it.len, e0 = it.e0, nrows = it.nrows, row0 = it.row0;
+  const int npages = min((len + PAGE - 1) / PAGE, a.chunk * a.splits), p0 = it.p0;
+  const int slice = a.fixed ? a.chunk : (it.nsplit >> 23) & 0x1fe, nsplit = a.fixed ? it.nsplit : it.nsplit & 0xffffff;
+  int p1 = __builtin_amdgcn_readfirstlane(min(p0 + slice, npages));
   if (row0 >= nrows || p0 >= p1) return;  // (never listed)
   const int row = row0 + L;
   const bool row_ok = row < nrows;
   const int rr = row_ok ? row : row0;
   const int entry = e0 + rr / a.G, head = hk * a.G + rr % a.G;
-  const bool store_ok = row_ok && entry < a.total_readers;  // (a reader list longer than announced: no partial)
-  const size_t pbase = ((size_t)split * a.total_readers + entry) * a.hq + head;
+  const int place = it.place + rr / a.G * nsplit;
+  const bool store_ok = row_ok && entry < a.total_readers && place < a.splits * a.total_readers;  // (reader lists longer than announced: no partial)
+  const size_t pbase = (size_t)place * a.hq + head;
   // per-reader visible prefix of the segment (a token of a node being prefilled sees the node's
   // tokens up to itself): the slice ends at the longest prefix of the wave's rows
   int lim = len, lim_min = len;
@@ -495,15 +593,21 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
   float mx = -1e30f, lsum = 0.f;
   const int e0 = a.branch_entry_off[r];
-  const int npairs = (a.branch_entry_off[r + 1] - e0) * a.splits;
+  const int splits = a.splits > 0 ? a.totals[2] : 0;
+  const int npairs = (a.branch_entry_off[r + 1] - e0) * splits;
   for (int b = 0; b < npairs; b += 64) {
     const int i = b + lane;
     float ms = -1e30f, ls = 0.f;
     uint32_t base = 0;
     if (i < npairs) {
-      const int entry = a.branch_entries[e0 + i / a.splits];
-      if (entry >= 0 && entry < a.total_readers && i % a.splits < a.entry_nsplit[entry]) {
-        base = (uint32_t)(((size_t)(i % a.splits) * a.total_readers + entry) * a.hq + head);
+      const int entry = a.branch_entries[e0 + i / splits];
+      int place = -1, behind = -1;  // of this partial, of the entry's last one
+      if (entry >= 0 && entry < a.total_readers) {
+        place = a.entry_first[entry] + i % splits;
+        behind = entry + 1 < a.total_readers ? a.entry_first[entry + 1] : a.totals[1];
+      }
+      if (place >= 0 && place < min(behind, a.splits * a.total_readers)) {
+        base = (uint32_t)((size_t)place * a.hq + head);
         const float2 ml = *(const float2*)(a.part_ml + (size_t)base * 2);
         if (ml.y > 0.f) {
           ms = ml.x;
@@ -1454,10 +1558,12 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
   const int64_t base_b = (int64_t)d->n_live * hkv;
   const DecodeKnobs& knobs = decode_knobs();
   p->wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_BLOCKS;
-  p->th = 8.f;
+  p->th = p->wide ? 8.f : ITEM_TH;
   p->settle = 1024.f;
-  // slices of at least `least` pages, halved until there are `shared` / `own` workgroups or waves
-  auto slices = [&](bool wide, int64_t shared, int least, int64_t own) {
+  // Slices of at least `least` pages, halved until there are `shared` / `own` workgroups or waves.  An eighth more than that
+  // (`longer`; two pages at least) where it saves a slice: a context of 65 pages was one of 64 and one of a page, which is a partial as
+  // large as any (60 random steps 1.02 times as fast, one sequence of 509 shared and 43 own pages 17.2 -> 15.4 us).
+  auto slices = [&](bool wide, int64_t shared, int least, int64_t own, bool longer) {
     int ca = knobs.chunk_a ? knobs.chunk_a : 128, cb = knobs.chunk_b ? knobs.chunk_b : 64;
     ca += ca & 1;
     cb += cb & 1;
@@ -1467,6 +1573,12 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
       while (ca > least && base * dag_ceil_div(d->max_shared_pages, ca) < shared) ca /= 2;
     if (!knobs.chunk_b)
       while (cb > 4 && base_b * dag_ceil_div(d->max_branch_pages, cb) < own) cb /= 2;
+    auto stretch = [&](int pages, int c, int most) {
+      const int more = c + (c / 8 > 2 ? c / 8 : 2), longest = more < most ? more : most, n = (int)dag_ceil_div(pages, longest);
+      return n > 0 && n < dag_ceil_div(pages, c) ? ((pages + n - 1) / n + 1) & ~1 : c;
+    };
+    if (longer && !knobs.chunk_a) ca = stretch(d->max_shared_pages, ca, p->wide ? WIDE_MAX_PAGES : INT32_MAX);
+    if (longer && !knobs.chunk_b) cb = stretch(d->max_branch_pages, cb, INT32_MAX);
     p->splits_a = d->max_shared_pages > 0 ? (int)dag_ceil_div(d->max_shared_pages, ca) : 0;
     p->splits_b = d->max_branch_pages > 0 ? (int)dag_ceil_div(d->max_branch_pages, cb) : 0;
     if (wide && !knobs.chunk_a && p->splits_a > 1) {  // slices of one length, unless that is more rounds of workgroups
@@ -1487,17 +1599,19 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
     p->bytes = off + 256;
     return DAG_OK;
   };
-  const int rc = slices(p->wide, p->wide ? 256 : 512, 8, p->wide ? 512 : 1024);
-  if (rc != DAG_OK || !p->wide) return rc;
+  const int rc = slices(p->wide, p->wide ? 256 : 512, 8, p->wide ? 512 : 1024, false);
+  if (rc != DAG_OK) return rc;
   const size_t bytes = p->bytes;  // (what follows has at most as many items of either kind)
   const int shorter_a = p->chunk_a, shorter_b = p->chunk_b;
-  if (d->max_shared_pages <= NARROW_CONTEXT_PAGES && base_a * d->max_shared_pages * D <= NARROW_PAGES * 128 &&
+  if (!p->wide) {
+    slices(false, 512, 8, 1024, true);
+  } else if (d->max_shared_pages <= NARROW_CONTEXT_PAGES && base_a * d->max_shared_pages * D <= NARROW_PAGES * 128 &&
       base_b * d->max_branch_pages * D <= NARROW_OWN_PAGES * 128) {
-    slices(false, 512, 8, 512);
+    slices(false, 512, 8, 512, true);
     p->wide = false;
     p->th = 0.f;
   } else {
-    slices(true, 100, 16, 256);
+    slices(true, 100, 16, 256, true);
     if (p->chunk_a > shorter_a) p->settle = 6.f;
     if (p->chunk_a > shorter_a || p->chunk_b > shorter_b) p->th = 0.f;
   }
@@ -1687,7 +1801,7 @@ namespace {
 struct SegPlan {
   int rb_max, chunk, splits;
   long items;  // bound on the work items (per kv head)
-  size_t off_o, off_ml, off_items, off_total, off_nsplit, bytes;
+  size_t off_o, off_ml, off_items, off_total, off_first, bytes;
 };
 
 // One split size for all segments (their lengths live in device memory): as long as possible
@@ -1720,7 +1834,7 @@ int make_seg_plan(const dag_decode_seg_desc_t* d, int hq, int hkv, int D, SegPla
   p->off_ml = off; off += dag_align_up(rows * 2 * 4, 256);
   p->off_items = off;  off += dag_align_up((size_t)items * sizeof(SegItem), 256);
   p->off_total = off;  off += 256;
-  p->off_nsplit = off; off += dag_align_up((size_t)d->total_readers * 4, 256);
+  p->off_first = off; off += dag_align_up((size_t)d->total_readers * 4, 256);
   p->bytes = off + 256;
   return DAG_OK;
 }
@@ -1765,8 +1879,8 @@ extern "C" int dag_attn_decode_segments(const dag_decode_seg_desc_t* d, const vo
   a.part_o = (float*)(base + p.off_o);
   a.part_ml = (float*)(base + p.off_ml);
   a.items = (SegItem*)(base + p.off_items);
-  a.item_total = (int32_t*)(base + p.off_total);
-  a.entry_nsplit = (int32_t*)(base + p.off_nsplit);
+  a.totals = (int32_t*)(base + p.off_total);
+  a.entry_first = (int32_t*)(base + p.off_first);
   a.item_cap = (int)p.items;
   a.n_segments = d->n_segments;
   a.n_live = d->n_live;
@@ -1777,11 +1891,15 @@ extern "C" int dag_attn_decode_segments(const dag_decode_seg_desc_t* d, const vo
   a.chunk = p.chunk;
   a.splits = p.splits;
   a.total_readers = d->total_readers;
+  a.fixed = decode_knobs().chunk_seg > 0;
+  a.weight = (float)hkv * (float)head_dim / 128.f;
+  a.few = !a.fixed && p.chunk == 8 && (int64_t)d->n_segments * p.rb_max * d->max_seg_pages * hkv * head_dim < SEG_PAGES_16 * 128;
   a.sc = softmax_scale * 1.4426950408889634f;
-  a.th = 8.f / a.sc;
+  a.th = ITEM_TH / a.sc;
   hipStream_t stream = (hipStream_t)stream_;
   if (p.items > 0) {
-    hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(PLAN_THREADS), 0, stream, a);
+    const int64_t waves = dag_ceil_div(d->n_segments, 64);
+    hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3((unsigned)(waves * 64 < PLAN_THREADS ? waves * 64 : PLAN_THREADS)), 0, stream, a);
     DAG_LAUNCH_CHECK();
     const unsigned grid = (unsigned)(p.items * hkv);
     if (head_dim == 128) hipLaunchKernelGGL(k_decode_seg<128>, dim3(grid), dim3(64), 0, stream, a);

@@ -65,3 +65,29 @@ def test_wide_groups_in_every_kind_of_slice(groups, nb, group, hkv, shared, own,
     ref = orc.attn_decode(st["desc"], dags.to_f64(st["q"]), dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"]), branches=rows)
     check_close(out[rows], ref[rows], torch.bfloat16, "%d groups x %d branches x %d heads" % (groups, nb, group))
     assert torch.isfinite(out.float()).all()
+
+
+# Leaves under segments of several lengths: the slices that the pages to be read call for (8 pages up to 128, for these shapes by name),
+# segments whose last pages join a slice (65 of 64 pages, 130 of 128), which do not (73, 145), of one page and of one token.
+@pytest.mark.gpu
+@pytest.mark.parametrize("hkv,group,d,sizes,leaves", [
+    (1, 4, 128, [16 * 10, 16 * 11, 1], [3, 40]),                                # 8 pages: 10 in one slice, 11 in two
+    (2, 3, 64, [16 * 18, 16 * 19, 300, 16 * 73 - 7], [17, 700, 33]),            # 8
+    (2, 5, 128, [16 * 300, 16 * 73, 16 * 37, 5], [16 * 18, 16 * 20 + 1, 600]),  # 16
+    (8, 4, 128, [16 * 200, 16 * 36 - 3, 16 * 40], [100] * 9),                   # 32: two row blocks
+    (8, 8, 128, [16 * 258, 16 * 130 - 5, 16 * 65], [16 * 66, 1] * 6),           # 64: three row blocks
+    (8, 8, 128, [16 * 145, 16 * 130, 16 * 258], [16 * 145, 16 * 65 + 3] * 12),  # 128: six
+])
+def test_frontiers_in_slices_of_every_length(hkv, group, d, sizes, leaves):
+    n, m = len(sizes), len(leaves)
+    parents = [[i - 1] if i else [] for i in range(n)] + [[i % n] for i in range(m)]  # a chain with leaves at every node of it
+    dag = (np.asarray(sizes + leaves, dtype=np.int32), dags.bits_from_sets(dags.closure_from_parents(parents)))
+    hq = hkv * group
+    st = dags.decode_segments_state(m + d + group, [dag], [list(range(n, n + m))], hq, hkv, d, keep_tokens=False)
+    sd = B.SegDecodeDesc(st["desc"], DEV)
+    out = torch.full_like(st["q"], float("nan"), device=DEV)
+    ws = torch.empty(B.dag_decode_segments_workspace_bytes(sd, hq, hkv, d), dtype=torch.uint8, device=DEV).fill_(0xff)
+    B.dag_attn_decode_segments(sd, st["q"].to(DEV), st["k_pool"].to(DEV), st["v_pool"].to(DEV), out, ws)
+    torch.cuda.synchronize()
+    ref = orc.attn_decode_segments(st["desc"], dags.to_f64(st["q"]), dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"]))
+    check_close(out, ref, torch.bfloat16, "frontier of %d leaves" % m)
