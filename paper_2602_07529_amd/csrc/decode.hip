@@ -8,7 +8,7 @@
 //                   a slice of the shared pages -- each shared page is fetched once per group;
 //     own items     (branch, kv head, page split): the branch's query heads against its own pages.
 //   Every item writes an un-normalised partial (o, m, l); a second launch merges the partials of
-//   each (branch, head) by log-sum-exp.
+//   each (branch, head) by log-sum-exp.  Steps over short contexts are one launch of k_whole_branch.
 //
 // Pool formats (bf16, 16 tokens per page) are chosen so that global loads land directly in MFMA
 // operand layout, fully coalesced, with no LDS staging:
@@ -1235,13 +1235,7 @@ __global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a
 constexpr int64_t MERGE_FEW_ROWS = 4096;
 constexpr int merge_per(int D, bool few) { return few ? 4 : D / 64; }
 constexpr int merge_threads(bool few) { return few ? 256 : 64; }
-template <int D, bool FEW>
-__global__ void __launch_bounds__(merge_threads(FEW)) k_decode_merge(DecodeArgs a) {
-  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (merge_threads(FEW) / 64) + (threadIdx.x >> 6));
-  const int r = wid / a.hq, head = wid % a.hq;
-  if (r >= a.n_live) return;
-  const int hk = head / a.G, j = head % a.G;
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ int group_of_branch(const DecodeArgs& a, int r, int lane) {
   int g = 0;  // the last group that starts at or before r, one of the n from g on
   for (int n = a.n_groups; n > 1;) {
     const int step = (n + 63) / 64, at = min(lane * step, n - 1);
@@ -1249,6 +1243,16 @@ __global__ void __launch_bounds__(merge_threads(FEW)) k_decode_merge(DecodeArgs 
     g += max(before, 0) * step;
     n = min(step, n - max(before, 0) * step);
   }
+  return g;
+}
+template <int D, bool FEW>
+__global__ void __launch_bounds__(merge_threads(FEW)) k_decode_merge(DecodeArgs a) {
+  const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * (merge_threads(FEW) / 64) + (threadIdx.x >> 6));
+  const int r = wid / a.hq, head = wid % a.hq;
+  if (r >= a.n_live) return;
+  const int hk = head / a.G, j = head % a.G;
+  const int lane = threadIdx.x & 63;
+  const int g = group_of_branch(a, r, lane);
   const int row = (r - a.group_branch_off[g]) * a.G + j;
   const int rb = row >> 5, rr = row & 31;
   const size_t ia0 = (((size_t)g * a.hkv + hk) * a.rb_max + rb) * a.splits_a;
@@ -1333,6 +1337,73 @@ __global__ void __launch_bounds__(merge_threads(FEW)) k_decode_merge(DecodeArgs 
   if constexpr (PER == 4) *(u32x2*)o = u32x2{dag_pack_bf2(acc[0] * inv, acc[1] * inv), dag_pack_bf2(acc[2] * inv, acc[3] * inv)};
   else if constexpr (PER == 2) *(uint32_t*)o = dag_pack_bf2(acc[0] * inv, acc[1] * inv);
   else *o = (uint16_t)dag_f2bf(acc[0] * inv);
+}
+
+// Short contexts: a workgroup takes a (branch, KV head) whole, a wave a slice of the shared or of the own pages, and puts the
+// partials together in LDS: no partials in memory and no launch for the merge, which is what these steps consist of (13.0 -> 10.6 us).
+// Every branch reads the shared pages for itself.  Eight waves, two a SIMD, because a slice's two blocks take the registers of that.
+constexpr int WHOLE_WAVES = 8, WHOLE_ROWS = 8;
+// Up to these pages in a context (a wave walks its slice alone, 1 us a block) and workgroups (one a compute unit: two take turns);
+// 88 random steps with up to 8 rows a branch: inside 1.02 to 1.40 times as fast as items and merge; above 64 pages of dimension 128
+// 0.99 to 1.16, above 110 0.66 to 0.92, between 257 and 360 workgroups 0.82 to 0.98, above that 0.68 to 1.25.
+constexpr int WHOLE_PAGES_128 = 64, WHOLE_PAGES_64 = 96, WHOLE_GROUPS = 256;
+template <int D>
+__global__ void __launch_bounds__(64 * WHOLE_WAVES, 2) k_whole_branch(DecodeArgs a) {
+  __shared__ bf16x8 qs_all[(D / 16) * 64];
+  __shared__ __align__(16) float part[WHOLE_WAVES][WHOLE_ROWS][D + 4];
+  __shared__ float part_ml[WHOLE_WAVES][WHOLE_ROWS][2];
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, L = lane & 31, H = lane >> 5;
+  const int r = blockIdx.x / a.hkv, hk = blockIdx.x % a.hkv;
+  if (w < D / 16) qs_all[w * 64 + lane] = *(const bf16x8*)(a.q + ((size_t)r * a.hq + hk * a.G + min(L, a.G - 1)) * D + 8 * H + 16 * w);
+  const int g = group_of_branch(a, r, lane);
+  const int len_a = a.splits_a > 0 ? a.shared_len[g] : 0, len_b = a.splits_b > 0 ? a.branch_len[r] : 0;
+  const int n_a = min((len_a + PAGE - 1) / PAGE, a.splits_a * a.chunk_a), n_b = min((len_b + PAGE - 1) / PAGE, a.splits_b * a.chunk_b);
+  const int blocks_a = (n_a + 1) / 2, blocks_b = (n_b + 1) / 2, blocks = blocks_a + blocks_b;
+  const int waves_a = blocks_b <= 0 ? WHOLE_WAVES : blocks_a <= 0 ? 0 : min(max((blocks_a * WHOLE_WAVES + blocks / 2) / blocks, 1), WHOLE_WAVES - 1);
+  const bool is_a = w < waves_a;
+  const int n = is_a ? n_a : n_b, ways = is_a ? waves_a : WHOLE_WAVES - waves_a, len = is_a ? len_a : len_b;
+  const int per = 2 * (((n + 1) / 2 + ways - 1) / ways), p0 = (is_a ? w : w - waves_a) * per, p1 = min(p0 + per, n);
+  __syncthreads();
+  if (p0 < p1) {
+    const int32_t* pages = is_a ? a.shared_pages + a.shared_page_off[g] : a.branch_pages + a.branch_page_off[r];
+    const bf16x8* qf = qs_all + lane;
+    auto qop = [&](int s) { return qf[s * 64]; };
+    f32x16 O[D / 32];
+    float m, l;
+    stream_slice<D>(a, pages, p0, p1, len, len, len, hk, lane, qop, O, m, l);
+    const float l_tot = l + __shfl_xor(l, 32);
+    if (L < a.G) {
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          *(f32x4*)&part[w][L][32 * db + 8 * r4 + 4 * H] = f32x4{O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
+      if (H == 0) {
+        part_ml[w][L][0] = m;
+        part_ml[w][L][1] = l_tot;
+      }
+    }
+  } else if (lane < a.G) {
+    part_ml[w][lane][0] = -1e30f;
+    part_ml[w][lane][1] = 0.f;
+  }
+  __syncthreads();
+  const int j = tid / (D / 4), c = tid % (D / 4) * 4;
+  if (j >= a.G) return;
+  float mx = -1e30f, lsum = 0.f;
+#pragma unroll
+  for (int p = 0; p < WHOLE_WAVES; ++p) mx = fmaxf(mx, part_ml[p][j][0]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < WHOLE_WAVES; ++p) {
+    const float lp = part_ml[p][j][1], wgt = lp > 0.f ? __builtin_amdgcn_exp2f((part_ml[p][j][0] - mx) * a.sc) : 0.f;
+    const f32x4 o = *(const f32x4*)&part[p][j][c];
+    lsum += lp > 0.f ? lp * wgt : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += wgt != 0.f ? wgt * o[e] : 0.f;
+  }
+  const float inv = 1.f / lsum;
+  *(u32x2*)(a.out + ((size_t)r * a.hq + hk * a.G + j) * D + c) = u32x2{dag_pack_bf2(acc[0] * inv, acc[1] * inv), dag_pack_bf2(acc[2] * inv, acc[3] * inv)};
 }
 
 // One block per live branch: rotate the new key at the branch's adaptive position and scatter
@@ -1506,6 +1577,7 @@ __global__ void __launch_bounds__(kRunThreads) k_kv_append_run(int n_live, const
 struct DecodePlan {
   int rb_max, chunk_a, splits_a, chunk_b, splits_b, items_a, items_b;
   bool wide;  // shared items by k_decode_wide (one workgroup per group, kv head and split)
+  bool whole;  // no items: k_whole_branch
   float th, settle;  // log2 of how far a score may exceed the reference maximum; DecodeArgs::settle
   size_t off_o_a, off_ml_a, off_o_b, off_ml_b, bytes;
 };
@@ -1616,6 +1688,9 @@ int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, DecodePlan* p)
     if (p->chunk_a > shorter_a || p->chunk_b > shorter_b) p->th = 0.f;
   }
   p->bytes = bytes;
+  p->whole = G <= WHOLE_ROWS && !knobs.chunk_a && !knobs.chunk_b && base_b <= WHOLE_GROUPS &&
+             (int64_t)d->max_shared_pages + d->max_branch_pages <= (D == 128 ? WHOLE_PAGES_128 : WHOLE_PAGES_64);
+  if (p->whole) p->th = 0.f;
   return DAG_OK;
 }
 
@@ -1736,6 +1811,12 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
   a.settle = p.settle;
   hipStream_t stream = (hipStream_t)stream_;
   a.item_base = 0;
+  if (p.whole) {
+    if (head_dim == 128) hipLaunchKernelGGL(k_whole_branch<128>, dim3((unsigned)(d->n_live * hkv)), dim3(64 * WHOLE_WAVES), 0, stream, a);
+    else hipLaunchKernelGGL(k_whole_branch<64>, dim3((unsigned)(d->n_live * hkv)), dim3(64 * WHOLE_WAVES), 0, stream, a);
+    DAG_LAUNCH_CHECK();
+    return DAG_OK;
+  }
   unsigned items = (unsigned)(p.items_a + p.items_b);
   if (p.wide && p.items_a > 0) {
     // Wide sibling groups: one launch of workgroups with own items, of those that stream a slice of the shared pages
