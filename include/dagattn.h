@@ -259,7 +259,7 @@ size_t dag_decode_workspace_bytes(const dag_decode_desc_t* desc, int32_t hq, int
  * (section 4.3 Fork), own pages once per branch, and the partial results are combined by
  * log-sum-exp.  q/out [n_live][hq][head_dim] bf16 DEVICE, q already rotated.  head_dim 128 or
  * 64, page_size 16, hq a multiple of hkv with hq/hkv <= 32.
- * Everything is enqueued on `stream` (two launches: the partial results, their combination);
+ * Everything is enqueued on `stream` (two launches: the partial results, their combination; one for short contexts);
  * the call allocates nothing and does not synchronise. */
 int dag_attn_decode(const dag_decode_desc_t* desc, const void* q, const void* k_pool,
                     const void* v_pool, void* out, int32_t hq, int32_t hkv, int32_t head_dim,
