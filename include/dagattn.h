@@ -304,7 +304,7 @@ typedef struct {
   int32_t n_live, n_segments, page_size;
   int32_t max_seg_pages;  /* HOST upper bound on pages of any segment                            */
   int32_t max_readers;    /* HOST upper bound on readers of any segment                          */
-  int32_t total_readers;  /* HOST: seg_reader_off[n_segments] (= branch_entry_off[n_live])       */
+  int32_t total_readers;  /* HOST upper bound on seg_reader_off[n_segments] (= branch_entry_off[n_live]) */
   const int32_t* seg_page_off;   /* [n_segments+1] into seg_pages                               */
   const int32_t* seg_pages;      /* page ids of each segment, in token order                    */
   const int32_t* seg_len;        /* [n_segments] tokens in the segment (0 allowed)              */

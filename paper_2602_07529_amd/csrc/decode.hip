@@ -495,6 +495,8 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
         if (g.e0 + e >= 0 && g.e0 + e < a.total_readers) a.entry_first[g.e0 + e] = first + e * nsp;
         if (g.e0 + e == a.total_readers - 1) a.totals[1] = first + (e + 1) * nsp;
       }
+      const int end = g.e0 + g.nr;  // (fewer entries listed than announced: the last one's partials end here all the same)
+      if (s + 1 == a.n_segments && end >= 0 && end < a.total_readers) a.entry_first[end] = first + parts;
     }
   }
   if (tid == 0) {

@@ -174,3 +174,22 @@ def test_incremental_prefill_in_slices_equals_the_prefill_kernel(monkeypatch):
     q_tok, k_tok, v_tok = st["tokens"][0]
     o_pre, _, _, _, _ = run_prefill([dag], q_tok, k_tok, v_tok, 1e4, rope=False)
     assert (out.float().cpu() - o_pre.float().cpu()[1000:]).abs().max().item() < 4e-2
+
+
+@pytest.mark.parametrize("spare", [1, 70])
+@pytest.mark.parametrize("fill", [0x00, 0x7f, 0xff])
+def test_more_readers_announced_than_listed(spare, fill):
+    """total_readers as an upper bound (a captured step replayed with fewer readers): the partials of the last listed entry end
+    where they do with the exact count, whatever the workspace holds behind it, and no other partial is read."""
+    hq, hkv, d = 8, 2, 128
+    st = dags.decode_segments_state(311, [_multilevel(40), _multilevel(1)], [[8, 6, 7, 4], [3, 5]], hq, hkv, d, kv_scale=0.7, q_scale=0.7)
+    exact = _gpu_decode_segments(st["desc"], st["q"], st["k_pool"], st["v_pool"], hq, hkv, d)
+    sd = B.SegDecodeDesc(st["desc"], DEV)
+    sd.c.total_readers += spare
+    ws = torch.full((B.dag_decode_segments_workspace_bytes(sd, hq, hkv, d),), fill, dtype=torch.uint8, device=DEV)
+    out = torch.full_like(st["q"], float("nan"), device=DEV)
+    B.dag_attn_decode_segments(sd, st["q"].to(DEV), st["k_pool"].to(DEV), st["v_pool"].to(DEV), out, ws)
+    torch.cuda.synchronize()
+    ref = orc.attn_decode_segments(st["desc"], dags.to_f64(st["q"]), dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"]))
+    check_close(out, ref, torch.bfloat16, "%d readers announced too many" % spare)
+    assert torch.equal(out, exact)
