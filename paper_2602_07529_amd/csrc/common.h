@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "dagattn.h"
+#include "sizes.h"
 
 #define DAG_HIP_CHECK(expr)                    \
   do {                                         \
@@ -18,8 +19,6 @@
   } while (0)
 
 static inline bool dag_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-static inline int64_t dag_ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-static inline size_t dag_align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
