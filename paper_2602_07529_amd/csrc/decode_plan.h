@@ -45,8 +45,8 @@ struct DecodePlan {
 // each slice leaves 32 rows of sums that the merge reads (a group of 22 branches over 13,072 tokens, four KV heads: 103 slices of 8
 // pages 32.4 us, 26 of 32 pages 20.2; 135 random shapes of both kinds 1.09 times as fast, four of them 3 to 7 % slower).
 // Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
-// slices get longer it follows the maximum: always in single waves, in k_decode_wide when 16 probabilities add up to six (error
-// against 64 bits, 150 shapes, with : without longer slices 0.997 on average, 0.95 to 1.05; at a sum of 1024 as elsewhere 1.02).
+// slices get longer it follows the maximum: always in single waves, in k_decode_wide when the sum of 16 probabilities grows by 2.5
+// (error against 64 bits, 110 shapes, with : without longer slices 0.997 on average, 0.95 to 1.05; by 4 1.006, by 1024 as elsewhere 1.017).
 // The workspace keeps the size of the shorter slices: buffers sized by an earlier library stay as good as they were.
 constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES = 6400;
 inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const DecodeKnobs& knobs, DecodePlan* p) {
@@ -116,7 +116,8 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     p->th = 0.f;
   } else {
     slices(true, 100, 16, 256, true);
-    if (p->chunk_a > shorter_a) p->settle = 6.f;
+    auto length = [](int pages, int c) { return pages < c ? pages : c; };
+    if (length(d->max_shared_pages, p->chunk_a) > length(d->max_shared_pages, shorter_a)) p->settle = 2.5f;
     if (p->chunk_a > shorter_a || p->chunk_b > shorter_b) p->th = 0.f;
   }
   p->bytes = bytes;

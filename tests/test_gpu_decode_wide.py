@@ -7,6 +7,7 @@ import torch
 from oracle import dag_oracle as orc
 from paper_2602_07529_amd import binding as B
 from workloads import dags
+from tests import decode_rules
 from tests.gpu_util import DEV, check_close
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +76,35 @@ def test_probabilities_are_rounded_near_the_maximum(groups, nb, shared, own, hq,
             err += (out[r, rows].cpu().double() - exact).square().sum().item()
             err_ref += (bf16(bf16(p) @ v / total) - exact).square().sum().item()
     assert err < most ** 2 * err_ref, "%.4f of the error with the row's maximum" % (err / err_ref) ** 0.5
+
+
+@pytest.mark.parametrize("groups,nb,shared,hq,hkv,d", [(2, 32, 16000, 16, 4, 64), (1, 12, 30000, 24, 8, 128)])
+def test_equal_scores_take_no_longer(groups, nb, shared, hq, hkv, d):
+    """Keys of zeros make every score equal: no probability leaves the reference.  Against keys that are largest in the first eight
+    pages of every slice, where the reference comes from, so that every other probability is next to nothing: the same launch,
+    the same time (of the two runs of one kind, the shortest of twelve, differ by less than 2 %)."""
+    st = dags.decode_state(5, groups, nb, shared, 1, hq, hkv, d, branch_len_list=[1] * (groups * nb))
+    plan = decode_rules.decode(B.DecodeDesc(st["desc"], DEV).c, hq, hkv, d)
+    assert plan.route == "wide" and plan.settle < 1024   # slices longer than the workspace is sized for
+    q, dd = torch.ones_like(st["q"], device=DEV), B.DecodeDesc(st["desc"], DEV)
+    out, vp = torch.empty_like(q), st["v_pool"].to(DEV)
+    equal = torch.zeros_like(st["k_pool"], device=DEV)
+    first = equal.clone()
+    for g in range(groups):
+        pages = st["desc"]["shared_pages"][st["desc"]["shared_page_off"][g]:st["desc"]["shared_page_off"][g + 1]]
+        lead = np.concatenate([pages[i:i + 8] for i in range(0, len(pages), plan.chunk_a)])
+        first[torch.from_numpy(lead).long().to(DEV)] = 2.0
+    ws = torch.empty(B.dag_decode_workspace_bytes(dd, hq, hkv, d), dtype=torch.uint8, device=DEV)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = [float("inf")] * 2
+    for turn in range(24):
+        kp = (equal, first)[turn % 2]
+        for _ in range(3):
+            B.dag_attn_decode(dd, q, kp, vp, out, ws)
+        a.record()
+        for _ in range(30):
+            B.dag_attn_decode(dd, q, kp, vp, out, ws)
+        b.record()
+        torch.cuda.synchronize()
+        best[turn % 2] = min(best[turn % 2], a.elapsed_time(b) / 30)
+    assert best[0] < 1.1 * best[1], "%.1f us with equal scores, %.1f us without" % (best[0] * 1e3, best[1] * 1e3)
