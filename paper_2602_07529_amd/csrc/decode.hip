@@ -678,11 +678,9 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 // 4 .. 7 share what is left, one half of every tile each (six) or of every second one (five): 105 -> 99 us.
 // 2 groups of 32 siblings x 5 heads on 8 KV heads, 32 K shared and 640 own tokens (436 MB): 128 us with units in
 // read - wait - multiply phases by ten waves, 91 us so = 4.8 TB/s; the matrix pipes need 17 us of it.
-constexpr int WIDE_WAVES = 8;        // of a workgroup: two per SIMD
 constexpr int WIDE_TILE_PAGES = 4;
 constexpr int WIDE_RING = 4;         // tiles in the K ring and in the V ring
 // dynamic LDS of a launch: the rings, or the query operands and the partials of the own items
-inline int wide_own_bytes(int G, int D, int own) { return WIDE_WAVES / own * (D / 16 * 1024) + WIDE_WAVES * G * (D + 6) * 4; }
 inline int wide_lds_bytes(int G, int D, int own) {
   const int rings = 2 * WIDE_RING * WIDE_TILE_PAGES * PAGE * D * 2, bytes = wide_own_bytes(G, D, own);
   return rings > bytes ? rings : bytes;
@@ -1711,14 +1709,9 @@ int decode_impl(const dag_decode_desc_t* d, const void* q, const void* k_pool, c
     // once for all rows of a group, and of the other own items.
     const unsigned shared_wgs = (unsigned)(d->n_groups * hkv * p.splits_a);
     const unsigned threads = 64u * WIDE_WAVES;
-    // Waves to an own item: as many as leave a workgroup for every compute unit (512 items of 40 pages by
-    // themselves: eight waves each 30.5 us, four 27.9).
     const int n_cu = dag_compute_units();
     if (n_cu < 1) return DAG_ERR_HIP;
-    a.wide_own = WIDE_WAVES;
-    while (a.wide_own > 1 && (int64_t)p.items_b * a.wide_own > (int64_t)WIDE_WAVES * n_cu &&
-           wide_own_bytes(a.G, head_dim, a.wide_own / 2) <= 160 * 1024)
-      a.wide_own /= 2;
+    a.wide_own = wide_own_waves(p.items_b, n_cu, a.G, head_dim);
     const unsigned own_wgs = (unsigned)dag_ceil_div(p.items_b, WIDE_WAVES / a.wide_own);
     // Half of the compute units start with own pages: an item keeps the memory idle for its first 6 us (lengths, page ids, pages), which all
     // of them at once waste and half of them leave to the others (2 x 32 siblings over 32 K: 9 us of 98).

@@ -9,8 +9,19 @@ constexpr int PAGE = DAG_PAGE_SIZE;
 // their maximum: error against 64 bits over 100 shapes 0.95 of that at 8, and the time of the largest steps the same (at 0: 0.93, and 0.2 %).
 constexpr float ITEM_TH = 1.f;
 
-constexpr int WIDE_MAX_BLOCKS = 8;     // k_decode_wide: row blocks of a workgroup
+constexpr int WIDE_WAVES = 8;          // k_decode_wide: waves of a workgroup, two per SIMD
+constexpr int WIDE_MAX_BLOCKS = 8;     // row blocks of a workgroup
 constexpr int WIDE_MAX_PAGES = 128;    // of a shared slice: its page ids sit in two registers
+constexpr int WIDE_LDS_BYTES = 160 * 1024;
+// LDS of workgroups with own pages: the query operands and the partials of their items
+inline int wide_own_bytes(int G, int D, int waves) { return WIDE_WAVES / waves * (D / 16 * 1024) + WIDE_WAVES * G * (D + 6) * 4; }
+// Waves to an own item: as many as leave a workgroup for every compute unit (512 items of 40 pages by themselves: eight waves each
+// 30.5 us, four 27.9).
+inline int wide_own_waves(int64_t items, int units, int G, int D) {
+  int waves = WIDE_WAVES;
+  while (waves > 1 && items * waves > (int64_t)WIDE_WAVES * units && wide_own_bytes(G, D, waves / 2) <= WIDE_LDS_BYTES) waves /= 2;
+  return waves;
+}
 constexpr int WHOLE_ROWS = 8;          // k_whole_branch: query heads of a KV head
 // Up to these pages in a context (a wave walks its slice alone, 1 us a block) and workgroups (one a compute unit: two take turns);
 // 88 random steps with up to 8 rows a branch: inside 1.02 to 1.40 times as fast as items and merge; above 64 pages of dimension 128
@@ -41,14 +52,27 @@ struct DecodePlan {
 // of 128 dimensions, shared ones once for each row block: up to 256 in a context, 5632 in all, and 6400 of the branches' own (96
 // random shapes, single waves : k_decode_wide below these lines 0.55 to 1.14, 0.87 on average, a step of 2 x 25 branches over 500
 // tokens 17.0 -> 12.6 us; above 5632 shared pages up to 2.5, above 256 in a context 1.04 to 1.25, above 6400 own ones 0.9 to 1.37).
-// What is left takes slices that make a hundred workgroups with shared pages and 256 with own ones, not 256 and 512:
-// each slice leaves 32 rows of sums that the merge reads (a group of 22 branches over 13,072 tokens, four KV heads: 103 slices of 8
-// pages 32.4 us, 26 of 32 pages 20.2; 135 random shapes of both kinds 1.09 times as fast, four of them 3 to 7 % slower).
-// Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
-// slices get longer it follows the maximum: always in single waves, in k_decode_wide when the sum of 16 probabilities grows by 2.5
-// (error against 64 bits, 110 shapes, with : without longer slices 0.997 on average, 0.95 to 1.05; by 4 1.006, by 1024 as elsewhere 1.017).
-// The workspace keeps the size of the shorter slices: buffers sized by an earlier library stay as good as they were.
 constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES = 6400;
+
+// What is left: a compute unit has room for one workgroup of k_decode_wide, and each slice leaves 32 rows of sums that the merge
+// reads, so the shared pages get WIDE_GROUPS workgroups and the own ones 256, in slices of one length.  At head dimension 64, where a
+// page takes its time in exponentials and not in memory, the shared pages get a workgroup for every unit if their slices are longer
+// than WIDE_LONG_64 pages (WIDE_LONG_64_TALL where a wave has a row block for itself) and the own pages are not the greater part.  If
+// that is more than one for each unit, the last workgroups with own pages begin when the first end: where two of them in a row
+// take a quarter longer than a shared one, the shared pages get as many as fit beside them (12 groups of 14 siblings over 3,849 shared and
+// 1,181 own tokens, five heads on one: 30.6 us, with 128 workgroups 39.5, with those of the shorter slices 45.1).  The times are those
+// that fit the measured steps best, in units of 0.05 us: 5 us and half a microsecond a page of a wave with own pages, 6 us and 0.35 (0.25 at dimension 64)
+// a page of a workgroup with shared ones.  Slices of eight pages become 16 where there are more than 64 of them or twice as many own
+// pages as shared ones: fewer partials.
+// 110 random shapes against the slices that `bytes` is for: dimension 64 1.12 times as fast on average (0.91 to 1.41), 128 1.17
+// (0.93 to 1.55); with a hundred workgroups and 16 pages at least everywhere 1.05 (0.79 to 1.37) and 1.12 (0.85 to 1.43).
+// Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
+// slices get longer it follows the maximum: always in single waves, in k_decode_wide when the sum of 16 probabilities grows by 3 (2.5 at
+// dimension 128): error against 64 bits over these shapes, with : without longer slices, 0.996 and 1.000 on average, 0.96 to 1.05;
+// by 4 1.002 and 1.011, by 1024 as elsewhere 1.014 and 1.021.
+// The workspace keeps the size of the shorter slices: buffers sized by an earlier library stay as good as they were.
+constexpr int WIDE_UNITS = 256, WIDE_GROUPS = 128, WIDE_BESIDE = 48, WIDE_LONG_64 = 64, WIDE_LONG_64_TALL = 42;
+
 inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const DecodeKnobs& knobs, DecodePlan* p) {
   if (!d) return DAG_ERR_NULL;
   if (d->n_groups < 0 || d->n_live < 0 || d->max_shared_pages < 0 || d->max_branch_pages < 0 || d->max_group_size < 0)
@@ -56,41 +80,16 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
   if (d->page_size != PAGE) return DAG_ERR_UNSUPPORTED;
   if (hq < 1 || hkv < 1 || hq % hkv != 0 || hq / hkv > 32) return DAG_ERR_UNSUPPORTED;
   if (D != 64 && D != 128) return DAG_ERR_UNSUPPORTED;
-  const int G = hq / hkv;
+  const int G = hq / hkv, shared = d->max_shared_pages, own = d->max_branch_pages;
   p->rb_max = (int)dag_ceil_div((int64_t)d->max_group_size * G, 32);
   if (p->rb_max < 1) p->rb_max = 1;
-  const int64_t base_a = (int64_t)d->n_groups * hkv * p->rb_max;
-  const int64_t base_b = (int64_t)d->n_live * hkv;
-  p->wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_BLOCKS;
-  p->th = p->wide ? 8.f : ITEM_TH;
-  p->settle = 1024.f;
-  // Slices of at least `least` pages, halved until there are `shared` / `own` workgroups or waves.  An eighth more than that
-  // (`longer`; two pages at least) where it saves a slice: a context of 65 pages was one of 64 and one of a page, which is a partial as
-  // large as any (60 random steps 1.02 times as fast, one sequence of 509 shared and 43 own pages 17.2 -> 15.4 us).
-  auto slices = [&](bool wide, int64_t shared, int least, int64_t own, bool longer) {
-    int ca = knobs.chunk_a ? knobs.chunk_a : 128, cb = knobs.chunk_b ? knobs.chunk_b : 64;
-    ca += ca & 1;
-    cb += cb & 1;
-    if (p->wide && ca > WIDE_MAX_PAGES) ca = WIDE_MAX_PAGES;
-    const int64_t base = wide ? (int64_t)d->n_groups * hkv : base_a;
-    if (!knobs.chunk_a)
-      while (ca > least && base * dag_ceil_div(d->max_shared_pages, ca) < shared) ca /= 2;
-    if (!knobs.chunk_b)
-      while (cb > 4 && base_b * dag_ceil_div(d->max_branch_pages, cb) < own) cb /= 2;
-    auto stretch = [&](int pages, int c, int most) {
-      const int more = c + (c / 8 > 2 ? c / 8 : 2), longest = more < most ? more : most, n = (int)dag_ceil_div(pages, longest);
-      return n > 0 && n < dag_ceil_div(pages, c) ? ((pages + n - 1) / n + 1) & ~1 : c;
-    };
-    if (longer && !knobs.chunk_a) ca = stretch(d->max_shared_pages, ca, p->wide ? WIDE_MAX_PAGES : INT32_MAX);
-    if (longer && !knobs.chunk_b) cb = stretch(d->max_branch_pages, cb, INT32_MAX);
-    p->splits_a = d->max_shared_pages > 0 ? (int)dag_ceil_div(d->max_shared_pages, ca) : 0;
-    p->splits_b = d->max_branch_pages > 0 ? (int)dag_ceil_div(d->max_branch_pages, cb) : 0;
-    if (wide && !knobs.chunk_a && p->splits_a > 1) {  // slices of one length, unless that is more rounds of workgroups
-      const int same = ((d->max_shared_pages + p->splits_a - 1) / p->splits_a + 1) & ~1;
-      if (dag_ceil_div(base * p->splits_a, 256) * same <= dag_ceil_div(base * (p->splits_a - 1), 256) * ca) ca = same;
-    }
+  const int64_t base_w = (int64_t)d->n_groups * hkv, base_a = base_w * p->rb_max, base_b = (int64_t)d->n_live * hkv;
+  const bool wide = p->rb_max >= 2 && p->rb_max <= WIDE_MAX_BLOCKS;
+  auto lay_out = [&](int ca, int cb) {
     p->chunk_a = ca;
     p->chunk_b = cb;
+    p->splits_a = (int)dag_ceil_div(shared, ca);
+    p->splits_b = (int)dag_ceil_div(own, cb);
     const int64_t ia = base_a * p->splits_a, ib = base_b * p->splits_b;
     if (ia + ib > INT32_MAX) return DAG_ERR_UNSUPPORTED;
     p->items_a = (int)ia;
@@ -103,26 +102,57 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     p->bytes = off + 256;
     return DAG_OK;
   };
-  const int rc = slices(p->wide, p->wide ? 256 : 512, 8, p->wide ? 512 : 1024, false);
+  auto even = [](int64_t c) { return (int)(c + (c & 1)); };
+  auto halved = [](int c, int least, int64_t base, int pages, int64_t want) {  // until there are `want` workgroups or waves
+    while (c > least && base * dag_ceil_div(pages, c) < want) c /= 2;
+    return c;
+  };
+  // An eighth more than that (two pages at least) where it saves a slice: a context of 65 pages was one of 64 and one of a page, which
+  // is a partial as large as any (60 random steps 1.02 times as fast, one sequence of 509 shared and 43 own pages 17.2 -> 15.4 us).
+  auto longer = [&](int pages, int c) {
+    const int64_t n = dag_ceil_div(pages, c + (c / 8 > 2 ? c / 8 : 2));
+    return n > 0 && n < dag_ceil_div(pages, c) ? even(dag_ceil_div(pages, n)) : c;
+  };
+  int ca = knobs.chunk_a ? even(knobs.chunk_a) : halved(128, 8, wide ? base_w : base_a, shared, wide ? 256 : 512);
+  int cb = knobs.chunk_b ? even(knobs.chunk_b) : halved(64, 4, base_b, own, wide ? 512 : 1024);
+  if (wide && ca > WIDE_MAX_PAGES) ca = WIDE_MAX_PAGES;
+  const int rc = lay_out(ca, cb);
   if (rc != DAG_OK) return rc;
   const size_t bytes = p->bytes;  // (what follows has at most as many items of either kind)
-  const int shorter_a = p->chunk_a, shorter_b = p->chunk_b;
+  p->wide = wide && base_w > 0 && shared > 0 &&
+            (shared > NARROW_CONTEXT_PAGES || base_a * shared * D > NARROW_PAGES * 128 || base_b * own * D > NARROW_OWN_PAGES * 128);
+  p->th = 8.f;
+  p->settle = 1024.f;
   if (!p->wide) {
-    slices(false, 512, 8, 1024, true);
-  } else if (d->max_shared_pages <= NARROW_CONTEXT_PAGES && base_a * d->max_shared_pages * D <= NARROW_PAGES * 128 &&
-      base_b * d->max_branch_pages * D <= NARROW_OWN_PAGES * 128) {
-    slices(false, 512, 8, 512, true);
-    p->wide = false;
-    p->th = 0.f;
-  } else {
-    slices(true, 100, 16, 256, true);
-    auto length = [](int pages, int c) { return pages < c ? pages : c; };
-    if (length(d->max_shared_pages, p->chunk_a) > length(d->max_shared_pages, shorter_a)) p->settle = 2.5f;
-    if (p->chunk_a > shorter_a || p->chunk_b > shorter_b) p->th = 0.f;
+    if (!knobs.chunk_a) ca = longer(shared, halved(128, 8, base_a, shared, 512));
+    if (!knobs.chunk_b) cb = longer(own, cb);
+    p->th = wide ? 0.f : ITEM_TH;
+    lay_out(ca, cb);
+  } else if (!knobs.chunk_a && !knobs.chunk_b) {
+    int lb = longer(own, halved(64, 4, base_b, own, 256));
+    if (lb < cb) lb = cb;
+    if (own > lb) lb = even(dag_ceil_div(own, dag_ceil_div(own, lb)));  // of one length
+    const int64_t items = base_b * dag_ceil_div(own, lb);
+    const int waves = wide_own_waves(items, WIDE_UNITS, G, D);
+    const int64_t beside = WIDE_UNITS - dag_ceil_div(items, WIDE_WAVES / waves);
+    const int64_t own_time = 100 + 10 * dag_ceil_div(own < lb ? own : lb, waves);
+    auto slice = [&](int64_t groups) {  // of that many workgroups
+      const int64_t c = dag_ceil_div(shared, base_w < groups ? groups / base_w : 1);
+      return c < WIDE_MAX_PAGES ? even(c) : WIDE_MAX_PAGES;
+    };
+    int la = slice(WIDE_GROUPS);
+    if (D == 64 && la > (p->rb_max <= WIDE_WAVES / 2 ? WIDE_LONG_64 : WIDE_LONG_64_TALL) && base_b * own < base_w * shared) la = slice(WIDE_UNITS);
+    const int64_t shared_time = 120 + (D == 64 ? 5 : 7) * (int64_t)la;
+    if (base_w * dag_ceil_div(shared, la) > beside && 8 * own_time > 5 * shared_time && beside >= WIDE_BESIDE) la = slice(beside);
+    if (la < 16 && (dag_ceil_div(shared, 8) > 64 || base_b * own >= 2 * base_w * shared)) la = 16;
+    if (la < ca) la = ca;
+    if ((la < shared ? la : shared) > (ca < shared ? ca : shared)) p->settle = D == 64 ? 3.f : 2.5f;
+    if (la > ca || lb != cb) p->th = 0.f;
+    lay_out(la, lb);
   }
   p->bytes = bytes;
   p->whole = G <= WHOLE_ROWS && !knobs.chunk_a && !knobs.chunk_b && base_b <= WHOLE_GROUPS &&
-             (int64_t)d->max_shared_pages + d->max_branch_pages <= (D == 128 ? WHOLE_PAGES_128 : WHOLE_PAGES_64);
+             (int64_t)shared + own <= (D == 128 ? WHOLE_PAGES_128 : WHOLE_PAGES_64);
   if (p->whole) p->th = 0.f;
   return DAG_OK;
 }

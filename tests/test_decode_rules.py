@@ -2,6 +2,7 @@
 import ctypes as C
 
 import numpy as np
+import pytest
 
 from paper_2602_07529_amd import binding as B
 from tests import decode_rules
@@ -16,3 +17,40 @@ def test_the_rules_are_those_of_the_library():
         assert decode_rules.decode(desc, hkv * g, hkv, d).bytes == B.lib().dag_decode_workspace_bytes(C.byref(desc), hkv * g, hkv, d)
         seg = B.dag_decode_seg_desc_t(groups * size, groups + groups * size, 16, max(shared, own), size, 2 * groups * size, *([0x1000] * 8))
         assert decode_rules.segments(seg, hkv * g, hkv, d).bytes == B.lib().dag_decode_segments_workspace_bytes(C.byref(seg), hkv * g, hkv, d)
+
+
+# Sibling groups of more than 32 rows: shared slices x pages, own slices x pages; False: the slices that the workspace is sized for.
+@pytest.mark.parametrize("groups,nb,shared,own,hq,hkv,d,want,lengthened", [
+    (8, 17, 1488, 4, 8, 2, 64, (16, 94, 1, 64), True),       # a workgroup for every compute unit, not half of them in slices of 128
+    (7, 21, 706, 29, 20, 4, 64, (9, 80, 1, 64), True),
+    (3, 20, 395, 7, 32, 8, 128, (5, 80, 1, 64), True),       # 120 workgroups
+    (1, 22, 817, 13, 8, 4, 128, (32, 26, 3, 6), True),       # 128
+    (2, 23, 335, 9, 5, 1, 64, (42, 8, 2, 6), False),         # few workgroups with little each: slices of eight pages
+    (2, 21, 1091, 9, 3, 1, 128, (61, 18, 2, 6), True),       # 64 workgroups to a group
+    (12, 14, 241, 75, 5, 1, 128, (7, 36, 2, 38), True),      # 84 workgroups beside 168 with own pages
+    (4, 26, 144, 87, 20, 4, 128, (3, 48, 2, 44), True),      # 48 beside 208
+    (8, 10, 79, 93, 8, 2, 128, (5, 16, 2, 48), True) ,        # own pages are most of it
+    (2, 32, 2048, 40, 40, 8, 128, (16, 128, 1, 64), False),
+])
+def test_slices_of_wide_groups(groups, nb, shared, own, hq, hkv, d, want, lengthened):
+    p = decode_rules.step(groups, nb, shared, own, hq, hkv, d)
+    assert (p.splits_a, p.chunk_a, p.splits_b, p.chunk_b) == want
+    assert p.route == "wide" and (p.settle < 1024) == lengthened
+
+
+def test_wide_groups_without_a_shared_context_are_enough_single_waves():
+    for groups, nb, own, hq, hkv in ((1, 30, 500, 8, 1), (2, 20, 300, 16, 2), (1, 12, 4000, 24, 4)):
+        p = decode_rules.step(groups, nb, 0, own, hq, hkv, 128)
+        assert p.route == "items" and groups * nb * hkv * p.splits_b >= 512
+
+
+def test_rules_never_make_more_partials_than_the_workspace_holds():
+    rng = np.random.default_rng(9)
+    for _ in range(4000):
+        groups, hkv, g, size = (int(rng.integers(1, x)) for x in (40, 9, 33, 70))
+        d, shared, own = int(rng.choice([64, 128])), int(2 ** rng.uniform(0, 13)) - 1, int(2 ** rng.uniform(0, 9)) - 1
+        p = decode_rules.step(groups, size, shared, own, hkv * g, hkv, d)
+        assert p.splits_a * p.chunk_a >= shared and p.splits_b * p.chunk_b >= own and p.chunk_a % 2 == 0 and p.chunk_b % 2 == 0
+        assert not p.wide or p.chunk_a <= 128
+        rows = groups * hkv * p.rb_max * p.splits_a * 32 + groups * size * hkv * p.splits_b * g
+        assert rows * (d + 2) * 4 + 256 <= p.bytes
