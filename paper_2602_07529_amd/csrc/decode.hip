@@ -1229,7 +1229,6 @@ __global__ void __launch_bounds__(64 * WIDE_WAVES, 2) k_decode_wide(DecodeArgs a
 // then has the same D / 64 dimensions of every partial, at addresses that the wave computes once, and the partials need no sum over
 // lanes.  Few partials, first and second form: dimension 64, 4096 rows 4.2 and 5.1 us, 8192 rows 7.1 and 5.9, 16384 rows 12.6 and 9.1,
 // 65536 rows 46 and 33; dimension 128 4.2 and 4.5, 8.0 and 6.8, 12.0 and 10.2, 46 and 38.
-constexpr int64_t MERGE_FEW_ROWS = 4096;
 constexpr int merge_per(int D, bool few) { return few ? 4 : D / 64; }
 constexpr int merge_threads(bool few) { return few ? 256 : 64; }
 __device__ __forceinline__ int group_of_branch(const DecodeArgs& a, int r, int lane) {

@@ -28,6 +28,8 @@ constexpr int WHOLE_ROWS = 8;          // k_whole_branch: query heads of a KV he
 // 0.99 to 1.16, above 110 0.66 to 0.92, between 257 and 360 workgroups 0.82 to 0.98, above that 0.68 to 1.25.
 constexpr int WHOLE_PAGES_128 = 64, WHOLE_PAGES_64 = 96, WHOLE_GROUPS = 256;
 constexpr int SEG_PAGES_16 = 2048, SEG_PAGES_32 = 9216, SEG_PAGES_64 = 32768, SEG_PAGES_128 = 65536;
+// k_decode_merge: rows (branches x query heads) up to which a wave takes several partials to a load, 16 loads at a time
+constexpr int64_t MERGE_FEW_ROWS = 4096;
 constexpr size_t SEG_ITEM_BYTES = 32;  // of the list of work items
 
 // Development knobs (pages per decode work item); 0 = not set, the split sizes then follow the shape of the batch.
@@ -107,9 +109,7 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     while (c > least && base * dag_ceil_div(pages, c) < want) c /= 2;
     return c;
   };
-  // An eighth more than that (two pages at least) where it saves a slice: a context of 65 pages was one of 64 and one of a page, which
-  // is a partial as large as any (60 random steps 1.02 times as fast, one sequence of 509 shared and 43 own pages 17.2 -> 15.4 us).
-  auto longer = [&](int pages, int c) {
+  auto longer = [&](int pages, int c) {  // an eighth more (two pages at least) where it saves a slice
     const int64_t n = dag_ceil_div(pages, c + (c / 8 > 2 ? c / 8 : 2));
     return n > 0 && n < dag_ceil_div(pages, c) ? even(dag_ceil_div(pages, n)) : c;
   };
@@ -124,8 +124,19 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
   p->th = 8.f;
   p->settle = 1024.f;
   if (!p->wide) {
-    if (!knobs.chunk_a) ca = longer(shared, halved(128, 8, base_a, shared, 512));
-    if (!knobs.chunk_b) cb = longer(own, cb);
+    // Single waves: a slice takes a microsecond for two of its pages, so longer ones pay where the merge goes round once less (509 shared and
+    // 43 own pages of one sequence, 75 partials and 59: 17.2 -> 15.4 us; 92 and 81, 33 and 24: 13.1 -> 12.0; where it does not, slices of ten
+    // pages for eight and six for four cost up to a tenth: 94 and 16, 14.9 us for 14.5), and a last slice of an eighth of the others,
+    // which is a partial as large as any, where they have 16 pages or more (91 and 18 pages of 117 branches, 16 / 8 heads: 61.4 -> 53.7;
+    // slices that are merely fewer: 0.97 to 1.01).
+    if (!knobs.chunk_a) ca = halved(128, 8, base_a, shared, 512);
+    const int round = (int64_t)d->n_live * hq > MERGE_FEW_ROWS ? 16 : D == 128 ? 32 : 64;
+    auto rounds = [&](int xa, int xb) { return dag_ceil_div(dag_ceil_div(shared, xa) + dag_ceil_div(own, xb), round); };
+    auto joined = [&](int pages, int c) { return c >= 16 && pages > c && pages % c > 0 && pages % c <= c / 8 ? even(dag_ceil_div(pages, pages / c)) : c; };
+    const int la = longer(shared, ca), lb = longer(own, cb);
+    const bool merged = rounds(knobs.chunk_a ? ca : la, knobs.chunk_b ? cb : lb) < rounds(ca, cb);
+    if (!knobs.chunk_a) ca = merged ? la : joined(shared, ca);
+    if (!knobs.chunk_b) cb = merged ? lb : joined(own, cb);
     p->th = wide ? 0.f : ITEM_TH;
     lay_out(ca, cb);
   } else if (!knobs.chunk_a && !knobs.chunk_b) {

@@ -54,3 +54,21 @@ def test_rules_never_make_more_partials_than_the_workspace_holds():
         assert not p.wide or p.chunk_a <= 128
         rows = groups * hkv * p.rb_max * p.splits_a * 32 + groups * size * hkv * p.splits_b * g
         assert rows * (d + 2) * 4 + 256 <= p.bytes
+
+
+# Single waves: slices get longer where the merge goes round once less (32 partials at head dimension 128, 64 at 64, 16 in many rows) or
+# where the last one would be an eighth of 16 pages or more, and not where a step is one chain of a few blocks.
+@pytest.mark.parametrize("groups,nb,shared,own,hq,hkv,d,want", [
+    (1, 4, 94, 16, 32, 8, 128, (12, 8, 4, 4)),       # 16 partials either way
+    (1, 1, 211, 5, 2, 1, 128, (27, 8, 2, 4)),
+    (2, 5, 29, 41, 5, 1, 128, (4, 8, 11, 4)),
+    (1, 1, 509, 43, 8, 1, 128, (51, 10, 8, 6)),      # 75 -> 59
+    (1, 1, 509, 43, 8, 1, 64, (51, 10, 8, 6)),       # 75 -> 59: two rounds -> one
+    (1, 1, 747, 49, 2, 2, 64, (94, 8, 13, 4)),       # 107 -> 84: two either way
+    (16, 32, 257, 4, 16, 16, 128, (2, 130, 1, 64)),   # a last page of 128: joined
+    (16, 32, 275, 4, 16, 16, 128, (3, 128, 1, 64)),   # 19 pages are not
+    (3, 3, 17, 0, 4, 1, 128, (3, 8, 0, 4)),
+])
+def test_slices_of_single_waves(groups, nb, shared, own, hq, hkv, d, want):
+    p = decode_rules.step(groups, nb, shared, own, hq, hkv, d)
+    assert not p.wide and (p.splits_a, p.chunk_a, p.splits_b, p.chunk_b) == want
