@@ -65,9 +65,11 @@ constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES 
 // 1,181 own tokens, five heads on one: 30.6 us, with 128 workgroups 39.5, with those of the shorter slices 45.1).  The times are those
 // that fit the measured steps best, in units of 0.05 us: 5 us and half a microsecond a page of a wave with own pages, 6 us and 0.35 (0.25 at dimension 64)
 // a page of a workgroup with shared ones.  Slices of eight pages become 16 where there are more than 64 of them or twice as many own
-// pages as shared ones: fewer partials.
-// 110 random shapes against the slices that `bytes` is for: dimension 64 1.12 times as fast on average (0.91 to 1.41), 128 1.17
-// (0.93 to 1.55); with a hundred workgroups and 16 pages at least everywhere 1.05 (0.79 to 1.37) and 1.12 (0.85 to 1.43).
+// pages as shared ones: fewer partials.  If the longest slices there are still make more than WIDE_GROUPS workgroups, they are as
+// short as a workgroup for every unit makes them (12 groups of 19 over 11,129 tokens, 8 / 2 heads: 77 -> 66 us), and the
+// shorter slices stay where their workgroups have room at once and these do not (29 siblings over 936 and 574 tokens, 48 / 8 heads: 29.8 -> 25.6).
+// 180 random shapes against the slices that `bytes` is for: dimension 64 1.11 times as fast on average (0.91 to 1.42), 128 1.15
+// (0.99 to 1.55); with a hundred workgroups and 16 pages at least everywhere 1.04 (0.79 to 1.37) and 1.11 (0.85 to 1.43).
 // Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
 // slices get longer it follows the maximum: always in single waves, in k_decode_wide when the sum of 16 probabilities grows by 3 (2.5 at
 // dimension 128): error against 64 bits over these shapes, with : without longer slices, 0.996 and 1.000 on average, 0.96 to 1.05;
@@ -153,10 +155,19 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     };
     int la = slice(WIDE_GROUPS);
     if (D == 64 && la > (p->rb_max <= WIDE_WAVES / 2 ? WIDE_LONG_64 : WIDE_LONG_64_TALL) && base_b * own < base_w * shared) la = slice(WIDE_UNITS);
+    if (la == WIDE_MAX_PAGES) la = slice(WIDE_UNITS);
     const int64_t shared_time = 120 + (D == 64 ? 5 : 7) * (int64_t)la;
     if (base_w * dag_ceil_div(shared, la) > beside && 8 * own_time > 5 * shared_time && beside >= WIDE_BESIDE) la = slice(beside);
     if (la < 16 && (dag_ceil_div(shared, 8) > 64 || base_b * own >= 2 * base_w * shared)) la = 16;
     if (la < ca) la = ca;
+    auto together = [&](int xa, int xb) {
+      const int64_t n = base_b * dag_ceil_div(own, xb);
+      return base_w * dag_ceil_div(shared, xa) + dag_ceil_div(n, WIDE_WAVES / wide_own_waves(n, WIDE_UNITS, G, D)) <= WIDE_UNITS;
+    };
+    if (together(ca, cb) && !together(la, lb)) {
+      la = ca;
+      lb = cb;
+    }
     if ((la < shared ? la : shared) > (ca < shared ? ca : shared)) p->settle = D == 64 ? 3.f : 2.5f;
     if (la > ca || lb != cb) p->th = 0.f;
     lay_out(la, lb);
