@@ -155,7 +155,7 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     };
     int la = slice(WIDE_GROUPS);
     if (D == 64 && la > (p->rb_max <= WIDE_WAVES / 2 ? WIDE_LONG_64 : WIDE_LONG_64_TALL) && base_b * own < base_w * shared) la = slice(WIDE_UNITS);
-    if (la == WIDE_MAX_PAGES) la = slice(WIDE_UNITS);
+    if (base_w * dag_ceil_div(shared, la) > WIDE_GROUPS) la = slice(WIDE_UNITS);
     const int64_t shared_time = 120 + (D == 64 ? 5 : 7) * (int64_t)la;
     if (base_w * dag_ceil_div(shared, la) > beside && 8 * own_time > 5 * shared_time && beside >= WIDE_BESIDE) la = slice(beside);
     if (la < 16 && (dag_ceil_div(shared, 8) > 64 || base_b * own >= 2 * base_w * shared)) la = 16;

@@ -31,6 +31,7 @@ def test_the_rules_are_those_of_the_library():
     (4, 26, 144, 87, 20, 4, 128, (3, 48, 2, 44), True),      # 48 beside 208
     (8, 10, 79, 93, 8, 2, 128, (5, 16, 2, 48), True) ,        # own pages are most of it
     (12, 19, 696, 28, 8, 2, 128, (10, 70, 1, 64), True),     # slices of 128 pages would be 144 workgroups
+    (10, 10, 128, 17, 32, 8, 128, (1, 128, 1, 64), True),    # 80 workgroups: not too many
     (1, 29, 59, 37, 48, 8, 128, (8, 8, 3, 16), False),       # 64 and 174 workgroups: all at once
     (2, 32, 2048, 40, 40, 8, 128, (16, 128, 1, 64), False),
 ])
