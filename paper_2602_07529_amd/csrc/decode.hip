@@ -164,13 +164,15 @@ __device__ __forceinline__ void block_scores(const bf16x8 (&kop)[D / 16], QF&& q
   // is then rare, and probabilities above one are absorbed exactly by fp32 accumulation and the final division.
   if (__builtin_amdgcn_ballot_w64(bm > m + th) != 0) {
     const float m_new = fmaxf(m, bm);
-    const float alpha = __builtin_amdgcn_exp2f((m - m_new) * sc);
+    if (__builtin_amdgcn_ballot_w64(m > -1e30f) != 0) {  // (the first block finds zeros: what a step of a few blocks loses by the nearer reference)
+      const float alpha = __builtin_amdgcn_exp2f((m - m_new) * sc);
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[db][r] *= alpha;
+    }
     m = m_new;
-    l *= alpha;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) O[db][r] *= alpha;
   }
   const float msc = m * sc;
   f32x8 p0, p1;
