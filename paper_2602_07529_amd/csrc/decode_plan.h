@@ -24,10 +24,24 @@ inline int wide_own_waves(int64_t items, int units, int G, int D) {
   return waves;
 }
 constexpr int WHOLE_ROWS = 8;          // k_whole_branch: query heads of a KV head
-// Up to these pages in a context (a wave walks its slice alone, 1 us a block) and workgroups (one a compute unit: two take turns);
-// 88 random steps with up to 8 rows a branch: inside 1.02 to 1.40 times as fast as items and merge; above 64 pages of dimension 128
-// 0.99 to 1.16, above 110 0.66 to 0.92, between 257 and 360 workgroups 0.82 to 0.98, above that 0.68 to 1.25.
-constexpr int WHOLE_PAGES_128 = 64, WHOLE_PAGES_64 = 96, WHOLE_GROUPS = 256;
+// k_whole_branch takes a (branch, KV head) whole in one workgroup, so that every branch reads the shared pages for itself.  Its lines, from
+// 170 steps with up to 8 rows a branch, as fast : items and merge; inside them 0.95 to 1.55, 1.24 on average:
+// - 256 workgroups, one a compute unit: between 257 and 360 two take turns, 0.82 to 0.98.
+// - pages in a context (a wave walks its slice alone, 1 us a block), and shared ones among them, which items read in longer slices than
+//   own ones: branches of one row block above 52 or 41 pages of dimension 128 0.90 to 1.1, above 56 shared ones of 64 0.89 to 1.05.  More
+//   row blocks read the shared pages as often when they are items: 64 pages of dimension 128, at 64 below 79 shared ones (0.92).
+// - shared pages that pass through more than one L2: workgroups go to the eight dies in turn, so the siblings of a group are on eight of them,
+//   on four, two or one if hkv is a multiple of two, four or eight.  What they fetch again, in pages of 128 dimensions (16 groups of 8
+//   branches over 560 tokens, 4 / 1 heads: 3920 pages, 11.9 us as items and 15.1 so): above 1500 of one row block 0.77 to 1.04 (once 1.12), above 3000 of more 0.84 to 1.04.
+constexpr int WHOLE_GROUPS = 256, WHOLE_DIES = 8;
+inline bool whole_branches(int64_t base_w, int64_t base_b, int branches, int hkv, int G, int D, bool one_block, int64_t shared, int64_t own) {
+  if (G > WHOLE_ROWS || base_b > WHOLE_GROUPS) return false;
+  if (shared + own > (D == 64 ? 96 : one_block ? 52 : 64) || shared > (D == 64 ? (one_block ? 56 : 76) : one_block ? 41 : 64)) return false;
+  int64_t dies = WHOLE_DIES;  // a group's workgroups are on
+  while (dies > 1 && hkv % (2 * WHOLE_DIES / dies) == 0) dies /= 2;
+  if (dies > branches) dies = branches;
+  return (dies - 1) * base_w * shared * D <= (one_block ? 1500 : 3000) * 128;
+}
 constexpr int SEG_PAGES_16 = 2048, SEG_PAGES_32 = 9216, SEG_PAGES_64 = 32768, SEG_PAGES_128 = 65536;
 // k_decode_merge: rows (branches x query heads) up to which a wave takes several partials to a load, 16 loads at a time
 constexpr int64_t MERGE_FEW_ROWS = 4096;
@@ -174,8 +188,7 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     lay_out(la, lb);
   }
   p->bytes = bytes;
-  p->whole = G <= WHOLE_ROWS && !knobs.chunk_a && !knobs.chunk_b && base_b <= WHOLE_GROUPS &&
-             (int64_t)shared + own <= (D == 128 ? WHOLE_PAGES_128 : WHOLE_PAGES_64);
+  p->whole = !knobs.chunk_a && !knobs.chunk_b && whole_branches(base_w, base_b, d->max_group_size, hkv, G, D, p->rb_max == 1, shared, own);
   if (p->whole) p->th = 0.f;
   return DAG_OK;
 }

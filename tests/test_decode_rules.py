@@ -75,3 +75,19 @@ def test_rules_never_make_more_partials_than_the_workspace_holds():
 def test_slices_of_single_waves(groups, nb, shared, own, hq, hkv, d, want):
     p = decode_rules.step(groups, nb, shared, own, hq, hkv, d)
     assert not p.wide and (p.splits_a, p.chunk_a, p.splits_b, p.chunk_b) == want
+
+
+# A (branch, KV head) to a workgroup: where the shared pages are few enough to be read by every branch.
+@pytest.mark.parametrize("groups,nb,shared,own,hq,hkv,d,whole", [
+    (1, 4, 32, 20, 32, 8, 128, True), (1, 4, 33, 20, 32, 8, 128, False),
+    (1, 4, 41, 5, 32, 8, 128, True), (1, 4, 42, 5, 32, 8, 128, False),
+    (1, 4, 40, 56, 32, 8, 64, True), (1, 4, 40, 57, 32, 8, 64, False), (1, 4, 57, 2, 32, 8, 64, False),
+    (1, 9, 62, 2, 32, 8, 128, True), (1, 9, 62, 3, 32, 8, 128, False),            # two row blocks
+    (2, 9, 76, 20, 32, 8, 64, True), (2, 9, 77, 19, 32, 8, 64, False),
+    (16, 8, 35, 4, 4, 1, 128, False), (16, 1, 35, 4, 4, 1, 128, True),            # siblings on eight dies; no siblings
+    (2, 8, 35, 4, 32, 8, 128, True), (2, 8, 35, 4, 20, 5, 128, False), (2, 8, 35, 4, 16, 4, 128, True),
+    (4, 8, 7, 7, 9, 1, 128, False), (4, 8, 7, 7, 8, 1, 128, True),                # nine rows a branch
+    (2, 16, 7, 7, 8, 8, 128, True), (1, 33, 7, 7, 8, 8, 128, False),              # 256 workgroups
+])
+def test_short_contexts_that_a_workgroup_takes_whole(groups, nb, shared, own, hq, hkv, d, whole):
+    assert (decode_rules.step(groups, nb, shared, own, hq, hkv, d).route == "whole") == whole
