@@ -6,9 +6,10 @@
 constexpr int PAGE = DAG_PAGE_SIZE;
 
 // Single-wave items: log2 of how far a score may exceed the reference maximum.  Probabilities lose less to 16 bits the nearer it is to
-// their maximum: error against 64 bits over 100 shapes 0.95 of that at 8 (at 3 0.99, at 0 0.93).  The time of the largest steps is the same,
-// steps of a few blocks take 1 % longer (at 3 none), and 2 % if the first block is rescaled like the others.
-constexpr float ITEM_TH = 1.f;
+// their maximum: error against 64 bits over 80 frontiers 0.99 of that at 8 (at 1 0.95), over 120 decode steps with these slices 0.996 (0.97).
+// But at 1 some row of a wave raises its reference in most blocks: 14 x 16 leaves under 4 x 1,791 and 3,991 tokens 50.1 -> 52.3 us, 12
+// leaves under 1,729 and 1,156 17.5 -> 18.6; at 3 the times are those at 8.
+constexpr float ITEM_TH = 3.f;
 
 constexpr int WIDE_WAVES = 8;          // k_decode_wide: waves of a workgroup, two per SIMD
 constexpr int WIDE_MAX_BLOCKS = 8;     // row blocks of a workgroup

@@ -75,6 +75,7 @@ def test_rules_never_make_more_partials_than_the_workspace_holds():
 def test_slices_of_single_waves(groups, nb, shared, own, hq, hkv, d, want):
     p = decode_rules.step(groups, nb, shared, own, hq, hkv, d)
     assert not p.wide and (p.splits_a, p.chunk_a, p.splits_b, p.chunk_b) == want
+    assert p.th == 3 or p.route == "whole"   # at 1 frontiers of many rows took 2 to 6 % longer
 
 
 # A (branch, KV head) to a workgroup: where the shared pages are few enough to be read by every branch.
