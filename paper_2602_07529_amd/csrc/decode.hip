@@ -90,7 +90,7 @@ struct SegArgs {
   int rb_max;      // 32-row blocks per (segment, kv head)
   int chunk, splits, total_readers;  // pages of a slice and slices of a segment that the workspace has room for
   bool fixed;      // slices of `chunk` pages, whatever there is to read
-  bool few;        // the host's bounds leave less than SEG_PAGES_16 to read
+  bool few;        // by the host's bounds the slices have eight pages
   float weight;    // of a page: hkv * D / 128
   float sc, th;
 };
@@ -372,18 +372,14 @@ __global__ void __launch_bounds__(64, 2) k_decode(DecodeArgs a) {
 // those cost time even when they exit at once (they sit between the real items in the dispatch
 // order and hold wave slots while their loads return).  One workgroup therefore writes the compact
 // list: for every segment, in the caller's order, its slices x row blocks (exclusive scan of the
-// counts), and for every reader-list entry the number of slices its segment has.
+// counts), and for every reader-list entry the place of its first partial.
 //
-// The list also settles how long slices are.  The host knows the longest segment and takes every other one for as long, so its slices
-// are too long where one segment is; here all lengths are known.  Pages of 128 dimensions to be read (once for every row block) and
-// the slices that were fastest over 36 frontiers of 300 to 140,000 pages: 8 pages below 2,048, 16 below 9,216, 32 below 32,768,
-// 64 below 65,536, then 128 -- if the lists have room for so many, which have the sizes that the host's slices ask for: else twice
-// as long.  5 x 12 leaves under segments of 25 and 174 pages, 24 / 4 heads: 60 -> 38 us.  A segment's slices have one length, an
-// eighth more than that if this saves a slice (16 sequences of 254 to 258 | 2 x 126 to 130 | 8 x 63 to 67 pages: 227 -> 212 us).
+// The list also settles how long slices are (rules and figures: SEG_PAGES_16 and what follows it).  What that costs is exchanges between
+// the waves: one for what there is to read, and the scan of the counts tells whether the lists have room for slices of that length.  One
+// more for each length that is tried, before the scan, 0.5 to 2 us of a launch of 4 to 5.
 constexpr int PLAN_THREADS = 1024;
 __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
-  __shared__ int s_wave[2][PLAN_THREADS / 64];
-  __shared__ float s_sum[2][2][PLAN_THREADS / 64];
+  __shared__ uint32_t s_all[2][4][PLAN_THREADS / 64];  // (in turn: a barrier between two exchanges)
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, threads = blockDim.x, room = a.splits * a.total_readers;
   struct Seg {
     int len, e0, nr, npages, rbs;
@@ -400,94 +396,108 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
     return g;
   };
   const Seg mine = segment(tid);
+  static_assert(PLAN_THREADS == 16 * 64, "");
   int turn = 0;
+  auto exchange = [&](uint32_t x) __attribute__((always_inline)) {  // 16 lanes have a value of all waves each: that of lane 0, 1, 2, 3
+    uint32_t* const all = &s_all[turn & 1][0][0];
+    ++turn;
+    if (lane < 4) all[lane * (PLAN_THREADS / 64) + w] = x;
+    __syncthreads();
+    return (lane & 15) < threads / 64 ? all[lane] : 0u;
+  };
+  auto of_lane = [](float x, int from) __attribute__((always_inline)) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), from));
+  };
   struct Sums {
-    float x, y;
+    float x, y, top;
   };
-  auto gather = [&](float x, float y, bool top) __attribute__((always_inline)) {  // sums over all threads (exact up to 2^24), of y the maximum if `top`
-    x = dag_wave_sum(x);
-    y = top ? dag_wave_max(y) : dag_wave_sum(y);
+  auto gather = [&](Sums s) __attribute__((always_inline)) {  // sums over all threads (exact up to 2^24), the maximum of the last value
+    s = Sums{dag_wave_sum(s.x), dag_wave_sum(s.y), dag_wave_max(s.top)};
     if (threads > 64) {
-      float(*const all)[PLAN_THREADS / 64] = s_sum[turn & 1];
-      ++turn;
-      if (lane == 0) {
-        all[0][w] = x;
-        all[1][w] = y;
-      }
-      __syncthreads();
-      x = y = 0.f;
-      for (int i = 0; i < threads / 64; ++i) {
-        x += all[0][i];
-        y = top ? fmaxf(y, all[1][i]) : y + all[1][i];
-      }
+      const float v = __uint_as_float(exchange(__float_as_uint(lane == 0 ? s.x : lane == 1 ? s.y : s.top)));
+      const float sum = dag_wave_sum<8>(v);
+      s = Sums{of_lane(sum, 0), of_lane(sum, 16), of_lane(dag_wave_max<8>(v), 32)};
     }
-    return Sums{x, y};
+    return s;
   };
-  // pages of a segment's slices (even: a 32-key block never straddles two), at most c plus an eighth, all of them used
-  auto slice_of = [](int npages, int c) __attribute__((always_inline)) {
-    const int most = c + max(c / 8, 2), n = (npages + most - 1) / most;
-    return n > 0 ? ((npages + n - 1) / n + 1) & ~1 : 1;
+  // slices of a segment of at most 2^k pages (an eighth more of the longer ones), and the pages of them if all are alike and even
+  // (a 32-key block never straddles two)
+  auto longest_slice = [](int k) __attribute__((always_inline)) { return (1 << k) >= SEG_STRETCH ? 9 << (k - 3) : 1 << k; };
+  auto slices_of = [&](int npages, int k) __attribute__((always_inline)) {
+    const uint32_t x = (uint32_t)(npages + longest_slice(k) - 1);
+    return (int)((1 << k) >= SEG_STRETCH ? (x >> (k - 3)) / 9 : x >> k);
+  };
+  auto slice_of = [&](int npages, int k) __attribute__((always_inline)) {
+    const int n = slices_of(npages, k);
+    return n > 0 ? (int)((uint32_t)(npages + n - 1) / (uint32_t)n + 1) & ~1 : 1;
   };
   auto fits = [](float n, int most) { return n < 16777216.f ? n <= (float)most : n * 1.001f < (float)most; };
-  int chunk = a.chunk, most = a.splits;  // slices of a segment
-  if (a.few) {
-    chunk = 8;
-  } else if (!a.fixed) {
-    float t = (float)mine.rbs * (float)mine.npages, longest = (float)mine.npages;
-    for (int s = tid + threads; s < a.n_segments; s += threads) {
-      const Seg g = segment(s);
-      t += (float)g.rbs * (float)g.npages;
-      longest = fmaxf(longest, (float)g.npages);
+  const bool at_once = a.n_segments <= threads;
+  const int host = 31 - __builtin_clz(a.chunk);  // (of a power of two, unless a.fixed)
+  int k = a.few ? 3 : host;
+  float longest = (float)(a.chunk * a.splits);
+  if (!a.few && !a.fixed) {
+    Sums sums = {};
+    for (int s = tid; s < a.n_segments; s += threads) {
+      const Seg g = s == tid ? mine : segment(s);
+      sums.x += (float)g.rbs * (float)g.npages;
+      sums.y += (float)g.nr * (float)g.npages;
+      sums.top = fmaxf(sums.top, (float)g.npages);
     }
-    const Sums all = gather(t, longest, true);
-    const float pages = all.x * a.weight;
-    int c = pages < SEG_PAGES_16 ? 8 : pages < SEG_PAGES_32 ? 16 : pages < SEG_PAGES_64 ? 32 : pages < SEG_PAGES_128 ? 64 : 128;
-    for (; c < chunk; c *= 2) {
-      float items = 0.f, parts = 0.f;
+    sums = gather(sums);
+    longest = sums.top;
+    const float pages = sums.x * a.weight;
+    k = pages < (longest <= SEG_SHORT ? SEG_PAGES_16_SHORT : SEG_PAGES_16) ? 3 : pages < SEG_PAGES_32 ? 4 : pages < SEG_PAGES_64 ? 5 : pages < SEG_PAGES_128 ? 6 : 7;
+    for (; k < host; ++k) {
+      const float one = 1.f / (float)longest_slice(k);
+      if (!fits(sums.x * one, a.item_cap) || !fits(sums.y * one, room)) continue;
+      if (at_once) break;  // (the places tell)
+      Sums n = {};
       for (int s = tid; s < a.n_segments; s += threads) {
         const Seg g = s == tid ? mine : segment(s);
-        const int slice = slice_of(g.npages, c);
-        const float nsp = (float)((g.npages + slice - 1) / slice);
-        items += nsp * (float)g.rbs;
-        parts += nsp * (float)g.nr;
+        const float nsp = (float)slices_of(g.npages, k);
+        n.x += nsp * (float)g.rbs;
+        n.y += nsp * (float)g.nr;
       }
-      const Sums n = gather(items, parts, false);
+      n = gather(n);
       if (fits(n.x, a.item_cap) && fits(n.y, room)) break;
     }
-    chunk = c;
-    most = ((int)all.y + chunk - 1) / chunk;  // (at least; a segment of more than 2^24 pages is longer than any pool)
   }
   int start0 = 0, first0 = 0;  // items and partials of the segments in front
   for (int base = 0; base < a.n_segments; base += threads) {
     const int s = base + tid;
     const Seg g = base == 0 ? mine : segment(s);
-    const int slice = a.fixed ? chunk : slice_of(g.npages, chunk);
-    const int nsp = (g.npages + slice - 1) / slice, cnt = nsp * g.rbs, parts = nsp * g.nr;
-    const int incl = dag_wave_scan(cnt), pincl = dag_wave_scan(parts);
-    int start = start0 + incl - cnt, first = first0 + pincl - parts;
-    if (threads > 64) {
-      if (lane == 63) {
-        s_wave[0][w] = incl;
-        s_wave[1][w] = pincl;
+    int slice, nsp, cnt, parts, start, first;
+    for (;; ++k) {
+      slice = a.fixed ? a.chunk : slice_of(g.npages, k);
+      nsp = (int)((uint32_t)(g.npages + slice - 1) / (uint32_t)slice);
+      cnt = nsp * g.rbs;
+      parts = nsp * g.nr;
+      start = dag_wave_scan(cnt);
+      first = dag_wave_scan(parts);
+      int items = __builtin_amdgcn_readlane(start, 63), places = __builtin_amdgcn_readlane(first, 63);
+      start += start0 - cnt;
+      first += first0 - parts;
+      if (threads > 64) {
+        const uint32_t v = exchange(lane == 0 ? items : places);
+        const int front = dag_wave_sum<8>((lane & 15) < w ? (int)v : 0), sum = dag_wave_sum<8>((int)v);
+        start += __builtin_amdgcn_readlane(front, 0);
+        first += __builtin_amdgcn_readlane(front, 16);
+        items = __builtin_amdgcn_readlane(sum, 0);
+        places = __builtin_amdgcn_readlane(sum, 16);
       }
-      __syncthreads();
-      for (int i = 0; i < threads / 64; ++i) {
-        start += i < w ? s_wave[0][i] : 0;
-        first += i < w ? s_wave[1][i] : 0;
-        start0 += s_wave[0][i];
-        first0 += s_wave[1][i];
+      if (a.few || !at_once || k >= host || ((uint32_t)items <= (uint32_t)a.item_cap && (uint32_t)places <= (uint32_t)room)) {
+        start0 += items;
+        first0 += places;
+        break;
       }
-      if (base + threads < a.n_segments) __syncthreads();
-    } else {
-      start0 += __builtin_amdgcn_readlane(incl, 63);
-      first0 += __builtin_amdgcn_readlane(pincl, 63);
     }
     if (s < a.n_segments) {
-      int k = start;
+      int at = start;
       const int page_off = a.seg_page_off[s], code = a.fixed ? nsp : nsp | slice << 23;
       for (int sp = nsp - 1; sp >= 0; --sp)
-        for (int rb = 0; rb < g.rbs; ++rb, ++k)
-          if (k < a.item_cap) a.items[k] = SegItem{page_off, g.len, g.e0, g.nr * a.G, rb * 32, sp * slice, first + sp, code};
+        for (int rb = 0; rb < g.rbs; ++rb, ++at)
+          if (at < a.item_cap) a.items[at] = SegItem{page_off, g.len, g.e0, g.nr * a.G, rb * 32, sp * slice, first + sp, code};
       for (int e = 0; e < g.nr; ++e) {
         if (g.e0 + e >= 0 && g.e0 + e < a.total_readers) a.entry_first[g.e0 + e] = first + e * nsp;
         if (g.e0 + e == a.total_readers - 1) a.totals[1] = first + (e + 1) * nsp;
@@ -498,7 +508,8 @@ __global__ void __launch_bounds__(PLAN_THREADS) k_seg_plan(SegArgs a) {
   }
   if (tid == 0) {
     a.totals[0] = min(start0, a.item_cap);
-    a.totals[2] = most;
+    // most slices of a segment, at least (one of more than 2^24 pages is longer than any pool)
+    a.totals[2] = a.fixed || a.few ? a.splits : ((int)longest + (1 << k) - 1) >> k;
   }
 }
 
@@ -577,8 +588,8 @@ __global__ void __launch_bounds__(64, 2) k_decode_seg(SegArgs a) {
 }
 
 // Step 3: one wave per (branch, query head): log-sum-exp combination over the slices of every
-// segment the branch reads.  The branch's entries in the reader lists name its partials (and how
-// many slices each has); the lanes fetch the
+// segment the branch reads.  The branch's entries in the reader lists name its partials, which end
+// where those of the next entry begin; the lanes fetch the
 // (maximum, sum) pairs of up to 64 (entry, split) pairs at once, the wave agrees on the maximum
 // and the weights, and the weighted partial outputs are added pair by pair.  A branch without any
 // key gets zeros.
@@ -1811,7 +1822,8 @@ extern "C" int dag_attn_decode_segments(const dag_decode_seg_desc_t* d, const vo
   a.total_readers = d->total_readers;
   a.fixed = decode_knobs().chunk_seg > 0;
   a.weight = (float)hkv * (float)head_dim / 128.f;
-  a.few = !a.fixed && p.chunk == 8 && (int64_t)d->n_segments * p.rb_max * d->max_seg_pages * hkv * head_dim < SEG_PAGES_16 * 128;
+  const int64_t most_pages = (int64_t)d->n_segments * p.rb_max * d->max_seg_pages * hkv * head_dim;
+  a.few = !a.fixed && p.chunk == 8 && most_pages < (d->max_seg_pages <= SEG_SHORT ? SEG_PAGES_16_SHORT : SEG_PAGES_16) * 128;
   a.sc = softmax_scale * 1.4426950408889634f;
   a.th = ITEM_TH / a.sc;
   hipStream_t stream = (hipStream_t)stream_;

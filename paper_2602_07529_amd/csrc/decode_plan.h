@@ -43,7 +43,16 @@ inline bool whole_branches(int64_t base_w, int64_t base_b, int branches, int hkv
   if (dies > branches) dies = branches;
   return (dies - 1) * base_w * shared * D <= (one_block ? 1500 : 3000) * 128;
 }
-constexpr int SEG_PAGES_16 = 2048, SEG_PAGES_32 = 9216, SEG_PAGES_64 = 32768, SEG_PAGES_128 = 65536;
+// Decode over segments: k_seg_plan settles the slices, because the host knows the longest segment only and takes every other one for as
+// long.  Pages of 128 dimensions to be read (once for every row block) and the slices that were fastest over 150 frontiers of 200 to
+// 100,000 pages: 8 pages below 2,048, below 4,160 too if no segment has more than 96 (few partials to a branch: 11 x 12 leaves of 249 tokens
+// under segments of 90 and 44, 8 heads on one: 17.5 us in slices of 16, 15.4 so), 16 below 9,216, 32 below 32,768, 64 below 81,920, then 128 -- if the
+// lists have room for so many, which have the sizes that the host's slices ask for: else twice as long.  5 x 12 leaves under segments of 25 and 174 pages,
+// 24 / 4 heads: 60 us with the host's slices, 38 so.  A segment's slices have one length, from 32 pages on an eighth more than that if this
+// saves a slice (16 sequences of 254 to 258 | 2 x 126 to 130 | 8 x 63 to 67 pages: 227 -> 212 us); shorter ones are a chain of blocks
+// that is all a launch of so few consists of (12 branches over 34, 26 and 20 pages, 32 / 8 heads: slices of 18 pages 15.4 us, of 16 14.3).
+constexpr int SEG_PAGES_16 = 2048, SEG_PAGES_16_SHORT = 4160, SEG_SHORT = 96, SEG_PAGES_32 = 9216, SEG_PAGES_64 = 32768, SEG_PAGES_128 = 81920;
+constexpr int SEG_STRETCH = 32;
 // k_decode_merge: rows (branches x query heads) up to which a wave takes several partials to a load, 16 loads at a time
 constexpr int64_t MERGE_FEW_ROWS = 4096;
 constexpr size_t SEG_ITEM_BYTES = 32;  // of the list of work items

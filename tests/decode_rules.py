@@ -25,8 +25,9 @@ extern "C" int decode_rules(const dag_decode_desc_t* d, int hq, int hkv, int D, 
 extern "C" int segment_rules(const dag_decode_seg_desc_t* d, int hq, int hkv, int D, const int* knobs, double* out) {
   SegPlan p{};
   const int rc = make_seg_plan(d, hq, hkv, D, DecodeKnobs{knobs[0], knobs[1], knobs[2]}, &p);
-  const double v[] = {(double)p.rb_max, (double)p.chunk, (double)p.splits, (double)p.items, (double)p.off_total, (double)p.bytes};
-  for (int i = 0; i < 6; ++i) out[i] = v[i];
+  const double v[] = {(double)p.rb_max, (double)p.chunk, (double)p.splits, (double)p.items, (double)p.off_items, (double)p.off_total,
+                      (double)p.bytes};
+  for (int i = 0; i < 7; ++i) out[i] = v[i];
   return rc;
 }
 """
@@ -66,4 +67,11 @@ def step(groups, branches, shared_pages, own_pages, hq, hkv, d, **kw):
 
 def segments(desc, hq, hkv, d, knobs=(0, 0, 0)):
     """What the host settles for dag_attn_decode_segments."""
-    return _call(_lib().segment_rules, ("rb_max", "chunk", "splits", "items", "off_total", "bytes"), desc, hq, hkv, d, knobs)
+    return _call(_lib().segment_rules, ("rb_max", "chunk", "splits", "items", "off_items", "off_total", "bytes"), desc, hq, hkv, d, knobs)
+
+
+def listed_slices(plan, ws):
+    """{(first page-list position, first page): pages} of the work items that k_seg_plan left in a workspace (a uint8 array of the host)."""
+    n = int(ws[plan.off_total:plan.off_total + 4].view("int32")[0])
+    items = ws[plan.off_items:plan.off_items + 32 * n].view("int32").reshape(n, 8)
+    return {(int(i[0]), int(i[5])): int(i[7]) >> 23 & 0x1fe for i in items}

@@ -1,5 +1,9 @@
 """Helpers shared by the GPU parity tests: run the library through its binding, run the oracle on
 the same inputs, and compare to the stated tolerances."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import torch
 
@@ -154,3 +158,13 @@ def oracle_prefill(dag_list, q, k, v, theta, rows_per_seq=None, seed=0, heads=No
         rows_all.append(t0 + sel)
         t0 += Tb
     return ref, lse, np.concatenate(rows_all)
+
+
+def in_a_process_of_its_own(call, **env):
+    """Runs `call` ("module.function(arguments)" of the tests) with these environment variables, which the library reads once, at its
+    first decode call."""
+    module = call[:call.index("(")].rpartition(".")[0]
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", "import %s; %s" % (module, call)], cwd=root, env=dict(os.environ, **env), timeout=100,
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]

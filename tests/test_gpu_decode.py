@@ -6,13 +6,15 @@ import torch
 from oracle import dag_oracle as orc
 from paper_2602_07529_amd import binding as B
 from workloads import dags
-from tests.gpu_util import DEV, check_close
+from tests import decode_rules
+from tests.gpu_util import DEV, check_close, in_a_process_of_its_own
 
 pytestmark = pytest.mark.gpu
 
 
-def _gpu_decode(st, hq, hkv, d, theta, append=True):
+def _gpu_decode(st, hq, hkv, d, theta, append=True, route=None):
     dd = B.DecodeDesc(st["desc"], DEV)
+    assert route in (None, decode_rules.decode(dd.c, hq, hkv, d).route)
     kp, vp = st["k_pool"].to(DEV), st["v_pool"].to(DEV)
     if append:
         B.dag_kv_append_rope(dd, st["k_new"].to(DEV), st["v_new"].to(DEV), kp, vp, theta)
@@ -31,22 +33,26 @@ def _oracle_pools_after_append(st, theta):
     return kp, vp
 
 
-@pytest.mark.parametrize("hq,hkv,d,nb,shared,blens", [
-    (8, 2, 128, 3, 100, [17, 5, 32]),        # ragged shared context and tails
-    (32, 8, 128, 8, 512, [64] * 8),          # 32 rows per (group, kv head) like config 3
-    (10, 2, 128, 7, 48, [1, 2, 3, 16, 17, 31, 33]),   # G = 5; 35 rows -> two row blocks
-    (4, 4, 64, 2, 0, [40, 9]),               # no shared context at all, MHA, D = 64
-    (16, 2, 128, 1, 33, [1]),                # a single branch whose own context is just its token
-    (12, 2, 64, 9, 200, [3, 40, 16, 1, 7, 64, 33, 2, 20]),   # G = 6; 54 rows -> two row blocks, D = 64
-    (24, 2, 128, 11, 77, [5] * 11),          # G = 12; 132 rows -> five row blocks, the last one partly filled
-    (12, 2, 128, 30, 330, [3, 17, 1] * 10),  # G = 6; 180 rows -> six row blocks: two of them split over wave pairs
-    (10, 2, 64, 16, 1000, [2] * 16),         # G = 5; 160 rows -> five row blocks at D = 64, 63 pages of shared context
+@pytest.mark.parametrize("hq,hkv,d,nb,shared,blens,route", [
+    (8, 2, 128, 3, 100, [17, 5, 32], "whole"),        # ragged shared context and tails
+    (32, 8, 128, 8, 512, [64] * 8, "whole"),          # 32 rows per (group, kv head) like config 3
+    (10, 2, 128, 7, 48, [1, 2, 3, 16, 17, 31, 33], "whole"),   # G = 5; 35 rows -> two row blocks
+    (4, 4, 64, 2, 0, [40, 9], "whole"),               # no shared context at all, MHA, D = 64
+    (16, 2, 128, 1, 33, [1], "whole"),                # a single branch whose own context is just its token
+    (12, 2, 64, 9, 200, [3, 40, 16, 1, 7, 64, 33, 2, 20], "whole"),   # G = 6; 54 rows -> two row blocks, D = 64
+    (24, 2, 128, 11, 77, [5] * 11, "items"),          # G = 12; 132 rows -> five row blocks, the last one partly filled
+    (12, 2, 128, 30, 330, [3, 17, 1] * 10, "whole"),  # G = 6; 180 rows -> six row blocks
+    (10, 2, 64, 16, 1000, [2] * 16, "whole"),         # G = 5; 80 rows -> three row blocks at D = 64, 63 pages of shared context
+    (8, 2, 128, 3, 1000, [17, 5, 32], "items"),       # a row block, ragged shared context and tails
+    (24, 2, 128, 11, 4200, [5] * 11, "wide"),         # five row blocks: the last one over four waves
+    (12, 2, 128, 30, 4300, [3, 17, 1] * 10, "wide"),  # six: two of them split over wave pairs
+    (10, 2, 64, 16, 4100, [2] * 16, "wide"),          # three at D = 64
 ])
-def test_decode_small_cases_all_branches(hq, hkv, d, nb, shared, blens):
+def test_decode_small_cases_all_branches(hq, hkv, d, nb, shared, blens, route):
     st = dags.decode_state(500 + hq + nb, n_seqs=2, n_branches=nb, shared_len=shared, branch_len=0,
                            hq=hq, hkv=hkv, d=d, branch_len_list=blens * 2)
     theta = 5e5
-    out, kp, vp = _gpu_decode(st, hq, hkv, d, theta)
+    out, kp, vp = _gpu_decode(st, hq, hkv, d, theta, route=route)
     okp, ovp = _oracle_pools_after_append(st, theta)
     # appended keys: GPU pool equals the oracle's rotated key rounded to bf16 (tolerance of one rounding)
     check_close(kp, okp, torch.bfloat16, "k pool after append")
@@ -57,15 +63,21 @@ def test_decode_small_cases_all_branches(hq, hkv, d, nb, shared, blens):
 
 
 @pytest.mark.parametrize("hq,hkv,nb", [(8, 2, 3), (10, 2, 8)])
-def test_decode_long_slices_cross_the_page_id_window(monkeypatch, hq, hkv, nb):
+def test_decode_long_slices_cross_the_page_id_window(hq, hkv, nb):
     """Slices of more than 64 pages (forced through the development knobs; the default plan cuts a
     small batch into short slices): the kernels fetch page ids 64 at a time, here they have to
     move on to a second and a third window.  Narrow group (12 rows) and wide group (40 rows)."""
-    monkeypatch.setenv("DAGATTN_DECODE_CHUNK_A", "200")
-    monkeypatch.setenv("DAGATTN_DECODE_CHUNK_B", "200")
+    in_a_process_of_its_own("tests.test_gpu_decode.check_long_slices(%d, %d, %d)" % (hq, hkv, nb),
+                            DAGATTN_DECODE_CHUNK_A="200", DAGATTN_DECODE_CHUNK_B="200")
+
+
+def check_long_slices(hq, hkv, nb):
     d, theta = 128, 5e5
     st = dags.decode_state(900 + hq, n_seqs=1, n_branches=nb, shared_len=150 * 16 + 5, branch_len=70 * 16 + 3,
                            hq=hq, hkv=hkv, d=d)
+    plan = decode_rules.decode(B.DecodeDesc(st["desc"], DEV).c, hq, hkv, d, knobs=(200, 200, 0))   # (at most 128 pages in a wide group)
+    assert (plan.route, plan.chunk_a, plan.chunk_b) == ("items", 200 if nb * hq // hkv <= 32 else 128, 200)
+    assert plan.bytes == B.dag_decode_workspace_bytes(B.DecodeDesc(st["desc"], DEV), hq, hkv, d)
     out, kp, vp = _gpu_decode(st, hq, hkv, d, theta)
     ref = orc.attn_decode(st["desc"], dags.to_f64(st["q"]), dags.to_f64(kp), dags.to_f64(vp))
     check_close(out, ref, torch.bfloat16, "decode out, long slices")
@@ -120,8 +132,8 @@ def test_decode_growing_branches_over_steps_config5_shape_reduced():
 
 
 def test_decode_256_steps_of_growing_branches_every_branch_every_step():
-    """A run of decode steps as the execution phase makes them (config-3 shape at a reduced context:
-    two sibling groups of 8 branches, G = 4): every step appends one token per branch (a fresh page
+    """A run of decode steps as the execution phase makes them (config-3 shape at a reduced context, one launch
+    a step: two sibling groups of 8 branches, G = 4): every step appends one token per branch (a fresh page
     whenever a tail page is full: sixteen times per branch here), decodes, and every branch is
     checked against the oracle on the pools as they stand; 256 steps, the length of a decode run of
     the benchmark configurations."""
@@ -219,11 +231,14 @@ def test_decode_config5_every_branch_of_one_kv_head():
     check_close(out[:, 30:35], ref[:, 30:35], torch.bfloat16, "config 5 decode, kv head 6")
 
 
-@pytest.mark.parametrize("hq,hkv,d,nb,shared,blens", [
-    (8, 2, 128, 3, 100, [17, 5, 32]),             # single-wave items, ragged shared context and tails
-    (10, 2, 128, 16, 1000, [2, 19, 33, 16] * 4),  # 80 stacked rows: the wide kernel for the shared context
+@pytest.mark.parametrize("hq,hkv,d,nb,shared,blens,route", [
+    (8, 2, 128, 3, 100, [17, 5, 32], "whole"),             # a workgroup to a branch, ragged shared context and tails
+    (10, 2, 128, 16, 1000, [2, 19, 33, 16] * 4, "items"),  # 80 stacked rows in single-wave items
+    (8, 2, 128, 3, 1000, [17, 5, 32], "items"),            # a row block
+    (10, 2, 128, 16, 4501, [2, 19, 33, 16] * 4, "wide"),   # the wide kernel for the shared context and, beside it, for the own pages
+    (10, 2, 64, 16, 4509, [2, 19, 33, 16] * 4, "wide"),
 ])
-def test_decode_ignores_non_finite_bits_in_unused_slots(hq, hkv, d, nb, shared, blens):
+def test_decode_ignores_non_finite_bits_in_unused_slots(hq, hkv, d, nb, shared, blens, route):
     """The slots of a partly filled last page that hold no token yet (and pages of the pool that
     belong to nobody) carry NaN and infinity bit patterns: no result may depend on them."""
     st = dags.decode_state(900 + nb, n_seqs=2, n_branches=nb, shared_len=shared, branch_len=0,
@@ -248,7 +263,7 @@ def test_decode_ignores_non_finite_bits_in_unused_slots(hq, hkv, d, nb, shared, 
     assert len(unused) == 2
     kp[unused] = float("nan")
     vp[unused] = float("nan")
-    out, kpd, vpd = _gpu_decode(st, hq, hkv, d, 5e5, append=False)
+    out, kpd, vpd = _gpu_decode(st, hq, hkv, d, 5e5, append=False, route=route)
     assert torch.isfinite(out.float()).all()
     ref = orc.attn_decode(desc, dags.to_f64(st["q"]), dags.to_f64(kpd), dags.to_f64(vpd))
     check_close(out, ref, torch.bfloat16, "decode with poisoned unused slots")

@@ -7,7 +7,8 @@ import torch
 from oracle import dag_oracle as orc
 from paper_2602_07529_amd import binding as B
 from workloads import dags
-from tests.gpu_util import DEV, check_close
+from tests import decode_rules
+from tests.gpu_util import DEV, check_close, in_a_process_of_its_own
 
 pytestmark = pytest.mark.gpu
 
@@ -76,15 +77,25 @@ def test_many_readers_stack_into_several_row_blocks():
     check_close(out, ref, torch.bfloat16, "wide segment decode out")
 
 
-def test_long_segments_cross_the_page_id_window_and_several_splits(monkeypatch):
+def _slices_are(pages, desc, hq, hkv, d):
+    sd = B.SegDecodeDesc(desc, DEV)
+    plan = decode_rules.segments(sd.c, hq, hkv, d, knobs=(0, 0, pages))
+    assert plan.chunk == pages and plan.bytes == B.dag_decode_segments_workspace_bytes(sd, hq, hkv, d)
+
+
+def test_long_segments_cross_the_page_id_window_and_several_splits():
     """A 2,500-token root (157 pages) in slices of 70 pages: page ids are fetched 64 at a time and
     a slice crosses a window; the last slice is short and ends in a partly filled page."""
-    monkeypatch.setenv("DAGATTN_DECODE_CHUNK_SEG", "70")
+    in_a_process_of_its_own("tests.test_gpu_decode_segments.check_long_segments()", DAGATTN_DECODE_CHUNK_SEG="70")
+
+
+def check_long_segments():
     hq, hkv, d = 8, 2, 128
     parents = [[], [0], [0], [1, 2]]
     L = np.asarray([2500, 1130, 17, 3], dtype=np.int32)
     anc = dags.bits_from_sets(dags.closure_from_parents(parents))
     st = dags.decode_segments_state(43, [(L, anc)], [[3, 1]], hq, hkv, d, kv_scale=0.7, q_scale=0.7)
+    _slices_are(70, st["desc"], hq, hkv, d)
     out = _gpu_decode_segments(st["desc"], st["q"], st["k_pool"], st["v_pool"], hq, hkv, d)
     ref = orc.attn_decode_segments(st["desc"], dags.to_f64(st["q"]), dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"]))
     check_close(out, ref, torch.bfloat16, "long segment decode out")
@@ -157,15 +168,19 @@ def test_incremental_prefill_of_new_nodes_against_the_cached_context(hq, hkv, d,
     check_close(out, ref, torch.bfloat16, "incremental prefill out")
 
 
-def test_incremental_prefill_in_slices_equals_the_prefill_kernel(monkeypatch):
+def test_incremental_prefill_in_slices_equals_the_prefill_kernel():
     """A 700-token node prefilled whole against a 1,000-token parent, in page slices of 20 (so
     that slices lie entirely past the first rows' limits): against the oracle and against the
     prefill kernel's rows for the same tokens."""
+    in_a_process_of_its_own("tests.test_gpu_decode_segments.check_incremental_prefill()", DAGATTN_DECODE_CHUNK_SEG="20")
+
+
+def check_incremental_prefill():
     from tests.gpu_util import run_prefill
-    monkeypatch.setenv("DAGATTN_DECODE_CHUNK_SEG", "20")
     hq, hkv, d = 4, 1, 128
     dag = dags.linear_chain([1000, 700])
     st = dags.decode_segments_state(81, [dag], [[1]], hq, hkv, d, kv_scale=0.7, q_scale=0.7, new_tokens=[[700]])
+    _slices_are(20, st["desc"], hq, hkv, d)
     out = _gpu_decode_segments(st["desc"], st["q"], st["k_pool"], st["v_pool"], hq, hkv, d)
     rows = [0, 1, 15, 16, 17, 319, 320, 321, 350, 698, 699]
     ref = orc.attn_decode_segments(st["desc"], dags.to_f64(st["q"]), dags.to_f64(st["k_pool"]), dags.to_f64(st["v_pool"]),

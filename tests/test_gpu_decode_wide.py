@@ -13,25 +13,30 @@ from tests.gpu_util import DEV, check_close
 pytestmark = pytest.mark.gpu
 
 
-# 32 groups x 8 KV heads: a workgroup has the whole shared list of a group, 128 pages at most
-@pytest.mark.parametrize("nb,group,shared", [
-    (9, 4, 2048), (9, 4, 2001), (9, 4, 63),          # two row blocks, two waves each: 32 tiles; 31 and a ragged one; no whole tile
-    (12, 6, 129), (12, 6, 192),                      # three: an even number of tiles and a token; an odd number
-    (16, 8, 64), (16, 8, 1024), (16, 8, 1087),       # four, all rows used
-    (20, 8, 64), (20, 8, 65), (20, 8, 2048),         # five: the last one over four waves
-    (23, 8, 128), (23, 8, 1999),                     # six: the last two over two waves each, partly filled
-    (28, 8, 191), (32, 8, 1), (32, 8, 2032),         # seven and eight, a wave each
+# 32 groups x 8 KV heads: a workgroup has the whole shared list of a group, 128 pages at most.  Own contexts of a token to three; of 94 to
+# 96 where the shared lists are so little work that single waves would take them.
+@pytest.mark.parametrize("nb,group,shared,own", [
+    (9, 4, 2048, 3), (9, 4, 2001, 3), (9, 4, 63, 3),     # two row blocks, two waves each: 32 tiles; 31 and a ragged one; single waves
+    (12, 6, 129, 3), (12, 6, 192, 3),                    # three: an even number of tiles and a token; an odd number; at dimension 64 single waves
+    (16, 8, 64, 3), (16, 8, 1024, 3), (16, 8, 1087, 3),  # four, all rows used; the first by single waves
+    (20, 8, 64, 3), (20, 8, 65, 3), (20, 8, 2048, 3),    # five: the last one over four waves; the first, at dimension 64 the second, by single waves
+    (23, 8, 128, 3), (23, 8, 1999, 3),                   # six: the last two over two waves each, partly filled
+    (28, 8, 191, 3), (32, 8, 1, 3), (32, 8, 2032, 3),    # seven and eight, a wave each; one token at dimension 64 by single waves
+    (9, 4, 63, 96), (12, 6, 129, 96), (12, 6, 192, 96),  # no whole tile; and the short ones above, by the wide kernel
+    (16, 8, 64, 96), (20, 8, 64, 96), (20, 8, 65, 96), (32, 8, 1, 96),
 ])
 @pytest.mark.parametrize("d,growth", [(128, 1.0), (64, 8.0)])
-def test_wide_groups_at_every_number_of_row_blocks(nb, group, shared, d, growth):
+def test_wide_groups_at_every_number_of_row_blocks(nb, group, shared, own, d, growth):
     hkv, groups, head, g = 8, 32, 5, 17
     hq = hkv * group
-    st = dags.decode_state(nb + shared, groups, nb, shared, 1, hq, hkv, d, branch_len_list=[1 + r % 3 for r in range(groups * nb)])
+    st = dags.decode_state(nb + shared, groups, nb, shared, 1, hq, hkv, d, branch_len_list=[own - 2 + r % 3 for r in range(groups * nb)])
     desc = st["desc"]
     for g0 in range(groups):  # keys of the later pages have `growth` times the scores of the earlier ones
         pages = desc["shared_pages"][desc["shared_page_off"][g0]:desc["shared_page_off"][g0 + 1]]
         st["k_pool"][torch.from_numpy(np.ascontiguousarray(pages[len(pages) // 3:])).long()] *= growth
     dd = B.DecodeDesc(desc, DEV)
+    narrow = own < 16 and -(-nb * group // 32) * -(-shared // 16) * d <= 22 * 128 and nb * d <= 25 * 128   # 5632 shared and 6400 own pages in all
+    assert decode_rules.decode(dd.c, hq, hkv, d).route == ("items" if narrow else "wide")
     kp, vp, q = st["k_pool"].to(DEV), st["v_pool"].to(DEV), st["q"].to(DEV)
     out = torch.full_like(q, float("nan"))
     ws = torch.empty(B.dag_decode_workspace_bytes(dd, hq, hkv, d), dtype=torch.uint8, device=DEV)

@@ -7,6 +7,7 @@ import torch
 
 from paper_2602_07529_amd import binding as B
 from workloads import dags
+from tests import decode_rules
 from tests.gpu_util import DEV, build_meta
 
 pytestmark = pytest.mark.gpu
@@ -50,11 +51,16 @@ def test_prefill_prepare_and_attention_in_a_graph(hq, hkv):
     _capture_and_replay(step, out)
 
 
-@pytest.mark.parametrize("hq,hkv,nb", [(8, 2, 4), (10, 2, 7)])   # 16 stacked rows; 35 rows -> wide groups
-def test_decode_step_in_a_graph(hq, hkv, nb):
+@pytest.mark.parametrize("hq,hkv,nb,shared,route", [
+    (8, 2, 4, 300, "whole"), (10, 2, 7, 300, "whole"),   # 16 and 35 stacked rows over a short context: one launch
+    (8, 2, 4, 1500, "items"),                            # single waves and the merge
+    (10, 2, 7, 4500, "wide"),                            # 35 rows: wide groups
+])
+def test_decode_step_in_a_graph(hq, hkv, nb, shared, route):
     d = 128
-    st = dags.decode_state(700 + hq, n_seqs=2, n_branches=nb, shared_len=300, branch_len=45, hq=hq, hkv=hkv, d=d)
+    st = dags.decode_state(700 + hq, n_seqs=2, n_branches=nb, shared_len=shared, branch_len=45, hq=hq, hkv=hkv, d=d)
     dd = B.DecodeDesc(st["desc"], DEV)
+    assert decode_rules.decode(dd.c, hq, hkv, d).route == route
     kp, vp = st["k_pool"].to(DEV), st["v_pool"].to(DEV)
     k_new, v_new, q = st["k_new"].to(DEV), st["v_new"].to(DEV), st["q"].to(DEV)
     out = torch.zeros_like(q)

@@ -8,6 +8,7 @@ import torch
 from oracle import dag_oracle as orc
 from paper_2602_07529_amd import binding as B
 from workloads import dags
+from tests import decode_rules
 from tests.gpu_util import DEV, check_close, oracle_prefill, run_prefill
 
 pytestmark = pytest.mark.gpu
@@ -30,12 +31,14 @@ def test_prefill_batches_of_ragged_random_dags(hq, hkv, d):
 
 @pytest.mark.parametrize("hq,hkv,d,nb,shared,own", [(40, 8, 128, 32, 513, 17), (15, 3, 64, 8, 1000, 333),
                                                     (32, 4, 128, 5, 2049, 1), (24, 1, 128, 2, 300, 300),
-                                                    (64, 2, 64, 3, 129, 65), (18, 2, 128, 4, 16, 16)])
+                                                    (64, 2, 64, 3, 129, 65), (18, 2, 128, 4, 16, 16),
+                                                    (24, 1, 128, 2, 4100, 300), (64, 2, 64, 3, 4500, 65), (40, 8, 128, 8, 4200, 17)])
 def test_decode_odd_group_shapes_every_branch(hq, hkv, d, nb, shared, own):
-    """Three sibling groups each: 160, 40, 40, 48, 96 and 36 stacked rows per KV head (wide and
-    narrow), contexts that end inside a page, a block, a slice."""
+    """Three sibling groups each: 160, 40, 40, 48, 96 and 36 stacked rows per KV head (single waves, a workgroup to a
+    branch), 48, 96 and 40 (wide groups), contexts that end inside a page, a block, a slice."""
     st = dags.decode_state(900 + hq + nb, 3, nb, shared, own, hq, hkv, d, kv_scale=0.5, q_scale=0.5)
     dd = B.DecodeDesc(st["desc"], DEV)
+    assert (decode_rules.decode(dd.c, hq, hkv, d).route == "wide") == (shared > 4096)
     kp, vp = st["k_pool"].to(DEV), st["v_pool"].to(DEV)
     B.dag_kv_append_rope(dd, st["k_new"].to(DEV), st["v_new"].to(DEV), kp, vp, 5e5)
     qd = st["q"].to(DEV)
