@@ -691,7 +691,6 @@ __global__ void __launch_bounds__(64) k_decode_seg_merge(SegArgs a) {
 // 4 .. 7 share what is left, one half of every tile each (six) or of every second one (five): 105 -> 99 us.
 // 2 groups of 32 siblings x 5 heads on 8 KV heads, 32 K shared and 640 own tokens (436 MB): 128 us with units in
 // read - wait - multiply phases by ten waves, 91 us so = 4.8 TB/s; the matrix pipes need 17 us of it.
-constexpr int WIDE_TILE_PAGES = 4;
 constexpr int WIDE_RING = 4;         // tiles in the K ring and in the V ring
 // dynamic LDS of a launch: the rings, or the query operands and the partials of the own items
 inline int wide_lds_bytes(int G, int D, int own) {

@@ -13,6 +13,7 @@ constexpr float ITEM_TH = 3.f;
 
 constexpr int WIDE_WAVES = 8;          // k_decode_wide: waves of a workgroup, two per SIMD
 constexpr int WIDE_MAX_BLOCKS = 8;     // row blocks of a workgroup
+constexpr int WIDE_TILE_PAGES = 4;     // of a tile of the pipeline: what a slice has beyond whole ones is a unit by itself
 constexpr int WIDE_MAX_PAGES = 128;    // of a shared slice: its page ids sit in two registers
 constexpr int WIDE_LDS_BYTES = 160 * 1024;
 // LDS of workgroups with own pages: the query operands and the partials of their items
@@ -93,6 +94,8 @@ constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES 
 // pages as shared ones: fewer partials.  If the longest slices there are still make more than WIDE_GROUPS workgroups, they are as
 // short as a workgroup for every unit makes them (12 groups of 19 over 11,129 tokens, 8 / 2 heads: 77 -> 66 us), and the
 // shorter slices stay where their workgroups have room at once and these do not (29 siblings over 936 and 574 tokens, 48 / 8 heads: 29.8 -> 25.6).
+// Whole tiles: half a tile more (2 groups of 10 over 6,598 and 969 tokens, 12 / 2 heads: slices of 14 pages 21.3 us, of 16 19.7; 180 shapes
+// 1.005 times as fast, 0.98 at least).
 // 180 random shapes against the slices that `bytes` is for: dimension 64 1.11 times as fast on average (0.91 to 1.42), 128 1.15
 // (0.99 to 1.55); with a hundred workgroups and 16 pages at least everywhere 1.04 (0.79 to 1.37) and 1.11 (0.85 to 1.43).
 // Longer slices have fewer references, and probabilities lose less to 16 bits the nearer the reference is to their maximum, so where
@@ -184,6 +187,7 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     const int64_t shared_time = 120 + (D == 64 ? 5 : 7) * (int64_t)la;
     if (base_w * dag_ceil_div(shared, la) > beside && 8 * own_time > 5 * shared_time && beside >= WIDE_BESIDE) la = slice(beside);
     if (la < 16 && (dag_ceil_div(shared, 8) > 64 || base_b * own >= 2 * base_w * shared)) la = 16;
+    if (la > 8) la = (la + WIDE_TILE_PAGES - 1) / WIDE_TILE_PAGES * WIDE_TILE_PAGES;
     if (la < ca) la = ca;
     auto together = [&](int xa, int xb) {
       const int64_t n = base_b * dag_ceil_div(own, xb);
@@ -209,8 +213,8 @@ struct SegPlan {
   size_t off_o, off_ml, off_items, off_total, off_first, bytes;
 };
 
-// One split size for all segments (their lengths live in device memory): as long as possible
-// while the launch still has about a thousand items if every segment were the longest one.
+// What the lists have room for: one split size for all segments (their lengths live in device memory), as long as possible while the
+// launch still has about a thousand items if every segment were the longest one.  k_seg_plan settles the slices that are taken.
 inline int make_seg_plan(const dag_decode_seg_desc_t* d, int hq, int hkv, int D, const DecodeKnobs& knobs, SegPlan* p) {
   if (!d) return DAG_ERR_NULL;
   if (d->n_live < 0 || d->n_segments < 0 || d->max_seg_pages < 0 || d->max_readers < 0 || d->total_readers < 0)
