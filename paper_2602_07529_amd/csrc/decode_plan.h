@@ -94,6 +94,8 @@ constexpr int NARROW_CONTEXT_PAGES = 256, NARROW_PAGES = 5632, NARROW_OWN_PAGES 
 // pages as shared ones: fewer partials.  If the longest slices there are still make more than WIDE_GROUPS workgroups, they are as
 // short as a workgroup for every unit makes them (12 groups of 19 over 11,129 tokens, 8 / 2 heads: 77 -> 66 us), and the
 // shorter slices stay where their workgroups have room at once and these do not (29 siblings over 936 and 574 tokens, 48 / 8 heads: 29.8 -> 25.6).
+// A quarter longer at most where the merge has a round less to go (31 siblings over 19,910 and 125 tokens, 8 / 2 heads of dimension 64: 65 partials 19.2 us,
+// 54 17.6; 200 shapes 1.002 times as fast, 0.97 at least).
 // Whole tiles: half a tile more (2 groups of 10 over 6,598 and 969 tokens, 12 / 2 heads: slices of 14 pages 21.3 us, of 16 19.7; 180 shapes
 // 1.005 times as fast, 0.98 at least).
 // 180 random shapes against the slices that `bytes` is for: dimension 64 1.11 times as fast on average (0.91 to 1.42), 128 1.15
@@ -153,6 +155,7 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
             (shared > NARROW_CONTEXT_PAGES || base_a * shared * D > NARROW_PAGES * 128 || base_b * own * D > NARROW_OWN_PAGES * 128);
   p->th = 8.f;
   p->settle = 1024.f;
+  const int round = (int64_t)d->n_live * hq > MERGE_FEW_ROWS ? 16 : D == 128 ? 32 : 64;  // partials that the merge takes at a time
   if (!p->wide) {
     // Single waves: a slice takes a microsecond for two of its pages, so longer ones pay where the merge goes round once less (509 shared and
     // 43 own pages of one sequence, 75 partials and 59: 17.2 -> 15.4 us; 92 and 81, 33 and 24: 13.1 -> 12.0; where it does not, slices of ten
@@ -160,7 +163,6 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     // which is a partial as large as any, where they have 16 pages or more (91 and 18 pages of 117 branches, 16 / 8 heads: 61.4 -> 53.7;
     // slices that are merely fewer: 0.97 to 1.01).
     if (!knobs.chunk_a) ca = halved(128, 8, base_a, shared, 512);
-    const int round = (int64_t)d->n_live * hq > MERGE_FEW_ROWS ? 16 : D == 128 ? 32 : 64;
     auto rounds = [&](int xa, int xb) { return dag_ceil_div(dag_ceil_div(shared, xa) + dag_ceil_div(own, xb), round); };
     auto joined = [&](int pages, int c) { return c >= 16 && pages > c && pages % c > 0 && pages % c <= c / 8 ? even(dag_ceil_div(pages, pages / c)) : c; };
     const int la = longer(shared, ca), lb = longer(own, cb);
@@ -187,7 +189,11 @@ inline int make_plan(const dag_decode_desc_t* d, int hq, int hkv, int D, const D
     const int64_t shared_time = 120 + (D == 64 ? 5 : 7) * (int64_t)la;
     if (base_w * dag_ceil_div(shared, la) > beside && 8 * own_time > 5 * shared_time && beside >= WIDE_BESIDE) la = slice(beside);
     if (la < 16 && (dag_ceil_div(shared, 8) > 64 || base_b * own >= 2 * base_w * shared)) la = 16;
-    if (la > 8) la = (la + WIDE_TILE_PAGES - 1) / WIDE_TILE_PAGES * WIDE_TILE_PAGES;
+    auto tiles = [](int64_t c) { return (c + WIDE_TILE_PAGES - 1) / WIDE_TILE_PAGES * WIDE_TILE_PAGES; };
+    const int64_t own_slices = dag_ceil_div(own, lb), room = (dag_ceil_div(shared, la) + own_slices - 1) / round * round - own_slices;
+    const int64_t fewer = room > 0 ? tiles(dag_ceil_div(shared, room)) : 0;  // pages of slices with which the merge goes round once less
+    if (fewer > la && fewer <= la + la / 4 && fewer <= WIDE_MAX_PAGES) la = (int)fewer;
+    if (la > 8) la = (int)tiles(la);
     if (la < ca) la = ca;
     auto together = [&](int xa, int xb) {
       const int64_t n = base_b * dag_ceil_div(own, xb);

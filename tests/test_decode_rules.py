@@ -24,7 +24,10 @@ def test_the_rules_are_those_of_the_library():
     (8, 17, 1488, 4, 8, 2, 64, (16, 96, 1, 64), True),       # a workgroup for every compute unit, not half of them in slices of 128
     (7, 21, 706, 29, 20, 4, 64, (9, 80, 1, 64), True),
     (3, 20, 395, 7, 32, 8, 128, (5, 80, 1, 64), True),       # 120 workgroups
-    (1, 22, 817, 13, 8, 4, 128, (30, 28, 3, 6), True),       # 120, slices of whole tiles
+    (1, 22, 817, 13, 8, 4, 128, (26, 32, 3, 6), True),       # 104: 33 partials would be two rounds of the merge
+    (1, 22, 817, 10, 8, 4, 128, (30, 28, 2, 6), True),       # 120: 32 are one
+    (2, 20, 976, 57, 16, 2, 128, (28, 36, 4, 16), True),     # 112: 35 would be two
+    (1, 31, 1245, 8, 8, 2, 64, (52, 24, 2, 4), True),        # 65 at dimension 64
     (2, 23, 335, 9, 5, 1, 64, (42, 8, 2, 6), False),         # few workgroups with little each: slices of eight pages
     (2, 21, 1091, 9, 3, 1, 128, (55, 20, 2, 6), True),       # 55 workgroups to a group
     (12, 14, 241, 75, 5, 1, 128, (7, 36, 2, 38), True),      # 84 workgroups beside 168 with own pages

@@ -50,11 +50,11 @@ def test_workspace_sizes_follow_the_shorter_slices():
     (3, 32, 8, 1, 1300, 17, ("items", "items")),
     (2, 11, 6, 2, 4096, 65, ("items", "items")),     # 256 shared pages, the longest context of single waves
     (2, 11, 6, 2, 4097, 65, ((22, 12), (22, 12))),   # one more
-    (1, 12, 3, 1, 20000, 30, ((79, 16), (79, 16))),  # slices of eight pages would be more than 64
+    (1, 12, 3, 1, 20000, 30, ((63, 20), (63, 20))),  # slices of eight pages would be more than 64, of 16 more than two rounds of the merge
     (1, 20, 8, 2, 9999, 5, ((40, 16), (40, 16))),    # five row blocks
     (4, 24, 8, 1, 6007, 130, ((32, 12), (32, 12))),  # six; 128 workgroups
     (2, 9, 4, 1, 2500, 7000, ("items", (10, 16))),   # own pages of k_decode_wide in longer slices
-    (1, 22, 2, 4, 13072, 200, ((30, 28), (30, 28))),
+    (1, 22, 2, 4, 13072, 200, ((30, 28), (26, 32))),
     (3, 20, 4, 8, 6320, 100, ((10, 40), (5, 80))),   # a workgroup for every unit at dimension 64, half of them at 128
     (12, 19, 4, 2, 11129, 440, ((10, 72), (10, 72))),   # 128 pages would be too many workgroups: of one length for every unit
     (12, 14, 5, 1, 3849, 1181, ("items", (7, 36))),  # as many as fit beside the own pages
