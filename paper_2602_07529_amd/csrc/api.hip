@@ -58,6 +58,8 @@ int prefill_args(const dag_meta_t* m, const void* q, const void* k, const void* 
   a->node_tok_start = m->node_tok_start;
   a->total_tokens = m->sizes.total_tokens;
   a->total_nodes = m->sizes.total_nodes;
+  a->pack_heads = pack_heads_of(hq / hkv, head_dim);
+  a->pack_rows = a->pack_heads > 0 ? 32 * PACK_WAVES(head_dim) / a->pack_heads : 0;
   a->node_runs = nullptr;
   if (need > 0 && m->node_tok_start && a->total_nodes > 0 && m->words_per_node <= 2 &&
       prefill_node_table_bytes(a->total_tokens, a->total_nodes) <=
@@ -122,7 +124,10 @@ extern "C" int dag_attn_prefill_prepared(const dag_meta_t* m, const void* q, con
   if (rc != DAG_OK || empty) return rc;
   hipStream_t stream = (hipStream_t)stream_;
   if (dtype == DAG_F32) return launch_prefill_f32(a, head_dim, stream);
-  if (!prefill_on_chunks(a, head_dim) || !writes_v(a, head_dim)) return launch_prefill_bf16(a, head_dim, stream);
+  if (!prefill_on_chunks(a, head_dim) || !writes_v(a, head_dim)) {
+    const int rt = launch_prefill_pack_tables(a, head_dim, stream);
+    return rt != DAG_OK ? rt : launch_prefill_bf16(a, head_dim, stream);
+  }
   PrefillArgs tiles = a;  // the copy of V first; behind it the workspace becomes again what it was
   tiles.node_runs = nullptr;
   int rp = launch_prefill_bf16_prepare_v(tiles, head_dim, stream);

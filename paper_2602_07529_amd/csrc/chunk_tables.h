@@ -118,7 +118,7 @@ __device__ __forceinline__ void token_depths(const PrefillArgs& a, int64_t t0) {
   }
 }
 
-// The tables of several chunk sizes are built together (bit i of `sizes`: those of DAG_CHUNK_ROWS[i] rows;
+// The tables of several chunk sizes are built together (bit i of `sizes`: those of DAG_CHUNK_ROWS[i] rows, the last bit those of pack_rows;
 // blockIdx.y, in the small form blockIdx.x, counts the set bits).  The prefill builds all of them whatever the
 // launch behind it takes: the head counts of a call may differ from those that its workspace was prepared for.
 // What the sizes share by the blocks of the first one: the runs, the work counters of the attention kernel,
@@ -127,10 +127,10 @@ __device__ __forceinline__ int nth_size(int sizes, int n) {
   for (; n > 0; --n) sizes &= sizes - 1;
   return __builtin_ctz(sizes);
 }
-__device__ __forceinline__ ChunkTables tables_of(const PrefillArgs& a, int i) { return i == 0 ? a.chunk[0] : i == 1 ? a.chunk[1] : a.chunk[2]; }
-__device__ __forceinline__ int rows_of(int i) { return DAG_CHUNK_ROWS[0] << i; }
+__device__ __forceinline__ ChunkTables tables_of(const PrefillArgs& a, int i) { return i == 0 ? a.chunk[0] : i == 1 ? a.chunk[1] : i == 2 ? a.chunk[2] : a.chunk[3]; }
+__device__ __forceinline__ int rows_of(const PrefillArgs& a, int i) { return i == DAG_CHUNK_PACK ? a.pack_rows : DAG_CHUNK_ROWS[0] << i; }
 __device__ __forceinline__ int slots_of(const PrefillArgs& a, int i) {  // = chunk_slots
-  return (int)(a.total_tokens >> (__builtin_ctz(DAG_CHUNK_ROWS[0]) + i)) + (int)a.total_nodes;
+  return (i == DAG_CHUNK_PACK ? (int)a.total_tokens / a.pack_rows : (int)(a.total_tokens >> (__builtin_ctz(DAG_CHUNK_ROWS[0]) + i))) + (int)a.total_nodes;
 }
 
 }  // namespace

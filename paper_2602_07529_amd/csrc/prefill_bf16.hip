@@ -1,10 +1,11 @@
 // bf16 DAG attention prefill for gfx950 (paper Eq. 2 + Eq. 3), MFMA 32x32x16 with fp32 accumulation.
 //
 // Work decomposition.  A work item is one query tile of one KV head with some of that KV head's
-// query heads, eight waves, each wave one 32-row block of one head, so every wave of the workgroup
-// consumes the same K/V tiles: 64-row tiles x 4 heads for full groups of four heads, 256-row tiles
-// x 1 head for one or two heads left over (their rows over the key tiles are derived from the
-// 64 x 64 block map, see k_wide_rows).  The kernel is persistent: the grid has one workgroup per
+// query heads, eight waves of 32 (row, head) pairs each, so every wave of the workgroup
+// consumes the same K/V tiles: 256 rows of one head, 128 of two, 64 of four, and of any other group as
+// many rows as 256 pairs with all of its heads have (pack_heads_of); on the block map's tiles 64-row tiles x 4
+// heads and 256-row tiles x 1 head for the heads left over (their rows over the key tiles are derived
+// from the 64 x 64 block map, see k_wide_rows).  The kernel is persistent: the grid has one workgroup per
 // CU; workgroup g processes items g and g + grid of the launch list (query tiles heavy first, the
 // KV heads of a tile next to each other) and takes every further item from a counter, one item
 // ahead of its use.  The K/V stream of the next item is prefetched while the current one finishes.
@@ -275,17 +276,22 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
   if (qt < total_qtiles) wide_order(qt, total_qtiles, wide_cnt, wide_pre, wide_desc, wide_count);
 }
 
+// The work counters of the attention kernel, and which rows the table of packed heads is for.
+__device__ __forceinline__ void start_tables(const PrefillArgs& a) {
+  if (threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
+  if (threadIdx.x == 0) a.chunk[DAG_CHUNK_PACK].count[1] = a.pack_rows;
+}
 // Four nodes a block, then (of the first size) blocks of 256 tokens.
 template <int W>
 __global__ void __launch_bounds__(256) k_node_rows(PrefillArgs a, int sizes) {
-  const int node_blocks = ((int)a.total_nodes + 3) / 4, i = nth_size(sizes, blockIdx.y), rows = rows_of(i);
+  const int node_blocks = ((int)a.total_nodes + 3) / 4, i = nth_size(sizes, blockIdx.y), rows = rows_of(a, i);
   const bool first = blockIdx.y == 0;
   if ((int)blockIdx.x >= node_blocks) {
     if (first) token_depths(a, (int64_t)(blockIdx.x - node_blocks) * 256);
     return;
   }
   const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (blockIdx.x == 0 && first && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && first) start_tables(a);
   if (gv < a.total_nodes)
     node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, slots_of(a, i), a.node_start,
                  a.cu_seqlens, a.tok_node, a.node_tok_start, a.node_vis, first ? a.node_runs : nullptr, tables_of(a, i));
@@ -296,6 +302,21 @@ __global__ void __launch_bounds__(256) k_chunk_order(PrefillArgs a, int sizes) {
   const ChunkTables t = tables_of(a, i);
   if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
 }
+// The table of packed heads in a workspace that may have been prepared for another head count.
+template <int W>
+__global__ void __launch_bounds__(256) k_pack_rows(PrefillArgs a) {
+  const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
+  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t.count[1] == a.pack_rows || gv >= a.total_nodes) return;
+  node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, a.pack_rows, slots_of(a, DAG_CHUNK_PACK), a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
+               a.node_vis, nullptr, t);
+}
+__global__ void __launch_bounds__(256) k_pack_order(PrefillArgs a) {
+  const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
+  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), n_slots = slots_of(a, DAG_CHUNK_PACK);
+  if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
+  if (blockIdx.x == 0 && threadIdx.x == 0) t.count[1] = a.pack_rows;
+}
 // Few nodes: the tables of a size and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2), and
 // blocks of 1024 tokens.
 constexpr int SMALL_NODES = 64, SMALL_SLOTS = 128;
@@ -305,10 +326,10 @@ __global__ void __launch_bounds__(1024) k_node_rows_small(PrefillArgs a, int siz
   const int n_sizes = __builtin_popcount(sizes);
   if ((int)blockIdx.x >= n_sizes) return token_depths(a, (int64_t)(blockIdx.x - n_sizes) * 1024);
   const bool first = blockIdx.x == 0;
-  const int w = threadIdx.x >> 6, i = nth_size(sizes, blockIdx.x), rows = rows_of(i);
+  const int w = threadIdx.x >> 6, i = nth_size(sizes, blockIdx.x), rows = rows_of(a, i);
   const int n_slots = slots_of(a, i);
   const ChunkTables t = tables_of(a, i), local = {t.count, s_cnt, s_pre, t.desc};
-  if (first && threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
+  if (first) start_tables(a);
   for (int gv = w; gv < a.total_nodes; gv += 16)
     node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
                  a.node_vis, first ? a.node_runs : nullptr, local);
@@ -396,11 +417,19 @@ __device__ unsigned long long g_tlog[4096];
 #endif
 // PAGED: K and V^T tiles come from the paged pools of the decode path through a list of pages per
 // work item instead of from the packed sequence (see k_paged_rows); the pipeline is the same.
+// PACK: the 32 NW rows of an item are (row, head) pairs, row-major, of heads_item heads of a KV head: HG, or for HG = 0 as many as the
+// launch says.  Otherwise a wave has 32 rows of one head.
 template <int D, int HG, int NRG, int STREAM>
 __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
   constexpr bool PAGED = STREAM == STREAM_PAGES, NODES = STREAM == STREAM_NODES;
+  constexpr bool PACK = NODES || HG == 0;
+  constexpr int HGS = HG == 0 ? 1 : HG, NW = HGS * NRG;  // waves: NRG row blocks x HG query heads
+  // Waves without rows leave the arithmetic out, where they share their SIMD with another one (on the block map's tiles there
+  // is no register left for it).  8 x 64 random nodes, 32 / 8 heads, a seventh of the chunks' rows empty: 1625 -> 1553 us; 43 batches
+  // of one, two and four heads a group 1.026 times as fast (0.99 to 1.14), with the pairs row-major and not head after head, which
+  // puts the empty ones together.
+  constexpr bool SKIP = (PACK || PAGED) && (NW == 8 || (NW == 4 && D == 64));
   constexpr int RB = 1;                      // 32-row blocks per wave
-  constexpr int NW = HG * NRG;               // waves: NRG row blocks x HG query heads
   constexpr int CH = D / 8;                  // 16-byte chunks per K row
   constexpr int KSTEPS = D / 16;             // MFMA steps of the score product
   constexpr int DB = D / 32;                 // 32-row blocks of O^T
@@ -434,13 +463,18 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
   // The number of query tiles is known to the host for the 64-row tiles of the block map and
   // read from the workspace for the 256-row tiles derived from it.
   const int G = a.hq / a.hkv;
-  const int HS = (a.heads + HG - 1) / HG;
+  const int heads_item = HG == 0 ? a.pack_heads : HG, rows_item = HG == 0 ? a.pack_rows : 32 * NRG;
+  const int HS = (a.heads + heads_item - 1) / heads_item;
   const int nhw = a.hkv * HS;
   const long n_items = (long)(a.n_tiles_dev ? sgpr(*a.n_tiles_dev) : (int)a.total_qtiles) * nhw;
 
   const int tid = threadIdx.x, w = sgpr(tid >> 6), lane = tid & 63;
   const int L = lane & 31, H = lane >> 5;
-  const int rg = w / HG, hj = w % HG;
+  const int rg = w / HGS, hj = w % HGS;
+  // PACK: pair 32 w + L of the item is row pair / heads_item and head pair % heads_item (the division exact below 256 pairs)
+  const uint32_t per_head = HG == 0 ? (65536u + heads_item - 1) / heads_item : 0;
+  auto pair_row = [&](int pair) __attribute__((always_inline)) { return HG == 0 ? (int)((uint32_t)pair * per_head >> 16) : pair / HGS; };
+  const int prow = HG == 0 ? min(pair_row(32 * w + L), rows_item - 1) : pair_row(32 * w + L), phead = PACK ? 32 * w + L - pair_row(32 * w + L) * heads_item : 0;
 
   const uint16_t* qg = (const uint16_t*)a.q;
   const unsigned char* kg = (const unsigned char*)a.k;
@@ -465,12 +499,17 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     I.hk = sgpr(hw / HS); I.hs = sgpr(hw % HS);
     return I;
   };
-  auto row_of = [&](const Item& I, int r) __attribute__((always_inline)) { return I.row0 + 32 * (rg * RB + r) + L; };  // row inside the sequence
+  auto row_of = [&](const Item& I, int r) __attribute__((always_inline)) { return I.row0 + (PACK ? prow : 32 * (rg * RB + r) + L); };  // row inside the sequence
   auto token_of = [&](const Item& I, int r) __attribute__((always_inline)) { return I.cu + min(row_of(I, r), I.T - 1); };
   // The waves beyond the last head of a padded item repeat that head (they load valid rows and
   // take part in every barrier) and store nothing.
-  auto head_of = [&](const Item& I) __attribute__((always_inline)) { return I.hk * G + a.head0 + min(I.hs * HG + hj, a.heads - 1); };
-  auto head_is_mine = [&](const Item& I) __attribute__((always_inline)) { return I.hs * HG + hj < a.heads; };
+  auto head_of = [&](const Item& I) __attribute__((always_inline)) { return I.hk * G + a.head0 + min(I.hs * heads_item + (PACK ? phead : hj), a.heads - 1); };
+  auto head_is_mine = [&](const Item& I) __attribute__((always_inline)) { return I.hs * heads_item + (PACK ? phead : hj) < a.heads; };
+  // (wave-uniform) no row of the item is this wave's: it fetches its share of the tiles, meets the others at every barrier, and
+  // leaves the matrix pipe of its SIMD to them.
+  auto no_rows = [&](const Item& I) __attribute__((always_inline)) {
+    return PACK ? pair_row(32 * w) >= min(rows_item, I.T - I.row0) : I.row0 + 32 * RB * rg >= I.T || !head_is_mine(I);
+  };
 
   // NODES: K and V rows of the tile are gathered: load i fetches the same rows of both, at per-lane
   // offsets (row of the tile -> token through the runs of the item's node), in the K block layout.
@@ -909,7 +948,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     if (NODES) {
       is_kbase = kg + (size_t)I.hk * (D * 2);
       is_vbase = vtg + (size_t)I.hk * (D * 2);
-      is_P = I.nstart + min(I.row0 + 32 * NRG, I.T);
+      is_P = I.nstart + min(I.row0 + rows_item, I.T);
       run_pos = cols;
       run_delta = deltas;
       run_at = 0;
@@ -1052,6 +1091,23 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  auto publish_next = [&]() __attribute__((always_inline)) {
+    if (grabber && has_next) {
+      asm volatile("" ::"v"(grabbed));  // the wait for the counter's answer belongs here
+      const long g = 2L * nb + __builtin_amdgcn_readfirstlane(grabbed);
+      const int v = g < n_list ? (int)g : -1;
+      asm volatile("ds_write_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" ::"v"(lds_addr(mbox + mslot)), "v"(v) : "memory");
+    }
+  };
+  auto load_rows = [&]() __attribute__((always_inline)) {
+    if (has_next) {
+      load_q(nxt);
+      if (STREAM == STREAM_TILES) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) vis0[r] = a.node_vis[(int64_t)(nxt.nstart + rnode_nxt[r]) * a.W];
+      }
+    }
+  };
 
   while (true) {
     // The Q rows and the row data were loaded with ordinary global loads; make them "arrive"
@@ -1079,6 +1135,17 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     if (grabber && has_next && lane == 0)  // the item after `nxt`; the answer is needed at the end of this item only
       grabbed = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
+    if (SKIP && no_rows(cur)) {
+#pragma unroll 1
+      for (int n = cur.N; n > 1; --n) {
+        sync_next();
+        if (ti - tc < NSTAGE) try_issue();
+      }
+      publish_next();
+      sync_next();
+      load_rows();
+      if (ti - tc < NSTAGE) try_issue();
+    } else {
     const int F = cur.nfast;
     f32x16 SA[RB], SB[RB];
     auto Kt = [&](unsigned t) __attribute__((always_inline)) { return Kbase + (t % NSTAGE) * KTILE; };
@@ -1531,12 +1598,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // wait on the answer placed later would also wait for the next item's Q rows or for the
     // output stores.  Two slots, used in turn: a wave may still have to read the one written an
     // item ago.
-    if (grabber && has_next) {
-      asm volatile("" ::"v"(grabbed));  // the wait for the counter's answer belongs here
-      const long g = 2L * nb + __builtin_amdgcn_readfirstlane(grabbed);
-      const int v = g < n_list ? (int)g : -1;
-      asm volatile("ds_write_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" ::"v"(lds_addr(mbox + mslot)), "v"(v) : "memory");
-    }
+    publish_next();
     TSTAMP(te0);
     sync_next();
     TSTAMP(te1);
@@ -1544,13 +1606,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // next item's rows (its node ids were loaded an item ago).  Placed after the loop above on
     // purpose (a load of the Q registers in front of it would make the compiler wait for
     // everything in flight there) and after the wait of sync_next, which counts tile loads only.
-    if (has_next) {
-      load_q(nxt);
-      if (STREAM == STREAM_TILES) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r) vis0[r] = a.node_vis[(int64_t)(nxt.nstart + rnode_nxt[r]) * a.W];
-      }
-    }
+    load_rows();
     if (need) rescale(SB);
     TSTAMP(te2);
     step_sel(true, lvP0, lvB, N_, H0, H0, nullptr, nullptr, Vt(tc - 1), P0, SB, P1, refill_slot);
@@ -1578,7 +1634,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
           for (int e = 0; e < 16; e += 2)
             any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(O[r][db][e], O[r][db][e + 1]), any);
         if (__builtin_amdgcn_ballot_w64(any != any && l[r] + __shfl_xor(l[r], 32) < INFINITY) == 0) continue;
-        const int end = cur.nstart + min(cur.row0 + 32 * NRG, cur.T);      // (wave-uniform)
+        const int end = cur.nstart + min(cur.row0 + rows_item, cur.T);     // (wave-uniform)
         bool suspect = false;
 #pragma unroll 1
         for (int p0 = cur.nfast * TN; p0 < end && !suspect; p0 += 64) {  // a position per lane
@@ -1647,10 +1703,12 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     // every tile load in flight); the piece belongs to this wave, so no barrier is involved.
     const int head = head_of(cur);
     const bool store = head_is_mine(cur);
+    // (PACK: the rows that a lane stores behind the LDS are other pairs than its own)
+    const bool row_mine = !PACK || pair_row(32 * w + L) < rows_item;
     if (PAGED && cur.ktb != 0) {  // a piece of a row of tiles: the sums as they are, for k_paged_merge
       float* const to = a.part + (((size_t)((cur.ktb & 0xffff) - 1) * nhw + cur.hk * HS + cur.hs) * NW + w) * paged_part(D);
       const float l_tot = l[0] + __shfl_xor(l[0], 32);
-      if (store) {
+      if (PACK || store) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1663,7 +1721,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     for (int r = 0; r < RB; ++r) {
       const float l_tot = l[r] + __shfl_xor(l[r], 32);
       const float inv = 1.f / l_tot;
-      const bool mine = store && row_of(cur, r) < cur.T;
+      const bool mine = store && row_mine && row_of(cur, r) < cur.T;
       if (a.lse && mine && H == 0)
         a.lse[(size_t)token_of(cur, r) * a.hq + head] = M[r] * 0.6931471805599453f + logf(l_tot);
       const uint32_t ow = lds_addr(Obase) + L * OROW + 8 * H;          // this lane's row in the piece
@@ -1672,9 +1730,10 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
       bool omine[2];
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
-        const int rr = cur.row0 + 32 * (rg * RB + r) + 16 * jj + (lane >> 2);
-        omine[jj] = store && rr < cur.T;
-        orow[jj] = (uint16_t*)a.out + ((size_t)(cur.cu + min(rr, cur.T - 1)) * a.hq + head) * D + 8 * (lane & 3);
+        const int pair = 32 * w + 16 * jj + (lane >> 2), pr = pair_row(pair), ph = cur.hs * heads_item + pair - pr * heads_item;
+        const int rr = cur.row0 + (PACK ? pr : 32 * (rg * RB + r) + 16 * jj + (lane >> 2));
+        omine[jj] = (PACK ? pr < rows_item && ph < a.heads : store) && rr < cur.T;
+        orow[jj] = (uint16_t*)a.out + ((size_t)(cur.cu + min(rr, cur.T - 1)) * a.hq + (PACK ? cur.hk * G + a.head0 + min(ph, a.heads - 1) : head)) * D + 8 * (lane & 3);
       }
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
@@ -1696,6 +1755,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
     }
     TSTAMP(t_o);
     TACC(6, t_p1, t_o);
+    }
     if (!has_next) break;
     reset_acc();
     int after_next;
@@ -1767,6 +1827,12 @@ __global__ void __launch_bounds__(64 * HG * NRG, wgs_per_cu(D, HG * NRG)) k_pref
   prefill_body<D, HG, NRG, STREAM_NODES>(a);
 }
 
+// Head groups of other than one, two and four heads, packed (pack_heads_of).
+template <int D, int NW, int STREAM>
+__global__ void __launch_bounds__(64 * NW, STREAM == STREAM_NODES ? wgs_per_cu(D, NW) : 1) k_prefill_packed(PrefillArgs a) {
+  prefill_body<D, 0, NW, STREAM>(a);
+}
+
 // (heads of the paged prefill that do not fill items of four)
 template <int D, int HG, int NRG>
 __global__ void __launch_bounds__(64 * HG * NRG, 1) k_prefill_pages(PrefillArgs a) {
@@ -1827,18 +1893,13 @@ __global__ void __launch_bounds__(256) k_paged_merge(PrefillArgs a, int n_slots,
   *(u32x2*)(to + 8) = u32x2{dag_pack_bf2(O[4] * inv, O[5] * inv), dag_pack_bf2(O[6] * inv, O[7] * inv)};
 }
 
-// How the launches divide a KV head's G query heads.
-//   four: heads in items of four heads x 64 rows;  two: a pair in an item of its own;
-//   one:  heads one at a time in items of 256 (on chunks at head dimension 64: 128) rows.
-// On the block map's tiles there are no pairs (three left-over heads go one at a time: 16 % less
-// time than padded to four on long fork-joins, the same on short random DAGs).
+// How the launches on the block map's tiles divide a KV head's G query heads: heads in items of four heads x 64 rows, the
+// others one at a time in items of 256 rows (three of them: 16 % less time than padded to four on long fork-joins, the
+// same on short random DAGs).
 struct HeadSplit {
-  int four, two, one;
+  int four, one;
 };
-HeadSplit split_heads(int g, bool chunks) {
-  const int rem = g % 4;
-  return chunks ? HeadSplit{g - rem, rem & 2, rem & 1} : HeadSplit{g - rem, 0, rem};
-}
+HeadSplit split_heads(int g) { return {g - g % 4, g % 4}; }
 
 // Whether the query rows are cut at the borders of the nodes (k_node_rows) instead of every 64 tokens.
 // Short nodes leave most of a chunk's rows empty, and the more so the more rows a chunk has (256 for
@@ -1864,23 +1925,38 @@ int heads_of_small_batch(const PrefillArgs& a, int head_dim) {
   return chunks * g <= n ? 1 : chunks * ((g + 1) / 2) <= n ? 2 : 0;
 }
 
+// Long contexts at head dimension 64 and heads in fours: eight waves to an item read K and V half as often as the four of
+// packed heads (see PACK_WAVES).  34,000 and 50,000 tokens a sequence, 32 / 8 heads: 3653 against 3699 us, 9342 against 9522, 64 / 8
+// heads 7273 against 7490, 18,270 against 19,065; with less than twelve items a compute unit what counts is how evenly
+// they go round: 8 / 2 heads 1079 against 961 and 2370 against 2327, 4 x 4608 tokens, 32 / 8 heads 374 against 376.
+bool long_contexts(const PrefillArgs& a, int head_dim) {
+  const int64_t g = a.hq / a.hkv;
+  return head_dim == 64 && g % 4 == 0 && a.total_tokens >= (int64_t)16384 * a.n_seqs &&
+         a.total_tokens / 64 * a.hkv * (g / 4) >= 12 * (int64_t)dag_compute_units();
+}
+// Whether the call takes all heads of a group in one item (pack_heads_of), of those on query chunks.
+bool packed(const PrefillArgs& a, int head_dim) { return a.pack_heads > 0 && heads_of_small_batch(a, head_dim) == 0 && !long_contexts(a, head_dim); }
+
 template <int D, int HG, int NRG, int STREAM>
 int launch_one(const PrefillArgs& a, long max_tiles, hipStream_t stream) {
   constexpr int KPB = 64 / (D / 8), KTILE = TN / KPB * (1024 + 16), VTILE = STREAM == STREAM_NODES ? KTILE : D / 8 * (1024 + 128);
+  constexpr int NW = (HG == 0 ? 1 : HG) * NRG;
   constexpr size_t sm = (size_t)NSTAGE * (KTILE + VTILE + (STREAM == STREAM_TILES ? 256 : 0)) + 16 +
-                        (size_t)HG * NRG * 32 * (64 + 16);  // rings + node-id records + item mailbox + output pieces
-  constexpr int PER_CU = wgs_per_cu(D, HG * NRG);  // workgroups that share a compute unit
+                        (size_t)NW * 32 * (64 + 16);  // rings + node-id records + item mailbox + output pieces
+  constexpr int PER_CU = wgs_per_cu(D, NW);  // workgroups that share a compute unit
   static_assert(PER_CU * sm <= 160 * 1024, "LDS of a compute unit");
   void (*kernel)(PrefillArgs);
-  if constexpr (STREAM == STREAM_NODES) kernel = k_prefill_nodes<D, HG, NRG>;
+  if constexpr (HG == 0) kernel = k_prefill_packed<D, NRG, STREAM>;
+  else if constexpr (STREAM == STREAM_NODES) kernel = k_prefill_nodes<D, HG, NRG>;
   else if constexpr (STREAM == STREAM_PAGES && HG != 4) kernel = k_prefill_pages<D, HG, NRG>;
   else kernel = k_prefill_bf16<D, HG, NRG, STREAM == STREAM_PAGES>;
   if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess) return DAG_ERR_HIP;
   const int n_cu = dag_compute_units();
   if (n_cu < 1) return DAG_ERR_HIP;
-  const long n_items = max_tiles * a.hkv * ((a.heads + HG - 1) / HG), n_wg = (long)n_cu * PER_CU;
+  const int heads = HG == 0 ? a.pack_heads : HG;
+  const long n_items = max_tiles * a.hkv * ((a.heads + heads - 1) / heads), n_wg = (long)n_cu * PER_CU;
   const unsigned grid = (unsigned)(n_items < n_wg ? n_items : n_wg);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * HG * NRG), sm, stream, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * NW), sm, stream, a);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
@@ -1902,16 +1978,24 @@ int launch_chunks(const PrefillArgs& a, int head0, int heads, hipStream_t stream
 template <int D>
 int launch_d(const PrefillArgs& a, hipStream_t stream) {
   const bool chunks = on_chunks(a, D);
-  const HeadSplit h = split_heads(a.hq / a.hkv, chunks);
+  const HeadSplit h = split_heads(a.hq / a.hkv);
+  const int g = a.hq / a.hkv;
   int rc = DAG_OK;
   const int few = chunks ? heads_of_small_batch(a, D) : 0;
   if (few > 0) {
     return few == 1 ? launch_chunks<D, 1, 2>(a, 0, a.hq / a.hkv, stream) : launch_chunks<D, 2, 2>(a, 0, a.hq / a.hkv, stream);
+  } else if (chunks && packed(a, D)) {
+    PrefillArgs b = a;
+    b.head0 = 0;
+    b.heads = a.hq / a.hkv;
+    b.col = a.node_runs;
+    b.qtile_desc = a.chunk[DAG_CHUNK_PACK].desc;
+    b.n_tiles_dev = a.chunk[DAG_CHUNK_PACK].count;
+    return launch_one<D, 0, PACK_WAVES(D), STREAM_NODES>(b, chunk_slots(a.total_tokens, a.total_nodes, a.pack_rows), stream);
   } else if (chunks) {  // (at head dimension 64 four waves with half the rings: two workgroups per compute unit)
-    if (h.four > 0) rc = launch_chunks<D, 4, 2>(a, 0, h.four, stream);
-    if (rc == DAG_OK && h.two > 0) rc = D == 128 ? launch_chunks<128, 2, 4>(a, h.four, h.two, stream) : launch_chunks<64, 2, 2>(a, h.four, h.two, stream);
-    if (rc == DAG_OK && h.one > 0) rc = D == 128 ? launch_chunks<128, 1, 8>(a, h.four + h.two, 1, stream) : launch_chunks<64, 1, 4>(a, h.four + h.two, 1, stream);
-    return rc;
+    if (g == 1) return D == 128 ? launch_chunks<128, 1, 8>(a, 0, 1, stream) : launch_chunks<64, 1, 4>(a, 0, 1, stream);
+    if (g == 2) return D == 128 ? launch_chunks<128, 2, 4>(a, 0, 2, stream) : launch_chunks<64, 2, 2>(a, 0, 2, stream);
+    return launch_chunks<D, 4, 2>(a, 0, g, stream);
   }
   if (h.four > 0) {  // eight waves = 2 row blocks x 4 query heads
     PrefillArgs b = a;
@@ -1940,7 +2024,7 @@ bool prefill_on_chunks(const PrefillArgs& a, int head_dim) { return on_chunks(a,
 // The nodes' runs and the chunk tables of the sizes asked for: descriptors, then launch order (by descending tile count).
 static int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stream) {
   const unsigned n_sizes = (unsigned)__builtin_popcount((unsigned)sizes);
-  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, DAG_CHUNK_ROWS[__builtin_ctz(sizes)]);  // (the larger sizes have fewer)
+  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, std::min(DAG_CHUNK_ROWS[0], a.pack_rows > 0 ? a.pack_rows : 64));  // (the larger sizes have fewer)
   if (a.total_nodes <= SMALL_NODES && slots <= SMALL_SLOTS) {
     hipLaunchKernelGGL(a.W == 1 ? k_node_rows_small<1> : k_node_rows_small<2>, dim3(n_sizes + (unsigned)dag_ceil_div(a.total_tokens, 1024)), dim3(1024), 0, stream, a, sizes);
     DAG_LAUNCH_CHECK();
@@ -1955,8 +2039,12 @@ static int launch_chunk_tables(const PrefillArgs& a, int sizes, hipStream_t stre
 
 template <int D>
 int launch_prepare_v(const PrefillArgs& a, hipStream_t stream) {
-  if (on_chunks(a, D)) return launch_chunk_tables(a, (1 << DAG_CHUNK_SIZES) - 1, stream);  // V is read as it is
-  const HeadSplit h = split_heads(a.hq / a.hkv, false);
+  if (on_chunks(a, D)) {  // V is read as it is
+    PrefillArgs b = a;
+    if (!packed(a, D)) b.pack_rows = 0;
+    return launch_chunk_tables(b, (1 << DAG_CHUNK_SIZES) - 1 + (b.pack_rows > 0 ? 1 << DAG_CHUNK_PACK : 0), stream);
+  }
+  const HeadSplit h = split_heads(a.hq / a.hkv);
   hipLaunchKernelGGL((k_vt_prepare<D>), dim3((unsigned)a.total_ktiles, (unsigned)a.hkv), dim3(256), 0, stream,
                      (const uint16_t*)a.v, (uint16_t*)a.vt, a.ktile_start, a.cu_seqlens, a.n_seqs, a.hkv, a.sched);
   DAG_LAUNCH_CHECK();
@@ -2027,6 +2115,15 @@ int launch_paged(const PagedPrefillArgs& pa, hipStream_t stream) {
 
 int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t stream) {
   return head_dim == 128 ? launch_paged<128>(pa, stream) : launch_paged<64>(pa, stream);
+}
+
+int launch_prefill_pack_tables(const PrefillArgs& a, int head_dim, hipStream_t stream) {
+  if (!on_chunks(a, head_dim) || !packed(a, head_dim)) return DAG_OK;
+  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, a.pack_rows);
+  hipLaunchKernelGGL(a.W == 1 ? k_pack_rows<1> : k_pack_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(k_pack_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, a);
+  DAG_LAUNCH_CHECK();
+  return DAG_OK;
 }
 
 int launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t stream) {

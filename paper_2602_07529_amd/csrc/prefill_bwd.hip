@@ -429,9 +429,9 @@ __global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs
     int32_t* const runs = x < n.nodes ? p.node_runs : nullptr;
     if (gv >= p.total_nodes) return;
     if (a.W == 1)
-      node_rows<1>(gv, p.n_seqs, (int)p.total_nodes, rows_of(i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+      node_rows<1>(gv, p.n_seqs, (int)p.total_nodes, rows_of(p, i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
     else
-      node_rows<2>(gv, p.n_seqs, (int)p.total_nodes, rows_of(i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+      node_rows<2>(gv, p.n_seqs, (int)p.total_nodes, rows_of(p, i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
     return;
   }
   x -= n.nodes * n.sizes;

@@ -9,8 +9,11 @@ constexpr int DAG_SCHED_INTS = 128;  // [0..63] item counters, [64] finished wor
 // t / rows + v on.
 constexpr int DAG_CHUNK_SIZES = 3;
 constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};  // (each twice the one in front)
+// A fourth size belongs to the head counts that pack all heads of a group into an item (pack_of): as many rows as 32 NW
+// (row, head) pairs have, at least PACK_MIN_ROWS.
+constexpr int DAG_CHUNK_PACK = DAG_CHUNK_SIZES, PACK_MIN_ROWS = 16;
 struct ChunkTables {
-  int32_t* count;  // [1] number of chunks
+  int32_t* count;  // [2] number of chunks; (packed heads) the rows that the table was built for, 0: not built
   int32_t* cnt;    // [slots] key tiles of the chunk, -1: no chunk here
   int32_t* pre;    // [slots][8] its descriptor
   int32_t* desc;   // [slots][8] descriptors in launch order
@@ -56,17 +59,18 @@ struct PrefillArgs {
   int64_t total_tokens, total_nodes;
   int32_t* node_runs;  // [total_nodes][64][2], null when the workspace has no room for them
   int32_t* tok_depth;  // [total_tokens] tokens of its own node in front of every token
-  ChunkTables chunk[DAG_CHUNK_SIZES];
+  ChunkTables chunk[DAG_CHUNK_SIZES + 1];
+  int pack_heads, pack_rows;  // packed heads: heads of a KV head in an item and rows of a chunk; 0: not these head counts
   float* part;  // paged prefill: partial results of the pieces of its rows of tiles, null: no room for them
 };
 
 // The node tables hold 64 runs per node, the most that 128 nodes can have.  They take the place of the
-// transposed V, which is not needed with them: 716 bytes a node and 5.9 a token against at least 128 a
-// token, so that they fit wherever a node has six tokens on average.
+// transposed V, which is not needed with them: 784 bytes a node and 10.1 a token against at least 128 a
+// token, so that they fit wherever a node has seven tokens on average.
 inline size_t prefill_node_table_bytes(int64_t total_tokens, int64_t total_nodes) {
   size_t n = (size_t)total_nodes * 128 * 4 + (size_t)total_tokens * 4;
   for (int i = 0; i < DAG_CHUNK_SIZES; ++i) n += (size_t)(62 + 17 * chunk_slots(total_tokens, total_nodes, DAG_CHUNK_ROWS[i])) * 4;
-  return n;
+  return n + (size_t)(62 + 17 * chunk_slots(total_tokens, total_nodes, PACK_MIN_ROWS) + 1) * 4;
 }
 
 // Points the node tables of `a` into the memory at t (8-byte aligned, prefill_node_table_bytes of it).
@@ -79,6 +83,23 @@ inline void prefill_node_tables(PrefillArgs& a, int32_t* t) {
     t += 62 + 17 * n;
   }
   a.tok_depth = t;
+  t += a.total_tokens + (a.total_tokens & 1);
+  const int64_t n = chunk_slots(a.total_tokens, a.total_nodes, a.pack_rows > 0 ? a.pack_rows : 256);  // (where it lies does not depend on the head count)
+  a.chunk[DAG_CHUNK_PACK] = {t, t + 62, t + 62 + n, t + 62 + 9 * n};
+}
+
+constexpr int PACK_WAVES(int head_dim) { return head_dim == 128 ? 8 : 4; }  // of an item
+// Query heads of a KV head that are neither one, two nor four go into an item together: the 32 NW (row, head) pairs of an item
+// are row-major, every lane of a wave with a row and a head of its own, all on the same K / V tiles.  More than eight heads are
+// divided evenly.  Five heads were an item of four on 64 rows and, in a launch behind it, one on 256, which random DAGs leave
+// half empty: 60 nodes, 40 / 8 heads 154 -> 113 us, 5 x 53 nodes 704 -> 634, a fork-join of 17,000 tokens 7748 -> 7526; eight
+// heads on 32 rows instead of twice four on 64: 921 -> 864; 56 batches of 3, 5, 6, 7 and 8 heads 1.24 times as fast (0.98 at
+// worst, where one more table is built for nothing).  At head dimension 64 four heads, too: four waves on 32 rows instead of eight
+// on 64 leave room for two workgroups on a compute unit, 2 x 4500 tokens, 8 / 2 heads 90 -> 79 us (but see long_contexts).
+inline int pack_heads_of(int g, int head_dim) {
+  if (g == 1 || g == 2 || (g == 4 && head_dim == 128)) return 0;
+  const int groups = (g + 7) / 8;
+  return (g + groups - 1) / groups;
 }
 
 // Workspace of the bf16 path behind the transposed V: counters, then the tables above.
@@ -107,4 +128,5 @@ int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t s
 bool prefill_on_chunks(const PrefillArgs& a, int head_dim);  // bf16: query chunks or the block map's tiles
 int launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t stream);
 int launch_prefill_bf16_prepare_v(const PrefillArgs& a, int head_dim, hipStream_t stream);  // V -> workspace copy
+int launch_prefill_pack_tables(const PrefillArgs& a, int head_dim, hipStream_t stream);     // for a workspace prepared for any head count
 int launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t stream);            // needs the copy
