@@ -88,6 +88,7 @@ struct BwdArgs {
   int32_t* n_pieces;     // [2] pieces, split pairs
   f32x4* part;    // [split piece][hkv][4 waves][dK, dV: 32 dims][4][64 lanes]
   int max_split;  // room for this many pieces of split pairs (a KV head)
+  int32_t* block_start;  // [total key tiles] first keys of a sequence's blocks (see cut_keys; T: no block); null: blocks are pairs of key tiles
   bool again;     // k_dkv_finish may read the inputs once more
   int dq_pieces;  // dQ on chunks: workgroups that may share a chunk, set per launch (see dq_cuts)
 };
@@ -406,6 +407,97 @@ __device__ __forceinline__ void bwd_weight(const BwdArgs& a, int kt, int lane) {
   n = dag_wave_sum(n);
   if (lane == 0) a.kt_weight[kt] = (ktl & 1) ? -1 : n;
 }
+// Blocks of keys whose borders are the nodes' where those allow it.  The stream of a block has every row that sees one of its
+// keys, and its tiles take masks but for those of rows that see all of them: 128 keys from the start of a sequence on
+// multiply 1.73 times the visible pairs of 4 x 64 random nodes of 32 to 256 tokens, 1263 of 5319 tiles without masks.  A block that
+// ends at the last border of nodes 64 to 128 keys behind its first key, and where there is none has 128: 1.49 times, 2513 of
+// 4579 tiles.  Cut at every border short nodes leave most of a workgroup idle (1.3 to 2.1 times the tiles for nodes of 35 to 60
+// tokens), at least 96 keys a block are 0.5 % slower than 64, and with 64 there are no more blocks than key tiles.
+// Where the siblings of a fork have about 100 tokens, blocks of 128 keys cost less: a sequence takes what needs less
+// time by the tiles of the streams, one with masks 1.25 times one without, and DKV_BLOCK_STEPS iterations a workgroup.
+// Forward and backward of 4 x 64 random nodes, 16 / 8 heads of dimension 64: 835 -> 788 us; 21 other batches 1.012 times as fast,
+// random ones with long nodes 1.03 to 1.13 (0.984 at worst).
+// (A workgroup a sequence.  The blocks follow one from the other, so every wave finds all of them, 80 clocks each; a thread
+// then weighs a block, the nodes in LDS.  Blocks weighed by whole waves, a node a lane, took 5 to 28 us.)
+constexpr int BLOCK_MIN = 64, DKV_BLOCK_STEPS = 8;
+__device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
+  __shared__ uint64_t s_word[2][128];  // what a node sees
+  __shared__ int s_first[129];
+  __shared__ float s_cost[2][4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int n0 = a.node_start[b], n = a.node_start[b + 1] - n0, cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu;
+  const int slots = (T + BN - 1) / BN, n_even = (slots + 1) / 2;
+  if (tid <= 128) s_first[tid] = tid < n ? a.node_tok_start[n0 + tid] : T;
+  s_word[tid >> 7][tid & 127] = (tid >> 7) < a.W && (tid & 127) < n ? a.node_vis[(int64_t)(n0 + (tid & 127)) * a.W + (tid >> 7)] : 0;
+  __syncthreads();
+  int32_t* const start = a.block_start + a.ktile_start[b];
+  int32_t* const weight = a.kt_weight + a.ktile_start[b];
+  int32_t* const weight_even = a.kt_order + a.ktile_start[b];  // (with pieces nothing else is here yet)
+  const int first0 = s_first[lane], first1 = s_first[64 + lane];
+  int n_cut = 0, mine = 0;
+  for (int key0 = 0; key0 < T; ++n_cut) {
+    mine = lane == (n_cut & 63) ? key0 : mine;
+    if ((n_cut & 63) == 63 && tid < 64) start[n_cut - 63 + lane] = mine;
+    const uint32_t lo = key0 + BLOCK_MIN, hi = key0 + 2 * BN;
+    const uint64_t m0 = __builtin_amdgcn_ballot_w64((uint32_t)first0 - lo <= hi - lo), m1 = n > 64 ? __builtin_amdgcn_ballot_w64((uint32_t)first1 - lo <= hi - lo) : 0;
+    key0 = hi;
+    if (m0 != 0) key0 = __builtin_amdgcn_readlane(first0, 63 - __builtin_clzll(m0));
+    if (m1 != 0) key0 = __builtin_amdgcn_readlane(first1, 63 - __builtin_clzll(m1));
+    if ((uint32_t)T <= hi) key0 = T;
+  }
+  if (tid < (n_cut & 63)) start[(n_cut & ~63) + lane] = mine;
+  __syncthreads();
+  float cost[2] = {0.f, 0.f};  // blocks of 128 keys, blocks cut at borders
+  for (int i0 = 0; i0 < n_even + n_cut; i0 += 64) {  // four threads a block, each with every fourth node
+    const int i = min(i0 + (tid >> 2), n_even + n_cut - 1), part = tid & 3;
+    const bool cut = i >= n_even, count = i0 + (tid >> 2) == i && part == 0;
+    const int x = cut ? i - n_even : i;
+    const int key0 = cut ? start[x] : x * 2 * BN, key1 = !cut ? min(key0 + 2 * BN, T) : x + 1 < n_cut ? start[x + 1] : T;
+    const int u0 = a.tok_node[cu + key0], u1 = a.tok_node[cu + key1 - 1];
+    uint64_t range[2];  // bits u0 .. u1
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int from = max(u0 - 64 * y, 0), to = min(u1 - 64 * y, 63);
+      range[y] = from <= to ? (~0ull >> (63 - to)) & (~0ull << from) : 0ull;
+    }
+    int rows = 0, sure = 0;  // of the stream, and those of them that see all of the keys
+    for (int u = part; u < n; u += 4) {
+      const uint64_t w0 = s_word[0][u], w1 = a.W > 1 ? s_word[1][u] : 0;
+      const int len = s_first[u + 1] - s_first[u];
+      rows += ((w0 & range[0]) | (w1 & range[1])) != 0 ? len : 0;
+      const bool all = ((~w0 & range[0]) | (~w1 & range[1])) == 0;
+      sure += all ? (u == u1 ? s_first[u + 1] - key1 : len) : 0;
+    }
+    rows = dag_wave_sum<2>(rows) + s_first[u0] - key0;
+    sure = dag_wave_sum<2>(sure);
+    const int tiles = (rows + BM - 1) / BM;
+    const float c = a.G * (1.25f * tiles - 0.25f * (sure / BM)) + DKV_BLOCK_STEPS;
+    cost[0] += cut || !count ? 0.f : c;
+    cost[1] += cut && count ? c : 0.f;
+    if (count) (cut ? weight : weight_even)[x] = tiles;
+  }
+#pragma unroll
+  for (int y = 0; y < 2; ++y) {
+    const float c = dag_wave_sum(cost[y]);
+    if (lane == 0) s_cost[y][tid >> 6] = c;
+  }
+  __syncthreads();
+  const bool even = s_cost[0][0] + s_cost[0][1] + s_cost[0][2] + s_cost[0][3] < 1.03f * (s_cost[1][0] + s_cost[1][1] + s_cost[1][2] + s_cost[1][3]);
+  for (int x = tid; x < slots; x += 256) {  // (behind the barrier: weight_even is another thread's)
+    if (even) {
+      start[x] = x < n_even ? x * 2 * BN : T;
+      weight[x] = x < n_even ? weight_even[x] : -1;
+    } else if (x >= n_cut) {
+      start[x] = T;
+      weight[x] = -1;
+    }
+  }
+}
+// The keys [x, y) of the workgroup of key tile kt (the ktl-th of its sequence).
+__device__ __forceinline__ int2 dkv_keys(const BwdArgs& a, int kt, int ktl, int T) {
+  if (!a.block_start) return int2{ktl * BN, min((ktl + 2) * BN, T)};
+  return int2{a.block_start[kt], (ktl + 1) * BN < T ? a.block_start[kt + 1] : T};
+}
 // First visibility word of every token's node, so that the dQ kernels on the block map's tiles can fetch it for
 // their rows without a load that depends on another load.
 __device__ __forceinline__ void bwd_token_vis(const BwdArgs& a, int t) {
@@ -446,7 +538,10 @@ __global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs
   }
   x -= n.tokens;
   if (x < n.weights) {
-    if (4 * x + w < a.total_ktiles) bwd_weight(a, 4 * x + w, lane);
+    if (a.block_start)
+      cut_keys(a, x);
+    else if (4 * x + w < a.total_ktiles)
+      bwd_weight(a, 4 * x + w, lane);
     return;
   }
   bwd_delta<D>(a, x - n.weights);
@@ -972,16 +1067,18 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   const int kt = piece.x;
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int ktl = kt - a.ktile_start[b];
-  if (ktl & 1) return;  // the workgroup of the even tile takes the pair
+  if ((!NODES || !a.block_start) && (ktl & 1)) return;  // the workgroup of the even tile takes the pair
   const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu;
+  const int2 keys = NODES ? dkv_keys(a, kt, ktl, T) : int2{ktl * BN, min((ktl + 2) * BN, T)};
+  const int key0 = keys.x, key1 = keys.y;
   const int QT = (T + BM - 1) / BM, KT = (T + BN - 1) / BN;
   const uint8_t* bm = a.block_map + a.block_map_off[b];
   const int nbase = a.node_start[b];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, L = lane & 31, H = lane >> 5;
   const int my_kt = ktl + (w >> 1);
-  const int j = ktl * BN + 32 * w + L;  // this lane's key
-  const bool key_ok = j < T;
-  const int jc = min(j, T - 1);
+  const int j = key0 + 32 * w + L;  // this lane's key
+  const bool key_ok = j < key1;
+  const int jc = min(j, key1 - 1);
   const size_t koff = ((size_t)(cu + jc) * a.hkv + hk) * D;
   bf16x8 kf[D / 16], vf[D / 16];
 #pragma unroll
@@ -1016,8 +1113,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
       }
     }
     if constexpr (NODES) {
-      const int u0 = a.tok_node[cu + ktl * BN], u1 = a.tok_node[cu + min(ktl * BN + 2 * BN, T) - 1];  // the keys' nodes
-      const int key0 = ktl * BN, key1 = min(key0 + 2 * BN, T);
+      const int u0 = a.tok_node[cu + key0], u1 = a.tok_node[cu + key1 - 1];  // the keys' nodes
       // Rows [from, to) of node 64 x + lane in either part.  Of the keys' own nodes the rows in front of the
       // first key see none of them, and those behind the last key what their node sees.
       int from[2][2], to[2][2];
@@ -1068,8 +1164,6 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
           n_fast = n_pos / BM;
         }
       }
-      // every key of the pair exists in a tile without tests (else the words of the lanes say so)
-      if ((ktl + 2) * BN > T) n_fast = 0;
     }
   }
   auto word_of = [&](uint32_t n) __attribute__((always_inline)) -> uint64_t {  // (n is wave-uniform)
@@ -1389,7 +1483,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     // accumulation registers over the whole loop; without the hint the allocator moves three of
     // the eight back and forth every iteration)
     while (NODES ? cq >= n0 : cq >= 0) {  // one query tile: (with masks) its visibility word once, then an iteration per head
-      bool active = true;  // a visible pair in this wave's key tile
+      bool active = !NODES || key0 + 32 * w < key1;  // a visible pair in this wave's key tile (tiles without tests: a lane past the last key computes what nobody stores)
       uint64_t vis = 0;
       if constexpr (KIND == 1 && NODES) {
         const int at = key_pos - cq * BM;  // the key's own row in the tile: the rows of its node see it from there on
@@ -1414,7 +1508,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         for (int db = 0; db < DB; ++db)
           if constexpr (D == 128) asm volatile("" : "+a"(dK[db]), "+a"(dV[db]));
         const IssueCtx ic = prepare_issue(iq, ig);
-        if (KIND == 0 || active) {
+        if ((KIND == 0 && !NODES) || active) {
           pipelined_iter(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
         } else {  // only the ring's business
           sync_mid();
@@ -1435,7 +1529,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   ring_loop(std::true_type{});
   int key = 32 * w + L;
   asm volatile("" : "+v"(key));  // (recomputed here: its offsets need no registers across the loops)
-  const int j_out = ktl * BN + key;
+  const int j_out = key0 + key;
   if (NODES && cuts > 1) {
     f32x4* to = a.part + ((size_t)(slot * a.hkv + hk) * 4 + w) * (8 * DB * 64) + lane;
 #pragma unroll
@@ -1447,14 +1541,14 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
       }
     return;
   }
-  dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < T, H, dK, dV);
+  dkv_store<D>(a, ((size_t)(cu + min(j_out, T - 1)) * a.hkv + hk) * D, j_out < key1, H, dK, dV);
   if constexpr (NODES) {  // sums that are not numbers: k_dkv_finish looks into it
     float any = 0.f;  // (maximum, unlike fmaxf, hands a NaN on)
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int e = 0; e < 16; ++e) any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(dK[db][e], dV[db][e]), any);
-    if (any != any) a.kt_again[kt] = 1;
+    if (j_out < key1 && any != any) a.kt_again[kt] = 1;
   }
 }
 __global__ void __launch_bounds__(256) k_bwd_dkv2(BwdArgs a) { dkv_ring_body<128, false>(a); }
@@ -1472,13 +1566,14 @@ __device__ void dkv_again(const BwdArgs& a, int kt, int hk, int w) {
   const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
   const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu, nbase = a.node_start[b];
   const int lane = threadIdx.x & 63, H = lane >> 5;
-  const int j0 = (kt - a.ktile_start[b]) * BN + 32 * w, j = j0 + (lane & 31), jc = min(j, T - 1);
-  if (j0 >= T) return;
-  const bool key_ok = j < T;
-  const int node = a.tok_node[cu + jc], u0 = a.tok_node[cu + j0], j1 = min(j0 + 31, T - 1), u1 = a.tok_node[cu + j1];
+  const int2 keys = dkv_keys(a, kt, kt - a.ktile_start[b], T);
+  const int j0 = keys.x + 32 * w, j = j0 + (lane & 31), jc = min(j, keys.y - 1);
+  if (j0 >= keys.y) return;
+  const bool key_ok = j < keys.y;
+  const int node = a.tok_node[cu + jc], u0 = a.tok_node[cu + j0], j1 = min(j0 + 31, keys.y - 1), u1 = a.tok_node[cu + j1];
   auto sees = [&](int ni, int u) { return ((a.node_vis[(int64_t)(nbase + ni) * a.W + (u >> 6)] >> (u & 63)) & 1) != 0; };
   bool suspect = false;
-  for (int i0 = (kt - a.ktile_start[b]) * BN; i0 < T && !suspect; i0 += 64) {  // a row per lane
+  for (int i0 = keys.x; i0 < T && !suspect; i0 += 64) {  // a row per lane
     const int i = min(i0 + lane, T - 1), ni = a.tok_node[cu + i];
     bool all = i >= j1;
     for (int u = u0; u <= u1; ++u) all = all && sees(ni, u);
@@ -1573,15 +1668,17 @@ __global__ void __launch_bounds__(256) k_dkv_finish(BwdArgs a) {
       for (int r = 0; r < NR; ++r) sum[r] += from[r * 64];
     }
     const int b = dag_find_segment(a.ktile_start, a.n_seqs, kt);
-    const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu, j = (kt - a.ktile_start[b]) * BN + 32 * group + L;
+    const int cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu;
+    const int2 keys = dkv_keys(a, kt, kt - a.ktile_start[b], T);
+    const int j = keys.x + 32 * group + L;
     const float scale = w < 2 ? a.scale : 1.f;
     uint16_t* to = (w < 2 ? a.dk : a.dv) + ((size_t)(cu + min(j, T - 1)) * a.hkv + hk) * D + (w & 1) * (D / 2) + 4 * H;
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      bad |= sum[r][0] != sum[r][0] || sum[r][1] != sum[r][1] || sum[r][2] != sum[r][2] || sum[r][3] != sum[r][3];
+      bad |= j < keys.y && (sum[r][0] != sum[r][0] || sum[r][1] != sum[r][1] || sum[r][2] != sum[r][2] || sum[r][3] != sum[r][3]);
       const u32x2 o = {dag_pack_bf2(sum[r][0] * scale, sum[r][1] * scale), dag_pack_bf2(sum[r][2] * scale, sum[r][3] * scale)};
-      if (j < T) *(u32x2*)(to + 8 * r) = o;
+      if (j < keys.y) *(u32x2*)(to + 8 * r) = o;
     }
     if (!__syncthreads_or(bad) || !a.again || w != 0) return;
   }
@@ -2130,12 +2227,15 @@ bool bwd_first_version() {
   return v;
 }
 
+// At most this many blocks of cut_keys: one for every 128 tokens of a sequence that ends there, one for every border.
+int64_t bwd_cut_blocks(int64_t T, int64_t nodes, int64_t ktiles, int64_t n_seqs) { return std::min(ktiles, T / (2 * BN) + nodes + n_seqs); }
+
 template <int D>
 int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_qtiles, long total_ktiles, hipStream_t stream) {
   BwdArgs a = args;
   constexpr int RPB = 256 / (D / 8), NQ = Dq<D>::NPAIR;  // rows per workgroup of bwd_delta
   const int n_sizes = __builtin_popcount((unsigned)sizes), waves4 = (int)((total_ktiles + 3) / 4);
-  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 255) / 256), waves4, (int)((a.total_rows + RPB - 1) / RPB)};
+  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 255) / 256), a.block_start ? a.n_seqs : waves4, (int)((a.total_rows + RPB - 1) / RPB)};
   hipLaunchKernelGGL((k_bwd_delta_tables<D>), dim3((unsigned)(pre.nodes * pre.sizes + pre.tokens + pre.weights + pre.delta)), dim3(256), 0, stream, a, p, sizes, pre);
   // (without pieces the flags of k_dkv_finish lie where dQ on the block map's tiles reads the words of its rows)
   const bool order_now = a.pieces || a.runs || !a.dkv_stream;
@@ -2197,7 +2297,7 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_
     auto* const ring = D == 128 ? (a.dkv_stream ? k_nodes_dkv2 : k_bwd_dkv2) : a.dkv_stream ? k_nodes64_dkv : k_bwd64_dkv;
     if (hipFuncSetAttribute((const void*)ring, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    const long pairs = a.pieces ? (total_ktiles + a.n_seqs) / 2 : total_ktiles;
+    const long pairs = a.block_start ? (long)bwd_cut_blocks(p.total_tokens, p.total_nodes, total_ktiles, a.n_seqs) : a.pieces ? (total_ktiles + a.n_seqs) / 2 : total_ktiles;
     hipLaunchKernelGGL(ring, dim3((unsigned)((pairs + a.max_split) * a.hkv)), dim3(256), sm2, stream, a);
     // (it reads K, V, Q and dO once more: not where the gradients have been written over them)
     const size_t q_bytes = (size_t)a.total_rows * D * 2, k_bytes = q_bytes / a.G;
@@ -2548,6 +2648,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     a.part = (f32x4*)(at + piece_bytes - (size_t)a.max_split * hkv * (2 * BN) * head_dim * 2 * 4);
   }
   a.runs = nullptr;
+  a.block_start = nullptr;
   PrefillArgs p = {};
   int sizes = 0;
   if (bwd_dq_on_chunks(m, a, head_dim)) {
@@ -2565,6 +2666,16 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     }
     a.runs = p.node_runs;
     a.tok_depth = p.tok_depth;
+    // Blocks cut at node borders are more than the pairs that the piece list has room for, so it lies behind their first keys in the
+    // place of the words that dQ does not read on chunks (eight bytes a token).  Below 4096 tokens the 2 us of cut_keys
+    // are more than forks give back (68 and 118 us: 0.98), and with one head a group a workgroup has as few
+    // iterations as it costs (2 x 52 and 5 x 97 random nodes, 2 / 2 heads of dimension 128: 0.96 and 0.98).
+    const int64_t blocks = bwd_cut_blocks(p.total_tokens, p.total_nodes, a.total_ktiles, a.n_seqs);
+    const size_t start_bytes = dag_align_up((size_t)a.total_ktiles * 4, 8);
+    if (a.pieces && a.dkv_stream && a.G >= 2 && p.total_tokens >= 4096 && start_bytes + (size_t)(blocks + a.max_split) * 8 <= (size_t)p.total_tokens * 8) {
+      a.block_start = (int32_t*)a.tok_vis0;
+      a.pieces = (int2*)((char*)a.tok_vis0 + start_bytes);
+    }
   }
   return head_dim == 128 ? launch_bwd<128>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
                          : launch_bwd<64>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
