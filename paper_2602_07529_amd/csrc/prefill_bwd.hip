@@ -74,9 +74,10 @@ struct BwdArgs {
   int32_t* wide_col;    // [dense map] key tiles that one of the query tiles sees, those that all of them see in full first
   int32_t *wide_n, *wide_nfast;  // [total query tiles] length of the list, leading entries without tests (at every NQ-th tile)
   int32_t* wide_list;   // [total query tiles + 1] the first tiles of the groups, sequence after sequence; last element: their number
-  // dQ on query chunks (k_node_rows): the chunk tables of 64 and of 64 NQ rows, the nodes' runs
-  ChunkTables chunk[2];
-  int64_t chunk_slots[2];
+  // dQ on query chunks (k_node_rows): the chunk table of pack_rows rows, heads of a KV head in an item, the nodes' runs
+  ChunkTables chunk;
+  int64_t slots;
+  int pack_heads, pack_rows;
   const int32_t *runs, *tok_depth;
   // dK / dV on streams of query rows
   bool dkv_stream;
@@ -318,13 +319,12 @@ __device__ __forceinline__ DqTile dq_tile(const BwdArgs& a) {
   t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
   return t;
 }
-// (g: query head of the KV head, row0: first row of this wave pair's 64-row query tile)
+// (g: query head of the KV head, i: this lane's row of the sequence)
 template <int D>
-__device__ __forceinline__ void dq_setup_at(const BwdArgs& a, const DqTile& t, int hk, int g, bool head_ok, int row0, DqLane<D>& me) {
-  const int h = hk * a.G + min(g, a.G - 1);
-  const int tid = threadIdx.x, w = (tid >> 6) & 1, lane = tid & 63, L = lane & 31, H = lane >> 5;
-  me.i = row0 + 32 * w + L;
-  me.row_ok = me.i < t.T && head_ok;
+__device__ __forceinline__ void dq_setup_row(const BwdArgs& a, const DqTile& t, int hk, int g, bool ok, int i, DqLane<D>& me) {
+  const int h = hk * a.G + min(g, a.G - 1), H = (threadIdx.x & 63) >> 5;
+  me.i = i;
+  me.row_ok = me.i < t.T && ok;
   const int ic = min(me.i, t.T - 1);
   me.qoff = ((size_t)(t.cu + ic) * a.hq + h) * D;
 #pragma unroll
@@ -335,7 +335,17 @@ __device__ __forceinline__ void dq_setup_at(const BwdArgs& a, const DqTile& t, i
   me.lse2 = a.lse[(size_t)(t.cu + ic) * a.hq + h] * LOG2E;
   me.dl = a.delta[(size_t)(t.cu + ic) * a.hq + h];
   me.ni = a.tok_node[t.cu + ic];
-  me.vis0 = a.tok_vis0[t.cu + ic];
+  me.vis0 = a.runs ? 0 : a.tok_vis0[t.cu + ic];
+}
+// (row0: first row of this wave pair's 64-row query tile)
+template <int D>
+__device__ __forceinline__ void dq_setup_at(const BwdArgs& a, const DqTile& t, int hk, int g, bool head_ok, int row0, DqLane<D>& me) {
+  dq_setup_row<D>(a, t, hk, g, head_ok, row0 + 32 * ((threadIdx.x >> 6) & 1) + (threadIdx.x & 31), me);
+}
+// Query chunks: (row, head) pair p of an item, row-major: its row and its head (heads <= 8, p < 256: exact).
+__device__ __forceinline__ int2 dq_pair(int p, int heads) {
+  const int row = (int)((uint32_t)p * ((65536u + heads - 1) / heads) >> 16);
+  return {row, p - row * heads};
 }
 template <int D, int HG>
 __device__ __forceinline__ void dq_setup(const BwdArgs& a, const DqTile& t, int hk, DqLane<D>& me) {
@@ -505,28 +515,27 @@ __device__ __forceinline__ void bwd_token_vis(const BwdArgs& a, int t) {
   a.tok_vis0[t] = a.node_vis[(int64_t)(a.node_start[b] + a.tok_node[t]) * a.W];
 }
 
-// What the other kernels read, as far as it comes from the inputs alone: the chunks of dQ (tables of the sizes in `sizes`) or the
+// What the other kernels read, as far as it comes from the inputs alone: the chunks of dQ or the
 // words of its rows on the block map's tiles, the weights of the key tiles, delta.  One launch, because none of
 // them waits for another and a launch of any of them costs 4.6 us, however little it does; the longest chains
 // first.  Five launches were 23 us of the 114 that 33 nodes of 80 tokens take forward and backward.
 struct PrepareBlocks {
-  int nodes, sizes, tokens, weights, delta;  // blocks of a size, sizes of chunks, and blocks of each of the rest
+  int nodes, tokens, weights, delta;  // blocks of each
 };
 template <int D>
-__global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs p, int sizes, PrepareBlocks n) {
+__global__ void __launch_bounds__(256) k_bwd_delta_tables(BwdArgs a, PrefillArgs p, PrepareBlocks n) {
   int x = blockIdx.x;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (x < n.nodes * n.sizes) {
-    const int i = nth_size(sizes, x / n.nodes), gv = x % n.nodes * 4 + w;
-    int32_t* const runs = x < n.nodes ? p.node_runs : nullptr;
+  if (x < n.nodes) {
+    const int gv = 4 * x + w;
     if (gv >= p.total_nodes) return;
     if (a.W == 1)
-      node_rows<1>(gv, p.n_seqs, (int)p.total_nodes, rows_of(p, i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+      node_rows<1>(gv, p.n_seqs, (int)p.total_nodes, a.pack_rows, a.slots, p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, p.node_runs, a.chunk);
     else
-      node_rows<2>(gv, p.n_seqs, (int)p.total_nodes, rows_of(p, i), slots_of(p, i), p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, runs, tables_of(p, i));
+      node_rows<2>(gv, p.n_seqs, (int)p.total_nodes, a.pack_rows, a.slots, p.node_start, p.cu_seqlens, p.tok_node, p.node_tok_start, p.node_vis, p.node_runs, a.chunk);
     return;
   }
-  x -= n.nodes * n.sizes;
+  x -= n.nodes;
   if (x < n.tokens) {
     if (a.runs) {
       token_depths(p, (int64_t)x * 256);
@@ -1743,10 +1752,10 @@ __device__ void bwd_wide_rows(const BwdArgs& a, int x, int lane) {
 // The tables that need those of the launch in front, a wave each: launch order of the chunks, of the dK / dV workgroups, and
 // (with it for the same reason) the lists above.
 struct OrderBlocks {
-  int chunks, sizes, wide, order;
+  int chunks, wide, order;
 };
 template <int NQ>
-__global__ void __launch_bounds__(256) k_bwd_orders(BwdArgs a, PrefillArgs p, int sizes, OrderBlocks n) {
+__global__ void __launch_bounds__(256) k_bwd_orders(BwdArgs a, OrderBlocks n) {
   int x = blockIdx.x;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (x < n.order) {
@@ -1759,9 +1768,8 @@ __global__ void __launch_bounds__(256) k_bwd_orders(BwdArgs a, PrefillArgs p, in
     return;
   }
   x -= n.wide;
-  const int i = nth_size(sizes, x / n.chunks), slot = x % n.chunks * 4 + w, n_slots = slots_of(p, i);
-  const ChunkTables t = tables_of(p, i);
-  if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
+  const int slot = 4 * x + w;
+  if (slot < a.slots) wide_order(slot, (int)a.slots, a.chunk.cnt, a.chunk.pre, a.chunk.desc, a.chunk.count);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1822,6 +1830,11 @@ struct Dq {
 // in the order of what its node sees, gathered row by row, so that only its last tiles take a mask, and
 // that mask is arithmetic on positions.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of
 // dimension 64: 336 us on the block map's tiles, 240 on chunks.
+// The 32 NW columns of an item are (row, head) pairs, row-major, of all heads of the group (more than eight evenly divided), as in the
+// forward: no head is left over for a launch of its own on chunks of 256 rows, which random DAGs leave half empty, and the
+// pairs without a row are whole waves at the end, which fetch their share of the tiles and leave the matrix pipe to
+// the others.  Forward and backward: 40 / 8 heads, 3 x 82 random nodes 425 -> 340 us, 48 / 8 heads, 3 x 45 663 -> 509; 4 x 64 nodes,
+// 16 / 8 heads of dimension 64 808 -> 786; 26 batches 1.045 times as fast (0.997 at worst).
 // Few chunks leave compute units idle, and a chunk is a chain of 2 us a tile: its tiles are then shared out over up to
 // `pieces` workgroups of at least DQ_PIECE tiles, whose sums k_dq_sum adds up (2214 tokens of one head 70 -> 33 + 5 us, 3515 tokens, 8 / 2 heads: 106 -> 42 + 5).
 // Forward and backward of 40 batches of up to 9000 tokens: of at least 3, 4, 9, 12 tiles 1.00, 1.01, 0.99, 0.99 times as fast (0.97,
@@ -1847,8 +1860,8 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   int cuts = 1, tile0 = 0, tile1 = 0;
   if constexpr (NODES) {
     const int chunk = blockIdx.x / a.dq_pieces, cut = blockIdx.x % a.dq_pieces;
-    if (chunk >= *a.chunk[WIDE].count) return;  // (the launch is sized by a bound)
-    const int32_t* d = a.chunk[WIDE].desc + (size_t)chunk * 8;
+    if (chunk >= *a.chunk.count) return;  // (the launch is sized by a bound)
+    const int32_t* d = a.chunk.desc + (size_t)chunk * 8;
     t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
     cuts = dq_cuts(t.N, a.dq_pieces);
     if (cut >= cuts) return;
@@ -1868,7 +1881,13 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   }
   const int hk = blockIdx.y, cu = t.cu, T = t.T;
   DqLane<D> me;
-  if constexpr (!WIDE)
+  bool idle = false;
+  if constexpr (NODES) {
+    const int2 p = dq_pair(32 * w + L, a.pack_heads);
+    const int g = (int)blockIdx.z * a.pack_heads + p.y;
+    dq_setup_row<D>(a, t, hk, g, p.x < a.pack_rows && g < a.G, t.row0 + min(p.x, a.pack_rows - 1), me);
+    idle = dq_pair(32 * w, a.pack_heads).x >= min(a.pack_rows, t.T - t.row0);
+  } else if constexpr (!WIDE)
     dq_setup<D, NPAIR>(a, t, hk, me);
   else
     dq_setup_at<D>(a, t, hk, a.dq_narrow + (int)blockIdx.z, true, t.row0 + BM * pair, me);
@@ -1885,7 +1904,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   }
   // NODES: the runs of the chunk's node, run e in lane e {first position, token - position}; where the issue
   // cursor is in them; the tokens of its own node in front of this lane's row
-  const int anc = t.nbase, n_pos = t.nbase + min(t.row0 + (WIDE ? BM * NPAIR : BM), t.T);
+  const int anc = t.nbase, n_pos = t.nbase + min(t.row0 + (NODES ? a.pack_rows : 0), t.T);
   int run_pos = 0, run_delta = 0, run_at = 0, run_end = 0, run_d = 0, depth = 0;
   if constexpr (NODES) {
     const int2 run = ((const int2*)a.runs)[t.c0 + lane];
@@ -2072,7 +2091,15 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
         vis = tile_visibility(smem_base + (uint32_t)cs * STAGEB + ND, lane, (uint32_t)nq, own, T - kt * BN, word_of);
         vis = row_ok ? vis >> (4 * H) : 0ull;
       }
-      pipelined_tile(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
+      if (NODES && idle) {  // only the ring's business
+        wait_vmcnt_only<LPS>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int p = 0; p < LPS; ++p) issue_piece(p, ic, is);
+      } else {
+        pipelined_tile(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
+      }
       cs = cs + 1 == NST ? 0 : cs + 1;
       is = is + 1 == NST ? 0 : is + 1;
     }
@@ -2161,16 +2188,16 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
 }
 // Sums of the chunks whose tiles several workgroups share, in the order of the tiles: a wave per sixteen dimensions of a wave of
 // the dQ kernel, everything of eight pieces fetched at once.
-template <int D, bool WIDE>
+template <int D>
 __global__ void __launch_bounds__(256) k_dq_sum(BwdArgs a, int nz) {
-  constexpr int NPAIR = Dq<D>::NPAIR, NW = 2 * NPAIR, PARTS = D / 16, AT_ONCE = 8;
+  constexpr int NW = 2 * Dq<D>::NPAIR, PARTS = D / 16, AT_ONCE = 8;
   const int x = blockIdx.x * 4 + (threadIdx.x >> 6), part = x % PARTS, w = x / PARTS % NW, z = x / (PARTS * NW) % nz;
   const int hk = x / (PARTS * NW) / nz % a.hkv, chunk = x / (PARTS * NW) / nz / a.hkv;
   const int lane = threadIdx.x & 63, L = lane & 31, H = lane >> 5;
-  if (chunk >= *a.chunk[WIDE].count) return;
-  const int32_t* const d = a.chunk[WIDE].desc + (size_t)chunk * 8;
-  const int n = dq_cuts(d[4], a.dq_pieces), g = WIDE ? a.dq_narrow + z : z * NPAIR + (w >> 1);
-  if (n < 2 || (!WIDE && g >= a.dq_narrow)) return;
+  if (chunk >= *a.chunk.count) return;
+  const int32_t* const d = a.chunk.desc + (size_t)chunk * 8;
+  const int n = dq_cuts(d[4], a.dq_pieces), rows = min(a.pack_rows, d[1] - d[2]);
+  if (n < 2 || dq_pair(32 * w, a.pack_heads).x >= rows) return;
   const size_t step = (size_t)a.hkv * nz * NW * (D / 4 * 32);
   const f32x4* const from = a.part + (size_t)chunk * a.dq_pieces * step + (((size_t)hk * nz + z) * NW + w) * (D / 4 * 32) + 2 * part * 64 + lane;
   f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
@@ -2189,9 +2216,10 @@ __global__ void __launch_bounds__(256) k_dq_sum(BwdArgs a, int nz) {
         s1 += v[i][1];
       }
   }
-  const int row = d[2] + (WIDE ? BM * (w >> 1) : 0) + 32 * (w & 1) + L;
-  if (row >= d[1]) return;
-  uint16_t* const to = a.dq + ((size_t)(d[0] + row) * a.hq + hk * a.G + g) * D + 16 * part + 4 * H;
+  const int2 p = dq_pair(32 * w + L, a.pack_heads);
+  const int g = z * a.pack_heads + p.y;
+  if (p.x >= rows || g >= a.G) return;
+  uint16_t* const to = a.dq + ((size_t)(d[0] + d[2] + p.x) * a.hq + hk * a.G + g) * D + 16 * part + 4 * H;
   *(u32x2*)to = u32x2{dag_pack_bf2(s0[0] * a.scale, s0[1] * a.scale), dag_pack_bf2(s0[2] * a.scale, s0[3] * a.scale)};
   *(u32x2*)(to + 8) = u32x2{dag_pack_bf2(s1[0] * a.scale, s1[1] * a.scale), dag_pack_bf2(s1[2] * a.scale, s1[3] * a.scale)};
 }
@@ -2199,10 +2227,8 @@ template <bool WIDE>
 __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE, false>(a); }
 template <bool WIDE>
 __global__ void __launch_bounds__(256, 2) k_bwd64_dq(BwdArgs a) { dq_ring_body<64, WIDE, false>(a); }
-template <bool WIDE>
-__global__ void __launch_bounds__(512) k_nodes_dq2(BwdArgs a) { dq_ring_body<128, WIDE, true>(a); }
-template <bool WIDE>
-__global__ void __launch_bounds__(256, 2) k_nodes64_dq(BwdArgs a) { dq_ring_body<64, WIDE, true>(a); }
+__global__ void __launch_bounds__(512) k_nodes_dq2(BwdArgs a) { dq_ring_body<128, false, true>(a); }
+__global__ void __launch_bounds__(256, 2) k_nodes64_dq(BwdArgs a) { dq_ring_body<64, false, true>(a); }
 
 template <int D, int HG>
 int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
@@ -2214,6 +2240,9 @@ int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }
+
+// Query heads of a KV head in an item of dQ on chunks: all of them, more than eight evenly divided.
+int bwd_pack_heads(int G) { return (G + (G + 7) / 8 - 1) / ((G + 7) / 8); }
 
 // Query heads per KV head that the dQ kernel takes one at a time on several query tiles.
 int bwd_wide_heads(int G, int head_dim) { return G % (head_dim == 128 ? Dq<128>::NPAIR : Dq<64>::NPAIR); }
@@ -2231,55 +2260,47 @@ bool bwd_first_version() {
 int64_t bwd_cut_blocks(int64_t T, int64_t nodes, int64_t ktiles, int64_t n_seqs) { return std::min(ktiles, T / (2 * BN) + nodes + n_seqs); }
 
 template <int D>
-int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_qtiles, long total_ktiles, hipStream_t stream) {
+int launch_bwd(const BwdArgs& args, const PrefillArgs& p, long total_qtiles, long total_ktiles, hipStream_t stream) {
   BwdArgs a = args;
   constexpr int RPB = 256 / (D / 8), NQ = Dq<D>::NPAIR;  // rows per workgroup of bwd_delta
-  const int n_sizes = __builtin_popcount((unsigned)sizes), waves4 = (int)((total_ktiles + 3) / 4);
-  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, n_sizes, (int)((a.total_rows / a.hq + 255) / 256), a.block_start ? a.n_seqs : waves4, (int)((a.total_rows + RPB - 1) / RPB)};
-  hipLaunchKernelGGL((k_bwd_delta_tables<D>), dim3((unsigned)(pre.nodes * pre.sizes + pre.tokens + pre.weights + pre.delta)), dim3(256), 0, stream, a, p, sizes, pre);
+  const int waves4 = (int)((total_ktiles + 3) / 4);
+  const PrepareBlocks pre = {a.runs ? (int)((p.total_nodes + 3) / 4) : 0, (int)((a.total_rows / a.hq + 255) / 256), a.block_start ? a.n_seqs : waves4, (int)((a.total_rows + RPB - 1) / RPB)};
+  hipLaunchKernelGGL((k_bwd_delta_tables<D>), dim3((unsigned)(pre.nodes + pre.tokens + pre.weights + pre.delta)), dim3(256), 0, stream, a, p, pre);
   // (without pieces the flags of k_dkv_finish lie where dQ on the block map's tiles reads the words of its rows)
   const bool order_now = a.pieces || a.runs || !a.dkv_stream;
-  const OrderBlocks ord = {a.runs ? (int)((chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[__builtin_ctz(sizes)]) + 3) / 4) : 0, n_sizes,
+  const OrderBlocks ord = {a.runs ? (int)((a.slots + 3) / 4) : 0,
                            !a.runs && a.dq_narrow < a.G && !bwd_first_version() ? (int)((total_qtiles + 3) / 4) : 0, order_now ? waves4 : 0};
-  if (ord.chunks * ord.sizes + ord.wide + ord.order > 0)
-    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)(ord.chunks * ord.sizes + ord.wide + ord.order)), dim3(256), 0, stream, a, p, sizes, ord);
+  if (ord.chunks + ord.wide + ord.order > 0)
+    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)(ord.chunks + ord.wide + ord.order)), dim3(256), 0, stream, a, ord);
   DAG_LAUNCH_CHECK();
   int rc;
   if (!bwd_first_version()) {
-    // the heads left over by the groups of NPAIR take NPAIR query tiles each
     constexpr int NPAIR = Dq<D>::NPAIR, sm2 = Dq<D>::NST * Dq<D>::STAGEB;
     const int wide = a.G - a.dq_narrow;
     const bool nodes = a.runs != nullptr;
-    auto* const one_tile = D == 128 ? (nodes ? k_nodes_dq2<false> : k_bwd_dq2<false>) : nodes ? k_nodes64_dq<false> : k_bwd64_dq<false>;
-    auto* const many_tiles = D == 128 ? (nodes ? k_nodes_dq2<true> : k_bwd_dq2<true>) : nodes ? k_nodes64_dq<true> : k_bwd64_dq<true>;
+    auto* const one_tile = D == 128 ? (nodes ? k_nodes_dq2 : k_bwd_dq2<false>) : nodes ? k_nodes64_dq : k_bwd64_dq<false>;
+    auto* const many_tiles = D == 128 ? k_bwd_dq2<true> : k_bwd64_dq<true>;
     if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
         hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
-    // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
-    auto pieces_of = [&](int64_t slots, int nz) {
-      const int64_t items = slots * a.hkv * nz, fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
-      return a.pieces && total_qtiles >= 16 * a.n_seqs ? (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES)) : 1;
-    };
-    auto sum_pieces = [&](auto wide_c, int64_t slots, int nz) {
-      if (a.dq_pieces > 1)
-        hipLaunchKernelGGL((k_dq_sum<D, decltype(wide_c)::value>), dim3((unsigned)(slots * a.hkv * nz * 2 * NPAIR * (D / 16) / 4)), dim3(256), 0, stream, a, nz);
-    };
     a.dq_pieces = 1;
-    if (a.dq_narrow > 0) {
-      const int nz = (a.dq_narrow + NPAIR - 1) / NPAIR;
-      if (nodes) a.dq_pieces = pieces_of(a.chunk_slots[0], nz);
-      hipLaunchKernelGGL(one_tile, dim3((unsigned)(nodes ? a.chunk_slots[0] * a.dq_pieces : total_qtiles), (unsigned)a.hkv, (unsigned)nz),
-                         dim3(128 * NPAIR), sm2, stream, a);
-      sum_pieces(std::false_type{}, a.chunk_slots[0], nz);
-    }
-    if (wide > 0 && nodes) {
-      a.dq_pieces = pieces_of(a.chunk_slots[1], wide);
-      hipLaunchKernelGGL(many_tiles, dim3((unsigned)(a.chunk_slots[1] * a.dq_pieces), (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
-      sum_pieces(std::true_type{}, a.chunk_slots[1], wide);
-    } else if (wide > 0) {
-      const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
-      hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
+    if (nodes) {
+      const int nz = (a.G + a.pack_heads - 1) / a.pack_heads;
+      // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
+      // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
+      const int64_t items = a.slots * a.hkv * nz, fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
+      if (a.pieces && total_qtiles >= 16 * a.n_seqs)
+        a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES));
+      hipLaunchKernelGGL(one_tile, dim3((unsigned)(a.slots * a.dq_pieces), (unsigned)a.hkv, (unsigned)nz), dim3(128 * NPAIR), sm2, stream, a);
+      if (a.dq_pieces > 1)
+        hipLaunchKernelGGL((k_dq_sum<D>), dim3((unsigned)(items * 2 * NPAIR * (D / 16) / 4)), dim3(256), 0, stream, a, nz);
+    } else {
+      if (a.dq_narrow > 0)
+        hipLaunchKernelGGL(one_tile, dim3((unsigned)total_qtiles, (unsigned)a.hkv, (unsigned)((a.dq_narrow + NPAIR - 1) / NPAIR)), dim3(128 * NPAIR), sm2, stream, a);
+      if (wide > 0) {  // the heads left over by the groups of NPAIR take NPAIR query tiles each
+        const long groups_bound = std::min(total_qtiles, (total_qtiles + NPAIR - 1) / NPAIR + a.n_seqs);
+        hipLaunchKernelGGL(many_tiles, dim3((unsigned)groups_bound, (unsigned)a.hkv, (unsigned)wide), dim3(128 * NPAIR), sm2, stream, a);
+      }
     }
     rc = hipGetLastError() == hipSuccess ? DAG_OK : DAG_ERR_HIP;
   } else {
@@ -2289,7 +2310,7 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, int sizes, long total_
   }
   if (rc != DAG_OK) return rc;
   if (!order_now) {
-    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)waves4), dim3(256), 0, stream, a, p, 0, OrderBlocks{0, 0, 0, waves4});
+    hipLaunchKernelGGL((k_bwd_orders<NQ>), dim3((unsigned)waves4), dim3(256), 0, stream, a, OrderBlocks{0, 0, waves4});
     DAG_LAUNCH_CHECK();
   }
   if (!bwd_first_version()) {
@@ -2557,10 +2578,11 @@ static bool bwd_dq_on_chunks(const dag_meta_t* m, const BwdArgs& a, int32_t head
   if (!apart(a.q, q_bytes) || !apart(a.dout, q_bytes) || !apart(a.out, q_bytes) || !apart(a.dq, q_bytes) ||
       !apart(a.k, dk_bytes) || !apart(a.v, dk_bytes) || !apart(a.lse, (size_t)a.total_rows * 4))
     return false;
-  // Forward and backward of 4 x 64 nodes of 24 / 32 / 64 / 144 tokens on average, block map : chunks: 32 / 8 heads of
-  // dimension 128 1.06 / 1.05 / 1.06 / 1.05, 16 / 8 heads 0.93 / 0.90 / 1.00 / 1.08 (chunks of 256 rows), 16 / 8
-  // heads of dimension 64 1.09 / 1.05 / 1.10 / 1.07.
-  return T >= (head_dim == 128 && a.dq_narrow < a.G ? 64 : 16) * n;
+  // Forward and backward, block map : chunks (of 256 rows of one head to 32 of eight), 64 random nodes of 17 / 24 / 36 / 55 tokens on
+  // average, dimension 128: 16 / 8 heads 1.09 / 1.15 / 1.21 / 1.29 (four times, once 1.12 to 1.24), 8 / 8 heads 0.96 / 1.00 /
+  // 1.07 / 1.15 (once 1.11 to 1.33), 40 / 8 heads - / 1.23 / 1.28 / 1.37; 32 / 8 heads before the heads were
+  // packed 1.06 / 1.05 / 1.06 from 24 tokens on, 16 / 8 heads of dimension 64 1.09 / 1.05 / 1.10.
+  return T >= 16 * n;
 }
 
 extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const void* k, const void* v, const void* out,
@@ -2650,20 +2672,17 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
   a.runs = nullptr;
   a.block_start = nullptr;
   PrefillArgs p = {};
-  int sizes = 0;
   if (bwd_dq_on_chunks(m, a, head_dim)) {
     p.n_seqs = m->n_seqs; p.W = m->words_per_node;
     p.total_tokens = m->sizes.total_tokens; p.total_nodes = m->sizes.total_nodes;
     p.cu_seqlens = m->cu_seqlens; p.node_start = m->node_start; p.tok_node = m->tok_node; p.node_vis = m->node_vis;
     p.node_tok_start = m->node_tok_start;
     p.sched = (int32_t*)dk;
+    p.pack_heads = a.pack_heads = bwd_pack_heads(a.G);
+    p.pack_rows = a.pack_rows = 32 * PACK_WAVES(head_dim) / a.pack_heads;
     prefill_node_tables(p, p.sched + DAG_SCHED_INTS);
-    const int wide = head_dim == 128 ? 2 : 1;  // chunks of NPAIR x 64 rows
-    sizes = (a.dq_narrow > 0) | (a.dq_narrow < a.G) << wide;
-    for (int i = 0; i < 2; ++i) {
-      a.chunk[i] = p.chunk[i ? wide : 0];
-      a.chunk_slots[i] = chunk_slots(p.total_tokens, p.total_nodes, DAG_CHUNK_ROWS[i ? wide : 0]);
-    }
+    a.chunk = p.chunk[DAG_CHUNK_PACK];
+    a.slots = chunk_slots(p.total_tokens, p.total_nodes, p.pack_rows);
     a.runs = p.node_runs;
     a.tok_depth = p.tok_depth;
     // Blocks cut at node borders are more than the pairs that the piece list has room for, so it lies behind their first keys in the
@@ -2677,6 +2696,6 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
       a.pieces = (int2*)((char*)a.tok_vis0 + start_bytes);
     }
   }
-  return head_dim == 128 ? launch_bwd<128>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
-                         : launch_bwd<64>(a, p, sizes, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
+  return head_dim == 128 ? launch_bwd<128>(a, p, m->sizes.total_qtiles, m->sizes.total_ktiles, s)
+                         : launch_bwd<64>(a, p, m->sizes.total_qtiles, m->sizes.total_ktiles, s);
 }
