@@ -954,6 +954,22 @@ struct Dkv {
     const int n = issued_through(last) - issued_through(i);
     return n < 15 ? n : 15;
   }
+  // The turned iteration (see turned_iter): row operands in the first and third quarter, transposed ones in the second and the
+  // last; the row data of four rows every eight slots.  The first element of a half follows TURN_GAP slots behind the end of its
+  // scores.
+  static constexpr int TURN_GAP = 4;
+  static constexpr bool turned_row(int i) { return i / 16 % 2 == 0; }
+  static constexpr int turned_issued(int k) {
+    int t = 0;
+    for (int o = 0; o <= k; ++o) t += (o >= PF && (o - PF) % 8 == TURN_GAP ? XR : 0) + (turned_row(o) ? 1 : 2);
+    return t;
+  }
+  static constexpr int turned_wait(int i) {
+    const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
+    int n = turned_issued(last) - turned_issued(i);
+    for (int o = last + 1 - PF; o <= i; ++o) n += o % 8 == TURN_GAP ? XR : 0;  // (behind the last operand)
+    return i == NSLOT - 1 ? 0 : n < 15 ? n : 15;
+  }
   // byte offset (after the per-lane part) of operand i
   static constexpr int row_imm(int i) {  // i < NSC: row operand of half i / HS, k-step (i % HS) / 2, of Q (even) or dO (odd)
     return (i & 1) * TILEB + R::row_imm(i / HS, (i % HS) / 2);
@@ -1448,6 +1464,148 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     });
   };
 
+  // ---- The iteration of streams at head dimension 128, turned: a tile's two halves of 32 rows half an iteration apart, so that every
+  // slot has an MFMA and half an element of the exponentials.  One wave has its SIMD to itself, and what does not fit
+  // between two MFMAs (32 clocks) adds to the iteration: with all exponentials in the middle 32 of the 64 slots (pipelined_iter) those slots
+  // were too full and the others idle.  Quarters of 16 slots: scores of half 1 of this tile; dV / dK of half 0; scores
+  // of half 0 of the next tile; dV / dK of half 1.  The exponentials of half 1 start TURN_GAP slots behind its scores, those of the next
+  // tile's half 0 likewise, and so run over into the next iteration (with masks what is done of them then waits for the
+  // next tile's word and is packed behind it).  In the gap more instructions issue than the 19 wait states between the last
+  // MFMA of a chain and a vector instruction that reads its result, so that the scores need no idle states (20 behind each
+  // chain, 60 us of 1170); dV / dK take the rows 0 .. 15 of a half first.
+  struct Turned {
+    f32x16 S[2], dP[2];
+    float pt[2][16], dt[2][16];
+    bf16x8 pp[2][2], dss[2][2];
+    f32x4 nl[2][4], dl[2][4];
+  };
+  auto turned_score = [&](Turned& t, auto hc, auto ec) __attribute__((always_inline)) {  // row element e of half h: P
+    constexpr int h = decltype(hc)::value, e = decltype(ec)::value;
+    t.pt[h][e] = __builtin_amdgcn_exp2f(fmaf(t.S[h][e], sc, t.nl[h][e >> 2][e & 3]));
+  };
+  auto turned_pack = [&](Turned& t, auto hc, auto ec) __attribute__((always_inline)) {  // ... elements e - 1 and e
+    constexpr int h = decltype(hc)::value, e = decltype(ec)::value;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const bf16x2 pb = __builtin_bit_cast(bf16x2, dag_pack_bf2(t.pt[h][e - 1], t.pt[h][e])), db2 = __builtin_bit_cast(bf16x2, dag_pack_bf2(t.dt[h][e - 1], t.dt[h][e]));
+    t.pp[h][e >> 3][(e & 7) - 1] = pb[0];
+    t.pp[h][e >> 3][e & 7] = pb[1];
+    t.dss[h][e >> 3][(e & 7) - 1] = db2[0];
+    t.dss[h][e >> 3][e & 7] = db2[1];
+  };
+  auto turned_rows = [&](Turned& t, uint32_t base, auto hc, auto xc) __attribute__((always_inline)) {  // row data of rows 32 h + 8 x + 4 H .. + 3
+    constexpr int h = decltype(hc)::value, x = decltype(xc)::value;
+    f32x4(*const nlp)[4] = t.nl;
+    f32x4(*const dlp)[4] = t.dl;
+    const uint32_t v = base;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(nlp[h][x]) : "v"(v), "n"(128 * h + 32 * x));
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][x]) : "v"(v), "n"(256 + 128 * h + 32 * x));
+  };
+  auto turned_iter = [&](auto msk_c, Turned& t, int cs, const IssueCtx& ictx, int is, uint32_t vis_lo, uint32_t vis_hi) __attribute__((always_inline)) {
+    constexpr bool MSK = decltype(msk_c)::value;
+    const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB, nbase_ = smem_base + (uint32_t)(cs + 1 == NST ? 0 : cs + 1) * STAGEB;
+    const uint32_t ra = sbase + roff[0], rn = nbase_ + roff[0], ta = sbase + toff, va = sbase + RD + 16 * H, vn = nbase_ + RD + 16 * H;
+    bf16x8 op[NSLOT];
+    v4i16 lo[NSLOT], hi[NSLOT];
+    auto fetch = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      const uint32_t r = i < 32 ? ra : rn, tt = ta;
+      bf16x8* const opp = op;
+      v4i16* const lop = lo;
+      v4i16* const hip_ = hi;
+      if constexpr (i < NSLOT) {
+        if constexpr (C::turned_row(i)) {
+          constexpr int o = i < 16 ? HS + i : i - 32;  // half 1 of this tile, half 0 of the next
+          asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(opp[i]) : "v"(r), "n"(C::row_imm(o) + 32 * (((o % HS) / 2) & 1)));
+        } else {
+          constexpr int r = i % 16, o = NSC + (i < 32 ? 0 : HS) + r % 8 / 2 * 4 + r / 8 * 2 + (r & 1);
+          asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                       : "=&v"(lop[i]), "=&v"(hip_[i])
+                       : "v"(tt), "n"(C::tr_imm(o, 0)), "n"(C::tr_imm(o, 1)));
+        }
+      }
+    };
+    static_for<0, PF>(fetch);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value, q = i / 16, r = i % 16;
+      constexpr int ISSUE = 2 * HS - PF;  // the first operand of the next tile is fetched here
+      if constexpr (i == ISSUE) {
+        sync_mid();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (i % 8 == C::TURN_GAP) {
+        constexpr int x = (i / 8 + 3) % 4, h = i < 8 || i > 40 ? 0 : 1;  // used eight slots later
+        turned_rows(t, i > 40 ? vn : va, std::integral_constant<int, h>{}, std::integral_constant<int, x>{});
+      }
+      fetch(std::integral_constant<int, i + PF>{});
+      wait_lgkmcnt_only<C::turned_wait(i)>();
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (C::turned_row(i)) {
+        constexpr int h = q == 0 ? 1 : 0, s = r / 2;
+        const bf16x8 b_acc = (r & 1) == 0 ? kf[s] : vf[s];
+        f32x16& acc = (r & 1) == 0 ? t.S[h] : t.dP[h];
+        if constexpr (s == 0)
+          acc = mfma32_first_v(op[i], b_acc);
+        else
+          acc = mfma32_next_v(op[i], b_acc, acc);
+      } else {
+        constexpr int h = q == 1 ? 0 : 1, db = r % 8 / 2, hh = r / 8;
+        const v8i16 x = {lo[i][0], lo[i][1], lo[i][2], lo[i][3], hi[i][0], hi[i][1], hi[i][2], hi[i][3]};
+        const bf16x8 opx = __builtin_bit_cast(bf16x8, x);
+        if constexpr ((r & 1) == 0)
+          dV[db] = mfma32(opx, t.pp[h][hh], dV[db]);
+        else
+          dK[db] = mfma32(opx, t.dss[h][hh], dK[db]);
+      }
+      if constexpr (i >= ISSUE && i < ISSUE + LPS) issue_piece(i - ISSUE, ictx, is);
+      {  // an element every two slots: P, then dS (and the pair's packing)
+        constexpr int j = (i + 16 - C::TURN_GAP) % NSLOT, h = j / 32, e = j / 2 % 16;
+        constexpr int LATE = 8 - C::TURN_GAP / 2;  // elements of half 0 that the iteration in front has done
+        std::integral_constant<int, h> hc;
+        std::integral_constant<int, e> ec;
+        if constexpr (j % 2 == 0) {
+          turned_score(t, hc, ec);
+          if constexpr (MSK && i < 48 + C::TURN_GAP) t.pt[h][e] = keep_if_bit<8 * (e >> 2) + (e & 3)>(t.pt[h][e], h == 0 ? vis_lo : vis_hi);
+        } else {
+          t.dt[h][e] = t.pt[h][e] * (t.dP[h][e] - t.dl[h][e >> 2][e & 3]);
+          if constexpr (e % 2 == 1 && !(MSK && i >= 48 + C::TURN_GAP)) turned_pack(t, hc, ec);
+        }
+        if constexpr (MSK && i < 2 * LATE) {
+          constexpr int e0 = i / 2;
+          float& x = i % 2 == 0 ? t.pt[0][e0] : t.dt[0][e0];
+          x = keep_if_bit<8 * (e0 >> 2) + (e0 & 3)>(x, vis_lo);
+          if constexpr (i % 4 == 3) turned_pack(t, std::integral_constant<int, 0>{}, std::integral_constant<int, e0>{});
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // What the first iteration of a walk finds done: the last half of an iteration on the tile in stage cs.
+  auto turned_start = [&](auto msk_c, Turned& t, int cs) __attribute__((always_inline)) {
+    const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB, r = sbase + roff[0], va = sbase + RD + 16 * H;
+    static_for<0, 3>([&](auto xc) __attribute__((always_inline)) { turned_rows(t, va, std::integral_constant<int, 0>{}, xc); });
+    static_for<0, HS>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value, s = i / 2;
+      bf16x8 op;
+      asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=v"(op) : "v"(r), "n"(C::row_imm(i) + 32 * (s & 1)));
+      const bf16x8 b_acc = (i & 1) == 0 ? kf[s] : vf[s];
+      f32x16& acc = (i & 1) == 0 ? t.S[0] : t.dP[0];
+      if constexpr (s == 0)
+        acc = mfma32_first_v(op, b_acc);
+      else if constexpr (s < D / 16 - 1)
+        acc = mfma32_next_v(op, b_acc, acc);
+      else
+        acc = mfma32_last_v(op, b_acc, acc);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, 8 - C::TURN_GAP / 2>([&](auto ec) __attribute__((always_inline)) {
+      constexpr int e = decltype(ec)::value;
+      turned_score(t, std::integral_constant<int, 0>{}, ec);
+      t.dt[0][e] = t.pt[0][e] * (t.dP[0][e] - t.dl[0][e >> 2][e & 3]);
+      if constexpr (e % 2 == 1 && !decltype(msk_c)::value) turned_pack(t, std::integral_constant<int, 0>{}, ec);
+    });
+  };
+
   // ---- the walk of one kind of iteration: query tiles from the last one down (as do the other workgroups of the
   // KV head: they share the rows of the sequence's end in L2), the heads of the group inside
   const int n_tiles = (n_pos + BM - 1) / BM, cuts = piece.y >> 16, cut = piece.y & 0xffff;  // (NODES)
@@ -1488,6 +1646,9 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     int cs = 0, is = NST - 1;
+    constexpr bool TURNED = D == 128 && NODES;
+    Turned t;
+    if constexpr (TURNED) turned_start(msk_c, t, cs);
     // (register classes, at the top of every iteration: the dK / dV accumulators stay in the
     // accumulation registers over the whole loop; without the hint the allocator moves three of
     // the eight back and forth every iteration)
@@ -1517,7 +1678,9 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         for (int db = 0; db < DB; ++db)
           if constexpr (D == 128) asm volatile("" : "+a"(dK[db]), "+a"(dV[db]));
         const IssueCtx ic = prepare_issue(iq, ig);
-        if ((KIND == 0 && !NODES) || active) {
+        if constexpr (TURNED) {  // (a wave to a SIMD: those that have nothing to do wait for the others either way)
+          turned_iter(msk_c, t, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
+        } else if ((KIND == 0 && !NODES) || active) {
           pipelined_iter(msk_c, cs, ic, is, (uint32_t)vis, (uint32_t)(vis >> 32));
         } else {  // only the ring's business
           sync_mid();
@@ -1841,7 +2004,7 @@ struct Dq {
 // 0.99, 0.88, 0.77 at worst), at most 8 or 32 workgroups 1.00.
 constexpr int DQ_PIECE = 6, DQ_MAX_PIECES = 16;
 __device__ __forceinline__ int dq_cuts(int tiles, int pieces) { return max(min(pieces, tiles / DQ_PIECE), 1); }
-template <int D, bool WIDE, bool NODES>
+template <int D, bool WIDE, bool NODES, bool PIECES = false>
 __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   using C = Dq<D>;
   using R = RingTile<D>;
@@ -1859,11 +2022,11 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   int64_t wide_base = 0;
   int cuts = 1, tile0 = 0, tile1 = 0;
   if constexpr (NODES) {
-    const int chunk = blockIdx.x / a.dq_pieces, cut = blockIdx.x % a.dq_pieces;
+    const int chunk = PIECES ? blockIdx.x / a.dq_pieces : blockIdx.x, cut = PIECES ? blockIdx.x % a.dq_pieces : 0;
     if (chunk >= *a.chunk.count) return;  // (the launch is sized by a bound)
     const int32_t* d = a.chunk.desc + (size_t)chunk * 8;
     t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
-    cuts = dq_cuts(t.N, a.dq_pieces);
+    if constexpr (PIECES) cuts = dq_cuts(t.N, a.dq_pieces);
     if (cut >= cuts) return;
     tile0 = cut * (t.N / cuts) + min(cut, t.N % cuts);
     tile1 = tile0 + t.N / cuts + (cut < t.N % cuts);
@@ -2175,7 +2338,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
       }
     }
   }
-  if (NODES && cuts > 1) {
+  if (PIECES && cuts > 1) {
     f32x4* const to = a.part + ((((size_t)blockIdx.x * a.hkv + hk) * gridDim.z + blockIdx.z) * NW + w) * (D / 4 * 32) + lane;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -2227,8 +2390,10 @@ template <bool WIDE>
 __global__ void __launch_bounds__(512) k_bwd_dq2(BwdArgs a) { dq_ring_body<128, WIDE, false>(a); }
 template <bool WIDE>
 __global__ void __launch_bounds__(256, 2) k_bwd64_dq(BwdArgs a) { dq_ring_body<64, WIDE, false>(a); }
-__global__ void __launch_bounds__(512) k_nodes_dq2(BwdArgs a) { dq_ring_body<128, false, true>(a); }
-__global__ void __launch_bounds__(256, 2) k_nodes64_dq(BwdArgs a) { dq_ring_body<64, false, true>(a); }
+template <bool PIECES>
+__global__ void __launch_bounds__(512) k_nodes_dq2(BwdArgs a) { dq_ring_body<128, false, true, PIECES>(a); }
+template <bool PIECES>
+__global__ void __launch_bounds__(256, 2) k_nodes64_dq(BwdArgs a) { dq_ring_body<64, false, true, PIECES>(a); }
 
 template <int D, int HG>
 int launch_dq(const BwdArgs& a, long total_qtiles, hipStream_t stream) {
@@ -2278,19 +2443,24 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, long total_qtiles, lon
     constexpr int NPAIR = Dq<D>::NPAIR, sm2 = Dq<D>::NST * Dq<D>::STAGEB;
     const int wide = a.G - a.dq_narrow;
     const bool nodes = a.runs != nullptr;
-    auto* const one_tile = D == 128 ? (nodes ? k_nodes_dq2 : k_bwd_dq2<false>) : nodes ? k_nodes64_dq : k_bwd64_dq<false>;
+    a.dq_pieces = 1;
+    const int nz = nodes ? (a.G + a.pack_heads - 1) / a.pack_heads : 0;
+    const int64_t items = a.slots * a.hkv * nz;
+    // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
+    // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
+    // (where the chunks alone nearly fill it there is nothing to gain: 6 x 38 nodes, 4 / 1 heads of dimension 64: 84 us in two pieces, 76 without)
+    const int64_t chunks = nodes ? (p.total_tokens / a.pack_rows + p.total_nodes / 2) * a.hkv * nz : 0;
+    if (nodes && a.pieces && total_qtiles >= 16 * a.n_seqs && 4 * chunks < 3 * (D == 128 ? 256 : 512)) {
+      const int64_t fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
+      a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES));
+    }
+    auto* const on_chunks = D == 128 ? (a.dq_pieces > 1 ? k_nodes_dq2<true> : k_nodes_dq2<false>) : a.dq_pieces > 1 ? k_nodes64_dq<true> : k_nodes64_dq<false>;
+    auto* const one_tile = nodes ? on_chunks : D == 128 ? k_bwd_dq2<false> : k_bwd64_dq<false>;
     auto* const many_tiles = D == 128 ? k_bwd_dq2<true> : k_bwd64_dq<true>;
     if (hipFuncSetAttribute((const void*)one_tile, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess ||
         hipFuncSetAttribute((const void*)many_tiles, hipFuncAttributeMaxDynamicSharedMemorySize, sm2) != hipSuccess)
       return DAG_ERR_HIP;
-    a.dq_pieces = 1;
     if (nodes) {
-      const int nz = (a.G + a.pack_heads - 1) / a.pack_heads;
-      // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
-      // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
-      const int64_t items = a.slots * a.hkv * nz, fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
-      if (a.pieces && total_qtiles >= 16 * a.n_seqs)
-        a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES));
       hipLaunchKernelGGL(one_tile, dim3((unsigned)(a.slots * a.dq_pieces), (unsigned)a.hkv, (unsigned)nz), dim3(128 * NPAIR), sm2, stream, a);
       if (a.dq_pieces > 1)
         hipLaunchKernelGGL((k_dq_sum<D>), dim3((unsigned)(items * 2 * NPAIR * (D / 16) / 4)), dim3(256), 0, stream, a, nz);
@@ -2670,6 +2840,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     a.part = (f32x4*)(at + piece_bytes - (size_t)a.max_split * hkv * (2 * BN) * head_dim * 2 * 4);
   }
   a.runs = nullptr;
+  a.slots = 0;
   a.block_start = nullptr;
   PrefillArgs p = {};
   if (bwd_dq_on_chunks(m, a, head_dim)) {
