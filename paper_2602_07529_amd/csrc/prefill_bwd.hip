@@ -936,12 +936,20 @@ struct Dkv {
   static constexpr int NSC = 2 * HS, NSLOT = 4 * HS;
   static constexpr int EPS = 16 / HS;              // scores turned into P and dS per slot (slots HS .. 3 HS - 1)
   static constexpr int VAHEAD = D == 128 ? 8 : 3;  // the row data of four rows are read this many slots before their first use
-  static constexpr int XR = 2;                     // row-data reads per group of four rows: -lse and delta
+  static constexpr int XR = D == 128 ? 2 : 1;      // row-data reads per group of four rows: -lse and delta
+  // V is negated, and the sums of -dP start from delta: no vector instruction subtracts it (but on the block map's tiles at head dimension
+  // 128).  At head dimension 64 it is read in front of the iteration (half 0) or at this slot.
+  // 32 of 171 (dimension 64) and 32 of 153 vector instructions an iteration: 4 x 64 random nodes, 16 / 8 heads of dimension 64 831 -> 810 us, 32 / 8 of
+  // 128 2583 -> 2532, fork-joins 1.00 to 1.01 times as fast.
+  static constexpr int DELTA_SLOT = HS - PF;
   static constexpr int opnd_reads(int o) { return o < NSC ? 1 : 2; }
   // The scores of rows 4 x .. 4 x + 3 of half h are taken from slot HS (1 + h) + 4 x / EPS on; the XR reads
   // of their row data go out VAHEAD >= PF slots earlier, i.e. before the operand read that slot waits
   // for, so they have arrived with it.
   static constexpr int extra_reads(int slot) {
+    return (D != 128 && slot == DELTA_SLOT ? 4 : 0) + row_reads(slot);
+  }
+  static constexpr int row_reads(int slot) {
     return slot >= HS - VAHEAD && slot < 3 * HS - VAHEAD && (slot - (HS - VAHEAD)) % (4 / EPS) == 0 ? XR : 0;
   }
   static constexpr int issued_through(int k) {  // LDS reads issued up to and including those of operand k
@@ -959,15 +967,17 @@ struct Dkv {
   // scores.
   static constexpr int TURN_GAP = 4;
   static constexpr bool turned_row(int i) { return i / 16 % 2 == 0; }
+  static constexpr int TURN_SYNC = 2 * HS - PF;  // the next tile is there; its first operand is fetched in this slot, delta of its half 0 in front of it
+  static constexpr int turned_extra(int slot) { return (slot % 8 == TURN_GAP ? 1 : 0) + (slot == TURN_SYNC ? 4 : 0); }
   static constexpr int turned_issued(int k) {
     int t = 0;
-    for (int o = 0; o <= k; ++o) t += (o >= PF && (o - PF) % 8 == TURN_GAP ? XR : 0) + (turned_row(o) ? 1 : 2);
+    for (int o = 0; o <= k; ++o) t += (o >= PF ? turned_extra(o - PF) : 0) + (turned_row(o) ? 1 : 2);
     return t;
   }
   static constexpr int turned_wait(int i) {
     const int last = i + PF < NSLOT ? i + PF : NSLOT - 1;
     int n = turned_issued(last) - turned_issued(i);
-    for (int o = last + 1 - PF; o <= i; ++o) n += o % 8 == TURN_GAP ? XR : 0;  // (behind the last operand)
+    for (int slot = last + 1 - PF; slot <= i; ++slot) n += turned_extra(slot);  // (behind the last operand)
     return i == NSLOT - 1 ? 0 : n < 15 ? n : 15;
   }
   // byte offset (after the per-lane part) of operand i
@@ -1110,6 +1120,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   for (int s = 0; s < D / 16; ++s) {
     kf[s] = *(const bf16x8*)(a.k + koff + 16 * s + 8 * H);
     vf[s] = *(const bf16x8*)(a.v + koff + 16 * s + 8 * H);
+    if constexpr (D != 128 || NODES) vf[s] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[s]) ^ 0x80008000u);
   }
   const int nj = a.tok_node[cu + jc];
   // the nodes that see this lane's key: bit ni % 64 of seen_by[ni / 64] = bit nj of node ni's words,
@@ -1390,7 +1401,16 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
       f32x4(*const nlp)[4] = nl;
       f32x4(*const dlp)[4] = dl;
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(nlp[h][x]) : "v"(v), "n"(128 * h + 32 * x));
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][x]) : "v"(v), "n"(256 + 128 * h + 32 * x));
+      if constexpr (D == 128) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][x]) : "v"(v), "n"(256 + 128 * h + 32 * x));
+    };
+    auto fetch_delta = [&](auto hc) __attribute__((always_inline)) {
+      constexpr int h = decltype(hc)::value, at = 256 + 128 * h;
+      f32x4(*const dlp)[4] = dl;
+      const uint32_t v = va;
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][0]) : "v"(v), "n"(at));
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][1]) : "v"(v), "n"(at + 32));
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][2]) : "v"(v), "n"(at + 64));
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][3]) : "v"(v), "n"(at + 96));
     };
     auto fetch = [&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
@@ -1406,15 +1426,17 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
                      : "=&v"(lop[i]), "=&v"(hip_[i])
                      : "v"(t), "n"(C::tr_imm(i, 0)), "n"(C::tr_imm(i, 1)));
     };
+    if constexpr (D != 128) fetch_delta(std::integral_constant<int, 0>{});
     static_for<0, PF>(fetch);
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
+      if constexpr (D != 128 && i == C::DELTA_SLOT) fetch_delta(std::integral_constant<int, 1>{});
       if constexpr (i == NSC) {
         sync_mid();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (C::extra_reads(i) != 0) {
+      if constexpr (C::row_reads(i) != 0) {
         constexpr int u = (i + C::VAHEAD - HS) / (4 / EPS);  // rows 4 u .. 4 u + 3 of the 64
         fetch_val(std::integral_constant<int, u / 4>{}, std::integral_constant<int, u % 4>{});
       }
@@ -1427,7 +1449,9 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         f32x16& acc = (i & 1) == 0 ? S[rb] : dP[rb];
         if constexpr (D != 128) {
           const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          acc = mfma32(op[i], b_acc, s == 0 ? zero : acc);
+          const f32x4* const c = dl[rb];
+          const f32x16 from = {c[0][0], c[0][1], c[0][2], c[0][3], c[1][0], c[1][1], c[1][2], c[1][3], c[2][0], c[2][1], c[2][2], c[2][3], c[3][0], c[3][1], c[3][2], c[3][3]};
+          acc = mfma32(op[i], b_acc, s > 0 ? acc : (i & 1) == 0 ? zero : from);
         } else if constexpr (s == 0)
           acc = mfma32_first_v(op[i], b_acc);
         else if constexpr (s < D / 16 - 1)
@@ -1449,7 +1473,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         float pe = __builtin_amdgcn_exp2f(fmaf(S[h][e], sc, nl[h][e >> 2][e & 3]));
         if constexpr (MSK) pe = keep_if_bit<8 * (e >> 2) + (e & 3)>(pe, h == 0 ? vis_lo : vis_hi);  // Eq. 3 and the end of the sequence
         pt[h][e] = pe;
-        dt[h][e] = pe * (dP[h][e] - dl[h][e >> 2][e & 3]);
+        dt[h][e] = D == 128 ? pe * (dP[h][e] - dl[h][e >> 2][e & 3]) : pe * -dP[h][e];  // (V is negated)
         if constexpr ((e & 1) == 1) {
           const uint32_t pw = dag_pack_bf2(pt[h][e - 1], pt[h][e]), dw = dag_pack_bf2(dt[h][e - 1], dt[h][e]);
           typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -1495,10 +1519,22 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   auto turned_rows = [&](Turned& t, uint32_t base, auto hc, auto xc) __attribute__((always_inline)) {  // row data of rows 32 h + 8 x + 4 H .. + 3
     constexpr int h = decltype(hc)::value, x = decltype(xc)::value;
     f32x4(*const nlp)[4] = t.nl;
-    f32x4(*const dlp)[4] = t.dl;
     const uint32_t v = base;
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(nlp[h][x]) : "v"(v), "n"(128 * h + 32 * x));
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dlp[h][x]) : "v"(v), "n"(256 + 128 * h + 32 * x));
+  };
+  auto turned_delta = [&](Turned& t, uint32_t base, auto hc) __attribute__((always_inline)) {  // delta of the rows of half h
+    constexpr int h = decltype(hc)::value, at = 256 + 128 * h;
+    f32x4* const to = t.dl[h];
+    const uint32_t v = base;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to[0]) : "v"(v), "n"(at));
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to[1]) : "v"(v), "n"(at + 32));
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to[2]) : "v"(v), "n"(at + 64));
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to[3]) : "v"(v), "n"(at + 96));
+  };
+  auto turned_first_dp = [&](Turned& t, bf16x8 op, auto hc) __attribute__((always_inline)) {
+    const f32x4* const c = t.dl[decltype(hc)::value];
+    const f32x16 from = {c[0][0], c[0][1], c[0][2], c[0][3], c[1][0], c[1][1], c[1][2], c[1][3], c[2][0], c[2][1], c[2][2], c[2][3], c[3][0], c[3][1], c[3][2], c[3][3]};
+    return mfma32_next_v(op, vf[0], from);
   };
   auto turned_iter = [&](auto msk_c, Turned& t, int cs, const IssueCtx& ictx, int is, uint32_t vis_lo, uint32_t vis_hi) __attribute__((always_inline)) {
     constexpr bool MSK = decltype(msk_c)::value;
@@ -1524,14 +1560,16 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         }
       }
     };
+    turned_delta(t, va, std::integral_constant<int, 1>{});
     static_for<0, PF>(fetch);
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSLOT>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value, q = i / 16, r = i % 16;
-      constexpr int ISSUE = 2 * HS - PF;  // the first operand of the next tile is fetched here
+      constexpr int ISSUE = C::TURN_SYNC;
       if constexpr (i == ISSUE) {
         sync_mid();
         __builtin_amdgcn_sched_barrier(0);
+        turned_delta(t, vn, std::integral_constant<int, 0>{});
       }
       if constexpr (i % 8 == C::TURN_GAP) {
         constexpr int x = (i / 8 + 3) % 4, h = i < 8 || i > 40 ? 0 : 1;  // used eight slots later
@@ -1544,8 +1582,10 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
         constexpr int h = q == 0 ? 1 : 0, s = r / 2;
         const bf16x8 b_acc = (r & 1) == 0 ? kf[s] : vf[s];
         f32x16& acc = (r & 1) == 0 ? t.S[h] : t.dP[h];
-        if constexpr (s == 0)
+        if constexpr (r == 0)
           acc = mfma32_first_v(op[i], b_acc);
+        else if constexpr (r == 1)
+          acc = turned_first_dp(t, op[i], std::integral_constant<int, h>{});
         else
           acc = mfma32_next_v(op[i], b_acc, acc);
       } else {
@@ -1567,7 +1607,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
           turned_score(t, hc, ec);
           if constexpr (MSK && i < 48 + C::TURN_GAP) t.pt[h][e] = keep_if_bit<8 * (e >> 2) + (e & 3)>(t.pt[h][e], h == 0 ? vis_lo : vis_hi);
         } else {
-          t.dt[h][e] = t.pt[h][e] * (t.dP[h][e] - t.dl[h][e >> 2][e & 3]);
+          t.dt[h][e] = t.pt[h][e] * -t.dP[h][e];
           if constexpr (e % 2 == 1 && !(MSK && i >= 48 + C::TURN_GAP)) turned_pack(t, hc, ec);
         }
         if constexpr (MSK && i < 2 * LATE) {
@@ -1584,14 +1624,17 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
   auto turned_start = [&](auto msk_c, Turned& t, int cs) __attribute__((always_inline)) {
     const uint32_t sbase = smem_base + (uint32_t)cs * STAGEB, r = sbase + roff[0], va = sbase + RD + 16 * H;
     static_for<0, 3>([&](auto xc) __attribute__((always_inline)) { turned_rows(t, va, std::integral_constant<int, 0>{}, xc); });
+    turned_delta(t, va, std::integral_constant<int, 0>{});
     static_for<0, HS>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value, s = i / 2;
       bf16x8 op;
       asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=v"(op) : "v"(r), "n"(C::row_imm(i) + 32 * (s & 1)));
       const bf16x8 b_acc = (i & 1) == 0 ? kf[s] : vf[s];
       f32x16& acc = (i & 1) == 0 ? t.S[0] : t.dP[0];
-      if constexpr (s == 0)
+      if constexpr (i == 0)
         acc = mfma32_first_v(op, b_acc);
+      else if constexpr (i == 1)
+        acc = turned_first_dp(t, op, std::integral_constant<int, 0>{});
       else if constexpr (s < D / 16 - 1)
         acc = mfma32_next_v(op, b_acc, acc);
       else
@@ -1601,7 +1644,7 @@ __device__ __forceinline__ void dkv_ring_body(const BwdArgs& a) {
     static_for<0, 8 - C::TURN_GAP / 2>([&](auto ec) __attribute__((always_inline)) {
       constexpr int e = decltype(ec)::value;
       turned_score(t, std::integral_constant<int, 0>{}, ec);
-      t.dt[0][e] = t.pt[0][e] * (t.dP[0][e] - t.dl[0][e >> 2][e & 3]);
+      t.dt[0][e] = t.pt[0][e] * -t.dP[0][e];
       if constexpr (e % 2 == 1 && !decltype(msk_c)::value) turned_pack(t, std::integral_constant<int, 0>{}, ec);
     });
   };
