@@ -422,8 +422,9 @@ __device__ unsigned long long g_tlog[4096];
 template <int D, int HG, int NRG, int STREAM>
 __device__ __forceinline__ void prefill_body(const PrefillArgs& a) {
   constexpr bool PAGED = STREAM == STREAM_PAGES, NODES = STREAM == STREAM_NODES;
-  constexpr bool PACK = NODES || HG == 0;
   constexpr int HGS = HG == 0 ? 1 : HG, NW = HGS * NRG;  // waves: NRG row blocks x HG query heads
+  // (not where a wave has its SIMD to itself: the items of small batches, 650 tokens of 32 / 8 heads 39.0 us packed, 38.8 so)
+  constexpr bool PACK = HG == 0 || (NODES && (NW == 8 || (NW == 4 && D == 64)));
   // Waves without rows leave the arithmetic out, where they share their SIMD with another one (on the block map's tiles there
   // is no register left for it).  8 x 64 random nodes, 32 / 8 heads, a seventh of the chunks' rows empty: 1625 -> 1553 us; 43 batches
   // of one, two and four heads a group 1.026 times as fast (0.99 to 1.14), with the pairs row-major and not head after head, which
