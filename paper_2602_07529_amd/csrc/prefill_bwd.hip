@@ -18,8 +18,9 @@
 //                 head) = 64 slots (described at the kernel); nothing is accumulated through
 //                 atomics, so the results do not depend on the order of execution
 //   k_bwd64_dq, k_bwd64_dkv   the same two for head dimension 64
-//   k_nodes_dq2, k_nodes64_dq   dQ on the forward's query chunks instead of the block map's tiles
-//   k_nodes_dkv2, k_nodes64_dkv   dK/dV with the query rows that see the keys as one compact stream;
+//   k_nodes_dq2, k_nodes64_dq   dQ on the forward's query chunks instead of the block map's tiles, all heads of a group in one item
+//   k_nodes_dkv2, k_nodes64_dkv   dK/dV with the query rows that see the keys as one compact stream, the
+//                 keys in blocks cut at node borders (cut_keys);
 //                 k_dkv_finish behind them for streams in pieces and for keys that a
 //                 hidden Inf or NaN has reached
 //   k_bwd_dq, k_bwd_dkv   the first versions (tiles staged through registers, compiler-scheduled),
@@ -1073,7 +1074,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // NODES: the query rows come as one compact stream instead of the block map's query tiles: the rows of the nodes
-// that see every node of the workgroup's 128 keys (and of the last key's node the rows behind the keys), then
+// that see every node of the workgroup's keys (and of the last key's node the rows behind the keys), then
 // the rows of the other nodes that see one of them, the keys' own among them, each part in token order,
 // gathered row by row.  The tiles made of the first part alone run without tests.  Random DAGs of 4 x 64 nodes of 32 to 256 tokens, 16 / 8 heads of dimension
 // 64: 571 us on the block map's tiles, 529 so; 4 x 4608 fork-join, 32 / 8 heads of dimension 128: 1381 -> 1303 us.

@@ -16,20 +16,45 @@ pytestmark = pytest.mark.gpu
 def _dags(name):
     rng = np.random.Generator(np.random.PCG64(8100))
     return {
-        # every block ends at a border (64, 65, 127, 128 and 129 keys a node), last blocks of 1 and of 63 keys
+        # blocks that end at borders (64, 127, 128 and 129 keys a node), a last block of 63 keys, beside a chain that keeps blocks of 128
         "edges": [dags.linear_chain([64, 65, 127, 128, 129, 1, 63, 192] * 3 + [1]), dags.fork_join(700, [128, 64, 129, 127, 1] * 2, 63),
                   dags.linear_chain([133])],
-        "words": [dags.random_dag(rng, n_nodes=100, depth=6, len_lo=1, len_hi=60)[:2], dags.random_dag(rng, n_nodes=64, depth=5, len_lo=20, len_hi=60)[:2]],
+        "words": [dags.random_dag(rng, n_nodes=70, depth=6, len_lo=10, len_hi=90)[:2], dags.random_dag(rng, n_nodes=30, depth=5, len_lo=20, len_hi=160)[:2]],
         # siblings of about 100 tokens, for which blocks of 128 keys cost less, beside one that is cut
-        "even": [dags.fork_join(484, [106, 90, 120, 100] * 2, 229), dags.random_dag(rng, n_nodes=40, depth=5, len_lo=30, len_hi=150)[:2], dags.linear_chain([700])],
+        "even": [dags.fork_join(484, [106, 95, 100, 111] * 3, 30), dags.random_dag(rng, n_nodes=40, depth=5, len_lo=30, len_hi=150)[:2], dags.linear_chain([700])],
     }[name]
 
 
-@pytest.mark.parametrize("name", ["edges", "words", "even"])
+def _is_cut(L, anc, g):
+    """The rule of cut_keys: blocks at borders where their streams cost 3 % less than those of blocks of 128 keys."""
+    L = [int(x) for x in L]
+    n, starts = len(L), [int(x) for x in np.cumsum([0] + L)]
+    T = starts[-1]
+    sees = np.zeros((n, n), dtype=bool)
+    for v in range(n):
+        sees[v, [u for u in range(n) if int(anc[v][u >> 6]) >> (u & 63) & 1]] = sees[v, v] = True
+    node = np.repeat(np.arange(n), L)
+    costs = []
+    for cut in (False, True):
+        key0, cost = 0, 0.0
+        while key0 < T:
+            ends = [b for b in starts if key0 + 64 <= b <= key0 + 128]
+            key1 = T if T <= key0 + 128 else ends[-1] if cut and ends else key0 + 128
+            u0, u1 = node[key0], node[key1 - 1]
+            rows = starts[u0] - key0 + sum(L[v] for v in range(n) if sees[v, u0:u1 + 1].any())
+            sure = sum(starts[u1 + 1] - key1 if v == u1 else L[v] for v in range(n) if sees[v, u0:u1 + 1].all())
+            cost += g * (1.25 * (-(-rows // 64)) - 0.25 * (sure // 64)) + 8
+            key0 = key1
+        costs.append(cost)
+    return not costs[0] < 1.03 * costs[1]
+
+
+@pytest.mark.parametrize("name,cut", [("edges", [False, True, False]), ("words", [True, True]), ("even", [False, True, False])])
 @pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (8, 2, 64), (4, 2, 128), (5, 1, 128)])
-def test_dkv_blocks(name, hq, hkv, d):
+def test_dkv_blocks(name, cut, hq, hkv, d):
     dag_list = _dags(name)
     assert sum(int(np.sum(L)) for L, _ in dag_list) >= 4096
+    assert [_is_cut(L, anc, hq // hkv) for L, anc in dag_list] == cut
     inputs, grads = _forward_backward(dag_list, hq, hkv, d, 8200 + hq)
     _check_against_oracle(dag_list, inputs, grads)
 
@@ -38,22 +63,22 @@ def test_dkv_blocks(name, hq, hkv, d):
 def test_hidden_keys_behind_a_short_block(hq, hkv, d):
     """A branch whose rows are Inf, next to blocks of fewer than 128 keys: the lanes of those blocks without a key of their own take part
     in the tiles without masks and must not reach anything that is stored."""
-    L, anc = dag = dags.fork_join(50, [1000, 130, 900, 70, 1900], 300)
+    L, anc = dag = dags.fork_join(300, [128, 64, 129, 127, 193] * 7, 63)
     T = int(np.sum(L))
-    assert T >= 4096
+    assert T >= 4096 and _is_cut(L, anc, hq // hkv)
     q, k, v = dags.make_qkv(8300, T, hq, hkv, d, 0.7, torch.bfloat16)
     dout = dags.make_qkv(8301, T, hq, hkv, d, 1.0, torch.bfloat16)[0]
     ref = orc.attn_prefill_bwd(*(dags.to_f64(x) for x in (q, k, v, dout)), L, anc)
     _, meta = build_meta([dag], hq, hkv, d, torch.bfloat16)
     out, lse = torch.empty_like(q, device=DEV), torch.empty(T, hq, dtype=torch.float32, device=DEV)
     B.dag_attn_prefill(meta, q.to(DEV), k.to(DEV), v.to(DEV), out, lse)
-    bad = slice(1050, 1180)  # the second branch
+    bad = slice(428, 492)  # the second branch
     qd, dod = q.to(DEV), dout.to(DEV)
     qd[bad], dod[bad] = float("inf"), float("inf")
     dq, dk, dv = torch.empty_like(qd), torch.empty(T, hkv, d, dtype=torch.bfloat16, device=DEV), torch.empty(T, hkv, d, dtype=torch.bfloat16, device=DEV)
     B.dag_attn_prefill_bwd(meta, qd, k.to(DEV), v.to(DEV), out, dod, lse, dq, dk, dv)
     torch.cuda.synchronize()
-    for sl in (slice(50, 1050), slice(1180, T)):
+    for sl in (slice(300, 428), slice(492, T)):
         check_close(dk[sl], ref[1][sl], torch.bfloat16, "dk")
         check_close(dv[sl], ref[2][sl], torch.bfloat16, "dv")
-    assert not torch.isfinite(dv[:50].float()).all(dim=-1).any()
+    assert not torch.isfinite(dv[:300].float()).all(dim=-1).any()
