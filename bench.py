@@ -332,26 +332,25 @@ def _shape(pw):
 
 def prefill_kernels(pw):
     """The attention launches of dag_attn_prefill at head dimension 128 (bf16, batches that fill the device): on query
-    chunks items of four heads on 64 rows, pairs on 128, single heads on 256; on the block map's tiles four heads
-    on 64 rows, the others one by one on 256."""
+    chunks items of four heads on 64 rows, pairs on 128, single heads on 256, other groups packed; on the block map's
+    tiles four heads on 64 rows, the others one by one on 256."""
     T, nodes, words, G = _shape(pw)
     rest = G % 4
     if words <= 2 and T >= (32 if G % 2 else 16) * nodes:
-        return (["k_prefill_nodes<128,4,2>"] if G > rest else []) + (["k_prefill_nodes<128,2,4>"] if rest & 2 else []) + \
-               (["k_prefill_nodes<128,1,8>"] if rest & 1 else [])
+        return [{1: "k_prefill_nodes<128,1,8>", 2: "k_prefill_nodes<128,2,4>", 4: "k_prefill_nodes<128,4,2>"}.get(G, "k_prefill_packed<128,8,2>")]
     return (["k_prefill_bf16<128,4,2,false>"] if G > rest else []) + (["k_prefill_bf16<128,1,8,false>"] if rest else [])
 
 
 def bwd_kernels(pw):
     """The launches of dag_attn_prefill_bwd at head dimension 128 (batches with more chunks than the device holds, so that
-    no chunk is shared and k_dq_sum not launched): delta and tables, orders, dQ for groups of four heads on one chunk or query
-    tile (<false>) and for the left-over heads one by one on 256 rows (<true>), dK / dV and the sums of its pieces."""
+    no chunk is shared and k_dq_sum not launched): delta and tables, orders, dQ for all heads of a group on query chunks or, on
+    the block map's tiles, for groups of four heads on one tile (<false>) and the left-over heads one by one on 256 rows
+    (<true>), dK / dV and the sums of its pieces."""
     T, nodes, words, G = _shape(pw)
     rest = G % 4
-    chunks = words <= 2 and T >= (64 if rest else 16) * nodes
-    dq = "k_nodes_dq2" if chunks else "k_bwd_dq2"
-    return ("k_bwd_delta_tables<128>", "k_bwd_orders<4>") + ((dq + "<false>",) if G > rest else ()) + ((dq + "<true>",) if rest else ()) + \
-        (("k_nodes_dkv2", "k_dkv_finish<128>") if words <= 2 and T >= 16 * nodes else ("k_bwd_dkv2",))
+    chunks = words <= 2 and T >= 16 * nodes
+    dq = ("k_nodes_dq2<false>",) if chunks else (("k_bwd_dq2<false>",) if G > rest else ()) + (("k_bwd_dq2<true>",) if rest else ())
+    return ("k_bwd_delta_tables<128>", "k_bwd_orders<4>") + dq + (("k_nodes_dkv2", "k_dkv_finish<128>") if chunks else ("k_bwd_dkv2",))
 
 
 def prefill_leg(cfg, dev, launches, warmup, workload_key, with_bwd=False):
