@@ -302,18 +302,23 @@ __global__ void __launch_bounds__(256) k_chunk_order(PrefillArgs a, int sizes) {
   const ChunkTables t = tables_of(a, i);
   if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
 }
-// The table of packed heads in a workspace that may have been prepared for another head count.
+// The table of packed heads in a workspace that may have been prepared for another head count.  Where it is of the call's rows already it
+// stays: the counts and descriptors that the order is made from are then not always there (k_node_rows_small keeps them in LDS).
+// The first launch says in count[2] whether it has built them, so that the blocks of the second agree while one of them writes count[1].
 template <int W>
 __global__ void __launch_bounds__(256) k_pack_rows(PrefillArgs a) {
   const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
   const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t.count[1] == a.pack_rows || gv >= a.total_nodes) return;
+  const bool build = t.count[1] != a.pack_rows;
+  if (blockIdx.x == 0 && threadIdx.x == 0) t.count[2] = build;
+  if (!build || gv >= a.total_nodes) return;
   node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, a.pack_rows, slots_of(a, DAG_CHUNK_PACK), a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
                a.node_vis, nullptr, t);
 }
 __global__ void __launch_bounds__(256) k_pack_order(PrefillArgs a) {
   const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
   const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), n_slots = slots_of(a, DAG_CHUNK_PACK);
+  if (t.count[2] == 0) return;
   if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
   if (blockIdx.x == 0 && threadIdx.x == 0) t.count[1] = a.pack_rows;
 }

@@ -73,6 +73,42 @@ def test_prepared_for_another_group(order, d):
         assert torch.equal(out, ref)
 
 
+# few nodes and slots: the tables come from the kernel that keeps their counts and descriptors in LDS, so that nothing but the ordered
+# table is in the workspace.  The same group, twice, another one in between, and behind a combined call.
+@pytest.mark.gpu
+@pytest.mark.parametrize("g,other,d", [(5, 8, 128), (8, 3, 128), (3, 5, 128), (6, 7, 128), (4, 8, 64), (5, 3, 64), (8, 4, 64)])
+@pytest.mark.parametrize("lengths", [[700, 200, 150, 256, 188, 170], [400, 64, 90, 130, 150, 33, 256, 120, 75, 80, 100, 166]])
+def test_prepared_for_few_nodes(g, other, d, lengths):
+    hkv = 8
+    dag_list = [dags.fork_join(lengths[0], lengths[1:-1], lengths[-1])]
+    T, nodes = _sizes(dag_list)[:2]
+    assert T == 1664 and nodes == len(lengths) <= 64
+    _, meta = build_meta(dag_list, hkv, hkv, d, torch.bfloat16)
+    v = dags.make_qkv(9420, T, hkv, hkv, d, 0.5, torch.bfloat16)[2].to(DEV)
+    calls = {}
+    for x in (g, other):
+        assert _packed(dag_list, x * hkv, hkv, d) and T // ((256 if d == 128 else 128) // x) + nodes <= 128
+        q, k, _ = (t.to(DEV) for t in dags.make_qkv(9421 + x, T, x * hkv, hkv, d, 0.5, torch.bfloat16))
+        ref = torch.empty_like(q)
+        B.dag_attn_prefill(meta, q, k, v, ref)
+        calls[x] = q, k, ref
+    ws = torch.ones(B.dag_prefill_workspace_bytes(meta, hkv, d, B.DAG_BF16), dtype=torch.uint8, device=DEV)
+
+    def prepared(x):
+        q, k, ref = calls[x]
+        out = torch.zeros_like(q)
+        B.dag_attn_prefill(meta, q, k, v, out, workspace=ws, prepared=True)
+        assert torch.equal(out, ref)
+
+    B.dag_prefill_prepare_v(meta, v, g * hkv, workspace=ws)
+    for x in (g, g, other, other, g):
+        prepared(x)
+    ws.fill_(1)
+    B.dag_attn_prefill(meta, calls[g][0], calls[g][1], v, torch.empty_like(calls[g][0]), workspace=ws)
+    for x in (g, g, other):
+        prepared(x)
+
+
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 def test_generated_code_of_the_packed_kernels(tmp_path):
     seen = 0
