@@ -276,10 +276,10 @@ __global__ void __launch_bounds__(256) k_wide_order(int total_qtiles, const int3
   if (qt < total_qtiles) wide_order(qt, total_qtiles, wide_cnt, wide_pre, wide_desc, wide_count);
 }
 
-// The work counters of the attention kernel, and which rows the table of packed heads is for.
+// The work counters of the attention kernel, which rows the table of packed heads is for, and the counter of k_pack_tables.
 __device__ __forceinline__ void start_tables(const PrefillArgs& a) {
   if (threadIdx.x < DAG_SCHED_INTS) a.sched[threadIdx.x] = 0;
-  if (threadIdx.x == 0) a.chunk[DAG_CHUNK_PACK].count[1] = a.pack_rows;
+  if (threadIdx.x < 2) a.chunk[DAG_CHUNK_PACK].count[1 + threadIdx.x] = threadIdx.x == 0 ? a.pack_rows : 0;
 }
 // Four nodes a block, then (of the first size) blocks of 256 tokens.
 template <int W>
@@ -302,25 +302,57 @@ __global__ void __launch_bounds__(256) k_chunk_order(PrefillArgs a, int sizes) {
   const ChunkTables t = tables_of(a, i);
   if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
 }
-// The table of packed heads in a workspace that may have been prepared for another head count.  Where it is of the call's rows already it
-// stays: the counts and descriptors that the order is made from are then not always there (k_node_rows_small keeps them in LDS).
-// The first launch says in count[2] whether it has built them, so that the blocks of the second agree while one of them writes count[1].
+// The table of packed heads in a workspace that may have been prepared for another head count: nothing to do where it is of the call's
+// rows already, MATCHED.  Otherwise four nodes a block, and the block that ends last makes the launch order, by
+// descending tile count (4095 tiles and more are one) in a counting sort: the ranks of wide_order are quadratic in the slots, which
+// one workgroup cannot afford, and a launch of their own would be paid by the calls that find their table, too.
+// (count[2]: blocks that have ended.  count[1] is written when all of them have read it.)
+constexpr int PACK_BUCKETS = 4096;
 template <int W>
-__global__ void __launch_bounds__(256) k_pack_rows(PrefillArgs a) {
+__global__ void __launch_bounds__(256) k_pack_tables(PrefillArgs a) {
+  __shared__ int s_place[PACK_BUCKETS], s_wave[4], s_last;
   const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
-  const int gv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const bool build = t.count[1] != a.pack_rows;
-  if (blockIdx.x == 0 && threadIdx.x == 0) t.count[2] = build;
-  if (!build || gv >= a.total_nodes) return;
-  node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, a.pack_rows, slots_of(a, DAG_CHUNK_PACK), a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start,
-               a.node_vis, nullptr, t);
-}
-__global__ void __launch_bounds__(256) k_pack_order(PrefillArgs a) {
-  const ChunkTables t = a.chunk[DAG_CHUNK_PACK];
-  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), n_slots = slots_of(a, DAG_CHUNK_PACK);
-  if (t.count[2] == 0) return;
-  if (slot < n_slots) wide_order(slot, n_slots, t.cnt, t.pre, t.desc, t.count);
-  if (blockIdx.x == 0 && threadIdx.x == 0) t.count[1] = a.pack_rows;
+  if (t.count[1] == a.pack_rows) return;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gv = blockIdx.x * 4 + w, n_slots = slots_of(a, DAG_CHUNK_PACK);
+  if (gv < a.total_nodes)
+    node_rows<W>(gv, a.n_seqs, (int)a.total_nodes, a.pack_rows, n_slots, a.node_start, a.cu_seqlens, a.tok_node, a.node_tok_start, a.node_vis,
+                 nullptr, t);
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) s_last = __hip_atomic_fetch_add(t.count + 2, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  constexpr int PER = PACK_BUCKETS / 256;  // buckets of a thread: bucket x has the chunks of PACK_BUCKETS - 1 - x tiles
+  for (int x = tid; x < PACK_BUCKETS; x += 256) s_place[x] = 0;
+  __syncthreads();
+  auto bucket = [&](int tiles) { return PACK_BUCKETS - 1 - min(tiles, PACK_BUCKETS - 1); };
+  for (int x = tid; x < n_slots; x += 256)
+    if (t.cnt[x] >= 0) atomicAdd(s_place + bucket(t.cnt[x]), 1);
+  __syncthreads();
+  int sum = 0;
+  for (int x = 0; x < PER; ++x) sum += s_place[tid * PER + x];
+  const int incl = dag_wave_scan(sum);
+  if (lane == 63) s_wave[w] = incl;
+  __syncthreads();
+  int at = incl - sum;
+  for (int x = 0; x < w; ++x) at += s_wave[x];
+  if (tid == 255) t.count[0] = at + sum;
+  for (int x = 0; x < PER; ++x) {
+    const int n = s_place[tid * PER + x];
+    s_place[tid * PER + x] = at;
+    at += n;
+  }
+  __syncthreads();
+  for (int x = tid; x < n_slots; x += 256)
+    if (t.cnt[x] >= 0) {
+      const int64_t to = atomicAdd(s_place + bucket(t.cnt[x]), 1);
+      for (int y = 0; y < 8; ++y) t.desc[to * 8 + y] = t.pre[(int64_t)x * 8 + y];
+    }
+  if (tid == 0) {
+    t.count[1] = a.pack_rows;
+    t.count[2] = 0;
+  }
 }
 // Few nodes: the tables of a size and their order in one workgroup (15 slots: 4.0 us instead of 3.8 + 2.2), and
 // blocks of 1024 tokens.
@@ -2125,9 +2157,7 @@ int launch_prefill_paged(const PagedPrefillArgs& pa, int head_dim, hipStream_t s
 
 int launch_prefill_pack_tables(const PrefillArgs& a, int head_dim, hipStream_t stream) {
   if (!on_chunks(a, head_dim) || !packed(a, head_dim)) return DAG_OK;
-  const int64_t slots = chunk_slots(a.total_tokens, a.total_nodes, a.pack_rows);
-  hipLaunchKernelGGL(a.W == 1 ? k_pack_rows<1> : k_pack_rows<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream, a);
-  hipLaunchKernelGGL(k_pack_order, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(a.W == 1 ? k_pack_tables<1> : k_pack_tables<2>, dim3((unsigned)((a.total_nodes + 3) / 4)), dim3(256), 0, stream, a);
   DAG_LAUNCH_CHECK();
   return DAG_OK;
 }

@@ -13,7 +13,7 @@ constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};  // (each twice 
 // (row, head) pairs have, at least PACK_MIN_ROWS.
 constexpr int DAG_CHUNK_PACK = DAG_CHUNK_SIZES, PACK_MIN_ROWS = 16;
 struct ChunkTables {
-  int32_t* count;  // [3] number of chunks; (packed heads) the rows that the table was built for, 0: not built; whether a prepared call builds it
+  int32_t* count;  // [3] number of chunks; (packed heads) the rows that the table was built for, 0: not built; see k_pack_tables
   int32_t* cnt;    // [slots] key tiles of the chunk, -1: no chunk here
   int32_t* pre;    // [slots][8] its descriptor
   int32_t* desc;   // [slots][8] descriptors in launch order

@@ -1,5 +1,6 @@
 """Helpers shared by the GPU parity tests: run the library through its binding, run the oracle on
 the same inputs, and compare to the stated tolerances."""
+import ctypes as C
 import os
 import subprocess
 import sys
@@ -168,3 +169,31 @@ def in_a_process_of_its_own(call, **env):
     r = subprocess.run([sys.executable, "-c", "import %s; %s" % (module, call)], cwd=root, env=dict(os.environ, **env), timeout=100,
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+class _KernelNode(C.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3), ("params", C.c_void_p),
+                ("shared", C.c_uint32)]
+
+
+def launched_kernels(step):
+    """The mangled names of the kernels that `step` launches, in their order: a capture of it, taken apart."""
+    hip = B.lib()  # (the HIP runtime that it is linked to)
+    hip.hipKernelNameRefByPtr.restype = C.c_char_p
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        step()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=s):
+            step()
+    graph, n = C.c_void_p(g.raw_cuda_graph()), C.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    names = []
+    for x in nodes:
+        node = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(x), C.byref(node)) == 0  # (an error for a node that is no kernel)
+        names.append(hip.hipKernelNameRefByPtr(C.c_void_p(node.func), None).decode())
+    return names

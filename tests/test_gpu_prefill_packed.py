@@ -8,7 +8,7 @@ import torch
 
 from paper_2602_07529_amd import binding as B
 from workloads import dags
-from tests.gpu_util import DEV, build_meta, check_close, oracle_prefill, run_prefill
+from tests.gpu_util import DEV, build_meta, check_close, launched_kernels, oracle_prefill, run_prefill
 from tests.test_asm_lds_reads import HIPCC, _assembly, _conflicts_of_kernel, _kernels
 from tests.test_gpu_prefill_routes import _heads_per_item_of_a_small_batch, _on_chunks, _sizes
 
@@ -107,6 +107,22 @@ def test_prepared_for_few_nodes(g, other, d, lengths):
     B.dag_attn_prefill(meta, calls[g][0], calls[g][1], v, torch.empty_like(calls[g][0]), workspace=ws)
     for x in (g, g, other):
         prepared(x)
+
+
+# a prepared call is the attention kernel, with packed heads behind a look at their table
+@pytest.mark.gpu
+@pytest.mark.parametrize("g,d,copies", [(5, 128, 30), (8, 128, 4), (4, 64, 30), (4, 128, 30), (2, 64, 30), (5, 128, 1)])
+def test_launches_of_a_prepared_call(g, d, copies):
+    hkv = 2
+    dag_list = [dags.fork_join(130, [40, 64, 33, 150, 63], 70)] * copies
+    q, k, v = (t.to(DEV) for t in dags.make_qkv(9430, _sizes(dag_list)[0], g * hkv, hkv, d, 0.5, torch.bfloat16))
+    _, meta = build_meta(dag_list, g * hkv, hkv, d, torch.bfloat16)
+    ws = torch.zeros(B.dag_prefill_workspace_bytes(meta, hkv, d, B.DAG_BF16), dtype=torch.uint8, device=DEV)
+    B.dag_prefill_prepare_v(meta, v, g * hkv, workspace=ws)
+    out = torch.empty_like(q)
+    names = launched_kernels(lambda: B.dag_attn_prefill(meta, q, k, v, out, workspace=ws, prepared=True))
+    want = ["k_pack_tables", "k_prefill_packed"] if _packed(dag_list, g * hkv, hkv, d) else ["k_prefill_nodes"]
+    assert len(names) == len(want) and all(w in n for w, n in zip(want, names)), names
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
