@@ -25,8 +25,9 @@ def _dags(name):
     }[name]
 
 
-def _is_cut(L, anc, g):
-    """The rule of cut_keys: blocks at borders where their streams cost 3 % less than those of blocks of 128 keys."""
+def _blocks(L, anc, g):
+    """The rule of cut_keys: (first keys of the blocks, whether they are cut at borders), which they are where their streams cost 3 % less
+    than those of blocks of 128 keys."""
     L = [int(x) for x in L]
     n, starts = len(L), [int(x) for x in np.cumsum([0] + L)]
     T = starts[-1]
@@ -34,10 +35,11 @@ def _is_cut(L, anc, g):
     for v in range(n):
         sees[v, [u for u in range(n) if int(anc[v][u >> 6]) >> (u & 63) & 1]] = sees[v, v] = True
     node = np.repeat(np.arange(n), L)
-    costs = []
+    costs, keys = [], [[], []]
     for cut in (False, True):
         key0, cost = 0, 0.0
         while key0 < T:
+            keys[cut].append(key0)
             ends = [b for b in starts if key0 + 64 <= b <= key0 + 128]
             key1 = T if T <= key0 + 128 else ends[-1] if cut and ends else key0 + 128
             u0, u1 = node[key0], node[key1 - 1]
@@ -46,16 +48,40 @@ def _is_cut(L, anc, g):
             cost += g * (1.25 * (-(-rows // 64)) - 0.25 * (sure // 64)) + 8
             key0 = key1
         costs.append(cost)
-    return not costs[0] < 1.03 * costs[1]
+    cut = not costs[0] < 1.03 * costs[1]
+    return keys[cut], cut
+
+
+def _is_cut(L, anc, g):
+    return _blocks(L, anc, g)[1]
+
+
+def _key_tables(meta, ws, hq):
+    """What a call has left of its blocks in the workspace: (weights, first keys), a slot for every 64 keys of a sequence."""
+    up = lambda n: -(-n // 256) * 256  # noqa: E731
+    rows, tiles = up(meta.sizes.total_tokens * hq * 4), meta.sizes.total_ktiles
+    skip = -ws.data_ptr() % 256
+    at = lambda o: ws[skip + o:skip + o + 4 * tiles].view(torch.int32).cpu().numpy()  # noqa: E731
+    return at(2 * rows), at(2 * rows + 2 * up(4 * tiles))
 
 
 @pytest.mark.parametrize("name,cut", [("edges", [False, True, False]), ("words", [True, True]), ("even", [False, True, False])])
 @pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (8, 2, 64), (4, 2, 128), (5, 1, 128)])
-def test_dkv_blocks(name, cut, hq, hkv, d):
+def test_dkv_blocks(name, cut, hq, hkv, d, monkeypatch):
     dag_list = _dags(name)
     assert sum(int(np.sum(L)) for L, _ in dag_list) >= 4096
-    assert [_is_cut(L, anc, hq // hkv) for L, anc in dag_list] == cut
+    blocks = [_blocks(L, anc, hq // hkv) for L, anc in dag_list]
+    assert [c for _, c in blocks] == cut
+    _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
+    ws = torch.zeros(B.dag_prefill_bwd_workspace_bytes(meta, hq, hkv, d), dtype=torch.uint8, device=DEV)
+    call = B.dag_attn_prefill_bwd
+    monkeypatch.setattr(B, "dag_attn_prefill_bwd", lambda *args, **kw: call(*args, workspace=ws, **kw))
     inputs, grads = _forward_backward(dag_list, hq, hkv, d, 8200 + hq)
+    first = _key_tables(meta, ws, hq)[1]
+    for (L, _), (keys, _) in zip(dag_list, blocks):   # (slots without a block hold the end of the sequence)
+        T = int(np.sum(L))
+        slots, first = first[:-(-T // 64)], first[-(-T // 64):]
+        assert slots.tolist() == keys + [T] * (len(slots) - len(keys))
     _check_against_oracle(dag_list, inputs, grads)
 
 
