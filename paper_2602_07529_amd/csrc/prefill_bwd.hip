@@ -428,43 +428,37 @@ __device__ __forceinline__ void bwd_weight(const BwdArgs& a, int kt, int lane) {
 // time by the tiles of the streams, one with masks 1.25 times one without, and DKV_BLOCK_STEPS iterations a workgroup.
 // Forward and backward of 4 x 64 random nodes, 16 / 8 heads of dimension 64: 835 -> 788 us; 21 other batches 1.012 times as fast,
 // random ones with long nodes 1.03 to 1.13 (0.984 at worst).
-// (A workgroup a sequence.  The blocks follow one from the other, so every wave finds all of them, 80 clocks each; a thread
-// then weighs a block, the nodes in LDS.  Blocks weighed by whole waves, a node a lane, took 5 to 28 us.)
-constexpr int BLOCK_MIN = 64, DKV_BLOCK_STEPS = 8;
+// (A workgroup a sequence.  The blocks follow one from the other, 80 clocks each: the first wave finds them while the others weigh the blocks
+// of 128, and then all weigh those.  Four lanes a block, the nodes and the first keys in LDS.  With all waves finding the blocks first, and
+// their keys and nodes read from memory, the launch in front of dQ took 24.0 instead of 16.7 us for one sequence of 67 nodes, 10,700
+// tokens, 12.9 instead of 10.9 for a fork of 18, 6600 tokens; without cuts 9.4 and 7.4.  Blocks weighed by whole waves, a node a
+// lane, took 5 to 28 us.)
+constexpr int BLOCK_MIN = 64, DKV_BLOCK_STEPS = 8, MAX_CUT_BLOCKS = 1024;
 __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
-  __shared__ uint64_t s_word[2][128];  // what a node sees
+  __shared__ uint64_t s_word[128][2];  // what a node sees
   __shared__ int s_first[129];
+  __shared__ int s_start[MAX_CUT_BLOCKS + 1];  // first keys of the blocks cut at borders
+  __shared__ int s_weight[MAX_CUT_BLOCKS];
   __shared__ float s_cost[2][4];
-  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ int s_blocks;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n0 = a.node_start[b], n = a.node_start[b + 1] - n0, cu = a.cu_seqlens[b], T = a.cu_seqlens[b + 1] - cu;
   const int slots = (T + BN - 1) / BN, n_even = (slots + 1) / 2;
-  if (tid <= 128) s_first[tid] = tid < n ? a.node_tok_start[n0 + tid] : T;
-  s_word[tid >> 7][tid & 127] = (tid >> 7) < a.W && (tid & 127) < n ? a.node_vis[(int64_t)(n0 + (tid & 127)) * a.W + (tid >> 7)] : 0;
-  __syncthreads();
   int32_t* const start = a.block_start + a.ktile_start[b];
   int32_t* const weight = a.kt_weight + a.ktile_start[b];
-  int32_t* const weight_even = a.kt_order + a.ktile_start[b];  // (with pieces nothing else is here yet)
-  const int first0 = s_first[lane], first1 = s_first[64 + lane];
-  int n_cut = 0, mine = 0;
-  for (int key0 = 0; key0 < T; ++n_cut) {
-    mine = lane == (n_cut & 63) ? key0 : mine;
-    if ((n_cut & 63) == 63 && tid < 64) start[n_cut - 63 + lane] = mine;
-    const uint32_t lo = key0 + BLOCK_MIN, hi = key0 + 2 * BN;
-    const uint64_t m0 = __builtin_amdgcn_ballot_w64((uint32_t)first0 - lo <= hi - lo), m1 = n > 64 ? __builtin_amdgcn_ballot_w64((uint32_t)first1 - lo <= hi - lo) : 0;
-    key0 = hi;
-    if (m0 != 0) key0 = __builtin_amdgcn_readlane(first0, 63 - __builtin_clzll(m0));
-    if (m1 != 0) key0 = __builtin_amdgcn_readlane(first1, 63 - __builtin_clzll(m1));
-    if ((uint32_t)T <= hi) key0 = T;
-  }
-  if (tid < (n_cut & 63)) start[(n_cut & ~63) + lane] = mine;
+  if (tid <= 128) s_first[tid] = tid < n ? a.node_tok_start[n0 + tid] : T;
+  s_word[tid >> 1][tid & 1] = (tid & 1) < a.W && (tid >> 1) < n ? a.node_vis[(int64_t)(n0 + (tid >> 1)) * a.W + (tid & 1)] : 0;
   __syncthreads();
-  float cost[2] = {0.f, 0.f};  // blocks of 128 keys, blocks cut at borders
-  for (int i0 = 0; i0 < n_even + n_cut; i0 += 64) {  // four threads a block, each with every fourth node
-    const int i = min(i0 + (tid >> 2), n_even + n_cut - 1), part = tid & 3;
-    const bool cut = i >= n_even, count = i0 + (tid >> 2) == i && part == 0;
-    const int x = cut ? i - n_even : i;
-    const int key0 = cut ? start[x] : x * 2 * BN, key1 = !cut ? min(key0 + 2 * BN, T) : x + 1 < n_cut ? start[x + 1] : T;
-    const int u0 = a.tok_node[cu + key0], u1 = a.tok_node[cu + key1 - 1];
+  auto node_of = [&](int key) {
+    int u = 0;
+#pragma unroll
+    for (int step = 64; step > 0; step >>= 1) u += s_first[u + step] <= key ? step : 0;
+    return u;
+  };
+  // the block [key0, key1), by its four lanes, each with a quarter of the nodes: its tiles, and what it costs
+  const int quarter = (n + 3) / 4, part = tid & 3;
+  auto weigh = [&](int key0, int key1, int& tiles) {
+    const int u0 = node_of(key0), u1 = node_of(key1 - 1);
     uint64_t range[2];  // bits u0 .. u1
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
@@ -472,36 +466,69 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
       range[y] = from <= to ? (~0ull >> (63 - to)) & (~0ull << from) : 0ull;
     }
     int rows = 0, sure = 0;  // of the stream, and those of them that see all of the keys
-    for (int u = part; u < n; u += 4) {
-      const uint64_t w0 = s_word[0][u], w1 = a.W > 1 ? s_word[1][u] : 0;
-      const int len = s_first[u + 1] - s_first[u];
-      rows += ((w0 & range[0]) | (w1 & range[1])) != 0 ? len : 0;
-      const bool all = ((~w0 & range[0]) | (~w1 & range[1])) == 0;
-      sure += all ? (u == u1 ? s_first[u + 1] - key1 : len) : 0;
+#pragma unroll 4
+    for (int u = part * quarter; u < min((part + 1) * quarter, n); ++u) {
+      const uint64_t w0 = s_word[u][0], w1 = s_word[u][1];
+      const int first = u == u0 ? key0 : s_first[u], end = s_first[u + 1];
+      const bool any = ((w0 & range[0]) | (w1 & range[1])) != 0, all = ((~w0 & range[0]) | (~w1 & range[1])) == 0;
+      rows += any ? end - first : 0;
+      sure += all ? end - (u == u1 ? key1 : first) : 0;
     }
-    rows = dag_wave_sum<2>(rows) + s_first[u0] - key0;
+    rows = dag_wave_sum<2>(rows);
     sure = dag_wave_sum<2>(sure);
-    const int tiles = (rows + BM - 1) / BM;
-    const float c = a.G * (1.25f * tiles - 0.25f * (sure / BM)) + DKV_BLOCK_STEPS;
-    cost[0] += cut || !count ? 0.f : c;
-    cost[1] += cut && count ? c : 0.f;
-    if (count) (cut ? weight : weight_even)[x] = tiles;
+    tiles = (rows + BM - 1) / BM;
+    return a.G * (1.25f * tiles - 0.25f * (sure / BM)) + DKV_BLOCK_STEPS;
+  };
+  float cost[2] = {0.f, 0.f};  // blocks of 128 keys, blocks cut at borders
+  if (slots <= MAX_CUT_BLOCKS && w == 0) {
+    const int first0 = s_first[lane], first1 = s_first[64 + lane];
+    int n_cut = 0, mine = 0;
+    for (int key0 = 0; key0 < T; ++n_cut) {
+      mine = lane == (n_cut & 63) ? key0 : mine;
+      if ((n_cut & 63) == 63) s_start[n_cut - 63 + lane] = mine;
+      const uint32_t lo = key0 + BLOCK_MIN, hi = key0 + 2 * BN;
+      const uint64_t m0 = __builtin_amdgcn_ballot_w64((uint32_t)first0 - lo <= hi - lo), m1 = n > 64 ? __builtin_amdgcn_ballot_w64((uint32_t)first1 - lo <= hi - lo) : 0;
+      key0 = hi;
+      if (m0 != 0) key0 = __builtin_amdgcn_readlane(first0, 63 - __builtin_clzll(m0));
+      if (m1 != 0) key0 = __builtin_amdgcn_readlane(first1, 63 - __builtin_clzll(m1));
+      if ((uint32_t)T <= hi) key0 = T;
+    }
+    if (lane < (n_cut & 63)) s_start[(n_cut & ~63) + lane] = mine;
+    if (lane == 0) s_start[n_cut] = T, s_blocks = n_cut;
+  } else if (w > 0) {
+    for (int i0 = 0; i0 < n_even; i0 += 48) {
+      const int at = i0 + ((tid - 64) >> 2), i = min(at, n_even - 1);
+      int tiles;
+      const float c = weigh(i * 2 * BN, min((i + 1) * 2 * BN, T), tiles);
+      if (at == i && part == 0) {
+        cost[0] += c;
+        weight[i] = tiles;
+      }
+    }
+  }
+  __syncthreads();
+  bool even = slots > MAX_CUT_BLOCKS;  // (a sequence that has more blocks keeps them)
+  const int n_cut = even ? 0 : s_blocks;
+  for (int i0 = 0; i0 < n_cut; i0 += 64) {
+    const int at = i0 + (tid >> 2), i = min(at, n_cut - 1);
+    int tiles;
+    const float c = weigh(s_start[i], s_start[i + 1], tiles);
+    if (at == i && part == 0) {
+      cost[1] += c;
+      s_weight[i] = tiles;
+    }
   }
 #pragma unroll
   for (int y = 0; y < 2; ++y) {
     const float c = dag_wave_sum(cost[y]);
-    if (lane == 0) s_cost[y][tid >> 6] = c;
+    if (lane == 0) s_cost[y][w] = c;
   }
   __syncthreads();
-  const bool even = s_cost[0][0] + s_cost[0][1] + s_cost[0][2] + s_cost[0][3] < 1.03f * (s_cost[1][0] + s_cost[1][1] + s_cost[1][2] + s_cost[1][3]);
-  for (int x = tid; x < slots; x += 256) {  // (behind the barrier: weight_even is another thread's)
-    if (even) {
-      start[x] = x < n_even ? x * 2 * BN : T;
-      weight[x] = x < n_even ? weight_even[x] : -1;
-    } else if (x >= n_cut) {
-      start[x] = T;
-      weight[x] = -1;
-    }
+  if (!even) even = s_cost[0][0] + s_cost[0][1] + s_cost[0][2] + s_cost[0][3] < 1.03f * (s_cost[1][0] + s_cost[1][1] + s_cost[1][2] + s_cost[1][3]);
+  for (int x = tid; x < slots; x += 256) {  // (behind the barrier: the weights of the blocks of 128 are other threads')
+    const bool block = x < (even ? n_even : n_cut);
+    start[x] = !block ? T : even ? x * 2 * BN : s_start[x];
+    if (!block || !even) weight[x] = block ? s_weight[x] : -1;
   }
 }
 // The keys [x, y) of the workgroup of key tile kt (the ktl-th of its sequence).
@@ -2907,7 +2934,7 @@ extern "C" int dag_attn_prefill_bwd(const dag_meta_t* m, const void* q, const vo
     a.runs = p.node_runs;
     a.tok_depth = p.tok_depth;
     // Blocks cut at node borders are more than the pairs that the piece list has room for, so it lies behind their first keys in the
-    // place of the words that dQ does not read on chunks (eight bytes a token).  Below 4096 tokens the 2 us of cut_keys
+    // place of the words that dQ does not read on chunks (eight bytes a token).  Below 4096 tokens the 2 to 4 us of cut_keys
     // are more than forks give back (68 and 118 us: 0.98), and with one head a group a workgroup has as few
     // iterations as it costs (2 x 52 and 5 x 97 random nodes, 2 / 2 heads of dimension 128: 0.96 and 0.98).
     const int64_t blocks = bwd_cut_blocks(p.total_tokens, p.total_nodes, a.total_ktiles, a.n_seqs);

@@ -8,6 +8,7 @@ from oracle import dag_oracle as orc
 from paper_2602_07529_amd import binding as B
 from workloads import dags
 from tests.gpu_util import DEV, build_meta
+from tests.test_gpu_bwd_pieces import _without_pieces
 from tests.test_gpu_prefill_bwd import _check_against_oracle, _forward_backward, check_close
 
 pytestmark = pytest.mark.gpu
@@ -108,3 +109,29 @@ def test_hidden_keys_behind_a_short_block(hq, hkv, d):
         check_close(dk[sl], ref[1][sl], torch.bfloat16, "dk")
         check_close(dv[sl], ref[2][sl], torch.bfloat16, "dv")
     assert not torch.isfinite(dv[:300].float()).all(dim=-1).any()
+
+
+def test_a_sequence_of_more_blocks_than_there_is_room_for():
+    """Over 1024 key tiles: the sequence keeps blocks of 128, beside one that is cut.  Against the call without room for pieces, which has
+    no blocks."""
+    hq, hkv, d = 2, 1, 64
+    long, short = dags.fork_join(40, [600] * 110, 30), dags.fork_join(700, [128, 64, 129, 127, 1] * 2, 63)
+    keys, cut = _blocks(*short, hq // hkv)
+    T = [int(np.sum(L)) for L, _ in (long, short)]
+    assert T[0] > 1024 * 64 and cut
+    q, k, v, dout = (x.to(DEV) for x in (*dags.make_qkv(8400, sum(T), hq, hkv, d, 0.7, torch.bfloat16), dags.make_qkv(8401, sum(T), hq, hkv, d, 1.0, torch.bfloat16)[0]))
+    _, meta = build_meta([long, short], hq, hkv, d, torch.bfloat16)
+    out, lse = torch.empty_like(q), torch.empty(sum(T), hq, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, q, k, v, out, lse)
+    grads = []
+    for size in (_without_pieces(meta, hq, hkv, d), B.dag_prefill_bwd_workspace_bytes(meta, hq, hkv, d)):
+        ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+        grads.append((torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)))
+        B.dag_attn_prefill_bwd(meta, q, k, v, out, dout, lse, *grads[-1], workspace=ws)
+    first = _key_tables(meta, ws, hq)[1].tolist()
+    slots = [-(-t // 64) for t in T]
+    even = list(range(0, T[0], 128))
+    assert first[:slots[0]] == even + [T[0]] * (slots[0] - len(even))
+    assert first[slots[0]:] == keys + [T[1]] * (slots[1] - len(keys))
+    for a, b in zip(*grads):   # (fp32 sums in another order, half a unit of bf16 each: 2^-9)
+        assert torch.isfinite(b.float()).all() and float((a.double() - b.double()).norm()) <= 4e-3 * float(a.double().norm())
