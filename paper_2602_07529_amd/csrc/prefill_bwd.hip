@@ -455,12 +455,9 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
     for (int step = 64; step > 0; step >>= 1) u += s_first[u + step] <= key ? step : 0;
     return u;
   };
-  // the block [key0, key1), by its four lanes, each with a quarter of the nodes: its tiles, those of the sequence (64 rows from a multiple of 64
-  // on) that a row of its stream lies in, and what it costs.  Blocks of 128 weigh the tiles of the sequence, as without cuts: by those of
-  // their streams, a few per cent fewer, the even share of bwd_order is smaller and the pieces are more than go at once (forks of
-  // 4304 and 4 x 5927 tokens, 8 / 4 heads of dimension 64, 532 workgroups for 504 and 1024 for 1012: 181 -> 192 and 691 -> 727 us).
+  // the block [key0, key1), by its four lanes, each with a quarter of the nodes: its tiles, and what it costs
   const int quarter = (n + 3) / 4, part = tid & 3;
-  auto weigh = [&](int key0, int key1, int& tiles, int& tiles_seq) {
+  auto weigh = [&](int key0, int key1, int& tiles) {
     const int u0 = node_of(key0), u1 = node_of(key1 - 1);
     uint64_t range[2];  // bits u0 .. u1
 #pragma unroll
@@ -469,7 +466,6 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
       range[y] = from <= to ? (~0ull >> (63 - to)) & (~0ull << from) : 0ull;
     }
     int rows = 0, sure = 0;  // of the stream, and those of them that see all of the keys
-    int n_seq = 0, first_seq = INT32_MAX, last_seq = -1;
 #pragma unroll 4
     for (int u = part * quarter; u < min((part + 1) * quarter, n); ++u) {
       const uint64_t w0 = s_word[u][0], w1 = s_word[u][1];
@@ -477,21 +473,10 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
       const bool any = ((w0 & range[0]) | (w1 & range[1])) != 0, all = ((~w0 & range[0]) | (~w1 & range[1])) == 0;
       rows += any ? end - first : 0;
       sure += all ? end - (u == u1 ? key1 : first) : 0;
-      n_seq += any ? (end - 1) / BM - max(first / BM, last_seq + 1) + 1 : 0;
-      first_seq = any ? min(first_seq, first / BM) : first_seq;
-      last_seq = any ? (end - 1) / BM : last_seq;
     }
-    int in_front = -1;  // the last tile of the lanes in front, which may be this lane's first, too
-#pragma unroll
-    for (int x = 1; x < 4; ++x) {
-      const int y = __shfl_up(last_seq, x);
-      in_front = x <= part ? max(in_front, y) : in_front;
-    }
-    n_seq -= in_front == first_seq;
     rows = dag_wave_sum<2>(rows);
     sure = dag_wave_sum<2>(sure);
     tiles = (rows + BM - 1) / BM;
-    tiles_seq = dag_wave_sum<2>(n_seq);
     return a.G * (1.25f * tiles - 0.25f * (sure / BM)) + DKV_BLOCK_STEPS;
   };
   float cost[2] = {0.f, 0.f};  // blocks of 128 keys, blocks cut at borders
@@ -513,11 +498,11 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
   } else if (w > 0) {
     for (int i0 = 0; i0 < n_even; i0 += 48) {
       const int at = i0 + ((tid - 64) >> 2), i = min(at, n_even - 1);
-      int tiles, tiles_seq;
-      const float c = weigh(i * 2 * BN, min((i + 1) * 2 * BN, T), tiles, tiles_seq);
+      int tiles;
+      const float c = weigh(i * 2 * BN, min((i + 1) * 2 * BN, T), tiles);
       if (at == i && part == 0) {
         cost[0] += c;
-        weight[i] = tiles_seq;
+        weight[i] = tiles;
       }
     }
   }
@@ -526,8 +511,8 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
   const int n_cut = even ? 0 : s_blocks;
   for (int i0 = 0; i0 < n_cut; i0 += 64) {
     const int at = i0 + (tid >> 2), i = min(at, n_cut - 1);
-    int tiles, tiles_seq;
-    const float c = weigh(s_start[i], s_start[i + 1], tiles, tiles_seq);
+    int tiles;
+    const float c = weigh(s_start[i], s_start[i + 1], tiles);
     if (at == i && part == 0) {
       cost[1] += c;
       s_weight[i] = tiles;

@@ -27,8 +27,8 @@ def _dags(name):
 
 
 def _blocks(L, anc, g):
-    """The rule of cut_keys: (first keys of the blocks, whether they are cut at borders, their weights).  They are cut where their streams
-    cost 3 % less than those of blocks of 128 keys.  A cut block weighs the tiles of its stream, one of 128 those of the sequence with a row of it."""
+    """The rule of cut_keys: (first keys of the blocks, whether they are cut at borders), which they are where their streams cost 3 % less
+    than those of blocks of 128 keys."""
     L = [int(x) for x in L]
     n, starts = len(L), [int(x) for x in np.cumsum([0] + L)]
     T = starts[-1]
@@ -36,7 +36,7 @@ def _blocks(L, anc, g):
     for v in range(n):
         sees[v, [u for u in range(n) if int(anc[v][u >> 6]) >> (u & 63) & 1]] = sees[v, v] = True
     node = np.repeat(np.arange(n), L)
-    costs, keys, weights = [], [[], []], [[], []]
+    costs, keys = [], [[], []]
     for cut in (False, True):
         key0, cost = 0, 0.0
         while key0 < T:
@@ -46,14 +46,11 @@ def _blocks(L, anc, g):
             u0, u1 = node[key0], node[key1 - 1]
             rows = starts[u0] - key0 + sum(L[v] for v in range(n) if sees[v, u0:u1 + 1].any())
             sure = sum(starts[u1 + 1] - key1 if v == u1 else L[v] for v in range(n) if sees[v, u0:u1 + 1].all())
-            stream = np.concatenate([np.arange(max(key0, starts[v]), starts[v + 1]) for v in range(n) if sees[v, u0:u1 + 1].any()])
-            assert len(stream) == rows
-            weights[cut].append(-(-rows // 64) if cut else len(np.unique(stream // 64)))
             cost += g * (1.25 * (-(-rows // 64)) - 0.25 * (sure // 64)) + 8
             key0 = key1
         costs.append(cost)
     cut = not costs[0] < 1.03 * costs[1]
-    return keys[cut], cut, weights[cut]
+    return keys[cut], cut
 
 
 def _is_cut(L, anc, g):
@@ -75,19 +72,17 @@ def test_dkv_blocks(name, cut, hq, hkv, d, monkeypatch):
     dag_list = _dags(name)
     assert sum(int(np.sum(L)) for L, _ in dag_list) >= 4096
     blocks = [_blocks(L, anc, hq // hkv) for L, anc in dag_list]
-    assert [c for _, c, _ in blocks] == cut
+    assert [c for _, c in blocks] == cut
     _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
     ws = torch.zeros(B.dag_prefill_bwd_workspace_bytes(meta, hq, hkv, d), dtype=torch.uint8, device=DEV)
     call = B.dag_attn_prefill_bwd
     monkeypatch.setattr(B, "dag_attn_prefill_bwd", lambda *args, **kw: call(*args, workspace=ws, **kw))
     inputs, grads = _forward_backward(dag_list, hq, hkv, d, 8200 + hq)
-    weight, first = (x.tolist() for x in _key_tables(meta, ws, hq))
-    for (L, _), (keys, _, weights) in zip(dag_list, blocks):   # (slots without a block hold the end of the sequence)
+    first = _key_tables(meta, ws, hq)[1]
+    for (L, _), (keys, _) in zip(dag_list, blocks):   # (slots without a block hold the end of the sequence)
         T = int(np.sum(L))
-        slots = -(-T // 64)
-        assert first[:slots] == keys + [T] * (slots - len(keys))
-        assert weight[:slots] == weights + [-1] * (slots - len(keys))
-        weight, first = weight[slots:], first[slots:]
+        slots, first = first[:-(-T // 64)], first[-(-T // 64):]
+        assert slots.tolist() == keys + [T] * (len(slots) - len(keys))
     _check_against_oracle(dag_list, inputs, grads)
 
 
@@ -121,7 +116,7 @@ def test_a_sequence_of_more_blocks_than_there_is_room_for():
     no blocks."""
     hq, hkv, d = 2, 1, 64
     long, short = dags.fork_join(40, [600] * 110, 30), dags.fork_join(700, [128, 64, 129, 127, 1] * 2, 63)
-    keys, cut, _ = _blocks(*short, hq // hkv)
+    keys, cut = _blocks(*short, hq // hkv)
     T = [int(np.sum(L)) for L, _ in (long, short)]
     assert T[0] > 1024 * 64 and cut
     q, k, v, dout = (x.to(DEV) for x in (*dags.make_qkv(8400, sum(T), hq, hkv, d, 0.7, torch.bfloat16), dags.make_qkv(8401, sum(T), hq, hkv, d, 1.0, torch.bfloat16)[0]))
