@@ -92,7 +92,7 @@ struct BwdArgs {
   int max_split;  // room for this many pieces of split pairs (a KV head)
   int32_t* block_start;  // [total key tiles] first keys of a sequence's blocks (see cut_keys; T: no block); null: blocks are pairs of key tiles
   bool again;     // k_dkv_finish may read the inputs once more
-  int dq_pieces;  // dQ on chunks: workgroups that may share a chunk, set per launch (see dq_cuts)
+  int dq_pieces, dq_piece;  // dQ on chunks: workgroups that may share a chunk, and tiles that each has at least, set per launch (see dq_cuts)
 };
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -2073,8 +2073,8 @@ struct Dq {
 // `pieces` workgroups of at least DQ_PIECE tiles, whose sums k_dq_sum adds up (2214 tokens of one head 70 -> 33 + 5 us, 3515 tokens, 8 / 2 heads: 106 -> 42 + 5).
 // Forward and backward of 40 batches of up to 9000 tokens: of at least 3, 4, 9, 12 tiles 1.00, 1.01, 0.99, 0.99 times as fast (0.97,
 // 0.99, 0.88, 0.77 at worst), at most 8 or 32 workgroups 1.00.
-constexpr int DQ_PIECE = 6, DQ_MAX_PIECES = 16;
-__device__ __forceinline__ int dq_cuts(int tiles, int pieces) { return max(min(pieces, tiles / DQ_PIECE), 1); }
+constexpr int DQ_PIECE = 6, DQ_LONG_PIECE = 16, DQ_MAX_PIECES = 16;
+__device__ __forceinline__ int dq_cuts(int tiles, int pieces, int piece) { return max(min(pieces, tiles / piece), 1); }
 template <int D, bool WIDE, bool NODES, bool PIECES = false>
 __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
   using C = Dq<D>;
@@ -2097,7 +2097,7 @@ __device__ __forceinline__ void dq_ring_body(const BwdArgs& a) {
     if (chunk >= *a.chunk.count) return;  // (the launch is sized by a bound)
     const int32_t* d = a.chunk.desc + (size_t)chunk * 8;
     t.cu = d[0], t.T = d[1], t.row0 = d[2], t.c0 = d[3], t.N = d[4], t.nfast = d[5], t.nbase = d[6];
-    if constexpr (PIECES) cuts = dq_cuts(t.N, a.dq_pieces);
+    if constexpr (PIECES) cuts = dq_cuts(t.N, a.dq_pieces, a.dq_piece);
     if (cut >= cuts) return;
     tile0 = cut * (t.N / cuts) + min(cut, t.N % cuts);
     tile1 = tile0 + t.N / cuts + (cut < t.N % cuts);
@@ -2436,7 +2436,7 @@ __global__ void __launch_bounds__(256) k_dq_sum(BwdArgs a, int nz) {
   const int lane = threadIdx.x & 63, L = lane & 31, H = lane >> 5;
   if (chunk >= *a.chunk.count) return;
   const int32_t* const d = a.chunk.desc + (size_t)chunk * 8;
-  const int n = dq_cuts(d[4], a.dq_pieces), rows = min(a.pack_rows, d[1] - d[2]);
+  const int n = dq_cuts(d[4], a.dq_pieces, a.dq_piece), rows = min(a.pack_rows, d[1] - d[2]);
   if (n < 2 || dq_pair(32 * w, a.pack_heads).x >= rows) return;
   const size_t step = (size_t)a.hkv * nz * NW * (D / 4 * 32);
   const f32x4* const from = a.part + (size_t)chunk * a.dq_pieces * step + (((size_t)hk * nz + z) * NW + w) * (D / 4 * 32) + 2 * part * 64 + lane;
@@ -2525,9 +2525,14 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, long total_qtiles, lon
     const int64_t items = a.slots * a.hkv * nz;
     // (pieces for twice the workgroups that the device holds: about half of the slots have a chunk; sequences of less than 16
     // tiles on average would pay for the launch behind them, 4.5 us, and have next to nothing to share)
-    // (where the chunks alone nearly fill it there is nothing to gain: 6 x 38 nodes, 4 / 1 heads of dimension 64: 84 us in two pieces, 76 without)
+    // (Where the chunks alone nearly fill it there is nothing to gain but in chunks that are much longer than the others, as the join of a
+    // fork: long sequences of few nodes, and of those the chunks of two DQ_LONG_PIECE.  Forks of 53 to 118 tiles, whole : in pieces
+    // 1.03 to 1.26 (a fork of 28 nodes, 7376 tokens, 6 / 2 heads of dimension 128: 507 -> 409 us), of 49 to 51 tiles 0.92 to 0.99; random
+    // nodes of 60 to 220 tokens 0.91 to 1.00, 6 x 38 nodes, 4 / 1 heads of dimension 64 76 : 84 us.)
     const int64_t chunks = nodes ? (p.total_tokens / a.pack_rows + p.total_nodes / 2) * a.hkv * nz : 0;
-    if (nodes && a.pieces && total_qtiles >= 16 * a.n_seqs && 4 * chunks < 3 * (D == 128 ? 256 : 512)) {
+    const bool filled = 4 * chunks >= 3 * (D == 128 ? 256 : 512);
+    a.dq_piece = filled ? DQ_LONG_PIECE : DQ_PIECE;
+    if (nodes && a.pieces && total_qtiles >= (filled ? 52 : 16) * a.n_seqs && (!filled || p.total_tokens >= 256 * p.total_nodes)) {
       const int64_t fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
       a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES));
     }

@@ -2,8 +2,11 @@
 that belong to no row or no head, waves without rows, items of more than eight heads, tiles shared out over several workgroups."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2602_07529_amd import binding as B
 from workloads import dags
+from tests.gpu_util import DEV, build_meta, launched_kernels
 from tests.test_gpu_prefill_bwd import _check_against_oracle, _forward_backward
 
 pytestmark = pytest.mark.gpu
@@ -27,4 +30,30 @@ def test_every_group(name, g, d):
     hkv = 2 if name == "batch" and g < 9 else 1
     dag_list = _dags(name)
     inputs, grads = _forward_backward(dag_list, g * hkv, hkv, d, 8500 + g + d)
+    _check_against_oracle(dag_list, inputs, grads)
+
+
+# chunks that nearly fill the device: in pieces only where some may be much longer than the others, and then the long ones
+@pytest.mark.parametrize("name,pieces", [("long fork", True), ("short fork", False), ("random", False)])
+@pytest.mark.parametrize("hq,hkv,d,rows", [(7, 1, 128, 36), (8, 4, 64, 64)])
+def test_pieces_of_chunks_that_fill_the_device(name, pieces, hq, hkv, d, rows):
+    rng = np.random.Generator(np.random.PCG64(8600))
+    n = {128: 7400, 64: 6200}[d]   # tokens that make about 0.8 of the chunks that go at once
+    dag_list = {"long fork": [dags.fork_join(n // 8, [n // 10] * 8, n - n // 8 - n // 10 * 8)],
+                "short fork": [dags.fork_join(700, [200] * 3, n // 4 - 1300)] * 4,
+                "random": [dags.random_dag(rng, n_nodes=30, depth=5, len_lo=n // 62, len_hi=n // 21)[:2]]}[name]
+    T, nodes = sum(int(np.sum(L)) for L, _ in dag_list), sum(len(L) for L, _ in dag_list)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    full = units * (1 if d == 128 else 2)
+    assert 4 * (T // rows + nodes // 2) * hkv >= 3 * full and (T // rows + nodes) * hkv <= full
+    assert pieces == (sum(-(-int(np.sum(L)) // 64) for L, _ in dag_list) >= 52 * len(dag_list) and T >= 256 * nodes)
+    inputs, grads = _forward_backward(dag_list, hq, hkv, d, 8700)
+    _, meta = build_meta(dag_list, hq, hkv, d, torch.bfloat16)
+    q, k, v, dout = (x.to(DEV) for x in inputs)
+    out, lse = torch.empty_like(q), torch.empty(T, hq, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, q, k, v, out, lse)
+    ws = torch.empty(B.dag_prefill_bwd_workspace_bytes(meta, hq, hkv, d), dtype=torch.uint8, device=DEV)
+    names = launched_kernels(lambda: B.dag_attn_prefill_bwd(meta, q, k, v, out, dout, lse, *grads, workspace=ws))
+    assert sum("k_dq_sum" in x for x in names) == pieces, names
+    assert any(("k_nodes_dq2ILb%d" if d == 128 else "k_nodes64_dqILb%d") % pieces in x for x in names), names
     _check_against_oracle(dag_list, inputs, grads)
