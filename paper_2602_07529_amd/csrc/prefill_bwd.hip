@@ -430,8 +430,8 @@ __device__ __forceinline__ void bwd_weight(const BwdArgs& a, int kt, int lane) {
 // random ones with long nodes 1.03 to 1.13 (0.984 at worst).
 // (A workgroup a sequence.  The blocks follow one from the other, 80 clocks each: the first wave finds them while the others weigh the blocks
 // of 128, and then all weigh those.  Four lanes a block, the nodes and the first keys in LDS.  With all waves finding the blocks first, and
-// their keys and nodes read from memory, the launch in front of dQ took 24.0 instead of 16.7 us for one sequence of 67 nodes, 10,700
-// tokens, 12.9 instead of 10.9 for a fork of 18, 6600 tokens; without cuts 9.4 and 7.4.  Blocks weighed by whole waves, a node a
+// their keys and nodes read from memory, the launch in front of dQ took 24.0 instead of 19.2 us for one sequence of 67 nodes, 9800
+// tokens, 12.9 instead of 11.8 for a fork of 18, 6600 tokens; without cuts 9.4 and 7.4.  Blocks weighed by whole waves, a node a
 // lane, took 5 to 28 us.)
 constexpr int BLOCK_MIN = 64, DKV_BLOCK_STEPS = 8, MAX_CUT_BLOCKS = 1024;
 __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
@@ -466,7 +466,7 @@ __device__ __forceinline__ void cut_keys(const BwdArgs& a, int b) {
       range[y] = from <= to ? (~0ull >> (63 - to)) & (~0ull << from) : 0ull;
     }
     int rows = 0, sure = 0;  // of the stream, and those of them that see all of the keys
-#pragma unroll 4
+#pragma unroll 3  // (62 registers; four times 97, 16.7 us, and the rows of delta in this launch run at half the occupancy: 1147 -> 1172 us in all for 34,000 tokens of 16 heads)
     for (int u = part * quarter; u < min((part + 1) * quarter, n); ++u) {
       const uint64_t w0 = s_word[u][0], w1 = s_word[u][1];
       const int first = u == u0 ? key0 : s_first[u], end = s_first[u + 1];
