@@ -2831,9 +2831,13 @@ static bool bwd_dq_on_chunks(const dag_meta_t* m, const BwdArgs& a, int32_t head
       !apart(a.k, dk_bytes) || !apart(a.v, dk_bytes) || !apart(a.lse, (size_t)a.total_rows * 4))
     return false;
   // Forward and backward, block map : chunks (of 256 rows of one head to 32 of eight), 64 random nodes of 17 / 24 / 36 / 55 tokens on
-  // average, dimension 128: 16 / 8 heads 1.09 / 1.15 / 1.21 / 1.29 (four times, once 1.12 to 1.24), 8 / 8 heads 0.96 / 1.00 /
-  // 1.07 / 1.15 (once 1.11 to 1.33), 40 / 8 heads - / 1.23 / 1.28 / 1.37; 32 / 8 heads before the heads were
+  // average, dimension 128: 16 / 8 heads 1.09 / 1.15 / 1.21 / 1.29 (four times, once 1.12 to 1.24), 40 / 8 heads - / 1.23 / 1.28 / 1.37;
+  // 80 batches of 2, 3, 5, 6 and 7 heads, nodes of 16 to 62 tokens 0.99 and more; 32 / 8 heads before the heads were
   // packed 1.06 / 1.05 / 1.06 from 24 tokens on, 16 / 8 heads of dimension 64 1.09 / 1.05 / 1.10.
+  // One head of dimension 128 fills 256 rows with a node of 16 to 32 tokens: where such items are ten and more for a compute unit and their
+  // streams short, chunks cost more than tiles (random nodes of 16 to 30 tokens, sequences of 300 to 1000, 8 to 32 heads 0.86 to
+  // 0.96, forks 1.00 to 1.11).  Fewer items 0.92 to 1.56, longer streams 0.92 to 1.11, longer nodes 0.94 to 1.33 (120 batches).
+  if (head_dim == 128 && a.G == 1 && T < 32 * n && T < 1000 * (int64_t)a.n_seqs && n * a.hkv >= 2560) return false;
   return T >= 16 * n;
 }
 

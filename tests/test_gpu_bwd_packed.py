@@ -57,3 +57,22 @@ def test_pieces_of_chunks_that_fill_the_device(name, pieces, hq, hkv, d, rows):
     assert sum("k_dq_sum" in x for x in names) == pieces, names
     assert any(("k_nodes_dq2ILb%d" if d == 128 else "k_nodes64_dqILb%d") % pieces in x for x in names), names
     _check_against_oracle(dag_list, inputs, grads)
+
+
+# one head a group on nodes of 16 to 32 tokens: query chunks where the items are few, or the sequences long; else the block map's tiles
+@pytest.mark.parametrize("n_seqs,n_nodes,avg,hkv,chunks", [(11, 30, 22, 8, False), (4, 30, 22, 8, True), (6, 60, 22, 8, True), (11, 30, 36, 8, True), (11, 30, 22, 7, True)])
+def test_single_heads_on_short_nodes(n_seqs, n_nodes, avg, hkv, chunks):
+    d = 128
+    rng = np.random.Generator(np.random.PCG64(8800))
+    dag_list = [dags.random_dag(rng, n_nodes=n_nodes, depth=4, len_lo=avg - 9, len_hi=avg + 9)[:2] for _ in range(n_seqs)]
+    T, nodes = sum(int(np.sum(L)) for L, _ in dag_list), n_seqs * n_nodes
+    assert T >= 16 * nodes and chunks == (T >= 32 * nodes or T >= 1000 * n_seqs or nodes * hkv < 2560)
+    inputs, grads = _forward_backward(dag_list, hkv, hkv, d, 8900)
+    _, meta = build_meta(dag_list, hkv, hkv, d, torch.bfloat16)
+    q, k, v, dout = (x.to(DEV) for x in inputs)
+    out, lse = torch.empty_like(q), torch.empty(T, hkv, dtype=torch.float32, device=DEV)
+    B.dag_attn_prefill(meta, q, k, v, out, lse)
+    ws = torch.empty(B.dag_prefill_bwd_workspace_bytes(meta, hkv, hkv, d), dtype=torch.uint8, device=DEV)
+    names = launched_kernels(lambda: B.dag_attn_prefill_bwd(meta, q, k, v, out, dout, lse, *grads, workspace=ws))
+    assert any(("k_nodes_dq2" if chunks else "k_bwd_dq2") in x for x in names), names
+    _check_against_oracle(dag_list, inputs, grads)
