@@ -2530,11 +2530,13 @@ int launch_bwd(const BwdArgs& args, const PrefillArgs& p, long total_qtiles, lon
     // 1.03 to 1.26 (a fork of 28 nodes, 7376 tokens, 6 / 2 heads of dimension 128: 507 -> 409 us), of 49 to 51 tiles 0.92 to 0.99; random
     // nodes of 60 to 220 tokens 0.91 to 1.00, 6 x 38 nodes, 4 / 1 heads of dimension 64 76 : 84 us.)
     const int64_t chunks = nodes ? (p.total_tokens / a.pack_rows + p.total_nodes / 2) * a.hkv * nz : 0;
-    const bool filled = 4 * chunks >= 3 * (D == 128 ? 256 : 512);
+    const int64_t at_once = (int64_t)dag_compute_units() * (D == 128 ? 1 : 2);  // workgroups that run together
+    if (at_once < 1) return DAG_ERR_HIP;
+    const bool filled = 4 * chunks >= 3 * at_once;
     a.dq_piece = filled ? DQ_LONG_PIECE : DQ_PIECE;
     if (nodes && a.pieces && total_qtiles >= (filled ? 52 : 16) * a.n_seqs && (!filled || p.total_tokens >= 256 * p.total_nodes)) {
       const int64_t fits = (int64_t)a.max_split * a.hkv * (D == 128 ? 1 : 2);
-      a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((D == 128 ? 512 : 1024) / items, fits / items), DQ_MAX_PIECES));
+      a.dq_pieces = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(2 * at_once / items, fits / items), DQ_MAX_PIECES));
     }
     auto* const on_chunks = D == 128 ? (a.dq_pieces > 1 ? k_nodes_dq2<true> : k_nodes_dq2<false>) : a.dq_pieces > 1 ? k_nodes64_dq<true> : k_nodes64_dq<false>;
     auto* const one_tile = nodes ? on_chunks : D == 128 ? k_bwd_dq2<false> : k_bwd64_dq<false>;
