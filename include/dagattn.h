@@ -172,7 +172,9 @@ int dag_attn_prefill(const dag_meta_t* meta, const void* q, const void* k, const
  * lists or a key-tile-wise transposed copy of v [T][hkv][head_dim] -- (a no-op for
  * DAG_F32); dag_attn_prefill_prepared is dag_attn_prefill without that
  * step: it expects `ws` as dag_prefill_prepare_v left it for the same meta, v, hkv, head_dim and
- * dtype and an hq with the same remainder of hq / hkv modulo 4, and v as it was then.
+ * dtype and an hq with the same remainder of hq / hkv modulo 4, and v as it was then.  (Groups of other
+ * than one, two and four heads have a work list of their own, which the call looks at, and builds again in
+ * `ws` where it is that of another hq.)
  * Arguments, layouts, errors and the workspace size are those of dag_attn_prefill.
  * The workspace also holds the attention kernel's work-distribution counters: dag_prefill_prepare_v
  * zeroes them and every attention launch leaves them zeroed, so a workspace must go through
@@ -200,10 +202,10 @@ size_t dag_prefill_workspace_bytes(const dag_meta_t* meta, int32_t hkv, int32_t 
  * accumulation; gradients bf16) or DAG_F32 (plain fp32 arithmetic, the accuracy path; gradients
  * fp32), head_dim 128 or 64; all tensors DEVICE, 16-byte aligned; `ws` DEVICE scratch of
  * dag_prefill_bwd_workspace_bytes (less is taken where it only leaves out room for sums of pieces, about 67 MB
- * and unused in DAG_F32: the rows that see 128 keys, and the keys that a chunk sees, are then one workgroup's, and
- * the sums of dq, dk and dv are those of one piece).  `meta` is the one dag_build_meta filled for the forward.  In
+ * and unused in DAG_F32: the rows that see a block of up to 128 keys, and the keys that a chunk sees, are then one
+ * workgroup's, and the sums of dq, dk and dv are those of one piece).  `meta` is the one dag_build_meta filled for the forward.  In
  * bf16 dQ works on the forward's chunks or on the block map's tiles (launch order, tile descriptors,
- * FULL-first CSR), dK / dV on the rows that see 128 keys or on the block map's columns, by rules of
+ * FULL-first CSR), dK / dV on the rows that see a block of up to 128 keys or on the block map's columns, by rules of
  * their own on node lengths and sizes.  `dk` is scratch during the call (the work lists of the chunks
  * are built there before it is written), except where it overlaps an input or dq: dq then takes the
  * block map's tiles, so that dk and dv may lie on the memory of k and v.

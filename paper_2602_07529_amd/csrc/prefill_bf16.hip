@@ -1941,11 +1941,14 @@ HeadSplit split_heads(int g) { return {g - g % 4, g % 4}; }
 
 // Whether the query rows are cut at the borders of the nodes (k_node_rows) instead of every 64 tokens.
 // Short nodes leave most of a chunk's rows empty, and the more so the more rows a chunk has (256 for
-// the single left-over head of an odd group at head dimension 128): measured on random DAGs of 64
+// one head a group at head dimension 128): measured on random DAGs of 64
 // nodes, time on the block map's tiles : on chunks, for an average node of 8 / 16 / 32 / 48 / 144 tokens
-// (256 for chains of long nodes): 32 / 8 heads 0.80 / 1.10 / 1.40 / 1.66 / 1.35 / 1.21; 40 / 8 heads
-// 0.68 / 0.95 / 1.28 / 1.45 / 1.37 / 1.24; 8 / 8 heads 0.61 / 0.85 / 1.11 / 1.18 / 1.58 / 1.27; 16 / 8
-// heads of dimension 64: 1.17 / 1.72 / 2.15 / 2.65 / 2.30 / 1.89; long fork-joins 1.0 to 1.4.
+// (256 for chains of long nodes): 32 / 8 heads 0.80 / 1.10 / 1.40 / 1.66 / 1.35 / 1.21; 8 / 8 heads 0.61 / 0.85 / 1.11 /
+// 1.18 / 1.58 / 1.27; 16 / 8 heads of dimension 64: 1.17 / 1.72 / 2.15 / 2.65 / 2.30 / 1.89; long fork-joins 1.0 to 1.4.
+// The line of one head is that of all odd groups, because a workspace prepared for one head of a KV head is taken for five and
+// nine (the same remainder modulo 4), which then have to take the same route.  Nodes of 17 / 20 / 24 / 28 / 31 tokens, 12 x 80: 8 / 8 heads
+// 0.94 / 1.10 / 1.13 / 1.13 / 1.13; 24 / 8, 40 / 8 and 56 / 8 heads, 85 to 36 rows a chunk, would gain on chunks from 16 tokens on, too
+// (1.44 to 1.82, 1.61 to 1.77, 1.79 to 2.06).
 bool on_chunks(const PrefillArgs& a, int head_dim) {
   if (!a.node_runs || a.total_tokens * a.hkv * (2 * head_dim) > UINT32_MAX) return false;  // (row offsets are 32-bit)
   const int shortest = head_dim == 128 && a.hq / a.hkv % 2 == 1 ? 32 : 16;
@@ -1953,7 +1956,7 @@ bool on_chunks(const PrefillArgs& a, int head_dim) {
 }
 
 // Batches too small to give every compute unit an item of four heads take one or two heads to an item, all of
-// them in one launch (0: not such a batch, split_heads).  40 / 8 heads, 260 / 360 tokens: 49.5 / 56.7 ->
+// them in one launch (0: not such a batch).  40 / 8 heads, 260 / 360 tokens: 49.5 / 56.7 ->
 // 33.2 / 36.6 us with meta and RoPE, 32 / 8 heads, 650 tokens: 43.3 -> 41.9 us, 4 / 2 heads, 2450 tokens:
 // 82.7 -> 79.2 us.  One or two heads of dimension 64 per KV head stay with their items (4 / 2 heads: 60
 // against 68 us).

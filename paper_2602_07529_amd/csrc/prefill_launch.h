@@ -9,7 +9,7 @@ constexpr int DAG_SCHED_INTS = 128;  // [0..63] item counters, [64] finished wor
 // t / rows + v on.
 constexpr int DAG_CHUNK_SIZES = 3;
 constexpr int DAG_CHUNK_ROWS[DAG_CHUNK_SIZES] = {64, 128, 256};  // (each twice the one in front)
-// A fourth size belongs to the head counts that pack all heads of a group into an item (pack_of): as many rows as 32 NW
+// A fourth size belongs to the head counts that pack all heads of a group into an item (pack_heads_of): as many rows as 32 NW
 // (row, head) pairs have, at least PACK_MIN_ROWS.
 constexpr int DAG_CHUNK_PACK = DAG_CHUNK_SIZES, PACK_MIN_ROWS = 16;
 struct ChunkTables {
@@ -93,8 +93,10 @@ constexpr int PACK_WAVES(int head_dim) { return head_dim == 128 ? 8 : 4; }  // o
 // are row-major, every lane of a wave with a row and a head of its own, all on the same K / V tiles.  More than eight heads are
 // divided evenly.  Five heads were an item of four on 64 rows and, in a launch behind it, one on 256, which random DAGs leave
 // half empty: 60 nodes, 40 / 8 heads 154 -> 113 us, 5 x 53 nodes 704 -> 634, a fork-join of 17,000 tokens 7748 -> 7526; eight
-// heads on 32 rows instead of twice four on 64: 921 -> 864; 56 batches of 3, 5, 6, 7 and 8 heads 1.24 times as fast (0.98 at
-// worst, where one more table is built for nothing).  At head dimension 64 four heads, too: four waves on 32 rows instead of eight
+// heads on 32 rows instead of twice four on 64: 921 -> 864; 56 batches of 3, 5, 6, 7 and 8 heads 1.24 times as fast.  Where all
+// siblings together are a multiple of 256 tokens the rows of four heads, of pairs and of one had no chunk partly empty and these
+// have: 16 x 4608 tokens, 24 / 8 heads 1860 -> 1918 us, 16 x 5120 of 48 / 8 heads 2743 -> 2849, with any other lengths 1.02 to
+// 1.2 times as fast (the lengths are not known to the host).  At head dimension 64 four heads, too: four waves on 32 rows instead of eight
 // on 64 leave room for two workgroups on a compute unit, 2 x 4500 tokens, 8 / 2 heads 90 -> 79 us (but see long_contexts).
 inline int pack_heads_of(int g, int head_dim) {
   if (g == 1 || g == 2 || (g == 4 && head_dim == 128)) return 0;
