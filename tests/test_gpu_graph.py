@@ -32,9 +32,10 @@ def _capture_and_replay(step, out, n_replays=3):
             assert torch.equal(out, eager)
 
 
-@pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1)])   # four-head items only; a left-over head on 256-row tiles (two launches)
-def test_prefill_prepare_and_attention_in_a_graph(hq, hkv):
-    dag_list = [dags.fork_join(300, [100, 90, 64], 70), dags.linear_chain([130, 77])]
+# single heads on 64 rows (small batches); items of all heads of a group, behind the look at their table; four heads on 64 rows
+@pytest.mark.parametrize("hq,hkv,copies", [(8, 2, 1), (5, 1, 1), (10, 2, 12), (8, 2, 12)])
+def test_prefill_prepare_and_attention_in_a_graph(hq, hkv, copies):
+    dag_list = [dags.fork_join(300, [100, 90, 64], 70), dags.linear_chain([130, 77])] * copies
     T = int(sum(int(np.sum(L)) for L, _ in dag_list))
     d = 128
     q, k, v = dags.make_qkv(17, T, hq, hkv, d, 0.5, torch.bfloat16)
